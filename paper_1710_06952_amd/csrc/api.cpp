@@ -591,14 +591,113 @@ int launch_updates(adpsgd_t* h, const EventCall& c, int32_t r) {
     return end_timing(h, e0, e1, h->ev_fused);
 }
 
-// The events of one call: plan, tables, then per round the gradients and one update launch.
-int run_events_impl(adpsgd_t* h, const adpsgd_schedule_t* s, float* loss, adpsgd_gradient_fn fn, void* user) {
-    if (!s || s->K < 0) return fail(h, ADPSGD_ERR_ARG, "run_events: schedule is NULL or K < 0");
-    if (s->K == 0) return ADPSGD_OK;
-    EventCall c;
-    int rc = prepare_call(h, s, c);
+// Synthetic gradients: how the column kernel (kernels_columns.hip) would execute the call.
+struct ColumnPlan {
+    std::vector<int32_t> rows;          // rows the call touches; the pairs use positions in this list
+    std::vector<ColumnPair> pairs;      // the call's operations in event order
+    std::vector<int64_t> place;         // position of every operation in the table
+    int32_t quads = 0;                  // float4 columns per wavefront, 0: the call goes through the rounds
+    int64_t batches = 0;
+};
+
+// The operations and the width of the strips.  A strip of q quads takes rows * 16 q bytes of LDS and leaves room for
+// 64 / q operations in a batch: narrow strips let more wavefronts share a compute unit, wide ones lose less to batches
+// that the dependences leave half empty.  The estimate below (cycles of a SIMD; measured at n = 128, d = 25.6 M: a
+// batch costs a wavefront about 1500 cycles from its operands to its results, and a SIMD with several of them one per
+// 560) is compared for every width whose strips leave at least eight wavefronts to a compute unit.  Below that the
+// rounds are the better route: 32 KB strips (n = 500, four quads) leave one wavefront per SIMD to hide that latency.
+void plan_columns(adpsgd_t* h, const EventCall& c, ColumnPlan& out) {
+    const adpsgd_schedule_t* s = c.s;
+    if (h->d > (1ll << 34)) return;                 // the quad has to fit one word of the generator's counter
+    std::vector<int32_t> local(h->n, -1);
+    auto row = [&](int32_t r) {
+        if (local[r] < 0) {
+            local[r] = static_cast<int32_t>(out.rows.size());
+            out.rows.push_back(r);
+        }
+        return local[r];
+    };
+    out.pairs.reserve(static_cast<size_t>(c.A + c.n_extra));
+    for (int64_t k = 0; k < c.A; ++k) {
+        const int32_t i = row(s->worker[k]), j = row(s->neighbour[k]);
+        out.pairs.push_back(ColumnPair{i, j, k});
+        if (s->extra_ptr)
+            for (int64_t q = s->extra_ptr[k]; q < s->extra_ptr[k + 1]; ++q) {
+                const int32_t a = row(s->extra_a[q]), b = row(s->extra_b[q]);
+                out.pairs.push_back(ColumnPair{a, b, -1});
+            }
+    }
+    const int64_t n_vec = (h->d + 3) / 4, n_rows = static_cast<int64_t>(out.rows.size());
+    constexpr double kIssue = 560.0, kLatency = 1500.0, kSimds = 1024.0, kLdsPerCu = 160.0 * 1024.0;
+    double best = 0.0;
+    std::vector<int64_t> place;
+    for (int32_t quads = 4; quads <= 64; quads *= 2) {
+        const double strip = static_cast<double>(n_rows) * quads * 16.0 * (h->o.V ? 2.0 : 1.0);
+        const double per_cu = std::min(16.0, std::floor(kLdsPerCu / strip));
+        if (per_cu < 8.0) break;
+        const int64_t batches = pack_columns(out.pairs, static_cast<int32_t>(n_rows), 64 / quads, place);
+        const double waves = static_cast<double>((n_vec + quads - 1) / quads) / kSimds;
+        const double cost = static_cast<double>(batches) * std::max(kLatency, waves * std::max(kIssue, kLatency / (per_cu / 4.0)));
+        if (out.quads == 0 || cost < best) {
+            best = cost;
+            out.quads = quads;
+            out.batches = batches;
+            out.place.swap(place);
+        }
+    }
+    if (out.batches > 0x7FFFFFF0) out.quads = 0;
+}
+
+// All events of the call in one launch of the column kernel.
+int run_columns(adpsgd_t* h, const EventCall& c, const ColumnPlan& plan) {
+    const int32_t capacity = 64 / plan.quads;
+    const size_t n_ops = static_cast<size_t>(plan.batches + 1) * capacity, off_rows = n_ops * sizeof(ColumnOp);
+    const size_t total = off_rows + plan.rows.size() * sizeof(int32_t);
+    TableSet& T = h->tables[h->next_table];
+    h->next_table ^= 1;
+    if (T.in_flight) {
+        HIP_TRY(h, hipEventSynchronize(T.done));
+        T.in_flight = false;
+    }
+    HIP_TRY(h, T.stage.reserve(total));
+    HIP_TRY(h, T.dev.reserve(total));
+    char* stage = static_cast<char*>(T.stage.p);
+    ColumnOp* ops = reinterpret_cast<ColumnOp*>(stage);
+    std::memset(stage, 0, off_rows);
+    for (size_t t = 0; t < plan.pairs.size(); ++t) {
+        const ColumnPair& pr = plan.pairs[t];
+        ColumnOp& op = ops[plan.place[t]];
+        op.rows = static_cast<uint32_t>(pr.i) | (static_cast<uint32_t>(pr.j) << 16);
+        op.flags = pr.event >= 0 ? kColumnEvent : kColumnAverage;
+        if (pr.event < 0) continue;
+        op.gamma = c.s->gamma ? c.s->gamma[pr.event] : h->o.gamma;
+        column_words(h->events_done + static_cast<uint64_t>(pr.event), h->o.synth_seed, op);
+    }
+    std::memcpy(stage + off_rows, plan.rows.data(), plan.rows.size() * sizeof(int32_t));
+    HIP_TRY(h, hipMemcpyAsync(T.dev.p, T.stage.p, total, hipMemcpyHostToDevice, h->stream));
+    const char* dev = static_cast<const char*>(T.dev.p);
+    hipEvent_t e0, e1;
+    int rc = begin_timing(h, e0, e1);
     if (rc != ADPSGD_OK) return rc;
-    rc = upload_tables(h, c);
+    ColumnArgs a{h->o.X, h->o.V, h->o.ldx, h->d, reinterpret_cast<const ColumnOp*>(dev), reinterpret_cast<const int32_t*>(dev + off_rows),
+                 static_cast<int32_t>(plan.rows.size()), static_cast<int32_t>(plan.batches), plan.quads, h->o.synth_seed, h->o.synth_std,
+                 h->o.momentum, h->o.weight_decay};
+    HIP_TRY(h, launch_column_events(a, h->stream));
+    rc = end_timing(h, e0, e1, h->ev_fused);
+    if (rc != ADPSGD_OK) return rc;
+    for (int32_t r = 0; r < c.plan.n_rounds; ++r) {     // the rounds are counted however they are executed
+        const int64_t nu = c.u_off[r + 1] - c.u_off[r];
+        h->stats.fused_launches += nu > 0;
+        h->stats.max_round_pairs = std::max<int64_t>(h->stats.max_round_pairs, nu);
+    }
+    HIP_TRY(h, hipEventRecord(T.done, h->stream));
+    T.in_flight = true;
+    return ADPSGD_OK;
+}
+
+// The rounds of the call: tables, then per round the gradients and one update launch.
+int run_rounds(adpsgd_t* h, EventCall& c, float* loss, adpsgd_gradient_fn fn, void* user) {
+    int rc = upload_tables(h, c);
     if (rc != ADPSGD_OK) return rc;
     std::vector<adpsgd_grad_request_t> requests;
     for (int32_t r = 0; r < c.plan.n_rounds; ++r) {
@@ -609,6 +708,20 @@ int run_events_impl(adpsgd_t* h, const adpsgd_schedule_t* s, float* loss, adpsgd
     }
     HIP_TRY(h, hipEventRecord(c.T->done, h->stream));
     c.T->in_flight = true;
+    return ADPSGD_OK;
+}
+
+// The events of one call: plan, then one launch for all of them where the model allows it, or round by round.
+int run_events_impl(adpsgd_t* h, const adpsgd_schedule_t* s, float* loss, adpsgd_gradient_fn fn, void* user) {
+    if (!s || s->K < 0) return fail(h, ADPSGD_ERR_ARG, "run_events: schedule is NULL or K < 0");
+    if (s->K == 0) return ADPSGD_OK;
+    EventCall c;
+    int rc = prepare_call(h, s, c);
+    if (rc != ADPSGD_OK) return rc;
+    ColumnPlan columns;
+    if (!c.with_grad) plan_columns(h, c, columns);
+    rc = columns.quads > 0 ? run_columns(h, c, columns) : run_rounds(h, c, loss, fn, user);
+    if (rc != ADPSGD_OK) return rc;
     h->events_done += static_cast<uint64_t>(c.A);
     h->stats.events += c.A;
     h->stats.rounds += c.plan.n_rounds;

@@ -7,6 +7,8 @@
 
 #include <cstdint>
 
+#include "internal.hpp"
+
 namespace adpsgd_impl {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -24,28 +26,31 @@ __device__ __forceinline__ void store4(float* p, v4f v) {
     else *reinterpret_cast<v4f*>(p) = v;
 }
 
-// Philox4x32, 10 rounds (Salmon et al., SC'11).  The key and the upper counter
-// words are uniform over a workgroup, so the key schedule lives in scalar registers.
-__device__ __forceinline__ v4u philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                             uint32_t k0, uint32_t k1) {
+// Philox4x32 (Salmon et al., SC'11), kRounds rounds starting with the key (k0, k1).  The key is uniform over a
+// workgroup, so the key schedule lives in scalar registers.
+template <int kRounds>
+__device__ __forceinline__ v4u philox4x32_rounds(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
+                                                 uint32_t k0, uint32_t k1) {
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        const uint64_t pa = static_cast<uint64_t>(0xD2511F53u) * c0;
-        const uint64_t pb = static_cast<uint64_t>(0xCD9E8D57u) * c2;
+    for (int r = 0; r < kRounds; ++r) {
+        const uint64_t pa = static_cast<uint64_t>(kPhiloxM0) * c0;
+        const uint64_t pb = static_cast<uint64_t>(kPhiloxM1) * c2;
         const uint32_t n0 = static_cast<uint32_t>(pb >> 32) ^ c1 ^ k0;
         const uint32_t n2 = static_cast<uint32_t>(pa >> 32) ^ c3 ^ k1;
         c1 = static_cast<uint32_t>(pb);
         c3 = static_cast<uint32_t>(pa);
         c0 = n0;
         c2 = n2;
-        k0 += 0x9E3779B9u;
-        k1 += 0xBB67AE85u;
+        k0 += kPhiloxW0;
+        k1 += kPhiloxW1;
     }
     v4u out = {c0, c1, c2, c3};
     return out;
 }
-
-constexpr uint32_t kStreamGrad = 2u << 24;
+__device__ __forceinline__ v4u philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
+                                             uint32_t k0, uint32_t k1) {
+    return philox4x32_rounds<10>(c0, c1, c2, c3, k0, k1);
+}
 
 // Box-Muller on two 32-bit words: u1 = ((wa >> 9) + 1/2) 2^-23 in (0,1) and
 // u2 = (wb >> 8) 2^-24 in [0,1) are exact in fp32; returns r cos(2 pi u2), r sin(2 pi u2).
@@ -61,17 +66,21 @@ __device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float& zc, 
     zs = r * s;
 }
 
-// Four standard normals for elements 4q .. 4q+3 of the synthetic gradient of event k.
-__device__ __forceinline__ v4f synth_normals4(uint32_t q_lo, uint32_t q_hi, uint32_t k_lo, uint32_t k_hi,
-                                              uint32_t key0, uint32_t key1) {
-    const v4u w = philox4x32_10(q_lo, q_hi, k_lo, (k_hi & 0x00FFFFFFu) | kStreamGrad, key0, key1);
+// The four normals of one generator output, times std.
+__device__ __forceinline__ v4f synth_normals_of(v4u w, float std) {
     v4f z;
     float a, b;
     box_muller(w.x, w.y, a, b);
     z.x = a; z.y = b;
     box_muller(w.z, w.w, a, b);
     z.z = a; z.w = b;
-    return z;
+    return z * std;
+}
+
+// Elements 4q .. 4q+3 of the synthetic gradient of event k: std times a standard normal each.
+__device__ __forceinline__ v4f synth_normals4(uint32_t q_lo, uint32_t q_hi, uint32_t k_lo, uint32_t k_hi,
+                                              uint32_t key0, uint32_t key1, float std) {
+    return synth_normals_of(philox4x32_10(q_lo, q_hi, k_lo, (k_hi & 0x00FFFFFFu) | kStreamGrad, key0, key1), std);
 }
 
 __device__ __forceinline__ uint16_t bf16_rne(float f) {
@@ -108,6 +117,14 @@ __device__ __forceinline__ void average_then_apply_momentum(float a, float b, fl
     const float step = gamma * v_new;
     new_j = avg;
     new_i = avg - step;
+}
+
+// all lanes of a wavefront have finished their LDS accesses before any of them goes on (LDS operations of one
+// wavefront execute in order; this only keeps the compiler from moving accesses across)
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __device__ __forceinline__ float wave_sum(float v) {

@@ -40,6 +40,21 @@ struct GradOp {
                             //   shadow (the compensated copy x - gamma_k' g_k'), or nullptr
 };
 
+// constants of the counter-based generator (Philox4x32): multipliers, key increments, stream of the gradients
+constexpr uint32_t kPhiloxM0 = 0xD2511F53u, kPhiloxM1 = 0xCD9E8D57u;
+constexpr uint32_t kPhiloxW0 = 0x9E3779B9u, kPhiloxW1 = 0xBB67AE85u;
+constexpr uint32_t kStreamGrad = 2u << 24;
+
+// One operation of the column kernel (kernels_columns.hip): an event of the synthetic model or an extra pair.
+constexpr uint32_t kColumnEvent = 1, kColumnAverage = 2;
+struct alignas(32) ColumnOp {
+    uint32_t rows;      // i | j << 16, local row numbers
+    uint32_t flags;     // 0: empty, kColumnEvent, kColumnAverage
+    float gamma;
+    uint32_t a, b, c, d;   // what the first two Philox rounds take from the event number (see column_words)
+    uint32_t pad;
+};
+
 struct WorkerData {
     const void* features = nullptr;
     const void* targets = nullptr;
@@ -93,6 +108,34 @@ struct FusedArgs {
     float weight_decay;
 };
 hipError_t launch_fused_gossip_apply(const FusedArgs& a, hipStream_t st);
+
+struct ColumnArgs {
+    float* X;
+    float* V;               // momentum buffers or nullptr
+    int64_t ld, d;
+    const ColumnOp* ops;    // device, [batches + 1][64 / quads]
+    const int32_t* rows;    // device, the rows of X that the operations name
+    int32_t n_rows, batches;
+    int32_t quads;          // float4 columns per wavefront: 4, 8, 16, 32 or 64
+    uint64_t synth_seed;
+    float synth_std;
+    float momentum, weight_decay;
+};
+hipError_t launch_column_events(const ColumnArgs& a, hipStream_t st);
+
+// Averaging and update operations of a call in the order of its events, for the column kernel.
+struct ColumnPair {
+    int32_t i, j;           // local row numbers
+    int64_t event;          // index of the event in the call, or -1: averaging only
+};
+// Packs the operations into batches of `capacity` with pairwise disjoint rows such that the operations of every row
+// keep their order from batch to batch: every operation goes into the first batch with room behind those of its rows.
+// place[t] = batch * capacity + position; returns the number of batches.
+int64_t pack_columns(const std::vector<ColumnPair>& pairs, int32_t n_rows, int32_t capacity, std::vector<int64_t>& place);
+// Words a..d of an event's ColumnOp: with the counter (quad, 0, k_lo, k_hi) the first Philox round gives
+//   (hi(M1 k_lo) ^ key0, lo(M1 k_lo), hi(M0 quad) ^ a, lo(M0 quad))
+// and the second   (hi(p) ^ b, lo(p), lo(M0 quad) ^ c, d)   with p = M1 (hi(M0 quad) ^ a).
+void column_words(uint64_t event, uint64_t seed, ColumnOp& op);
 
 struct LinearGradArgs {
     int model;              // LSQ or LOGREG

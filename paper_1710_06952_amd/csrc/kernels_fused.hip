@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kThreads) void fused_gossip_apply_kernel(const Fuse
         const int64_t eq = tile + (lane >> 4) * kThreads + 64 * wave + 4 * (lane & 15);
         const int64_t q = eq >> 2;
         const v4f z = synth_normals4(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), op.k_lo, op.k_hi,
-                                     p.key0, p.key1) * p.synth_std;
+                                     p.key0, p.key1, p.synth_std);
         *reinterpret_cast<v4f*>(&zs[wave * 256 + 4 * lane]) = z;
         __syncthreads();
 #pragma unroll
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kThreads) void synth_gradient_kernel(float* out, in
                                                                   uint32_t k_hi, uint32_t key0, uint32_t key1) {
     const int64_t v = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
     if (4 * v >= d) return;
-    const v4f g = synth_normals4(static_cast<uint32_t>(v), static_cast<uint32_t>(v >> 32), k_lo, k_hi, key0, key1) * std;
+    const v4f g = synth_normals4(static_cast<uint32_t>(v), static_cast<uint32_t>(v >> 32), k_lo, k_hi, key0, key1, std);
     const float gv[4] = {g.x, g.y, g.z, g.w};
     for (int t = 0; t < 4; ++t)
         if (4 * v + t < d) out[4 * v + t] = gv[t];

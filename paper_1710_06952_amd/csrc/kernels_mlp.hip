@@ -55,14 +55,6 @@ struct MlpParams {
     float* b2f;         // [op][kMaxOut]
 };
 
-// all lanes of a wavefront have finished their LDS accesses before any of them goes on (LDS operations of one
-// wavefront execute in order; this only keeps the compiler from moving accesses across)
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ v4f mfma_bf16(v8h a, v8h b, v4f c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a), __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
 }

@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kThreads) void sync_mix_apply_kernel(const SyncPara
                 const uint64_t k = p.event0 + static_cast<uint64_t>(i);
                 const uint64_t q = static_cast<uint64_t>(c) >> 2;
                 g[u] = synth_normals4(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), static_cast<uint32_t>(k),
-                                      static_cast<uint32_t>(k >> 32), p.key0, p.key1) * p.synth_std;
+                                      static_cast<uint32_t>(k >> 32), p.key0, p.key1, p.synth_std);
             } else {
                 g[u] = load4<STREAM>(p.slots + static_cast<int64_t>(i) * p.ld + c);
             }
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(kRingThreads) void sync_ring_apply_kernel(const Syn
                     const uint64_t k = p.event0 + static_cast<uint64_t>(i);
                     const uint64_t q = static_cast<uint64_t>(c) >> 2;
                     const v4f z = synth_normals4(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), static_cast<uint32_t>(k),
-                                                 static_cast<uint32_t>(k >> 32), p.key0, p.key1) * p.synth_std;
+                                                 static_cast<uint32_t>(k >> 32), p.key0, p.key1, p.synth_std);
                     g[u][0] = z.x; g[u][1] = z.y; g[u][2] = z.z; g[u][3] = z.w;
                 } else {
                     ring_load<STREAM>(p.slots + static_cast<int64_t>(i) * p.ld, c, g[u]);
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(kRingThreads) void sync_ring_rows_kernel(const Sync
         const uint64_t k = p.event0 + static_cast<uint64_t>(i);
         const uint64_t q = static_cast<uint64_t>(c) >> 2;
         const v4f z = synth_normals4(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), static_cast<uint32_t>(k),
-                                     static_cast<uint32_t>(k >> 32), p.key0, p.key1) * p.synth_std;
+                                     static_cast<uint32_t>(k >> 32), p.key0, p.key1, p.synth_std);
         g[0] = z.x; g[1] = z.y; g[2] = z.z; g[3] = z.w;
     } else {
         ring_load<STREAM>(p.slots + static_cast<int64_t>(i) * p.ld, c, g);
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kRingThreads) void sync_graph_rows_kernel(const Syn
         const uint64_t k = p.event0 + static_cast<uint64_t>(i);
         const uint64_t q = static_cast<uint64_t>(c) >> 2;
         const v4f z = synth_normals4(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), static_cast<uint32_t>(k),
-                                     static_cast<uint32_t>(k >> 32), p.key0, p.key1) * p.synth_std;
+                                     static_cast<uint32_t>(k >> 32), p.key0, p.key1, p.synth_std);
         g[0] = z.x; g[1] = z.y; g[2] = z.z; g[3] = z.w;
     } else {
         ring_load<STREAM>(p.slots + static_cast<int64_t>(i) * p.ld, c, g);

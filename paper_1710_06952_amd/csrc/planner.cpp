@@ -220,6 +220,40 @@ bool verify_plan(int32_t n, int64_t K, const int32_t* worker, const int32_t* nei
     return true;
 }
 
+int64_t pack_columns(const std::vector<ColumnPair>& pairs, int32_t n_rows, int32_t capacity, std::vector<int64_t>& place) {
+    place.resize(pairs.size());
+    std::vector<int64_t> after(n_rows, 0);       // first batch behind the operations of the row so far
+    std::vector<int32_t> fill;
+    std::vector<int64_t> open;                   // a batch at or behind this one that may have room (path-compressed)
+    for (size_t t = 0; t < pairs.size(); ++t) {
+        int64_t b = std::max(after[pairs[t].i], after[pairs[t].j]);
+        while (b < static_cast<int64_t>(open.size()) && open[b] != b) {
+            const int64_t nb = open[b];
+            if (nb < static_cast<int64_t>(open.size())) open[b] = open[nb];
+            b = nb;
+        }
+        while (b >= static_cast<int64_t>(fill.size())) {
+            open.push_back(static_cast<int64_t>(fill.size()));
+            fill.push_back(0);
+        }
+        place[t] = b * capacity + fill[b];
+        if (++fill[b] == capacity) open[b] = b + 1;
+        after[pairs[t].i] = after[pairs[t].j] = b + 1;
+    }
+    return static_cast<int64_t>(fill.size());
+}
+
+void column_words(uint64_t event, uint64_t seed, ColumnOp& op) {
+    const uint32_t k_lo = static_cast<uint32_t>(event), k_hi = (static_cast<uint32_t>(event >> 32) & 0x00FFFFFFu) | kStreamGrad;
+    const uint32_t key0 = static_cast<uint32_t>(seed), key1 = static_cast<uint32_t>(seed >> 32);
+    const uint64_t first = static_cast<uint64_t>(kPhiloxM1) * k_lo;
+    const uint64_t second = static_cast<uint64_t>(kPhiloxM0) * (static_cast<uint32_t>(first >> 32) ^ key0);
+    op.a = k_hi ^ key1;
+    op.b = static_cast<uint32_t>(first) ^ (key0 + kPhiloxW0);
+    op.c = static_cast<uint32_t>(second >> 32) ^ (key1 + kPhiloxW1);
+    op.d = static_cast<uint32_t>(second);
+}
+
 }  // namespace adpsgd_impl
 
 using namespace adpsgd_impl;
