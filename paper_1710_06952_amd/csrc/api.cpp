@@ -604,7 +604,7 @@ struct ColumnPlan {
 // 64 / q operations in a batch: narrow strips let more wavefronts share a compute unit, wide ones lose less to batches
 // that the dependences leave half empty.  The estimate below (cycles of a SIMD; measured at n = 128, d = 25.6 M: a
 // batch costs a wavefront about 1500 cycles from its operands to its results, and a SIMD with several of them one per
-// 560) is compared for every width whose strips leave at least eight wavefronts to a compute unit.  Below that the
+// 420) is compared for every width whose strips leave at least eight wavefronts to a compute unit.  Below that the
 // rounds are the better route: 32 KB strips (n = 500, four quads) leave one wavefront per SIMD to hide that latency.
 void plan_columns(adpsgd_t* h, const EventCall& c, ColumnPlan& out) {
     const adpsgd_schedule_t* s = c.s;
@@ -628,7 +628,7 @@ void plan_columns(adpsgd_t* h, const EventCall& c, ColumnPlan& out) {
             }
     }
     const int64_t n_vec = (h->d + 3) / 4, n_rows = static_cast<int64_t>(out.rows.size());
-    constexpr double kIssue = 560.0, kLatency = 1500.0, kSimds = 1024.0, kLdsPerCu = 160.0 * 1024.0;
+    constexpr double kIssue = 420.0, kLatency = 1500.0, kSimds = 1024.0, kLdsPerCu = 160.0 * 1024.0;
     double best = 0.0;
     std::vector<int64_t> place;
     for (int32_t quads = 4; quads <= 64; quads *= 2) {

@@ -52,29 +52,58 @@ __device__ __forceinline__ v4u philox4x32_10(uint32_t c0, uint32_t c1, uint32_t 
     return philox4x32_rounds<10>(c0, c1, c2, c3, k0, k1);
 }
 
-// Box-Muller on two 32-bit words: u1 = ((wa >> 9) + 1/2) 2^-23 in (0,1) and
-// u2 = (wb >> 8) 2^-24 in [0,1) are exact in fp32; returns r cos(2 pi u2), r sin(2 pi u2).
-__device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float& zc, float& zs) {
-    const float u1 = (static_cast<float>(wa >> 9) + 0.5f) * 0x1p-23f;
-    const float u2 = static_cast<float>(wb >> 8) * 0x1p-24f;
-    // accurate library functions: the hardware approximations (v_log / v_sin / v_cos) were measured
-    // and buy nothing, the kernel being bound by memory at the same time
-    const float r = sqrtf(-2.0f * logf(u1));
-    float s, c;
-    sincospif(2.0f * u2, &s, &c);
-    zc = r * c;
-    zs = r * s;
+// Box-Muller on two 32-bit words: u1 = ((wa >> 9) + 1/2) 2^-23 in (0,1) and u2 = (wb >> 8) 2^-24 in [0,1) are exact
+// in fp32; gives std r cos(2 pi u2), std r sin(2 pi u2) with r = sqrt(-2 ln u1).
+// The kernels that draw gradients in registers are bound by these instructions, so nothing is computed that the
+// ranges above rule out (no subnormals, infinities or large arguments):
+//   r       t = -2 ln 2 log2(u1) (v_log_f32), sqrt by one Newton step on v_rsq_f32 that also takes in the rounding
+//           error of t (the residual of its product);
+//   angle   quarter turns: n = round(4 u2) and f = 4 u2 - n in [-1/2, 1/2) are read off the bits of the word, then
+//           minimax polynomials in f^2 for sin(pi/2 f) / f and cos(pi/2 f) (relative error 3e-9 and 6e-11, the leading
+//           coefficient pi/2 in two parts), swapped and signed by n.
+// Against 64-bit arithmetic over 1.3e8 variates: rms error 5.5e-8 relative, 0.66 ulp, at most 3.7 ulp; logf, sqrtf and
+// sincospif with separate products have 5.7e-8, 0.70 and 3.9.  Time of one quad of variates per wavefront with the
+// generator below: 411 SIMD cycles (197 of them Philox) against 700.  Written out in single operations, so that every
+// kernel that draws a gradient gets the same bits.
+__device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float std, float& zc, float& zs) {
+#pragma clang fp contract(off)
+    const float u1 = __builtin_fmaf(static_cast<float>(wa >> 9), 0x1p-23f, 0x1p-24f);
+    const float l2 = __builtin_amdgcn_logf(u1);
+    constexpr float kM2Ln2 = -1.3862943611198906f;      // its rounding is 3e-9 relative
+    const float t = l2 * kM2Ln2;
+    const float y0 = __builtin_amdgcn_rsqf(t);
+    const float g = t * y0, h = 0.5f * y0;
+    const float rest = __builtin_fmaf(-g, g, t) + __builtin_fmaf(l2, kM2Ln2, -t);
+    const float r = __builtin_fmaf(rest, h, g) * std;
+
+    const float f = static_cast<float>(static_cast<int32_t>(__builtin_amdgcn_sbfe(static_cast<int32_t>(wb), 8, 22))) * 0x1p-22f;
+    const float y = f * f;
+    constexpr float kS0 = 1.5707963217077767f, kS0Rest = static_cast<float>(1.5707963217077767 - static_cast<double>(kS0));
+    float p = __builtin_fmaf(y, -0.004601657568828705f, 0.07968003262819402f);
+    p = __builtin_fmaf(p, y, -0.6459634602154649f);
+    p = __builtin_fmaf(p, y, kS0Rest);
+    const float s = __builtin_fmaf(f, kS0, f * p);
+    float q = __builtin_fmaf(y, 0.0009040605687702003f, -0.020860308502213997f);
+    q = __builtin_fmaf(q, y, 0.25366924722875356f);
+    q = __builtin_fmaf(q, y, -1.2337005435078803f);
+    const float c = __builtin_fmaf(q, y, 1.0f);
+
+    const uint32_t turn = wb + 0x20000000u;             // bits 31..30: n mod 4
+    const bool odd = (turn & 0x40000000u) != 0;
+    const float cv = odd ? s : c, sv = odd ? c : s;
+    zc = __uint_as_float(__float_as_uint(r * cv) ^ ((turn + 0x40000000u) & 0x80000000u));
+    zs = __uint_as_float(__float_as_uint(r * sv) ^ (turn & 0x80000000u));
 }
 
 // The four normals of one generator output, times std.
 __device__ __forceinline__ v4f synth_normals_of(v4u w, float std) {
     v4f z;
     float a, b;
-    box_muller(w.x, w.y, a, b);
+    box_muller(w.x, w.y, std, a, b);
     z.x = a; z.y = b;
-    box_muller(w.z, w.w, a, b);
+    box_muller(w.z, w.w, std, a, b);
     z.z = a; z.w = b;
-    return z * std;
+    return z;
 }
 
 // Elements 4q .. 4q+3 of the synthetic gradient of event k: std times a standard normal each.
