@@ -5,6 +5,7 @@
 #include <memory>
 
 #include "handle.hpp"
+#include "strips.hpp"
 
 namespace adpsgd_impl {
 
@@ -77,6 +78,12 @@ hipEvent_t take_event(adpsgd_t* h) {
     hipEvent_t e = nullptr;
     if (hipEventCreate(&e) != hipSuccess) return nullptr;
     return e;
+}
+
+int check_exchange(adpsgd_t* h) {
+    const volatile int* status = static_cast<const volatile int*>(h->exchange_status.p);
+    if (!status || *status == 0) return ADPSGD_OK;
+    return fail(h, ADPSGD_ERR_HIP, "run_events: the blocks of a launch lost each other, the models are undefined");
 }
 
 // Fold the timings of finished launches into the statistics (synchronises the stream).
@@ -187,6 +194,8 @@ extern "C" void adpsgd_destroy(adpsgd_t* h) {
     h->comp_rows.release();
     h->diag.release();
     h->sync_other.release();
+    h->exchange.release();
+    h->exchange_status.release();
     delete h;
 }
 
@@ -214,6 +223,10 @@ extern "C" int adpsgd_load_data(adpsgd_t* h, int32_t worker, const void* feature
 extern "C" int adpsgd_set_models(adpsgd_t* h, const float* x, int64_t ld_in, int32_t on_device) {
     if (!h || !x) return h ? fail(h, ADPSGD_ERR_ARG, "set_models: x is NULL") : ADPSGD_ERR_ARG;
     if (ld_in != 0 && ld_in < h->d) return fail(h, ADPSGD_ERR_ARG, "set_models: ld_in < d");
+    if (check_exchange(h) != ADPSGD_OK) {      // what an incomplete launch left is replaced
+        HIP_TRY(h, hipStreamSynchronize(h->stream));
+        *static_cast<int*>(h->exchange_status.p) = 0;
+    }
     h->pending.clear();      // gradients evaluated at the old models are dropped
     h->pending_batch.clear();
     const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
@@ -313,6 +326,8 @@ struct EventCall {
     bool ext_comp = false;      // caller's function, wait-free variant: compensated fp32 rows
     bool factored = false;      // perceptron: dW1 stays in factored form until the update kernel
     bool lin_factored = false;  // least squares on long models: the gradient stays M coefficients
+    int32_t compute_units = 0;
+    bool strips = false;        // linear models: all events in one launch (kernels_strips.hip)
     Plan plan;
     std::vector<int64_t> u_off, r_off;      // first update / gradient operation of every round
     int32_t group = 1;                      // gradients of a round are launched in groups of this many operations
@@ -326,8 +341,40 @@ struct EventCall {
     int32_t* batch_u = nullptr;             // ... and of uops (pinned staging)
     const int32_t* d_batch_r = nullptr;
     const int32_t* d_batch_u = nullptr;
+    std::vector<int32_t> carried_slot;      // per event: slot of a gradient evaluated by an earlier call, or -1; or empty
     size_t off_coef = 0;                    // linear models: offset of the coefficients in the gradient scratch
 };
+
+// Whether the calls of this handle take the one-launch path of the linear models (kernels_strips.hip).  Decided by the
+// handle alone, so that a schedule gives the same bits however it is cut into calls; only a stream under capture goes by
+// rounds (a captured call would need a cooperative launch in a graph).
+// Where the line lies: an iteration of the strip kernel holds the rows of a few gradients (teams / 2), and a round has
+// about n / 4 of them, so its time per round grows with n and with M, while the kernels of a round take more gradients
+// side by side.  Measured (least squares on a 4-regular graph, per 100 events, strips against rounds, us): n = 8, M = 12:
+// d = 300 142 / 318, 4096 157 / 878, 65 536 305 / 1160;  n = 16, M = 64: 292 / 306, 452 / 686, 708 / 1080;  n = 32,
+// M = 48: 215 / 200, 361 / 517, 574 / 745;  n = 64, M = 12: 82 / 72, 123 / 214, 199 / 300, M = 24: 136 / 81, 218 / 246,
+// 347 / 357, M = 48: 206 / 101, 350 / 266, 545 / 503.  So n M <= 1024, and half of it for many workers and short models.
+bool can_run_strips(const adpsgd_t* h, int32_t& compute_units) {
+    const int32_t model = h->o.model;
+    const int64_t width = static_cast<int64_t>(h->n) * h->o.M;
+    if ((model != ADPSGD_MODEL_LSQ && model != ADPSGD_MODEL_LOGREG) || h->d > kStripMaxD || h->o.M > kStripMaxM || width > 1024 ||
+        (h->n > 32 && h->d <= 1024 && width > 512))
+        return false;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (capture != hipStreamCaptureStatusNone) return false;
+    int dev = 0, cus = 0, cooperative = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess)
+        return false;
+    for (const WorkerData& w : h->data)
+        if (w.ld > 0xFFFFFFFFll) return false;          // the row pitch has to fit a word of a record
+    compute_units = std::min(cus, kStripGroups * kStripGroupBlocks);
+    return cooperative != 0 && strip_blocks(h->d) <= compute_units;
+}
 
 // Validation, choice of paths, plan of rounds, counting sort of the operations by round.
 int prepare_call(adpsgd_t* h, const adpsgd_schedule_t* s, EventCall& c) {
@@ -344,12 +391,15 @@ int prepare_call(adpsgd_t* h, const adpsgd_schedule_t* s, EventCall& c) {
     if (rc_valid != ADPSGD_OK) return rc_valid;
     c.A = c.K - s->lookahead;
     c.n_extra = s->extra_ptr ? s->extra_ptr[c.A] : 0;
-    std::vector<int32_t> carried_slot;
+    bool any_carried = false;
     if (!h->pending.empty()) {
-        carried_slot.assign(static_cast<size_t>(c.K), -1);
-        for (size_t k = 0; k < h->pending.size(); ++k) carried_slot[k] = h->pending[k].slot;
+        c.carried_slot.assign(static_cast<size_t>(c.K), -1);
+        for (size_t k = 0; k < h->pending.size(); ++k) {
+            c.carried_slot[k] = h->pending[k].slot;
+            any_carried |= h->pending[k].slot >= 0;
+        }
     }
-    const int32_t* carried = carried_slot.empty() ? nullptr : carried_slot.data();
+    const int32_t* carried = c.carried_slot.empty() ? nullptr : c.carried_slot.data();
 
     // the wait-free variant reads the pending gradient as a dense vector, so it keeps the dense form
     const bool comp = h->o.local_compensation != 0, dense = (h->o.flags & ADPSGD_FLAG_DENSE_GRADIENT) != 0;
@@ -357,6 +407,9 @@ int prepare_call(adpsgd_t* h, const adpsgd_schedule_t* s, EventCall& c) {
     c.ext_comp = c.external && comp;
     c.factored = h->o.model == ADPSGD_MODEL_MLP && !dense && !comp && mlp_can_factor(h->o.mlp_in, h->o.mlp_hidden, c.M);
     c.lin_factored = with_data && !dense && !comp && linear_can_factor(h->o.model, h->d, c.M, h->o.ldx);
+    // gradients pending from an earlier call come as it left them: dense vectors, or coefficients
+    c.strips = with_data && can_run_strips(h, c.compute_units) && (!any_carried || h->pending_dense);
+    if (any_carried && h->pending_dense) c.lin_factored = false;
 
     std::string perr;
     const int rc = plan_rounds(h->n, c.K, s->worker, s->neighbour, s->tau, h->n_slots, c.with_grad, c.plan, perr,
@@ -695,6 +748,124 @@ int run_columns(adpsgd_t* h, const EventCall& c, const ColumnPlan& plan) {
     return ADPSGD_OK;
 }
 
+// All events of the call in one launch of the strip kernel.  Sets `launched` when the launch was made; a launch that the
+// device refuses leaves everything as it was, for the rounds.
+int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
+    launched = false;
+    const int32_t M = c.M, n = h->n;
+    const bool mom = h->o.V != nullptr;
+    const size_t words = strip_exchange_bytes(h->o.model, M);
+    if (words > h->exchange.cap) {
+        HIP_TRY(h, h->exchange.reserve(words));
+        HIP_TRY(h, hipMemsetAsync(h->exchange.p, 0, h->exchange.cap, h->stream));      // no sequence number
+        h->exchange_seq = 0;
+    }
+    if (!h->exchange_status.p) {
+        HIP_TRY(h, h->exchange_status.reserve(sizeof(int)));
+        *static_cast<int*>(h->exchange_status.p) = 0;
+    }
+    if (h->exchange_seq > 0xF0000000u) {                                               // before the numbers wrap
+        HIP_TRY(h, hipMemsetAsync(h->exchange.p, 0, h->exchange.cap, h->stream));
+        h->exchange_seq = 0;
+    }
+    StripCall sc{c.K, c.A, c.s->worker, c.s->neighbour, c.s->gamma, h->o.gamma, c.s->extra_ptr, c.s->extra_a, c.s->extra_b,
+                 &c.plan, c.carried_slot.empty() ? nullptr : c.carried_slot.data(), h->data.data(), true,
+                 h->exchange_seq + 1};
+    const int32_t teams = strip_teams(M);
+    StripProgram prog;
+    build_strips(sc, teams, prog);
+    const bool lds_state = strip_lds_bytes(M, n, mom, prog.n_slots, true) <= static_cast<size_t>(kStripLdsBytes);
+    if (!lds_state) {
+        sc.renumber = false;
+        build_strips(sc, teams, prog);
+    }
+    // slots that cross the ends of the call: (slot of the call, slot of the workspace)
+    std::vector<int32_t> carry;
+    int32_t n_in = 0, n_out = 0;
+    if (lds_state) {
+        for (int64_t k = 0; k < c.K; ++k)
+            if (!c.carried_slot.empty() && c.carried_slot[k] >= 0) carry.insert(carry.end(), {prog.slot[k], c.carried_slot[k]}), ++n_in;
+        for (int64_t k = c.A; k < c.K; ++k)
+            if (prog.slot[k] >= 0) carry.insert(carry.end(), {prog.slot[k], c.plan.slot[k]}), ++n_out;
+    }
+    const size_t bytes_recs = prog.recs.size() * sizeof(StripEntry), off_idx = bytes_recs;
+    const size_t off_carry = off_idx + prog.order.size() * M * sizeof(int32_t);
+    const size_t off_count = (off_carry + carry.size() * sizeof(int32_t) + 63) & ~size_t(63);
+    const size_t total = off_count + kStripCounters * sizeof(uint32_t);
+    TableSet& T = h->tables[h->next_table];
+    h->next_table ^= 1;
+    if (T.in_flight) {
+        HIP_TRY(h, hipEventSynchronize(T.done));
+        T.in_flight = false;
+    }
+    HIP_TRY(h, T.stage.reserve(total));
+    HIP_TRY(h, T.dev.reserve(total));
+    char* stage = static_cast<char*>(T.stage.p);
+    std::memset(stage + off_count, 0, kStripCounters * sizeof(uint32_t));
+    std::memcpy(stage, prog.recs.data(), bytes_recs);
+    int32_t* idx = reinterpret_cast<int32_t*>(stage + off_idx);
+    for (size_t q = 0; q < prog.order.size(); ++q)
+        std::memcpy(idx + q * M, c.s->batch_idx + prog.order[q] * static_cast<int64_t>(M), static_cast<size_t>(M) * sizeof(int32_t));
+    if (!carry.empty()) std::memcpy(stage + off_carry, carry.data(), carry.size() * sizeof(int32_t));
+    HIP_TRY(h, hipMemcpyAsync(T.dev.p, T.stage.p, total, hipMemcpyHostToDevice, h->stream));
+    const char* dev = static_cast<const char*>(T.dev.p);
+    StripArgs a{};
+    a.X = h->o.X;
+    a.V = h->o.V;
+    a.ld = h->o.ldx;
+    a.d = h->d;
+    a.n = n;
+    a.model = h->o.model;
+    a.M = M;
+    a.teams = teams;
+    a.recs = reinterpret_cast<const StripEntry*>(dev);
+    a.rec_len = prog.rec_len;
+    a.iterations = static_cast<int32_t>(prog.iterations);
+    a.idx = reinterpret_cast<const int32_t*>(dev + off_idx);
+    a.carry = reinterpret_cast<const int32_t*>(dev + off_carry);
+    a.n_in = n_in;
+    a.n_out = n_out;
+    a.slots = static_cast<float*>(h->o.workspace);
+    a.n_lds_slots = prog.n_slots;
+    a.lds_state = lds_state;
+    a.words = static_cast<unsigned long long*>(h->exchange.p);
+    a.counters = reinterpret_cast<unsigned int*>(static_cast<char*>(T.dev.p) + off_count);
+    // few strips: one block per compute unit, of which those on one XCD stay; more: as many on every XCD (see the kernel)
+    a.grid = strip_blocks(h->d) <= kStripGroupBlocks ? c.compute_units
+                                                     : std::min(c.compute_units, kStripGroups * strip_group_size(h->d));
+    a.gscale = h->o.grad_sum ? 1.0f : 1.0f / static_cast<float>(std::max(M, 1));
+    a.lambda = h->o.lambda;
+    a.momentum = h->o.momentum;
+    a.weight_decay = h->o.weight_decay;
+    a.loss = loss;
+    a.status = static_cast<int*>(h->exchange_status.p);
+    hipEvent_t e0, e1;
+    int rc = begin_timing(h, e0, e1);
+    if (rc != ADPSGD_OK) return rc;
+    const hipError_t e = launch_strips(a, h->stream);
+    if (e != hipSuccess) {                     // nothing has run; the tables may still be on their way
+        (void)hipGetLastError();
+        HIP_TRY(h, hipEventRecord(T.done, h->stream));
+        T.in_flight = true;
+        return ADPSGD_OK;
+    }
+    launched = true;
+    h->exchange_seq += static_cast<uint32_t>(prog.order.size());
+    rc = end_timing(h, e0, e1, h->ev_fused);
+    if (rc != ADPSGD_OK) return rc;
+    // the rounds are counted however they are executed
+    const int64_t per_group = h->d <= 2048 && M <= 256 ? 1 : c.lin_factored ? 2 : 3;
+    for (int32_t r = 0; r < c.plan.n_rounds; ++r) {
+        const int64_t nu = c.u_off[r + 1] - c.u_off[r];
+        h->stats.fused_launches += nu > 0;
+        h->stats.max_round_pairs = std::max<int64_t>(h->stats.max_round_pairs, nu);
+        h->stats.grad_launches += per_group * ((c.r_off[r + 1] - c.r_off[r] + c.group - 1) / c.group);
+    }
+    HIP_TRY(h, hipEventRecord(T.done, h->stream));
+    T.in_flight = true;
+    return ADPSGD_OK;
+}
+
 // The rounds of the call: tables, then per round the gradients and one update launch.
 int run_rounds(adpsgd_t* h, EventCall& c, float* loss, adpsgd_gradient_fn fn, void* user) {
     int rc = upload_tables(h, c);
@@ -716,12 +887,17 @@ int run_events_impl(adpsgd_t* h, const adpsgd_schedule_t* s, float* loss, adpsgd
     if (!s || s->K < 0) return fail(h, ADPSGD_ERR_ARG, "run_events: schedule is NULL or K < 0");
     if (s->K == 0) return ADPSGD_OK;
     EventCall c;
-    int rc = prepare_call(h, s, c);
+    int rc = check_exchange(h);
+    if (rc != ADPSGD_OK) return rc;
+    rc = prepare_call(h, s, c);
     if (rc != ADPSGD_OK) return rc;
     ColumnPlan columns;
     if (!c.with_grad) plan_columns(h, c, columns);
-    rc = columns.quads > 0 ? run_columns(h, c, columns) : run_rounds(h, c, loss, fn, user);
+    if (c.strips) rc = run_strips(h, c, loss, c.strips);
     if (rc != ADPSGD_OK) return rc;
+    if (!c.strips) rc = columns.quads > 0 ? run_columns(h, c, columns) : run_rounds(h, c, loss, fn, user);
+    if (rc != ADPSGD_OK) return rc;
+    h->pending_dense = c.strips || !c.lin_factored;
     h->events_done += static_cast<uint64_t>(c.A);
     h->stats.events += c.A;
     h->stats.rounds += c.plan.n_rounds;

@@ -14,7 +14,7 @@ extern "C" int adpsgd_get_models(adpsgd_t* h, float* out, int64_t ld_out, int32_
                                 static_cast<size_t>(h->d) * 4, h->n,
                                 on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
-    return ADPSGD_OK;
+    return check_exchange(h);
 }
 
 extern "C" int adpsgd_get_momentum(adpsgd_t* h, float* out, int64_t ld_out, int32_t on_device) {
@@ -25,7 +25,7 @@ extern "C" int adpsgd_get_momentum(adpsgd_t* h, float* out, int64_t ld_out, int3
                                 static_cast<size_t>(h->d) * 4, h->n,
                                 on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
-    return ADPSGD_OK;
+    return check_exchange(h);
 }
 
 extern "C" int adpsgd_get_bf16_models(adpsgd_t* h, uint16_t* out, int64_t ld_out, int32_t on_device) {

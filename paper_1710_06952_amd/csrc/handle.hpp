@@ -73,6 +73,10 @@ struct adpsgd {
     adpsgd_impl::DevBuf diag;             // consensus partials, result, mean / broadcast staging
     adpsgd_impl::DevBuf sync_other;       // synchronous schedule: the second model matrix of the out-of-place iterations
     bool sync_other_refused = false;      // ... its allocation failed once: the iterations run in place from then on
+    bool pending_dense = true;            // pending gradients evaluated by the last call are dense vectors (else coefficients)
+    adpsgd_impl::DevBuf exchange;         // linear models in one launch: words the blocks exchange ...
+    uint32_t exchange_seq = 0;            // ... the sequence number of the last gradient
+    adpsgd_impl::HostBuf exchange_status; // ... and a word the kernel sets when a wait had to be given up
     adpsgd_stats_t stats{};
     std::vector<hipEvent_t> ev_pool;                       // profiling events
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_fused, ev_grad;
@@ -95,6 +99,8 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 bool is_neighbour(const adpsgd_t* h, int32_t i, int32_t j);
 void metropolis(const std::vector<int32_t>& rowptr, const std::vector<int32_t>& col, float* w_self, float* w_edge);
 hipEvent_t take_event(adpsgd_t* h);
+// An earlier launch that could not complete its exchange left the models undefined: report it.
+int check_exchange(adpsgd_t* h);
 // Fold the timings of finished launches into the statistics (synchronises the stream).
 int drain_profile(adpsgd_t* h);
 

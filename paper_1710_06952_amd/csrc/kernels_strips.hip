@@ -1,0 +1,491 @@
+// All events of a call of a linear model in one persistent launch.
+//
+// The rounds of short and medium models are chains of small kernels: launches, round trips to memory and the gather of
+// minibatch rows that miss every cache bind them, not bytes (n = 16, d = 4096, M = 8: 22 us per round of four events,
+// of which 14 us in the kernel of the dot products).  Here block c owns the columns [256 c, 256 c + 256) of all models
+// for the whole call.  Averaging and updates couple rows, never columns, so the only thing the blocks exchange are the
+// M dot products a_m . x^ of every gradient; models, momentum buffers and pending gradients of a strip stay in LDS,
+// minibatch rows are read once, into registers, ahead of the events that need them (the schedule names them), and are
+// still there when the coefficients arrive.
+// Measured, a call against the same call in rounds: n = 8, d = 1024, M = 32, 200 events 0.36 against 0.79 ms;  n = 16,
+// d = 4096, M = 8, 1280 events 1.33 against 7.2 ms;  n = 16, d = 20 001, M = 50, wait-free with momentum, 400 events 2.05
+// against 4.28 ms.  What binds now is the chain of an iteration, 3.5 us for the second of these: exchange 1.0, the
+// helpers' sums and coefficients 0.9, updates and x^ 0.7, dot products 0.2, combination 0.2, barriers and records the rest.
+//
+// A block has 12 main wavefronts in `teams` teams, each team with the rows of one gradient in its registers, and 4
+// helper wavefronts (one thread per column, and one per minibatch sample).  An iteration has three phases:
+//   A  helpers: finish the gradients of the last iteration, apply updates, write x^ of the next gradients to LDS
+//   B  main: dot products of a team's rows with x^, published;  helpers: wait for the sums, make the coefficients
+//   C  main: sum_m c_m a_m of the team's rows to LDS, request the rows of the next gradient
+// The waits of phase B are in the helpers, so that they do not queue behind the rows in flight (loads of a wavefront
+// return in order).
+//
+// The sums go through the words of exchange.hpp: up to 32 strips exchange them directly; more sum within their XCD first
+// (the blocks of a group share out the samples), and only these sums cross the chip, at most 8 per sample.
+#include "device_common.hpp"
+#include "exchange.hpp"
+#include "strips.hpp"
+
+namespace adpsgd_impl {
+namespace {
+
+constexpr int kMainThreads = 64 * kStripMainWaves;
+constexpr int kStripThreads = kMainThreads + kStripHelpers;
+constexpr int kWordsInFlight = 4;      // per lane of a helper
+
+struct StripParams {
+    StripArgs a;
+    int32_t samples;             // words per block and gradient: M, and |x^|^2 of the logistic loss
+    int32_t blocks, group_size;  // strips, and how many form a group
+    unsigned long long* sums;    // the groups' sums, [ring][samples][kStripGroups]
+};
+
+__device__ __forceinline__ float dot4(v4f a, v4f b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
+
+// LDS offsets fit 32 bits, places in global memory need 64
+template <bool kLds> struct Pitch { typedef uint32_t type; };
+template <> struct Pitch<false> { typedef int64_t type; };
+
+// kTeams teams of 12 / kTeams wavefronts, kRows rows per wavefront; kLds: the strip's models, momentum buffers and
+// slots in LDS, otherwise in their global places (every entry is touched by one thread only, its column's).
+template <int kTeams, int kRows, bool kLds, bool kMom>
+__global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const StripParams p) {
+    constexpr int kTeamWaves = kStripMainWaves / kTeams;
+    constexpr int kTeamHelpers = kTeams == 12 ? 16 : kTeams == 6 ? 32 : kTeams == 4 ? 64 : 128;      // threads, one per sample
+    constexpr int kHalf = kTeams / 2;                  // evaluations and loads of a record, at most
+    // teams of one wavefront have the whole gradient and put it into its slot themselves
+    constexpr bool kDirect = kLds && kTeamWaves == 1;
+    constexpr int kChunk = kRows > 16 ? 4 : kRows < 8 ? kRows : 8;      // rows whose sums or addresses are in registers at a time
+    const StripArgs& a = p.a;
+    extern __shared__ __attribute__((aligned(16))) float state_s[];      // [rows of X][rows of V][slots] x 256
+    __shared__ __attribute__((aligned(16))) v4f red_s[kStripMainWaves][64];      // partial gradients
+    __shared__ __attribute__((aligned(16))) float xh_s[kTeams][kStripCols];
+    __shared__ v4u rec_s[4][kStripMaxRec];
+    __shared__ const float* rowp_s[2][kStripHelpers];                    // [iteration][team][sample]: the sample's row ...
+    __shared__ const float* targetp_s[2][kStripHelpers];                 // ... where its target is ...
+    __shared__ float target_s[kStripHelpers];                            // ... and its target
+    __shared__ float coef_s[kStripHelpers];
+    __shared__ float loss_s[kStripHelpers];
+    __shared__ Assembly assembly_s;
+    __shared__ int given_up_s;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int M = a.M, S = p.samples;
+    if (tid == 0) {
+        bool lost;
+        assembly_s = assemble(a.counters, p.blocks, p.group_size, lost);
+        given_up_s = lost;
+    }
+    __syncthreads();
+    const Assembly as = assembly_s;
+    const int block = __builtin_amdgcn_readfirstlane(as.strip);
+    if (block < 0) return;
+    const int64_t col0 = static_cast<int64_t>(block) * kStripCols;
+    const int group = __builtin_amdgcn_readfirstlane(as.group), rank = __builtin_amdgcn_readfirstlane(as.rank);
+    const int group_blocks = __builtin_amdgcn_readfirstlane(as.group_blocks), groups = __builtin_amdgcn_readfirstlane(as.groups);
+
+    const int slots_at = a.n * (kMom ? 2 : 1) * kStripCols;
+    const float regularise = a.lambda * a.gscale * static_cast<float>(M);
+    if (wave < kStripMainWaves) {
+        // ---- main wavefronts ------------------------------------------------------------------------------------
+        const int team = wave / kTeamWaves, first = wave % kTeamWaves;       // rows first, first + kTeamWaves, ...
+        const int64_t at = col0 + 4 * lane;
+        const bool ragged = col0 + kStripCols > a.d;
+        const int from = at < a.d ? 4 * lane : 0;       // lanes beyond d read (and drop) the strip's first columns
+        const int mine = first + kTeamWaves * lane;     // the sample whose target this lane brings
+        float target = 0.0f;
+        v4f row[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) row[r] = v4f{0, 0, 0, 0};
+        __syncthreads();       // the first records
+        for (int it = 0; it < a.iterations; ++it) {
+            __syncthreads();   // phase A done
+            const v4u* rec = rec_s[it & 3];
+            const uint32_t evaluate = __builtin_amdgcn_readfirstlane(rec[0].z), load = __builtin_amdgcn_readfirstlane(rec[0].y);
+            const bool evaluates = (evaluate >> team & 1) != 0;
+            const v4u* eval = rec + 1 + 2 * __popc(evaluate & ((1u << team) - 1));
+            if (evaluates) {
+                const uint32_t seq = __builtin_amdgcn_readfirstlane(eval[0].y);
+                const uint32_t words = ((seq % kStripRing) * groups + group) * S * kStripGroupBlocks + rank;
+                const v4f x = *reinterpret_cast<const v4f*>(&xh_s[team][4 * lane]);
+                if (ragged && at + 4 > a.d) {       // what lies beyond d in a padded row is arbitrary
+#pragma unroll
+                    for (int r = 0; r < kRows; ++r) {
+                        if (at >= a.d) row[r].x = 0.0f;
+                        if (at + 1 >= a.d) row[r].y = 0.0f;
+                        if (at + 2 >= a.d) row[r].z = 0.0f;
+                        if (at + 3 >= a.d) row[r].w = 0.0f;
+                    }
+                }
+                // the target of a sample is in LDS before any block can have the sample's sum
+                if (mine < M && lane < kRows) target_s[team * kTeamHelpers + mine] = target;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+#pragma unroll
+                for (int r0 = 0; r0 < kRows; r0 += kChunk) {
+                    float v[kChunk];
+#pragma unroll
+                    for (int r = 0; r < kChunk; ++r) v[r] = r0 + r < kRows ? dot4(row[r0 + r < kRows ? r0 + r : 0], x) : 0.0f;
+                    const float z = wave_sums(v, lane);
+                    const int r = r0 + lane / (64 / kChunk), m = first + kTeamWaves * r;
+                    if (lane % (64 / kChunk) == 0 && r < kRows && m < M) put_word(a.words, words + m * kStripGroupBlocks, z, seq);
+                }
+                if (S > M && first == kTeamWaves - 1) {
+                    const float z = all_sum(dot4(x, x));
+                    if (lane == 0) put_word(a.words, words + M * kStripGroupBlocks, z, seq);
+                }
+            }
+            if ((load >> team & 1) != 0) {      // another team's exchange hides the time this takes
+                // no branch around a load: the wavefront would wait for one row before it requests the next
+#pragma unroll
+                for (int r0 = 0; r0 < kRows; r0 += kChunk) {
+                    const float* src[kChunk];
+#pragma unroll
+                    for (int r = 0; r < kChunk; ++r) src[r] = rowp_s[it & 1][team * kTeamHelpers + min(first + kTeamWaves * (r0 + r), M - 1)];
+#pragma unroll
+                    for (int r = 0; r < kChunk; ++r)
+                        if (r0 + r < kRows) row[r0 + r < kRows ? r0 + r : 0] = *reinterpret_cast<const v4f*>(src[r] + from);
+                }
+                target = *targetp_s[it & 1][team * kTeamHelpers + min(mine, M - 1)];
+            }
+            __syncthreads();   // the coefficients are there
+            if (evaluates) {
+                v4f acc = {0, 0, 0, 0};
+#pragma unroll
+                for (int r0 = 0; r0 < kRows; r0 += kChunk) {
+                    float coef[kChunk];
+#pragma unroll
+                    for (int r = 0; r < kChunk; ++r) coef[r] = coef_s[team * kTeamHelpers + min(first + kTeamWaves * (r0 + r), kTeamHelpers - 1)];
+#pragma unroll
+                    for (int r = 0; r < kChunk; ++r)
+                        if (r0 + r < kRows && first + kTeamWaves * (r0 + r) < M) acc += row[r0 + r < kRows ? r0 + r : 0] * coef[r];
+                }
+                if (kDirect) {
+                    if (a.model == ADPSGD_MODEL_LOGREG) acc += *reinterpret_cast<const v4f*>(&xh_s[team][4 * lane]) * regularise;
+                    *reinterpret_cast<v4f*>(state_s + slots_at + static_cast<int>(__builtin_amdgcn_readfirstlane(eval[0].w)) * kStripCols + 4 * lane) = acc;
+                } else {
+                    red_s[wave][lane] = acc;
+                }
+            }
+            __syncthreads();   // phase C done
+        }
+        return;
+    }
+
+    // ---- helper wavefronts: column t, and sample t % kTeamHelpers of team t / kTeamHelpers ---------------------------
+    const int t = tid - kMainThreads, hw = t >> 6;
+    const int team = min(t / kTeamHelpers, kTeams - 1), m = t / kTeamHelpers < kTeams ? t % kTeamHelpers : kStripHelpers;
+    const int64_t col = col0 + t;
+    const bool inside = col < a.d;
+    float* const xs = kLds ? state_s + t : a.X + col;
+    float* const vs = kLds ? xs + static_cast<int64_t>(a.n) * kStripCols : a.V + col;
+    float* const gs = kLds ? state_s + t + slots_at : a.slots + col;
+    const typename Pitch<kLds>::type ld = kLds ? kStripCols : static_cast<typename Pitch<kLds>::type>(a.ld);
+    if (kLds) {
+        for (int r = 0; r < a.n; ++r) {
+            xs[r * ld] = inside ? a.X[r * a.ld + col] : 0.0f;
+            if (kMom) vs[r * ld] = inside ? a.V[r * a.ld + col] : 0.0f;
+        }
+        for (int i = 0; i < a.n_in; ++i)
+            gs[a.carry[2 * i] * ld] = inside ? a.slots[a.carry[2 * i + 1] * a.ld + col] : 0.0f;
+    }
+    const v4u* recs = reinterpret_cast<const v4u*>(a.recs) + lane;
+    const bool copies = hw == 3 && lane < a.rec_len;
+    v4u ahead = {0, 0, 0, 0};             // wavefront 3: the record after the next one
+    int32_t index = 0;                    // row of this thread's sample in the worker's data
+    const uint32_t teams_below = (1u << team) - 1;
+    auto load_entry = [&](const v4u* rec, uint32_t load) { return rec + 1 + 2 * kHalf + 2 * __popc(load & teams_below); };
+    auto fetch_index = [&](const v4u* rec) {
+        const uint32_t load = rec[0].y;
+        if ((load >> team & 1) != 0 && m < M) index = a.idx[static_cast<int64_t>(load_entry(rec, load)[0].x) * M + m];
+    };
+    auto put_addresses = [&](const v4u* rec, int parity) {
+        const uint32_t load = rec[0].y;
+        if ((load >> team & 1) != 0 && m < M) {
+            const v4u* e = load_entry(rec, load);
+            const v4u f = e[0], g = e[1];
+            rowp_s[parity][t] = reinterpret_cast<const float*>(static_cast<uint64_t>(f.w) << 32 | f.z) + static_cast<int64_t>(index) * f.y + col0;
+            targetp_s[parity][t] = reinterpret_cast<const float*>(static_cast<uint64_t>(g.y) << 32 | g.x) + index;
+        }
+    };
+    // What phase A and the waits of phase B take from a record, and the rows of the first updates: read while the
+    // exchange before is under way.
+    constexpr int kUps = 4, kEvals = kHalf < 3 ? kHalf : 3;
+    uint32_t evaluate = 0;
+    int n_updates = 0, n_evals = 0;
+    v4u up[kUps], ev[kEvals], ev2[kEvals];
+    float xi[kUps], xj[kUps], vi[kUps];
+    auto read_rows = [&] {
+#pragma unroll
+        for (int u = 0; u < kUps; ++u) {
+            xi[u] = kLds || inside ? xs[(up[u].x & 0xFFFFu) * ld] : 0.0f;
+            xj[u] = kLds || inside ? xs[(up[u].x >> 16) * ld] : 0.0f;
+            vi[u] = kMom && (kLds || inside) ? vs[(up[u].x & 0xFFFFu) * ld] : 0.0f;
+        }
+    };
+    auto read_updates = [&](const v4u* rec, int from, int count) {
+#pragma unroll
+        for (int u = 0; u < kUps; ++u) up[u] = rec[1 + 4 * kHalf + min(from + u, max(count, 1) - 1)];      // none: row 0, unused
+        read_rows();
+    };
+    const int log_width = sum_width(groups > 1 ? groups : group_blocks), sub = t & ((1 << log_width) - 1);
+    const int words = groups > 1 ? groups : group_blocks;               // of a sum
+    const uint32_t pitch = groups > 1 ? kStripGroups : kStripGroupBlocks;
+    const int pair0 = t >> log_width, pair_step = kStripHelpers >> log_width;
+    uint32_t at[kWordsInFlight], seq[kWordsInFlight], place[kWordsInFlight];
+    auto read_pairs = [&](const v4u* rec, int from, int count) {        // (gradient, sample) pairs, samples padded to a power of two
+#pragma unroll
+        for (int u = 0; u < kWordsInFlight; ++u) {
+            const int pair = from + u * pair_step + pair0, i = pair / kTeamHelpers, q = pair % kTeamHelpers;
+            const bool live = i < count && q < M;
+            const v4u e = rec[1 + 2 * min(i, kHalf - 1)];
+            place[u] = live ? e.x * kTeamHelpers + q : kStripHelpers;
+            seq[u] = live && sub < words ? e.y : 0;
+            at[u] = live ? ((e.y % kStripRing) * S + q) * pitch + min(sub, words - 1) : 0;
+        }
+    };
+    if (copies) {
+        rec_s[0][lane] = recs[0];
+        rec_s[1][lane] = recs[a.rec_len];
+        ahead = recs[2 * a.rec_len];
+    }
+    bool given_up = given_up_s != 0;
+    __syncthreads();
+    fetch_index(rec_s[0]);
+    put_addresses(rec_s[0], 0);
+    fetch_index(rec_s[1]);
+    n_updates = __builtin_amdgcn_readfirstlane(rec_s[0][0].x);
+    evaluate = __builtin_amdgcn_readfirstlane(rec_s[0][0].z);           // record 0 evaluates nothing
+    read_updates(rec_s[0], 0, n_updates);
+#pragma unroll
+    for (int i = 0; i < kEvals; ++i) {
+        ev[i] = rec_s[0][1 + 2 * i];
+        ev2[i] = rec_s[0][2 + 2 * i];
+    }
+
+    for (int it = 0; it < a.iterations; ++it) {
+        const v4u* rec = rec_s[it & 3];
+        // ---- A1: the gradients of the last iteration
+        if (!kDirect && it > 0) {
+            const v4u* last = rec_s[(it - 1) & 3];
+            const int n_last = __popc(__builtin_amdgcn_readfirstlane(last[0].z));
+            for (int i0 = 0; i0 < n_last; i0 += kEvals) {
+                v4u e[kEvals];
+                float g[kEvals];
+#pragma unroll
+                for (int i = 0; i < kEvals; ++i) e[i] = last[1 + 2 * min(i0 + i, n_last - 1)];
+#pragma unroll
+                for (int i = 0; i < kEvals; ++i) {
+                    const float* part = reinterpret_cast<const float*>(&red_s[e[i].x * kTeamWaves][0]) + t;
+                    g[i] = part[0];
+#pragma unroll
+                    for (int w = 1; w < kTeamWaves; ++w) g[i] += part[w * kStripCols];
+                    if (a.model == ADPSGD_MODEL_LOGREG) g[i] += xh_s[e[i].x][t] * regularise;
+                }
+#pragma unroll
+                for (int i = 0; i < kEvals; ++i)
+                    if (i0 + i < n_last && (kLds || inside)) gs[e[i].w * ld] = g[i];
+            }
+        }
+        // ---- A2: updates; their rows are pairwise different
+        for (int u0 = 0; u0 < n_updates; u0 += kUps) {
+            if (u0 > 0) read_updates(rec, u0, n_updates);
+            if (kLds || inside) {
+                float g[kUps];
+#pragma unroll
+                for (int u = 0; u < kUps; ++u) g[u] = gs[up[u].y * ld];          // slot 0 where the pair is only averaged
+#pragma unroll
+                for (int u = 0; u < kUps; ++u) {
+                    if (u0 + u < n_updates) {
+                        const float gamma = __uint_as_float(up[u].z);
+                        const bool average_only = (up[u].w & 1) != 0;
+                        float ni, nj;
+                        if (kMom) {
+                            float vn;
+                            average_then_apply_momentum(xi[u], xj[u], g[u], vi[u], gamma, a.momentum, a.weight_decay, ni, nj, vn);
+                            vs[(up[u].x & 0xFFFFu) * ld] = average_only ? vi[u] : vn;
+                        } else {
+                            average_then_apply(xi[u], xj[u], g[u], gamma, ni, nj);
+                        }
+                        xs[(up[u].x >> 16) * ld] = nj;       // before x^i: without a partner (i == j) the step stands
+                        xs[(up[u].x & 0xFFFFu) * ld] = average_only ? nj : ni;
+                    }
+                }
+            }
+        }
+        // ---- A3: points of evaluation
+        n_evals = __popc(evaluate);
+        for (int i0 = 0; i0 < n_evals; i0 += kEvals) {
+            float x[kEvals];
+            if (i0 > 0) {
+#pragma unroll
+                for (int i = 0; i < kEvals; ++i) {
+                    ev[i] = rec[1 + 2 * min(i0 + i, n_evals - 1)];
+                    ev2[i] = rec[2 + 2 * min(i0 + i, n_evals - 1)];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < kEvals; ++i) x[i] = kLds || inside ? xs[ev[i].z * ld] : 0.0f;      // none: row 0, unused
+#pragma unroll
+            for (int i = 0; i < kEvals; ++i) {
+                if (i0 + i < n_evals) {
+                    if (__builtin_amdgcn_readfirstlane(ev2[i].x) != 0xFFFFFFFFu && (kLds || inside)) {
+#pragma clang fp contract(off)
+                        const float step = gs[ev2[i].x * ld] * __uint_as_float(ev2[i].y);
+                        x[i] = x[i] - step;
+                    }
+                    xh_s[ev[i].x][t] = x[i];
+                }
+            }
+        }
+        if (copies) rec_s[(it + 2) & 3][lane] = ahead;
+        __syncthreads();
+
+        // ---- B: sums of the dot products, coefficients; first what the next phase A needs
+        const v4u* next = rec_s[(it + 1) & 3];
+        n_updates = __builtin_amdgcn_readfirstlane(next[0].x);
+        evaluate = __builtin_amdgcn_readfirstlane(next[0].z);
+        read_updates(next, 0, n_updates);
+#pragma unroll
+        for (int i = 0; i < kEvals; ++i) {
+            ev[i] = next[1 + 2 * i];
+            ev2[i] = next[2 + 2 * i];
+        }
+        put_addresses(next, (it + 1) & 1);
+        if (groups > 1) {       // the group's sums: sample q is summed by the block of rank q mod group_blocks
+            const int log_group = sum_width(group_blocks), part = t & ((1 << log_group) - 1), slots = kStripHelpers >> log_group;
+            const int mine = rank < S ? (S - rank + group_blocks - 1) / group_blocks : 0;      // samples of a gradient
+            for (int d0 = 0; d0 < n_evals * mine; d0 += slots) {
+                int d = d0 + (t >> log_group), i = 0;
+                const bool live = part < group_blocks && d < n_evals * mine;
+#pragma unroll
+                for (int k = 1; k < kHalf; ++k)
+                    if (d >= mine && i < n_evals - 1) d -= mine, ++i;
+                const uint32_t of = rec[1 + 2 * i].y;
+                const uint32_t where[1] = {live ? (((of % kStripRing) * groups + group) * S + rank + d * group_blocks) * kStripGroupBlocks + part : 0};
+                const uint32_t number[1] = {live ? of : 0};
+                float v[1];
+                wait_words<1>(a.words, where, number, v, given_up);
+                const float sum = group_sum(v[0], log_group);
+                if (part == 0 && live) put_word(p.sums, ((of % kStripRing) * S + rank + d * group_blocks) * kStripGroups + group, sum, of);
+            }
+        }
+        for (int from = 0; from < n_evals * kTeamHelpers; from += kWordsInFlight * pair_step) {
+            float z[kWordsInFlight], reg[kWordsInFlight];
+            const unsigned long long* base = groups > 1 ? p.sums : a.words;
+            read_pairs(rec, from, n_evals);
+            wait_words<kWordsInFlight>(base, at, seq, z, given_up);
+#pragma unroll
+            for (int u = 0; u < kWordsInFlight; ++u) reg[u] = 0.0f;
+            if (S > M) {
+#pragma unroll
+                for (int u = 0; u < kWordsInFlight; ++u) at[u] += place[u] == kStripHelpers ? 0 : (M - place[u] % kTeamHelpers) * pitch;
+                wait_words<kWordsInFlight>(base, at, seq, reg, given_up);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+#pragma unroll
+            for (int u = 0; u < kWordsInFlight; ++u) {
+                z[u] = group_sum(z[u], log_width);
+                if (S > M) reg[u] = group_sum(reg[u], log_width);
+            }
+#pragma unroll
+            for (int u = 0; u < kWordsInFlight; ++u) {
+                if (sub != 0 || place[u] == kStripHelpers) continue;
+                const float target = target_s[place[u]];
+                float coef, loss;
+                if (a.model == ADPSGD_MODEL_LSQ) {
+                    const float r = z[u] - target;              // a.x - b
+                    loss = 0.5f * r * r;
+                    coef = r;
+                } else {
+                    const float s = -target * z[u];             // F = log(1 + e^s) + reg
+                    loss = a.loss ? (s > 0.0f ? s + log1pf(expf(-s)) : log1pf(expf(s))) + 0.5f * a.lambda * reg[u] : 0.0f;
+                    coef = -target / (1.0f + expf(-s));         // -y sigmoid(s)
+                }
+                coef_s[place[u]] = coef * a.gscale;
+                loss_s[place[u]] = loss;
+            }
+        }
+        __syncthreads();
+
+        // ---- C: losses; indices and record of the iterations after the next (what a helper loads here has arrived when
+        // the next waits of phase B begin)
+        fetch_index(rec_s[(it + 2) & 3]);
+        if (copies) ahead = recs[static_cast<int64_t>(it + 3) * a.rec_len];
+        if (a.loss) {
+            for (int i = hw; i < n_evals; i += 4) {
+                const v4u e = rec[1 + 2 * i];
+                if (__builtin_amdgcn_readfirstlane(e.y) % static_cast<uint32_t>(p.blocks) != static_cast<uint32_t>(block)) continue;
+                float sum = lane < M ? loss_s[e.x * kTeamHelpers + lane] : 0.0f;
+                if (lane + 64 < M) sum += loss_s[e.x * kTeamHelpers + lane + 64];
+                sum = all_sum(sum);
+                if (lane == 0) a.loss[rec[2 + 2 * i].z] = sum * a.gscale;
+            }
+        }
+        __syncthreads();
+    }
+    if (given_up) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (!kLds) return;
+    if (inside) {
+        for (int r = 0; r < a.n; ++r) {
+            a.X[r * a.ld + col] = xs[r * ld];
+            if (kMom) a.V[r * a.ld + col] = vs[r * ld];
+        }
+        for (int i = a.n_in; i < a.n_in + a.n_out; ++i) a.slots[a.carry[2 * i + 1] * a.ld + col] = gs[a.carry[2 * i] * ld];
+    }
+}
+
+template <int kTeams, int kRows>
+hipError_t launch_rows(StripParams& p, hipStream_t st) {
+    const StripArgs& a = p.a;
+    const size_t lds = a.lds_state ? static_cast<size_t>(a.n * (a.V ? 2 : 1) + a.n_lds_slots) * kStripCols * 4 : 0;
+    void* fn = a.lds_state ? (a.V ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, true, true>)
+                                  : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, true, false>))
+                           : (a.V ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, false, true>)
+                                  : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, false, false>));
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
+    if (e != hipSuccess) return e;
+    void* args[] = {&p};
+    return hipLaunchCooperativeKernel(fn, dim3(static_cast<uint32_t>(a.grid)), dim3(kStripThreads), args, lds, st);
+}
+
+int strip_samples(int model, int32_t M) { return M + (model == ADPSGD_MODEL_LOGREG ? 1 : 0); }
+
+}  // namespace
+
+int32_t strip_blocks(int64_t d) { return static_cast<int32_t>((d + kStripCols - 1) / kStripCols); }
+
+// Up to 32 strips form one group; more are spread evenly over 8.
+int32_t strip_group_size(int64_t d) {
+    const int32_t blocks = strip_blocks(d);
+    return blocks <= kStripGroupBlocks ? blocks : (blocks + kStripGroups - 1) / kStripGroups;
+}
+
+size_t strip_exchange_bytes(int model, int32_t M) {
+    return static_cast<size_t>(kStripRing) * strip_samples(model, M) * (kStripGroups * kStripGroupBlocks + kStripGroups) * sizeof(unsigned long long);
+}
+
+// LDS of a block: the kernel's fixed arrays and the state of the strip
+size_t strip_lds_bytes(int32_t M, int32_t n, bool momentum, int32_t n_slots, bool lds_state) {
+    const size_t fixed = (kStripMainWaves + strip_teams(M)) * 1024 + 4 * kStripMaxRec * sizeof(StripEntry) + kStripHelpers * 48 + 1024;
+    return fixed + (lds_state ? (static_cast<size_t>(n) * (momentum ? 2 : 1) + n_slots) * kStripCols * 4 : 0);
+}
+
+hipError_t launch_strips(const StripArgs& a, hipStream_t st) {
+    const int32_t blocks = strip_blocks(a.d);
+    if (a.d > kStripMaxD || a.M < 1 || a.M > kStripMaxM || a.rec_len > kStripMaxRec || a.teams != strip_teams(a.M) || a.grid < blocks)
+        return hipErrorInvalidValue;
+    StripParams p;
+    p.a = a;
+    p.samples = a.loss ? strip_samples(a.model, a.M) : a.M;
+    p.blocks = blocks;
+    p.group_size = strip_group_size(a.d);
+    p.sums = a.words + static_cast<int64_t>(kStripRing) * strip_samples(a.model, a.M) * kStripGroups * kStripGroupBlocks;
+    switch (a.teams) {
+        case 12: return a.M <= 8 ? launch_rows<12, 8>(p, st) : launch_rows<12, 16>(p, st);
+        case 6: return launch_rows<6, 16>(p, st);
+        case 4: return a.M <= 48 ? launch_rows<4, 16>(p, st) : launch_rows<4, 22>(p, st);
+        default: return a.M <= 96 ? launch_rows<2, 16>(p, st) : launch_rows<2, 22>(p, st);
+    }
+}
+
+}  // namespace adpsgd_impl

@@ -1,0 +1,87 @@
+// Interface between the host code that lays a call of a linear model out as one persistent launch
+// (strips.cpp) and the kernel that executes it (kernels_strips.hip).
+#pragma once
+
+#include "internal.hpp"
+
+namespace adpsgd_impl {
+
+constexpr int kStripCols = 256;          // columns of the models a block owns
+constexpr int kStripMainWaves = 12;      // wavefronts that hold minibatch rows, split evenly over the teams
+constexpr int kStripHelpers = 256;       // further threads, one per column: models, slots, exchange
+constexpr int kStripRing = 32;           // exchanges whose words are kept (more than twice the teams)
+constexpr int kStripGroups = 8;          // groups of blocks that sum among themselves first (one per XCD) ...
+constexpr int kStripGroupBlocks = 32;    // ... and blocks in a group, at most
+constexpr int kStripCounters = 16;       // words that the blocks count themselves with, zero before the launch
+constexpr int kStripMaxRec = 64;         // entries of a record
+constexpr int64_t kStripMaxD = kStripGroups * kStripGroupBlocks * kStripCols;    // at most one block per compute unit
+constexpr int32_t kStripMaxM = 128;
+constexpr int kStripLdsBytes = 160 * 1024;
+
+// A record is one iteration of the kernel: a header, two entries for each of up to teams / 2 evaluations, two for each of
+// as many loads (both in the order of their teams), then the updates.  All fields are 32-bit words.
+//   header            updates, teams that load (bit mask), teams that evaluate (bit mask), -
+//   evaluation        team, sequence number of the gradient, worker read, slot the gradient goes to;
+//                     slot of the pending gradient that compensates the read (or -1), its step size, the event, -
+//   load              position in the index table, row pitch of the features, features (64 bits);  targets (64 bits), -, -
+//   update            row i | row j << 16, slot, step size, flags (bit 0: averaging only)
+struct alignas(16) StripEntry {
+    uint32_t x, y, z, w;
+};
+// The iterations of a call, laid out by build_strips.
+struct StripProgram {
+    int32_t teams = 0, rec_len = 0;
+    int64_t iterations = 0;
+    std::vector<StripEntry> recs;        // (iterations + 3) x rec_len, the last three empty
+    std::vector<int64_t> order;          // events in the order their gradients are evaluated (rows of the index table)
+    std::vector<int32_t> slot;           // per event: slot inside the call (-1: none)
+    int32_t n_slots = 0;                 // slots used inside the call
+};
+
+struct StripCall {
+    int64_t K, A;          // events in the arrays, events applied
+    const int32_t *worker, *neighbour;
+    const float* gamma;                  // per event or nullptr
+    float gamma_default;
+    const int64_t* extra_ptr;
+    const int32_t *extra_a, *extra_b;
+    const Plan* plan;
+    const int32_t* carried_slot;         // per event or nullptr
+    const WorkerData* data;
+    bool renumber;                       // slots of the call numbered from 0 by lifetime (they live in LDS)
+    uint32_t seq0;                       // sequence number of the first gradient
+};
+// Teams of wavefronts (gradients whose rows are held) for a minibatch of M samples: as many as their rows leave
+// registers for (at most 22 rows of a wavefront).
+inline int32_t strip_teams(int32_t M) { return M <= 16 ? 12 : M <= 32 ? 6 : M <= 64 ? 4 : 2; }
+void build_strips(const StripCall& c, int32_t teams, StripProgram& out);
+
+struct StripArgs {
+    float* X;
+    float* V;                // momentum buffers or nullptr
+    int64_t ld, d;
+    int32_t n;
+    int model;               // LSQ or LOGREG
+    int32_t M, teams;
+    const StripEntry* recs;  // device
+    int32_t rec_len, iterations;
+    const int32_t* idx;      // device, minibatch indices in the order of evaluation
+    const int32_t* carry;    // device: n_in + n_out pairs (slot of the call, slot of the workspace)
+    int32_t n_in, n_out;
+    float* slots;            // the workspace
+    int32_t n_lds_slots;
+    bool lds_state;          // models, momentum buffers and slots of the strip live in LDS
+    unsigned long long* words;    // exchange memory: strip_exchange_bytes
+    unsigned int* counters;  // device, kStripCounters zeros
+    int32_t grid;            // blocks to launch, at least one per strip
+    float gscale, lambda, momentum, weight_decay;
+    float* loss;             // device, indexed by event, or nullptr
+    int* status;             // pinned host word, set when an exchange never completes
+};
+int32_t strip_blocks(int64_t d);
+int32_t strip_group_size(int64_t d);
+size_t strip_exchange_bytes(int model, int32_t M);
+size_t strip_lds_bytes(int32_t M, int32_t n, bool momentum, int32_t n_slots, bool lds_state);
+hipError_t launch_strips(const StripArgs& a, hipStream_t st);
+
+}  // namespace adpsgd_impl

@@ -1,0 +1,110 @@
+"""GPU: the linear models' events executed in one persistent launch (blocks own columns and exchange dot products) at
+the sizes where that path changes shape, against the oracle; and a bigger handle that goes by rounds."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import logreg_data, lsq_data, random_extra_pairs, random_regular4_graph, ring_graph, with_identity_events
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5          # of the whole suite for 32-bit models: max over workers of |x - x_ref|_inf / |x_ref|_inf
+
+
+@pytest.fixture(scope="module")
+def P():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1710_06952_amd as pkg
+    pkg.lib()
+    return pkg
+
+
+def rel_err(x, ref):
+    num = np.max(np.abs(x.astype(np.float64) - ref.astype(np.float64)), axis=1)
+    return float(np.max(num / np.maximum(np.max(np.abs(ref.astype(np.float64)), axis=1), 1e-30)))
+
+
+# d around the float4, the strip of 256 columns, 32 strips (one group of blocks, then several) and the largest, 65 536;
+# M around the numbers of teams and rows (8, 16, 32, 48, 64, 96, 128) and n up to where the strips' state leaves LDS
+# (170 workers) and n M = 1024, the last that go this way; then the first sizes that go by rounds
+@pytest.mark.parametrize("model,n,d,M,K,T,mu,comp", [
+    ("lsq", 2, 1, 1, 40, 3, 0.0, False), ("logreg", 5, 3, 2, 60, 4, 0.9, False), ("lsq", 6, 255, 8, 80, 4, 0.9, False),
+    ("logreg", 6, 256, 9, 80, 5, 0.0, True), ("lsq", 8, 257, 16, 120, 6, 0.0, False), ("logreg", 7, 1030, 17, 100, 4, 0.9, True),
+    ("lsq", 9, 2047, 32, 120, 8, 0.0, True), ("logreg", 8, 2049, 33, 100, 3, 0.0, False), ("lsq", 6, 8191, 48, 60, 3, 0.9, False),
+    ("logreg", 6, 8193, 49, 60, 4, 0.0, True), ("lsq", 5, 16_385, 64, 50, 3, 0.0, False), ("logreg", 5, 9001, 65, 50, 3, 0.9, False),
+    ("lsq", 4, 4100, 96, 50, 2, 0.0, False), ("logreg", 4, 8705, 97, 40, 3, 0.0, False), ("lsq", 8, 3003, 128, 40, 3, 0.0, True),
+    ("logreg", 4, 65_535, 12, 40, 6, 0.9, False), ("lsq", 3, 65_536, 24, 30, 0, 0.0, False),
+    ("lsq", 170, 1101, 6, 500, 6, 0.0, False), ("logreg", 90, 1101, 8, 300, 4, 0.9, True), ("lsq", 64, 8200, 16, 250, 30, 0.0, False),
+    ("lsq", 4, 65_537, 8, 30, 3, 0.0, False), ("lsq", 5, 1500, 129, 30, 3, 0.0, False), ("logreg", 40, 300, 14, 150, 4, 0.0, False)])
+def test_events_in_one_launch_against_the_oracle(P, model, n, d, M, K, T, mu, comp):
+    print("strips %s n=%d d=%d M=%d mu=%g comp=%d" % (model, n, d, M, mu, comp), flush=True)
+    rows = max(M, 24)
+    g = ring_graph(n) if n % 2 or n < 6 else random_regular4_graph(n, 3)
+    if model == "lsq":
+        feats, targs, _ = lsq_data(n, rows, d, seed=5, feature_var=1.0 / d)
+        omodel, base, lam = oracle.MODEL_LSQ, 0.3, 0.0
+    else:
+        feats, targs, _ = logreg_data(n, rows, d, seed=5)
+        omodel, base, lam = oracle.MODEL_LOGREG, 0.5, 1e-3
+    base *= 0.1 if mu else 1.0
+    sched = oracle.make_schedule(g, K, seed=6, T_max=T, M=M, rows=[rows] * n)
+    sched["neighbour"] = with_identity_events(sched["worker"], sched["neighbour"], 0.1, seed=1)
+    sched["gamma"] = (base * (1 + np.arange(K) % 3)).astype(np.float32)
+    if not comp:
+        sched["extra_pairs"] = random_extra_pairs(g, sched["worker"], sched["neighbour"], max_extra=1, seed=2)
+    x0 = np.random.default_rng(3).standard_normal((n, d)).astype(np.float32)
+    wd = 1e-3 if mu else 0.0
+    eng = P.Engine(g, d, model, M=M, gamma=base, lam=lam, T_max=T, momentum=mu, weight_decay=wd, local_compensation=comp, verify_plan=True)
+    eng.load_data(feats, targs)
+    eng.set_models(x0, broadcast=False)
+    Xr, Vr = x0.copy(), np.zeros_like(x0) if mu else None
+    for call in range(2):                            # the second call starts from the state of the first
+        eng.run_events(sched, want_loss=call == 0)
+        r = oracle.run_events(Xr, sched, omodel, base, M=M, gscale=1.0 / M, lam=lam, features=feats, targets=targs, gamma_k=sched["gamma"],
+                              extra_pairs=sched.get("extra_pairs"), momentum=mu, weight_decay=wd, V=Vr, local_compensation=comp,
+                              want_loss=True)
+        if call == 0:
+            assert np.allclose(eng.get_loss(), r["loss"], rtol=2e-4, atol=1e-6)
+    assert rel_err(eng.get_models(), Xr) <= TOL
+    if mu:
+        assert rel_err(eng.get_momentum(), Vr) <= TOL
+    assert not eng.X[:, d:].any()                    # the padding of the rows stays zero
+    st = eng.get_stats()                             # the rounds are counted however they are executed
+    assert st["events"] == 2 * K and 0 < st["fused_launches"] <= st["rounds"] and st["grad_launches"] > 0
+    eng.close()
+
+
+def test_two_engines_on_two_streams_share_the_chip(P):
+    """Launches whose blocks wait for each other, from two streams without an order between them: both complete, with the
+    bits of engines that run alone."""
+    import torch
+    n, d, M, K = 8, 20_001, 12, 150
+    g = ring_graph(n)
+    feats, targs, _ = lsq_data(n, 32, d, seed=8, feature_var=1.0 / d)
+    sched = oracle.make_schedule(g, K, seed=9, T_max=4, M=M, rows=[32] * n)
+    x0 = np.random.default_rng(1).standard_normal((n, d)).astype(np.float32)
+
+    def engine():
+        e = P.Engine(g, d, "lsq", M=M, gamma=0.3, T_max=4)
+        e.load_data(feats, targs)
+        e.set_models(x0, broadcast=False)
+        return e
+
+    alone = engine()
+    for _ in range(4):
+        alone.run_events(sched)
+    want = alone.get_models()
+    pair = []
+    for _ in range(2):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            pair.append(engine())
+    for _ in range(4):
+        for e in pair:
+            e.run_events(sched)
+    for e in pair:
+        assert np.array_equal(e.get_models(), want)
+        e.close()
+    alone.close()
