@@ -770,7 +770,7 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     }
     StripCall sc{c.K, c.A, c.s->worker, c.s->neighbour, c.s->gamma, h->o.gamma, c.s->extra_ptr, c.s->extra_a, c.s->extra_b,
                  &c.plan, c.carried_slot.empty() ? nullptr : c.carried_slot.data(), h->data.data(), true,
-                 h->exchange_seq + 1};
+                 h->exchange_seq + 1, strip_blocks(h->d)};
     const int32_t teams = strip_teams(M);
     StripProgram prog;
     build_strips(sc, teams, prog);

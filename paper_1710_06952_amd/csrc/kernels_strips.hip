@@ -7,18 +7,20 @@
 // M dot products a_m . x^ of every gradient; models, momentum buffers and pending gradients of a strip stay in LDS,
 // minibatch rows are read once, into registers, ahead of the events that need them (the schedule names them), and are
 // still there when the coefficients arrive.
-// Measured, a call against the same call in rounds: n = 8, d = 1024, M = 32, 200 events 0.36 against 0.79 ms;  n = 16,
-// d = 4096, M = 8, 1280 events 1.33 against 7.2 ms;  n = 16, d = 20 001, M = 50, wait-free with momentum, 400 events 2.05
-// against 4.28 ms.  What binds now is the chain of an iteration, 3.5 us for the second of these: exchange 1.0, the
-// helpers' sums and coefficients 0.9, updates and x^ 0.7, dot products 0.2, combination 0.2, barriers and records the rest.
+// Measured, a call against the same call in rounds: n = 8, d = 1024, M = 32, 200 events 0.32 against 0.77 ms;  n = 16,
+// d = 4096, M = 8, 1280 events 1.25 against 7.2 ms;  n = 16, d = 20 001, M = 50, wait-free with momentum, 400 events 1.89
+// against 4.1 ms.  What binds now is the chain of an iteration, 3.4 us for the second of these: updates and x^ 0.6, dot
+// products 0.15, exchange and coefficients 1.9, combination 0.3, barriers and records the rest; with many rows per
+// gradient (the third, 7.8 us) also their address translation, about 40 cycles per row and compute unit.
 //
 // A block has 12 main wavefronts in `teams` teams, each team with the rows of one gradient in its registers, and 4
 // helper wavefronts (one thread per column, and one per minibatch sample).  An iteration has three phases:
-//   A  helpers: finish the gradients of the last iteration, apply updates, write x^ of the next gradients to LDS
+//   A  helpers: finish the gradients of the last iteration, apply updates, write x^ of the next gradients to LDS;
+//      main: idle teams request the rows of their next gradient
 //   B  main: dot products of a team's rows with x^, published;  helpers: wait for the sums, make the coefficients
-//   C  main: sum_m c_m a_m of the team's rows to LDS, request the rows of the next gradient
-// The waits of phase B are in the helpers, so that they do not queue behind the rows in flight (loads of a wavefront
-// return in order).
+//   C  main: sum_m c_m a_m of the team's rows to LDS
+// A compute unit returns vector loads in order, so a wait of phase B stands behind the rows requested before it: they go
+// out at the start of phase A (in phase B they cost 0.5 us per iteration), and the helpers load nothing else before a wait.
 //
 // The sums go through the words of exchange.hpp: up to 32 strips exchange them directly; more sum within their XCD first
 // (the blocks of a group share out the samples), and only these sums cross the chip, at most 8 per sample.
@@ -37,7 +39,8 @@ struct StripParams {
     StripArgs a;
     int32_t samples;             // words per block and gradient: M, and |x^|^2 of the logistic loss
     int32_t blocks, group_size;  // strips, and how many form a group
-    unsigned long long* sums;    // the groups' sums, [ring][samples][kStripGroups]
+    unsigned long long* sums;    // the groups' sums, [ring][group][samples, whole lines]: a line is written on one XCD only
+    int32_t sum_pitch;           // words of a group's sums
 };
 
 __device__ __forceinline__ float dot4(v4f a, v4f b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
@@ -98,10 +101,24 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
 #pragma unroll
         for (int r = 0; r < kRows; ++r) row[r] = v4f{0, 0, 0, 0};
         __syncthreads();       // the first records
+        __syncthreads();       // their addresses
         for (int it = 0; it < a.iterations; ++it) {
-            __syncthreads();   // phase A done
             const v4u* rec = rec_s[it & 3];
             const uint32_t evaluate = __builtin_amdgcn_readfirstlane(rec[0].z), load = __builtin_amdgcn_readfirstlane(rec[0].y);
+            if ((load >> team & 1) != 0) {      // early: the polls of phase B stand behind these loads
+                // no branch around a load: the wavefront would wait for one row before it requests the next
+#pragma unroll
+                for (int r0 = 0; r0 < kRows; r0 += kChunk) {
+                    const float* src[kChunk];
+#pragma unroll
+                    for (int r = 0; r < kChunk; ++r) src[r] = rowp_s[it & 1][team * kTeamHelpers + min(first + kTeamWaves * (r0 + r), M - 1)];
+#pragma unroll
+                    for (int r = 0; r < kChunk; ++r)
+                        if (r0 + r < kRows) row[r0 + r < kRows ? r0 + r : 0] = *reinterpret_cast<const v4f*>(src[r] + from);
+                }
+                target = *targetp_s[it & 1][team * kTeamHelpers + min(mine, M - 1)];
+            }
+            __syncthreads();   // phase A done
             const bool evaluates = (evaluate >> team & 1) != 0;
             const v4u* eval = rec + 1 + 2 * __popc(evaluate & ((1u << team) - 1));
             if (evaluates) {
@@ -134,19 +151,6 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                     if (lane == 0) put_word(a.words, words + M * kStripGroupBlocks, z, seq);
                 }
             }
-            if ((load >> team & 1) != 0) {      // another team's exchange hides the time this takes
-                // no branch around a load: the wavefront would wait for one row before it requests the next
-#pragma unroll
-                for (int r0 = 0; r0 < kRows; r0 += kChunk) {
-                    const float* src[kChunk];
-#pragma unroll
-                    for (int r = 0; r < kChunk; ++r) src[r] = rowp_s[it & 1][team * kTeamHelpers + min(first + kTeamWaves * (r0 + r), M - 1)];
-#pragma unroll
-                    for (int r = 0; r < kChunk; ++r)
-                        if (r0 + r < kRows) row[r0 + r < kRows ? r0 + r : 0] = *reinterpret_cast<const v4f*>(src[r] + from);
-                }
-                target = *targetp_s[it & 1][team * kTeamHelpers + min(mine, M - 1)];
-            }
             __syncthreads();   // the coefficients are there
             if (evaluates) {
                 v4f acc = {0, 0, 0, 0};
@@ -158,6 +162,12 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
 #pragma unroll
                     for (int r = 0; r < kChunk; ++r)
                         if (r0 + r < kRows && first + kTeamWaves * (r0 + r) < M) acc += row[r0 + r < kRows ? r0 + r : 0] * coef[r];
+                }
+                if (a.loss && first == 0 && __builtin_amdgcn_readfirstlane(eval[1].w) == static_cast<uint32_t>(block)) {
+                    float sum = lane < M ? loss_s[team * kTeamHelpers + lane] : 0.0f;
+                    if (lane + 64 < M) sum += loss_s[team * kTeamHelpers + lane + 64];
+                    sum = all_sum(sum);
+                    if (lane == 0) a.loss[__builtin_amdgcn_readfirstlane(eval[1].z)] = sum * a.gscale;
                 }
                 if (kDirect) {
                     if (a.model == ADPSGD_MODEL_LOGREG) acc += *reinterpret_cast<const v4f*>(&xh_s[team][4 * lane]) * regularise;
@@ -229,7 +239,9 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     };
     const int log_width = sum_width(groups > 1 ? groups : group_blocks), sub = t & ((1 << log_width) - 1);
     const int words = groups > 1 ? groups : group_blocks;               // of a sum
-    const uint32_t pitch = groups > 1 ? kStripGroups : kStripGroupBlocks;
+    // word of sample q and partial sum `sub`: by groups of whole lines, or by samples
+    const uint32_t q_pitch = groups > 1 ? 1 : kStripGroupBlocks, sub_pitch = groups > 1 ? p.sum_pitch : 1;
+    const uint32_t ring_pitch = groups > 1 ? groups * p.sum_pitch : S * kStripGroupBlocks;
     const int pair0 = t >> log_width, pair_step = kStripHelpers >> log_width;
     uint32_t at[kWordsInFlight], seq[kWordsInFlight], place[kWordsInFlight];
     auto read_pairs = [&](const v4u* rec, int from, int count) {        // (gradient, sample) pairs, samples padded to a power of two
@@ -240,7 +252,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
             const v4u e = rec[1 + 2 * min(i, kHalf - 1)];
             place[u] = live ? e.x * kTeamHelpers + q : kStripHelpers;
             seq[u] = live && sub < words ? e.y : 0;
-            at[u] = live ? ((e.y % kStripRing) * S + q) * pitch + min(sub, words - 1) : 0;
+            at[u] = live ? (e.y % kStripRing) * ring_pitch + q * q_pitch + min(sub, words - 1) * sub_pitch : 0;
         }
     };
     if (copies) {
@@ -252,6 +264,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     __syncthreads();
     fetch_index(rec_s[0]);
     put_addresses(rec_s[0], 0);
+    __syncthreads();
     fetch_index(rec_s[1]);
     n_updates = __builtin_amdgcn_readfirstlane(rec_s[0][0].x);
     evaluate = __builtin_amdgcn_readfirstlane(rec_s[0][0].z);           // record 0 evaluates nothing
@@ -366,7 +379,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                 float v[1];
                 wait_words<1>(a.words, where, number, v, given_up);
                 const float sum = group_sum(v[0], log_group);
-                if (part == 0 && live) put_word(p.sums, ((of % kStripRing) * S + rank + d * group_blocks) * kStripGroups + group, sum, of);
+                if (part == 0 && live) put_word(p.sums, ((of % kStripRing) * groups + group) * p.sum_pitch + rank + d * group_blocks, sum, of);
             }
         }
         for (int from = 0; from < n_evals * kTeamHelpers; from += kWordsInFlight * pair_step) {
@@ -378,7 +391,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
             for (int u = 0; u < kWordsInFlight; ++u) reg[u] = 0.0f;
             if (S > M) {
 #pragma unroll
-                for (int u = 0; u < kWordsInFlight; ++u) at[u] += place[u] == kStripHelpers ? 0 : (M - place[u] % kTeamHelpers) * pitch;
+                for (int u = 0; u < kWordsInFlight; ++u) at[u] += place[u] == kStripHelpers ? 0 : (M - place[u] % kTeamHelpers) * q_pitch;
                 wait_words<kWordsInFlight>(base, at, seq, reg, given_up);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -387,40 +400,38 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                 z[u] = group_sum(z[u], log_width);
                 if (S > M) reg[u] = group_sum(reg[u], log_width);
             }
+            // every lane of a group has the sums of its pairs: the u-th lane finishes the u-th pair
+            float dot = z[0], square = reg[0];
+            uint32_t to = place[0];
 #pragma unroll
-            for (int u = 0; u < kWordsInFlight; ++u) {
-                if (sub != 0 || place[u] == kStripHelpers) continue;
-                const float target = target_s[place[u]];
+            for (int u = 1; u < kWordsInFlight; ++u)
+                if (sub == u) {
+                    dot = z[u];
+                    square = reg[u];
+                    to = place[u];
+                }
+            if (sub < kWordsInFlight && to != kStripHelpers) {
+                const float target = target_s[to];
                 float coef, loss;
                 if (a.model == ADPSGD_MODEL_LSQ) {
-                    const float r = z[u] - target;              // a.x - b
+                    const float r = dot - target;               // a.x - b
                     loss = 0.5f * r * r;
                     coef = r;
                 } else {
-                    const float s = -target * z[u];             // F = log(1 + e^s) + reg
-                    loss = a.loss ? (s > 0.0f ? s + log1pf(expf(-s)) : log1pf(expf(s))) + 0.5f * a.lambda * reg[u] : 0.0f;
+                    const float s = -target * dot;              // F = log(1 + e^s) + reg
+                    loss = a.loss ? (s > 0.0f ? s + log1pf(expf(-s)) : log1pf(expf(s))) + 0.5f * a.lambda * square : 0.0f;
                     coef = -target / (1.0f + expf(-s));         // -y sigmoid(s)
                 }
-                coef_s[place[u]] = coef * a.gscale;
-                loss_s[place[u]] = loss;
+                coef_s[to] = coef * a.gscale;
+                loss_s[to] = loss;
             }
         }
         __syncthreads();
 
-        // ---- C: losses; indices and record of the iterations after the next (what a helper loads here has arrived when
-        // the next waits of phase B begin)
+        // ---- C: indices and record of the iterations after the next (what a helper loads here has arrived when the next
+        // waits of phase B begin)
         fetch_index(rec_s[(it + 2) & 3]);
         if (copies) ahead = recs[static_cast<int64_t>(it + 3) * a.rec_len];
-        if (a.loss) {
-            for (int i = hw; i < n_evals; i += 4) {
-                const v4u e = rec[1 + 2 * i];
-                if (__builtin_amdgcn_readfirstlane(e.y) % static_cast<uint32_t>(p.blocks) != static_cast<uint32_t>(block)) continue;
-                float sum = lane < M ? loss_s[e.x * kTeamHelpers + lane] : 0.0f;
-                if (lane + 64 < M) sum += loss_s[e.x * kTeamHelpers + lane + 64];
-                sum = all_sum(sum);
-                if (lane == 0) a.loss[rec[2 + 2 * i].z] = sum * a.gscale;
-            }
-        }
         __syncthreads();
     }
     if (given_up) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -461,7 +472,7 @@ int32_t strip_group_size(int64_t d) {
 }
 
 size_t strip_exchange_bytes(int model, int32_t M) {
-    return static_cast<size_t>(kStripRing) * strip_samples(model, M) * (kStripGroups * kStripGroupBlocks + kStripGroups) * sizeof(unsigned long long);
+    return static_cast<size_t>(kStripRing) * (strip_samples(model, M) * kStripGroupBlocks + ((strip_samples(model, M) + 15) & ~15)) * kStripGroups * sizeof(unsigned long long);
 }
 
 // LDS of a block: the kernel's fixed arrays and the state of the strip
@@ -479,6 +490,7 @@ hipError_t launch_strips(const StripArgs& a, hipStream_t st) {
     p.samples = a.loss ? strip_samples(a.model, a.M) : a.M;
     p.blocks = blocks;
     p.group_size = strip_group_size(a.d);
+    p.sum_pitch = (p.samples + 15) & ~15;
     p.sums = a.words + static_cast<int64_t>(kStripRing) * strip_samples(a.model, a.M) * kStripGroups * kStripGroupBlocks;
     switch (a.teams) {
         case 12: return a.M <= 8 ? launch_rows<12, 8>(p, st) : launch_rows<12, 16>(p, st);

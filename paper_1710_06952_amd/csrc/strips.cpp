@@ -168,7 +168,7 @@ void build_strips(const StripCall& c, int32_t teams, StripProgram& out) {
                 if (c.renumber) out.slot[k] = b.take_slot();
                 e[0] = StripEntry{static_cast<uint32_t>(team), c.seq0 + static_cast<uint32_t>(at), static_cast<uint32_t>(c.worker[k]),
                                   static_cast<uint32_t>(out.slot[k])};
-                e[1] = StripEntry{0xFFFFFFFFu, 0, static_cast<uint32_t>(k), 0};
+                e[1] = StripEntry{0xFFFFFFFFu, 0, static_cast<uint32_t>(k), static_cast<uint32_t>(at % c.strips)};
                 if (kp >= 0) {
                     e[1].x = static_cast<uint32_t>(out.slot[kp]);
                     e[1].y = bits(c.gamma ? c.gamma[kp] : c.gamma_default);

@@ -22,7 +22,8 @@ constexpr int kStripLdsBytes = 160 * 1024;
 // as many loads (both in the order of their teams), then the updates.  All fields are 32-bit words.
 //   header            updates, teams that load (bit mask), teams that evaluate (bit mask), -
 //   evaluation        team, sequence number of the gradient, worker read, slot the gradient goes to;
-//                     slot of the pending gradient that compensates the read (or -1), its step size, the event, -
+//                     slot of the pending gradient that compensates the read (or -1), its step size, the event, the
+//                     strip that writes its loss
 //   load              position in the index table, row pitch of the features, features (64 bits);  targets (64 bits), -, -
 //   update            row i | row j << 16, slot, step size, flags (bit 0: averaging only)
 struct alignas(16) StripEntry {
@@ -50,6 +51,7 @@ struct StripCall {
     const WorkerData* data;
     bool renumber;                       // slots of the call numbered from 0 by lifetime (they live in LDS)
     uint32_t seq0;                       // sequence number of the first gradient
+    int32_t strips;                      // blocks with a strip
 };
 // Teams of wavefronts (gradients whose rows are held) for a minibatch of M samples: as many as their rows leave
 // registers for (at most 22 rows of a wavefront).
