@@ -140,20 +140,35 @@ __global__ __launch_bounds__(kThreads) void consensus_final_kernel(const double*
 }
 
 // ---- divergence check: number of entries of X that are NaN or infinite -----------------------
-// grid-stride over float4 pieces of all rows; one count per block, summed by the host.
+// Blocks stride over tiles of kCountTile float4 pieces of a row, eight loads of a thread in flight; one count per block,
+// summed by the host.  A read of all models, bound by memory: n = 64, d = 25.6 M (6.55 GB) 0.94 ms (7.0 TB/s) against
+// 1.22 ms for single pieces in row order, whose row and column cost a 64-bit division each.
+// STREAM: X does not fit the caches: non-temporal loads
+constexpr int kCountUnroll = 8;
+constexpr int64_t kCountTile = kThreads * kCountUnroll;
+template <bool STREAM>
 __global__ __launch_bounds__(kThreads) void count_nonfinite_kernel(const float* X, int64_t ld, int64_t d, int32_t n,
                                                                   unsigned long long* partial) {
     __shared__ unsigned long long red[kWaves];
-    const int64_t n_vec = (d + 3) / 4, total = n_vec * n;
+    const int64_t n_vec = (d + 3) / 4, row_tiles = (n_vec + kCountTile - 1) / kCountTile, tiles = row_tiles * n;
     unsigned long long bad = 0;
-    for (int64_t t = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; t < total;
-         t += static_cast<int64_t>(gridDim.x) * kThreads) {
-        const int64_t row = t / n_vec, v = t % n_vec;
-        const v4f x = *reinterpret_cast<const v4f*>(X + row * ld + 4 * v);     // the padding beyond d is zero
-        bad += !isfinite(x.x);
-        bad += !isfinite(x.y);
-        bad += !isfinite(x.z);
-        bad += !isfinite(x.w);
+    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {       // uniform: the division is scalar
+        const int64_t row = t / row_tiles, v0 = (t - row * row_tiles) * kCountTile + threadIdx.x;
+        const float* __restrict__ src = X + row * ld;
+        v4f x[kCountUnroll];
+#pragma unroll
+        for (int u = 0; u < kCountUnroll; ++u) {
+            const int64_t v = v0 + u * kThreads;
+            x[u] = load4<STREAM>(src + 4 * (v < n_vec ? v : 0));      // the padding beyond d is zero
+        }
+        uint32_t here = 0;
+#pragma unroll
+        for (int u = 0; u < kCountUnroll; ++u)
+            if (v0 + u * kThreads < n_vec) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) here += (__float_as_uint(x[u][c]) & 0x7F800000u) == 0x7F800000u;
+            }
+        bad += here;
     }
     for (int off = 32; off > 0; off >>= 1) bad += __shfl_xor(bad, off, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = bad;
@@ -276,7 +291,8 @@ hipError_t launch_compensated_rows(const float* X, int64_t ld, const GradOp* ops
 
 hipError_t launch_count_nonfinite(const float* X, int64_t ld, int64_t d, int32_t n, unsigned long long* partial,
                                   int32_t blocks, hipStream_t st) {
-    hipLaunchKernelGGL(count_nonfinite_kernel, dim3(blocks), dim3(kThreads), 0, st, X, ld, d, n, partial);
+    if (static_cast<int64_t>(n) * ld * 4 > kStreamBytes) hipLaunchKernelGGL(count_nonfinite_kernel<true>, dim3(blocks), dim3(kThreads), 0, st, X, ld, d, n, partial);
+    else hipLaunchKernelGGL(count_nonfinite_kernel<false>, dim3(blocks), dim3(kThreads), 0, st, X, ld, d, n, partial);
     return hipGetLastError();
 }
 
