@@ -8,7 +8,8 @@
 //   backward  dW1 = Xb^T dH                in x M  times  M x hid
 // The hidden activations and their back-propagated error are rounded to bf16
 // before they enter those products.  The second layer (hid x out, out <= 16) is
-// small and stays on the vector ALUs in fp32.
+// small: its forward products are on the vector ALUs, its backward ones on the
+// matrix cores, both in fp32.
 //
 // Launches per group of gradient operations: forward; softmax with the second-layer
 // gradients and the hidden error dH; and, only where a dense gradient is wanted
@@ -270,22 +271,27 @@ __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
 //   a. thread (m, o) finishes logit o of sample m (sum of the hid / 32 forward-tile contributions
 //      in tile order); the 16 lanes of a sample take the softmax together (butterfly max and sum).
 //      The 16 blocks of a gradient repeat this small step rather than wait for a kernel of its own.
-//   b. thread (hl, mg): hidden unit h = 64 blockIdx.x + hl, minibatch rows [4 mg, 4 mg + 4):
-//      its share of dW2 and db1, and the hidden error dH (rounded to bf16) of its four rows.
-//   c. the 16 row groups are added pairwise in a fixed tree through LDS.
+//   b. wavefront (ht, mt): hidden units 16 ht .. + 15 of the block's 64 and samples 16 mt .. + 15.  Both products are
+//      contractions of 16 on the matrix cores in fp32 (16x16x4, four steps): the hidden error dH = dl W2^T (rounded to
+//      bf16) and the samples' share of dW2 = H^T dl.  A lane's entries of H (hidden unit l % 16, samples 4 (l / 16) ..
+//      + 3) are the places of its results of the first and its operands of the second.
+//   c. the four shares of dW2 and db1 are added in order through LDS, one thread per (h, o).
+// (On the vector ALUs, with a tree of eight barriers over 16 row groups, this kernel took 8.8 us for the rounds of
+// 784-1024-10, M = 64, and 7.3 us for those of 64-256-10, M = 32; now 6.2 and 5.5.)
 constexpr int kBwdT = 1024;
-constexpr int kBwdGroups = kBwdT / 64;            // 16 row groups
-constexpr int kBwdRows = kMaxM / kBwdGroups;      // 4 minibatch rows per thread
 
 __global__ __launch_bounds__(kBwdT) void mlp_backward_small_kernel(const MlpParams p) {
     __shared__ __attribute__((aligned(16))) float dl_s[kMaxM][kMaxOut];   // softmax - onehot, zero beyond M and out
     __shared__ float loss_s[kMaxM];
-    __shared__ float red[kBwdGroups / 2][kMaxOut + 1][64];
+    __shared__ float red[4][64][kMaxOut];           // shares of dW2, by sample tile
+    __shared__ float red1[4][64];                   // shares of db1
     const GradOp op = p.ops[blockIdx.y];     // needed for the stores only: no load below waits for it
     uint16_t* __restrict__ dH = p.factored ? reinterpret_cast<uint16_t*>(p.slots + static_cast<int64_t>(op.slot) * p.ld)
                                            : p.dHb + static_cast<int64_t>(blockIdx.y) * kMaxM * p.hid;
-    const int hl = threadIdx.x & 63, mg = threadIdx.x >> 6;
-    const int h = blockIdx.x * 64 + hl;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lrow = lane & 15, lgrp = lane >> 4;
+    const int ht = wave & 3, mt = wave >> 2;
+    const int hl = 16 * ht + lrow, h = blockIdx.x * 64 + hl;      // this lane's hidden unit ...
+    const int m0 = 16 * mt + 4 * lgrp;                            // ... and the first of its four samples
     const int sm = threadIdx.x >> 4, so = threadIdx.x & 15;       // step a: sample and logit
 
     // ---- all global loads (everything the forward kernel left in the scratch memory, addressed by block index)
@@ -297,18 +303,12 @@ __global__ __launch_bounds__(kBwdT) void mlp_backward_small_kernel(const MlpPara
 #pragma unroll
     for (int t = 0; t < kTileBatch; ++t) part[t] = t < tiles ? src[static_cast<int64_t>(t) * kMaxM * kMaxOut] : 0.0f;
     const float b2v = p.b2f[static_cast<int64_t>(blockIdx.y) * kMaxOut + so];         // zero beyond `out`
-    v4f w2q[kMaxOut / 4];
-    uint16_t hraw[kBwdRows];
-    {
-        const v4f* __restrict__ w2p = reinterpret_cast<const v4f*>(p.W2f + (static_cast<int64_t>(blockIdx.y) * p.hid + h) * kMaxOut);
+    // outputs 4 lgrp .. + 3 of the hidden unit
+    const v4f w2 = *reinterpret_cast<const v4f*>(p.W2f + (static_cast<int64_t>(blockIdx.y) * p.hid + h) * kMaxOut + 4 * lgrp);
+    uint16_t hraw[4];
 #pragma unroll
-        for (int q = 0; q < kMaxOut / 4; ++q) w2q[q] = w2p[q];
-    }
-#pragma unroll
-    for (int r = 0; r < kBwdRows; ++r) {
-        const int m = kBwdRows * mg + r;
-        hraw[r] = m < p.M ? p.Hb[(static_cast<int64_t>(blockIdx.y) * kMaxM + m) * p.hid + h] : static_cast<uint16_t>(0);
-    }
+    for (int v = 0; v < 4; ++v)
+        hraw[v] = p.Hb[(static_cast<int64_t>(blockIdx.y) * kMaxM + min(m0 + v, p.M - 1)) * p.hid + h];
 
     // ---- a. logits and softmax
     {
@@ -337,66 +337,46 @@ __global__ __launch_bounds__(kBwdT) void mlp_backward_small_kernel(const MlpPara
     }
     __syncthreads();
 
-    // ---- b. this thread's hidden unit and rows
+    // ---- b. dH and this sample tile's share of dW2
     float* __restrict__ g = p.slots + static_cast<int64_t>(op.slot) * p.ld;
     float* __restrict__ gb1 = g + static_cast<int64_t>(p.in) * p.hid;
     float* __restrict__ gW2 = gb1 + p.hid;
     float* __restrict__ gb2 = gW2 + static_cast<int64_t>(p.hid) * p.out;
-    float w2[kMaxOut], gw2[kMaxOut];
+    {
+        const v4f dl = *reinterpret_cast<const v4f*>(&dl_s[16 * mt + lrow][4 * lgrp]);     // zero beyond M and out
+        v4f back = {0, 0, 0, 0}, share = {0, 0, 0, 0};      // entries o >= out are zero in dl and w2
 #pragma unroll
-    for (int q = 0; q < kMaxOut / 4; ++q) {
-        w2[4 * q] = w2q[q].x; w2[4 * q + 1] = w2q[q].y; w2[4 * q + 2] = w2q[q].z; w2[4 * q + 3] = w2q[q].w;
-    }
+        for (int s = 0; s < 4; ++s) back = __builtin_amdgcn_mfma_f32_16x16x4f32(dl[s], w2[s], back, 0, 0, 0);
+        float sum_dh = 0.0f;
 #pragma unroll
-    for (int o = 0; o < kMaxOut; ++o) gw2[o] = 0.0f;
-    float sum_dh = 0.0f;
-#pragma unroll
-    for (int r = 0; r < kBwdRows; ++r) {
-        const int m = kBwdRows * mg + r;
-        float dl[kMaxOut];
-#pragma unroll
-        for (int q = 0; q < kMaxOut / 4; ++q) {
-            const v4f t4 = *reinterpret_cast<const v4f*>(&dl_s[m][4 * q]);
-            dl[4 * q] = t4.x; dl[4 * q + 1] = t4.y; dl[4 * q + 2] = t4.z; dl[4 * q + 3] = t4.w;
+        for (int v = 0; v < 4; ++v) {
+            const int m = m0 + v;
+            const float hv = m < p.M ? bf16_to_float(hraw[v]) : 0.0f;
+            share = __builtin_amdgcn_mfma_f32_16x16x4f32(hv, dl_s[m][lrow], share, 0, 0, 0);
+            const uint16_t dh = hv > 0.0f ? bf16_rne(back[v] * p.gscale) : static_cast<uint16_t>(0);
+            sum_dh += bf16_to_float(dh);
+            dH[static_cast<int64_t>(m) * p.hid + h] = dh;    // rows m >= M are the zero padding of the dW1 product
         }
-        const float hv = bf16_to_float(hraw[r]);       // zero for rows m >= M, whose dl is zero as well
-        float back = 0.0f;
+        sum_dh += __shfl_xor(sum_dh, 16, 64);
+        sum_dh += __shfl_xor(sum_dh, 32, 64);
+        if (lgrp == 0) red1[mt][hl] = sum_dh;
 #pragma unroll
-        for (int o = 0; o < kMaxOut; ++o) {             // entries o >= out are zero in dl_s and w2
-            gw2[o] += hv * dl[o];
-            back += dl[o] * w2[o];
-        }
-        const uint16_t dh = (m < p.M && hv > 0.0f) ? bf16_rne(back * p.gscale) : static_cast<uint16_t>(0);
-        sum_dh += bf16_to_float(dh);
-        dH[static_cast<int64_t>(m) * p.hid + h] = dh;    // rows m >= M are the zero padding of the dW1 product
+        for (int v = 0; v < 4; ++v) red[mt][16 * ht + 4 * lgrp + v][lrow] = share[v];
     }
+    __syncthreads();
 
-    // ---- c. fixed pairwise tree over the 16 row groups: (g, g + 8), then (g, g + 4), (g, g + 2), (g, g + 1)
-#pragma unroll
-    for (int half = kBwdGroups / 2; half > 0; half >>= 1) {
-        if (mg >= half && mg < 2 * half) {
-#pragma unroll
-            for (int o = 0; o < kMaxOut; ++o) red[mg - half][o][hl] = gw2[o];
-            red[mg - half][kMaxOut][hl] = sum_dh;
-        }
-        __syncthreads();
-        if (mg < half) {
-#pragma unroll
-            for (int o = 0; o < kMaxOut; ++o) gw2[o] += red[mg][o][hl];
-            sum_dh += red[mg][kMaxOut][hl];
-        }
-        __syncthreads();
+    // ---- c. the four sample tiles in order
+    {
+        const int hh = threadIdx.x >> 4, o = threadIdx.x & 15;       // 1024 = 64 hidden units x 16 outputs
+        const float sum = ((red[0][hh][o] + red[1][hh][o]) + red[2][hh][o]) + red[3][hh][o];
+        if (o < p.out) gW2[static_cast<int64_t>(blockIdx.x * 64 + hh) * p.out + o] = sum * p.gscale;
+        if (threadIdx.x < 64)
+            gb1[blockIdx.x * 64 + threadIdx.x] = ((red1[0][threadIdx.x] + red1[1][threadIdx.x]) + red1[2][threadIdx.x]) + red1[3][threadIdx.x];
     }
-    if (mg == 0) {
-#pragma unroll
-        for (int o = 0; o < kMaxOut; ++o)
-            if (o < p.out) gW2[static_cast<int64_t>(h) * p.out + o] = gw2[o] * p.gscale;
-        gb1[h] = sum_dh;
-    }
-    if (blockIdx.x == 0 && mg == 1 && hl < p.out) {
+    if (blockIdx.x == 0 && wave == 1 && lane < p.out) {
         float sdl = 0.0f;
-        for (int m = 0; m < p.M; ++m) sdl += dl_s[m][hl];
-        gb2[hl] = sdl * p.gscale;
+        for (int m = 0; m < p.M; ++m) sdl += dl_s[m][lane];
+        gb2[lane] = sdl * p.gscale;
     }
     if (blockIdx.x == 0 && threadIdx.x == 128 && p.loss) {
         float sl = 0.0f;
