@@ -302,7 +302,19 @@ def main():
     prof.destroy()
 
     events_per_launch = ps["events"] / ps["fused_launches"]
-    if synth:
+    in_columns = synth and n <= (160 if eng.V is not None else 320)   # all events of a call in one launch, X crosses HBM once
+    if in_columns:
+        # bound by the generator's arithmetic: a quad of normals takes a SIMD 411 cycles per 64 lanes (csrc/device_common.hpp);
+        # 1024 SIMDs at 2.4 GHz
+        launch_s = ps["fused_ms"] * 1e-3 / n_prof
+        per_call = ps["events"] / n_prof
+        peak = 1024 * 2.4e9 / 411 * 64 * 4 / 1e9
+        achieved = per_call * d / launch_s / 1e9
+        roof = {"bound": "valu", "achieved": achieved, "peak": peak, "unit": "1e9 normals/s", "frac": achieved / peak,
+                "traffic": None, "traffic_source": None, "kernel": "column_events_kernel", "avg_launch_ms": launch_s * 1e3,
+                "events_per_launch": per_call, "hbm_GBs": (16.0 if eng.V is not None else 8.0) * n * d / launch_s / 1e9,
+                "hbm_GBs_if_streamed": (24.0 if eng.V is not None else 16.0) * d * per_call / launch_s / 1e9}
+    elif synth:
         bytes_per_event = (24.0 if eng.V is not None else 16.0) * d   # read x_i, x_j; write x_i, x_j (+ v_i read and written)
         avg_launch_s = ps["fused_ms"] * 1e-3 / ps["fused_launches"]
         achieved = bytes_per_event * events_per_launch / avg_launch_s / 1e9
@@ -357,7 +369,8 @@ def main():
         out["config"]["gradient"] = "N(0,1e-3) Philox4x32-10 + Box-Muller, generated in registers"
         if eng.V is not None:
             out["config"]["optimizer"] = {"momentum": args.momentum, "weight_decay": args.weight_decay}
-            out["roofline"]["kernel"] = "fused_gossip_apply_kernel<synth, momentum>"
+            if not in_columns:
+                out["roofline"]["kernel"] = "fused_gossip_apply_kernel<synth, momentum>"
     # diagnostics (outside the timed region): consensus distance and mean model each read X once.  The second of two
     # calls is timed (the first one allocates the library's small result buffers), the output vector allocated before;
     # HIP events on the library's stream bracket each call: for the consensus distance its kernels, its 8-byte copy and

@@ -768,17 +768,17 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
         HIP_TRY(h, hipMemsetAsync(h->exchange.p, 0, h->exchange.cap, h->stream));
         h->exchange_seq = 0;
     }
-    StripCall sc{c.K, c.A, c.s->worker, c.s->neighbour, c.s->gamma, h->o.gamma, c.s->extra_ptr, c.s->extra_a, c.s->extra_b,
-                 &c.plan, c.carried_slot.empty() ? nullptr : c.carried_slot.data(), h->data.data(), true,
+    // gradients ahead of the updates: as many as there is LDS for, 64 at most and T_max + 1 at least
+    const int64_t fixed = static_cast<int64_t>(strip_lds_bytes(M, n, mom, 0, true));
+    const int64_t slots_fit = (kStripLdsBytes - fixed) / (kStripCols * static_cast<int64_t>(sizeof(float)));
+    const bool lds_state = slots_fit >= static_cast<int64_t>(h->o.T_max) + 1;
+    const int32_t window = static_cast<int32_t>(std::max<int64_t>(h->o.T_max + 1, std::min<int64_t>(64, lds_state ? slots_fit : h->n_slots)));
+    StripCall sc{n, h->n_slots, window, c.K, c.A, c.s->worker, c.s->neighbour, c.s->tau, c.s->gamma, h->o.gamma, c.s->extra_ptr, c.s->extra_a, c.s->extra_b,
+                 &c.plan, c.carried_slot.empty() ? nullptr : c.carried_slot.data(), h->data.data(), lds_state,
                  h->exchange_seq + 1, strip_blocks(h->d)};
     const int32_t teams = strip_teams(M);
     StripProgram prog;
-    build_strips(sc, teams, prog);
-    const bool lds_state = strip_lds_bytes(M, n, mom, prog.n_slots, true) <= static_cast<size_t>(kStripLdsBytes);
-    if (!lds_state) {
-        sc.renumber = false;
-        build_strips(sc, teams, prog);
-    }
+    if (!build_strips(sc, teams, prog)) return ADPSGD_OK;
     // slots that cross the ends of the call: (slot of the call, slot of the workspace)
     std::vector<int32_t> carry;
     int32_t n_in = 0, n_out = 0;
@@ -850,6 +850,9 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
         return ADPSGD_OK;
     }
     launched = true;
+    if (!lds_state)
+        for (int64_t k = c.A; k < c.K; ++k)
+            if (prog.slot[k] >= 0) c.plan.slot[k] = prog.slot[k];
     h->exchange_seq += static_cast<uint32_t>(prog.order.size());
     rc = end_timing(h, e0, e1, h->ev_fused);
     if (rc != ADPSGD_OK) return rc;

@@ -1,7 +1,9 @@
-// Layout of a call of a linear model as one persistent launch: the rounds of the plan, cut into iterations of the
-// kernel (kernels_strips.hip).
+// Layout of a call of a linear model as one persistent launch: its events in the order of their dependences, cut into
+// iterations of the kernel (kernels_strips.hip).
 #include <algorithm>
 #include <cstring>
+#include <functional>
+#include <queue>
 #include <utility>
 
 #include "strips.hpp"
@@ -19,16 +21,13 @@ uint32_t bits(float f) {
 struct Builder {
     const StripCall& c;
     StripProgram& out;
-    const int32_t T;
-    int32_t max_updates = 0;
     std::vector<int32_t> free_slots;
-
-    Builder(const StripCall& call, int32_t teams, StripProgram& program) : c(call), out(program), T(teams), P(teams / 2) {}
-
     const int32_t P;              // evaluations and loads of a record, at most
     std::vector<int32_t> free_teams;
     int64_t loaded = 0;           // gradients whose rows have been requested, in the order of evaluation
     std::vector<int32_t> team_of;
+
+    Builder(const StripCall& call, int32_t teams, StripProgram& program) : c(call), out(program), P(teams / 2) {}
 
     // a new record; the teams that the previous one has left idle request the rows of the next gradients
     StripEntry* open() {
@@ -56,136 +55,220 @@ struct Builder {
         free_slots.pop_back();
         return s;
     }
-    void update(StripEntry* rec, int32_t i, int32_t j, int32_t slot, float gamma, bool average_only) {
-        rec[1 + 4 * P + rec[0].x++] = StripEntry{static_cast<uint32_t>(i) | static_cast<uint32_t>(j) << 16,
-                                                 static_cast<uint32_t>(slot), bits(gamma), average_only ? 1u : 0u};
-    }
 };
 
 }  // namespace
 
-// Iteration order.  The gradients of a round come first, one for half of the teams at a time; the updates of the
-// round open the next iteration.  Minibatch rows are requested in the order of evaluation, each set by a team whose
-// last gradient was finished in the iteration before, so a team's next rows are in flight while the others work.
-void build_strips(const StripCall& c, int32_t teams, StripProgram& out) {
+namespace {
+
+// What the schedule of a call depends on, per event and per row.
+struct Order {
+    std::vector<std::vector<int32_t>> updates;     // per row: the events that update it, in order ...
+    std::vector<int32_t> next;                     // ... and the first one not applied yet
+    std::vector<std::vector<std::pair<int32_t, int32_t>>> reads;    // per row: (updates before the read, event), sorted ...
+    std::vector<int32_t> ready;                    // ... reads whose row has reached their version
+    std::vector<int32_t> done;                     // ... reads evaluated
+};
+
+}  // namespace
+
+// Iteration order.  An update is applied when its gradient is there, the earlier updates of its rows are applied and
+// the reads that precede it are evaluated; an iteration applies all that can be (in waves of pairwise different rows,
+// each filled up to whole batches of the kernel) and then evaluates the gradients that are ready, the oldest events
+// first, one for half of the teams at most.  So an iteration is spent per link of a chain of gradients, not per round.
+// Gradients run at most `window` events ahead of the first event not applied: that bounds the slots, and as no read is
+// further than T_max events ahead of an update that waits for it, window > T_max cannot block.
+// Minibatch rows are requested in the order of evaluation, each set by a team whose last gradient was finished in the
+// iteration before, so a team's next rows are in flight while the others work.
+bool build_strips(const StripCall& c, int32_t teams, StripProgram& out) {
     const Plan& plan = *c.plan;
-    const int32_t R = plan.n_rounds;
     out = StripProgram{};
     out.teams = teams;
     out.slot.assign(static_cast<size_t>(c.K), -1);
+    auto carried = [&](int64_t k) { return c.carried_slot && c.carried_slot[k] >= 0; };
+    auto rows_of = [&](int64_t k, auto&& f) {
+        f(c.worker[k]);
+        if (c.neighbour[k] != c.worker[k]) f(c.neighbour[k]);
+        if (c.extra_ptr)
+            for (int64_t q = c.extra_ptr[k]; q < c.extra_ptr[k + 1]; ++q) {
+                f(c.extra_a[q]);
+                f(c.extra_b[q]);
+            }
+    };
 
-    // events by round (counting sort): evaluations and updates
-    std::vector<int64_t> r_off(static_cast<size_t>(R) + 1, 0), u_off(static_cast<size_t>(R) + 1, 0);
-    std::vector<int64_t> u_ops(static_cast<size_t>(R), 0);
+    Order o;
+    o.updates.resize(c.n);
+    o.reads.resize(c.n);
+    o.next.assign(c.n, 0);
+    o.ready.assign(c.n, 0);
+    o.done.assign(c.n, 0);
+    for (int64_t k = 0; k < c.A; ++k) rows_of(k, [&](int32_t r) { o.updates[r].push_back(static_cast<int32_t>(k)); });
+    int64_t reads_left = 0;
     for (int64_t k = 0; k < c.K; ++k) {
-        if (plan.r_round[k] >= 0) ++r_off[plan.r_round[k] + 1];
-        if (k < c.A) {
-            ++u_off[plan.u_round[k] + 1];
-            u_ops[plan.u_round[k]] += 1 + (c.extra_ptr ? c.extra_ptr[k + 1] - c.extra_ptr[k] : 0);
-        }
+        if (plan.r_round[k] < 0) continue;                     // carried, or left to the next call
+        const auto& u = o.updates[c.worker[k]];
+        const int64_t before = k - c.tau[k];
+        o.reads[c.worker[k]].push_back({static_cast<int32_t>(std::lower_bound(u.begin(), u.end(), before) - u.begin()), static_cast<int32_t>(k)});
+        ++reads_left;
     }
-    int64_t widest = 1;
-    for (int32_t r = 0; r < R; ++r) {
-        widest = std::max(widest, u_ops[r]);
-        r_off[r + 1] += r_off[r];
-        u_off[r + 1] += u_off[r];
-    }
-    out.order.resize(static_cast<size_t>(r_off[R]));
-    std::vector<int64_t> updates(static_cast<size_t>(u_off[R]));
-    {
-        std::vector<int64_t> ra(r_off.begin(), r_off.end() - 1), ua(u_off.begin(), u_off.end() - 1);
-        for (int64_t k = 0; k < c.K; ++k) {
-            if (plan.r_round[k] >= 0) out.order[ra[plan.r_round[k]]++] = k;
-            if (k < c.A) updates[ua[plan.u_round[k]]++] = k;
-        }
-    }
+    for (auto& r : o.reads) std::sort(r.begin(), r.end());
 
     Builder b(c, teams, out);
-    const int64_t room = kStripMaxRec - 1 - 4 * (teams / 2);
-    b.max_updates = static_cast<int32_t>(std::min(widest, room));
-    out.rec_len = 1 + 4 * (teams / 2) + b.max_updates;
-    out.recs.reserve(static_cast<size_t>(2 * out.order.size() / teams + 2 * R + 8) * out.rec_len);
-
+    const int32_t room = (kStripMaxRec - 1 - 4 * b.P) / kStripBatch * kStripBatch;
     if (c.renumber) {
-        if (c.carried_slot)
-            for (int64_t k = 0; k < c.K; ++k)
-                if (c.carried_slot[k] >= 0) out.slot[k] = b.take_slot();
+        for (int64_t k = 0; k < c.K; ++k)
+            if (carried(k)) out.slot[k] = b.take_slot();
     } else {
-        for (int64_t k = 0; k < c.K; ++k) out.slot[k] = plan.slot[k];
+        std::vector<char> taken(static_cast<size_t>(c.n_slots), 0);
+        for (int64_t k = 0; k < c.K; ++k)
+            if (carried(k)) {
+                out.slot[k] = c.carried_slot[k];
+                taken[c.carried_slot[k]] = 1;
+            }
+        for (int32_t s = c.n_slots - 1; s >= 0; --s)
+            if (!taken[s]) b.free_slots.push_back(s);
     }
 
+    // first pass: what every iteration applies and evaluates
+    struct Step {
+        size_t updates, order;        // where its updates and its evaluations begin
+    };
+    std::vector<Step> steps;
+    std::vector<StripEntry> ops;
+    steps.reserve(static_cast<size_t>(c.K) + 2);
+    ops.reserve(static_cast<size_t>(2 * c.K) + 64);
+    out.order.reserve(static_cast<size_t>(c.K));
+    std::vector<int32_t> evaluated(static_cast<size_t>(c.K), -1);      // step of the evaluation
+    std::vector<char> applied(static_cast<size_t>(c.A), 0);
+    std::priority_queue<int32_t, std::vector<int32_t>, std::greater<int32_t>> ready;
+    std::vector<int32_t> candidates, again, wave, deferred;
+    int64_t first = 0;
+    auto open_reads = [&](int32_t r) {
+        for (auto& at = o.ready[r]; at < static_cast<int32_t>(o.reads[r].size()) && o.reads[r][at].first <= o.next[r]; ++at)
+            ready.push(o.reads[r][at].second);
+    };
+    // the first event of a row that is not applied yet, if its gradient is there (otherwise its evaluation brings it up)
+    auto consider = [&](int32_t r) {
+        if (o.next[r] >= static_cast<int32_t>(o.updates[r].size())) return;
+        const int32_t k = o.updates[r][o.next[r]];
+        if (evaluated[k] >= 0 || plan.r_round[k] < 0) candidates.push_back(k);
+    };
+    for (int32_t r = 0; r < c.n; ++r) {
+        open_reads(r);
+        consider(r);
+    }
+    while (first < c.A || reads_left > 0) {
+        const int32_t now = static_cast<int32_t>(steps.size());
+        const size_t ops0 = ops.size(), order0 = out.order.size();
+        steps.push_back(Step{ops0, order0});
+        auto applicable = [&](int32_t k) {
+            if (applied[k] || (plan.r_round[k] >= 0 ? evaluated[k] < 0 || evaluated[k] >= now : !carried(k))) return false;
+            bool ok = true;
+            rows_of(k, [&](int32_t r) {
+                const int32_t at = o.next[r];
+                ok = ok && at < static_cast<int32_t>(o.updates[r].size()) && o.updates[r][at] == k &&
+                     (o.done[r] == static_cast<int32_t>(o.reads[r].size()) || o.reads[r][o.done[r]].first > at);
+            });
+            return ok;
+        };
+        again.clear();
+        while (!candidates.empty()) {
+            if (candidates.size() > 1) {
+                std::sort(candidates.begin(), candidates.end());
+                candidates.erase(std::unique(candidates.begin(), candidates.end()), candidates.end());
+            }
+            wave.clear();
+            for (const int32_t k : candidates)
+                if (applicable(k)) wave.push_back(k);
+            candidates.clear();
+            if (wave.empty()) break;
+            while ((ops.size() - ops0) % kStripBatch != 0) ops.push_back(StripEntry{0, 0, 0, kStripEmpty});
+            for (const int32_t k : wave) {
+                const int32_t pairs = 1 + static_cast<int32_t>(c.extra_ptr ? c.extra_ptr[k + 1] - c.extra_ptr[k] : 0);
+                if (static_cast<int32_t>(ops.size() - ops0) + pairs > room && ops.size() > ops0) {
+                    again.push_back(k);          // the record is full
+                    continue;
+                }
+                auto put = [&](int32_t i, int32_t j, int32_t slot, float gamma, uint32_t flags) {
+                    ops.push_back(StripEntry{static_cast<uint32_t>(i) | static_cast<uint32_t>(j) << 16, static_cast<uint32_t>(slot), bits(gamma), flags});
+                };
+                put(c.worker[k], c.neighbour[k], out.slot[k], c.gamma ? c.gamma[k] : c.gamma_default, 0);
+                if (c.extra_ptr)
+                    for (int64_t q = c.extra_ptr[k]; q < c.extra_ptr[k + 1]; ++q) put(c.extra_a[q], c.extra_b[q], 0, 0.0f, kStripAverage);
+                b.free_slots.push_back(out.slot[k]);
+                applied[k] = 1;
+                rows_of(k, [&](int32_t r) {
+                    ++o.next[r];
+                    consider(r);
+                    open_reads(r);
+                });
+            }
+        }
+        while (first < c.A && applied[first]) ++first;
+        candidates = again;
+        deferred.clear();
+        while (!ready.empty() && out.order.size() < order0 + b.P) {
+            const int32_t k = ready.top();
+            ready.pop();
+            const int64_t kp = plan.prev[k];
+            if (k >= first + c.window || (kp >= 0 && !carried(kp) && (evaluated[kp] < 0 || evaluated[kp] >= now))) {
+                deferred.push_back(k);
+                continue;
+            }
+            evaluated[k] = now;
+            out.slot[k] = b.take_slot();
+            out.order.push_back(k);
+            const int32_t r = c.worker[k];
+            ++o.done[r];
+            --reads_left;
+            consider(r);                  // the read was what its next update waited for, or that update is event k
+        }
+        for (const int32_t k : deferred) ready.push(k);
+        if (ops.size() == ops0 && out.order.size() == order0) return false;      // cannot happen with a valid plan
+    }
+
+    // second pass: the records, with the loads
+    size_t widest = 1;
+    steps.push_back(Step{ops.size(), out.order.size()});
+    for (size_t i = 0; i + 1 < steps.size(); ++i) widest = std::max(widest, steps[i + 1].updates - steps[i].updates);
+    const int32_t width = std::min<int32_t>(room, static_cast<int32_t>((widest + kStripBatch - 1) / kStripBatch) * kStripBatch);
+    out.rec_len = 1 + 4 * b.P + width;
+    out.n_slots = std::max(out.n_slots, 1);
+    out.recs.reserve((steps.size() + ops.size() / width + 6) * out.rec_len);
     b.team_of.assign(out.order.size(), -1);
     for (int32_t t = 0; t < teams; ++t) b.free_teams.push_back(t);
     b.open();
     std::vector<std::pair<int32_t, int64_t>> evals;      // (team, position) of a record
-
-    int64_t pending = 0, pending_end = 0;       // range of `updates` not laid out yet, of one round
-    int64_t extra_at = 0;                       // next extra pair of updates[pending], 0: its own pair
-    // as many of the pending updates as the record holds; they touch pairwise different rows
-    auto put_updates = [&](StripEntry* rec) {
-        while (pending < pending_end) {
-            const int64_t k = updates[pending];
-            const int64_t n_extra = c.extra_ptr ? c.extra_ptr[k + 1] - c.extra_ptr[k] : 0;
-            for (; extra_at <= n_extra; ++extra_at) {
-                if (static_cast<int32_t>(rec[0].x) >= b.max_updates) return;
-                if (extra_at == 0) {
-                    b.update(rec, c.worker[k], c.neighbour[k], out.slot[k], c.gamma ? c.gamma[k] : c.gamma_default, false);
-                    if (c.renumber) b.free_slots.push_back(out.slot[k]);
-                } else {
-                    const int64_t q = c.extra_ptr[k] + extra_at - 1;
-                    b.update(rec, c.extra_a[q], c.extra_b[q], 0, 0.0f, true);
-                }
-            }
-            extra_at = 0;
-            ++pending;
+    for (size_t i = 0; i + 1 < steps.size(); ++i) {
+        StripEntry* rec = b.open();
+        const size_t count = steps[i + 1].updates - steps[i].updates;
+        for (size_t from = 0; from < count; from += width) {
+            if (from > 0) rec = b.open();                // an event with more pairs than a record holds
+            const size_t n = std::min<size_t>(width, count - from);
+            std::copy_n(ops.begin() + steps[i].updates + from, n, rec + 1 + 4 * b.P);
+            rec[0].x = static_cast<uint32_t>(n);
         }
-    };
-    auto flush_updates = [&] {
-        while (pending < pending_end) put_updates(b.open());
-    };
-    for (int32_t r = 0; r < R; ++r) {
-        for (int64_t q = r_off[r]; q < r_off[r + 1];) {
-            const int64_t room_left = b.max_updates;
-            // the last record of the pending updates also carries gradients
-            while (pending < pending_end) {
-                int64_t ops = 0;
-                for (int64_t u = pending; u < pending_end && ops <= room_left; ++u)
-                    ops += 1 + (c.extra_ptr ? c.extra_ptr[updates[u] + 1] - c.extra_ptr[updates[u]] : 0);
-                ops -= extra_at;
-                if (ops <= room_left) break;
-                put_updates(b.open());
+        evals.clear();
+        for (size_t q = steps[i].order; q < steps[i + 1].order; ++q) evals.push_back({b.team_of[q], static_cast<int64_t>(q)});
+        std::sort(evals.begin(), evals.end());
+        StripEntry* e = rec + 1;
+        for (const auto& [team, at] : evals) {
+            const int64_t k = out.order[at], kp = plan.prev[k];
+            e[0] = StripEntry{static_cast<uint32_t>(team), c.seq0 + static_cast<uint32_t>(at), static_cast<uint32_t>(c.worker[k]),
+                              static_cast<uint32_t>(out.slot[k])};
+            e[1] = StripEntry{0xFFFFFFFFu, 0, static_cast<uint32_t>(k), static_cast<uint32_t>(at % c.strips)};
+            if (kp >= 0) {
+                e[1].x = static_cast<uint32_t>(out.slot[kp]);
+                e[1].y = bits(c.gamma ? c.gamma[kp] : c.gamma_default);
             }
-            const int64_t ready = b.loaded;        // requested by an earlier record
-            StripEntry* rec = b.open();
-            put_updates(rec);
-            const int64_t end = std::min(std::min(q + b.P, r_off[r + 1]), ready);
-            evals.clear();
-            for (; q < end; ++q) evals.push_back({b.team_of[q], q});
-            std::sort(evals.begin(), evals.end());
-            StripEntry* e = rec + 1;
-            for (const auto& [team, at] : evals) {
-                const int64_t k = out.order[at], kp = plan.prev[k];
-                if (c.renumber) out.slot[k] = b.take_slot();
-                e[0] = StripEntry{static_cast<uint32_t>(team), c.seq0 + static_cast<uint32_t>(at), static_cast<uint32_t>(c.worker[k]),
-                                  static_cast<uint32_t>(out.slot[k])};
-                e[1] = StripEntry{0xFFFFFFFFu, 0, static_cast<uint32_t>(k), static_cast<uint32_t>(at % c.strips)};
-                if (kp >= 0) {
-                    e[1].x = static_cast<uint32_t>(out.slot[kp]);
-                    e[1].y = bits(c.gamma ? c.gamma[kp] : c.gamma_default);
-                }
-                rec[0].z |= 1u << team;
-                b.free_teams.push_back(team);
-                e += 2;
-            }
+            rec[0].z |= 1u << team;
+            b.free_teams.push_back(team);
+            e += 2;
         }
-        flush_updates();       // left over where the round evaluates no gradient
-        pending = u_off[r];
-        pending_end = u_off[r + 1];
-        extra_at = 0;
     }
-    flush_updates();
     b.open();                  // finishes the gradients of the last record
     out.recs.resize(out.recs.size() + 3 * static_cast<size_t>(out.rec_len), StripEntry{0, 0, 0, 0});
+    return true;
 }
 
 }  // namespace adpsgd_impl

@@ -25,7 +25,9 @@ constexpr int kStripLdsBytes = 160 * 1024;
 //                     slot of the pending gradient that compensates the read (or -1), its step size, the event, the
 //                     strip that writes its loss
 //   load              position in the index table, row pitch of the features, features (64 bits);  targets (64 bits), -, -
-//   update            row i | row j << 16, slot, step size, flags (bit 0: averaging only)
+//   update            row i | row j << 16, slot, step size, flags; within a batch of kStripBatch all rows are different
+constexpr int kStripBatch = 4;
+constexpr uint32_t kStripAverage = 1, kStripEmpty = 2;      // flags of an update: averaging only; no update
 struct alignas(16) StripEntry {
     uint32_t x, y, z, w;
 };
@@ -40,8 +42,10 @@ struct StripProgram {
 };
 
 struct StripCall {
+    int32_t n, n_slots;    // workers, slots of the workspace
+    int32_t window;        // gradients at most this many events ahead of the first one not applied, > T_max
     int64_t K, A;          // events in the arrays, events applied
-    const int32_t *worker, *neighbour;
+    const int32_t *worker, *neighbour, *tau;
     const float* gamma;                  // per event or nullptr
     float gamma_default;
     const int64_t* extra_ptr;
@@ -56,7 +60,8 @@ struct StripCall {
 // Teams of wavefronts (gradients whose rows are held) for a minibatch of M samples: as many as their rows leave
 // registers for (at most 22 rows of a wavefront).
 inline int32_t strip_teams(int32_t M) { return M <= 16 ? 12 : M <= 32 ? 6 : M <= 64 ? 4 : 2; }
-void build_strips(const StripCall& c, int32_t teams, StripProgram& out);
+// false: the events do not come in any order (the plan is not one of this schedule)
+bool build_strips(const StripCall& c, int32_t teams, StripProgram& out);
 
 struct StripArgs {
     float* X;
