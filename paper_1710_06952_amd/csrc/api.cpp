@@ -348,17 +348,18 @@ struct EventCall {
 // Whether the calls of this handle take the one-launch path of the linear models (kernels_strips.hip).  Decided by the
 // handle alone, so that a schedule gives the same bits however it is cut into calls; only a stream under capture goes by
 // rounds (a captured call would need a cooperative launch in a graph).
-// Where the line lies: an iteration of the strip kernel holds the rows of a few gradients (teams / 2), and a round has
-// about n / 4 of them, so its time per round grows with n and with M, while the kernels of a round take more gradients
-// side by side.  Measured (least squares on a 4-regular graph, per 100 events, strips against rounds, us): n = 8, M = 12:
-// d = 300 142 / 318, 4096 157 / 878, 65 536 305 / 1160;  n = 16, M = 64: 292 / 306, 452 / 686, 708 / 1080;  n = 32,
-// M = 48: 215 / 200, 361 / 517, 574 / 745;  n = 64, M = 12: 82 / 72, 123 / 214, 199 / 300, M = 24: 136 / 81, 218 / 246,
-// 347 / 357, M = 48: 206 / 101, 350 / 266, 545 / 503.  So n M <= 1024, and half of it for many workers and short models.
+// Where the line lies: an iteration of the strip kernel evaluates a few gradients (teams / 2), so its time per event grows
+// with M and hardly falls with n, while the kernels of a round, of about n / 4 events, take its gradients side by side.
+// Measured (least squares on a 4-regular graph, us per 100 events, strips / rounds):  n = 8, M = 12: d = 300 110 / 318,
+// 4096 122 / 878, 20 000 159 / 1008;  n = 16, M = 64: 229 / 306, 295 / 686, 479 / 916;  n = 32, M = 48: 188 / 200, 270 / 517,
+// 361 / 596;  n = 64, M = 12: 82 / 72, 101 / 214, 123 / 259, M = 24: 132 / 81, 176 / 246, 217 / 278, M = 48: 186 / 101,
+// 275 / 266, 354 / 318.  So n M <= 1600, where the rounds have a gradient in one launch (d <= 2048) 1024, and half of
+// that for many workers and the shortest models.
 bool can_run_strips(const adpsgd_t* h, int32_t& compute_units) {
     const int32_t model = h->o.model;
     const int64_t width = static_cast<int64_t>(h->n) * h->o.M;
-    if ((model != ADPSGD_MODEL_LSQ && model != ADPSGD_MODEL_LOGREG) || h->d > kStripMaxD || h->o.M > kStripMaxM || width > 1024 ||
-        (h->n > 32 && h->d <= 1024 && width > 512))
+    if ((model != ADPSGD_MODEL_LSQ && model != ADPSGD_MODEL_LOGREG) || h->d > kStripMaxD || h->o.M > kStripMaxM ||
+        width > (h->d > 2048 ? 1600 : 1024) || (h->n > 32 && h->d <= 1024 && width > 512))
         return false;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess) {

@@ -7,11 +7,11 @@
 // M dot products a_m . x^ of every gradient; models, momentum buffers and pending gradients of a strip stay in LDS,
 // minibatch rows are read once, into registers, ahead of the events that need them (the schedule names them), and are
 // still there when the coefficients arrive.
-// Measured, a call against the same call in rounds: n = 8, d = 1024, M = 32, 200 events 0.32 against 0.77 ms;  n = 16,
-// d = 4096, M = 8, 1280 events 1.25 against 7.2 ms;  n = 16, d = 20 001, M = 50, wait-free with momentum, 400 events 1.89
-// against 4.1 ms.  What binds now is the chain of an iteration, 3.4 us for the second of these: updates and x^ 0.6, dot
-// products 0.15, exchange and coefficients 1.9, combination 0.3, barriers and records the rest; with many rows per
-// gradient (the third, 7.8 us) also their address translation, about 40 cycles per row and compute unit.
+// Measured, a call against the same call in rounds: n = 8, d = 1024, M = 32, 200 events 0.27 against 0.78 ms;  n = 16,
+// d = 4096, M = 8, 1280 events 1.08 against 7.2 ms;  n = 16, d = 20 001, M = 50, wait-free with momentum, 400 events 1.72
+// against 4.1 ms.  What binds now is the chain of an iteration, 4.7 us with 5.8 gradients for the second of these: updates
+// and x^ 1, dot products 0.2, exchange and coefficients 2.2, combination 0.3, barriers and records the rest; with many rows
+// per gradient (the third, 7.8 us) also their address translation, about 40 cycles per row and compute unit.
 //
 // A block has 12 main wavefronts in `teams` teams, each team with the rows of one gradient in its registers, and 4
 // helper wavefronts (one thread per column, and one per minibatch sample).  An iteration has three phases:

@@ -28,7 +28,7 @@ def rel_err(x, ref):
 
 # d around the float4, the strip of 256 columns, 32 strips (one group of blocks, then several) and the largest, 65 536;
 # M around the numbers of teams and rows (8, 16, 32, 48, 64, 96, 128) and n up to where the strips' state leaves LDS
-# (170 workers) and n M = 1024, the last that go this way; then the first sizes that go by rounds
+# (170 workers) and n M = 1024 and 1600, the last that go this way; then the first sizes that go by rounds
 @pytest.mark.parametrize("model,n,d,M,K,T,mu,comp", [
     ("lsq", 2, 1, 1, 40, 3, 0.0, False), ("logreg", 5, 3, 2, 60, 4, 0.9, False), ("lsq", 6, 255, 8, 80, 4, 0.9, False),
     ("logreg", 6, 256, 9, 80, 5, 0.0, True), ("lsq", 8, 257, 16, 120, 6, 0.0, False), ("logreg", 7, 1030, 17, 100, 4, 0.9, True),
@@ -36,7 +36,7 @@ def rel_err(x, ref):
     ("logreg", 6, 8193, 49, 60, 4, 0.0, True), ("lsq", 5, 16_385, 64, 50, 3, 0.0, False), ("logreg", 5, 9001, 65, 50, 3, 0.9, False),
     ("lsq", 4, 4100, 96, 50, 2, 0.0, False), ("logreg", 4, 8705, 97, 40, 3, 0.0, False), ("lsq", 8, 3003, 128, 40, 3, 0.0, True),
     ("logreg", 4, 65_535, 12, 40, 6, 0.9, False), ("lsq", 3, 65_536, 24, 30, 0, 0.0, False),
-    ("lsq", 170, 1101, 6, 500, 6, 0.0, False), ("logreg", 90, 1101, 8, 300, 4, 0.9, True), ("lsq", 64, 8200, 16, 250, 30, 0.0, False),
+    ("lsq", 50, 2100, 32, 200, 4, 0.0, False), ("lsq", 170, 1101, 6, 500, 6, 0.0, False), ("logreg", 90, 1101, 8, 300, 4, 0.9, True), ("lsq", 64, 8200, 16, 250, 30, 0.0, False),
     ("lsq", 4, 65_537, 8, 30, 3, 0.0, False), ("lsq", 5, 1500, 129, 30, 3, 0.0, False), ("logreg", 40, 300, 14, 150, 4, 0.0, False)])
 def test_events_in_one_launch_against_the_oracle(P, model, n, d, M, K, T, mu, comp):
     print("strips %s n=%d d=%d M=%d mu=%g comp=%d" % (model, n, d, M, mu, comp), flush=True)
