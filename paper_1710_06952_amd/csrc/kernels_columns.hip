@@ -15,7 +15,8 @@
 // computed once per wavefront, the event's part once on the host (ColumnOp).  Measured at n = 128, d = 25.6 M on the
 // ring, 2000 events per call: 39.2 ms (19.6 us per event, of which X in and out are 2.2) against 128.8 ms in rounds of
 // the streaming kernel; an operation costs a SIMD 420 cycles per 64 quads, about what the generator alone takes.
-// n = 32, d = 3.0 M with momentum, 500 events: 1.81 against 6.18 ms.
+// n = 32, d = 3.0 M with momentum, 500 events: 1.62 against 6.18 ms; n = 128, d = 25.6 M with momentum, where the velocities
+// halve the wavefronts that fit a compute unit, 26.7 us per event against about 100.
 #include <algorithm>
 
 #include "device_common.hpp"
