@@ -137,6 +137,8 @@ __global__ __launch_bounds__(256) void column_events_kernel(const ColumnParams p
     }
 }
 
+// Four wavefronts to a block, one to each SIMD, as far as 64 KB of LDS go.  Measured with 4 / 3 / 2 / 1 at n = 128, d = 25.6 M,
+// 10 000 events: 182.6 / 191.4 / 194.1 / 191.4 ms, with momentum 266 / 277 / 305 / 271.
 template <int kQuads>
 hipError_t launch_quads(const ColumnParams& p, hipStream_t st) {
     const int64_t strip = static_cast<int64_t>(p.n_rows) * kQuads * 16 * (p.V ? 2 : 1);
