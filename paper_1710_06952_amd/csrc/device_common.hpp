@@ -113,10 +113,9 @@ __device__ __forceinline__ v4f synth_normals4(uint32_t q_lo, uint32_t q_hi, uint
 }
 
 __device__ __forceinline__ uint16_t bf16_rne(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7FFFFFFFu) > 0x7F800000u) return static_cast<uint16_t>((u >> 16) | 0x0040u);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return static_cast<uint16_t>(u >> 16);
+    const uint32_t u = __float_as_uint(f), rounded = u + 0x7FFFu + ((u >> 16) & 1u);
+    const bool nan = (u & 0x7FFFFFFFu) > 0x7F800000u;
+    return static_cast<uint16_t>((nan ? u | 0x00400000u : rounded) >> 16);      // a select: no branch around three operations
 }
 __device__ __forceinline__ float bf16_to_float(uint16_t h) {
     return __uint_as_float(static_cast<uint32_t>(h) << 16);

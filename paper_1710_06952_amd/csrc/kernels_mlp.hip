@@ -271,19 +271,39 @@ __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
 //   a. thread (m, o) finishes logit o of sample m (sum of the hid / 32 forward-tile contributions
 //      in tile order); the 16 lanes of a sample take the softmax together (butterfly max and sum).
 //      The 16 blocks of a gradient repeat this small step rather than wait for a kernel of its own.
-//   b. wavefront (ht, mt): hidden units 16 ht .. + 15 of the block's 64 and samples 16 mt .. + 15.  Both products are
-//      contractions of 16 on the matrix cores in fp32 (16x16x4, four steps): the hidden error dH = dl W2^T (rounded to
-//      bf16) and the samples' share of dW2 = H^T dl.  A lane's entries of H (hidden unit l % 16, samples 4 (l / 16) ..
-//      + 3) are the places of its results of the first and its operands of the second.
-//   c. the four shares of dW2 and db1 are added in order through LDS, one thread per (h, o).
+//   b. wavefront (ht, mt): hidden units 16 ht .. + 15 of the block's 64 and the sample groups mt, mt + 4, mt + 8 and mt + 12
+//      of four samples each.  Both products are on the matrix cores in fp32 (16x16x4): the hidden error dH = dl W2^T
+//      (rounded to bf16), in four steps over the outputs in order, and dW2 = H^T dl, one step per sample group.
+//      A step adds its four products one after the other, so an entry has the bits of a chain of fused multiply-adds, and
+//      the sample groups are added as the fixed pairwise tree (g, g + 8), (g, g + 4), (g, g + 2), (g, g + 1): a hidden
+//      error next to a boundary of its bf16 rounding falls on the same side whichever unit forms the sums.
+//      Operands arrive by rows (a lane's four outputs, its four samples) and are transposed between the four groups of 16
+//      lanes in registers.
+//   c. the last two steps of the tree through LDS, one thread per (h, o).
 // (On the vector ALUs, with a tree of eight barriers over 16 row groups, this kernel took 8.8 us for the rounds of
 // 784-1024-10, M = 64, and 7.3 us for those of 64-256-10, M = 32; now 6.2 and 5.5.)
 constexpr int kBwdT = 1024;
 
+// r[v] of the lanes 16 g .. + 15  <->  r[g] of the lanes 16 v .. + 15
+__device__ __forceinline__ void transpose_groups(float (&r)[4]) {
+#pragma unroll
+    for (int v = 0; v < 2; ++v) {
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(r[v]), __float_as_uint(r[v + 2]), false, false);
+        r[v] = __uint_as_float(s[0]);
+        r[v + 2] = __uint_as_float(s[1]);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; v += 2) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(r[v]), __float_as_uint(r[v + 1]), false, false);
+        r[v] = __uint_as_float(s[0]);
+        r[v + 1] = __uint_as_float(s[1]);
+    }
+}
+
 __global__ __launch_bounds__(kBwdT) void mlp_backward_small_kernel(const MlpParams p) {
     __shared__ __attribute__((aligned(16))) float dl_s[kMaxM][kMaxOut];   // softmax - onehot, zero beyond M and out
     __shared__ float loss_s[kMaxM];
-    __shared__ float red[4][64][kMaxOut];           // shares of dW2, by sample tile
+    __shared__ float red[4][64][kMaxOut];           // shares of dW2, by mt
     __shared__ float red1[4][64];                   // shares of db1
     const GradOp op = p.ops[blockIdx.y];     // needed for the stores only: no load below waits for it
     uint16_t* __restrict__ dH = p.factored ? reinterpret_cast<uint16_t*>(p.slots + static_cast<int64_t>(op.slot) * p.ld)
@@ -291,7 +311,7 @@ __global__ __launch_bounds__(kBwdT) void mlp_backward_small_kernel(const MlpPara
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lrow = lane & 15, lgrp = lane >> 4;
     const int ht = wave & 3, mt = wave >> 2;
     const int hl = 16 * ht + lrow, h = blockIdx.x * 64 + hl;      // this lane's hidden unit ...
-    const int m0 = 16 * mt + 4 * lgrp;                            // ... and the first of its four samples
+    const int m0 = 16 * lgrp + 4 * mt;                            // ... and the first of its four samples
     const int sm = threadIdx.x >> 4, so = threadIdx.x & 15;       // step a: sample and logit
 
     // ---- all global loads (everything the forward kernel left in the scratch memory, addressed by block index)
@@ -304,7 +324,7 @@ __global__ __launch_bounds__(kBwdT) void mlp_backward_small_kernel(const MlpPara
     for (int t = 0; t < kTileBatch; ++t) part[t] = t < tiles ? src[static_cast<int64_t>(t) * kMaxM * kMaxOut] : 0.0f;
     const float b2v = p.b2f[static_cast<int64_t>(blockIdx.y) * kMaxOut + so];         // zero beyond `out`
     // outputs 4 lgrp .. + 3 of the hidden unit
-    const v4f w2 = *reinterpret_cast<const v4f*>(p.W2f + (static_cast<int64_t>(blockIdx.y) * p.hid + h) * kMaxOut + 4 * lgrp);
+    const v4f w2v = *reinterpret_cast<const v4f*>(p.W2f + (static_cast<int64_t>(blockIdx.y) * p.hid + h) * kMaxOut + 4 * lgrp);
     uint16_t hraw[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v)
@@ -335,43 +355,53 @@ __global__ __launch_bounds__(kBwdT) void mlp_backward_small_kernel(const MlpPara
         dl_s[sm][so] = (live && sm < p.M) ? ez / zsum - (so == label ? 1.0f : 0.0f) : 0.0f;
         if (so == 0) loss_s[sm] = sm < p.M ? -(lsel - zmax - logf(zsum)) : 0.0f;
     }
+    // operands of step b that do not come from this step, before the barrier
+    float w2[4] = {w2v.x, w2v.y, w2v.z, w2v.w}, hs[4], hv[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) hs[v] = hv[v] = m0 + v < p.M ? bf16_to_float(hraw[v]) : 0.0f;
+    transpose_groups(w2);         // w2[s]: output 4 s + lgrp
+    transpose_groups(hs);         // hs[q]: sample lgrp of group mt + 4 q
     __syncthreads();
 
-    // ---- b. dH and this sample tile's share of dW2
+    // ---- b. dH and this wavefront's share of dW2
     float* __restrict__ g = p.slots + static_cast<int64_t>(op.slot) * p.ld;
     float* __restrict__ gb1 = g + static_cast<int64_t>(p.in) * p.hid;
     float* __restrict__ gW2 = gb1 + p.hid;
     float* __restrict__ gb2 = gW2 + static_cast<int64_t>(p.hid) * p.out;
     {
-        const v4f dl = *reinterpret_cast<const v4f*>(&dl_s[16 * mt + lrow][4 * lgrp]);     // zero beyond M and out
-        v4f back = {0, 0, 0, 0}, share = {0, 0, 0, 0};      // entries o >= out are zero in dl and w2
+        // rows of the product of dH: sample 16 (i / 4) + 4 mt + i % 4 in row i, so a lane's results are its four samples
+        const v4f dl4 = *reinterpret_cast<const v4f*>(&dl_s[16 * (lrow >> 2) + 4 * mt + (lrow & 3)][4 * lgrp]);     // zero beyond M and out
+        float dl[4] = {dl4.x, dl4.y, dl4.z, dl4.w};
+        transpose_groups(dl);
+        v4f back = {0, 0, 0, 0};      // entries o >= out are zero in dl and w2
 #pragma unroll
         for (int s = 0; s < 4; ++s) back = __builtin_amdgcn_mfma_f32_16x16x4f32(dl[s], w2[s], back, 0, 0, 0);
+        v4f share[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            share[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(hs[q], dl_s[16 * q + 4 * mt + lgrp][lrow], v4f{0, 0, 0, 0}, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[mt][16 * ht + 4 * lgrp + v][lrow] = (share[0][v] + share[2][v]) + (share[1][v] + share[3][v]);
         float sum_dh = 0.0f;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int m = m0 + v;
-            const float hv = m < p.M ? bf16_to_float(hraw[v]) : 0.0f;
-            share = __builtin_amdgcn_mfma_f32_16x16x4f32(hv, dl_s[m][lrow], share, 0, 0, 0);
-            const uint16_t dh = hv > 0.0f ? bf16_rne(back[v] * p.gscale) : static_cast<uint16_t>(0);
+            const uint16_t rounded = bf16_rne(back[v] * p.gscale), dh = hv[v] > 0.0f ? rounded : static_cast<uint16_t>(0);
             sum_dh += bf16_to_float(dh);
-            dH[static_cast<int64_t>(m) * p.hid + h] = dh;    // rows m >= M are the zero padding of the dW1 product
+            dH[static_cast<int64_t>(m0 + v) * p.hid + h] = dh;    // rows m >= M are the zero padding of the dW1 product
         }
-        sum_dh += __shfl_xor(sum_dh, 16, 64);
         sum_dh += __shfl_xor(sum_dh, 32, 64);
+        sum_dh += __shfl_xor(sum_dh, 16, 64);
         if (lgrp == 0) red1[mt][hl] = sum_dh;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) red[mt][16 * ht + 4 * lgrp + v][lrow] = share[v];
     }
     __syncthreads();
 
-    // ---- c. the four sample tiles in order
+    // ---- c. the four shares
     {
         const int hh = threadIdx.x >> 4, o = threadIdx.x & 15;       // 1024 = 64 hidden units x 16 outputs
-        const float sum = ((red[0][hh][o] + red[1][hh][o]) + red[2][hh][o]) + red[3][hh][o];
+        const float sum = (red[0][hh][o] + red[2][hh][o]) + (red[1][hh][o] + red[3][hh][o]);
         if (o < p.out) gW2[static_cast<int64_t>(blockIdx.x * 64 + hh) * p.out + o] = sum * p.gscale;
         if (threadIdx.x < 64)
-            gb1[blockIdx.x * 64 + threadIdx.x] = ((red1[0][threadIdx.x] + red1[1][threadIdx.x]) + red1[2][threadIdx.x]) + red1[3][threadIdx.x];
+            gb1[blockIdx.x * 64 + threadIdx.x] = (red1[0][threadIdx.x] + red1[2][threadIdx.x]) + (red1[1][threadIdx.x] + red1[3][threadIdx.x]);
     }
     if (blockIdx.x == 0 && wave == 1 && lane < p.out) {
         float sdl = 0.0f;
