@@ -212,6 +212,13 @@ void adpsgd_destroy(adpsgd_t* h);
 /* Message for the last error on h (h may be NULL: message of the last failed create). */
 const char* adpsgd_last_error(const adpsgd_t* h);
 
+/* How adpsgd_run_events executes the calls from now on.  ADPSGD_ROUTE_AUTO (the default): in one launch per call where
+ * the library has that form and expects it to be faster (synthetic gradients; short and medium linear models), else
+ * round by round.  ADPSGD_ROUTE_ROUNDS: always round by round.  The results are the same within rounding (the same bits
+ * with synthetic gradients).  Gradients that a call has looked ahead to stay valid across a change. */
+enum { ADPSGD_ROUTE_AUTO = 0, ADPSGD_ROUTE_ROUNDS = 1 };
+int adpsgd_set_route(adpsgd_t* h, int32_t route);
+
 /* Local data of one worker: D_i is the uniform distribution over its rows
  * (Strategy-2 of the remark in Sec. 3.1).
  *   features: device, rows x ld elements, 16-byte aligned, ld a multiple of 4 (fp32)

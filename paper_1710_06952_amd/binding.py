@@ -15,10 +15,11 @@ LIB_PATH = _HERE / "libadpsgd.so"
 
 OK, ERR_ARG, ERR_GRAPH, ERR_SCHEDULE, ERR_STATE, ERR_HIP, ERR_CALLBACK = 0, -1, -2, -3, -4, -5, -6
 MODEL_LSQ, MODEL_LOGREG, MODEL_SYNTH, MODEL_MLP, MODEL_EXTERNAL = 0, 1, 2, 3, 4
+ROUTE_AUTO, ROUTE_ROUNDS = 0, 1
 FLAG_PROFILE, FLAG_DENSE_GRADIENT, FLAG_VERIFY_PLAN, FLAG_SYNC_IN_PLACE = 1, 2, 4, 8
 
 EXPORTS = [
-    "adpsgd_create", "adpsgd_destroy", "adpsgd_last_error", "adpsgd_load_data", "adpsgd_set_models",
+    "adpsgd_create", "adpsgd_destroy", "adpsgd_last_error", "adpsgd_load_data", "adpsgd_set_models", "adpsgd_set_route",
     "adpsgd_run_events", "adpsgd_run_events_with", "adpsgd_get_models", "adpsgd_get_mean_model", "adpsgd_consensus_distance", "adpsgd_consensus_distance_weighted",
     "adpsgd_consensus_distance_static",
     "adpsgd_get_bf16_models", "adpsgd_classification_error", "adpsgd_get_momentum", "adpsgd_get_stats", "adpsgd_make_schedule", "adpsgd_plan_rounds",
@@ -112,6 +113,7 @@ def lib():
         L.adpsgd_last_error.restype = C.c_char_p
         L.adpsgd_load_data.argtypes = [vp, i32, vp, i64, i64, vp]
         L.adpsgd_set_models.argtypes = [vp, vp, i64, i32]
+        L.adpsgd_set_route.argtypes = [vp, i32]
         L.adpsgd_run_events.argtypes = [vp, P(Schedule), vp]
         L.adpsgd_get_models.argtypes = [vp, vp, i64, i32]
         L.adpsgd_get_mean_model.argtypes = [vp, vp, i32]
@@ -296,6 +298,10 @@ class Handle:
             x = np.ascontiguousarray(x, dtype=np.float32)
             ptr = x.ctypes.data
         _check(self._h, lib().adpsgd_set_models(self._h, ptr, ld_in, 1 if on_device else 0))
+
+    def set_route(self, route):
+        """ROUTE_AUTO or ROUTE_ROUNDS (never a whole call in one launch) for the calls from now on."""
+        _check(self._h, lib().adpsgd_set_route(self._h, route))
 
     def run_events(self, schedule, loss_ptr=None):
         worker, nbr, tau = (_as_i32(schedule[k]) for k in ("worker", "neighbour", "tau"))

@@ -347,7 +347,7 @@ struct EventCall {
 
 // Whether the calls of this handle take the one-launch path of the linear models (kernels_strips.hip).  Decided by the
 // handle alone, so that a schedule gives the same bits however it is cut into calls; only a stream under capture goes by
-// rounds (a captured call would need a cooperative launch in a graph).
+// rounds (a captured call would need a cooperative launch in a graph), and a handle whose caller has asked for them.
 // Where the line lies: an iteration of the strip kernel evaluates a few gradients (teams / 2), so its time per event grows
 // with M and hardly falls with n, while the kernels of a round, of about n / 4 events, take its gradients side by side.
 // Measured (least squares on a 4-regular graph, us per 100 events, strips / rounds):  n = 8, M = 12: d = 300 110 / 318,
@@ -358,7 +358,7 @@ struct EventCall {
 bool can_run_strips(const adpsgd_t* h, int32_t& compute_units) {
     const int32_t model = h->o.model;
     const int64_t width = static_cast<int64_t>(h->n) * h->o.M;
-    if ((model != ADPSGD_MODEL_LSQ && model != ADPSGD_MODEL_LOGREG) || h->d > kStripMaxD || h->o.M > kStripMaxM ||
+    if (h->route != ADPSGD_ROUTE_AUTO || (model != ADPSGD_MODEL_LSQ && model != ADPSGD_MODEL_LOGREG) || h->d > kStripMaxD || h->o.M > kStripMaxM ||
         width > (h->d > 2048 ? 1600 : 1024) || (h->n > 32 && h->d <= 1024 && width > 512))
         return false;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -896,7 +896,7 @@ int run_events_impl(adpsgd_t* h, const adpsgd_schedule_t* s, float* loss, adpsgd
     rc = prepare_call(h, s, c);
     if (rc != ADPSGD_OK) return rc;
     ColumnPlan columns;
-    if (!c.with_grad) plan_columns(h, c, columns);
+    if (!c.with_grad && h->route == ADPSGD_ROUTE_AUTO) plan_columns(h, c, columns);
     if (c.strips) rc = run_strips(h, c, loss, c.strips);
     if (rc != ADPSGD_OK) return rc;
     if (!c.strips) rc = columns.quads > 0 ? run_columns(h, c, columns) : run_rounds(h, c, loss, fn, user);
@@ -929,6 +929,13 @@ extern "C" int adpsgd_run_events_with(adpsgd_t* h, const adpsgd_schedule_t* s, a
         return fail(h, ADPSGD_ERR_STATE, "run_events_with: the handle was not created with ADPSGD_MODEL_EXTERNAL");
     if (!fn) return fail(h, ADPSGD_ERR_ARG, "run_events_with: fn is NULL");
     return run_events_impl(h, s, nullptr, fn, user);
+}
+
+extern "C" int adpsgd_set_route(adpsgd_t* h, int32_t route) {
+    if (!h) return ADPSGD_ERR_ARG;
+    if (route != ADPSGD_ROUTE_AUTO && route != ADPSGD_ROUTE_ROUNDS) return fail(h, ADPSGD_ERR_ARG, "set_route: unknown route");
+    h->route = route;
+    return ADPSGD_OK;
 }
 
 extern "C" int adpsgd_get_stats(adpsgd_t* h, adpsgd_stats_t* out) {

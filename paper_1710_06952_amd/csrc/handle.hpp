@@ -61,6 +61,7 @@ struct adpsgd {
     std::vector<int32_t> rowptr, col;
     std::vector<adpsgd_impl::WorkerData> data;
     int32_t n_slots = 0;
+    int32_t route = ADPSGD_ROUTE_AUTO;
     hipStream_t stream = nullptr;
     bool streaming = false;
     uint64_t events_done = 0;

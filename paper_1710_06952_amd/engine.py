@@ -29,7 +29,8 @@ def _device_vector(torch, ptr, d, device):
 class Engine:
     def __init__(self, graph, d, model, *, M=0, gamma=0.0, lam=0.0, grad_sum=False, T_max=0, synth_std=0.0,
                  synth_seed=0, mlp=(0, 0, 0), n_slots=None, profile=False, momentum=0.0, weight_decay=0.0,
-                 local_compensation=False, dense_gradient=False, verify_plan=False, sync_in_place=False, device="cuda:0"):
+                 local_compensation=False, dense_gradient=False, verify_plan=False, sync_in_place=False, device="cuda:0",
+                 rounds=False):
         import torch
         if not torch.cuda.is_available():
             raise RuntimeError("Engine needs a GPU: the HIP library is the only implementation")
@@ -67,6 +68,8 @@ class Engine:
                           (B.FLAG_VERIFY_PLAN if verify_plan else 0) | (B.FLAG_SYNC_IN_PLACE if sync_in_place else 0), momentum=momentum, weight_decay=weight_decay,
                           V_ptr=None if self.V is None else self.V.data_ptr(),
                           local_compensation=local_compensation)
+        if rounds:                          # never a whole call in one launch
+            self.h.set_route(B.ROUTE_ROUNDS)
         self._data = []
         self.loss = None
 

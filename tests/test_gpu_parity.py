@@ -142,7 +142,7 @@ def test_synth_per_event_gamma_and_degenerate_calls(P):
 
 # ------------------------------------------------------------------ linear models
 def _run_linear(P, model, n, d, rows, K, M, T, gamma, lam, graph, seed, feature_var=1.0, n_slots=None,
-                sched_kw=None, grad_sum=False):
+                sched_kw=None, grad_sum=False, rounds=False):
     g = ring_graph(n) if graph == "ring" else random_regular4_graph(n, seed)
     if model == "lsq":
         feats, targs, _ = lsq_data(n, rows, d, seed=seed, feature_var=feature_var)
@@ -151,7 +151,7 @@ def _run_linear(P, model, n, d, rows, K, M, T, gamma, lam, graph, seed, feature_
         feats, targs, _ = logreg_data(n, rows, d, seed=seed)
         omodel = oracle.MODEL_LOGREG
     sched = oracle.make_schedule(g, K, seed=seed, T_max=T, M=M, rows=[rows] * n, **(sched_kw or {}))
-    eng = P.Engine(g, d, model, M=M, gamma=gamma, lam=lam, T_max=T, n_slots=n_slots, grad_sum=grad_sum)
+    eng = P.Engine(g, d, model, M=M, gamma=gamma, lam=lam, T_max=T, n_slots=n_slots, grad_sum=grad_sum, rounds=rounds)
     eng.load_data(feats, targs)
     x0 = np.zeros(d, np.float32)
     eng.set_models(x0)
@@ -637,13 +637,14 @@ def test_multi_pair_averaging_matrix(P, model):
 
 
 # ------------------------------------------------------------------ wait-free variant (local compensation)
+@pytest.mark.parametrize("rounds", [False, True])
 @pytest.mark.parametrize("model,n,d,rows,K,M,T,gamma,lam", [("lsq", 4, 5003, 24, 400, 4, 6, 0.3, 0.0),
                                                               ("logreg", 6, 4097, 32, 400, 8, 5, 8.0, 1e-3),
                                                               ("lsq", 1, 130, 16, 100, 2, 3, 0.2, 0.0)])
-def test_waitfree_local_compensation(P, model, n, d, rows, K, M, T, gamma, lam):
+def test_waitfree_local_compensation(P, model, n, d, rows, K, M, T, gamma, lam, rounds):
     """Appendix, wait-free training: the worker applies its own pending gradient to the copy it reads.
     Few workers and long staleness, so that most reads are compensated."""
-    _say("wait-free variant, %s n=%d d=%d" % (model, n, d))
+    _say("wait-free variant, %s n=%d d=%d rounds=%d" % (model, n, d, rounds))
     g = ring_graph(n)
     if model == "lsq":
         feats, targs, _ = lsq_data(n, rows, d, seed=12, feature_var=1.0 / d)
@@ -654,7 +655,7 @@ def test_waitfree_local_compensation(P, model, n, d, rows, K, M, T, gamma, lam):
     sched = oracle.make_schedule(g, K, seed=13, T_max=T, M=M, rows=[rows] * n)
     sched["gamma"] = (gamma * (1.0 + 0.25 * (np.arange(K) % 3))).astype(np.float32)
     x0 = np.random.default_rng(4).standard_normal(d).astype(np.float32)
-    eng = P.Engine(g, d, model, M=M, gamma=gamma, lam=lam, T_max=T, local_compensation=True)
+    eng = P.Engine(g, d, model, M=M, gamma=gamma, lam=lam, T_max=T, local_compensation=True, rounds=rounds)
     eng.load_data(feats, targs)
     eng.set_models(x0)
     eng.run_events(sched, want_loss=True)
@@ -700,12 +701,12 @@ def test_waitfree_local_compensation_mlp(P):
     eng.close()
 
 
-@pytest.mark.parametrize("model", ["lsq", "logreg", "mlp"])
-def test_waitfree_variant_with_momentum(P, model):
+@pytest.mark.parametrize("model,rounds", [("lsq", False), ("logreg", False), ("mlp", False), ("lsq", True), ("logreg", True)])
+def test_waitfree_variant_with_momentum(P, model, rounds):
     """Compensation with the buffered gradient, update with the optimizer's rule: models and momentum
     buffers against the oracle, and not what either option gives alone."""
     from workloads import mixture_data, mlp_init
-    _say("wait-free variant with momentum, %s" % model)
+    _say("wait-free variant with momentum, %s rounds=%d" % (model, rounds))
     mu, wd = 0.9, 1e-3
     if model == "mlp":
         n, dims, rows, K, M, T, gamma, lam = 4, (24, 64, 5), 40, 250, 16, 5, 0.02, 0.0
@@ -724,7 +725,7 @@ def test_waitfree_variant_with_momentum(P, model):
     g = ring_graph(n)
     sched = oracle.make_schedule(g, K, seed=13, T_max=T, M=M, rows=[rows] * n)
     eng = P.Engine(g, d, model, M=M, gamma=gamma, lam=lam, T_max=T, mlp=dims, local_compensation=True,
-                   momentum=mu, weight_decay=wd)
+                   momentum=mu, weight_decay=wd, rounds=rounds)
     eng.load_data(feats, targs)
     eng.set_models(x0)
     eng.run_events(sched)
@@ -1030,12 +1031,12 @@ def test_sync_steps_validation(P):
                                                    ("logreg", 4, 2047, 50, 150, 200, 2), ("lsq", 8, 513, 32, 300, 17, 4),
                                                    ("lsq", 5, 2048, 16, 200, 256, 1)])
 def test_short_models_take_the_single_block_gradient(P, model, n, d, rows, K, M, T):
-    """d <= 2048: the whole gradient of an operation is computed by one block (1, 2, 4 or 8 float4
+    """d <= 2048, round by round: the whole gradient of an operation is computed by one block (1, 2, 4 or 8 float4
     elements of the model per lane, ragged tails, up to 256 samples); one launch per round."""
     _say("short model %s d=%d M=%d" % (model, d, M))
     gamma, lam = (0.3, 0.0) if model == "lsq" else (2.0, 1e-3)
     eng, Xg, Xr, lg, lr, sched = _run_linear(P, model, n, d, rows, K, M, T, gamma, lam, "ring", 21,
-                                             feature_var=1.0 / d)
+                                             feature_var=1.0 / d, rounds=True)
     st = eng.get_stats()
     assert 0 < st["grad_launches"] <= st["rounds"]          # one launch per round that has gradients
     assert rel_err(Xg, Xr) <= TOL
@@ -1079,7 +1080,7 @@ def test_mlp_factored_and_dense_first_layer_gradient_give_the_same_bits(P, mu, w
 @pytest.mark.parametrize("model,n,d,K,T", [("synth", 1000, 300, 20000, 8), ("lsq", 500, 2100, 6000, 6), ("lsq", 600, 130, 6000, 6),
                                            ("logreg", 400, 2500, 4000, 5)])
 def test_many_workers_fill_the_rounds(P, model, n, d, K, T):
-    """Large rings: a round carries a few hundred pairs and gradient operations (the second grid
+    """Large rings, round by round: a round carries a few hundred pairs and gradient operations (the second grid
     dimension of every kernel), on each gradient path."""
     _say("many workers %s n=%d d=%d" % (model, n, d))
     g = ring_graph(n)
@@ -1087,7 +1088,7 @@ def test_many_workers_fill_the_rounds(P, model, n, d, K, T):
     rows, M = (6, 3) if model != "synth" else (0, 0)
     sched = oracle.make_schedule(g, K, seed=31, T_max=T, M=M, rows=[rows] * n if M else None)
     lam = 1e-3 if model == "logreg" else 0.0
-    eng = P.Engine(g, d, model, M=M, gamma=0.1, lam=lam, T_max=T, synth_std=std, synth_seed=9, verify_plan=True)
+    eng = P.Engine(g, d, model, M=M, gamma=0.1, lam=lam, T_max=T, synth_std=std, synth_seed=9, verify_plan=True, rounds=True)
     x0 = np.random.default_rng(8).standard_normal((n, d)).astype(np.float32)
     kw = {}
     if model != "synth":
@@ -1255,15 +1256,17 @@ def test_external_gradients_from_pytorch_follow_algorithm_1(P):
 
 
 # ------------------------------------------------------------------ a run split into calls that look ahead
-@pytest.mark.parametrize("model,comp,mu", [("lsq", False, 0.0), ("lsq_short", True, 0.0), ("logreg", False, 0.9), ("mlp", False, 0.0),
-                                           ("mlp", True, 0.9), ("external", True, 0.9)])
-def test_calls_that_look_ahead_equal_one_long_run(P, model, comp, mu):
+@pytest.mark.parametrize("model,comp,mu,rounds", [("lsq", False, 0.0, False), ("lsq_short", True, 0.0, False), ("logreg", False, 0.9, False),
+                                                  ("mlp", False, 0.0, False), ("mlp", True, 0.9, False), ("external", True, 0.9, False),
+                                                  ("lsq", False, 0.0, True), ("lsq_short", True, 0.0, True), ("logreg", False, 0.9, True),
+                                                  ("lsq", True, 0.9, True)])
+def test_calls_that_look_ahead_equal_one_long_run(P, model, comp, mu, rounds):
     """The whole schedule in one call, and the same schedule cut into calls that look T_max events ahead
     (so that staleness reaches across the cuts): the same bits on the GPU, and the oracle's single run within
     the tolerance.  Self-contained calls (staleness clipped at every cut) give something else."""
     import torch
     from workloads import mixture_data, mlp_init
-    _say("calls that look ahead: %s comp=%d mu=%g" % (model, comp, mu))
+    _say("calls that look ahead: %s comp=%d mu=%g rounds=%d" % (model, comp, mu, rounds))
     n, K, T = 6, 420, 5
     cuts = [0, 100, 103, 260, 420]
     g = ring_graph(n)
@@ -1290,7 +1293,7 @@ def test_calls_that_look_ahead_equal_one_long_run(P, model, comp, mu):
 
     def make():
         eng = P.Engine(g, d, kind, M=M if kind != "external" else 0, gamma=gamma, lam=lam, T_max=T, mlp=dims,
-                       local_compensation=comp, momentum=mu, weight_decay=wd, verify_plan=True)
+                       local_compensation=comp, momentum=mu, weight_decay=wd, verify_plan=True, rounds=rounds)
         if kind != "external":
             eng.load_data(feats, targs)
         eng.set_models(x0)
@@ -1419,9 +1422,6 @@ def test_seeded_sweep_of_small_set_ups(P, block):
             c["ident"]))
         n, d, M = c["n"], c["d"], c["M"]
         std = float(np.float32(0.1))
-        eng = P.Engine(c["g"], d, c["model"], M=M, gamma=0.1, lam=1e-3 if c["model"] == "logreg" else 0.0, T_max=c["T"],
-                       synth_std=std, synth_seed=c["seed"], momentum=c["momentum"], weight_decay=c["wd"],
-                       local_compensation=c["comp"], verify_plan=True)
         x0 = np.random.default_rng(c["seed"]).standard_normal((n, d)).astype(np.float32)
         kw = {}
         if c["model"] != "synth":
@@ -1429,15 +1429,12 @@ def test_seeded_sweep_of_small_set_ups(P, block):
                 feats, targs, _ = lsq_data(n, c["rows"], d, seed=c["seed"] % 1000, feature_var=1.0 / d)
             else:
                 feats, targs, _ = logreg_data(n, c["rows"], d, seed=c["seed"] % 1000)
-            eng.load_data(feats, targs)
             kw = dict(M=M, gscale=1.0 / M, lam=1e-3 if c["model"] == "logreg" else 0.0, features=feats, targets=targs)
-        eng.set_models(x0, broadcast=False)
         gs = dict(c["sched"])
         if c["extra"] is not None:
             gs["extra_pairs"] = c["extra"]
         if c["gam"] is not None:
             gs["gamma"] = c["gam"]
-        eng.run_events(gs)
         Xr = x0.copy()
         V = np.zeros_like(Xr) if (c["momentum"] or c["wd"]) else None
         omodel = {"synth": oracle.MODEL_SYNTH, "lsq": oracle.MODEL_LSQ, "logreg": oracle.MODEL_LOGREG}[c["model"]]
@@ -1445,10 +1442,18 @@ def test_seeded_sweep_of_small_set_ups(P, block):
                           momentum=c["momentum"], weight_decay=c["wd"], V=V, extra_pairs=c["extra"],
                           local_compensation=c["comp"], **kw)
         assert np.isfinite(Xr).all()
-        assert rel_err(eng.get_models(), Xr) <= TOL, c
-        if V is not None:
-            assert np.abs(eng.get_momentum() - V).max() <= TOL * max(np.abs(V).max(), 1e-30), c
-        eng.close()
+        for rounds in (False, True):         # in one launch, and round by round
+            eng = P.Engine(c["g"], d, c["model"], M=M, gamma=0.1, lam=1e-3 if c["model"] == "logreg" else 0.0, T_max=c["T"],
+                           synth_std=std, synth_seed=c["seed"], momentum=c["momentum"], weight_decay=c["wd"],
+                           local_compensation=c["comp"], verify_plan=True, rounds=rounds)
+            if kw:
+                eng.load_data(feats, targs)
+            eng.set_models(x0, broadcast=False)
+            eng.run_events(gs)
+            assert rel_err(eng.get_models(), Xr) <= TOL, (c, rounds)
+            if V is not None:
+                assert np.abs(eng.get_momentum() - V).max() <= TOL * max(np.abs(V).max(), 1e-30), (c, rounds)
+            eng.close()
 
 
 def test_checkpoint_and_resume_continue_bit_for_bit(P):
@@ -1732,8 +1737,8 @@ def test_the_abi_drives_the_gpu_from_plain_c():
 
 @pytest.mark.parametrize("mu,wd", [(0.0, 0.0), (0.9, 1e-3)])
 def test_least_squares_factored_and_dense_gradient_give_the_same_bits(P, mu, wd):
-    """Long least-squares models keep the gradient as its M coefficients until the update kernel applies it;
-    the result must be exactly that of the dense path (also with extra averaging pairs, a ragged d and the
+    """Round by round, long least-squares models keep the gradient as its M coefficients until the update kernel applies
+    it; the result must be exactly that of the dense path (also with extra averaging pairs, a ragged d and the
     experiments' optimizer), and agree with the oracle."""
     from workloads import random_extra_pairs, with_identity_events
     n, d, rows, K, M, T = 10, 4099, 24, 400, 7, 4
@@ -1749,7 +1754,7 @@ def test_least_squares_factored_and_dense_gradient_give_the_same_bits(P, mu, wd)
     out = []
     for dense in (False, True):
         eng = P.Engine(g, d, "lsq", M=M, gamma=base, T_max=T, dense_gradient=dense, verify_plan=True,
-                       momentum=mu, weight_decay=wd)
+                       momentum=mu, weight_decay=wd, rounds=True)
         eng.load_data(feats, targs)
         eng.set_models(x0, broadcast=False)
         eng.run_events(sched, want_loss=True)

@@ -1,0 +1,67 @@
+"""GPU: a run of a linear model cut into calls that look ahead, where consecutive calls are executed in one launch and
+round by round in turn: gradients pending across the cut are dense vectors or, from a least-squares call in rounds, the
+coefficients of their minibatch rows, and every kind is applied by the route that comes next."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import logreg_data, lsq_data, random_extra_pairs, ring_graph
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5          # of the whole suite for 32-bit models
+
+
+def rel_err(x, ref):
+    num = np.max(np.abs(x.astype(np.float64) - ref.astype(np.float64)), axis=1)
+    return float(np.max(num / np.maximum(np.max(np.abs(ref.astype(np.float64)), axis=1), 1e-30)))
+
+
+@pytest.mark.parametrize("model,d,comp,mu", [("lsq", 4099, False, 0.0), ("lsq", 4099, False, 0.9), ("lsq", 700, True, 0.0),
+                                             ("logreg", 4099, True, 0.9), ("logreg", 1030, False, 0.0)])
+def test_routes_change_between_calls_that_look_ahead(model, d, comp, mu):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1710_06952_amd as P
+    print("routes %s d=%d comp=%d mu=%g" % (model, d, comp, mu), flush=True)
+    n, K, T, M, rows = 6, 420, 5, 5, 24
+    g = ring_graph(n)
+    if model == "lsq":
+        feats, targs, _ = lsq_data(n, rows, d, seed=4, feature_var=1.0 / d)
+        omodel, gamma, lam = oracle.MODEL_LSQ, 0.03 if mu else 0.3, 0.0
+    else:
+        feats, targs, _ = logreg_data(n, rows, d, seed=4)
+        omodel, gamma, lam = oracle.MODEL_LOGREG, 0.05 if mu else 0.5, 1e-3
+    sched = oracle.make_schedule(g, K, seed=14, T_max=T, M=M, rows=[rows] * n)
+    sched["gamma"] = (gamma * (1 + np.arange(K) % 2)).astype(np.float32)
+    sched["extra_pairs"] = random_extra_pairs(g, sched["worker"], sched["neighbour"], max_extra=1, seed=3)
+    x0 = np.random.default_rng(4).standard_normal(d).astype(np.float32)
+    wd = 1e-3 if mu else 0.0
+    eng = P.Engine(g, d, model, M=M, gamma=gamma, lam=lam, T_max=T, momentum=mu, weight_decay=wd, local_compensation=comp, verify_plan=True)
+    eng.load_data(feats, targs)
+    eng.set_models(x0)
+    turn = iter([P.ROUTE_ROUNDS, P.ROUTE_AUTO, P.ROUTE_ROUNDS, P.ROUTE_ROUNDS, P.ROUTE_AUTO, P.ROUTE_AUTO, P.ROUTE_ROUNDS])
+    eng.run_events_in_pieces(sched, 60, between=lambda done: eng.h.set_route(next(turn)))      # the first call goes in one launch
+    X, V = eng.get_models(), eng.get_momentum() if mu else None
+    eng.close()
+    Xr = np.tile(x0, (n, 1))
+    Vr = np.zeros_like(Xr) if mu else None
+    extra = sched.pop("extra_pairs")
+    oracle.run_events(Xr, sched, omodel, gamma, M=M, gscale=1.0 / M, lam=lam, features=feats, targets=targs, gamma_k=sched["gamma"],
+                      extra_pairs=extra, momentum=mu, weight_decay=wd, V=Vr, local_compensation=comp)
+    assert rel_err(X, Xr) <= TOL
+    if mu:
+        assert rel_err(V, Vr) <= TOL
+
+
+def test_unknown_route_is_refused():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1710_06952_amd as P
+    eng = P.Engine(ring_graph(4), 64, "synth", gamma=0.1, synth_std=0.1)
+    with pytest.raises(P.AdpsgdError) as ei:
+        eng.h.set_route(2)
+    assert ei.value.code == -1
+    eng.close()
