@@ -8,9 +8,12 @@ adpsgd_run_events call on a slice of the seeded event schedule; the default 10 s
 model matrix) are resident in HBM before the timed region; the schedule slices are
 generated on the host beforehand.
 
-Prints ONE JSON line: worker updates/s, plus the HBM roofline of the dominant kernel
-(config 3: fused gossip-average + apply, algorithmic bytes = 16 B per parameter per
-event: read and write the two averaged rows) and the CPU oracle timed on this host.
+Prints ONE JSON line: worker updates/s, plus the roofline of the dominant kernel and the
+CPU oracle timed on this host.  Where a call goes in one launch (config 3: the column
+kernel, X crosses HBM once per call) the generator's arithmetic binds: the roofline is in
+normals/s, and hbm_GBs is what the launch moves.  Round by round it is the HBM roofline of
+the fused gossip-average + apply kernel (16 B per parameter and event: the two averaged
+rows read and written).  Which of the two ran is read off the library's launch counters.
 
 ``--config 1|2|4|5`` times the other configurations the same way (data generated in GPU
 memory; a step is a tenth of the configuration's events); those lines are context for the
@@ -302,7 +305,8 @@ def main():
     prof.destroy()
 
     events_per_launch = ps["events"] / ps["fused_launches"]
-    in_columns = synth and n <= (160 if eng.V is not None else 320)   # all events of a call in one launch, X crosses HBM once
+    one_launch = ps["fused_launches"] == n_prof < ps["rounds"]     # all events of a call in one launch
+    in_columns = synth and one_launch                              # ... with X crossing HBM once per call
     if in_columns:
         # bound by the generator's arithmetic: a quad of normals takes a SIMD 411 cycles per 64 lanes (csrc/device_common.hpp);
         # 1024 SIMDs at 2.4 GHz
@@ -313,7 +317,7 @@ def main():
         roof = {"bound": "valu", "achieved": achieved, "peak": peak, "unit": "1e9 normals/s", "frac": achieved / peak,
                 "traffic": None, "traffic_source": None, "kernel": "column_events_kernel", "avg_launch_ms": launch_s * 1e3,
                 "events_per_launch": per_call, "hbm_GBs": (16.0 if eng.V is not None else 8.0) * n * d / launch_s / 1e9,
-                "hbm_GBs_if_streamed": (24.0 if eng.V is not None else 16.0) * d * per_call / launch_s / 1e9}
+                "hbm_frac": (16.0 if eng.V is not None else 8.0) * n * d / launch_s / 1e9 / HBM_PEAK_GBS}
     elif synth:
         bytes_per_event = (24.0 if eng.V is not None else 16.0) * d   # read x_i, x_j; write x_i, x_j (+ v_i read and written)
         avg_launch_s = ps["fused_ms"] * 1e-3 / ps["fused_launches"]
@@ -340,7 +344,7 @@ def main():
         roof = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK_GBS,
                 "traffic": traffic, "traffic_source": traffic_source,   # recorded bytes per event, as `achieved` is
-                "kernel": "gradient + update kernels (per event)", "avg_gradient_us": per_grad_s * 1e6,
+                "kernel": "strip_events_kernel (per event)" if one_launch else "gradient + update kernels (per event)", "avg_gradient_us": per_grad_s * 1e6,
                 "fused_us_per_event": per_update_s * 1e6, "bytes_per_event": bytes_per_event,
                 "bytes_per_gradient": grad_rows_bytes, "events_per_launch": events_per_launch}
 
@@ -361,10 +365,11 @@ def main():
         "config": {"workload": cfg["name"], "n": n, "d": d, "graph": cfg["graph"], "events_per_step": E,
                    "events": events, "M": M, "gamma": cfg["gamma"], "T_max": cfg["T_max"],
                    "rounds": st1["rounds"] - st0["rounds"], "fused_launches": launches,
-                   "grad_launches": st1["grad_launches"] - st0["grad_launches"],
-                   "algorithmic_GBs_whole_run": algorithmic_bytes_per_event(cfg) * events / elapsed / 1e9},
+                   "grad_launches": st1["grad_launches"] - st0["grad_launches"]},
         "roofline": roof,
     }
+    if not one_launch:        # a call in one launch does not move the bytes of the events one by one
+        out["config"]["algorithmic_GBs_whole_run"] = algorithmic_bytes_per_event(cfg) * events / elapsed / 1e9
     if synth:
         out["config"]["gradient"] = "N(0,1e-3) Philox4x32-10 + Box-Muller, generated in registers"
         if eng.V is not None:

@@ -192,10 +192,10 @@ typedef struct {
 typedef struct {
     int64_t events;          /* events executed since creation                    */
     int64_t rounds;          /* conflict-free rounds they were packed into        */
-    int64_t fused_launches;  /* rounds that update models: one launch each of the gossip-average + apply kernel, */
-    int64_t grad_launches;   /*   and launches of gradient kernels; where a call executes its rounds inside one  */
-                             /*   launch both count what the rounds stand for                                    */
-    int64_t max_round_pairs; /* most update events in one round                   */
+    int64_t fused_launches;  /* launches that update models: one per round that does, or one per call that goes in a */
+                             /*   single launch                                                                     */
+    int64_t grad_launches;   /* launches of gradient kernels (none where a call goes in a single launch)             */
+    int64_t max_round_pairs; /* most update operations the plan has put into one round                               */
     int64_t slots;           /* pending-gradient slots available                  */
     double fused_ms;         /* summed kernel time, only with ADPSGD_FLAG_PROFILE */
     double grad_ms;

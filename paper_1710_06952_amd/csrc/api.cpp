@@ -641,7 +641,6 @@ int launch_updates(adpsgd_t* h, const EventCall& c, int32_t r) {
         HIP_TRY(h, launch_fused_gossip_apply(a, h->stream));
     }
     ++h->stats.fused_launches;
-    h->stats.max_round_pairs = std::max<int64_t>(h->stats.max_round_pairs, nu);
     return end_timing(h, e0, e1, h->ev_fused);
 }
 
@@ -739,11 +738,7 @@ int run_columns(adpsgd_t* h, const EventCall& c, const ColumnPlan& plan) {
     HIP_TRY(h, launch_column_events(a, h->stream));
     rc = end_timing(h, e0, e1, h->ev_fused);
     if (rc != ADPSGD_OK) return rc;
-    for (int32_t r = 0; r < c.plan.n_rounds; ++r) {     // the rounds are counted however they are executed
-        const int64_t nu = c.u_off[r + 1] - c.u_off[r];
-        h->stats.fused_launches += nu > 0;
-        h->stats.max_round_pairs = std::max<int64_t>(h->stats.max_round_pairs, nu);
-    }
+    ++h->stats.fused_launches;
     HIP_TRY(h, hipEventRecord(T.done, h->stream));
     T.in_flight = true;
     return ADPSGD_OK;
@@ -857,14 +852,7 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     h->exchange_seq += static_cast<uint32_t>(prog.order.size());
     rc = end_timing(h, e0, e1, h->ev_fused);
     if (rc != ADPSGD_OK) return rc;
-    // the rounds are counted however they are executed
-    const int64_t per_group = h->d <= 2048 && M <= 256 ? 1 : c.lin_factored ? 2 : 3;
-    for (int32_t r = 0; r < c.plan.n_rounds; ++r) {
-        const int64_t nu = c.u_off[r + 1] - c.u_off[r];
-        h->stats.fused_launches += nu > 0;
-        h->stats.max_round_pairs = std::max<int64_t>(h->stats.max_round_pairs, nu);
-        h->stats.grad_launches += per_group * ((c.r_off[r + 1] - c.r_off[r] + c.group - 1) / c.group);
-    }
+    ++h->stats.fused_launches;
     HIP_TRY(h, hipEventRecord(T.done, h->stream));
     T.in_flight = true;
     return ADPSGD_OK;
@@ -905,6 +893,7 @@ int run_events_impl(adpsgd_t* h, const adpsgd_schedule_t* s, float* loss, adpsgd
     h->events_done += static_cast<uint64_t>(c.A);
     h->stats.events += c.A;
     h->stats.rounds += c.plan.n_rounds;
+    for (int32_t r = 0; r < c.plan.n_rounds; ++r) h->stats.max_round_pairs = std::max<int64_t>(h->stats.max_round_pairs, c.u_off[r + 1] - c.u_off[r]);
     // the events looked ahead to: the next call must start with them; some have their gradient pending already
     h->pending.clear();
     h->pending_batch.clear();

@@ -83,7 +83,7 @@ def test_synth_workload_small(P, n, d, K, T):
     oracle.run_events(Xr, sched2, oracle.MODEL_SYNTH, 0.1, synth_std=std, synth_seed=9, event_base=K)
     assert rel_err(eng.get_models(), Xr) <= TOL
     st = eng.get_stats()
-    assert st["events"] == K + 100 and st["fused_launches"] == st["rounds"]
+    assert st["events"] == K + 100 and st["fused_launches"] == 2 < st["rounds"]      # each call in one launch
     eng.close()
 
 
