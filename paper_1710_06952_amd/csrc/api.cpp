@@ -659,9 +659,20 @@ struct ColumnPlan {
 // batch costs a wavefront about 1500 cycles from its operands to its results, and a SIMD with several of them one per
 // 420) is compared for every width whose strips leave at least eight wavefronts to a compute unit.  Below that the
 // rounds are the better route: 32 KB strips (n = 500, four quads) leave one wavefront per SIMD to hide that latency.
+//
+// The rounds are also the better route for a call that touches its rows once or twice: they move 16 (24) bytes per
+// parameter and event at 6.4 TB/s, the column kernel 8 (16) per touched row, at 0.3 TB/s per wavefront of a compute unit
+// (measured 2.6 with 8 to 8 with 16; half as much again where the state fits the memory-side cache), before and after it
+// computes.  Measured, one launch / rounds in us:  n = 160,
+// d = 4 M, 19 events 320 / 209, 80 events 1129 / 822, 240 events 1930 / 2440;  n = 320, d = 16 M, 480 events 24 800 /
+// 19 400, 960 events 31 500 / 38 600;  n = 117 with momentum, d = 1 M, 29 events 199 / 128, 117 events 480 / 490.  And a
+// launch of its own costs 4.5 us where a round costs 2.5 at least, so a call of a single round stays one (one event:
+// 25 / 22), and what cannot gain is turned away before the strips are laid out.  Of 700 set-ups measured (n 4 ... 320, d 1000 ... 16 M, 1 to 5 n events, with and without momentum) the line
+// takes none to the slower route by more than 5 %, where all to the column kernel lost up to 2.0 times.
 void plan_columns(adpsgd_t* h, const EventCall& c, ColumnPlan& out) {
     const adpsgd_schedule_t* s = c.s;
     if (h->d > (1ll << 34)) return;                 // the quad has to fit one word of the generator's counter
+    if (c.plan.n_rounds < 2) return;                // one launch as it is
     std::vector<int32_t> local(h->n, -1);
     auto row = [&](int32_t r) {
         if (local[r] < 0) {
@@ -671,18 +682,26 @@ void plan_columns(adpsgd_t* h, const EventCall& c, ColumnPlan& out) {
         return local[r];
     };
     out.pairs.reserve(static_cast<size_t>(c.A + c.n_extra));
+    int64_t accesses = 0;                           // rows that the rounds read or write
     for (int64_t k = 0; k < c.A; ++k) {
         const int32_t i = row(s->worker[k]), j = row(s->neighbour[k]);
+        accesses += (i == j ? 2 : 4) + (h->o.V ? 2 : 0);
         out.pairs.push_back(ColumnPair{i, j, k});
         if (s->extra_ptr)
             for (int64_t q = s->extra_ptr[k]; q < s->extra_ptr[k + 1]; ++q) {
                 const int32_t a = row(s->extra_a[q]), b = row(s->extra_b[q]);
+                accesses += 4;
                 out.pairs.push_back(ColumnPair{a, b, -1});
             }
     }
     const int64_t n_vec = (h->d + 3) / 4, n_rows = static_cast<int64_t>(out.rows.size());
     constexpr double kIssue = 420.0, kLatency = 1500.0, kSimds = 1024.0, kLdsPerCu = 160.0 * 1024.0;
-    double best = 0.0;
+    constexpr double kCycle = 1.0 / 2.4e9, kRoundRate = 6.4e12, kLaunch = 4.5e-6, kRound = 2.5e-6;
+    const double state = static_cast<double>(h->n) * h->o.ldx * 4.0 * (h->o.V ? 2.0 : 1.0), row_bytes = 4.0 * static_cast<double>(h->d);
+    const double moved = static_cast<double>(n_rows) * row_bytes * (h->o.V ? 4.0 : 2.0), rate = state > kStreamingThreshold ? 0.3e12 : 0.45e12;
+    const double rounds = static_cast<double>(c.plan.n_rounds) * kRound + static_cast<double>(accesses) * row_bytes / kRoundRate;
+    if (kLaunch + kLatency * kCycle + moved / (rate * 16.0) >= rounds) return;
+    double best = 0.0, waves_per_cu = 16.0;
     std::vector<int64_t> place;
     for (int32_t quads = 4; quads <= 64; quads *= 2) {
         const double strip = static_cast<double>(n_rows) * quads * 16.0 * (h->o.V ? 2.0 : 1.0);
@@ -693,12 +712,13 @@ void plan_columns(adpsgd_t* h, const EventCall& c, ColumnPlan& out) {
         const double cost = static_cast<double>(batches) * std::max(kLatency, waves * std::max(kIssue, kLatency / (per_cu / 4.0)));
         if (out.quads == 0 || cost < best) {
             best = cost;
+            waves_per_cu = per_cu;
             out.quads = quads;
             out.batches = batches;
             out.place.swap(place);
         }
     }
-    if (out.batches > 0x7FFFFFF0) out.quads = 0;
+    if (out.batches > 0x7FFFFFF0 || kLaunch + best * kCycle + moved / (rate * waves_per_cu) >= rounds) out.quads = 0;
 }
 
 // All events of the call in one launch of the column kernel.
