@@ -345,22 +345,48 @@ struct EventCall {
     size_t off_coef = 0;                    // linear models: offset of the coefficients in the gradient scratch
 };
 
-// Whether the calls of this handle take the one-launch path of the linear models (kernels_strips.hip).  Decided by the
-// handle alone, so that a schedule gives the same bits however it is cut into calls; only a stream under capture goes by
-// rounds (a captured call would need a cooperative launch in a graph), and a handle whose caller has asked for them.
-// Where the line lies: an iteration of the strip kernel evaluates a few gradients (teams / 2), so its time per event grows
-// with M and hardly falls with n, while the kernels of a round, of about n / 4 events, take its gradients side by side.
-// Measured (least squares on a 4-regular graph, us per 100 events, strips / rounds):  n = 8, M = 12: d = 300 110 / 318,
-// 4096 122 / 878, 20 000 159 / 1008;  n = 16, M = 64: 229 / 306, 295 / 686, 479 / 916;  n = 32, M = 48: 188 / 200, 270 / 517,
-// 361 / 596;  n = 64, M = 12: 82 / 72, 101 / 214, 123 / 259, M = 24: 132 / 81, 176 / 246, 217 / 278, M = 48: 186 / 101,
-// 275 / 266, 354 / 318.  So n M <= 1600, where the rounds have a gradient in one launch (d <= 2048) 1024, and half of
-// that for many workers and the shortest models.
+// Workers up to which the one-launch path of the linear models (kernels_strips.hip) is the faster one.  An iteration of the
+// strip kernel evaluates teams / 2 gradients at most, so its time per event jumps with the number of teams (M = 16, 32, 64)
+// and does not fall with n, while the kernels of a round, of n / 4 events on a ring and n / 5 or n / 6 on denser graphs, take
+// its gradients side by side.  Measured, rounds over strips for a call of 12 n events (the lesser of a call alone and one of
+// several; least squares and logistic regression, momentum, T_max 0 ... 40):
+//                          ring                                     random 4-regular graph
+//   d = 64     M <= 16     n = 16 1.19 ... 1.57, n = 28 0.76        n = 24 1.03 ... 1.16, n = 40 0.76
+//   d = 1024   M <= 16     n = 20 0.97 ... 1.6,  n = 32 0.86        n = 32 1.0 ... 1.6,   n = 56 0.80
+//   d = 4096   M = 8       n = 40 1.4,           n = 72 0.93        n = 64 1.2 ... 1.4,   n = 100 0.7
+//   d = 4096   M = 32      n = 28 1.1,           n = 48 0.7         n = 48 1.1
+// A direct exchange between 17 to 32 strips (d = 8192) is the slowest for its size.  The line keeps below the first loss of
+// any of them; beyond it the strips would still win in places (n = 32, M = 64: d = 4096 2356 / 3515 us a call;  n = 16,
+// M = 128, d = 20 000 6115 / 7528;  n = 32, M = 48, d = 1024 1218 / 1505) and lose near by (n = 16, M = 128, d = 300 2986 /
+// 2800;  n = 1600, M = 1, d = 4096 10 200 / 1180).  Models and slots that do not fit LDS cost more than the table says.
+int32_t strip_workers(int64_t d, int32_t M, bool ring, bool lds_state) {
+    const bool slow_exchange = d > 16 * kStripCols && d <= kStripGroupBlocks * kStripCols;
+    int32_t n;
+    if (d < 1024) n = M <= 16 ? (ring ? 16 : 24) : M <= 32 ? (ring ? 12 : 16) : M <= 64 ? 8 : 5;
+    else if (d <= 2048) n = M <= 16 ? (ring ? 20 : 32) : M <= 32 ? (ring ? 16 : 24) : M <= 64 ? 16 : 8;
+    else if (M <= 3) n = ring ? 28 : 32;
+    else if (M <= 16) n = ring ? 40 : 64;
+    else if (M <= 32) n = ring ? (slow_exchange ? 20 : 28) : 48;
+    else if (M <= 64) n = ring ? 16 : slow_exchange ? 20 : 24;
+    else n = slow_exchange ? (ring ? 5 : 8) : 12;
+    return lds_state ? n : std::min(n, 16);
+}
+
+// Gradients of a call that the strip kernel can hold in LDS beside the models of its columns.
+int64_t strip_lds_slots(const adpsgd_t* h) {
+    const int64_t fixed = static_cast<int64_t>(strip_lds_bytes(h->o.M, h->n, h->o.V != nullptr, 0, true));
+    return (kStripLdsBytes - fixed) / (kStripCols * static_cast<int64_t>(sizeof(float)));
+}
+
+// Whether the calls of this handle take the one-launch path of the linear models.  Decided by the handle, so that a
+// schedule gives the same bits however it is cut into calls; only a stream under capture goes by rounds (a captured call
+// would need a cooperative launch in a graph), a handle whose caller has asked for them, and short calls (small_call).
 bool can_run_strips(const adpsgd_t* h, int32_t& compute_units) {
     const int32_t model = h->o.model;
-    const int64_t width = static_cast<int64_t>(h->n) * h->o.M;
-    if (h->route != ADPSGD_ROUTE_AUTO || (model != ADPSGD_MODEL_LSQ && model != ADPSGD_MODEL_LOGREG) || h->d > kStripMaxD || h->o.M > kStripMaxM ||
-        width > (h->d > 2048 ? 1600 : 1024) || (h->n > 32 && h->d <= 1024 && width > 512))
+    if (h->route != ADPSGD_ROUTE_AUTO || (model != ADPSGD_MODEL_LSQ && model != ADPSGD_MODEL_LOGREG) || h->d > kStripMaxD || h->o.M > kStripMaxM)
         return false;
+    const bool ring = h->rowptr[h->n] <= 3 * static_cast<int64_t>(h->n), lds_state = strip_lds_slots(h) >= static_cast<int64_t>(h->o.T_max) + 1;
+    if (h->n > strip_workers(h->d, h->o.M, ring, lds_state)) return false;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess) {
         (void)hipGetLastError();
@@ -375,6 +401,21 @@ bool can_run_strips(const adpsgd_t* h, int32_t& compute_units) {
         if (w.ld > 0xFFFFFFFFll) return false;          // the row pitch has to fit a word of a record
     compute_units = std::min(cus, kStripGroups * kStripGroupBlocks);
     return cooperative != 0 && strip_blocks(h->d) <= compute_units;
+}
+
+// A call of few events: the cooperative launch, the assembly of its blocks and the first iterations take 44 us, where a call in
+// rounds takes 14 and 2.6 for each launch (plus the minibatch rows, read once or twice).  Measured among other calls, strips /
+// rounds in us:  n = 8, d = 1024, M = 32: 1 event 47 / 23, 8 events 55 / 38, 16 events 66 / 63, 32 events 84 / 116;  n = 16,
+// d = 4096, M = 8: 4 events 50 / 40, 8 events 54 / 54, 16 events 60 / 82;  n = 16, d = 7395, M = 6, T_max = 100, where most
+// reads of a short call precede its first update and share their launches: 23 events 83 / 48.
+// Calls that are cut out of one schedule (looking ahead, or without stale reads at all) keep the handle's route.
+bool small_call(const adpsgd_t* h, const EventCall& c) {
+    if (c.K > 128 || h->o.T_max == 0 || c.s->lookahead > 0 || !h->pending.empty()) return false;
+    const int32_t per_set = h->d <= 2048 ? 1 : c.lin_factored ? 2 : 3, teams = strip_teams(c.M);
+    int64_t launches = 0;
+    for (int32_t r = 0; r < c.plan.n_rounds; ++r) launches += (c.u_off[r + 1] > c.u_off[r]) + per_set * (c.r_off[r + 1] > c.r_off[r]);
+    const double row_us = 4.0 * c.M * static_cast<double>(h->d) * static_cast<double>(c.K) / 6.0e6, per_event = teams == 12 ? 0.9 : teams == 6 ? 1.4 : teams == 4 ? 2.2 : 4.5;
+    return 14.0 + 2.6 * static_cast<double>(launches) + row_us * (per_set == 1 ? 1.0 : 2.0) < 44.0 + per_event * static_cast<double>(c.K) + row_us;
 }
 
 // Validation, choice of paths, plan of rounds, counting sort of the operations by round.
@@ -434,6 +475,7 @@ int prepare_call(adpsgd_t* h, const adpsgd_schedule_t* s, EventCall& c) {
         c.u_off[r + 1] += c.u_off[r];
         c.r_off[r + 1] += c.r_off[r];
     }
+    c.strips = c.strips && !small_call(h, c);
     if (c.with_grad)
         c.group = static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(max_r, 1), h->o.model == ADPSGD_MODEL_MLP ? 64 : 65535));
     return ADPSGD_OK;
@@ -769,7 +811,6 @@ int run_columns(adpsgd_t* h, const EventCall& c, const ColumnPlan& plan) {
 int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     launched = false;
     const int32_t M = c.M, n = h->n;
-    const bool mom = h->o.V != nullptr;
     const size_t words = strip_exchange_bytes(h->o.model, M);
     if (words > h->exchange.cap) {
         HIP_TRY(h, h->exchange.reserve(words));
@@ -785,8 +826,7 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
         h->exchange_seq = 0;
     }
     // gradients ahead of the updates: as many as there is LDS for, 64 at most and T_max + 1 at least
-    const int64_t fixed = static_cast<int64_t>(strip_lds_bytes(M, n, mom, 0, true));
-    const int64_t slots_fit = (kStripLdsBytes - fixed) / (kStripCols * static_cast<int64_t>(sizeof(float)));
+    const int64_t slots_fit = strip_lds_slots(h);
     const bool lds_state = slots_fit >= static_cast<int64_t>(h->o.T_max) + 1;
     const int32_t window = static_cast<int32_t>(std::max<int64_t>(h->o.T_max + 1, std::min<int64_t>(64, lds_state ? slots_fit : h->n_slots)));
     StripCall sc{n, h->n_slots, window, c.K, c.A, c.s->worker, c.s->neighbour, c.s->tau, c.s->gamma, h->o.gamma, c.s->extra_ptr, c.s->extra_a, c.s->extra_b,

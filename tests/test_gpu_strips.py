@@ -11,6 +11,11 @@ pytestmark = pytest.mark.gpu
 TOL = 1e-5          # of the whole suite for 32-bit models: max over workers of |x - x_ref|_inf / |x_ref|_inf
 
 
+BY_ROUNDS = [("lsq", 4, 65_537, 8, 30, 3, 0.0, False), ("lsq", 5, 1500, 129, 30, 3, 0.0, False), ("logreg", 40, 300, 14, 150, 4, 0.0, False),
+             ("lsq", 200, 1101, 1, 500, 6, 0.0, False), ("logreg", 31, 2500, 20, 150, 4, 0.9, True), ("lsq", 64, 4100, 3, 300, 60, 0.9, False),
+             ("lsq", 8, 1024, 8, 4, 2, 0.0, False), ("logreg", 8, 4096, 8, 3, 2, 0.9, True)]
+
+
 @pytest.fixture(scope="module")
 def P():
     import torch
@@ -27,8 +32,8 @@ def rel_err(x, ref):
 
 
 # d around the float4, the strip of 256 columns, 32 strips (one group of blocks, then several) and the largest, 65 536;
-# M around the numbers of teams and rows (8, 16, 32, 48, 64, 96, 128) and n up to where the strips' state leaves LDS
-# (170 workers) and n M = 1024 and 1600, the last that go this way; then the first sizes that go by rounds
+# M around the numbers of teams and rows (8, 16, 32, 48, 64, 96, 128), up to the largest n that go this way, and staleness
+# for which the strips' state leaves LDS; then sizes beyond the line and calls of few rounds, which go by rounds
 @pytest.mark.parametrize("model,n,d,M,K,T,mu,comp", [
     ("lsq", 2, 1, 1, 40, 3, 0.0, False), ("logreg", 5, 3, 2, 60, 4, 0.9, False), ("lsq", 6, 255, 8, 80, 4, 0.9, False),
     ("logreg", 6, 256, 9, 80, 5, 0.0, True), ("lsq", 8, 257, 16, 120, 6, 0.0, False), ("logreg", 7, 1030, 17, 100, 4, 0.9, True),
@@ -36,8 +41,8 @@ def rel_err(x, ref):
     ("logreg", 6, 8193, 49, 60, 4, 0.0, True), ("lsq", 5, 16_385, 64, 50, 3, 0.0, False), ("logreg", 5, 9001, 65, 50, 3, 0.9, False),
     ("lsq", 4, 4100, 96, 50, 2, 0.0, False), ("logreg", 4, 8705, 97, 40, 3, 0.0, False), ("lsq", 8, 3003, 128, 40, 3, 0.0, True),
     ("logreg", 4, 65_535, 12, 40, 6, 0.9, False), ("lsq", 3, 65_536, 24, 30, 0, 0.0, False),
-    ("lsq", 50, 2100, 32, 200, 4, 0.0, False), ("lsq", 170, 1101, 6, 500, 6, 0.0, False), ("logreg", 90, 1101, 8, 300, 4, 0.9, True), ("lsq", 64, 8200, 16, 250, 30, 0.0, False),
-    ("lsq", 4, 65_537, 8, 30, 3, 0.0, False), ("lsq", 5, 1500, 129, 30, 3, 0.0, False), ("logreg", 40, 300, 14, 150, 4, 0.0, False)])
+    ("lsq", 48, 2100, 32, 200, 4, 0.0, False), ("lsq", 16, 1101, 6, 500, 140, 0.0, False), ("logreg", 12, 1101, 8, 300, 120, 0.9, True), ("lsq", 64, 8200, 16, 250, 30, 0.0, False)]
+    + BY_ROUNDS)
 def test_events_in_one_launch_against_the_oracle(P, model, n, d, M, K, T, mu, comp):
     print("strips %s n=%d d=%d M=%d mu=%g comp=%d" % (model, n, d, M, mu, comp), flush=True)
     rows = max(M, 24)
@@ -73,10 +78,10 @@ def test_events_in_one_launch_against_the_oracle(P, model, n, d, M, K, T, mu, co
     assert not eng.X[:, d:].any()                    # the padding of the rows stays zero
     st = eng.get_stats()                             # launches that were made: two of the strip kernel, or those of the rounds
     assert st["events"] == 2 * K and 0 < st["max_round_pairs"] <= 2 * n
-    if d <= 65_536 and M <= 128 and (n * M <= 1024 or (d > 2048 and n * M <= 1600)) and not (n > 32 and d <= 1024 and n * M > 512):
-        assert st["fused_launches"] == 2 and st["grad_launches"] == 0
-    else:
+    if (model, n, d, M, K, T, mu, comp) in BY_ROUNDS:
         assert 2 < st["fused_launches"] <= st["rounds"] and st["grad_launches"] > 0
+    else:
+        assert st["fused_launches"] == 2 and st["grad_launches"] == 0
     eng.close()
 
 
