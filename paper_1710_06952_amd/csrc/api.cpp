@@ -105,6 +105,68 @@ int drain_profile(adpsgd_t* h) {
     return ADPSGD_OK;
 }
 
+namespace {
+
+// Workers up to which the one-launch path of the linear models (kernels_strips.hip) is the faster one.  An iteration of the
+// strip kernel evaluates teams / 2 gradients at most, so its time per event jumps with the number of teams (M = 16, 32, 64)
+// and does not fall with n, while the kernels of a round, of n / 4 events on a ring and n / 5 or n / 6 on denser graphs, take
+// its gradients side by side.  Measured, rounds over strips for a call of 12 n events (the lesser of a call alone and one of
+// several; least squares and logistic regression, momentum, T_max 0 ... 40):
+//                          ring                                     random 4-regular graph
+//   d = 64     M <= 16     n = 16 1.19 ... 1.57, n = 28 0.76        n = 24 1.03 ... 1.16, n = 40 0.76
+//   d = 1024   M <= 16     n = 20 0.97 ... 1.6,  n = 32 0.86        n = 32 1.0 ... 1.6,   n = 56 0.80
+//   d = 4096   M = 8       n = 40 1.4,           n = 72 0.93        n = 64 1.2 ... 1.4,   n = 100 0.7
+//   d = 4096   M = 32      n = 28 1.1,           n = 48 0.7         n = 48 1.1
+// A direct exchange between 17 to 32 strips (d = 8192) is the slowest for its size.  The line keeps below the first loss of
+// any of them; beyond it the strips would still win in places (n = 32, M = 64: d = 4096 2356 / 3515 us a call;  n = 16,
+// M = 128, d = 20 000 6115 / 7528;  n = 32, M = 48, d = 1024 1218 / 1505) and lose near by (n = 16, M = 128, d = 300 2986 /
+// 2800;  n = 1600, M = 1, d = 4096 10 200 / 1180).  Models and slots that do not fit LDS cost more than the table says.
+int32_t strip_workers(int64_t d, int32_t M, bool ring, bool lds_state) {
+    const bool slow_exchange = d > 16 * kStripCols && d <= kStripGroupBlocks * kStripCols;
+    int32_t n;
+    if (d < 1024) n = M <= 16 ? (ring ? 16 : 24) : M <= 32 ? (ring ? 12 : 16) : M <= 64 ? 8 : 5;
+    else if (d <= 2048) n = M <= 16 ? (ring ? 20 : 32) : M <= 32 ? (ring ? 16 : 24) : M <= 64 ? 16 : 8;
+    else if (M <= 3) n = ring ? 28 : 32;
+    else if (M <= 16) n = ring ? 40 : 64;
+    else if (M <= 32) n = ring ? (slow_exchange ? 20 : 28) : 48;
+    else if (M <= 64) n = ring ? 16 : slow_exchange ? 20 : 24;
+    else n = slow_exchange ? (ring ? 5 : 8) : 12;
+    return lds_state ? n : std::min(n, 16);
+}
+
+// Gradients of a call that the strip kernel can hold in LDS beside the models of its columns.
+int64_t strip_lds_slots(const adpsgd_t* h) {
+    const int64_t fixed = static_cast<int64_t>(strip_lds_bytes(h->o.M, h->n, h->o.V != nullptr, 0, true));
+    return (kStripLdsBytes - fixed) / (kStripCols * static_cast<int64_t>(sizeof(float)));
+}
+
+}  // namespace
+
+// Whether the calls of a handle may take the one-launch path of the linear models is settled when it is created, with the
+// memory that path needs; a handle that cannot have it goes by rounds.
+void settle_strips(adpsgd_t* h) {
+    const int32_t model = h->o.model;
+    if ((model != ADPSGD_MODEL_LSQ && model != ADPSGD_MODEL_LOGREG) || h->d > kStripMaxD || h->o.M > kStripMaxM) return;
+    const bool ring = h->rowptr[h->n] <= 3 * static_cast<int64_t>(h->n), lds_state = strip_lds_slots(h) >= static_cast<int64_t>(h->o.T_max) + 1;
+    if (h->n > strip_workers(h->d, h->o.M, ring, lds_state)) return;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    int dev = 0, cus = 0, cooperative = 0;
+    const size_t words = strip_exchange_bytes(model, h->o.M);
+    if (hipStreamIsCapturing(h->stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone && hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+        hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && cooperative != 0 &&
+        strip_blocks(h->d) <= std::min(cus, kStripGroups * kStripGroupBlocks) && h->exchange.reserve(words) == hipSuccess &&
+        h->exchange_status.reserve(sizeof(int)) == hipSuccess && hipMemset(h->exchange.p, 0, h->exchange.cap) == hipSuccess &&      // no sequence number
+        hipStreamSynchronize(nullptr) == hipSuccess) {
+        *static_cast<int*>(h->exchange_status.p) = 0;
+        h->strip_units = std::min(cus, kStripGroups * kStripGroupBlocks);
+        return;
+    }
+    (void)hipGetLastError();
+    h->exchange.release();
+    h->exchange_status.release();
+}
+
 }  // namespace adpsgd_impl
 
 using namespace adpsgd_impl;
@@ -167,11 +229,14 @@ extern "C" int adpsgd_create(adpsgd_t** out, const adpsgd_graph_t* graph, int64_
     h->stream = static_cast<hipStream_t>(o.stream);
     h->streaming = static_cast<int64_t>(n) * o.ldx * 4 > kStreamingThreshold;
     h->stats.slots = n_slots;
+    settle_strips(h.get());
     for (auto& t : h->tables) {
         hipError_t e = hipEventCreateWithFlags(&t.done, hipEventDisableTiming);
         if (e != hipSuccess) {
             for (auto& u : h->tables)
                 if (u.done) (void)hipEventDestroy(u.done);
+            h->exchange.release();
+            h->exchange_status.release();
             return hip_fail(nullptr, e, "create: hipEventCreate");
         }
     }
@@ -326,7 +391,6 @@ struct EventCall {
     bool ext_comp = false;      // caller's function, wait-free variant: compensated fp32 rows
     bool factored = false;      // perceptron: dW1 stays in factored form until the update kernel
     bool lin_factored = false;  // least squares on long models: the gradient stays M coefficients
-    int32_t compute_units = 0;
     bool strips = false;        // linear models: all events in one launch (kernels_strips.hip)
     Plan plan;
     std::vector<int64_t> u_off, r_off;      // first update / gradient operation of every round
@@ -345,62 +409,20 @@ struct EventCall {
     size_t off_coef = 0;                    // linear models: offset of the coefficients in the gradient scratch
 };
 
-// Workers up to which the one-launch path of the linear models (kernels_strips.hip) is the faster one.  An iteration of the
-// strip kernel evaluates teams / 2 gradients at most, so its time per event jumps with the number of teams (M = 16, 32, 64)
-// and does not fall with n, while the kernels of a round, of n / 4 events on a ring and n / 5 or n / 6 on denser graphs, take
-// its gradients side by side.  Measured, rounds over strips for a call of 12 n events (the lesser of a call alone and one of
-// several; least squares and logistic regression, momentum, T_max 0 ... 40):
-//                          ring                                     random 4-regular graph
-//   d = 64     M <= 16     n = 16 1.19 ... 1.57, n = 28 0.76        n = 24 1.03 ... 1.16, n = 40 0.76
-//   d = 1024   M <= 16     n = 20 0.97 ... 1.6,  n = 32 0.86        n = 32 1.0 ... 1.6,   n = 56 0.80
-//   d = 4096   M = 8       n = 40 1.4,           n = 72 0.93        n = 64 1.2 ... 1.4,   n = 100 0.7
-//   d = 4096   M = 32      n = 28 1.1,           n = 48 0.7         n = 48 1.1
-// A direct exchange between 17 to 32 strips (d = 8192) is the slowest for its size.  The line keeps below the first loss of
-// any of them; beyond it the strips would still win in places (n = 32, M = 64: d = 4096 2356 / 3515 us a call;  n = 16,
-// M = 128, d = 20 000 6115 / 7528;  n = 32, M = 48, d = 1024 1218 / 1505) and lose near by (n = 16, M = 128, d = 300 2986 /
-// 2800;  n = 1600, M = 1, d = 4096 10 200 / 1180).  Models and slots that do not fit LDS cost more than the table says.
-int32_t strip_workers(int64_t d, int32_t M, bool ring, bool lds_state) {
-    const bool slow_exchange = d > 16 * kStripCols && d <= kStripGroupBlocks * kStripCols;
-    int32_t n;
-    if (d < 1024) n = M <= 16 ? (ring ? 16 : 24) : M <= 32 ? (ring ? 12 : 16) : M <= 64 ? 8 : 5;
-    else if (d <= 2048) n = M <= 16 ? (ring ? 20 : 32) : M <= 32 ? (ring ? 16 : 24) : M <= 64 ? 16 : 8;
-    else if (M <= 3) n = ring ? 28 : 32;
-    else if (M <= 16) n = ring ? 40 : 64;
-    else if (M <= 32) n = ring ? (slow_exchange ? 20 : 28) : 48;
-    else if (M <= 64) n = ring ? 16 : slow_exchange ? 20 : 24;
-    else n = slow_exchange ? (ring ? 5 : 8) : 12;
-    return lds_state ? n : std::min(n, 16);
-}
-
-// Gradients of a call that the strip kernel can hold in LDS beside the models of its columns.
-int64_t strip_lds_slots(const adpsgd_t* h) {
-    const int64_t fixed = static_cast<int64_t>(strip_lds_bytes(h->o.M, h->n, h->o.V != nullptr, 0, true));
-    return (kStripLdsBytes - fixed) / (kStripCols * static_cast<int64_t>(sizeof(float)));
-}
-
-// Whether the calls of this handle take the one-launch path of the linear models.  Decided by the handle, so that a
-// schedule gives the same bits however it is cut into calls; only a stream under capture goes by rounds (a captured call
-// would need a cooperative launch in a graph), a handle whose caller has asked for them, and short calls (small_call).
-bool can_run_strips(const adpsgd_t* h, int32_t& compute_units) {
-    const int32_t model = h->o.model;
-    if (h->route != ADPSGD_ROUTE_AUTO || (model != ADPSGD_MODEL_LSQ && model != ADPSGD_MODEL_LOGREG) || h->d > kStripMaxD || h->o.M > kStripMaxM)
-        return false;
-    const bool ring = h->rowptr[h->n] <= 3 * static_cast<int64_t>(h->n), lds_state = strip_lds_slots(h) >= static_cast<int64_t>(h->o.T_max) + 1;
-    if (h->n > strip_workers(h->d, h->o.M, ring, lds_state)) return false;
+// Whether a call takes the one-launch path of the linear models.  Decided by the handle, so that a schedule gives the same
+// bits however it is cut into calls; only a stream under capture goes by rounds (a captured call would need a cooperative
+// launch in a graph), a handle whose caller has asked for them, and short calls (small_call).
+bool can_run_strips(const adpsgd_t* h) {
+    if (h->strip_units == 0 || h->route != ADPSGD_ROUTE_AUTO) return false;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
     if (capture != hipStreamCaptureStatusNone) return false;
-    int dev = 0, cus = 0, cooperative = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess)
-        return false;
     for (const WorkerData& w : h->data)
         if (w.ld > 0xFFFFFFFFll) return false;          // the row pitch has to fit a word of a record
-    compute_units = std::min(cus, kStripGroups * kStripGroupBlocks);
-    return cooperative != 0 && strip_blocks(h->d) <= compute_units;
+    return true;
 }
 
 // A call of few events: the cooperative launch, the assembly of its blocks and the first iterations take 44 us, where a call in
@@ -450,7 +472,7 @@ int prepare_call(adpsgd_t* h, const adpsgd_schedule_t* s, EventCall& c) {
     c.factored = h->o.model == ADPSGD_MODEL_MLP && !dense && !comp && mlp_can_factor(h->o.mlp_in, h->o.mlp_hidden, c.M);
     c.lin_factored = with_data && !dense && !comp && linear_can_factor(h->o.model, h->d, c.M, h->o.ldx);
     // gradients pending from an earlier call come as it left them: dense vectors, or coefficients
-    c.strips = with_data && can_run_strips(h, c.compute_units) && (!any_carried || h->pending_dense);
+    c.strips = with_data && can_run_strips(h) && (!any_carried || h->pending_dense);
     if (any_carried && h->pending_dense) c.lin_factored = false;
 
     std::string perr;
@@ -806,22 +828,13 @@ int run_columns(adpsgd_t* h, const EventCall& c, const ColumnPlan& plan) {
     return ADPSGD_OK;
 }
 
-// All events of the call in one launch of the strip kernel.  Sets `launched` when the launch was made; a launch that the
-// device refuses leaves everything as it was, for the rounds.
+// All events of the call in one launch of the strip kernel.  Sets `launched` when the launch was made; without memory for the
+// records, which take several times that of the rounds' tables, or with a launch that the device refuses, everything is
+// as it was, for the rounds.
 int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     launched = false;
     const int32_t M = c.M, n = h->n;
-    const size_t words = strip_exchange_bytes(h->o.model, M);
-    if (words > h->exchange.cap) {
-        HIP_TRY(h, h->exchange.reserve(words));
-        HIP_TRY(h, hipMemsetAsync(h->exchange.p, 0, h->exchange.cap, h->stream));      // no sequence number
-        h->exchange_seq = 0;
-    }
-    if (!h->exchange_status.p) {
-        HIP_TRY(h, h->exchange_status.reserve(sizeof(int)));
-        *static_cast<int*>(h->exchange_status.p) = 0;
-    }
-    if (h->exchange_seq > 0xF0000000u) {                                               // before the numbers wrap
+    if (h->exchange_seq > 0xFFFFFFFFu - static_cast<uint64_t>(c.K)) {                  // before the numbers wrap
         HIP_TRY(h, hipMemsetAsync(h->exchange.p, 0, h->exchange.cap, h->stream));
         h->exchange_seq = 0;
     }
@@ -834,7 +847,11 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
                  h->exchange_seq + 1, strip_blocks(h->d)};
     const int32_t teams = strip_teams(M);
     StripProgram prog;
-    if (!build_strips(sc, teams, prog)) return ADPSGD_OK;
+    try {
+        if (!build_strips(sc, teams, prog)) return ADPSGD_OK;
+    } catch (const std::bad_alloc&) {
+        return ADPSGD_OK;
+    }
     // slots that cross the ends of the call: (slot of the call, slot of the workspace)
     std::vector<int32_t> carry;
     int32_t n_in = 0, n_out = 0;
@@ -854,8 +871,10 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
         HIP_TRY(h, hipEventSynchronize(T.done));
         T.in_flight = false;
     }
-    HIP_TRY(h, T.stage.reserve(total));
-    HIP_TRY(h, T.dev.reserve(total));
+    if (T.stage.reserve(total) != hipSuccess || T.dev.reserve(total) != hipSuccess) {
+        (void)hipGetLastError();
+        return ADPSGD_OK;
+    }
     char* stage = static_cast<char*>(T.stage.p);
     std::memset(stage + off_count, 0, kStripCounters * sizeof(uint32_t));
     std::memcpy(stage, prog.recs.data(), bytes_recs);
@@ -887,8 +906,8 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     a.words = static_cast<unsigned long long*>(h->exchange.p);
     a.counters = reinterpret_cast<unsigned int*>(static_cast<char*>(T.dev.p) + off_count);
     // few strips: one block per compute unit, of which those on one XCD stay; more: as many on every XCD (see the kernel)
-    a.grid = strip_blocks(h->d) <= kStripGroupBlocks ? c.compute_units
-                                                     : std::min(c.compute_units, kStripGroups * strip_group_size(h->d));
+    a.grid = strip_blocks(h->d) <= kStripGroupBlocks ? h->strip_units
+                                                     : std::min(h->strip_units, kStripGroups * strip_group_size(h->d));
     a.gscale = h->o.grad_sum ? 1.0f : 1.0f / static_cast<float>(std::max(M, 1));
     a.lambda = h->o.lambda;
     a.momentum = h->o.momentum;
@@ -901,6 +920,7 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     const hipError_t e = launch_strips(a, h->stream);
     if (e != hipSuccess) {                     // nothing has run; the tables may still be on their way
         (void)hipGetLastError();
+        if (e0) h->ev_pool.insert(h->ev_pool.end(), {e0, e1});
         HIP_TRY(h, hipEventRecord(T.done, h->stream));
         T.in_flight = true;
         return ADPSGD_OK;
@@ -963,13 +983,22 @@ int run_events_impl(adpsgd_t* h, const adpsgd_schedule_t* s, float* loss, adpsgd
     return ADPSGD_OK;
 }
 
+// No exception leaves the library: the host memory a call's plan takes is the only one there is.
+int run_events_guarded(adpsgd_t* h, const adpsgd_schedule_t* s, float* loss, adpsgd_gradient_fn fn, void* user) {
+    try {
+        return run_events_impl(h, s, loss, fn, user);
+    } catch (const std::bad_alloc&) {
+        return fail(h, ADPSGD_ERR_ARG, "run_events: out of host memory");
+    }
+}
+
 }  // namespace
 
 extern "C" int adpsgd_run_events(adpsgd_t* h, const adpsgd_schedule_t* s, float* loss) {
     if (!h) return ADPSGD_ERR_ARG;
     if (h->o.model == ADPSGD_MODEL_EXTERNAL)
         return fail(h, ADPSGD_ERR_STATE, "run_events: caller-supplied gradients need adpsgd_run_events_with");
-    return run_events_impl(h, s, loss, nullptr, nullptr);
+    return run_events_guarded(h, s, loss, nullptr, nullptr);
 }
 
 extern "C" int adpsgd_run_events_with(adpsgd_t* h, const adpsgd_schedule_t* s, adpsgd_gradient_fn fn, void* user) {
@@ -977,7 +1006,7 @@ extern "C" int adpsgd_run_events_with(adpsgd_t* h, const adpsgd_schedule_t* s, a
     if (h->o.model != ADPSGD_MODEL_EXTERNAL)
         return fail(h, ADPSGD_ERR_STATE, "run_events_with: the handle was not created with ADPSGD_MODEL_EXTERNAL");
     if (!fn) return fail(h, ADPSGD_ERR_ARG, "run_events_with: fn is NULL");
-    return run_events_impl(h, s, nullptr, fn, user);
+    return run_events_guarded(h, s, nullptr, fn, user);
 }
 
 extern "C" int adpsgd_set_route(adpsgd_t* h, int32_t route) {

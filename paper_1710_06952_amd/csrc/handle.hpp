@@ -75,7 +75,8 @@ struct adpsgd {
     adpsgd_impl::DevBuf sync_other;       // synchronous schedule: the second model matrix of the out-of-place iterations
     bool sync_other_refused = false;      // ... its allocation failed once: the iterations run in place from then on
     bool pending_dense = true;            // pending gradients evaluated by the last call are dense vectors (else coefficients)
-    adpsgd_impl::DevBuf exchange;         // linear models in one launch: words the blocks exchange ...
+    int32_t strip_units = 0;              // linear models in one launch: compute units for it, 0: this handle goes by rounds
+    adpsgd_impl::DevBuf exchange;         // ... words the blocks exchange ...
     uint32_t exchange_seq = 0;            // ... the sequence number of the last gradient
     adpsgd_impl::HostBuf exchange_status; // ... and a word the kernel sets when a wait had to be given up
     adpsgd_stats_t stats{};
@@ -102,6 +103,8 @@ void metropolis(const std::vector<int32_t>& rowptr, const std::vector<int32_t>& 
 hipEvent_t take_event(adpsgd_t* h);
 // An earlier launch that could not complete its exchange left the models undefined: report it.
 int check_exchange(adpsgd_t* h);
+// Create-time decision and memory of the one-launch path of the linear models (strip_units, exchange).
+void settle_strips(adpsgd_t* h);
 // Fold the timings of finished launches into the statistics (synchronises the stream).
 int drain_profile(adpsgd_t* h);
 
