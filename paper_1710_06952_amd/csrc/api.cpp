@@ -838,10 +838,9 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
         HIP_TRY(h, hipMemsetAsync(h->exchange.p, 0, h->exchange.cap, h->stream));
         h->exchange_seq = 0;
     }
-    // gradients ahead of the updates: as many as there is LDS for, 64 at most and T_max + 1 at least
     const int64_t slots_fit = strip_lds_slots(h);
     const bool lds_state = slots_fit >= static_cast<int64_t>(h->o.T_max) + 1;
-    const int32_t window = static_cast<int32_t>(std::max<int64_t>(h->o.T_max + 1, std::min<int64_t>(64, lds_state ? slots_fit : h->n_slots)));
+    const int32_t window = strip_window(h->o.T_max, lds_state, slots_fit, h->n_slots);
     StripCall sc{n, h->n_slots, window, c.K, c.A, c.s->worker, c.s->neighbour, c.s->tau, c.s->gamma, h->o.gamma, c.s->extra_ptr, c.s->extra_a, c.s->extra_b,
                  &c.plan, c.carried_slot.empty() ? nullptr : c.carried_slot.data(), h->data.data(), lds_state,
                  h->exchange_seq + 1, strip_blocks(h->d)};

@@ -49,8 +49,8 @@ struct Builder {
         free_teams.erase(free_teams.begin(), free_teams.begin() + n);
         return rec;
     }
-    int32_t take_slot() {
-        if (free_slots.empty()) return out.n_slots++;
+    int32_t take_slot() {         // -1: none left
+        if (free_slots.empty()) return c.renumber ? out.n_slots++ : -1;
         const int32_t s = free_slots.back();
         free_slots.pop_back();
         return s;
@@ -77,7 +77,7 @@ struct Order {
 // each filled up to whole batches of the kernel) and then evaluates the gradients that are ready, the oldest events
 // first, one for half of the teams at most.  So an iteration is spent per link of a chain of gradients, not per round.
 // Gradients run at most `window` events ahead of the first event not applied: that bounds the slots, and as no read is
-// further than T_max events ahead of an update that waits for it, window > T_max cannot block.
+// further than the largest tau ahead of an update that waits for it, a window beyond that cannot block.
 // Minibatch rows are requested in the order of evaluation, each set by a team whose last gradient was finished in the
 // iteration before, so a team's next rows are in flight while the others work.
 bool build_strips(const StripCall& c, int32_t teams, StripProgram& out) {
@@ -217,6 +217,7 @@ bool build_strips(const StripCall& c, int32_t teams, StripProgram& out) {
             }
             evaluated[k] = now;
             out.slot[k] = b.take_slot();
+            if (out.slot[k] < 0) return false;
             out.order.push_back(k);
             const int32_t r = c.worker[k];
             ++o.done[r];

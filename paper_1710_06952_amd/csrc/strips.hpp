@@ -2,6 +2,8 @@
 // (strips.cpp) and the kernel that executes it (kernels_strips.hip).
 #pragma once
 
+#include <algorithm>
+
 #include "internal.hpp"
 
 namespace adpsgd_impl {
@@ -43,7 +45,7 @@ struct StripProgram {
 
 struct StripCall {
     int32_t n, n_slots;    // workers, slots of the workspace
-    int32_t window;        // gradients at most this many events ahead of the first one not applied, > T_max
+    int32_t window;        // strip_window
     int64_t K, A;          // events in the arrays, events applied
     const int32_t *worker, *neighbour, *tau;
     const float* gamma;                  // per event or nullptr
@@ -60,7 +62,15 @@ struct StripCall {
 // Teams of wavefronts (gradients whose rows are held) for a minibatch of M samples: as many as their rows leave
 // registers for (at most 22 rows of a wavefront).
 inline int32_t strip_teams(int32_t M) { return M <= 16 ? 12 : M <= 32 ? 6 : M <= 64 ? 4 : 2; }
-// false: the events do not come in any order (the plan is not one of this schedule)
+// Gradients run at most this many events ahead of the first event not applied: as many as there are slots for, 64 at most
+// and T_max + 1 at least.  In LDS slots_fit slots fit (lds_state: more than T_max); in the workspace there are n_slots, which
+// may be fewer than T_max + 1 (the library uses 4096 at most): more than the largest tau of the call all the same, or there is
+// no plan, and that is all the order needs.
+inline int32_t strip_window(int64_t T_max, bool lds_state, int64_t slots_fit, int32_t n_slots) {
+    return static_cast<int32_t>(lds_state ? std::max<int64_t>(T_max + 1, std::min<int64_t>(64, slots_fit))
+                                          : std::min<int64_t>(n_slots, std::max<int64_t>(T_max + 1, 64)));
+}
+// false: the events do not come in any order (the plan is not one of this schedule), or there is no slot for a gradient
 bool build_strips(const StripCall& c, int32_t teams, StripProgram& out);
 
 struct StripArgs {

@@ -13,6 +13,9 @@ int main() {
         int n = 2 + rng() % 20, K = 1 + rng() % 150, T = rng() % 12, look = rng() % 2 ? std::min<int>(K, rng() % (T + 3)) : 0;
         int A = K - look; bool comp = rng() % 3 == 0, extra = rng() % 3 == 0, renum = rng() % 2;
         int n_slots = T + 1 + rng() % 20, window = T + 1 + rng() % 10; if (window > n_slots) window = n_slots;
+        // a handle whose T_max is beyond the slots of its workspace (4096 at most) and the taus of its calls
+        const bool far = rng() % 4 == 0;
+        if (far) window = strip_window(100 + rng() % 50, false, 0, n_slots);
         std::vector<int> w(K), nb(K), tau(K), carried(K, -1);
         int npend = rng() % 2 ? rng() % (std::min(K, T) + 1) : 0;   // leading events that may be carried
         std::vector<int> sl(n_slots); for (int i = 0; i < n_slots; ++i) sl[i] = i; std::shuffle(sl.begin(), sl.end(), rng);
@@ -25,6 +28,7 @@ int main() {
             if (extra && n >= 6 && rng() % 3 == 0) { int a, b; do { a = rng() % n; b = rng() % n; } while (a == b || a == w[k] || b == w[k] || a == nb[k] || b == nb[k]); ea.push_back(a); eb.push_back(b); }
             ep[k + 1] = ea.size();
         }
+        if (far) renum = false;
         Plan plan; std::string err;
         int rc = plan_rounds(n, K, w.data(), nb.data(), tau.data(), n_slots, true, plan, err, extra ? ep.data() : nullptr, ea.data(), eb.data(), comp, A, anyc ? carried.data() : nullptr);
         if (rc) { continue; }
