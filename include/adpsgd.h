@@ -68,10 +68,11 @@ enum {
 
 enum {
     ADPSGD_FLAG_PROFILE = 1, /* time every kernel launch with HIP events (see adpsgd_get_stats) */
-    ADPSGD_FLAG_VERIFY_PLAN = 4, /* check every plan of rounds against the serial semantics before anything is
-                                    launched (no two updates of a round share a row, every stale read sees exactly
-                                    the updates before its logical time, slots live long enough); a violation is a
-                                    library bug and returns ADPSGD_ERR_STATE.  O(K log K) host work per call */
+    ADPSGD_FLAG_VERIFY_PLAN = 4, /* check every plan of rounds, and the layout of a call that goes in one launch, against
+                                    the serial semantics before anything is launched (no two updates of a round share
+                                    a row, every stale read sees exactly the updates before its logical time, slots
+                                    live long enough); a violation is a library bug and returns ADPSGD_ERR_STATE.
+                                    O(K log K) host work per call */
     ADPSGD_FLAG_SYNC_IN_PLACE = 8,  /* adpsgd_run_sync_steps: never allocate the second model matrix that the iterations
                                        otherwise alternate with; every iteration then mixes in place (same
                                        results, 12 - 30 % slower at n = 128, d = 25.6 M depending on the graph) */

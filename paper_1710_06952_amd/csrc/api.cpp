@@ -788,6 +788,8 @@ void plan_columns(adpsgd_t* h, const EventCall& c, ColumnPlan& out) {
 // All events of the call in one launch of the column kernel.
 int run_columns(adpsgd_t* h, const EventCall& c, const ColumnPlan& plan) {
     const int32_t capacity = 64 / plan.quads;
+    if ((h->o.flags & ADPSGD_FLAG_VERIFY_PLAN) && !verify_columns(plan.pairs, static_cast<int32_t>(plan.rows.size()), capacity, plan.place, plan.batches))
+        return fail(h, ADPSGD_ERR_STATE, "column layout: the order of the events is not kept");
     const size_t n_ops = static_cast<size_t>(plan.batches + 1) * capacity, off_rows = n_ops * sizeof(ColumnOp);
     const size_t total = off_rows + plan.rows.size() * sizeof(int32_t);
     TableSet& T = h->tables[h->next_table];
@@ -851,6 +853,8 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     } catch (const std::bad_alloc&) {
         return ADPSGD_OK;
     }
+    std::string verr;
+    if ((h->o.flags & ADPSGD_FLAG_VERIFY_PLAN) && !verify_strips(sc, prog, verr)) return fail(h, ADPSGD_ERR_STATE, verr);
     // slots that cross the ends of the call: (slot of the call, slot of the workspace)
     std::vector<int32_t> carry;
     int32_t n_in = 0, n_out = 0;

@@ -132,6 +132,9 @@ struct ColumnPair {
 // keep their order from batch to batch: every operation goes into the first batch with room behind those of its rows.
 // place[t] = batch * capacity + position; returns the number of batches.
 int64_t pack_columns(const std::vector<ColumnPair>& pairs, int32_t n_rows, int32_t capacity, std::vector<int64_t>& place);
+// Whether such a packing keeps the semantics (ADPSGD_FLAG_VERIFY_PLAN): places of their own, the rows of a batch pairwise
+// different, the operations of every row in order from batch to batch.
+bool verify_columns(const std::vector<ColumnPair>& pairs, int32_t n_rows, int32_t capacity, const std::vector<int64_t>& place, int64_t batches);
 // Words a..d of an event's ColumnOp: with the counter (quad, 0, k_lo, k_hi) the first Philox round gives
 //   (hi(M1 k_lo) ^ key0, lo(M1 k_lo), hi(M0 quad) ^ a, lo(M0 quad))
 // and the second   (hi(p) ^ b, lo(p), lo(M0 quad) ^ c, d)   with p = M1 (hi(M0 quad) ^ a).

@@ -243,6 +243,20 @@ int64_t pack_columns(const std::vector<ColumnPair>& pairs, int32_t n_rows, int32
     return static_cast<int64_t>(fill.size());
 }
 
+bool verify_columns(const std::vector<ColumnPair>& pairs, int32_t n_rows, int32_t capacity, const std::vector<int64_t>& place, int64_t batches) {
+    if (place.size() != pairs.size()) return false;
+    std::vector<char> taken(static_cast<size_t>(batches) * capacity, 0);
+    std::vector<int64_t> last(n_rows, -1);       // batch of the row's latest operation
+    for (size_t t = 0; t < pairs.size(); ++t) {
+        if (place[t] < 0 || place[t] >= batches * capacity || taken[place[t]]) return false;
+        taken[place[t]] = 1;
+        const int64_t b = place[t] / capacity;
+        if (last[pairs[t].i] >= b || last[pairs[t].j] >= b) return false;      // the same batch: the row would be named twice
+        last[pairs[t].i] = last[pairs[t].j] = b;
+    }
+    return true;
+}
+
 void column_words(uint64_t event, uint64_t seed, ColumnOp& op) {
     const uint32_t k_lo = static_cast<uint32_t>(event), k_hi = (static_cast<uint32_t>(event >> 32) & 0x00FFFFFFu) | kStreamGrad;
     const uint32_t key0 = static_cast<uint32_t>(seed), key1 = static_cast<uint32_t>(seed >> 32);

@@ -272,4 +272,159 @@ bool build_strips(const StripCall& c, int32_t teams, StripProgram& out) {
     return true;
 }
 
+namespace {
+
+// One averaging that a row takes part in: the event, and the other row.
+struct RowUpdate {
+    int64_t event;
+    int32_t partner;
+    bool extra;
+};
+
+struct Checker {
+    const StripCall& c;
+    const StripProgram& p;
+    std::string& err;
+    std::vector<std::vector<RowUpdate>> due;       // per row: its updates in the order of the events ...
+    std::vector<size_t> done;                      // ... and how many are applied
+    std::vector<int64_t> slot_event;               // gradient held by a slot, or -1
+    std::vector<int64_t> loaded;                   // per team: position whose minibatch rows it holds or has requested, or -1
+    std::vector<int64_t> loaded_in;                // ... and the record that requested them
+    std::vector<char> evaluated, applied;
+
+    bool fail(const char* what, int64_t record) {
+        err = "strip layout: " + std::string(what) + " in record " + std::to_string(record);
+        return false;
+    }
+    bool slot_ok(uint32_t s) const { return s < slot_event.size(); }
+
+    bool update(const StripEntry& e, int64_t record, std::vector<int32_t>& batch) {
+        const int32_t i = static_cast<int32_t>(e.x & 0xFFFFu), j = static_cast<int32_t>(e.x >> 16);
+        if (i >= c.n || j >= c.n) return fail("row out of range", record);
+        for (const int32_t r : batch)
+            if (r == i || r == j) return fail("a batch names a row twice", record);
+        batch.push_back(i);
+        batch.push_back(j);
+        const bool extra = (e.w & kStripAverage) != 0;
+        if (done[i] >= due[i].size() || done[j] >= due[j].size()) return fail("an update that no event makes", record);
+        const RowUpdate &a = due[i][done[i]], &b = due[j][done[j]];
+        if (a.event != b.event || a.partner != j || b.partner != i || a.extra != extra || b.extra != extra)
+            return fail("an update out of the order of its rows", record);
+        ++done[i];
+        if (j != i) ++done[j];
+        if (extra) return true;
+        if (!slot_ok(e.y) || slot_event[e.y] != a.event || c.worker[a.event] != i) return fail("an update without its gradient", record);
+        if (e.z != bits(c.gamma ? c.gamma[a.event] : c.gamma_default)) return fail("a wrong step size", record);
+        slot_event[e.y] = -1;
+        applied[a.event] = 1;
+        return true;
+    }
+
+    bool evaluation(const StripEntry& a, const StripEntry& b, int64_t record, std::vector<std::pair<uint32_t, int64_t>>& finished) {
+        const int64_t k = b.z;
+        if (k >= c.K || a.x >= loaded.size()) return fail("an evaluation of no event", record);
+        const int64_t at = static_cast<int64_t>(a.y - c.seq0);
+        if (at < 0 || at >= static_cast<int64_t>(p.order.size()) || p.order[at] != k) return fail("a wrong sequence number", record);
+        if (loaded[a.x] != at || loaded_in[a.x] >= record) return fail("a team without the rows of its gradient", record);
+        loaded[a.x] = -1;
+        if (evaluated[k] || static_cast<int32_t>(a.z) != c.worker[k]) return fail("a gradient of the wrong worker", record);
+        evaluated[k] = 1;
+        const auto& u = due[c.worker[k]];
+        const int64_t before = k - c.tau[k];
+        const size_t seen = std::lower_bound(u.begin(), u.end(), before, [](const RowUpdate& r, int64_t e) { return r.event < e; }) - u.begin();
+        if (done[c.worker[k]] != seen) return fail("a read of the wrong version", record);
+        const int64_t kp = c.plan->prev[k];
+        if (kp < 0 ? b.x != 0xFFFFFFFFu : !slot_ok(b.x) || slot_event[b.x] != kp || b.y != bits(c.gamma ? c.gamma[kp] : c.gamma_default))
+            return fail("a read compensated with the wrong gradient", record);
+        if (!slot_ok(a.w) || slot_event[a.w] != -1) return fail("a gradient into a slot that is in use", record);
+        for (const auto& f : finished)
+            if (f.first == a.w) return fail("two gradients into one slot", record);
+        if (b.w >= static_cast<uint32_t>(c.strips)) return fail("a loss that no block writes", record);
+        finished.push_back({a.w, k});
+        return true;
+    }
+
+    bool load(const StripEntry& a, const StripEntry& b, int32_t team, int64_t record) {
+        if (a.x >= p.order.size()) return fail("rows of no gradient requested", record);
+        const WorkerData& w = c.data[c.worker[p.order[a.x]]];
+        const uint64_t f = reinterpret_cast<uint64_t>(w.features), t = reinterpret_cast<uint64_t>(w.targets);
+        if (loaded[team] != -1) return fail("rows requested by a team that is not idle", record);
+        if (a.y != w.ld || (static_cast<uint64_t>(a.w) << 32 | a.z) != f || (static_cast<uint64_t>(b.y) << 32 | b.x) != t)
+            return fail("rows of the wrong worker requested", record);
+        loaded[team] = a.x;
+        loaded_in[team] = record;
+        return true;
+    }
+
+    bool run() {
+        const int32_t teams = p.teams, half = teams / 2;
+        if (static_cast<int64_t>(p.recs.size()) != (p.iterations + 3) * p.rec_len || p.rec_len > kStripMaxRec || p.rec_len < 2 + 4 * half)
+            return fail("a table of the wrong size", 0);
+        const int64_t slots = c.renumber ? p.n_slots : c.n_slots;
+        if (c.renumber && p.n_slots > std::max(c.window, 1)) return fail("more slots than the window", 0);
+        due.resize(c.n);
+        done.assign(c.n, 0);
+        slot_event.assign(slots, -1);
+        loaded.assign(teams, -1);
+        loaded_in.assign(teams, -1);
+        evaluated.assign(c.K, 0);
+        applied.assign(c.K, 0);
+        for (int64_t k = 0; k < c.A; ++k) {
+            const int32_t i = c.worker[k], j = c.neighbour[k];
+            due[i].push_back({k, j, false});
+            if (j != i) due[j].push_back({k, i, false});
+            if (c.extra_ptr)
+                for (int64_t q = c.extra_ptr[k]; q < c.extra_ptr[k + 1]; ++q) {
+                    due[c.extra_a[q]].push_back({k, c.extra_b[q], true});
+                    due[c.extra_b[q]].push_back({k, c.extra_a[q], true});
+                }
+        }
+        for (int64_t k = 0; k < c.K; ++k)
+            if (c.carried_slot && c.carried_slot[k] >= 0) {
+                if (!slot_ok(p.slot[k]) || slot_event[p.slot[k]] != -1 || (!c.renumber && p.slot[k] != c.carried_slot[k])) return fail("a pending gradient in the wrong slot", 0);
+                slot_event[p.slot[k]] = k;
+            }
+        std::vector<std::pair<uint32_t, int64_t>> finished;
+        std::vector<int32_t> batch;
+        for (int64_t it = 0; it < p.iterations; ++it) {
+            const StripEntry* rec = &p.recs[it * p.rec_len];
+            for (const auto& f : finished) slot_event[f.first] = f.second;      // the gradients of the record before
+            finished.clear();
+            if (1 + 4 * half + static_cast<int64_t>(rec[0].x) > p.rec_len) return fail("more updates than a record holds", it);
+            for (uint32_t u = 0; u < rec[0].x; ++u) {
+                if (u % kStripBatch == 0) batch.clear();
+                const StripEntry& e = rec[1 + 4 * half + u];
+                if ((e.w & kStripEmpty) == 0 && !update(e, it, batch)) return false;
+            }
+            int32_t evals = 0, loads = 0;
+            for (int32_t t = 0; t < teams; ++t) {
+                if (rec[0].z >> t & 1) {
+                    const StripEntry* e = rec + 1 + 2 * evals;
+                    if (++evals > half || static_cast<int32_t>(e[0].x) != t) return fail("evaluations out of the order of their teams", it);
+                    if (!evaluation(e[0], e[1], it, finished)) return false;
+                    if (rec[0].y >> t & 1) return fail("a team loads and evaluates at once", it);
+                }
+                if (rec[0].y >> t & 1) {
+                    const StripEntry* e = rec + 1 + 2 * half + 2 * loads;
+                    if (++loads > half) return fail("more loads than a record holds", it);
+                    if (!load(e[0], e[1], t, it)) return false;
+                }
+            }
+        }
+        if (!finished.empty()) return fail("gradients left unfinished", p.iterations);
+        for (int64_t k = 0; k < c.K; ++k) {
+            const bool carried = c.carried_slot && c.carried_slot[k] >= 0;
+            if (k < c.A ? !applied[k] : (c.plan->r_round[k] >= 0 || carried) && slot_event[p.slot[k]] != k) return fail("an event left out", p.iterations);
+            if (evaluated[k] != (c.plan->r_round[k] >= 0)) return fail("a gradient left out", p.iterations);
+        }
+        for (int32_t r = 0; r < c.n; ++r)
+            if (done[r] != due[r].size()) return fail("an averaging left out", p.iterations);
+        return true;
+    }
+};
+
+}  // namespace
+
+bool verify_strips(const StripCall& c, const StripProgram& p, std::string& err) { return Checker{c, p, err, {}, {}, {}, {}, {}, {}, {}}.run(); }
+
 }  // namespace adpsgd_impl

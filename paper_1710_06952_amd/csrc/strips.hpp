@@ -3,6 +3,7 @@
 #pragma once
 
 #include <algorithm>
+#include <string>
 
 #include "internal.hpp"
 
@@ -72,6 +73,11 @@ inline int32_t strip_window(int64_t T_max, bool lds_state, int64_t slots_fit, in
 }
 // false: the events do not come in any order (the plan is not one of this schedule), or there is no slot for a gradient
 bool build_strips(const StripCall& c, int32_t teams, StripProgram& out);
+// Executes the records on paper and compares with the serial semantics (ADPSGD_FLAG_VERIFY_PLAN): every read sees exactly
+// the updates before its logical time and the pending gradient it is compensated with, every update finds its gradient and
+// keeps the order of its rows, a batch of updates names a row once, minibatch rows are requested before they are used, by a
+// team that is idle, and no slot is given away early.
+bool verify_strips(const StripCall& c, const StripProgram& p, std::string& err);
 
 struct StripArgs {
     float* X;

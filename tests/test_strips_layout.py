@@ -1,7 +1,6 @@
-"""CPU: the layout of a call as one persistent launch (csrc/strips.cpp) against the serial semantics: random schedules
-with stale reads, carried and looked-ahead events, extra pairs, the wait-free variant, few slots and all numbers of
-teams are executed entry by entry (strips_layout_check.cpp): every read sees exactly the updates before it, every update
-finds its gradient, batches name a row once, rows are requested before they are used, slots are not given away."""
+"""CPU: the layouts of calls that go in one launch (csrc/strips.cpp, pack_columns) against the serial semantics: random
+schedules through the checks that ADPSGD_FLAG_VERIFY_PLAN runs (verify_strips, verify_columns), and planted mistakes that
+these have to find (strips_layout_check.cpp)."""
 import os
 import subprocess
 import sys
