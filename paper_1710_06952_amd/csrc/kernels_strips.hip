@@ -191,6 +191,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     const int team = min(t / kTeamHelpers, kTeams - 1), m = t / kTeamHelpers < kTeams ? t % kTeamHelpers : kStripHelpers;
     const int64_t col = col0 + t;
     const bool inside = col < a.d;
+    const uint32_t inside_bits = inside ? 0xFFFFFFFFu : 0u;      // a point is zero beyond d, whatever infinite coefficients have left there
     float* const xs = kLds ? state_s + t : a.X + col;
     float* const vs = kLds ? xs + static_cast<int64_t>(a.n) * kStripCols : a.V + col;
     float* const gs = kLds ? state_s + t + slots_at : a.slots + col;
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                         const float step = gs[ev2[i].x * ld] * __uint_as_float(ev2[i].y);
                         x[i] = x[i] - step;
                     }
-                    xh_s[ev[i].x][t] = x[i];
+                    xh_s[ev[i].x][t] = __uint_as_float(__float_as_uint(x[i]) & inside_bits);
                 }
             }
         }
