@@ -220,6 +220,18 @@ const char* adpsgd_last_error(const adpsgd_t* h);
 enum { ADPSGD_ROUTE_AUTO = 0, ADPSGD_ROUTE_ROUNDS = 1 };
 int adpsgd_set_route(adpsgd_t* h, int32_t route);
 
+/* How long the blocks of a call in one launch wait for each other (linear models).
+ *   assembly_us     the state is touched only once all blocks of the launch are on the device.  While other work holds
+ *                   compute units for longer than this, one block executes the call by itself, which is slow but gives the
+ *                   same results within rounding.  0: always so.  Default 10 000 000.
+ *                   Outside [0, 2^31): ADPSGD_ERR_ARG.
+ *   lose_exchange   Once all blocks are on the device they exchange partial sums.  One that does not find a sum after 2^21
+ *                   polls (about a second: a fault of the device) gives the launch up and the models are undefined, which
+ *                   every later call on the handle that reads or advances them reports (ADPSGD_ERR_HIP) until
+ *                   adpsgd_set_models.  Non-zero: every launch ends like that, to see what a program does about it.
+ * Applies to the calls from now on. */
+int adpsgd_set_wait_limits(adpsgd_t* h, int64_t assembly_us, int32_t lose_exchange);
+
 /* Local data of one worker: D_i is the uniform distribution over its rows
  * (Strategy-2 of the remark in Sec. 3.1).
  *   features: device, rows x ld elements, 16-byte aligned, ld a multiple of 4 (fp32)

@@ -156,7 +156,9 @@ void settle_strips(adpsgd_t* h) {
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
         hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && cooperative != 0 &&
         strip_blocks(h->d) <= std::min(cus, kStripGroups * kStripGroupBlocks) && h->exchange.reserve(words) == hipSuccess &&
-        h->exchange_status.reserve(sizeof(int)) == hipSuccess && hipMemset(h->exchange.p, 0, h->exchange.cap) == hipSuccess &&      // no sequence number
+        h->exchange_status.reserve(sizeof(int)) == hipSuccess &&
+        (!lds_state || h->alone_slots.reserve(static_cast<size_t>(strip_window(h->o.T_max, true, strip_lds_slots(h), h->n_slots)) * h->o.ldx * sizeof(float)) == hipSuccess) &&
+        hipMemset(h->exchange.p, 0, h->exchange.cap) == hipSuccess &&      // no sequence number
         hipStreamSynchronize(nullptr) == hipSuccess) {
         *static_cast<int*>(h->exchange_status.p) = 0;
         h->strip_units = std::min(cus, kStripGroups * kStripGroupBlocks);
@@ -165,6 +167,7 @@ void settle_strips(adpsgd_t* h) {
     (void)hipGetLastError();
     h->exchange.release();
     h->exchange_status.release();
+    h->alone_slots.release();
 }
 
 }  // namespace adpsgd_impl
@@ -237,6 +240,7 @@ extern "C" int adpsgd_create(adpsgd_t** out, const adpsgd_graph_t* graph, int64_
                 if (u.done) (void)hipEventDestroy(u.done);
             h->exchange.release();
             h->exchange_status.release();
+            h->alone_slots.release();
             return hip_fail(nullptr, e, "create: hipEventCreate");
         }
     }
@@ -261,6 +265,7 @@ extern "C" void adpsgd_destroy(adpsgd_t* h) {
     h->sync_other.release();
     h->exchange.release();
     h->exchange_status.release();
+    h->alone_slots.release();
     delete h;
 }
 
@@ -867,7 +872,7 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     const size_t bytes_recs = prog.recs.size() * sizeof(StripEntry), off_idx = bytes_recs;
     const size_t off_carry = off_idx + prog.order.size() * M * sizeof(int32_t);
     const size_t off_count = (off_carry + carry.size() * sizeof(int32_t) + 63) & ~size_t(63);
-    const size_t total = off_count + kStripCounters * sizeof(uint32_t);
+    const size_t off_args = off_count + kStripCounters * sizeof(uint32_t), total = off_args + sizeof(StripArgs);
     TableSet& T = h->tables[h->next_table];
     h->next_table ^= 1;
     if (T.in_flight) {
@@ -885,7 +890,6 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     for (size_t q = 0; q < prog.order.size(); ++q)
         std::memcpy(idx + q * M, c.s->batch_idx + prog.order[q] * static_cast<int64_t>(M), static_cast<size_t>(M) * sizeof(int32_t));
     if (!carry.empty()) std::memcpy(stage + off_carry, carry.data(), carry.size() * sizeof(int32_t));
-    HIP_TRY(h, hipMemcpyAsync(T.dev.p, T.stage.p, total, hipMemcpyHostToDevice, h->stream));
     const char* dev = static_cast<const char*>(T.dev.p);
     StripArgs a{};
     a.X = h->o.X;
@@ -917,6 +921,13 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     a.weight_decay = h->o.weight_decay;
     a.loss = loss;
     a.status = static_cast<int*>(h->exchange_status.p);
+    a.alone_slots = static_cast<float*>(h->alone_slots.p);
+    a.seq0 = h->exchange_seq + 1;
+    a.wait_ticks = static_cast<uint64_t>(h->assembly_us) * kClockTicksPerUs;
+    a.lose = h->lose_exchange;
+    a.self = reinterpret_cast<const StripArgs*>(dev + off_args);
+    std::memcpy(stage + off_args, &a, sizeof(a));
+    HIP_TRY(h, hipMemcpyAsync(T.dev.p, T.stage.p, total, hipMemcpyHostToDevice, h->stream));
     hipEvent_t e0, e1;
     int rc = begin_timing(h, e0, e1);
     if (rc != ADPSGD_OK) return rc;
@@ -1010,6 +1021,14 @@ extern "C" int adpsgd_run_events_with(adpsgd_t* h, const adpsgd_schedule_t* s, a
         return fail(h, ADPSGD_ERR_STATE, "run_events_with: the handle was not created with ADPSGD_MODEL_EXTERNAL");
     if (!fn) return fail(h, ADPSGD_ERR_ARG, "run_events_with: fn is NULL");
     return run_events_guarded(h, s, nullptr, fn, user);
+}
+
+extern "C" int adpsgd_set_wait_limits(adpsgd_t* h, int64_t assembly_us, int32_t lose_exchange) {
+    if (!h) return ADPSGD_ERR_ARG;
+    if (assembly_us < 0 || assembly_us > 0x7FFFFFFF) return fail(h, ADPSGD_ERR_ARG, "set_wait_limits: assembly_us outside [0, 2^31)");
+    h->assembly_us = assembly_us;
+    h->lose_exchange = lose_exchange != 0;
+    return ADPSGD_OK;
 }
 
 extern "C" int adpsgd_set_route(adpsgd_t* h, int32_t route) {

@@ -11,6 +11,7 @@
 
 namespace adpsgd_impl {
 
+typedef float v2f __attribute__((ext_vector_type(2)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef uint16_t v4h __attribute__((ext_vector_type(4)));

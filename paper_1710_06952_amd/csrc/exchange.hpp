@@ -8,8 +8,12 @@
 // XCD and 0.64 us across the chip (0.9 and 1.2 us for all of 16 or 256 blocks to have the words of all).  So the blocks
 // of an XCD (hardware register XCC_ID) form a group, and up to 32 strips are given to the blocks of a single XCD, of one
 // block per compute unit launched.  Partial sums are added in a fixed order of the groups and blocks.
-// Every block waits for all others, so the launches are cooperative (all blocks resident or none), and every wait is
-// bounded: after kSpinLimit polls the block reports it and waits no more.
+// Every block waits for all others.  A cooperative launch makes sure that the grid fits the device, not that the device is
+// free: work of other streams or processes may hold compute units while the first blocks are there.  So the blocks agree
+// once, before any of them touches the state (assemble): all have arrived, or the first one that has
+// waited longer than the caller's limit goes alone, and then executes the whole call by itself while all others
+// leave.  Once all have arrived they are resident and every further wait ends; it is bounded by a number of polls
+// all the same, after which the block reports the launch as lost.
 #pragma once
 
 #include "device_common.hpp"
@@ -93,18 +97,36 @@ __device__ __forceinline__ float wave_sums(const float (&v)[8], int lane) {
 
 // What a block learns about the others: its group and rank in it.
 struct Assembly {
-    int32_t strip, group, rank, group_blocks, groups;     // strip < 0: no strip
+    int32_t strip, group, rank, group_blocks, groups;     // strip < 0: no strip, the block leaves
+    bool alone;                                           // ... or executes the call by itself
 };
-// The blocks count themselves per XCD and wait until all have.  Which columns form a group depends on the number of
-// strips alone (so the order of the sums does); if the XCDs do not have the blocks for it, the groups are formed in the
-// order of arrival.
-__device__ __forceinline__ Assembly assemble(unsigned int* counters, int blocks, int group_size, bool& given_up) {
+constexpr unsigned int kAlone = 0x80000000u;
+// The blocks count themselves, per XCD and in counters[8], until all are there or kAlone is set beside the count: both in
+// one word, so only one of them can come first.  wait_ticks: how long they wait at most, in ticks of the constant clock, 0:
+// one goes alone in any case.  Which columns form a group depends on the number of strips alone (so the order of the sums
+// does); if the XCDs do not have the blocks for it, the groups are formed in the order of arrival.
+__device__ __forceinline__ Assembly assemble(unsigned int* counters, int blocks, int group_size, uint64_t wait_ticks) {
+    const uint64_t start = wall_clock64();
     const int xcd = __builtin_amdgcn_s_getreg((3 << 11) | 20) & 7;        // HW_REG_XCC_ID, bits 3..0
     const int rank = static_cast<int>(__hip_atomic_fetch_add(counters + xcd, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    const int arrival = static_cast<int>(__hip_atomic_fetch_add(counters + 8, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT));
-    uint32_t spins = 0;
-    while (__hip_atomic_load(counters + 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != gridDim.x && ++spins < kSpinLimit) {}
-    given_up = spins >= kSpinLimit;
+    const unsigned int before = __hip_atomic_fetch_add(counters + 8, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    const int arrival = static_cast<int>(before & ~kAlone);
+    Assembly as;
+    as.alone = false;
+    unsigned int seen = before + 1;
+    while ((seen & kAlone) == 0 && (seen != gridDim.x || wait_ticks == 0)) {
+        if (wall_clock64() - start >= wait_ticks &&
+            __hip_atomic_compare_exchange_strong(counters + 8, &seen, seen | kAlone, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+            as.alone = true;
+            break;
+        }
+        seen = __hip_atomic_load(counters + 8, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (as.alone || (seen & kAlone) != 0) {
+        as.strip = -1;
+        return as;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");       // the counts of all blocks
     const int groups = (blocks + group_size - 1) / group_size;
     int count[kStripGroups], chosen = -1;
     bool enough = true;
@@ -114,7 +136,6 @@ __device__ __forceinline__ Assembly assemble(unsigned int* counters, int blocks,
         if (chosen < 0 && count[x] >= blocks) chosen = x;
         if (x < groups) enough &= count[x] >= min(group_size, blocks - x * group_size);
     }
-    Assembly as;
     as.groups = groups;
     const bool placed = groups == 1 ? chosen >= 0 : enough;
     const int place = !placed ? arrival : groups > 1 ? (rank < group_size ? xcd * group_size + rank : blocks) : xcd == chosen ? rank : blocks;

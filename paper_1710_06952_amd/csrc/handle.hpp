@@ -51,6 +51,7 @@ struct PendingEvent {
 
 constexpr int64_t kStreamingThreshold = 256ll << 20;
 constexpr int32_t kMaxSlots = 4096;
+constexpr int64_t kAssemblyUs = 10 * 1000 * 1000;      // default of adpsgd_set_wait_limits
 
 }  // namespace adpsgd_impl
 
@@ -78,7 +79,10 @@ struct adpsgd {
     int32_t strip_units = 0;              // linear models in one launch: compute units for it, 0: this handle goes by rounds
     adpsgd_impl::DevBuf exchange;         // ... words the blocks exchange ...
     uint32_t exchange_seq = 0;            // ... the sequence number of the last gradient
-    adpsgd_impl::HostBuf exchange_status; // ... and a word the kernel sets when a wait had to be given up
+    adpsgd_impl::HostBuf exchange_status; // ... a word the kernel sets when a wait had to be given up ...
+    adpsgd_impl::DevBuf alone_slots;      // ... and slots for a block that executes a call alone
+    int64_t assembly_us = adpsgd_impl::kAssemblyUs;      // adpsgd_set_wait_limits ...
+    bool lose_exchange = false;                          // ...
     adpsgd_stats_t stats{};
     std::vector<hipEvent_t> ev_pool;                       // profiling events
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_fused, ev_grad;

@@ -45,9 +45,115 @@ struct StripParams {
 
 __device__ __forceinline__ float dot4(v4f a, v4f b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
 
+// Coefficient (times gscale) and loss of a sample from its dot product with the point (square: |x^|^2, for the loss).
+__device__ __forceinline__ v2f strip_coefficient(const StripArgs& a, float dot, float target, float square) {
+    float coef, loss;
+    if (a.model == ADPSGD_MODEL_LSQ) {
+        const float r = dot - target;               // a.x - b
+        loss = 0.5f * r * r;
+        coef = r;
+    } else {
+        const float s = -target * dot;              // F = log(1 + e^s) + reg
+        loss = a.loss ? (s > 0.0f ? s + log1pf(expf(-s)) : log1pf(expf(s))) + 0.5f * a.lambda * square : 0.0f;
+        coef = -target / (1.0f + expf(-s));         // -y sigmoid(s)
+    }
+    return v2f{coef * a.gscale, loss};
+}
+
 // LDS offsets fit 32 bits, places in global memory need 64
 template <bool kLds> struct Pitch { typedef uint32_t type; };
 template <> struct Pitch<false> { typedef int64_t type; };
+
+// The whole call by one block, with the state in its global places: what a launch does whose blocks could not all become
+// resident in time.  Slow (one compute unit reads all minibatch rows, twice) but complete, and it needs no other block.
+// Columns belong to threads throughout; only the points of evaluation, which lie in the gradients' slots until these
+// replace them, are read across threads.  A function of its own with its arguments in device memory: inlined, it cost the
+// kernel's rows registers (M = 50: 1.72 -> 2.01 ms).
+template <bool kMom>
+__device__ __attribute__((noinline)) void run_alone(const StripArgs* args, int samples, v4u (*team_rows)[2], float* dots, float* coef_s, float* loss_s) {
+    const StripArgs& a = *args;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, M = a.M, half = a.teams / 2;
+    float* const slots = a.lds_state ? a.alone_slots : a.slots;
+    for (int i = 0; i < a.n_in; ++i)
+        for (int64_t c = tid; c < a.d; c += kStripThreads) slots[a.carry[2 * i] * a.ld + c] = a.slots[a.carry[2 * i + 1] * a.ld + c];
+    for (int it = 0; it < a.iterations; ++it) {
+        const v4u* rec = reinterpret_cast<const v4u*>(a.recs) + static_cast<int64_t>(it) * a.rec_len;
+        const v4u head = rec[0];
+        for (int64_t c = tid; c < a.d; c += kStripThreads)
+            for (uint32_t u = 0; u < head.x; ++u) {
+                const v4u op = rec[1 + 4 * half + u];
+                if ((op.w & kStripEmpty) != 0) continue;
+                float* const xi = a.X + static_cast<int64_t>(op.x & 0xFFFFu) * a.ld + c;
+                float* const xj = a.X + static_cast<int64_t>(op.x >> 16) * a.ld + c;
+                const bool average_only = (op.w & kStripAverage) != 0;
+                const float g = average_only ? 0.0f : slots[op.y * a.ld + c];
+                float ni, nj;
+                if (kMom) {
+                    float* const v = a.V + static_cast<int64_t>(op.x & 0xFFFFu) * a.ld + c;
+                    float vn;
+                    average_then_apply_momentum(*xi, *xj, g, *v, __uint_as_float(op.z), a.momentum, a.weight_decay, ni, nj, vn);
+                    if (!average_only) *v = vn;
+                } else {
+                    average_then_apply(*xi, *xj, g, __uint_as_float(op.z), ni, nj);
+                }
+                *xj = nj;
+                *xi = average_only ? nj : ni;
+            }
+        const int evals = __popc(head.z);
+        for (int i = 0; i < evals; ++i) {
+            const v4u ev = rec[1 + 2 * i], ev2 = rec[2 + 2 * i];
+            float* const point = slots + ev.w * a.ld;
+            for (int64_t c = tid; c < a.d; c += kStripThreads) {
+#pragma clang fp contract(off)
+                float x = a.X[ev.z * a.ld + c];
+                if (ev2.x != 0xFFFFFFFFu) {
+                    const float step = slots[ev2.x * a.ld + c] * __uint_as_float(ev2.y);
+                    x = x - step;
+                }
+                point[c] = x;
+            }
+            __syncthreads();
+            const v4u f = team_rows[ev.x][0], g = team_rows[ev.x][1];
+            const float* const features = reinterpret_cast<const float*>(static_cast<uint64_t>(f.w) << 32 | f.z);
+            const float* const targets = reinterpret_cast<const float*>(static_cast<uint64_t>(g.y) << 32 | g.x);
+            const int32_t* const index = a.idx + static_cast<int64_t>(ev.y - a.seq0) * M;
+            for (int m = wave; m < samples; m += kStripThreads / 64) {
+                const float* const row = m < M ? features + static_cast<int64_t>(index[m]) * f.y : point;      // the last: |x^|^2
+                double z = 0.0;
+                for (int64_t c = lane; c < a.d; c += 64) z += static_cast<double>(row[c]) * static_cast<double>(point[c]);
+                z = wave_sum(z);
+                if (lane == 0) dots[m] = static_cast<float>(z);
+            }
+            __syncthreads();
+            if (tid < M) {
+                const v2f r = strip_coefficient(a, dots[tid], targets[index[tid]], samples > M ? dots[M] : 0.0f);
+                coef_s[tid] = r.x;
+                loss_s[tid] = r.y;
+            }
+            __syncthreads();
+            if (a.loss && tid == 0) {
+                float sum = 0.0f;
+                for (int m = 0; m < M; ++m) sum += loss_s[m];
+                a.loss[ev2.z] = sum * a.gscale;
+            }
+            const float regularise = a.model == ADPSGD_MODEL_LOGREG ? a.lambda * a.gscale * static_cast<float>(M) : 0.0f;
+            for (int64_t c = tid; c < a.d; c += kStripThreads) {
+                double sum = 0.0;
+                for (int m = 0; m < M; ++m) sum += static_cast<double>(coef_s[m]) * static_cast<double>(features[static_cast<int64_t>(index[m]) * f.y + c]);
+                point[c] = static_cast<float>(sum) + (a.model == ADPSGD_MODEL_LOGREG ? point[c] * regularise : 0.0f);
+            }
+            __syncthreads();
+        }
+        if (tid < a.teams && (head.y >> tid & 1) != 0) {
+            const v4u* e = rec + 1 + 2 * half + 2 * __popc(head.y & ((1u << tid) - 1));
+            team_rows[tid][0] = e[0];
+            team_rows[tid][1] = e[1];
+        }
+        __syncthreads();
+    }
+    for (int i = a.n_in; i < a.n_in + a.n_out; ++i)
+        for (int64_t c = tid; c < a.d; c += kStripThreads) a.slots[a.carry[2 * i + 1] * a.ld + c] = slots[a.carry[2 * i] * a.ld + c];
+}
 
 // kTeams teams of 12 / kTeams wavefronts, kRows rows per wavefront; kLds: the strip's models, momentum buffers and
 // slots in LDS, otherwise in their global places (every entry is touched by one thread only, its column's).
@@ -70,17 +176,16 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     __shared__ float coef_s[kStripHelpers];
     __shared__ float loss_s[kStripHelpers];
     __shared__ Assembly assembly_s;
-    __shared__ int given_up_s;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.M, S = p.samples;
-    if (tid == 0) {
-        bool lost;
-        assembly_s = assemble(a.counters, p.blocks, p.group_size, lost);
-        given_up_s = lost;
-    }
+    if (tid == 0) assembly_s = assemble(a.counters, p.blocks, p.group_size, a.wait_ticks);
     __syncthreads();
     const Assembly as = assembly_s;
+    if (as.alone) {
+        run_alone<kMom>(a.self, S, reinterpret_cast<v4u(*)[2]>(&rec_s[0][0]), target_s, coef_s, loss_s);
+        return;
+    }
     const int block = __builtin_amdgcn_readfirstlane(as.strip);
     if (block < 0) return;
     const int64_t col0 = static_cast<int64_t>(block) * kStripCols;
@@ -266,7 +371,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         rec_s[1][lane] = recs[a.rec_len];
         ahead = recs[2 * a.rec_len];
     }
-    bool given_up = given_up_s != 0;
+    bool given_up = a.lose;
     __syncthreads();
     fetch_index(rec_s[0]);
     put_addresses(rec_s[0], 0);
@@ -417,19 +522,9 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                     to = place[u];
                 }
             if (sub < kWordsInFlight && to != kStripHelpers) {
-                const float target = target_s[to];
-                float coef, loss;
-                if (a.model == ADPSGD_MODEL_LSQ) {
-                    const float r = dot - target;               // a.x - b
-                    loss = 0.5f * r * r;
-                    coef = r;
-                } else {
-                    const float s = -target * dot;              // F = log(1 + e^s) + reg
-                    loss = a.loss ? (s > 0.0f ? s + log1pf(expf(-s)) : log1pf(expf(s))) + 0.5f * a.lambda * square : 0.0f;
-                    coef = -target / (1.0f + expf(-s));         // -y sigmoid(s)
-                }
-                coef_s[to] = coef * a.gscale;
-                loss_s[to] = loss;
+                const v2f r = strip_coefficient(a, dot, target_s[to], square);
+                coef_s[to] = r.x;
+                loss_s[to] = r.y;
             }
         }
         __syncthreads();

@@ -20,6 +20,7 @@ constexpr int kStripMaxRec = 64;         // entries of a record
 constexpr int64_t kStripMaxD = kStripGroups * kStripGroupBlocks * kStripCols;    // at most one block per compute unit
 constexpr int32_t kStripMaxM = 128;
 constexpr int kStripLdsBytes = 160 * 1024;
+constexpr uint64_t kClockTicksPerUs = 100;      // the constant clock of the device, 100 MHz on gfx950
 
 // A record is one iteration of the kernel: a header, two entries for each of up to teams / 2 evaluations, two for each of
 // as many loads (both in the order of their teams), then the updates.  All fields are 32-bit words.
@@ -92,6 +93,8 @@ struct StripArgs {
     const int32_t* carry;    // device: n_in + n_out pairs (slot of the call, slot of the workspace)
     int32_t n_in, n_out;
     float* slots;            // the workspace
+    float* alone_slots;      // lds_state: place of the call's slots, n_lds_slots x ld, for a block that executes the call alone
+    uint32_t seq0;           // sequence number of the first gradient
     int32_t n_lds_slots;
     bool lds_state;          // models, momentum buffers and slots of the strip live in LDS
     unsigned long long* words;    // exchange memory: strip_exchange_bytes
@@ -100,6 +103,9 @@ struct StripArgs {
     float gscale, lambda, momentum, weight_decay;
     float* loss;             // device, indexed by event, or nullptr
     int* status;             // pinned host word, set when an exchange never completes
+    const StripArgs* self;   // device: these arguments, for a block that executes the call alone
+    uint64_t wait_ticks;     // how long the blocks wait until all are resident (constant clock); then one goes alone
+    bool lose;               // wait for no word of the exchange: the launch ends as lost
 };
 int32_t strip_blocks(int64_t d);
 int32_t strip_group_size(int64_t d);

@@ -117,3 +117,86 @@ def test_two_engines_on_two_streams_share_the_chip(P):
         assert np.array_equal(e.get_models(), want)
         e.close()
     alone.close()
+
+
+# where not all blocks of a launch become resident in time, one executes the call by itself; a limit of zero makes it do so
+@pytest.mark.parametrize("model,n,d,M,K,T,mu,comp", [
+    ("lsq", 6, 255, 8, 80, 4, 0.0, False), ("logreg", 7, 1030, 16, 100, 4, 0.9, True), ("lsq", 8, 2100, 33, 100, 3, 0.9, False),
+    ("logreg", 5, 9001, 65, 40, 3, 0.0, False), ("lsq", 16, 1101, 6, 300, 140, 0.0, False), ("logreg", 3, 65_535, 12, 30, 6, 0.9, True)])
+def test_one_block_executes_a_call_alone(P, model, n, d, M, K, T, mu, comp):
+    print("alone %s n=%d d=%d M=%d mu=%g comp=%d" % (model, n, d, M, mu, comp), flush=True)
+    rows = max(M, 24)
+    g = ring_graph(n)
+    make = lsq_data if model == "lsq" else logreg_data
+    feats, targs, _ = make(n, rows, d, seed=5, **({"feature_var": 1.0 / d} if model == "lsq" else {}))
+    omodel, base, lam = (oracle.MODEL_LSQ, 0.3, 0.0) if model == "lsq" else (oracle.MODEL_LOGREG, 0.5, 1e-3)
+    base *= 0.1 if mu else 1.0
+    wd = 1e-3 if mu else 0.0
+    sched = oracle.make_schedule(g, K, seed=6, T_max=T, M=M, rows=[rows] * n)
+    sched["neighbour"] = with_identity_events(sched["worker"], sched["neighbour"], 0.1, seed=1)
+    sched["gamma"] = (base * (1 + np.arange(K) % 3)).astype(np.float32)
+    if not comp and n >= 6:
+        sched["extra_pairs"] = random_extra_pairs(g, sched["worker"], sched["neighbour"], max_extra=1, seed=2)
+    x0 = np.random.default_rng(3).standard_normal((n, d)).astype(np.float32)
+    eng = P.Engine(g, d, model, M=M, gamma=base, lam=lam, T_max=T, momentum=mu, weight_decay=wd, local_compensation=comp, verify_plan=True)
+    eng.load_data(feats, targs)
+    eng.set_models(x0, broadcast=False)
+    eng.h.set_wait_limits(assembly_us=0)
+    first = True
+
+    def back_and_forth(_done):        # gradients pending from a block alone are applied by all of them, and the other way
+        nonlocal first
+        first = not first
+        eng.h.set_wait_limits(assembly_us=0 if first else 10_000_000)
+
+    eng.run_events_in_pieces(sched, -(-K // 4), between=back_and_forth)
+    assert eng.get_stats()["fused_launches"] == 4 and eng.get_stats()["grad_launches"] == 0
+    Xr, Vr = x0.copy(), np.zeros_like(x0) if mu else None
+    kw = dict(M=M, gscale=1.0 / M, lam=lam, features=feats, targets=targs, gamma_k=sched["gamma"], extra_pairs=sched.get("extra_pairs"),
+              momentum=mu, weight_decay=wd, local_compensation=comp, want_loss=True)
+    oracle.run_events(Xr, sched, omodel, base, V=Vr, **kw)
+    assert rel_err(eng.get_models(), Xr) <= TOL
+    if mu:
+        assert rel_err(eng.get_momentum(), Vr) <= TOL
+    eng.h.set_wait_limits(assembly_us=0)             # a call of its own, with losses
+    eng.run_events(sched, want_loss=True)
+    r = oracle.run_events(Xr, sched, omodel, base, V=Vr, **kw)
+    assert np.allclose(eng.get_loss(), r["loss"], rtol=2e-4, atol=1e-6)
+    assert rel_err(eng.get_models(), Xr) <= TOL
+    assert not eng.X[:, d:].any()
+    with pytest.raises(P.AdpsgdError):
+        eng.h.set_wait_limits(assembly_us=-1)
+    eng.close()
+
+
+@pytest.mark.parametrize("assembly_us", [10_000_000, 500])
+def test_a_busy_device_delays_a_call_or_leaves_it_to_one_block(P, assembly_us):
+    """A launch beside some 50 ms of another handle's work: it waits, or, with a short limit, may be executed by one block."""
+    import torch
+    print("busy device, limit %d us" % assembly_us, flush=True)
+    n, d, M, K = 8, 20_001, 12, 60
+    g = ring_graph(n)
+    feats, targs, _ = lsq_data(n, 32, d, seed=8, feature_var=1.0 / d)
+    sched = oracle.make_schedule(g, K, seed=9, T_max=4, M=M, rows=[32] * n)
+    x0 = np.random.default_rng(1).standard_normal((n, d)).astype(np.float32)
+    other = torch.cuda.Stream()
+    with torch.cuda.stream(other):
+        busy = P.Engine(ring_graph(64), 4_000_000, "synth", gamma=0.1, T_max=4, synth_std=0.1, synth_seed=1)
+        busy.set_models(np.zeros(4_000_000, np.float32))
+    long = oracle.make_schedule(ring_graph(64), 15_000, seed=2, T_max=4)
+    eng = P.Engine(g, d, "lsq", M=M, gamma=0.3, T_max=4)
+    eng.load_data(feats, targs)
+    eng.set_models(x0, broadcast=False)
+    eng.h.set_wait_limits(assembly_us)
+    torch.cuda.synchronize()
+    busy.run_events(long)
+    for _ in range(2):
+        eng.run_events(sched)
+    X = eng.get_models()
+    Xr = x0.copy()
+    for _ in range(2):
+        oracle.run_events(Xr, sched, oracle.MODEL_LSQ, 0.3, M=M, gscale=1.0 / M, features=feats, targets=targs)
+    assert rel_err(X, Xr) <= TOL
+    torch.cuda.synchronize()
+    busy.close()
+    eng.close()
