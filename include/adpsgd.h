@@ -232,6 +232,10 @@ int adpsgd_set_route(adpsgd_t* h, int32_t route);
  * Applies to the calls from now on. */
 int adpsgd_set_wait_limits(adpsgd_t* h, int64_t assembly_us, int32_t lose_exchange);
 
+/* Waits for the handle's work.  Afterwards what the caller reads through its own pointers (the models, a loss array) is
+ * there, and a launch that was given up (adpsgd_set_wait_limits) is reported: ADPSGD_ERR_HIP. */
+int adpsgd_synchronize(adpsgd_t* h);
+
 /* Local data of one worker: D_i is the uniform distribution over its rows
  * (Strategy-2 of the remark in Sec. 3.1).
  *   features: device, rows x ld elements, 16-byte aligned, ld a multiple of 4 (fp32)

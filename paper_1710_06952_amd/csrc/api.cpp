@@ -83,7 +83,7 @@ hipEvent_t take_event(adpsgd_t* h) {
 int check_exchange(adpsgd_t* h) {
     const volatile int* status = static_cast<const volatile int*>(h->exchange_status.p);
     if (!status || *status == 0) return ADPSGD_OK;
-    return fail(h, ADPSGD_ERR_HIP, "run_events: the blocks of a launch lost each other, the models are undefined");
+    return fail(h, ADPSGD_ERR_HIP, "the blocks of a launch lost each other, the models are undefined (set_models replaces them)");
 }
 
 // Fold the timings of finished launches into the statistics (synchronises the stream).
@@ -293,7 +293,7 @@ extern "C" int adpsgd_load_data(adpsgd_t* h, int32_t worker, const void* feature
 extern "C" int adpsgd_set_models(adpsgd_t* h, const float* x, int64_t ld_in, int32_t on_device) {
     if (!h || !x) return h ? fail(h, ADPSGD_ERR_ARG, "set_models: x is NULL") : ADPSGD_ERR_ARG;
     if (ld_in != 0 && ld_in < h->d) return fail(h, ADPSGD_ERR_ARG, "set_models: ld_in < d");
-    if (check_exchange(h) != ADPSGD_OK) {      // what an incomplete launch left is replaced
+    if (h->strip_units > 0) {                  // what a launch that was given up has left is replaced; one may still be under way
         HIP_TRY(h, hipStreamSynchronize(h->stream));
         *static_cast<int*>(h->exchange_status.p) = 0;
     }
@@ -1036,6 +1036,12 @@ extern "C" int adpsgd_set_route(adpsgd_t* h, int32_t route) {
     if (route != ADPSGD_ROUTE_AUTO && route != ADPSGD_ROUTE_ROUNDS) return fail(h, ADPSGD_ERR_ARG, "set_route: unknown route");
     h->route = route;
     return ADPSGD_OK;
+}
+
+extern "C" int adpsgd_synchronize(adpsgd_t* h) {
+    if (!h) return ADPSGD_ERR_ARG;
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    return check_exchange(h);
 }
 
 extern "C" int adpsgd_get_stats(adpsgd_t* h, adpsgd_stats_t* out) {

@@ -42,6 +42,7 @@ extern "C" int adpsgd_get_bf16_models(adpsgd_t* h, uint16_t* out, int64_t ld_out
 extern "C" int adpsgd_get_mean_model(adpsgd_t* h, float* out, int32_t on_device) {
     if (!h) return ADPSGD_ERR_ARG;
     if (!out) return fail(h, ADPSGD_ERR_ARG, "get_mean_model: out is NULL");
+    if (const int rc = check_exchange(h)) return rc;
     float* dst = out;
     if (!on_device) {
         HIP_TRY(h, hipStreamSynchronize(h->stream));
@@ -52,7 +53,7 @@ extern "C" int adpsgd_get_mean_model(adpsgd_t* h, float* out, int32_t on_device)
     if (on_device) return ADPSGD_OK;      // ready in stream order: the caller goes on working on the stream
     HIP_TRY(h, hipMemcpyAsync(out, dst, static_cast<size_t>(h->d) * 4, hipMemcpyDeviceToHost, h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
-    return ADPSGD_OK;
+    return check_exchange(h);
 }
 
 namespace {
@@ -68,6 +69,7 @@ int consensus(adpsgd_t* h, const double* p, double* out) {
         if (std::fabs(psum - 1.0) > 1e-9) return fail(h, ADPSGD_ERR_ARG, "consensus_distance: the weights do not sum to 1");
     }
     HIP_TRY(h, hipStreamSynchronize(h->stream));
+    if (const int rc = check_exchange(h)) return rc;
     const int32_t blocks = consensus_blocks(h->d);
     // diag buffer: [partials][result][weights]
     HIP_TRY(h, h->diag.reserve(static_cast<size_t>(blocks + 1 + (p ? h->n : 0)) * sizeof(double)));
@@ -99,6 +101,7 @@ extern "C" int adpsgd_consensus_distance_weighted(adpsgd_t* h, const double* p, 
 extern "C" int adpsgd_consensus_distance_static(adpsgd_t* h, const double* p, double* out_device) {
     if (!h) return ADPSGD_ERR_ARG;
     if (!out_device) return fail(h, ADPSGD_ERR_ARG, "consensus_distance_static: out_device is NULL");
+    if (const int rc = check_exchange(h)) return rc;
     const int32_t blocks = consensus_blocks(h->d);
     if (blocks > kStaticPartials)
         return fail(h, ADPSGD_ERR_ARG, "consensus_distance_static: d needs more block partials than the fixed array holds");
@@ -131,6 +134,7 @@ extern "C" int adpsgd_count_nonfinite(adpsgd_t* h, int64_t* out) {
     if (!out) return fail(h, ADPSGD_ERR_ARG, "count_nonfinite: out is NULL");
     const int32_t blocks = 2048;
     HIP_TRY(h, hipStreamSynchronize(h->stream));
+    if (const int rc = check_exchange(h)) return rc;
     HIP_TRY(h, h->diag.reserve(static_cast<size_t>(blocks) * sizeof(unsigned long long)));
     HIP_TRY(h, launch_count_nonfinite(h->o.X, h->o.ldx, h->d, h->n, static_cast<unsigned long long*>(h->diag.p), blocks, h->stream));
     std::vector<unsigned long long> part(blocks);
@@ -226,6 +230,8 @@ int evaluate(adpsgd_t* h, const float* x, double* out, bool count_errors, const 
         max_rows = std::max(max_rows, h->data[i].rows);
     }
     HIP_TRY(h, hipStreamSynchronize(h->stream));
+    if (!x)
+        if (const int rc = check_exchange(h)) return rc;
     // diag buffer: [mean model d floats, 256-byte padded][worker table][partials][result][weights]
     const int64_t groups = objective_row_groups(max_rows);
     const size_t off_tab = (static_cast<size_t>(h->d) * 4 + 255) & ~size_t(255);

@@ -12,6 +12,7 @@ int run_sync_steps_impl(adpsgd_t* h, const adpsgd_sync_schedule_t* s, float* los
     if (!s || s->S < 0) return fail(h, ADPSGD_ERR_ARG, "run_sync_steps: schedule is NULL or S < 0");
     const int64_t S = s->S;
     if (S == 0) return ADPSGD_OK;
+    if (const int rc = check_exchange(h)) return rc;
     const int32_t n = h->n;
     const bool external = h->o.model == ADPSGD_MODEL_EXTERNAL;
     const bool with_grad = h->o.model != ADPSGD_MODEL_SYNTH;

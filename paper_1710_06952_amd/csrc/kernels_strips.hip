@@ -176,9 +176,11 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     __shared__ float coef_s[kStripHelpers];
     __shared__ float loss_s[kStripHelpers];
     __shared__ Assembly assembly_s;
+    __shared__ int lost_s;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.M, S = p.samples;
+    if (tid == 0) lost_s = 0;
     if (tid == 0) assembly_s = assemble(a.counters, p.blocks, p.group_size, a.wait_ticks);
     __syncthreads();
     const Assembly as = assembly_s;
@@ -527,6 +529,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                 loss_s[to] = r.y;
             }
         }
+        if (given_up) lost_s = 1;
         __syncthreads();
 
         // ---- C: indices and record of the iterations after the next (what a helper loads here has arrived when the next
@@ -537,7 +540,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     }
     if (given_up) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (!kLds) return;
-    if (inside) {
+    if (inside && lost_s == 0) {      // a lost launch writes nothing back
         for (int r = 0; r < a.n; ++r) {
             a.X[r * a.ld + col] = xs[r * ld];
             if (kMom) a.V[r * a.ld + col] = vs[r * ld];

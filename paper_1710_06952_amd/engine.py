@@ -166,6 +166,7 @@ class Engine:
 
     def get_loss(self):
         self.torch.cuda.synchronize(self.device)
+        self.h.synchronize()
         return self.loss.cpu().numpy()
 
     def get_models(self):
