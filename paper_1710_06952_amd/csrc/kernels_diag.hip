@@ -140,15 +140,16 @@ __global__ __launch_bounds__(kThreads) void consensus_final_kernel(const double*
 }
 
 // ---- divergence check: number of entries of X that are NaN or infinite -----------------------
-// Blocks stride over tiles of kCountTile float4 pieces of a row, eight loads of a thread in flight; one count per block,
-// summed by the host.  A read of all models, bound by memory: n = 64, d = 25.6 M (6.55 GB) 0.94 ms (7.0 TB/s) against
-// 1.22 ms for single pieces in row order, whose row and column cost a 64-bit division each.
+// Blocks stride over tiles of kCountTile float4 pieces of a row, eight loads of a thread in flight (as many as a row has
+// for it, where rows are short); one count per block, summed by the host.  A read of all models, bound by memory: n = 64,
+// d = 25.6 M (6.55 GB) 0.94 ms (7.0 TB/s) against 1.22 ms for single pieces in row order, whose row and column cost a 64-bit
+// division each.  n = 1000, d = 300: 3.7 us, 4.1 with eight loads of which seven lie behind the row, 3.4 in row order; n = 64,
+// d = 100 000: 4.5, and 4.8 with fewer loads in more tiles.
 // STREAM: X does not fit the caches: non-temporal loads
-constexpr int kCountUnroll = 8;
-constexpr int64_t kCountTile = kThreads * kCountUnroll;
-template <bool STREAM>
+template <bool STREAM, int kCountUnroll>
 __global__ __launch_bounds__(kThreads) void count_nonfinite_kernel(const float* X, int64_t ld, int64_t d, int32_t n,
                                                                   unsigned long long* partial) {
+    constexpr int64_t kCountTile = kThreads * kCountUnroll;
     __shared__ unsigned long long red[kWaves];
     const int64_t n_vec = (d + 3) / 4, row_tiles = (n_vec + kCountTile - 1) / kCountTile, tiles = row_tiles * n;
     unsigned long long bad = 0;
@@ -291,8 +292,12 @@ hipError_t launch_compensated_rows(const float* X, int64_t ld, const GradOp* ops
 
 hipError_t launch_count_nonfinite(const float* X, int64_t ld, int64_t d, int32_t n, unsigned long long* partial,
                                   int32_t blocks, hipStream_t st) {
-    if (static_cast<int64_t>(n) * ld * 4 > kStreamBytes) hipLaunchKernelGGL(count_nonfinite_kernel<true>, dim3(blocks), dim3(kThreads), 0, st, X, ld, d, n, partial);
-    else hipLaunchKernelGGL(count_nonfinite_kernel<false>, dim3(blocks), dim3(kThreads), 0, st, X, ld, d, n, partial);
+    const int64_t n_vec = (d + 3) / 4;
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, st, X, ld, d, n, partial); };
+    if (static_cast<int64_t>(n) * ld * 4 > kStreamBytes) launch(count_nonfinite_kernel<true, 8>);
+    else if (n_vec > 2 * kThreads) launch(count_nonfinite_kernel<false, 8>);
+    else if (n_vec > kThreads) launch(count_nonfinite_kernel<false, 2>);
+    else launch(count_nonfinite_kernel<false, 1>);
     return hipGetLastError();
 }
 

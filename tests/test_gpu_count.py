@@ -1,4 +1,4 @@
-"""GPU: the divergence check at the edges of its tiles (8192 entries of a row) against a count on the host."""
+"""GPU: the divergence check at the edges of its tiles (1024, 2048 and 8192 entries of a row) against a count on the host."""
 import numpy as np
 import pytest
 
@@ -7,7 +7,7 @@ from workloads import ring_graph
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,d", [(2, 1), (3, 5), (4, 8191), (5, 8192), (3, 8193), (64, 700), (7, 40_003)])
+@pytest.mark.parametrize("n,d", [(2, 1), (3, 5), (6, 1024), (6, 1025), (5, 2048), (5, 2049), (4, 8191), (5, 8192), (3, 8193), (64, 700), (7, 40_003)])
 def test_count_of_entries_that_are_not_finite(n, d):
     import torch
     if not torch.cuda.is_available():
