@@ -111,12 +111,14 @@ namespace {
 // strip kernel evaluates teams / 2 gradients at most, so its time per event jumps with the number of teams (M = 16, 32, 64)
 // and does not fall with n, while the kernels of a round, of n / 4 events on a ring and n / 5 or n / 6 on denser graphs, take
 // its gradients side by side.  Measured, rounds over strips for a call of 12 n events (the lesser of a call alone and one of
-// several; least squares and logistic regression, momentum, T_max 0 ... 40):
-//                          ring                                     random 4-regular graph
-//   d = 64     M <= 16     n = 16 1.19 ... 1.57, n = 28 0.76        n = 24 1.03 ... 1.16, n = 40 0.76
-//   d = 1024   M <= 16     n = 20 0.97 ... 1.6,  n = 32 0.86        n = 32 1.0 ... 1.6,   n = 56 0.80
-//   d = 4096   M = 8       n = 40 1.4,           n = 72 0.93        n = 64 1.2 ... 1.4,   n = 100 0.7
-//   d = 4096   M = 32      n = 28 1.1,           n = 48 0.7         n = 48 1.1
+// several; least squares and logistic regression, momentum, T_max 0 ... 40; the least and the
+// most of them):
+//                        ring                                              random 4-regular graph
+//   d = 64    M <= 16    n = 16 1.15 ... 1.50, n = 28 0.76 ... 1.00        n = 24 1.02 ... 1.26, n = 40 0.73 ... 0.88
+//   d = 1024  M <= 16    n = 20 1.15 ... 1.58, n = 32 0.76 ... 1.02        n = 32 1.26 ... 1.67, n = 56 0.78 ... 0.99
+//   d = 4096  M = 8      n = 40 1.49 ... 1.82, n = 72 0.82 ... 1.09        n = 64 1.50 ... 1.62, n = 100 0.66 ... 0.93
+//   d = 4096  M = 32     n = 28 1.29 ... 1.58, n = 48 0.75 ... 0.89        n = 48 1.21 ... 1.39
+//   d = 8192  M = 32     n = 20 1.17 ... 1.54, n = 28 0.90 ... 1.17        n = 48 0.98 ... 1.00
 // A direct exchange between 17 to 32 strips (d = 8192) is the slowest for its size.  The line keeps below the first loss of
 // any of them; beyond it the strips would still win in places (n = 32, M = 64: d = 4096 2356 / 3515 us a call;  n = 16,
 // M = 128, d = 20 000 6115 / 7528;  n = 32, M = 48, d = 1024 1218 / 1505) and lose near by (n = 16, M = 128, d = 300 2986 /
@@ -152,12 +154,13 @@ void settle_strips(adpsgd_t* h) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     int dev = 0, cus = 0, cooperative = 0;
     const size_t words = strip_exchange_bytes(model, h->o.M);
+    const size_t alone = static_cast<size_t>(strip_window(h->o.T_max, true, strip_lds_slots(h), h->n_slots)) * h->o.ldx * sizeof(float);
     if (hipStreamIsCapturing(h->stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone && hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
         hipDeviceGetAttribute(&cooperative, hipDeviceAttributeCooperativeLaunch, dev) == hipSuccess && cooperative != 0 &&
         strip_blocks(h->d) <= std::min(cus, kStripGroups * kStripGroupBlocks) && h->exchange.reserve(words) == hipSuccess &&
         h->exchange_status.reserve(sizeof(int)) == hipSuccess &&
-        (!lds_state || h->alone_slots.reserve(static_cast<size_t>(strip_window(h->o.T_max, true, strip_lds_slots(h), h->n_slots)) * h->o.ldx * sizeof(float)) == hipSuccess) &&
+        (!lds_state || h->alone_slots.reserve(alone) == hipSuccess) &&
         hipMemset(h->exchange.p, 0, h->exchange.cap) == hipSuccess &&      // no sequence number
         hipStreamSynchronize(nullptr) == hipSuccess) {
         *static_cast<int*>(h->exchange_status.p) = 0;
@@ -441,7 +444,8 @@ bool small_call(const adpsgd_t* h, const EventCall& c) {
     const int32_t per_set = h->d <= 2048 ? 1 : c.lin_factored ? 2 : 3, teams = strip_teams(c.M);
     int64_t launches = 0;
     for (int32_t r = 0; r < c.plan.n_rounds; ++r) launches += (c.u_off[r + 1] > c.u_off[r]) + per_set * (c.r_off[r + 1] > c.r_off[r]);
-    const double row_us = 4.0 * c.M * static_cast<double>(h->d) * static_cast<double>(c.K) / 6.0e6, per_event = teams == 12 ? 0.9 : teams == 6 ? 1.4 : teams == 4 ? 2.2 : 4.5;
+    const double row_us = 4.0 * c.M * static_cast<double>(h->d) * static_cast<double>(c.K) / 6.0e6;
+    const double per_event = teams == 12 ? 0.9 : teams == 6 ? 1.4 : teams == 4 ? 2.2 : 4.5;
     return 14.0 + 2.6 * static_cast<double>(launches) + row_us * (per_set == 1 ? 1.0 : 2.0) < 44.0 + per_event * static_cast<double>(c.K) + row_us;
 }
 
@@ -732,12 +736,12 @@ struct ColumnPlan {
 // The rounds are also the better route for a call that touches its rows once or twice: they move 16 (24) bytes per
 // parameter and event at 6.4 TB/s, the column kernel 8 (16) per touched row, at 0.3 TB/s per wavefront of a compute unit
 // (measured 2.6 with 8 to 8 with 16; half as much again where the state fits the memory-side cache), before and after it
-// computes.  Measured, one launch / rounds in us:  n = 160,
-// d = 4 M, 19 events 320 / 209, 80 events 1129 / 822, 240 events 1930 / 2440;  n = 320, d = 16 M, 480 events 24 800 /
-// 19 400, 960 events 31 500 / 38 600;  n = 117 with momentum, d = 1 M, 29 events 199 / 128, 117 events 480 / 490.  And a
-// launch of its own costs 4.5 us where a round costs 2.5 at least, so a call of a single round stays one (one event:
-// 25 / 22), and what cannot gain is turned away before the strips are laid out.  Of 700 set-ups measured (n 4 ... 320, d 1000 ... 16 M, 1 to 5 n events, with and without momentum) the line
-// takes none to the slower route by more than 5 %, where all to the column kernel lost up to 2.0 times.
+// computes.  Measured, one launch / rounds in us:  n = 160, d = 4 M, 19 events 320 / 209, 80 events 1129 / 822, 240 events
+// 1770 / 2467;  n = 320, d = 16 M, 480 events 24 800 / 19 400, 960 events 31 500 / 38 600;  n = 117 with momentum, d = 1 M,
+// 29 events 199 / 128, 117 events 461 / 506.  And a launch of its own costs 4.5 us where a round costs 2.5 at least, so a call
+// of a single round stays one (one event: 25 / 22), and what cannot gain is turned away before the strips are laid out.
+// Of 700 set-ups measured (n 4 ... 320, d 1000 ... 16 M, up to 5 n events, with and without momentum) the line takes none to
+// the slower route by more than 5 %, where all to the column kernel lost up to 2.0 times.
 void plan_columns(adpsgd_t* h, const EventCall& c, ColumnPlan& out) {
     const adpsgd_schedule_t* s = c.s;
     if (h->d > (1ll << 34)) return;                 // the quad has to fit one word of the generator's counter

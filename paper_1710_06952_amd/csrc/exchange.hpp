@@ -10,10 +10,10 @@
 // block per compute unit launched.  Partial sums are added in a fixed order of the groups and blocks.
 // Every block waits for all others.  A cooperative launch makes sure that the grid fits the device, not that the device is
 // free: work of other streams or processes may hold compute units while the first blocks are there.  So the blocks agree
-// once, before any of them touches the state (assemble): all have arrived, or the first one that has
-// waited longer than the caller's limit goes alone, and then executes the whole call by itself while all others
-// leave.  Once all have arrived they are resident and every further wait ends; it is bounded by a number of polls
-// all the same, after which the block reports the launch as lost.
+// once, before any of them touches the state (assemble): all have arrived, or the first one that has waited longer than the
+// caller's limit goes alone and executes the whole call by itself while all others leave.  Once all have arrived they are
+// resident and every further wait ends; it is bounded by a number of polls all the same, after which the block reports the
+// launch as lost.
 #pragma once
 
 #include "device_common.hpp"
