@@ -81,7 +81,8 @@ enum {
                                        update kernel applies them: the MLP's first layer as dH and the minibatch
                                        inputs, least squares on long models as its M coefficients.  The values
                                        are the same; the dense form costs one more launch and a write and
-                                       read-back of the gradient per event */
+                                       read-back of the gradient per event.  Calls in one launch keep the gradients
+                                       dense on the chip in any case */
 };
 
 /* Undirected communication graph (V, E) of Sec. 3.1 as CSR adjacency lists.
