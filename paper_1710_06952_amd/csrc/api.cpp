@@ -111,8 +111,7 @@ namespace {
 // strip kernel evaluates teams / 2 gradients at most, so its time per event jumps with the number of teams (M = 16, 32, 64)
 // and does not fall with n, while the kernels of a round, of n / 4 events on a ring and n / 5 or n / 6 on denser graphs, take
 // its gradients side by side.  Measured, rounds over strips for a call of 12 n events (the lesser of a call alone and one of
-// several; least squares and logistic regression, momentum, T_max 0 ... 40; the least and the
-// most of them):
+// several; least squares and logistic regression, momentum, T_max 0 ... 40; the least and the most of them):
 //                        ring                                              random 4-regular graph
 //   d = 64    M <= 16    n = 16 1.15 ... 1.50, n = 28 0.76 ... 1.00        n = 24 1.02 ... 1.26, n = 40 0.73 ... 0.88
 //   d = 1024  M <= 16    n = 20 1.15 ... 1.58, n = 32 0.76 ... 1.02        n = 32 1.26 ... 1.67, n = 56 0.78 ... 0.99
@@ -438,7 +437,8 @@ bool can_run_strips(const adpsgd_t* h) {
 // rounds in us:  n = 8, d = 1024, M = 32: 1 event 47 / 23, 8 events 55 / 38, 16 events 66 / 63, 32 events 84 / 116;  n = 16,
 // d = 4096, M = 8: 4 events 50 / 40, 8 events 54 / 54, 16 events 60 / 82;  n = 16, d = 7395, M = 6, T_max = 100, where most
 // reads of a short call precede its first update and share their launches: 23 events 83 / 48.
-// Calls that are cut out of one schedule (looking ahead, or without stale reads at all) keep the handle's route.
+// Calls that are cut out of one schedule (looking ahead, or without stale reads at all) keep the handle's route, up to 25 us
+// slower for a few events, so that the cut does not change the order of any sum.
 bool small_call(const adpsgd_t* h, const EventCall& c) {
     if (c.K > 128 || h->o.T_max == 0 || c.s->lookahead > 0 || !h->pending.empty()) return false;
     const int32_t per_set = h->d <= 2048 ? 1 : c.lin_factored ? 2 : 3, teams = strip_teams(c.M);
