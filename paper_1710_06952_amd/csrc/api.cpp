@@ -730,7 +730,7 @@ struct ColumnPlan {
 // 64 / q operations in a batch: narrow strips let more wavefronts share a compute unit, wide ones lose less to batches
 // that the dependences leave half empty.  The estimate below (cycles of a SIMD; measured at n = 128, d = 25.6 M: a
 // batch costs a wavefront about 1500 cycles from its operands to its results, and a SIMD with several of them one per
-// 420) is compared for every width whose strips leave at least eight wavefronts to a compute unit.  Below that the
+// 350, which the lines below, drawn at 420, leave as a margin) is compared for every width whose strips leave at least eight wavefronts to a compute unit.  Below that the
 // rounds are the better route: 32 KB strips (n = 500, four quads) leave one wavefront per SIMD to hide that latency.
 //
 // The rounds are also the better route for a call that touches its rows once or twice: they move 16 (24) bytes per
@@ -799,7 +799,7 @@ int run_columns(adpsgd_t* h, const EventCall& c, const ColumnPlan& plan) {
     const int32_t capacity = 64 / plan.quads;
     if ((h->o.flags & ADPSGD_FLAG_VERIFY_PLAN) && !verify_columns(plan.pairs, static_cast<int32_t>(plan.rows.size()), capacity, plan.place, plan.batches))
         return fail(h, ADPSGD_ERR_STATE, "column layout: the order of the events is not kept");
-    const size_t n_ops = static_cast<size_t>(plan.batches + 1) * capacity, off_rows = n_ops * sizeof(ColumnOp);
+    const size_t n_ops = static_cast<size_t>(plan.batches + 2) * capacity, off_rows = n_ops * sizeof(ColumnOp);
     const size_t total = off_rows + plan.rows.size() * sizeof(int32_t);
     TableSet& T = h->tables[h->next_table];
     h->next_table ^= 1;
@@ -815,7 +815,8 @@ int run_columns(adpsgd_t* h, const EventCall& c, const ColumnPlan& plan) {
     for (size_t t = 0; t < plan.pairs.size(); ++t) {
         const ColumnPair& pr = plan.pairs[t];
         ColumnOp& op = ops[plan.place[t]];
-        op.rows = static_cast<uint32_t>(pr.i) | (static_cast<uint32_t>(pr.j) << 16);
+        const uint32_t pitch = 16u * static_cast<uint32_t>(plan.quads);        // a strip has at most 64 KB: its places fit 16 bits
+        op.rows = pitch * static_cast<uint32_t>(pr.i) | (pitch * static_cast<uint32_t>(pr.j)) << 16;
         op.flags = pr.event >= 0 ? kColumnEvent : kColumnAverage;
         if (pr.event < 0) continue;
         op.gamma = c.s->gamma ? c.s->gamma[pr.event] : h->o.gamma;
@@ -829,7 +830,7 @@ int run_columns(adpsgd_t* h, const EventCall& c, const ColumnPlan& plan) {
     if (rc != ADPSGD_OK) return rc;
     ColumnArgs a{h->o.X, h->o.V, h->o.ldx, h->d, reinterpret_cast<const ColumnOp*>(dev), reinterpret_cast<const int32_t*>(dev + off_rows),
                  static_cast<int32_t>(plan.rows.size()), static_cast<int32_t>(plan.batches), plan.quads, h->o.synth_seed, h->o.synth_std,
-                 h->o.momentum, h->o.weight_decay};
+                 h->o.momentum, h->o.weight_decay, c.n_extra > 0};
     HIP_TRY(h, launch_column_events(a, h->stream));
     rc = end_timing(h, e0, e1, h->ev_fused);
     if (rc != ADPSGD_OK) return rc;

@@ -27,58 +27,96 @@ __device__ __forceinline__ void store4(float* p, v4f v) {
     else *reinterpret_cast<v4f*>(p) = v;
 }
 
-// Philox4x32 (Salmon et al., SC'11), kRounds rounds starting with the key (k0, k1).  The key is uniform over a
-// workgroup, so the key schedule lives in scalar registers.
+// What binds the kernels that draw gradients in registers is the issue of vector instructions.  Measured, time per
+// instruction and SIMD with eight wavefronts: 1.05 ns for additions, products and FMAs in fp32, for 32-bit integer additions,
+// AND / OR / XOR, three-input bit operations and right shifts; 1.83 ns for the same with an operand in a scalar register, for
+// left shifts, bit fields, conversions, comparisons, selects and 32-bit products; 3.45 ns for logarithm and root.  So what
+// every lane shares (keys, constants) is held in vector registers, and selects are bit operations.
+__device__ __forceinline__ uint32_t in_vector(uint32_t s) {
+    uint32_t v;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(v) : "s"(s));
+    return v;
+}
+__device__ __forceinline__ float in_vector(float s) { return __uint_as_float(in_vector(__float_as_uint(s))); }
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
+// bits of a where mask is set, of b elsewhere
+__device__ __forceinline__ float pick(uint32_t mask, float a, float b) {
+    return __uint_as_float(__builtin_amdgcn_bitop3_b32(mask, __float_as_uint(a), __float_as_uint(b), 0xCA));
+}
+// a with its sign flipped where the top bit of by is set
+__device__ __forceinline__ float flip(float a, uint32_t by, uint32_t top) {
+    return __uint_as_float(__builtin_amdgcn_bitop3_b32(__float_as_uint(a), by, top, 0x78));
+}
+
+// The keys of kRounds rounds of Philox4x32 starting with (k0, k1): uniform over a workgroup, in vector registers where a
+// wavefront draws often (kVector), else in scalar ones.
 template <int kRounds>
-__device__ __forceinline__ v4u philox4x32_rounds(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                                 uint32_t k0, uint32_t k1) {
+struct PhiloxKeys {
+    uint32_t k[2 * kRounds];
+};
+template <int kRounds, bool kVector = false>
+__device__ __forceinline__ PhiloxKeys<kRounds> philox_keys(uint32_t k0, uint32_t k1) {
+    PhiloxKeys<kRounds> keys;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        keys.k[2 * r] = kVector ? in_vector(k0 + r * kPhiloxW0) : k0 + r * kPhiloxW0;
+        keys.k[2 * r + 1] = kVector ? in_vector(k1 + r * kPhiloxW1) : k1 + r * kPhiloxW1;
+    }
+    return keys;
+}
+// Philox4x32 (Salmon et al., SC'11), kRounds rounds.
+template <int kRounds>
+__device__ __forceinline__ v4u philox4x32_rounds(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, const PhiloxKeys<kRounds>& keys) {
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
         const uint64_t pa = static_cast<uint64_t>(kPhiloxM0) * c0;
         const uint64_t pb = static_cast<uint64_t>(kPhiloxM1) * c2;
-        const uint32_t n0 = static_cast<uint32_t>(pb >> 32) ^ c1 ^ k0;
-        const uint32_t n2 = static_cast<uint32_t>(pa >> 32) ^ c3 ^ k1;
+        const uint32_t n0 = xor3(static_cast<uint32_t>(pb >> 32), c1, keys.k[2 * r]);
+        const uint32_t n2 = xor3(static_cast<uint32_t>(pa >> 32), c3, keys.k[2 * r + 1]);
         c1 = static_cast<uint32_t>(pb);
         c3 = static_cast<uint32_t>(pa);
         c0 = n0;
         c2 = n2;
-        k0 += kPhiloxW0;
-        k1 += kPhiloxW1;
     }
     v4u out = {c0, c1, c2, c3};
     return out;
 }
-__device__ __forceinline__ v4u philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                             uint32_t k0, uint32_t k1) {
-    return philox4x32_rounds<10>(c0, c1, c2, c3, k0, k1);
+
+// What Box-Muller takes beside the words, the same for all lanes.
+struct NormalConstants {
+    SynthScale scale;
+    uint32_t one, fraction, top; // bits of 1.0f, bits 22..1 of a fraction, the sign bit
+};
+template <bool kVector = false>
+__device__ __forceinline__ NormalConstants normal_constants(SynthScale s) {
+    const uint32_t one = 0x3F800000u, fraction = 0x007FFFFEu, top = 0x80000000u;
+    if (!kVector) return NormalConstants{s, one, fraction, top};
+    return NormalConstants{{in_vector(s.hi), in_vector(s.lo)}, in_vector(one), in_vector(fraction), in_vector(top)};
 }
 
 // Box-Muller on two 32-bit words: u1 = ((wa >> 9) + 1/2) 2^-23 in (0,1) and u2 = (wb >> 8) 2^-24 in [0,1) are exact
 // in fp32; gives std r cos(2 pi u2), std r sin(2 pi u2) with r = sqrt(-2 ln u1).
 // The kernels that draw gradients in registers are bound by these instructions, so nothing is computed that the
 // ranges above rule out (no subnormals, infinities or large arguments):
-//   r       t = -2 ln 2 log2(u1) (v_log_f32), sqrt by one Newton step on v_rsq_f32 that also takes in the rounding
-//           error of t (the residual of its product);
-//   angle   quarter turns: n = round(4 u2) and f = 4 u2 - n in [-1/2, 1/2) are read off the bits of the word, then
-//           polynomials in f^2 for sin(pi/2 f) / f (four terms) and cos(pi/2 f) (four terms beside the 1), least maximum
-//           relative error over [0, 1/4] by Remez's exchange: 3.2e-9, the leading coefficient in two parts, and 6.4e-11,
-//           7.7e-11 with the coefficients as written; swapped and signed by n.
-// Against 64-bit arithmetic over 1.3e8 variates: rms error 5.5e-8 relative, 0.66 ulp, at most 3.7 ulp; logf, sqrtf and
-// sincospif with separate products have 5.7e-8, 0.70 and 3.9.  Time of one quad of variates per wavefront with the
-// generator below: 411 SIMD cycles (197 of them Philox) against 700.  Written out in single operations, so that every
-// kernel that draws a gradient gets the same bits.
-__device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float std, float& zc, float& zs) {
+//   u1      the 23 bits as the fraction of a number in [1, 2), less 1 - 2^-24 (exact);
+//   r       std r = sqrt(-log2(u1)) std sqrt(2 ln 2), v_log_f32 and v_sqrt_f32 (which rounds all but correctly), the constant
+//           in two parts (SynthScale);
+//   angle   quarter turns: n = round(4 u2) and f = 4 u2 - n in [-1/2, 1/2), whose 22 bits become the fraction of 1.5 + f, are
+//           read off the word; then polynomials in f^2 for sin(pi/2 f) / f (four terms) and cos(pi/2 f) (four terms beside the
+//           1), least maximum relative error over [0, 1/4] by Remez's exchange: 3.2e-9, the leading coefficient in two parts,
+//           and 6.4e-11, 7.7e-11 with the coefficients as written; swapped and signed by n.
+// Against 64-bit arithmetic over 1.3e8 variates (std = 0.0316): rms error 5.27e-8 relative, 0.637 ulp, at most 3.7 ulp, mean
+// 5e-10; with a Newton step on v_rsq_f32 and a product by std 5.44e-8, 0.659, 3.7 and 1.5e-8 (only where that product is
+// exact, as for std = 1, 4.81e-8).
+// Written out in single operations, so that every kernel that draws a gradient gets the same bits.
+__device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, const NormalConstants& k, float& zc, float& zs) {
 #pragma clang fp contract(off)
-    const float u1 = __builtin_fmaf(static_cast<float>(wa >> 9), 0x1p-23f, 0x1p-24f);
-    const float l2 = __builtin_amdgcn_logf(u1);
-    constexpr float kM2Ln2 = -1.3862943611198906f;      // its rounding is 3e-9 relative
-    const float t = l2 * kM2Ln2;
-    const float y0 = __builtin_amdgcn_rsqf(t);
-    const float g = t * y0, h = 0.5f * y0;
-    const float rest = __builtin_fmaf(-g, g, t) + __builtin_fmaf(l2, kM2Ln2, -t);
-    const float r = __builtin_fmaf(rest, h, g) * std;
+    const float u1 = __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, wa, 9)) - 0x1.fffffep-1f;
+    const float root = __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1));
+    const float r = __builtin_fmaf(root, k.scale.hi, root * k.scale.lo);
 
-    const float f = static_cast<float>(static_cast<int32_t>(__builtin_amdgcn_sbfe(static_cast<int32_t>(wb), 8, 22))) * 0x1p-22f;
+    const uint32_t turn = wb + 0x20000000u;             // bits 31..30: n mod 4
+    const float f = __uint_as_float(__builtin_amdgcn_bitop3_b32(turn >> 7, k.fraction, k.one, 0xEA)) - 1.5f;
     const float y = f * f;
     constexpr float kS0 = 1.5707963217077767f, kS0Rest = static_cast<float>(1.5707963217077767 - static_cast<double>(kS0));
     float p = __builtin_fmaf(y, -0.004601657568828705f, 0.07968003262819402f);
@@ -90,28 +128,27 @@ __device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float std, 
     q = __builtin_fmaf(q, y, -1.2337005435078803f);
     const float c = __builtin_fmaf(q, y, 1.0f);
 
-    const uint32_t turn = wb + 0x20000000u;             // bits 31..30: n mod 4
-    const bool odd = (turn & 0x40000000u) != 0;
-    const float cv = odd ? s : c, sv = odd ? c : s;
-    zc = __uint_as_float(__float_as_uint(r * cv) ^ ((turn + 0x40000000u) & 0x80000000u));
-    zs = __uint_as_float(__float_as_uint(r * sv) ^ (turn & 0x80000000u));
+    const uint32_t odd = static_cast<uint32_t>(__builtin_amdgcn_sbfe(static_cast<int32_t>(turn), 30, 1));
+    zc = flip(r * pick(odd, s, c), turn + 0x40000000u, k.top);
+    zs = flip(r * pick(odd, c, s), turn, k.top);
 }
 
 // The four normals of one generator output, times std.
-__device__ __forceinline__ v4f synth_normals_of(v4u w, float std) {
+__device__ __forceinline__ v4f synth_normals_of(v4u w, const NormalConstants& k) {
     v4f z;
     float a, b;
-    box_muller(w.x, w.y, std, a, b);
+    box_muller(w.x, w.y, k, a, b);
     z.x = a; z.y = b;
-    box_muller(w.z, w.w, std, a, b);
+    box_muller(w.z, w.w, k, a, b);
     z.z = a; z.w = b;
     return z;
 }
 
 // Elements 4q .. 4q+3 of the synthetic gradient of event k: std times a standard normal each.
 __device__ __forceinline__ v4f synth_normals4(uint32_t q_lo, uint32_t q_hi, uint32_t k_lo, uint32_t k_hi,
-                                              uint32_t key0, uint32_t key1, float std) {
-    return synth_normals_of(philox4x32_10(q_lo, q_hi, k_lo, (k_hi & 0x00FFFFFFu) | kStreamGrad, key0, key1), std);
+                                              uint32_t key0, uint32_t key1, SynthScale scale) {
+    return synth_normals_of(philox4x32_rounds<10>(q_lo, q_hi, k_lo, (k_hi & 0x00FFFFFFu) | kStreamGrad, philox_keys<10>(key0, key1)),
+                            normal_constants(scale));
 }
 
 __device__ __forceinline__ uint16_t bf16_rne(float f) {

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -45,10 +46,20 @@ constexpr uint32_t kPhiloxM0 = 0xD2511F53u, kPhiloxM1 = 0xCD9E8D57u;
 constexpr uint32_t kPhiloxW0 = 0x9E3779B9u, kPhiloxW1 = 0xBB67AE85u;
 constexpr uint32_t kStreamGrad = 2u << 24;
 
+// std sqrt(2 ln 2) in two parts, the standard deviation of the synthetic gradients as the kernels take it.
+struct SynthScale {
+    float hi, lo;
+};
+inline SynthScale synth_scale(float std) {
+    const double exact = static_cast<double>(std) * 1.1774100225154747;
+    const float hi = static_cast<float>(exact);
+    return SynthScale{hi, std::isfinite(hi) ? static_cast<float>(exact - static_cast<double>(hi)) : 0.0f};
+}
+
 // One operation of the column kernel (kernels_columns.hip): an event of the synthetic model or an extra pair.
 constexpr uint32_t kColumnEvent = 1, kColumnAverage = 2;
 struct alignas(32) ColumnOp {
-    uint32_t rows;      // i | j << 16, local row numbers
+    uint32_t rows;      // places of rows i and j (upper half) in a strip, in bytes
     uint32_t flags;     // 0: empty, kColumnEvent, kColumnAverage
     float gamma;
     uint32_t a, b, c, d;   // what the first two Philox rounds take from the event number (see column_words)
@@ -113,13 +124,14 @@ struct ColumnArgs {
     float* X;
     float* V;               // momentum buffers or nullptr
     int64_t ld, d;
-    const ColumnOp* ops;    // device, [batches + 1][64 / quads]
+    const ColumnOp* ops;    // device, [batches + 2][64 / quads]
     const int32_t* rows;    // device, the rows of X that the operations name
     int32_t n_rows, batches;
     int32_t quads;          // float4 columns per wavefront: 4, 8, 16, 32 or 64
     uint64_t synth_seed;
     float synth_std;
     float momentum, weight_decay;
+    bool averages;          // some operations average only (extra pairs of a general W_k)
 };
 hipError_t launch_column_events(const ColumnArgs& a, hipStream_t st);
 

@@ -12,11 +12,11 @@
 //
 // What binds is the arithmetic of the generator.  Its counter is (quad, 0, event, ...): the first Philox round and one
 // of the two products of the second depend either on the quad alone or on the event alone.  The quad's part is
-// computed once per wavefront, the event's part once on the host (ColumnOp).  Measured at n = 128, d = 25.6 M on the
-// ring, 2000 events per call: 39.2 ms (19.6 us per event, of which X in and out are 2.2) against 128.8 ms in rounds of
-// the streaming kernel; an operation costs a SIMD 420 cycles per 64 quads, about what the generator alone takes.
-// n = 32, d = 3.0 M with momentum, 500 events: 1.62 against 6.18 ms; n = 128, d = 25.6 M with momentum, where the velocities
-// halve the wavefronts that fit a compute unit, 26.7 us per event against about 100.
+// computed once per wavefront, the event's part once on the host (ColumnOp); the rest is in vector registers, since an
+// operand in a scalar one nearly doubles the time of an instruction (see device_common.hpp).  Measured at n = 128, d = 25.6 M
+// on the ring, 2000 events per call: 32.9 ms (39.7 with keys in scalar registers, one batch per turn of the loop and a Newton
+// step on the root), 128.8 ms in rounds of the streaming kernel; an operation takes a SIMD 168 ns per 64 quads, of which the
+// instructions issue for about 145.  n = 32, d = 3.0 M with momentum, 500 events: 1.34 ms (1.62 before), 6.18 in rounds.
 #include <algorithm>
 
 #include "device_common.hpp"
@@ -29,24 +29,22 @@ struct ColumnParams {
     float* X;
     float* V;                  // momentum buffers (MOM), else nullptr
     int64_t ld, d, n_vec;
-    const ColumnOp* ops;       // [batches + 1][P], empty operations have flags 0
+    const ColumnOp* ops;       // [batches + 2][P], empty operations have flags 0
     const int32_t* rows;       // the rows of X behind the local row numbers of the operations
     int32_t n_rows, batches;
     uint32_t key0, key1;
-    float synth_std;
+    SynthScale synth;
     float momentum, weight_decay;
 };
 
 // Philox4x32-10 from the second round on: hq, lq the two words of M0 * quad, the operation's words a..d from the host
-__device__ __forceinline__ v4u philox_rest(uint32_t hq, uint32_t lq, uint32_t a, uint32_t b, uint32_t c, uint32_t d,
-                                           uint32_t k0, uint32_t k1) {
-    const uint64_t pb = static_cast<uint64_t>(kPhiloxM1) * (hq ^ a);
-    return philox4x32_rounds<8>(static_cast<uint32_t>(pb >> 32) ^ b, static_cast<uint32_t>(pb), lq ^ c, d,
-                                k0 + 2u * kPhiloxW0, k1 + 2u * kPhiloxW1);
+__device__ __forceinline__ v4u philox_rest(uint32_t hq, uint32_t lq, const ColumnOp& op, const PhiloxKeys<8>& keys) {
+    const uint64_t pb = static_cast<uint64_t>(kPhiloxM1) * (hq ^ op.a);
+    return philox4x32_rounds<8>(static_cast<uint32_t>(pb >> 32) ^ op.b, static_cast<uint32_t>(pb), lq ^ op.c, op.d, keys);
 }
 
-// grid: one wavefront per kQuads float4 columns
-template <int kQuads, bool MOM>
+// grid: one wavefront per kQuads float4 columns; AVERAGES: some operations average only
+template <int kQuads, bool MOM, bool AVERAGES>
 __global__ __launch_bounds__(256) void column_events_kernel(const ColumnParams p) {
     constexpr int P = 64 / kQuads;
     extern __shared__ __attribute__((aligned(16))) v4f strips[];
@@ -84,22 +82,22 @@ __global__ __launch_bounds__(256) void column_events_kernel(const ColumnParams p
 
     const uint64_t mq = static_cast<uint64_t>(kPhiloxM0) * static_cast<uint32_t>(q);       // d <= 2^34: the quad fits a word
     const uint32_t hq = static_cast<uint32_t>(mq >> 32), lq = static_cast<uint32_t>(mq);
-    const ColumnOp* __restrict__ at = p.ops + sub;
-    ColumnOp op = *at;
-    for (int b = 0; b < p.batches; ++b) {
-        at += P;
-        const ColumnOp next = *at;          // one batch ahead; the table ends with a batch of empty operations
+    const PhiloxKeys<8> keys = philox_keys<8, true>(p.key0 + 2u * kPhiloxW0, p.key1 + 2u * kPhiloxW1);
+    const NormalConstants normal = normal_constants<true>(p.synth);
+    const float mu = MOM ? in_vector(p.momentum) : 0.0f, wd = MOM ? in_vector(p.weight_decay) : 0.0f;
+    const int v_at = p.n_rows * kQuads;                    // from a row of the strip to its momentum buffer
+    auto execute = [&](const ColumnOp& op) {
         if (op.flags != 0) {
-            v4f* xi = xs + (op.rows & 0xFFFFu) * kQuads;
-            v4f* xj = xs + (op.rows >> 16) * kQuads;
+            v4f* xi = reinterpret_cast<v4f*>(reinterpret_cast<char*>(xs) + (op.rows & 0xFFFFu));
+            v4f* xj = reinterpret_cast<v4f*>(reinterpret_cast<char*>(xs) + (op.rows >> 16));
             const v4f av = *xi, bv = *xj;
             const float a[4] = {av.x, av.y, av.z, av.w}, c[4] = {bv.x, bv.y, bv.z, bv.w};
             float ni[4], nj[4];
-            if (op.flags == kColumnAverage) {      // an extra pair of a general W_k: no gradient, no step
+            if (AVERAGES && op.flags == kColumnAverage) {      // an extra pair of a general W_k: no gradient, no step
 #pragma unroll
                 for (int t = 0; t < 4; ++t) ni[t] = nj[t] = (a[t] + c[t]) * 0.5f;
             } else {
-                v4f g = synth_normals_of(philox_rest(hq, lq, op.a, op.b, op.c, op.d, p.key0, p.key1), p.synth_std);
+                v4f g = synth_normals_of(philox_rest(hq, lq, op, keys), normal);
                 if (tail) {
                     if (4 * q + 0 >= p.d) g.x = 0.0f;
                     if (4 * q + 1 >= p.d) g.y = 0.0f;
@@ -108,13 +106,13 @@ __global__ __launch_bounds__(256) void column_events_kernel(const ColumnParams p
                 }
                 const float gv[4] = {g.x, g.y, g.z, g.w};
                 if (MOM) {
-                    v4f* vi = vs + (op.rows & 0xFFFFu) * kQuads;
+                    v4f* vi = xi + v_at;
                     const v4f vo = *vi;
                     const float vold[4] = {vo.x, vo.y, vo.z, vo.w};
                     float vn[4];
 #pragma unroll
                     for (int t = 0; t < 4; ++t)
-                        average_then_apply_momentum(a[t], c[t], gv[t], vold[t], op.gamma, p.momentum, p.weight_decay, ni[t], nj[t], vn[t]);
+                        average_then_apply_momentum(a[t], c[t], gv[t], vold[t], op.gamma, mu, wd, ni[t], nj[t], vn[t]);
                     *vi = v4f{vn[0], vn[1], vn[2], vn[3]};
                 } else {
 #pragma unroll
@@ -125,7 +123,15 @@ __global__ __launch_bounds__(256) void column_events_kernel(const ColumnParams p
             *xi = v4f{ni[0], ni[1], ni[2], ni[3]};
         }
         wave_lds_sync();
-        op = next;
+    };
+    // two batches per turn, each requested one batch ahead; the table ends with two batches of empty operations
+    ColumnOp even = p.ops[sub];
+    for (int b = 0; b < p.batches; b += 2) {
+        const ColumnOp* __restrict__ next = p.ops + static_cast<int64_t>(b) * P;
+        const ColumnOp odd = next[P + sub];
+        execute(even);
+        even = next[2 * P + sub];
+        execute(odd);
     }
 
     if (!live) return;
@@ -137,17 +143,20 @@ __global__ __launch_bounds__(256) void column_events_kernel(const ColumnParams p
     }
 }
 
-// Four wavefronts to a block, one to each SIMD, as far as 64 KB of LDS go.  Measured with 4 / 3 / 2 / 1 at n = 128, d = 25.6 M,
-// 10 000 events: 182.6 / 191.4 / 194.1 / 191.4 ms, with momentum 266 / 277 / 305 / 271.
+// Four wavefronts to a block, one to each SIMD, as far as 64 KB of LDS go.  Measured with 1 / 2 / 3 / 4 / 5 / 8 / 10 / 16 at
+// n = 128, d = 25.6 M, 2000 events: 35.5 / 34.9 / 35.1 / 33.9 / 34.8 / 34.3 / 35.7 / 36.9 ms; at n = 32, d = 3.0 M with momentum,
+// 500 events: 1.37 / 1.40 / 1.49 / 1.36 / 1.40 / 1.38 / 1.43 / 1.56.
 template <int kQuads>
-hipError_t launch_quads(const ColumnParams& p, hipStream_t st) {
+hipError_t launch_quads(const ColumnParams& p, bool averages, hipStream_t st) {
     const int64_t strip = static_cast<int64_t>(p.n_rows) * kQuads * 16 * (p.V ? 2 : 1);
     const int waves = static_cast<int>(std::min<int64_t>(4, 65536 / strip));
     const int64_t blocks = ((p.n_vec + kQuads - 1) / kQuads + waves - 1) / waves;
     if (waves < 1 || blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     const dim3 grid(static_cast<uint32_t>(blocks)), block(64 * waves);
-    if (p.V) hipLaunchKernelGGL((column_events_kernel<kQuads, true>), grid, block, strip * waves, st, p);
-    else hipLaunchKernelGGL((column_events_kernel<kQuads, false>), grid, block, strip * waves, st, p);
+    if (p.V && averages) hipLaunchKernelGGL((column_events_kernel<kQuads, true, true>), grid, block, strip * waves, st, p);
+    else if (p.V) hipLaunchKernelGGL((column_events_kernel<kQuads, true, false>), grid, block, strip * waves, st, p);
+    else if (averages) hipLaunchKernelGGL((column_events_kernel<kQuads, false, true>), grid, block, strip * waves, st, p);
+    else hipLaunchKernelGGL((column_events_kernel<kQuads, false, false>), grid, block, strip * waves, st, p);
     return hipGetLastError();
 }
 
@@ -167,15 +176,16 @@ hipError_t launch_column_events(const ColumnArgs& a, hipStream_t st) {
     p.batches = a.batches;
     p.key0 = static_cast<uint32_t>(a.synth_seed);
     p.key1 = static_cast<uint32_t>(a.synth_seed >> 32);
-    p.synth_std = a.synth_std;
+    p.synth = synth_scale(a.synth_std);
+
     p.momentum = a.momentum;
     p.weight_decay = a.weight_decay;
     switch (a.quads) {
-        case 4: return launch_quads<4>(p, st);
-        case 8: return launch_quads<8>(p, st);
-        case 16: return launch_quads<16>(p, st);
-        case 32: return launch_quads<32>(p, st);
-        case 64: return launch_quads<64>(p, st);
+        case 4: return launch_quads<4>(p, a.averages, st);
+        case 8: return launch_quads<8>(p, a.averages, st);
+        case 16: return launch_quads<16>(p, a.averages, st);
+        case 32: return launch_quads<32>(p, a.averages, st);
+        case 64: return launch_quads<64>(p, a.averages, st);
         default: return hipErrorInvalidValue;
     }
 }

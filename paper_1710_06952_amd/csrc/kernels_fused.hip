@@ -29,7 +29,7 @@ struct FusedParams {
     const PairOp* ops;
     const float* slots;
     uint16_t* Xbf16;
-    float synth_std;
+    SynthScale synth;
     uint32_t key0, key1;
     float* V;
     float momentum, weight_decay;
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kThreads) void fused_gossip_apply_kernel(const Fuse
         const int64_t eq = tile + (lane >> 4) * kThreads + 64 * wave + 4 * (lane & 15);
         const int64_t q = eq >> 2;
         const v4f z = synth_normals4(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), op.k_lo, op.k_hi,
-                                     p.key0, p.key1, p.synth_std);
+                                     p.key0, p.key1, p.synth);
         *reinterpret_cast<v4f*>(&zs[wave * 256 + 4 * lane]) = z;
         __syncthreads();
 #pragma unroll
@@ -123,11 +123,11 @@ __global__ __launch_bounds__(kThreads) void fused_gossip_apply_kernel(const Fuse
     }
 }
 
-__global__ __launch_bounds__(kThreads) void synth_gradient_kernel(float* out, int64_t d, float std, uint32_t k_lo,
+__global__ __launch_bounds__(kThreads) void synth_gradient_kernel(float* out, int64_t d, SynthScale scale, uint32_t k_lo,
                                                                   uint32_t k_hi, uint32_t key0, uint32_t key1) {
     const int64_t v = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
     if (4 * v >= d) return;
-    const v4f g = synth_normals4(static_cast<uint32_t>(v), static_cast<uint32_t>(v >> 32), k_lo, k_hi, key0, key1, std);
+    const v4f g = synth_normals4(static_cast<uint32_t>(v), static_cast<uint32_t>(v >> 32), k_lo, k_hi, key0, key1, scale);
     const float gv[4] = {g.x, g.y, g.z, g.w};
     for (int t = 0; t < 4; ++t)
         if (4 * v + t < d) out[4 * v + t] = gv[t];
@@ -161,7 +161,7 @@ hipError_t launch_fused_gossip_apply(const FusedArgs& a, hipStream_t st) {
     p.ops = a.ops;
     p.slots = a.slots;
     p.Xbf16 = a.Xbf16;
-    p.synth_std = a.synth_std;
+    p.synth = synth_scale(a.synth_std);
     p.key0 = static_cast<uint32_t>(a.synth_seed);
     p.key1 = static_cast<uint32_t>(a.synth_seed >> 32);
     p.V = a.V;
@@ -180,7 +180,7 @@ hipError_t launch_synth_gradient(uint64_t seed, uint64_t k, float std, int64_t d
     const int64_t n_vec = (d + 3) / 4;
     const int64_t blocks = (n_vec + kThreads - 1) / kThreads;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(synth_gradient_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(kThreads), 0, st, out, d, std,
+    hipLaunchKernelGGL(synth_gradient_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(kThreads), 0, st, out, d, synth_scale(std),
                        static_cast<uint32_t>(k), static_cast<uint32_t>(k >> 32), static_cast<uint32_t>(seed),
                        static_cast<uint32_t>(seed >> 32));
     return hipGetLastError();

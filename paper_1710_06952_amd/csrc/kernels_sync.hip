@@ -40,7 +40,7 @@ struct SyncParams {
     const float* slots;        // gradient of worker i in slot i (data models)
     uint16_t* Xbf16;
     float gamma;
-    float synth_std;
+    SynthScale synth;
     uint32_t key0, key1;
     uint64_t event0;           // synthetic gradients: worker i draws event event0 + i
     float* V;                  // momentum buffers (MOM), else nullptr
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kThreads) void sync_mix_apply_kernel(const SyncPara
                 const uint64_t k = p.event0 + static_cast<uint64_t>(i);
                 const uint64_t q = static_cast<uint64_t>(c) >> 2;
                 g[u] = synth_normals4(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), static_cast<uint32_t>(k),
-                                      static_cast<uint32_t>(k >> 32), p.key0, p.key1, p.synth_std);
+                                      static_cast<uint32_t>(k >> 32), p.key0, p.key1, p.synth);
             } else {
                 g[u] = load4<STREAM>(p.slots + static_cast<int64_t>(i) * p.ld + c);
             }
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(kRingThreads) void sync_ring_apply_kernel(const Syn
                     const uint64_t k = p.event0 + static_cast<uint64_t>(i);
                     const uint64_t q = static_cast<uint64_t>(c) >> 2;
                     const v4f z = synth_normals4(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), static_cast<uint32_t>(k),
-                                                 static_cast<uint32_t>(k >> 32), p.key0, p.key1, p.synth_std);
+                                                 static_cast<uint32_t>(k >> 32), p.key0, p.key1, p.synth);
                     g[u][0] = z.x; g[u][1] = z.y; g[u][2] = z.z; g[u][3] = z.w;
                 } else {
                     ring_load<STREAM>(p.slots + static_cast<int64_t>(i) * p.ld, c, g[u]);
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(kRingThreads) void sync_ring_rows_kernel(const Sync
         const uint64_t k = p.event0 + static_cast<uint64_t>(i);
         const uint64_t q = static_cast<uint64_t>(c) >> 2;
         const v4f z = synth_normals4(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), static_cast<uint32_t>(k),
-                                     static_cast<uint32_t>(k >> 32), p.key0, p.key1, p.synth_std);
+                                     static_cast<uint32_t>(k >> 32), p.key0, p.key1, p.synth);
         g[0] = z.x; g[1] = z.y; g[2] = z.z; g[3] = z.w;
     } else {
         ring_load<STREAM>(p.slots + static_cast<int64_t>(i) * p.ld, c, g);
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kRingThreads) void sync_graph_rows_kernel(const Syn
         const uint64_t k = p.event0 + static_cast<uint64_t>(i);
         const uint64_t q = static_cast<uint64_t>(c) >> 2;
         const v4f z = synth_normals4(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), static_cast<uint32_t>(k),
-                                     static_cast<uint32_t>(k >> 32), p.key0, p.key1, p.synth_std);
+                                     static_cast<uint32_t>(k >> 32), p.key0, p.key1, p.synth);
         g[0] = z.x; g[1] = z.y; g[2] = z.z; g[3] = z.w;
     } else {
         ring_load<STREAM>(p.slots + static_cast<int64_t>(i) * p.ld, c, g);
@@ -490,7 +490,7 @@ hipError_t launch_sync_mix_apply(const SyncArgs& a, hipStream_t st) {
     p.slots = a.slots;
     p.Xbf16 = a.Xbf16;
     p.gamma = a.gamma;
-    p.synth_std = a.synth_std;
+    p.synth = synth_scale(a.synth_std);
     p.key0 = static_cast<uint32_t>(a.synth_seed);
     p.key1 = static_cast<uint32_t>(a.synth_seed >> 32);
     p.event0 = a.event0;

@@ -59,3 +59,28 @@ def test_events_in_columns_are_the_events_of_the_rounds(P, n, d, K, mu):
     assert ref.get_stats()["fused_launches"] == ref.get_stats()["rounds"]
     eng.close()
     ref.close()
+
+
+# calls without extra pairs (a variant of its own), whose number of batches is odd and even: every event of a pair of workers
+# depends on the one before, so K events are K batches; d with and without a tail
+@pytest.mark.parametrize("d", [4096, 4099])
+@pytest.mark.parametrize("K", [11, 12, 13])
+@pytest.mark.parametrize("mu", [0.0, 0.9])
+def test_calls_without_extra_pairs(P, K, d, mu):
+    print("columns without extra pairs d=%d K=%d mu=%g" % (d, K, mu), flush=True)
+    g, n = ring_graph(6), 6
+    sched = oracle.make_schedule(g, K, seed=8, T_max=2)
+    sched["worker"][:], sched["neighbour"][:] = 2, 3
+    x0 = np.random.default_rng(5).standard_normal((n, d)).astype(np.float32)
+    got = []
+    for rounds in (False, True):
+        eng = P.Engine(g, d, "synth", gamma=0.1, T_max=2, synth_std=0.3, synth_seed=5, momentum=mu, weight_decay=1e-3 if mu else 0.0,
+                       verify_plan=True, rounds=rounds)
+        eng.set_models(x0, broadcast=False)
+        eng.run_events(sched)
+        got.append((eng.get_models(), eng.get_momentum() if mu else None, eng.get_stats()["fused_launches"]))
+        eng.close()
+    assert (got[0][2], got[1][2]) == (1, K)
+    assert np.array_equal(got[0][0], got[1][0])
+    if mu:
+        assert np.array_equal(got[0][1], got[1][1])
