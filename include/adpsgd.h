@@ -79,7 +79,8 @@ enum {
     ADPSGD_FLAG_DENSE_GRADIENT = 2  /* always write gradients out as dense vectors.  By default (without the
                                        wait-free variant) low-rank gradients stay in factored form until the
                                        update kernel applies them: the MLP's first layer as dH and the minibatch
-                                       inputs, least squares on long models as its M coefficients.  The values
+                                       inputs, least squares on long models as its M coefficients (where these take
+                                       its rows in two passes; in one pass it is dense).  The values
                                        are the same; the dense form costs one more launch and a write and
                                        read-back of the gradient per event.  Calls in one launch keep the gradients
                                        dense on the chip in any case */
@@ -224,7 +225,9 @@ int adpsgd_set_route(adpsgd_t* h, int32_t route);
 /* How long the blocks of a call in one launch wait for each other (linear models).
  *   assembly_us     the state is touched only once all blocks of the launch are on the device.  While other work holds
  *                   compute units for longer than this, one block executes the call by itself, which is slow but gives the
- *                   same results within rounding.  0: always so.  Default 10 000 000.
+ *                   same results within rounding.  0: always so.  Default 10 000 000.  The gradients that are evaluated
+ *                   in one pass over the minibatch rows (rounds and synchronous iterations of linear models) wait for
+ *                   each other too, for this long or 1000 us if that is less; then a block goes on by itself likewise.
  *                   Outside [0, 2^31): ADPSGD_ERR_ARG.
  *   lose_exchange   Once all blocks are on the device they exchange partial sums.  One that does not find a sum after 2^21
  *                   polls (about a second: a fault of the device) gives the launch up and the models are undefined, which

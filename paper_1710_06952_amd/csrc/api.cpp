@@ -172,6 +172,48 @@ void settle_strips(adpsgd_t* h) {
     h->alone_slots.release();
 }
 
+void settle_onepass(adpsgd_t* h) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    int dev = 0, cus = 0;
+    if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    const OnePassShape s = onepass_shape(h->o.model, h->d, h->o.M, cus);
+    if (!s.ok()) return;
+    if (h->onepass_words.reserve(onepass_exchange_bytes(s, h->o.M)) == hipSuccess &&
+        hipMemset(h->onepass_words.p, 0, h->onepass_words.cap) == hipSuccess && hipStreamSynchronize(nullptr) == hipSuccess) {
+        h->onepass = s;
+        return;
+    }
+    (void)hipGetLastError();
+    h->onepass_words.release();
+}
+
+bool can_run_onepass(const adpsgd_t* h) {
+    if (!h->onepass.ok()) return false;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return capture == hipStreamCaptureStatusNone;
+}
+
+int launch_onepass(adpsgd_t* h, const LinearGradArgs& a) {
+    if (h->onepass_seq > 0xFFFFFFFFu - static_cast<uint32_t>(a.n_ops)) {      // before the numbers wrap
+        HIP_TRY(h, hipMemsetAsync(h->onepass_words.p, 0, h->onepass_words.cap, h->stream));
+        h->onepass_seq = 0;
+    }
+    const uint64_t wait_us = static_cast<uint64_t>(std::min(h->assembly_us, kOnePassWaitUs));
+    const OnePassArgs o{h->onepass, a.model, a.X, a.ld, a.d, a.ops, a.n_ops, a.M, a.batch_idx, a.slots, a.gscale, a.lambda, a.loss,
+                        static_cast<unsigned long long*>(h->onepass_words.p), h->onepass_seq + 1, wait_us * kClockTicksPerUs};
+    HIP_TRY(h, launch_onepass_gradient(o, h->stream));
+    h->onepass_seq += static_cast<uint32_t>(a.n_ops);
+    return ADPSGD_OK;
+}
+
 }  // namespace adpsgd_impl
 
 using namespace adpsgd_impl;
@@ -234,7 +276,9 @@ extern "C" int adpsgd_create(adpsgd_t** out, const adpsgd_graph_t* graph, int64_
     h->stream = static_cast<hipStream_t>(o.stream);
     h->streaming = static_cast<int64_t>(n) * o.ldx * 4 > kStreamingThreshold;
     h->stats.slots = n_slots;
+    settle_onepass(h.get());
     settle_strips(h.get());
+    settle_onepass(h.get());
     for (auto& t : h->tables) {
         hipError_t e = hipEventCreateWithFlags(&t.done, hipEventDisableTiming);
         if (e != hipSuccess) {
@@ -268,6 +312,7 @@ extern "C" void adpsgd_destroy(adpsgd_t* h) {
     h->exchange.release();
     h->exchange_status.release();
     h->alone_slots.release();
+    h->onepass_words.release();
     delete h;
 }
 
@@ -399,6 +444,7 @@ struct EventCall {
     bool factored = false;      // perceptron: dW1 stays in factored form until the update kernel
     bool lin_factored = false;  // least squares on long models: the gradient stays M coefficients
     bool strips = false;        // linear models: all events in one launch (kernels_strips.hip)
+    bool onepass = false;       // linear models: gradients in one pass over the rows (kernels_onepass.hip), dense
     Plan plan;
     std::vector<int64_t> u_off, r_off;      // first update / gradient operation of every round
     int32_t group = 1;                      // gradients of a round are launched in groups of this many operations
@@ -483,6 +529,8 @@ int prepare_call(adpsgd_t* h, const adpsgd_schedule_t* s, EventCall& c) {
     // gradients pending from an earlier call come as it left them: dense vectors, or coefficients
     c.strips = with_data && can_run_strips(h) && (!any_carried || h->pending_dense);
     if (any_carried && h->pending_dense) c.lin_factored = false;
+    c.onepass = with_data && onepass_for_events(h->onepass, h->o.model, c.M, comp) && can_run_onepass(h) && (!any_carried || h->pending_dense);
+    if (c.onepass) c.lin_factored = false;
 
     std::string perr;
     const int rc = plan_rounds(h->n, c.K, s->worker, s->neighbour, s->tau, h->n_slots, c.with_grad, c.plan, perr,
@@ -679,7 +727,13 @@ int launch_gradients(adpsgd_t* h, const EventCall& c, int32_t r, float* loss, ad
             LinearGradArgs a{h->o.model, h->o.X, h->o.ldx, h->d, c.d_rops + g0, cnt, c.M, c.d_batch, slots, gscale, h->o.lambda,
                              static_cast<float*>(h->grad_scratch.p),
                              reinterpret_cast<float*>(static_cast<char*>(h->grad_scratch.p) + c.off_coef), loss, c.lin_factored};
-            HIP_TRY(h, launch_linear_gradient(a, h->stream, &launches));
+            if (c.onepass) {
+                rc = launch_onepass(h, a);
+                if (rc != ADPSGD_OK) return rc;
+                launches = 1;
+            } else {
+                HIP_TRY(h, launch_linear_gradient(a, h->stream, &launches));
+            }
         }
         h->stats.grad_launches += launches;
         rc = end_timing(h, e0, e1, h->ev_grad);

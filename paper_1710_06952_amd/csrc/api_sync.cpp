@@ -112,6 +112,7 @@ int run_sync_steps_impl(adpsgd_t* h, const adpsgd_sync_schedule_t* s, float* los
             HIP_TRY(h, h->grad_scratch.reserve(off_coef + static_cast<size_t>(group) * M * 4));
         }
     }
+    const bool onepass = with_data && can_run_onepass(h);
     const bool profile = (h->o.flags & ADPSGD_FLAG_PROFILE) != 0;
     // a ring in canonical order: row i mixes with rows i - 1 and i + 1 only, listed in that order
     bool ring = n >= 3 && nnz == 2 * n;
@@ -160,7 +161,13 @@ int run_sync_steps_impl(adpsgd_t* h, const adpsgd_sync_schedule_t* s, float* los
                                  slots, gscale, h->o.lambda,
                                  static_cast<float*>(h->grad_scratch.p),
                                  reinterpret_cast<float*>(static_cast<char*>(h->grad_scratch.p) + off_coef), loss, false};
-                HIP_TRY(h, launch_linear_gradient(a, h->stream, &launches));
+                if (onepass) {
+                    const int rc = launch_onepass(h, a);
+                    if (rc != ADPSGD_OK) return rc;
+                    launches = 1;
+                } else {
+                    HIP_TRY(h, launch_linear_gradient(a, h->stream, &launches));
+                }
             }
             h->stats.grad_launches += launches;
         }

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "onepass.hpp"
 
 namespace adpsgd_impl {
 
@@ -81,6 +82,9 @@ struct adpsgd {
     uint32_t exchange_seq = 0;            // ... the sequence number of the last gradient
     adpsgd_impl::HostBuf exchange_status; // ... a word the kernel sets when a wait had to be given up ...
     adpsgd_impl::DevBuf alone_slots;      // ... and slots for a block that executes a call alone
+    adpsgd_impl::OnePassShape onepass;    // linear models, gradients in one pass over the rows; not ok(): in three launches ...
+    adpsgd_impl::DevBuf onepass_words;    // ... the words the blocks exchange ...
+    uint32_t onepass_seq = 0;             // ... the sequence number of the last gradient
     int64_t assembly_us = adpsgd_impl::kAssemblyUs;      // adpsgd_set_wait_limits ...
     bool lose_exchange = false;                          // ...
     adpsgd_stats_t stats{};
@@ -109,6 +113,12 @@ hipEvent_t take_event(adpsgd_t* h);
 int check_exchange(adpsgd_t* h);
 // Create-time decision and memory of the one-launch path of the linear models (strip_units, exchange).
 void settle_strips(adpsgd_t* h);
+// The same for the gradients in one pass over the minibatch rows (onepass, onepass_words).
+void settle_onepass(adpsgd_t* h);
+// Whether this call can take them: a stream under capture would replay their sequence numbers.
+bool can_run_onepass(const adpsgd_t* h);
+// One group of them; `a` as for launch_linear_gradient.
+int launch_onepass(adpsgd_t* h, const LinearGradArgs& a);
 // Fold the timings of finished launches into the statistics (synchronises the stream).
 int drain_profile(adpsgd_t* h);
 

@@ -14,13 +14,10 @@
 //   2. finalize: z -> per-sample coefficient c_m and the minibatch loss
 //   3. combine:  g[chunk] = sum_m c_m A[idx_m, chunk] (+ reg * x^[chunk]) into the pending slot
 // The gathered rows are read twice, both times from HBM (re-reading them from the
-// memory-side cache is no faster).  One pass needs the rows held on the chip and
-// a dependency across it: with fences and counters that took 167 us for two
-// gradients against 23 for two passes; the words of exchange.hpp take 1.2 us between 256 blocks,
-// less than the 5.4 us of a second read of 33 MB, but the layout measured with
-// them, the strip kernel's (two gradients of 1 KB pieces per block, rows
-// requested only after the last gradient is done), took 8.6 ms against 5.95 at
-// n = 64, d = 65 536, M = 128.  Others have not been tried.  Short models
+// memory-side cache is no faster).  Where a gradient fits the registers of the chip
+// its rows are read once instead (kernels_onepass.hip, where the line between
+// the two is drawn); with fences and counters in the place of its
+// exchange words one pass took 167 us for two gradients against 23.  Short models
 // (d <= 2048) take the single-block kernel at the end of this file.  Partial sums
 // are combined in a fixed order: results do not depend on scheduling.
 #include "device_common.hpp"

@@ -1,0 +1,45 @@
+// Interface of the linear gradients in one pass over the minibatch rows (kernels_onepass.hip).
+#pragma once
+
+#include "internal.hpp"
+
+namespace adpsgd_impl {
+
+constexpr int kOnePassThreads = 512;
+constexpr int kOnePassWaves = kOnePassThreads / 64;
+constexpr int kOnePassMaxM = 128;
+constexpr int kOnePassMaxStrips = 256;
+constexpr int64_t kOnePassWaitUs = 1000;      // how long a block waits for the others before it goes on by itself
+
+// How a gradient lies on the chip: its columns in `strips` strips of one block each, the rows of a strip over
+// `row_groups` groups of wavefronts with `rows` rows each, the strip's columns over 8 / row_groups wavefronts of `chunks` times
+// 256 columns; `groups` gradients at a time.
+struct OnePassShape {
+    int32_t rows = 0, chunks = 0, row_groups = 0, strips = 0, groups = 0;
+    bool ok() const { return strips > 0; }
+};
+// The shape for a handle, by its sizes alone (so that a gradient has the same bits in every call), or one that is not ok():
+// three launches per round (kernels_grad_linear.hip) are the better route, or the only one.
+OnePassShape onepass_shape(int model, int64_t d, int32_t M, int32_t compute_units);
+// Whether run_events takes it too (the synchronous schedule does wherever there is a shape).
+bool onepass_for_events(const OnePassShape& s, int model, int32_t M, bool wait_free);
+size_t onepass_exchange_bytes(const OnePassShape& s, int32_t M);
+
+struct OnePassArgs {
+    OnePassShape shape;
+    int model;
+    const float* X;
+    int64_t ld, d;
+    const GradOp* ops;          // device
+    int32_t n_ops, M;
+    const int32_t* batch_idx;   // device, by event
+    float* slots;
+    float gscale, lambda;
+    float* loss;                // device, by event, or nullptr
+    unsigned long long* words;  // onepass_exchange_bytes, zero before the first launch
+    uint32_t seq0;              // sequence number of the first gradient; n_ops of them are used
+    uint64_t wait_ticks;        // of the constant clock
+};
+hipError_t launch_onepass_gradient(const OnePassArgs& a, hipStream_t st);
+
+}  // namespace adpsgd_impl
