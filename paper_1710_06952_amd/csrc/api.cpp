@@ -442,6 +442,11 @@ struct EventCall {
     bool mlp_comp = false;      // perceptron, wait-free variant: compensated bf16 rows
     bool ext_comp = false;      // caller's function, wait-free variant: compensated fp32 rows
     bool factored = false;      // perceptron: dW1 stays in factored form until the update kernel
+    bool chained = false;       // perceptron: the updates of a round come in chains
+    std::vector<MlpChain> chains;           // chained: the updates, by round ...
+    std::vector<int64_t> chain_off;         // ... and where those of a round begin
+    std::vector<int64_t> chain_event;       // ... and the event of every operation, -1: averaging only
+    const MlpChain* d_chains = nullptr;
     bool lin_factored = false;  // least squares on long models: the gradient stays M coefficients
     bool strips = false;        // linear models: all events in one launch (kernels_strips.hip)
     bool onepass = false;       // linear models: gradients in one pass over the rows (kernels_onepass.hip), dense
@@ -454,8 +459,7 @@ struct EventCall {
     const PairOp* d_uops = nullptr;         // the device copy
     const GradOp* d_rops = nullptr;
     const int32_t* d_batch = nullptr;
-    int32_t* batch_r = nullptr;             // perceptron: the minibatch indices again, in the order of rops ...
-    int32_t* batch_u = nullptr;             // ... and of uops (pinned staging)
+    int32_t* batch_r = nullptr;             // perceptron: the minibatch indices again, in the order of rops (pinned staging)
     const int32_t* d_batch_r = nullptr;
     const int32_t* d_batch_u = nullptr;
     std::vector<int32_t> carried_slot;      // per event: slot of a gradient evaluated by an earlier call, or -1; or empty
@@ -525,6 +529,7 @@ int prepare_call(adpsgd_t* h, const adpsgd_schedule_t* s, EventCall& c) {
     c.mlp_comp = h->o.model == ADPSGD_MODEL_MLP && comp;
     c.ext_comp = c.external && comp;
     c.factored = h->o.model == ADPSGD_MODEL_MLP && !dense && !comp && mlp_can_factor(h->o.mlp_in, h->o.mlp_hidden, c.M);
+    c.chained = h->o.model == ADPSGD_MODEL_MLP;
     c.lin_factored = with_data && !dense && !comp && linear_can_factor(h->o.model, h->d, c.M, h->o.ldx);
     // gradients pending from an earlier call come as it left them: dense vectors, or coefficients
     c.strips = with_data && can_run_strips(h) && (!any_carried || h->pending_dense);
@@ -534,11 +539,11 @@ int prepare_call(adpsgd_t* h, const adpsgd_schedule_t* s, EventCall& c) {
 
     std::string perr;
     const int rc = plan_rounds(h->n, c.K, s->worker, s->neighbour, s->tau, h->n_slots, c.with_grad, c.plan, perr,
-                               s->extra_ptr, s->extra_a, s->extra_b, comp, c.A, carried);
+                               s->extra_ptr, s->extra_a, s->extra_b, comp, c.A, carried, c.chained ? kMlpChain : 1);
     if (rc != ADPSGD_OK) return fail(h, rc, perr);
     if ((h->o.flags & ADPSGD_FLAG_VERIFY_PLAN) &&
         !verify_plan(h->n, c.K, s->worker, s->neighbour, s->tau, h->n_slots, c.with_grad, c.plan, perr, s->extra_ptr, s->extra_a,
-                     s->extra_b, c.A, carried))
+                     s->extra_b, c.A, carried, c.chained))
         return fail(h, ADPSGD_ERR_STATE, perr);
 
     const int32_t R = c.plan.n_rounds;
@@ -565,8 +570,6 @@ void fill_update(adpsgd_t* h, EventCall& c, int64_t k, std::vector<int64_t>& u_f
     const adpsgd_schedule_t* s = c.s;
     const uint64_t gk = h->events_done + static_cast<uint64_t>(k);
     const int32_t ur = c.plan.u_round[k];
-    const bool factors = c.factored || c.lin_factored;
-    if (c.batch_u) std::memcpy(c.batch_u + u_fill[ur] * c.M, s->batch_idx + k * static_cast<int64_t>(c.M), static_cast<size_t>(c.M) * 4);
     PairOp& u = c.uops[u_fill[ur]++];
     u.i = s->worker[k];
     u.j = s->neighbour[k];
@@ -576,11 +579,56 @@ void fill_update(adpsgd_t* h, EventCall& c, int64_t k, std::vector<int64_t>& u_f
     u.slot = c.with_grad ? c.plan.slot[k] : 0;
     u.flags = 0;
     u.event = static_cast<int32_t>(k);
-    u.features = factors ? h->data[u.i].features : nullptr;
-    u.feat_ld = factors ? h->data[u.i].ld : 0;
+    u.features = c.lin_factored ? h->data[u.i].features : nullptr;
+    u.feat_ld = c.lin_factored ? h->data[u.i].ld : 0;
     if (s->extra_ptr)
         for (int64_t q = s->extra_ptr[k]; q < s->extra_ptr[k + 1]; ++q)
             c.uops[u_fill[ur]++] = PairOp{s->extra_a[q], s->extra_b[q], 0u, 0u, 0.0f, 0, 1, 0, nullptr, 0};
+}
+
+// The updates of a perceptron's call as the chains of every round.
+int build_chains(adpsgd_t* h, EventCall& c) {
+    const adpsgd_schedule_t* s = c.s;
+    std::vector<ColumnPair> pairs(static_cast<size_t>(c.A + c.n_extra));
+    std::vector<int64_t> fill(c.u_off.begin(), c.u_off.end() - 1);
+    for (int64_t k = 0; k < c.A; ++k) {
+        int64_t& at = fill[c.plan.u_round[k]];
+        pairs[at++] = ColumnPair{s->worker[k], s->neighbour[k], k};
+        if (s->extra_ptr)
+            for (int64_t q = s->extra_ptr[k]; q < s->extra_ptr[k + 1]; ++q) pairs[at++] = ColumnPair{s->extra_a[q], s->extra_b[q], -1};
+    }
+    ChainLayout layout;
+    chain_rounds(pairs, c.u_off, h->n, layout);
+    if ((h->o.flags & ADPSGD_FLAG_VERIFY_PLAN) && !verify_chains(pairs, c.u_off, h->n, kMlpChain, layout))
+        return fail(h, ADPSGD_ERR_STATE, "plan check: chains of updates out of order");
+    c.chain_off = layout.round;
+    c.chains.resize(layout.first.size() - 1);
+    c.chain_event.resize(pairs.size());
+    for (size_t t = 0; t < c.chains.size(); ++t) {
+        MlpChain& ch = c.chains[t];
+        ch = MlpChain{};
+        ch.first = static_cast<int32_t>(layout.first[t]);
+        ch.n_ops = static_cast<int32_t>(layout.first[t + 1] - layout.first[t]);
+        if (ch.n_ops > kMlpChain) return fail(h, ADPSGD_ERR_STATE, "run_events: a chain of updates is too long");
+        std::fill_n(ch.rows, kMlpChain + 1, -1);
+        int32_t n_rows = 0;
+        auto place = [&](int32_t row) {
+            const int32_t at = static_cast<int32_t>(std::find(ch.rows, ch.rows + n_rows, row) - ch.rows);
+            if (at == n_rows) ch.rows[n_rows++] = row;
+            return at;
+        };
+        for (int32_t u = 0; u < ch.n_ops; ++u) {
+            const ColumnPair& pair = pairs[layout.order[ch.first + u]];
+            const int64_t k = pair.event;
+            const int32_t pi = place(pair.i), pj = place(pair.j);
+            const WorkerData& w = h->data[pair.i];
+            c.chain_event[ch.first + u] = k;
+            ch.ops[u] = MlpChainOp{w.features, w.ld, k >= 0 ? c.plan.slot[k] : 0, k < 0 ? 0.0f : s->gamma ? s->gamma[k] : h->o.gamma, pi | pj << 4, k < 0};
+            if (k >= 0) ch.steps |= 1 << pi;
+        }
+        std::fill(ch.ops + ch.n_ops, ch.ops + kMlpChain, ch.ops[ch.n_ops - 1]);
+    }
+    return ADPSGD_OK;
 }
 
 // The stale read and gradient of event k, appended to its round.
@@ -606,7 +654,7 @@ void fill_gradient(adpsgd_t* h, EventCall& c, int64_t k, std::vector<int64_t>& r
         g.xrow_bf16 = static_cast<uint16_t*>(h->comp_rows.p) + ((at - c.r_off[rr]) % c.group) * h->o.ldx;
 }
 
-// Tables [PairOp x (K + extra pairs)][GradOp x K][batch_idx K x M], filled in pinned memory in round
+// Tables [PairOp x (K + extra pairs), or the chains][GradOp x K][batch_idx K x M], filled in pinned memory in round
 // order and uploaded with one copy; scratch memory of the gradient kernels.
 int upload_tables(adpsgd_t* h, EventCall& c) {
     const adpsgd_schedule_t* s = c.s;
@@ -614,14 +662,18 @@ int upload_tables(adpsgd_t* h, EventCall& c) {
     const int32_t M = c.M;
     if (c.mlp_comp) HIP_TRY(h, h->comp_rows.reserve(static_cast<size_t>(c.group) * h->o.ldx * sizeof(uint16_t)));
     if (c.ext_comp) HIP_TRY(h, h->comp_rows.reserve(static_cast<size_t>(c.group) * h->o.ldx * sizeof(float)));
-    const size_t bytes_u = static_cast<size_t>(c.A + c.n_extra) * sizeof(PairOp);
+    if (c.chained) {
+        const int rc = build_chains(h, c);
+        if (rc != ADPSGD_OK) return rc;
+    }
+    const size_t bytes_u = c.chained ? c.chains.size() * sizeof(MlpChain) : static_cast<size_t>(c.A + c.n_extra) * sizeof(PairOp);
     const size_t bytes_r = c.with_grad ? static_cast<size_t>(K) * sizeof(GradOp) : 0;
     const size_t bytes_b = static_cast<size_t>(K) * M * sizeof(int32_t);
     const size_t off_r = bytes_u, off_b = (off_r + bytes_r + 15) & ~size_t(15);
     // the perceptron's kernels read the indices by operation instead of by event: one copy in the order of the
-    // gradient operations, one in the order of the update operations (rows of averaging-only pairs stay zero)
+    // gradient operations, one in the order of the chains' operations (rows of averaging-only pairs stay zero)
     const bool by_op = h->o.model == ADPSGD_MODEL_MLP;
-    const size_t bytes_br = by_op ? bytes_b : 0, bytes_bu = by_op ? static_cast<size_t>(c.A + c.n_extra) * M * sizeof(int32_t) : 0;
+    const size_t bytes_br = by_op ? bytes_b : 0, bytes_bu = c.factored ? static_cast<size_t>(c.A + c.n_extra) * M * sizeof(int32_t) : 0;
     const size_t off_br = off_b + (by_op ? 0 : bytes_b), off_bu = off_br + bytes_br;
     const size_t total = off_bu + bytes_bu;
 
@@ -639,18 +691,24 @@ int upload_tables(adpsgd_t* h, EventCall& c) {
     c.rops = reinterpret_cast<GradOp*>(stage + off_r);
     if (by_op) {
         c.batch_r = reinterpret_cast<int32_t*>(stage + off_br);
-        c.batch_u = reinterpret_cast<int32_t*>(stage + off_bu);
         std::memset(stage + off_br, 0, bytes_br + bytes_bu);
+    }
+    if (c.chained) std::memcpy(stage, c.chains.data(), bytes_u);
+    if (c.factored) {
+        int32_t* batch_u = reinterpret_cast<int32_t*>(stage + off_bu);
+        for (size_t q = 0; q < c.chain_event.size(); ++q)
+            if (c.chain_event[q] >= 0) std::memcpy(batch_u + q * M, s->batch_idx + c.chain_event[q] * static_cast<int64_t>(M), static_cast<size_t>(M) * 4);
     }
     std::vector<int64_t> u_fill(c.u_off.begin(), c.u_off.end() - 1), r_fill(c.r_off.begin(), c.r_off.end() - 1);
     for (int64_t k = 0; k < K; ++k) {
-        if (k < c.A) fill_update(h, c, k, u_fill);
+        if (k < c.A && !c.chained) fill_update(h, c, k, u_fill);
         if (c.with_grad && c.plan.r_round[k] >= 0) fill_gradient(h, c, k, r_fill);
     }
     if (bytes_b > 0 && !by_op) std::memcpy(stage + off_b, s->batch_idx, bytes_b);
     HIP_TRY(h, hipMemcpyAsync(T.dev.p, T.stage.p, total, hipMemcpyHostToDevice, h->stream));
     const char* dev = static_cast<const char*>(T.dev.p);
     c.d_uops = reinterpret_cast<const PairOp*>(dev);
+    c.d_chains = reinterpret_cast<const MlpChain*>(dev);
     c.d_rops = reinterpret_cast<const GradOp*>(dev + off_r);
     c.d_batch = reinterpret_cast<const int32_t*>(dev + off_b);
     c.d_batch_r = reinterpret_cast<const int32_t*>(dev + off_br);
@@ -755,15 +813,16 @@ int launch_updates(adpsgd_t* h, const EventCall& c, int32_t r) {
         LinearApplyArgs a{h->o.X, h->o.ldx, h->d, d_ops, static_cast<int32_t>(nu), slots, c.d_batch, c.M,
                           h->streaming, h->o.V, h->o.momentum, h->o.weight_decay};
         HIP_TRY(h, launch_linear_apply_factored(a, h->stream));
-    } else if (c.factored) {
-        MlpApplyArgs a{h->o.X, h->o.ldx, h->d, h->o.mlp_in, h->o.mlp_hidden, c.M, d_ops, static_cast<int32_t>(nu), slots, h->o.Xbf16,
-                       c.d_batch_u + c.u_off[r] * c.M, h->o.V, h->o.momentum, h->o.weight_decay};
-        HIP_TRY(h, launch_mlp_apply_factored(a, h->stream));
+    } else if (c.chained) {
+        MlpApplyArgs a{h->o.X, h->o.ldx, h->d, h->o.mlp_in, h->o.mlp_hidden, c.M, c.d_chains + c.chain_off[r],
+                       static_cast<int32_t>(c.chain_off[r + 1] - c.chain_off[r]), slots, h->o.Xbf16, c.d_batch_u, c.factored, h->o.V,
+                       h->o.momentum, h->o.weight_decay};
+        HIP_TRY(h, launch_mlp_apply_chains(a, h->stream));
     } else {
         bool has_solo = false;
         for (int64_t t = c.u_off[r]; t < c.u_off[r + 1] && !has_solo; ++t) has_solo = c.uops[t].i == c.uops[t].j;
         FusedArgs a{h->o.X, h->o.ldx, h->d, d_ops, static_cast<int32_t>(nu), slots,
-                    h->o.model == ADPSGD_MODEL_MLP ? h->o.Xbf16 : nullptr, h->o.synth_std, h->o.synth_seed,
+                    h->o.synth_std, h->o.synth_seed,
                     !c.with_grad, h->streaming, has_solo, h->o.V, h->o.momentum, h->o.weight_decay};
         HIP_TRY(h, launch_fused_gossip_apply(a, h->stream));
     }

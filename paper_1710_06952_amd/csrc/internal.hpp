@@ -21,8 +21,8 @@ struct alignas(32) PairOp {
     float gamma;
     int32_t slot;     // pending-gradient slot holding g_k (data models)
     int32_t flags;    // bit 0: average only (an extra pair of a general W_k): no gradient, no step
-    int32_t event;    // index into the call's batch_idx array (perceptron, factored gradient)
-    const void* features;   // worker i's inputs (perceptron, factored gradient), else nullptr
+    int32_t event;    // index into the call's batch_idx array (least squares, factored gradient)
+    const void* features;   // worker i's inputs (least squares, factored gradient), else nullptr
     int64_t feat_ld;
 };
 
@@ -93,11 +93,11 @@ int plan_rounds(int32_t n, int64_t K, const int32_t* worker, const int32_t* neig
                 const int32_t* tau, int32_t n_slots, bool with_gradients, Plan& plan,
                 std::string& err, const int64_t* extra_ptr = nullptr, const int32_t* extra_a = nullptr,
                 const int32_t* extra_b = nullptr, bool local_compensation = false,
-                int64_t n_apply = -1, const int32_t* carried_slot = nullptr);
+                int64_t n_apply = -1, const int32_t* carried_slot = nullptr, int32_t chain = 1);
 bool verify_plan(int32_t n, int64_t K, const int32_t* worker, const int32_t* neighbour, const int32_t* tau,
                  int32_t n_slots, bool with_gradients, const Plan& plan, std::string& err,
                  const int64_t* extra_ptr = nullptr, const int32_t* extra_a = nullptr, const int32_t* extra_b = nullptr,
-                 int64_t n_apply = -1, const int32_t* carried_slot = nullptr);
+                 int64_t n_apply = -1, const int32_t* carried_slot = nullptr, bool chained = false);
 bool graph_ok(const adpsgd_graph_t* g, std::string& err);
 
 // ---- kernel launchers (each returns the hipError_t of the launch) ------------
@@ -108,7 +108,6 @@ struct FusedArgs {
     const PairOp* ops;   // device
     int32_t n_ops;
     const float* slots;  // device, slot s at slots + s * ld (data models)
-    uint16_t* Xbf16;     // device bf16 shadow or nullptr
     float synth_std;
     uint64_t synth_seed;
     bool synth;
@@ -140,6 +139,15 @@ struct ColumnPair {
     int32_t i, j;           // local row numbers
     int64_t event;          // index of the event in the call, or -1: averaging only
 };
+// The operations of every round (pairs[offset[r] .. offset[r + 1]), in event order) by chains: those connected by their rows.
+struct ChainLayout {
+    std::vector<int64_t> order;     // operations, chain after chain
+    std::vector<int64_t> first;     // per chain: where it begins in `order` (and the end)
+    std::vector<int64_t> round;     // per round: its first chain (and the end)
+};
+void chain_rounds(const std::vector<ColumnPair>& pairs, const std::vector<int64_t>& offset, int32_t n_rows, ChainLayout& out);
+// Whether a layout keeps the order of every row and has at most `most` operations in a chain (ADPSGD_FLAG_VERIFY_PLAN).
+bool verify_chains(const std::vector<ColumnPair>& pairs, const std::vector<int64_t>& offset, int32_t n_rows, int32_t most, const ChainLayout& c);
 // Packs the operations into batches of `capacity` with pairwise disjoint rows such that the operations of every row
 // keep their order from batch to batch: every operation goes into the first batch with room behind those of its rows.
 // place[t] = batch * capacity + position; returns the number of batches.
@@ -212,23 +220,41 @@ size_t mlp_scratch_bytes(int32_t n_ops, int32_t M, int32_t in, int32_t hid, int3
 hipError_t launch_mlp_loss(const MlpGradArgs& a, double* loss_sum, bool count_errors, hipStream_t st);
 bool mlp_can_factor(int32_t in, int32_t hid, int32_t M);
 
-// The perceptron's model update with the first-layer gradient still in factored form
+// The perceptron's model update, with the first-layer gradient still in factored form where that is possible
 // (dW1 = Xb^T dH, rank <= M): the product is formed tile by tile on the matrix cores inside
 // the update kernel instead of being written to and read back from the pending slot.
+// The updates of a round come in chains of operations that share rows (chain_rounds).
+constexpr int kMlpChain = 3;            // operations of a chain, at most; they touch one row more
+struct MlpChainOp {
+    const void* features;               // worker i's inputs (average only: any worker's, read and dropped)
+    int64_t feat_ld;
+    int32_t slot;
+    float gamma;
+    int32_t places;                     // of rows i and j (bits 4 and up) in the chain's rows
+    int32_t average;                    // an extra pair of a general W_k: no gradient, no step
+};
+struct alignas(32) MlpChain {
+    int32_t first, n_ops;               // row of the first operation in the table of minibatch indices
+    int32_t rows[kMlpChain + 1];        // -1: none
+    int32_t steps;                      // places whose row takes a gradient step (bits): their momentum is read and written
+    int32_t pad;
+    MlpChainOp ops[kMlpChain];          // beyond n_ops: the last one again (its operands are requested, and dropped)
+};
 struct MlpApplyArgs {
     float* X;
     int64_t ld;
     int64_t d;
     int32_t in, hid, M;
-    const PairOp* ops;      // device
-    int32_t n_ops;
+    const MlpChain* chains; // device
+    int32_t n_chains;
     const float* slots;
     uint16_t* Xbf16;
-    const int32_t* batch_by_op; // device, n_ops x M: row t holds the minibatch indices of the event of ops[t]
+    const int32_t* batch_by_op; // device, rows of M: the minibatch indices of the chains' operations (factored)
+    bool factored;              // dW1 as its factors, else the whole gradient is in the slot
     float* V;                   // momentum buffers or nullptr
     float momentum, weight_decay;
 };
-hipError_t launch_mlp_apply_factored(const MlpApplyArgs& a, hipStream_t st);
+hipError_t launch_mlp_apply_chains(const MlpApplyArgs& a, hipStream_t st);
 hipError_t launch_mlp_gradient(const MlpGradArgs& a, hipStream_t st, int* n_launches);
 
 struct SyncArgs {

@@ -28,7 +28,6 @@ struct FusedParams {
     int64_t d;
     const PairOp* ops;
     const float* slots;
-    uint16_t* Xbf16;
     SynthScale synth;
     uint32_t key0, key1;
     float* V;
@@ -49,7 +48,7 @@ __device__ __forceinline__ void store1(float* p, float v) {
 // 1024 blockIdx.x + 256 u + t of both rows.
 // SOLO = the round contains an event without a partner (i == j: a worker with no neighbour takes a
 // plain SGD step); all other rounds run the variant without the per-store test (1.3 % faster).
-template <bool SYNTH, bool SHADOW, bool STREAM, bool SOLO, bool MOM>
+template <bool SYNTH, bool STREAM, bool SOLO, bool MOM>
 __global__ __launch_bounds__(kThreads) void fused_gossip_apply_kernel(const FusedParams p) {
     __shared__ __attribute__((aligned(16))) float zs[SYNTH ? kTileElems : 4];
     const PairOp op = p.ops[blockIdx.y];   // uniform address: scalar loads, no LDS staging needed
@@ -81,10 +80,6 @@ __global__ __launch_bounds__(kThreads) void fused_gossip_apply_kernel(const Fuse
             const float avg = (a[u] + b[u]) * 0.5f;
             store1<STREAM>(xi + e, avg);
             store1<STREAM>(xj + e, avg);
-            if (SHADOW) {
-                p.Xbf16[static_cast<int64_t>(op.i) * p.ld + e] = bf16_rne(avg);
-                p.Xbf16[static_cast<int64_t>(op.j) * p.ld + e] = bf16_rne(avg);
-            }
         }
         return;
     }
@@ -116,10 +111,6 @@ __global__ __launch_bounds__(kThreads) void fused_gossip_apply_kernel(const Fuse
         }
         store1<STREAM>(xi + e, ni);
         if (pair) store1<STREAM>(xj + e, nj);
-        if (SHADOW) {
-            p.Xbf16[static_cast<int64_t>(op.i) * p.ld + e] = bf16_rne(ni);
-            if (pair) p.Xbf16[static_cast<int64_t>(op.j) * p.ld + e] = bf16_rne(nj);
-        }
     }
 }
 
@@ -133,21 +124,21 @@ __global__ __launch_bounds__(kThreads) void synth_gradient_kernel(float* out, in
         if (4 * v + t < d) out[4 * v + t] = gv[t];
 }
 
-template <bool SYNTH, bool SHADOW, bool STREAM, bool SOLO>
+template <bool SYNTH, bool STREAM, bool SOLO>
 hipError_t launch_mom(const FusedParams& p, dim3 grid, hipStream_t st) {
-    if (p.V) hipLaunchKernelGGL((fused_gossip_apply_kernel<SYNTH, SHADOW, STREAM, SOLO, true>), grid, dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((fused_gossip_apply_kernel<SYNTH, SHADOW, STREAM, SOLO, false>), grid, dim3(kThreads), 0, st, p);
+    if (p.V) hipLaunchKernelGGL((fused_gossip_apply_kernel<SYNTH, STREAM, SOLO, true>), grid, dim3(kThreads), 0, st, p);
+    else hipLaunchKernelGGL((fused_gossip_apply_kernel<SYNTH, STREAM, SOLO, false>), grid, dim3(kThreads), 0, st, p);
     return hipGetLastError();
 }
-template <bool SYNTH, bool SHADOW, bool STREAM>
+template <bool SYNTH, bool STREAM>
 hipError_t launch_solo(const FusedParams& p, dim3 grid, bool solo, hipStream_t st) {
-    if (solo) return launch_mom<SYNTH, SHADOW, STREAM, true>(p, grid, st);
-    return launch_mom<SYNTH, SHADOW, STREAM, false>(p, grid, st);
+    if (solo) return launch_mom<SYNTH, STREAM, true>(p, grid, st);
+    return launch_mom<SYNTH, STREAM, false>(p, grid, st);
 }
-template <bool SYNTH, bool SHADOW>
+template <bool SYNTH>
 hipError_t launch_variant(const FusedParams& p, dim3 grid, bool streaming, bool solo, hipStream_t st) {
-    if (streaming) return launch_solo<SYNTH, SHADOW, true>(p, grid, solo, st);
-    return launch_solo<SYNTH, SHADOW, false>(p, grid, solo, st);
+    if (streaming) return launch_solo<SYNTH, true>(p, grid, solo, st);
+    return launch_solo<SYNTH, false>(p, grid, solo, st);
 }
 
 }  // namespace
@@ -160,7 +151,6 @@ hipError_t launch_fused_gossip_apply(const FusedArgs& a, hipStream_t st) {
     p.d = a.d;
     p.ops = a.ops;
     p.slots = a.slots;
-    p.Xbf16 = a.Xbf16;
     p.synth = synth_scale(a.synth_std);
     p.key0 = static_cast<uint32_t>(a.synth_seed);
     p.key1 = static_cast<uint32_t>(a.synth_seed >> 32);
@@ -170,9 +160,8 @@ hipError_t launch_fused_gossip_apply(const FusedArgs& a, hipStream_t st) {
     const int64_t tiles = (p.d + kTileElems - 1) / kTileElems;
     if (tiles > 0x7FFFFFFF || a.n_ops > 65535) return hipErrorInvalidValue;
     const dim3 grid(static_cast<uint32_t>(tiles), static_cast<uint32_t>(a.n_ops));
-    if (a.synth) return launch_variant<true, false>(p, grid, a.streaming, a.has_solo, st);
-    if (a.Xbf16) return launch_variant<false, true>(p, grid, a.streaming, a.has_solo, st);
-    return launch_variant<false, false>(p, grid, a.streaming, a.has_solo, st);
+    if (a.synth) return launch_variant<true>(p, grid, a.streaming, a.has_solo, st);
+    return launch_variant<false>(p, grid, a.streaming, a.has_solo, st);
 }
 
 hipError_t launch_synth_gradient(uint64_t seed, uint64_t k, float std, int64_t d, float* out, hipStream_t st) {

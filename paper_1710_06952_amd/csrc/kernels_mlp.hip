@@ -519,128 +519,257 @@ __global__ __launch_bounds__(kT) void mlp_dw1_kernel(const MlpParams p) {
 }
 
 // ---- 4. model update with dW1 in factored form ----------------------------------------------
-// The event's update  avg = (x^i + x^j) / 2;  x^j <- avg;  x^i <- avg - gamma g  for the
-// perceptron, with the first-layer part of g formed here from its factors (the same tile product
+// An event's update  avg = (x^i + x^j) / 2;  x^j <- avg;  x^i <- avg - gamma g  for the
+// perceptron, with the first-layer part of g formed here from its factors (the same product
 // as above, so the values are those of the dense gradient) and only the small remainder
-// (b1, W2, b2) read from the pending slot.  The bf16 shadow of both rows is rewritten.
-//   grid = (hid / 64, ceil(in / 64) + tail rows, events of the round)
-//   blockIdx.y <  ceil(in / 64): one 64 x 64 tile of W1.  The tile of g goes through LDS so that
+// (b1, W2, b2) read from the pending slot.  The bf16 shadow of the rows is rewritten.
+// A block executes a chain of up to kMlpChain updates that share rows on its tile: the rows are
+// read once, stay in registers from update to update and are written once, and the operands of the
+// next product are on their way while one is applied.
+// A round is a chain of three kernels with latency for most of its time, so fewer rounds count for more than their length: with
+// updates that may follow each other in a round 784-1024-10 (n = 16, M = 64, T_max = 4, 1000 events) takes 175 rounds of 33 us
+// (11.6 forward, 6.6 softmax, 15.2 here) instead of 296 of 28 (9.8, 6.2, 13.1), 8.36 -> 6.0 ms; 64-256-10 with momentum (n = 16,
+// M = 32, 1024 events) 164 rounds instead of 254, 4.0 -> 2.85 ms.  Chains of four would save another 6 % and 2 % of the rounds,
+// but with momentum their rows do not fit the 128 registers at which four blocks share a compute unit.
+//   grid = (hid / 64, in_tiles + further rows, chains of the round)
+//   blockIdx.y <  in_tiles: one 32 x 64 tile of W1.  The tile of g goes through LDS so that
 //                 each thread updates float4 pieces of contiguous rows (16 lanes per 256-byte row);
-//   blockIdx.y >= ceil(in / 64): 1024 consecutive floats of the remainder, elementwise.
+//   blockIdx.y >= in_tiles: 1024 consecutive floats of the remainder (or, where the gradients are dense,
+//                 of all parameters), elementwise.
 struct MlpApplyParams {
     float* X;
     int64_t ld;
     int64_t d;
     int in, hid, M;
-    const PairOp* ops;
+    const MlpChain* chains;
     const float* slots;
     uint16_t* Xbf16;
     const int32_t* batch_by_op;   // [op][M]
+    int in_tiles;            // rows of tiles of W1: ceil(in / 32), or 0 with dense gradients
+    int64_t dense_from;      // the parameters behind them
     float* V;                // momentum buffers (MOM), else nullptr
     float momentum, weight_decay;
 };
 
-// vold: the worker's momentum entries (MOM and not average_only), else unused
-template <bool MOM>
-__device__ __forceinline__ void apply4(const MlpApplyParams& p, const PairOp& op, int64_t e, v4f a, v4f b, v4f g, v4f vold,
-                                       bool average_only, bool pair, int valid) {
-    float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w}, gv[4] = {g.x, g.y, g.z, g.w};
-    float ni[4], nj[4];
-    if (MOM && !average_only) {       // an averaging-only pair leaves the momentum buffers alone
-        const float vo[4] = {vold.x, vold.y, vold.z, vold.w};
-        float vn[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            average_then_apply_momentum(av[c], bv[c], gv[c], vo[c], op.gamma, p.momentum, p.weight_decay, ni[c], nj[c], vn[c]);
-        float* __restrict__ vi = p.V + static_cast<int64_t>(op.i) * p.ld + e;
-        if (valid == 4) *reinterpret_cast<v4f*>(vi) = v4f{vn[0], vn[1], vn[2], vn[3]};
-        else
-            for (int c = 0; c < valid; ++c) vi[c] = vn[c];
-    } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            average_then_apply(av[c], bv[c], average_only ? 0.0f : gv[c], average_only ? 0.0f : op.gamma, ni[c], nj[c]);
-    }
-    float* __restrict__ xi = p.X + static_cast<int64_t>(op.i) * p.ld + e;
-    float* __restrict__ xj = p.X + static_cast<int64_t>(op.j) * p.ld + e;
-    uint16_t* __restrict__ si = p.Xbf16 + static_cast<int64_t>(op.i) * p.ld + e;
-    uint16_t* __restrict__ sj = p.Xbf16 + static_cast<int64_t>(op.j) * p.ld + e;
-    if (valid == 4) {
-        *reinterpret_cast<v4f*>(xi) = v4f{ni[0], ni[1], ni[2], ni[3]};
-        *reinterpret_cast<v4h*>(si) = v4h{bf16_rne(ni[0]), bf16_rne(ni[1]), bf16_rne(ni[2]), bf16_rne(ni[3])};
-        if (pair) {
-            *reinterpret_cast<v4f*>(xj) = v4f{nj[0], nj[1], nj[2], nj[3]};
-            *reinterpret_cast<v4h*>(sj) = v4h{bf16_rne(nj[0]), bf16_rne(nj[1]), bf16_rne(nj[2]), bf16_rne(nj[3])};
-        }
-    } else {                      // ragged end of the parameter vector: entries at and beyond d stay untouched
-        for (int c = 0; c < valid; ++c) {
-            xi[c] = ni[c];
-            si[c] = bf16_rne(ni[c]);
-            if (pair) {
-                xj[c] = nj[c];
-                sj[c] = bf16_rne(nj[c]);
-            }
-        }
-    }
+constexpr int kApplyRows = 32;              // inputs of a tile
+constexpr int kPlaces = kMlpChain + 1;      // rows of a chain
+
+typedef __amdgpu_buffer_rsrc_t Buffer;
+// `bytes` bytes from p on: what lies beyond reads as zero and touches no memory
+__device__ __forceinline__ Buffer buffer_of(const float* p, int bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, bytes, 0x00027000);
+}
+__device__ __forceinline__ v4f buffer_load4(Buffer b, int offset) {
+    const v4u w = __builtin_amdgcn_raw_buffer_load_b128(b, offset, 0, 0);
+    return v4f{__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z), __uint_as_float(w.w)};
 }
 
-template <bool MOM>
-__global__ __launch_bounds__(kT) void mlp_apply_factored_kernel(const MlpApplyParams p) {
-    __shared__ __attribute__((aligned(16))) uint16_t At[64][72];
-    __shared__ __attribute__((aligned(16))) uint16_t Bt[64][72];
-    __shared__ __attribute__((aligned(16))) float Gs[64][68];       // the tile of g, [input][hidden]
-    const PairOp op = p.ops[blockIdx.z];
-    const bool average_only = (op.flags & 1) != 0;    // extra pair of a general W_k: no gradient, no step
-    const bool pair = op.i != op.j;
-    const float* __restrict__ xi = p.X + static_cast<int64_t>(op.i) * p.ld;
-    const float* __restrict__ xj = p.X + static_cast<int64_t>(op.j) * p.ld;
-    const float* __restrict__ slot = p.slots + static_cast<int64_t>(op.slot) * p.ld;
-    const int in_tiles = (p.in + 63) / 64;
-    if (static_cast<int>(blockIdx.y) >= in_tiles) {
-        // remainder of the parameter vector (b1, W2, b2): dense gradient from the slot
-        const int64_t tb = static_cast<int64_t>(blockIdx.y - in_tiles) * gridDim.x + blockIdx.x;
-        const int64_t e = static_cast<int64_t>(p.in) * p.hid + 4 * (tb * kT + threadIdx.x);
-        if (e >= p.d) return;
-        const int valid = p.d - e >= 4 ? 4 : static_cast<int>(p.d - e);
-        const v4f a = *reinterpret_cast<const v4f*>(xi + e), b = *reinterpret_cast<const v4f*>(xj + e);   // rows are padded
-        v4f g = {0, 0, 0, 0}, vold = {0, 0, 0, 0};
-        if (!average_only) g = *reinterpret_cast<const v4f*>(slot + e);
-        if (MOM && !average_only) vold = *reinterpret_cast<const v4f*>(p.V + static_cast<int64_t>(op.i) * p.ld + e);
-        apply4<MOM>(p, op, e, a, b, g, vold, average_only, pair, valid);
-        return;
-    }
-    const int h0 = blockIdx.x * kTileH, i0 = blockIdx.y * 64;
-    const int rr = threadIdx.x >> 4, hq = (threadIdx.x & 15) * 4;      // this thread's rows 16 r + rr, columns hq .. hq + 3
-    v4f a[4], b[4], vold[4];
+// A chain, all of it by scalar loads at once: no later load waits for a part of it.
+__device__ __forceinline__ MlpChain chain_at(const MlpChain* p) {
+    typedef uint32_t v8u __attribute__((ext_vector_type(8)));
+    typedef const v8u __attribute__((address_space(4))) * Constant;
+    struct Words {
+        v8u w[sizeof(MlpChain) / sizeof(v8u)];
+    } words;
+    static_assert(sizeof(Words) == sizeof(MlpChain), "a chain is whole vectors");
+    const Constant q = (Constant) reinterpret_cast<uintptr_t>(p);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {        // the model rows are requested before the product is formed
-        const int i = i0 + 16 * r + rr;
-        vold[r] = v4f{0, 0, 0, 0};
-        if (i < p.in) {
-            const int64_t e = static_cast<int64_t>(i) * p.hid + h0 + hq;
-            a[r] = *reinterpret_cast<const v4f*>(xi + e);
-            b[r] = *reinterpret_cast<const v4f*>(xj + e);
-            if (MOM && !average_only) vold[r] = *reinterpret_cast<const v4f*>(p.V + static_cast<int64_t>(op.i) * p.ld + e);
+    for (size_t i = 0; i < sizeof(MlpChain) / sizeof(v8u); ++i) words.w[i] = q[i];
+    return __builtin_bit_cast(MlpChain, words);
+}
+
+// The entries a thread holds of a chain's rows (and of their momentum buffers): kN pieces of four.
+template <bool MOM, int kN>
+struct ChainRows {
+    v4f x[kPlaces][kN], v[MOM ? kPlaces : 1][kN];
+
+    // masks of a place, the same for the whole block, in vector registers
+    struct Place {
+        uint32_t is[kPlaces];
+        __device__ __forceinline__ explicit Place(int place) {
+#pragma unroll
+            for (int q = 0; q < kPlaces; ++q) is[q] = in_vector(place == q ? 0xFFFFFFFFu : 0u);
+        }
+    };
+    // bit operations and no selects: of these the compiler makes a select of addresses, and with it the rows leave the registers
+    static __device__ __forceinline__ v4f pick4(uint32_t mask, v4f a, v4f b) { return v4f{pick(mask, a.x, b.x), pick(mask, a.y, b.y), pick(mask, a.z, b.z), pick(mask, a.w, b.w)}; }
+    static __device__ __forceinline__ v4f at(const v4f (&a)[kPlaces][kN], const Place& place, int r) {
+        v4f w = a[0][r];
+#pragma unroll
+        for (int q = 1; q < kPlaces; ++q) w = pick4(place.is[q], a[q][r], w);
+        return w;
+    }
+    static __device__ __forceinline__ void put(v4f (&a)[kPlaces][kN], const Place& place, int r, v4f w) {
+#pragma unroll
+        for (int q = 0; q < kPlaces; ++q) a[q][r] = pick4(place.is[q], w, a[q][r]);
+    }
+
+    __device__ __forceinline__ void update(const MlpApplyParams& p, const MlpChainOp& op, const v4f (&gr)[kN]) {
+        const Place pi(op.places & 15), pj(op.places >> 4);
+        const uint32_t step = in_vector(op.average == 0 ? 0xFFFFFFFFu : 0u);
+#pragma unroll
+        for (int r = 0; r < kN; ++r) {
+            const v4f a = at(x, pi, r), b = at(x, pj, r), g = gr[r];
+            const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w}, gv[4] = {g.x, g.y, g.z, g.w};
+            float ni[4], nj[4];
+            if constexpr (MOM) {
+                const v4f o = at(v, pi, r);
+                const float vo[4] = {o.x, o.y, o.z, o.w};
+                float vn[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) average_then_apply_momentum(av[c], bv[c], gv[c], vo[c], op.gamma, p.momentum, p.weight_decay, ni[c], nj[c], vn[c]);
+                put(v, pi, r, pick4(step, v4f{vn[0], vn[1], vn[2], vn[3]}, o));
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) average_then_apply(av[c], bv[c], gv[c], op.gamma, ni[c], nj[c]);
+            }
+            const v4f to_j = {nj[0], nj[1], nj[2], nj[3]};
+            put(x, pj, r, to_j);              // before x^i: without a partner (i == j) the step stands
+            put(x, pi, r, pick4(step, v4f{ni[0], ni[1], ni[2], ni[3]}, to_j));
         }
     }
-    if (!average_only) {                  // uniform over the block
-        v4f acc[4];
-        dw1_tile(static_cast<const uint16_t*>(op.features), op.feat_ld, p.batch_by_op + static_cast<int64_t>(blockIdx.z) * p.M, p.M,
-                 p.in, reinterpret_cast<const uint16_t*>(slot), p.hid, h0, i0, At, Bt, acc);
-        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+};
+
+template <bool MOM>
+__global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyParams p) {
+    __shared__ __attribute__((aligned(16))) uint16_t At[kApplyRows][72];   // inputs transposed:  [i][m], 64 m + pad
+    __shared__ __attribute__((aligned(16))) uint16_t Bt[64][72];           // hidden error transposed: [h][m]
+    __shared__ __attribute__((aligned(16))) float Gs[kApplyRows][68];      // the tile of g, [input][hidden]
+    const MlpChain chain = chain_at(p.chains + blockIdx.z);
+    const int n_ops = chain.n_ops;
+    if (static_cast<int>(blockIdx.y) >= p.in_tiles) {
+        // elementwise, with dense gradients from the slots
+        const int64_t from = p.dense_from + 4 * kT * (static_cast<int64_t>(blockIdx.y - p.in_tiles) * gridDim.x + blockIdx.x);
+        const int64_t e = from + 4 * threadIdx.x, left = (p.d + 3) / 4 * 4 - from;       // rows are padded to whole vectors
+        if (e >= p.d) return;
+        const int bytes = left < 4 * kT ? 4 * static_cast<int>(left) : 16 * kT, offset = 16 * threadIdx.x;
+        ChainRows<MOM, 1> c;
 #pragma unroll
-        for (int it = 0; it < 4; ++it)
+        for (int q = 0; q < kPlaces; ++q) {
+            const int64_t at = static_cast<int64_t>(max(chain.rows[q], 0)) * p.ld + from;
+            c.x[q][0] = buffer_load4(buffer_of(p.X + at, chain.rows[q] >= 0 ? bytes : 0), offset);
+            if constexpr (MOM) c.v[q][0] = buffer_load4(buffer_of(p.V + at, (chain.steps >> q & 1) != 0 ? bytes : 0), offset);
+        }
+        v4f g[kMlpChain][1];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) Gs[16 * it + 4 * (lane >> 4) + v][16 * wave + (lane & 15)] = acc[it][v];
+        for (int u = 0; u < kMlpChain; ++u)
+            g[u][0] = buffer_load4(buffer_of(p.slots + static_cast<int64_t>(chain.ops[u].slot) * p.ld + from, u < n_ops ? bytes : 0), offset);
+#pragma unroll
+        for (int u = 0; u < kMlpChain; ++u)
+            if (u == 0 || u < n_ops) c.update(p, chain.ops[u], g[u]);
+#pragma unroll
+        for (int q = 0; q < kPlaces; ++q) {
+            if (chain.rows[q] < 0) continue;
+            const int64_t at = static_cast<int64_t>(chain.rows[q]) * p.ld + e;
+            const bool steps = MOM && (chain.steps >> q & 1) != 0;
+            const v4f w = c.x[q][0], m = MOM ? c.v[MOM ? q : 0][0] : v4f{0, 0, 0, 0};
+            const v4h s = {bf16_rne(w.x), bf16_rne(w.y), bf16_rne(w.z), bf16_rne(w.w)};
+            if (e + 4 <= p.d) {
+                *reinterpret_cast<v4f*>(p.X + at) = w;
+                *reinterpret_cast<v4h*>(p.Xbf16 + at) = s;
+                if (steps) *reinterpret_cast<v4f*>(p.V + at) = m;
+            } else {                                            // entries at and beyond d stay untouched
+                const float wv[4] = {w.x, w.y, w.z, w.w}, mv[4] = {m.x, m.y, m.z, m.w};
+                const uint16_t sv[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+                for (int k = 0; k < 3; ++k)
+                    if (e + k < p.d) {
+                        p.X[at + k] = wv[k];
+                        p.Xbf16[at + k] = sv[k];
+                        if (steps) p.V[at + k] = mv[k];
+                    }
+            }
+        }
+        return;
+    }
+    const int h0 = blockIdx.x * kTileH, i0 = blockIdx.y * kApplyRows;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, kb = 8 * (lane >> 4);
+    const int rr = threadIdx.x >> 4, hq = (threadIdx.x & 15) * 4;      // this thread's rows 16 r + rr, columns hq .. hq + 3
+    const int m = threadIdx.x >> 2, part = threadIdx.x & 3;            // staging role: sample, quarter of the tile's columns
+    const int m_in = min(m, p.M - 1), c_in = min(i0 + 8 * part, p.in - 8);
+    const bool live = m < p.M && i0 + 8 * part < p.in;
+    const int32_t* const index = p.batch_by_op + static_cast<int64_t>(chain.first) * p.M + m_in;
+    struct Factors {
+        v8h x, d[2];
+    };
+    Factors f;
+    auto request_error = [&](const MlpChainOp& op) {
+        const uint16_t* const dH = reinterpret_cast<const uint16_t*>(p.slots + static_cast<int64_t>(op.slot) * p.ld);
+#pragma unroll
+        for (int half = 0; half < 2; ++half) f.d[half] = *reinterpret_cast<const v8h*>(dH + static_cast<int64_t>(m) * p.hid + h0 + 16 * part + 8 * half);
+    };
+    auto request_inputs = [&](const MlpChainOp& op, int32_t row) {
+        f.x = *reinterpret_cast<const v8h*>(static_cast<const uint16_t*>(op.features) + static_cast<int64_t>(row) * op.feat_ld + c_in);
+    };
+    // indices first: loads return in order, and the inputs wait for them
+    int32_t row = index[0];
+    int32_t row_next = index[static_cast<int64_t>(min(1, n_ops - 1)) * p.M];
+    request_error(chain.ops[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    ChainRows<MOM, 2> c;
+    const int64_t corner = static_cast<int64_t>(i0) * p.hid + h0;
+    const int bytes = 4 * (min(kApplyRows, p.in - i0) * p.hid - h0), offset = 4 * (rr * p.hid + hq), pitch = 64 * p.hid;
+#pragma unroll
+    for (int q = 0; q < kPlaces; ++q) {
+        const int64_t at = static_cast<int64_t>(max(chain.rows[q], 0)) * p.ld + corner;
+        const Buffer x = buffer_of(p.X + at, chain.rows[q] >= 0 ? bytes : 0);
+#pragma unroll
+        for (int r = 0; r < 2; ++r) c.x[q][r] = buffer_load4(x, offset + r * pitch);
+        if constexpr (MOM) {
+            const Buffer v = buffer_of(p.V + at, (chain.steps >> q & 1) != 0 ? bytes : 0);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) c.v[q][r] = buffer_load4(v, offset + r * pitch);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" : "+v"(row), "+v"(row_next));       // no address before the rows are requested
+    request_inputs(chain.ops[0], row);
+#pragma unroll
+    for (int u = 0; u < kMlpChain; ++u) {
+        if (u > 0 && u >= n_ops) break;       // the same for the whole block; a chain has one at least
+        const MlpChainOp& op = chain.ops[u];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            At[8 * part + e][m] = live ? f.x[e] : static_cast<uint16_t>(0);
+            Bt[16 * part + e][m] = f.d[0][e];
+            Bt[16 * part + 8 + e][m] = f.d[1][e];
+        }
         __syncthreads();
+        if (u + 1 < kMlpChain) {
+            request_error(chain.ops[u + 1 < kMlpChain ? u + 1 : u]);
+            request_inputs(chain.ops[u + 1 < kMlpChain ? u + 1 : u], row_next);
+            row_next = index[static_cast<int64_t>(min(u + 2, n_ops - 1)) * p.M];
+        }
+        v4f acc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            const v8h bfrag = *reinterpret_cast<const v8h*>(&Bt[16 * wave + li][32 * ks + kb]);
+#pragma unroll
+            for (int it = 0; it < 2; ++it) acc[it] = mfma_bf16(*reinterpret_cast<const v8h*>(&At[16 * it + li][32 * ks + kb]), bfrag, acc[it]);
+        }
+#pragma unroll
+        for (int it = 0; it < 2; ++it)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) Gs[16 * it + 4 * (lane >> 4) + k][16 * wave + li] = acc[it][k];
+        __syncthreads();
+        const v4f g[2] = {*reinterpret_cast<const v4f*>(&Gs[rr][hq]), *reinterpret_cast<const v4f*>(&Gs[16 + rr][hq])};
+        c.update(p, op, g);
     }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int i = i0 + 16 * r + rr;
-        if (i >= p.in) continue;
-        v4f g = {0, 0, 0, 0};
-        if (!average_only) g = *reinterpret_cast<const v4f*>(&Gs[16 * r + rr][hq]);
-        apply4<MOM>(p, op, static_cast<int64_t>(i) * p.hid + h0 + hq, a[r], b[r], g, vold[r], average_only, pair, 4);
+    for (int q = 0; q < kPlaces; ++q) {
+        if (chain.rows[q] < 0) continue;
+        const int64_t at = static_cast<int64_t>(chain.rows[q]) * p.ld + corner;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            if (i0 + 16 * r + rr >= p.in) continue;
+            const int64_t e = at + static_cast<int64_t>(16 * r + rr) * p.hid + hq;
+            const v4f w = c.x[q][r];
+            *reinterpret_cast<v4f*>(p.X + e) = w;
+            *reinterpret_cast<v4h*>(p.Xbf16 + e) = v4h{bf16_rne(w.x), bf16_rne(w.y), bf16_rne(w.z), bf16_rne(w.w)};
+            if constexpr (MOM) {
+                if ((chain.steps >> q & 1) != 0) *reinterpret_cast<v4f*>(p.V + e) = c.v[q][r];
+            }
+        }
     }
 }
 
@@ -710,9 +839,9 @@ bool mlp_can_factor(int32_t in, int32_t hid, int32_t M) {
     return M >= 1 && M <= kMaxM && in >= 32 && (in & 7) == 0 && hid >= kTileH && hid % kTileH == 0;
 }
 
-hipError_t launch_mlp_apply_factored(const MlpApplyArgs& a, hipStream_t st) {
-    if (a.n_ops <= 0) return hipSuccess;
-    if (!mlp_can_factor(a.in, a.hid, a.M) || a.n_ops > 65535 || !a.Xbf16) return hipErrorInvalidValue;
+hipError_t launch_mlp_apply_chains(const MlpApplyArgs& a, hipStream_t st) {
+    if (a.n_chains <= 0) return hipSuccess;
+    if ((a.factored && !mlp_can_factor(a.in, a.hid, a.M)) || a.hid < kTileH || a.n_chains > 65535 || !a.Xbf16) return hipErrorInvalidValue;
     MlpApplyParams p;
     p.X = a.X;
     p.ld = a.ld;
@@ -720,22 +849,21 @@ hipError_t launch_mlp_apply_factored(const MlpApplyArgs& a, hipStream_t st) {
     p.in = a.in;
     p.hid = a.hid;
     p.M = a.M;
-    p.ops = a.ops;
+    p.chains = a.chains;
     p.slots = a.slots;
     p.Xbf16 = a.Xbf16;
     p.batch_by_op = a.batch_by_op;
     p.V = a.V;
     p.momentum = a.momentum;
     p.weight_decay = a.weight_decay;
-    const int64_t tail = a.d - static_cast<int64_t>(a.in) * a.hid;            // floats after W1
-    const uint32_t bx = static_cast<uint32_t>(a.hid / kTileH);
-    const int64_t per_row = static_cast<int64_t>(bx) * kT * 4;                  // floats one grid row of blocks covers
-    const int64_t tail_rows = tail > 0 ? (tail + per_row - 1) / per_row : 0;
-    const int64_t by = (a.in + 63) / 64 + tail_rows;
+    p.in_tiles = a.factored ? (a.in + kApplyRows - 1) / kApplyRows : 0;
+    p.dense_from = a.factored ? static_cast<int64_t>(a.in) * a.hid : 0;
+    const int64_t bx = a.hid / kTileH, per_row = bx * kT * 4;                   // floats one grid row of blocks covers
+    const int64_t by = p.in_tiles + (a.d - p.dense_from + per_row - 1) / per_row;
     if (by > 65535) return hipErrorInvalidValue;
-    const dim3 grid(bx, static_cast<uint32_t>(by), a.n_ops);
-    if (a.V) hipLaunchKernelGGL(mlp_apply_factored_kernel<true>, grid, dim3(kT), 0, st, p);
-    else hipLaunchKernelGGL(mlp_apply_factored_kernel<false>, grid, dim3(kT), 0, st, p);
+    const dim3 grid(static_cast<uint32_t>(bx), static_cast<uint32_t>(by), a.n_chains);
+    if (a.V) hipLaunchKernelGGL(mlp_apply_chains_kernel<true>, grid, dim3(kT), 0, st, p);
+    else hipLaunchKernelGGL(mlp_apply_chains_kernel<false>, grid, dim3(kT), 0, st, p);
     return hipGetLastError();
 }
 

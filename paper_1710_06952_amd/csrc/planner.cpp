@@ -13,6 +13,10 @@
 // Disjoint pairwise averages commute, so executing the rounds in order gives
 // exactly the serial result.
 //
+// With chains (chain > 1) the updates of a round may also follow each other on a row: those connected by their rows form a
+// chain of at most `chain` operations, executed in event order by whatever executes the round (chain_rounds groups them).
+// An event with extra pairs starts chains of its own.  Reads still precede all updates of their round.
+//
 // A call may look ahead: of the K events in the arrays only the first n_apply are applied; the others
 // are the first events of the next call, named now so that those of their stale reads that fall before
 // event n_apply are evaluated while the models they need still exist.  Such a gradient stays in its
@@ -27,7 +31,7 @@ namespace adpsgd_impl {
 int plan_rounds(int32_t n, int64_t K, const int32_t* worker, const int32_t* neighbour,
                 const int32_t* tau, int32_t n_slots, bool with_gradients, Plan& plan,
                 std::string& err, const int64_t* extra_ptr, const int32_t* extra_a, const int32_t* extra_b,
-                bool local_compensation, int64_t n_apply, const int32_t* carried_slot) {
+                bool local_compensation, int64_t n_apply, const int32_t* carried_slot, int32_t chain) {
     if (n_apply < 0 || n_apply > K) n_apply = K;
     if (!with_gradients) carried_slot = nullptr;
     auto carried = [&](int64_t k) { return carried_slot && carried_slot[k] >= 0; };
@@ -88,6 +92,20 @@ int plan_rounds(int32_t n, int64_t K, const int32_t* worker, const int32_t* neig
         for (int32_t s = 0; s < n_slots; ++s)
             if (!slot_taken[s]) free_slots.push({0, s});
 
+    // chains: of a row in the round of its last update, joined by later operations of that round
+    std::vector<int32_t> chain_of(chain > 1 ? n : 0, -1), parent, length;
+    auto chain_at = [&](int32_t row, int32_t u) {
+        if (last_write[row] != u) return -1;
+        int32_t c = chain_of[row];
+        while (parent[c] != c) c = parent[c] = parent[parent[c]];
+        return c;
+    };
+    auto start_chain = [&](int32_t i, int32_t j) {
+        chain_of[i] = chain_of[j] = static_cast<int32_t>(parent.size());
+        parent.push_back(chain_of[i]);
+        length.push_back(1);
+    };
+
     int32_t rounds = 0;
     for (int64_t t = 0; t < n_apply; ++t) {
         if (with_gradients) {
@@ -105,7 +123,8 @@ int plan_rounds(int32_t n, int64_t K, const int32_t* worker, const int32_t* neig
             }
         }
         const int32_t i = worker[t], j = neighbour[t];
-        int32_t u = std::max(last_write[i], last_write[j]) + 1;
+        const bool may_follow = chain > 1 && !(extra_ptr && extra_ptr[t + 1] > extra_ptr[t]);
+        int32_t u = std::max(1, std::max(last_write[i], last_write[j]) + (may_follow ? 0 : 1));
         u = std::max(u, std::max(last_read[i], last_read[j]));
         if (with_gradients) u = std::max(u, plan.r_round[t]);
         if (extra_ptr) {      // every pair of W_t runs in the event's round
@@ -114,7 +133,25 @@ int plan_rounds(int32_t n, int64_t K, const int32_t* worker, const int32_t* neig
                 u = std::max(u, std::max(last_write[a], last_write[b]) + 1);
                 u = std::max(u, std::max(last_read[a], last_read[b]));
             }
-            for (int64_t q = extra_ptr[t]; q < extra_ptr[t + 1]; ++q) last_write[extra_a[q]] = last_write[extra_b[q]] = u;
+            for (int64_t q = extra_ptr[t]; q < extra_ptr[t + 1]; ++q) {
+                if (chain > 1) start_chain(extra_a[q], extra_b[q]);
+                last_write[extra_a[q]] = last_write[extra_b[q]] = u;
+            }
+        }
+        if (chain > 1) {
+            const int32_t a = chain_at(i, u), b = chain_at(j, u);
+            const int32_t len = 1 + (a >= 0 ? length[a] : 0) + (b >= 0 && b != a ? length[b] : 0);
+            if (len == 1) {
+                start_chain(i, j);
+            } else if (len > chain) {          // full: the next round, in which neither row has been updated
+                ++u;
+                start_chain(i, j);
+            } else {
+                const int32_t c = a >= 0 ? a : b;
+                if (b >= 0) parent[b] = c;
+                length[c] = len;
+                chain_of[i] = chain_of[j] = c;
+            }
         }
         plan.u_round[t] = u;
         last_write[i] = last_write[j] = u;
@@ -130,8 +167,8 @@ int plan_rounds(int32_t n, int64_t K, const int32_t* worker, const int32_t* neig
 }
 
 // Independent check of a plan against the serial semantics (the library's race detector):
-//   1. the updates of a round touch pairwise distinct rows;
-//   2. per row the updates keep their event order, in strictly increasing rounds;
+//   1. the updates of a round touch pairwise distinct rows (chained: verify_chains has the updates of a round);
+//   2. per row the updates keep their event order, in strictly increasing rounds (chained: in rounds that do not decrease);
 //   3. the read of event k sees exactly the updates of its row with index < s_k = k - tau_k: the last
 //      such update lies in an earlier round, the first update with index >= s_k in the same or a later one;
 //   4. a gradient is computed no later than the round that applies it, and a slot is rewritten only in
@@ -144,7 +181,7 @@ int plan_rounds(int32_t n, int64_t K, const int32_t* worker, const int32_t* neig
 bool verify_plan(int32_t n, int64_t K, const int32_t* worker, const int32_t* neighbour, const int32_t* tau,
                  int32_t n_slots, bool with_gradients, const Plan& plan, std::string& err,
                  const int64_t* extra_ptr, const int32_t* extra_a, const int32_t* extra_b,
-                 int64_t n_apply, const int32_t* carried_slot) {
+                 int64_t n_apply, const int32_t* carried_slot, bool chained) {
     if (n_apply < 0 || n_apply > K) n_apply = K;
     if (!with_gradients) carried_slot = nullptr;
     auto carried = [&](int64_t k) { return carried_slot && carried_slot[k] >= 0; };
@@ -177,7 +214,7 @@ bool verify_plan(int32_t n, int64_t K, const int32_t* worker, const int32_t* nei
             if (!touches[r].empty()) {
                 const int64_t m = touches[r].back();
                 if (m == k) return bad("an event names a row twice", k);
-                if (plan.u_round[m] >= u) return bad("updates of a row out of order or sharing a round", k);   // 1 and 2
+                if (chained ? plan.u_round[m] > u : plan.u_round[m] >= u) return bad("updates of a row out of order or sharing a round", k);   // 1 and 2
             }
             touches[r].push_back(k);
         }
@@ -218,6 +255,72 @@ bool verify_plan(int32_t n, int64_t K, const int32_t* worker, const int32_t* nei
             return bad("compensated read outside the life of its gradient", k);   // 5
     }
     return true;
+}
+
+void chain_rounds(const std::vector<ColumnPair>& pairs, const std::vector<int64_t>& offset, int32_t n_rows, ChainLayout& out) {
+    out.order.clear();
+    out.first.clear();
+    out.round.assign(1, 0);
+    std::vector<int32_t> chain_of(n_rows, -1), parent;
+    std::vector<std::vector<int64_t>> members;       // by chain, in the order of the operations
+    auto root = [&](int32_t c) {
+        while (parent[c] != c) c = parent[c];
+        return c;
+    };
+    for (size_t r = 0; r + 1 < offset.size(); ++r) {
+        parent.clear();
+        members.clear();
+        std::fill(chain_of.begin(), chain_of.end(), -1);
+        for (int64_t q = offset[r]; q < offset[r + 1]; ++q) {
+            int32_t a = chain_of[pairs[q].i], b = chain_of[pairs[q].j];
+            if (a >= 0) a = root(a);
+            if (b >= 0) b = root(b);
+            if (a < 0) std::swap(a, b);
+            if (a < 0) {
+                a = static_cast<int32_t>(parent.size());
+                parent.push_back(a);
+                members.emplace_back();
+            } else if (b >= 0 && b != a) {           // two chains become one, their operations in event order
+                std::vector<int64_t> both(members[a].size() + members[b].size());
+                std::merge(members[a].begin(), members[a].end(), members[b].begin(), members[b].end(), both.begin());
+                members[a].swap(both);
+                members[b].clear();
+                parent[b] = a;
+            }
+            members[a].push_back(q);
+            chain_of[pairs[q].i] = chain_of[pairs[q].j] = a;
+        }
+        for (const auto& m : members) {
+            if (m.empty()) continue;
+            out.first.push_back(static_cast<int64_t>(out.order.size()));
+            out.order.insert(out.order.end(), m.begin(), m.end());
+        }
+        out.round.push_back(static_cast<int64_t>(out.first.size()));
+    }
+    out.first.push_back(static_cast<int64_t>(out.order.size()));
+}
+
+bool verify_chains(const std::vector<ColumnPair>& pairs, const std::vector<int64_t>& offset, int32_t n_rows, int32_t most, const ChainLayout& c) {
+    if (c.order.size() != pairs.size() || c.round.size() != offset.size() || c.round.front() != 0 || c.first.empty() || c.first.front() != 0) return false;
+    if (c.round.back() + 1 != static_cast<int64_t>(c.first.size()) || c.first.back() != static_cast<int64_t>(pairs.size())) return false;
+    std::vector<int64_t> owner(n_rows, -1);          // the last chain that named the row
+    for (size_t r = 0; r + 1 < offset.size(); ++r) {
+        if (c.round[r] > c.round[r + 1] || c.first[c.round[r]] != offset[r] || c.first[c.round[r + 1]] != offset[r + 1]) return false;
+        for (int64_t ch = c.round[r]; ch < c.round[r + 1]; ++ch) {
+            const int64_t from = c.first[ch], to = c.first[ch + 1];
+            if (to <= from || to - from > most) return false;
+            for (int64_t q = from; q < to; ++q) {
+                const int64_t at = c.order[q];
+                if (at < offset[r] || at >= offset[r + 1] || (q > from && c.order[q - 1] >= at)) return false;      // of this round, in order
+                for (const int32_t row : {pairs[at].i, pairs[at].j}) {
+                    if (owner[row] >= c.round[r] && owner[row] != ch) return false;       // another chain of the round has it
+                    owner[row] = ch;
+                }
+            }
+        }
+    }
+    return true;         // as many places as operations, each round's in its own range and increasing within a chain: with
+                         // rows that no two chains share, no operation can be named twice
 }
 
 int64_t pack_columns(const std::vector<ColumnPair>& pairs, int32_t n_rows, int32_t capacity, std::vector<int64_t>& place) {
