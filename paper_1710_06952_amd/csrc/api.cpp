@@ -972,7 +972,7 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     const int32_t teams = strip_teams(M);
     StripProgram prog;
     try {
-        if (!build_strips(sc, teams, prog)) return ADPSGD_OK;
+        if (!build_strips(sc, 2 * teams, prog, strip_holders(M))) return ADPSGD_OK;
     } catch (const std::bad_alloc&) {
         return ADPSGD_OK;
     }
@@ -1018,6 +1018,7 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     a.model = h->o.model;
     a.M = M;
     a.teams = teams;
+    a.holders = prog.holders;
     a.recs = reinterpret_cast<const StripEntry*>(dev);
     a.rec_len = prog.rec_len;
     a.iterations = static_cast<int32_t>(prog.iterations);

@@ -33,7 +33,6 @@ namespace {
 
 constexpr int kMainThreads = 64 * kStripMainWaves;
 constexpr int kStripThreads = kMainThreads + kStripHelpers;
-constexpr int kWordsInFlight = 4;      // per lane of a helper
 
 struct StripParams {
     StripArgs a;
@@ -70,9 +69,9 @@ template <> struct Pitch<false> { typedef int64_t type; };
 // replace them, are read across threads.  A function of its own with its arguments in device memory: inlined, it cost the
 // kernel's rows registers (M = 50: 1.72 -> 2.01 ms).
 template <bool kMom>
-__device__ __attribute__((noinline)) void run_alone(const StripArgs* args, int samples, v4u (*team_rows)[2], float* dots, float* coef_s, float* loss_s) {
+__device__ __attribute__((noinline)) void run_alone(const StripArgs* args, int samples, v4u (*rows_of)[2], float* dots, float* coef_s, float* loss_s) {
     const StripArgs& a = *args;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, M = a.M, half = a.teams / 2;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, M = a.M, half = a.teams;
     float* const slots = a.lds_state ? a.alone_slots : a.slots;
     for (int i = 0; i < a.n_in; ++i)
         for (int64_t c = tid; c < a.d; c += kStripThreads) slots[a.carry[2 * i] * a.ld + c] = a.slots[a.carry[2 * i + 1] * a.ld + c];
@@ -99,6 +98,12 @@ __device__ __attribute__((noinline)) void run_alone(const StripArgs* args, int s
                 *xj = nj;
                 *xi = average_only ? nj : ni;
             }
+        if (tid < a.holders && (head.y >> tid & 1) != 0) {
+            const v4u* e = rec + 1 + 2 * half + 2 * __popc(head.y & ((1u << tid) - 1));
+            rows_of[tid][0] = e[0];
+            rows_of[tid][1] = e[1];
+        }
+        __syncthreads();
         const int evals = __popc(head.z);
         for (int i = 0; i < evals; ++i) {
             const v4u ev = rec[1 + 2 * i], ev2 = rec[2 + 2 * i];
@@ -113,7 +118,7 @@ __device__ __attribute__((noinline)) void run_alone(const StripArgs* args, int s
                 point[c] = x;
             }
             __syncthreads();
-            const v4u f = team_rows[ev.x][0], g = team_rows[ev.x][1];
+            const v4u f = rows_of[ev.x][0], g = rows_of[ev.x][1];
             const float* const features = reinterpret_cast<const float*>(static_cast<uint64_t>(f.w) << 32 | f.z);
             const float* const targets = reinterpret_cast<const float*>(static_cast<uint64_t>(g.y) << 32 | g.x);
             const int32_t* const index = a.idx + static_cast<int64_t>(ev.y - a.seq0) * M;
@@ -144,34 +149,30 @@ __device__ __attribute__((noinline)) void run_alone(const StripArgs* args, int s
             }
             __syncthreads();
         }
-        if (tid < a.teams && (head.y >> tid & 1) != 0) {
-            const v4u* e = rec + 1 + 2 * half + 2 * __popc(head.y & ((1u << tid) - 1));
-            team_rows[tid][0] = e[0];
-            team_rows[tid][1] = e[1];
-        }
-        __syncthreads();
     }
     for (int i = a.n_in; i < a.n_in + a.n_out; ++i)
         for (int64_t c = tid; c < a.d; c += kStripThreads) a.slots[a.carry[2 * i + 1] * a.ld + c] = slots[a.carry[2 * i] * a.ld + c];
 }
 
-// kTeams teams of 12 / kTeams wavefronts, kRows rows per wavefront; kLds: the strip's models, momentum buffers and
+// kTeams teams of 12 / kTeams wavefronts, kRows rows per wavefront and holder, kSets holders per team (holder h: set h / kTeams
+// of team h % kTeams); kLds: the strip's models, momentum buffers and
 // slots in LDS, otherwise in their global places (every entry is touched by one thread only, its column's).
-template <int kTeams, int kRows, bool kLds, bool kMom>
+template <int kTeams, int kRows, int kSets, bool kLds, bool kMom>
 __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const StripParams p) {
     constexpr int kTeamWaves = kStripMainWaves / kTeams;
-    constexpr int kTeamHelpers = kTeams == 12 ? 16 : kTeams == 6 ? 32 : kTeams == 4 ? 64 : 128;      // threads, one per sample
-    constexpr int kHalf = kTeams / 2;                  // evaluations and loads of a record, at most
+    constexpr int kHolders = kTeams * kSets, kTeamHelpers = kSets == 2 ? 8 : kTeams == 12 ? 16 : kTeams == 6 ? 32 : kTeams == 4 ? 64 : 128;      // threads, one per sample
+    constexpr int kWordsInFlight = kTeams == 12 ? 6 : 4;        // per lane of a helper
+    static_assert(kHolders * kTeamHelpers <= kStripHelpers, "a helper per sample of every holder");
     // teams of one wavefront have the whole gradient and put it into its slot themselves
     constexpr bool kDirect = kLds && kTeamWaves == 1;
     constexpr int kChunk = kRows > 16 ? 4 : kRows < 8 ? kRows : 8;      // rows whose sums or addresses are in registers at a time
     const StripArgs& a = p.a;
     extern __shared__ __attribute__((aligned(16))) float state_s[];      // [rows of X][rows of V][slots] x 256
-    __shared__ __attribute__((aligned(16))) v4f red_s[kStripMainWaves][64];      // partial gradients
-    __shared__ __attribute__((aligned(16))) float xh_s[kTeams][kStripCols];
+    __shared__ __attribute__((aligned(16))) v4f red_s[kStripMainWaves][64];      // partial gradients, in the same order
+    __shared__ __attribute__((aligned(16))) float xh_s[kTeams][kStripCols];            // points, in the order of a record's evaluations
     __shared__ v4u rec_s[4][kStripMaxRec];
-    __shared__ const float* rowp_s[2][kStripHelpers];                    // [iteration][team][sample]: the sample's row ...
-    __shared__ const float* targetp_s[2][kStripHelpers];                 // ... where its target is ...
+    __shared__ const float* rowp_s[2][kStripHelpers];                    // [iteration][holder][sample]: the sample's row ...
+    __shared__ int32_t index_s[2][kStripHelpers];                        // ... its number ...
     __shared__ float target_s[kStripHelpers];                            // ... and its target
     __shared__ float coef_s[kStripHelpers];
     __shared__ float loss_s[kStripHelpers];
@@ -203,52 +204,65 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         const bool ragged = col0 + kStripCols > a.d;
         const int from = at < a.d ? 4 * lane : 0;       // lanes beyond d read (and drop) the strip's first columns
         const int mine = first + kTeamWaves * lane;     // the sample whose target this lane brings
-        float target = 0.0f;
-        v4f row[kRows];
+        float target[kSets];
+        v4f row[kSets][kRows];
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) row[r] = v4f{0, 0, 0, 0};
+        for (int s = 0; s < kSets; ++s) {
+            target[s] = 0.0f;
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) row[s][r] = v4f{0, 0, 0, 0};
+        }
         __syncthreads();       // the first records
         __syncthreads();       // their addresses
         for (int it = 0; it < a.iterations; ++it) {
             const v4u* rec = rec_s[it & 3];
             const uint32_t evaluate = __builtin_amdgcn_readfirstlane(rec[0].z), load = __builtin_amdgcn_readfirstlane(rec[0].y);
-            if ((load >> team & 1) != 0) {      // early: the polls of phase B stand behind these loads
-                // no branch around a load: the wavefront would wait for one row before it requests the next
 #pragma unroll
-                for (int r0 = 0; r0 < kRows; r0 += kChunk) {
-                    const float* src[kChunk];
+            for (int s = 0; s < kSets; ++s) {
+                const int holder = team + kTeams * s;
+                if ((load >> holder & 1) != 0) {      // early: the polls of phase B stand behind these loads
+                    // no branch around a load: the wavefront would wait for one row before it requests the next
 #pragma unroll
-                    for (int r = 0; r < kChunk; ++r) src[r] = rowp_s[it & 1][team * kTeamHelpers + min(first + kTeamWaves * (r0 + r), M - 1)];
+                    for (int r0 = 0; r0 < kRows; r0 += kChunk) {
+                        const float* src[kChunk];
 #pragma unroll
-                    for (int r = 0; r < kChunk; ++r)
-                        if (r0 + r < kRows) row[r0 + r < kRows ? r0 + r : 0] = *reinterpret_cast<const v4f*>(src[r] + from);
+                        for (int r = 0; r < kChunk; ++r) src[r] = rowp_s[it & 1][holder * kTeamHelpers + min(first + kTeamWaves * (r0 + r), M - 1)];
+#pragma unroll
+                        for (int r = 0; r < kChunk; ++r)
+                            if (r0 + r < kRows) row[s][r0 + r < kRows ? r0 + r : 0] = *reinterpret_cast<const v4f*>(src[r] + from);
+                    }
+                    const v4u e = rec[2 + 2 * kTeams + 2 * __popc(load & ((1u << holder) - 1))];
+                    const uint32_t low = __builtin_amdgcn_readfirstlane(e.x), high = __builtin_amdgcn_readfirstlane(e.y);      // not signed
+                    const float* const targets = reinterpret_cast<const float*>(static_cast<uint64_t>(high) << 32 | low);
+                    target[s] = targets[index_s[it & 1][holder * kTeamHelpers + min(mine, M - 1)]];
                 }
-                target = *targetp_s[it & 1][team * kTeamHelpers + min(mine, M - 1)];
             }
             __syncthreads();   // phase A done
-            const bool evaluates = (evaluate >> team & 1) != 0;
-            const v4u* eval = rec + 1 + 2 * __popc(evaluate & ((1u << team) - 1));
-            if (evaluates) {
+#pragma unroll
+            for (int s = 0; s < kSets; ++s) {
+                const int holder = team + kTeams * s, number = __builtin_amdgcn_readfirstlane(__popc(evaluate & ((1u << holder) - 1)));
+                if ((evaluate >> holder & 1) == 0) continue;
+                const v4u* eval = rec + 1 + 2 * number;
                 const uint32_t seq = __builtin_amdgcn_readfirstlane(eval[0].y);
                 const uint32_t words = ((seq % kStripRing) * groups + group) * S * kStripGroupBlocks + rank;
-                const v4f x = *reinterpret_cast<const v4f*>(&xh_s[team][4 * lane]);
+                const v4f x = *reinterpret_cast<const v4f*>(&xh_s[number][4 * lane]);
                 if (ragged && at + 4 > a.d) {       // what lies beyond d in a padded row is arbitrary
 #pragma unroll
                     for (int r = 0; r < kRows; ++r) {
-                        if (at >= a.d) row[r].x = 0.0f;
-                        if (at + 1 >= a.d) row[r].y = 0.0f;
-                        if (at + 2 >= a.d) row[r].z = 0.0f;
-                        if (at + 3 >= a.d) row[r].w = 0.0f;
+                        if (at >= a.d) row[s][r].x = 0.0f;
+                        if (at + 1 >= a.d) row[s][r].y = 0.0f;
+                        if (at + 2 >= a.d) row[s][r].z = 0.0f;
+                        if (at + 3 >= a.d) row[s][r].w = 0.0f;
                     }
                 }
                 // the target of a sample is in LDS before any block can have the sample's sum
-                if (mine < M && lane < kRows) target_s[team * kTeamHelpers + mine] = target;
+                if (mine < M && lane < kRows) target_s[holder * kTeamHelpers + mine] = target[s];
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
 #pragma unroll
                 for (int r0 = 0; r0 < kRows; r0 += kChunk) {
                     float v[kChunk];
 #pragma unroll
-                    for (int r = 0; r < kChunk; ++r) v[r] = r0 + r < kRows ? dot4(row[r0 + r < kRows ? r0 + r : 0], x) : 0.0f;
+                    for (int r = 0; r < kChunk; ++r) v[r] = r0 + r < kRows ? dot4(row[s][r0 + r < kRows ? r0 + r : 0], x) : 0.0f;
                     const float z = wave_sums(v, lane);
                     const int r = r0 + lane / (64 / kChunk), m = first + kTeamWaves * r;
                     if (lane % (64 / kChunk) == 0 && r < kRows && m < M) put_word(a.words, words + m * kStripGroupBlocks, z, seq);
@@ -259,33 +273,37 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                 }
             }
             __syncthreads();   // the coefficients are there
-            if (evaluates) {
+#pragma unroll
+            for (int s = 0; s < kSets; ++s) {
+                const int holder = team + kTeams * s, number = __builtin_amdgcn_readfirstlane(__popc(evaluate & ((1u << holder) - 1)));
+                if ((evaluate >> holder & 1) == 0) continue;
+                const v4u* eval = rec + 1 + 2 * number;
                 v4f acc = {0, 0, 0, 0};      // sums of four rows at a time: shorter chains, smaller error
 #pragma unroll
                 for (int r0 = 0; r0 < kRows; r0 += kChunk) {
                     float coef[kChunk];
 #pragma unroll
-                    for (int r = 0; r < kChunk; ++r) coef[r] = coef_s[team * kTeamHelpers + min(first + kTeamWaves * (r0 + r), kTeamHelpers - 1)];
+                    for (int r = 0; r < kChunk; ++r) coef[r] = coef_s[holder * kTeamHelpers + min(first + kTeamWaves * (r0 + r), kTeamHelpers - 1)];
 #pragma unroll
                     for (int r1 = 0; r1 < kChunk; r1 += 4) {
                         v4f part = {0, 0, 0, 0};
 #pragma unroll
                         for (int r = r1; r < r1 + 4 && r < kChunk; ++r)
-                            if (r0 + r < kRows && first + kTeamWaves * (r0 + r) < M) part += row[r0 + r < kRows ? r0 + r : 0] * coef[r];
+                            if (r0 + r < kRows && first + kTeamWaves * (r0 + r) < M) part += row[s][r0 + r < kRows ? r0 + r : 0] * coef[r];
                         acc += part;
                     }
                 }
                 if (a.loss && first == 0 && __builtin_amdgcn_readfirstlane(eval[1].w) == static_cast<uint32_t>(block)) {
-                    float sum = lane < M ? loss_s[team * kTeamHelpers + lane] : 0.0f;
-                    if (lane + 64 < M) sum += loss_s[team * kTeamHelpers + lane + 64];
+                    float sum = lane < M ? loss_s[holder * kTeamHelpers + lane] : 0.0f;
+                    if (lane + 64 < M) sum += loss_s[holder * kTeamHelpers + lane + 64];
                     sum = all_sum(sum);
                     if (lane == 0) a.loss[__builtin_amdgcn_readfirstlane(eval[1].z)] = sum * a.gscale;
                 }
                 if (kDirect) {
-                    if (a.model == ADPSGD_MODEL_LOGREG) acc += *reinterpret_cast<const v4f*>(&xh_s[team][4 * lane]) * regularise;
+                    if (a.model == ADPSGD_MODEL_LOGREG) acc += *reinterpret_cast<const v4f*>(&xh_s[number][4 * lane]) * regularise;
                     *reinterpret_cast<v4f*>(state_s + slots_at + static_cast<int>(__builtin_amdgcn_readfirstlane(eval[0].w)) * kStripCols + 4 * lane) = acc;
                 } else {
-                    red_s[wave][lane] = acc;
+                    red_s[number * kTeamWaves + first][lane] = acc;
                 }
             }
             __syncthreads();   // phase C done
@@ -293,9 +311,9 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         return;
     }
 
-    // ---- helper wavefronts: column t, and sample t % kTeamHelpers of team t / kTeamHelpers ---------------------------
+    // ---- helper wavefronts: column t, and sample t % kTeamHelpers of holder t / kTeamHelpers ---------------------------
     const int t = tid - kMainThreads, hw = t >> 6;
-    const int team = min(t / kTeamHelpers, kTeams - 1), m = t / kTeamHelpers < kTeams ? t % kTeamHelpers : kStripHelpers;
+    const int holder = min(t / kTeamHelpers, kHolders - 1), m = t / kTeamHelpers < kHolders ? t % kTeamHelpers : kStripHelpers;
     const int64_t col = col0 + t;
     const bool inside = col < a.d;
     const uint32_t inside_bits = inside ? 0xFFFFFFFFu : 0u;      // a point is zero beyond d, whatever infinite coefficients have left there
@@ -312,27 +330,26 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
             gs[a.carry[2 * i] * ld] = inside ? a.slots[a.carry[2 * i + 1] * a.ld + col] : 0.0f;
     }
     const v4u* recs = reinterpret_cast<const v4u*>(a.recs) + lane;
-    const bool copies = hw == 3 && lane < a.rec_len;
-    v4u ahead = {0, 0, 0, 0};             // wavefront 3: the record after the next one
+    const bool copies = hw == 3 && lane < a.rec_len, copies_more = hw == 3 && lane + 64 < a.rec_len;
+    v4u ahead = {0, 0, 0, 0}, ahead_more = {0, 0, 0, 0};       // wavefront 3: the record after the next one
     int32_t index = 0;                    // row of this thread's sample in the worker's data
-    const uint32_t teams_below = (1u << team) - 1;
-    auto load_entry = [&](const v4u* rec, uint32_t load) { return rec + 1 + 2 * kHalf + 2 * __popc(load & teams_below); };
+    const uint32_t below = (1u << holder) - 1;
+    auto load_entry = [&](const v4u* rec, uint32_t load) { return rec + 1 + 2 * kTeams + 2 * __popc(load & below); };
     auto fetch_index = [&](const v4u* rec) {
         const uint32_t load = rec[0].y;
-        if ((load >> team & 1) != 0 && m < M) index = a.idx[static_cast<int64_t>(load_entry(rec, load)[0].x) * M + m];
+        if ((load >> holder & 1) != 0 && m < M) index = a.idx[static_cast<int64_t>(load_entry(rec, load)[0].x) * M + m];
     };
     auto put_addresses = [&](const v4u* rec, int parity) {
         const uint32_t load = rec[0].y;
-        if ((load >> team & 1) != 0 && m < M) {
-            const v4u* e = load_entry(rec, load);
-            const v4u f = e[0], g = e[1];
+        if ((load >> holder & 1) != 0 && m < M) {
+            const v4u f = load_entry(rec, load)[0];
             rowp_s[parity][t] = reinterpret_cast<const float*>(static_cast<uint64_t>(f.w) << 32 | f.z) + static_cast<int64_t>(index) * f.y + col0;
-            targetp_s[parity][t] = reinterpret_cast<const float*>(static_cast<uint64_t>(g.y) << 32 | g.x) + index;
+            index_s[parity][t] = index;
         }
     };
     // What phase A and the waits of phase B take from a record, and the rows of the first updates: read while the
     // exchange before is under way.
-    constexpr int kUps = kStripBatch, kEvals = kHalf < 3 ? kHalf : 3;
+    constexpr int kUps = kStripBatch, kEvals = kTeams < 3 ? kTeams : 3;
     uint32_t evaluate = 0;
     int n_updates = 0, n_evals = 0;
     v4u up[kUps], ev[kEvals], ev2[kEvals];
@@ -347,7 +364,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     };
     auto read_updates = [&](const v4u* rec, int from, int count) {
 #pragma unroll
-        for (int u = 0; u < kUps; ++u) up[u] = rec[1 + 4 * kHalf + min(from + u, max(count, 1) - 1)];      // none: row 0, unused
+        for (int u = 0; u < kUps; ++u) up[u] = rec[1 + 4 * kTeams + min(from + u, max(count, 1) - 1)];      // none: row 0, unused
         read_rows();
     };
     const int log_width = sum_width(groups > 1 ? groups : group_blocks), sub = t & ((1 << log_width) - 1);
@@ -362,7 +379,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         for (int u = 0; u < kWordsInFlight; ++u) {
             const int pair = from + u * pair_step + pair0, i = pair / kTeamHelpers, q = pair % kTeamHelpers;
             const bool live = i < count && q < M;
-            const v4u e = rec[1 + 2 * min(i, kHalf - 1)];
+            const v4u e = rec[1 + 2 * min(i, kTeams - 1)];
             place[u] = live ? e.x * kTeamHelpers + q : kStripHelpers;
             seq[u] = live && sub < words ? e.y : 0;
             at[u] = live ? (e.y % kStripRing) * ring_pitch + q * q_pitch + min(sub, words - 1) * sub_pitch : 0;
@@ -372,6 +389,11 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         rec_s[0][lane] = recs[0];
         rec_s[1][lane] = recs[a.rec_len];
         ahead = recs[2 * a.rec_len];
+    }
+    if (copies_more) {
+        rec_s[0][lane + 64] = recs[64];
+        rec_s[1][lane + 64] = recs[a.rec_len + 64];
+        ahead_more = recs[2 * a.rec_len + 64];
     }
     bool given_up = a.lose;
     __syncthreads();
@@ -401,11 +423,11 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                 for (int i = 0; i < kEvals; ++i) e[i] = last[1 + 2 * min(i0 + i, n_last - 1)];
 #pragma unroll
                 for (int i = 0; i < kEvals; ++i) {
-                    const float* part = reinterpret_cast<const float*>(&red_s[e[i].x * kTeamWaves][0]) + t;
+                    const float* part = reinterpret_cast<const float*>(&red_s[min(i0 + i, n_last - 1) * kTeamWaves][0]) + t;
                     g[i] = part[0];
 #pragma unroll
                     for (int w = 1; w < kTeamWaves; ++w) g[i] += part[w * kStripCols];
-                    if (a.model == ADPSGD_MODEL_LOGREG) g[i] += xh_s[e[i].x][t] * regularise;
+                    if (a.model == ADPSGD_MODEL_LOGREG) g[i] += xh_s[min(i0 + i, n_last - 1)][t] * regularise;
                 }
 #pragma unroll
                 for (int i = 0; i < kEvals; ++i)
@@ -459,11 +481,12 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                         const float step = gs[ev2[i].x * ld] * __uint_as_float(ev2[i].y);
                         x[i] = x[i] - step;
                     }
-                    xh_s[ev[i].x][t] = __uint_as_float(__float_as_uint(x[i]) & inside_bits);
+                    xh_s[i0 + i][t] = __uint_as_float(__float_as_uint(x[i]) & inside_bits);
                 }
             }
         }
         if (copies) rec_s[(it + 2) & 3][lane] = ahead;
+        if (copies_more) rec_s[(it + 2) & 3][lane + 64] = ahead_more;
         __syncthreads();
 
         // ---- B: sums of the dot products, coefficients; first what the next phase A needs
@@ -484,7 +507,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                 int d = d0 + (t >> log_group), i = 0;
                 const bool live = part < group_blocks && d < n_evals * mine;
 #pragma unroll
-                for (int k = 1; k < kHalf; ++k)
+                for (int k = 1; k < kTeams; ++k)
                     if (d >= mine && i < n_evals - 1) d -= mine, ++i;
                 const uint32_t of = rec[1 + 2 * i].y;
                 const uint32_t where[1] = {live ? (((of % kStripRing) * groups + group) * S + rank + d * group_blocks) * kStripGroupBlocks + part : 0};
@@ -514,19 +537,22 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                 if (S > M) reg[u] = group_sum(reg[u], log_width);
             }
             // every lane of a group has the sums of its pairs: the u-th lane finishes the u-th pair
-            float dot = z[0], square = reg[0];
-            uint32_t to = place[0];
+            const int lanes = min(1 << log_width, kWordsInFlight);
+            for (int u0 = 0; u0 < kWordsInFlight; u0 += lanes) {
+                float dot = z[0], square = reg[0];
+                uint32_t to = kStripHelpers;
 #pragma unroll
-            for (int u = 1; u < kWordsInFlight; ++u)
-                if (sub == u) {
-                    dot = z[u];
-                    square = reg[u];
-                    to = place[u];
+                for (int u = 0; u < kWordsInFlight; ++u)
+                    if (u0 + sub == u) {
+                        dot = z[u];
+                        square = reg[u];
+                        to = place[u];
+                    }
+                if (sub < lanes && to != kStripHelpers) {
+                    const v2f r = strip_coefficient(a, dot, target_s[to], square);
+                    coef_s[to] = r.x;
+                    loss_s[to] = r.y;
                 }
-            if (sub < kWordsInFlight && to != kStripHelpers) {
-                const v2f r = strip_coefficient(a, dot, target_s[to], square);
-                coef_s[to] = r.x;
-                loss_s[to] = r.y;
             }
         }
         if (given_up) lost_s = 1;
@@ -536,6 +562,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         // waits of phase B begin)
         fetch_index(rec_s[(it + 2) & 3]);
         if (copies) ahead = recs[static_cast<int64_t>(it + 3) * a.rec_len];
+        if (copies_more) ahead_more = recs[static_cast<int64_t>(it + 3) * a.rec_len + 64];
         __syncthreads();
     }
     if (given_up) __hip_atomic_store(a.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -549,14 +576,14 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     }
 }
 
-template <int kTeams, int kRows>
+template <int kTeams, int kRows, int kSets = 1>
 hipError_t launch_rows(StripParams& p, hipStream_t st) {
     const StripArgs& a = p.a;
     const size_t lds = a.lds_state ? static_cast<size_t>(a.n * (a.V ? 2 : 1) + a.n_lds_slots) * kStripCols * 4 : 0;
-    void* fn = a.lds_state ? (a.V ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, true, true>)
-                                  : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, true, false>))
-                           : (a.V ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, false, true>)
-                                  : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, false, false>));
+    void* fn = a.lds_state ? (a.V ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, kSets, true, true>)
+                                  : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, kSets, true, false>))
+                           : (a.V ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, kSets, false, true>)
+                                  : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, kSets, false, false>));
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (e != hipSuccess) return e;
     void* args[] = {&p};
@@ -581,13 +608,13 @@ size_t strip_exchange_bytes(int model, int32_t M) {
 
 // LDS of a block: the kernel's fixed arrays and the state of the strip
 size_t strip_lds_bytes(int32_t M, int32_t n, bool momentum, int32_t n_slots, bool lds_state) {
-    const size_t fixed = (kStripMainWaves + strip_teams(M)) * 1024 + 4 * kStripMaxRec * sizeof(StripEntry) + kStripHelpers * 48 + 1024;
+    const size_t fixed = (kStripMainWaves + strip_teams(M)) * 1024 + 4 * kStripMaxRec * sizeof(StripEntry) + kStripHelpers * 40 + 1024;
     return fixed + (lds_state ? (static_cast<size_t>(n) * (momentum ? 2 : 1) + n_slots) * kStripCols * 4 : 0);
 }
 
 hipError_t launch_strips(const StripArgs& a, hipStream_t st) {
     const int32_t blocks = strip_blocks(a.d);
-    if (a.d > kStripMaxD || a.M < 1 || a.M > kStripMaxM || a.rec_len > kStripMaxRec || a.teams != strip_teams(a.M) || a.grid < blocks)
+    if (a.d > kStripMaxD || a.M < 1 || a.M > kStripMaxM || a.rec_len > kStripMaxRec || a.teams != strip_teams(a.M) || a.holders != strip_holders(a.M) || a.grid < blocks)
         return hipErrorInvalidValue;
     StripParams p;
     p.a = a;
@@ -597,7 +624,7 @@ hipError_t launch_strips(const StripArgs& a, hipStream_t st) {
     p.sum_pitch = (p.samples + 15) & ~15;
     p.sums = a.words + static_cast<int64_t>(kStripRing) * strip_samples(a.model, a.M) * kStripGroups * kStripGroupBlocks;
     switch (a.teams) {
-        case 12: return a.M <= 8 ? launch_rows<12, 8>(p, st) : launch_rows<12, 16>(p, st);
+        case 12: return a.M <= 8 ? launch_rows<12, 8, 2>(p, st) : launch_rows<12, 16>(p, st);
         case 6: return launch_rows<6, 16>(p, st);
         case 4: return a.M <= 48 ? launch_rows<4, 16>(p, st) : launch_rows<4, 22>(p, st);
         default: return a.M <= 96 ? launch_rows<2, 16>(p, st) : launch_rows<2, 22>(p, st);

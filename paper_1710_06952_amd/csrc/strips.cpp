@@ -23,30 +23,30 @@ struct Builder {
     StripProgram& out;
     std::vector<int32_t> free_slots;
     const int32_t P;              // evaluations and loads of a record, at most
-    std::vector<int32_t> free_teams;
+    std::vector<int32_t> free_holders;
     int64_t loaded = 0;           // gradients whose rows have been requested, in the order of evaluation
-    std::vector<int32_t> team_of;
+    std::vector<int32_t> holder_of;
 
     Builder(const StripCall& call, int32_t teams, StripProgram& program) : c(call), out(program), P(teams / 2) {}
 
-    // a new record; the teams that the previous one has left idle request the rows of the next gradients
+    // a new record; the holders that the previous one has left idle request the rows of the next gradients
     StripEntry* open() {
         out.recs.resize(out.recs.size() + out.rec_len, StripEntry{0, 0, 0, 0});
         ++out.iterations;
         StripEntry* rec = out.recs.data() + out.recs.size() - out.rec_len;
-        const size_t n = std::min<size_t>(free_teams.size(), P);
-        std::sort(free_teams.begin(), free_teams.begin() + n);
-        // the order of the gradients is that of the loads; a record evaluates and loads in the order of the teams
+        const size_t n = std::min<size_t>(free_holders.size(), P);
+        std::sort(free_holders.begin(), free_holders.begin() + n);
+        // the order of the gradients is that of the loads; a record evaluates and loads in the order of the holders
         StripEntry* e = rec + 1 + 2 * P;
         for (size_t i = 0; i < n && loaded < static_cast<int64_t>(out.order.size()); ++i, e += 2) {
             const WorkerData& w = c.data[c.worker[out.order[loaded]]];
             const uint64_t f = reinterpret_cast<uint64_t>(w.features), t = reinterpret_cast<uint64_t>(w.targets);
             e[0] = StripEntry{static_cast<uint32_t>(loaded), static_cast<uint32_t>(w.ld), static_cast<uint32_t>(f), static_cast<uint32_t>(f >> 32)};
             e[1] = StripEntry{static_cast<uint32_t>(t), static_cast<uint32_t>(t >> 32), 0, 0};
-            rec[0].y |= 1u << free_teams[i];
-            team_of[loaded++] = free_teams[i];
+            rec[0].y |= 1u << free_holders[i];
+            holder_of[loaded++] = free_holders[i];
         }
-        free_teams.erase(free_teams.begin(), free_teams.begin() + n);
+        free_holders.erase(free_holders.begin(), free_holders.begin() + n);
         return rec;
     }
     int32_t take_slot() {         // -1: none left
@@ -75,15 +75,17 @@ struct Order {
 // Iteration order.  An update is applied when its gradient is there, the earlier updates of its rows are applied and
 // the reads that precede it are evaluated; an iteration applies all that can be (in waves of pairwise different rows,
 // each filled up to whole batches of the kernel) and then evaluates the gradients that are ready, the oldest events
-// first, one for half of the teams at most.  So an iteration is spent per link of a chain of gradients, not per round.
+// first, teams / 2 at most.  So an iteration is spent per link of a chain of gradients, not per round.
 // Gradients run at most `window` events ahead of the first event not applied: that bounds the slots, and as no read is
 // further than the largest tau ahead of an update that waits for it, a window beyond that cannot block.
-// Minibatch rows are requested in the order of evaluation, each set by a team whose last gradient was finished in the
-// iteration before, so a team's next rows are in flight while the others work.
-bool build_strips(const StripCall& c, int32_t teams, StripProgram& out) {
+// Minibatch rows are requested in the order of evaluation, each set for a holder whose last gradient was finished in the
+// iteration before, so the next rows are in flight while others are worked on.  All gradients before an iteration's own are
+// evaluated by then, so with teams / 2 holders or more its rows are there or go out at its start.
+bool build_strips(const StripCall& c, int32_t teams, StripProgram& out, int32_t holders) {
     const Plan& plan = *c.plan;
     out = StripProgram{};
     out.teams = teams;
+    out.holders = holders > 0 ? holders : teams;
     out.slot.assign(static_cast<size_t>(c.K), -1);
     auto carried = [&](int64_t k) { return c.carried_slot && c.carried_slot[k] >= 0; };
     auto rows_of = [&](int64_t k, auto&& f) {
@@ -236,10 +238,10 @@ bool build_strips(const StripCall& c, int32_t teams, StripProgram& out) {
     out.rec_len = 1 + 4 * b.P + width;
     out.n_slots = std::max(out.n_slots, 1);
     out.recs.reserve((steps.size() + ops.size() / width + 6) * out.rec_len);
-    b.team_of.assign(out.order.size(), -1);
-    for (int32_t t = 0; t < teams; ++t) b.free_teams.push_back(t);
+    b.holder_of.assign(out.order.size(), -1);
+    for (int32_t t = 0; t < out.holders; ++t) b.free_holders.push_back(t);
     b.open();
-    std::vector<std::pair<int32_t, int64_t>> evals;      // (team, position) of a record
+    std::vector<std::pair<int32_t, int64_t>> evals;      // (holder, position) of a record
     for (size_t i = 0; i + 1 < steps.size(); ++i) {
         StripEntry* rec = b.open();
         const size_t count = steps[i + 1].updates - steps[i].updates;
@@ -250,20 +252,20 @@ bool build_strips(const StripCall& c, int32_t teams, StripProgram& out) {
             rec[0].x = static_cast<uint32_t>(n);
         }
         evals.clear();
-        for (size_t q = steps[i].order; q < steps[i + 1].order; ++q) evals.push_back({b.team_of[q], static_cast<int64_t>(q)});
+        for (size_t q = steps[i].order; q < steps[i + 1].order; ++q) evals.push_back({b.holder_of[q], static_cast<int64_t>(q)});
         std::sort(evals.begin(), evals.end());
         StripEntry* e = rec + 1;
-        for (const auto& [team, at] : evals) {
+        for (const auto& [holder, at] : evals) {
             const int64_t k = out.order[at], kp = plan.prev[k];
-            e[0] = StripEntry{static_cast<uint32_t>(team), c.seq0 + static_cast<uint32_t>(at), static_cast<uint32_t>(c.worker[k]),
+            e[0] = StripEntry{static_cast<uint32_t>(holder), c.seq0 + static_cast<uint32_t>(at), static_cast<uint32_t>(c.worker[k]),
                               static_cast<uint32_t>(out.slot[k])};
             e[1] = StripEntry{0xFFFFFFFFu, 0, static_cast<uint32_t>(k), static_cast<uint32_t>(at % c.strips)};
             if (kp >= 0) {
                 e[1].x = static_cast<uint32_t>(out.slot[kp]);
                 e[1].y = bits(c.gamma ? c.gamma[kp] : c.gamma_default);
             }
-            rec[0].z |= 1u << team;
-            b.free_teams.push_back(team);
+            rec[0].z |= 1u << holder;
+            b.free_holders.push_back(holder);
             e += 2;
         }
     }
@@ -288,7 +290,7 @@ struct Checker {
     std::vector<std::vector<RowUpdate>> due;       // per row: its updates in the order of the events ...
     std::vector<size_t> done;                      // ... and how many are applied
     std::vector<int64_t> slot_event;               // gradient held by a slot, or -1
-    std::vector<int64_t> loaded;                   // per team: position whose minibatch rows it holds or has requested, or -1
+    std::vector<int64_t> loaded;                   // per holder: position whose minibatch rows it holds or has requested, or -1
     std::vector<int64_t> loaded_in;                // ... and the record that requested them
     std::vector<char> evaluated, applied;
 
@@ -325,7 +327,7 @@ struct Checker {
         if (k >= c.K || a.x >= loaded.size()) return fail("an evaluation of no event", record);
         const int64_t at = static_cast<int64_t>(a.y - c.seq0);
         if (at < 0 || at >= static_cast<int64_t>(p.order.size()) || p.order[at] != k) return fail("a wrong sequence number", record);
-        if (loaded[a.x] != at || loaded_in[a.x] >= record) return fail("a team without the rows of its gradient", record);
+        if (loaded[a.x] != at || loaded_in[a.x] > record) return fail("a holder without the rows of its gradient", record);
         loaded[a.x] = -1;
         if (evaluated[k] || static_cast<int32_t>(a.z) != c.worker[k]) return fail("a gradient of the wrong worker", record);
         evaluated[k] = 1;
@@ -344,20 +346,20 @@ struct Checker {
         return true;
     }
 
-    bool load(const StripEntry& a, const StripEntry& b, int32_t team, int64_t record) {
+    bool load(const StripEntry& a, const StripEntry& b, int32_t holder, int64_t record) {
         if (a.x >= p.order.size()) return fail("rows of no gradient requested", record);
         const WorkerData& w = c.data[c.worker[p.order[a.x]]];
         const uint64_t f = reinterpret_cast<uint64_t>(w.features), t = reinterpret_cast<uint64_t>(w.targets);
-        if (loaded[team] != -1) return fail("rows requested by a team that is not idle", record);
+        if (loaded[holder] != -1) return fail("rows requested for a holder that is not idle", record);
         if (a.y != w.ld || (static_cast<uint64_t>(a.w) << 32 | a.z) != f || (static_cast<uint64_t>(b.y) << 32 | b.x) != t)
             return fail("rows of the wrong worker requested", record);
-        loaded[team] = a.x;
-        loaded_in[team] = record;
+        loaded[holder] = a.x;
+        loaded_in[holder] = record;
         return true;
     }
 
     bool run() {
-        const int32_t teams = p.teams, half = teams / 2;
+        const int32_t holders = p.holders, half = p.teams / 2;
         if (static_cast<int64_t>(p.recs.size()) != (p.iterations + 3) * p.rec_len || p.rec_len > kStripMaxRec || p.rec_len < 2 + 4 * half)
             return fail("a table of the wrong size", 0);
         const int64_t slots = c.renumber ? p.n_slots : c.n_slots;
@@ -365,8 +367,8 @@ struct Checker {
         due.resize(c.n);
         done.assign(c.n, 0);
         slot_event.assign(slots, -1);
-        loaded.assign(teams, -1);
-        loaded_in.assign(teams, -1);
+        loaded.assign(holders, -1);
+        loaded_in.assign(holders, -1);
         evaluated.assign(c.K, 0);
         applied.assign(c.K, 0);
         for (int64_t k = 0; k < c.A; ++k) {
@@ -396,20 +398,20 @@ struct Checker {
                 const StripEntry& e = rec[1 + 4 * half + u];
                 if ((e.w & kStripEmpty) == 0 && !update(e, it, batch)) return false;
             }
+            if (holders < 32 && (rec[0].y >> holders != 0 || rec[0].z >> holders != 0)) return fail("a holder that does not exist", it);
             int32_t evals = 0, loads = 0;
-            for (int32_t t = 0; t < teams; ++t) {
-                if (rec[0].z >> t & 1) {
-                    const StripEntry* e = rec + 1 + 2 * evals;
-                    if (++evals > half || static_cast<int32_t>(e[0].x) != t) return fail("evaluations out of the order of their teams", it);
-                    if (!evaluation(e[0], e[1], it, finished)) return false;
-                    if (rec[0].y >> t & 1) return fail("a team loads and evaluates at once", it);
-                }
+            for (int32_t t = 0; t < holders; ++t)
                 if (rec[0].y >> t & 1) {
                     const StripEntry* e = rec + 1 + 2 * half + 2 * loads;
                     if (++loads > half) return fail("more loads than a record holds", it);
                     if (!load(e[0], e[1], t, it)) return false;
                 }
-            }
+            for (int32_t t = 0; t < holders; ++t)
+                if (rec[0].z >> t & 1) {
+                    const StripEntry* e = rec + 1 + 2 * evals;
+                    if (++evals > half || static_cast<int32_t>(e[0].x) != t) return fail("evaluations out of the order of their holders", it);
+                    if (!evaluation(e[0], e[1], it, finished)) return false;
+                }
         }
         if (!finished.empty()) return fail("gradients left unfinished", p.iterations);
         for (int64_t k = 0; k < c.K; ++k) {

@@ -16,16 +16,18 @@ constexpr int kStripRing = 32;           // exchanges whose words are kept (more
 constexpr int kStripGroups = 8;          // groups of blocks that sum among themselves first (one per XCD) ...
 constexpr int kStripGroupBlocks = 32;    // ... and blocks in a group, at most
 constexpr int kStripCounters = 16;       // words that the blocks count themselves with, zero before the launch
-constexpr int kStripMaxRec = 64;         // entries of a record
+constexpr int kStripMaxRec = 80;         // entries of a record (up to 128: two per lane of the wavefront that copies them)
 constexpr int64_t kStripMaxD = kStripGroups * kStripGroupBlocks * kStripCols;    // at most one block per compute unit
 constexpr int32_t kStripMaxM = 128;
 constexpr int kStripLdsBytes = 160 * 1024;
 constexpr uint64_t kClockTicksPerUs = 100;      // the constant clock of the device, 100 MHz on gfx950
 
 // A record is one iteration of the kernel: a header, two entries for each of up to teams / 2 evaluations, two for each of
-// as many loads (both in the order of their teams), then the updates.  All fields are 32-bit words.
-//   header            updates, teams that load (bit mask), teams that evaluate (bit mask), -
-//   evaluation        team, sequence number of the gradient, worker read, slot the gradient goes to;
+// as many loads (both in the order of their holders), then the updates.  A holder is a set of registers for the rows of one
+// gradient.  An iteration requests rows before it evaluates, so a holder may do both in one record: teams / 2 holders are
+// enough, and with as many as `teams` all rows are requested an iteration ahead.  All fields are 32-bit words.
+//   header            updates, holders that load (bit mask), holders that evaluate (bit mask), -
+//   evaluation        holder, sequence number of the gradient, worker read, slot the gradient goes to;
 //                     slot of the pending gradient that compensates the read (or -1), its step size, the event, the
 //                     strip that writes its loss
 //   load              position in the index table, row pitch of the features, features (64 bits);  targets (64 bits), -, -
@@ -37,7 +39,7 @@ struct alignas(16) StripEntry {
 };
 // The iterations of a call, laid out by build_strips.
 struct StripProgram {
-    int32_t teams = 0, rec_len = 0;
+    int32_t teams = 0, holders = 0, rec_len = 0;       // teams: twice the evaluations of a record
     int64_t iterations = 0;
     std::vector<StripEntry> recs;        // (iterations + 3) x rec_len, the last three empty
     std::vector<int64_t> order;          // events in the order their gradients are evaluated (rows of the index table)
@@ -61,9 +63,10 @@ struct StripCall {
     uint32_t seq0;                       // sequence number of the first gradient
     int32_t strips;                      // blocks with a strip
 };
-// Teams of wavefronts (gradients whose rows are held) for a minibatch of M samples: as many as their rows leave
-// registers for (at most 22 rows of a wavefront).
+// Teams of wavefronts for a minibatch of M samples, and holders: as many as their rows leave registers for (at most 22 rows
+// of a wavefront).  A record evaluates as many gradients as there are teams.
 inline int32_t strip_teams(int32_t M) { return M <= 16 ? 12 : M <= 32 ? 6 : M <= 64 ? 4 : 2; }
+inline int32_t strip_holders(int32_t M) { return M <= 8 ? 2 * strip_teams(M) : strip_teams(M); }
 // Gradients run at most this many events ahead of the first event not applied: as many as there are slots for, 64 at most
 // and T_max + 1 at least.  In LDS slots_fit slots fit (lds_state: more than T_max); in the workspace there are n_slots, which
 // may be fewer than T_max + 1 (the library uses 4096 at most): more than the largest tau of the call all the same, or there is
@@ -73,11 +76,12 @@ inline int32_t strip_window(int64_t T_max, bool lds_state, int64_t slots_fit, in
                                           : std::min<int64_t>(n_slots, std::max<int64_t>(T_max + 1, 64)));
 }
 // false: the events do not come in any order (the plan is not one of this schedule), or there is no slot for a gradient
-bool build_strips(const StripCall& c, int32_t teams, StripProgram& out);
+// teams: twice the evaluations of a record; holders: as many, or at least half (0: as many)
+bool build_strips(const StripCall& c, int32_t teams, StripProgram& out, int32_t holders = 0);
 // Executes the records on paper and compares with the serial semantics (ADPSGD_FLAG_VERIFY_PLAN): every read sees exactly
 // the updates before its logical time and the pending gradient it is compensated with, every update finds its gradient and
-// keeps the order of its rows, a batch of updates names a row once, minibatch rows are requested before they are used, by a
-// team that is idle, and no slot is given away early.
+// keeps the order of its rows, a batch of updates names a row once, minibatch rows are requested before they are used, for a
+// holder that is idle, and no slot is given away early.
 bool verify_strips(const StripCall& c, const StripProgram& p, std::string& err);
 
 struct StripArgs {
@@ -86,7 +90,7 @@ struct StripArgs {
     int64_t ld, d;
     int32_t n;
     int model;               // LSQ or LOGREG
-    int32_t M, teams;
+    int32_t M, teams, holders;
     const StripEntry* recs;  // device
     int32_t rec_len, iterations;
     const int32_t* idx;      // device, minibatch indices in the order of evaluation
