@@ -108,7 +108,7 @@ int drain_profile(adpsgd_t* h) {
 namespace {
 
 // Workers up to which the one-launch path of the linear models (kernels_strips.hip) is the faster one.  An iteration of the
-// strip kernel evaluates teams / 2 gradients at most, so its time per event jumps with the number of teams (M = 16, 32, 64)
+// strip kernel evaluates as many gradients as there are teams at most, so its time per event jumps with the number of teams (M = 16, 32, 64)
 // and does not fall with n, while the kernels of a round, of n / 4 events on a ring and n / 5 or n / 6 on denser graphs, take
 // its gradients side by side.  Measured, rounds over strips for a call of 12 n events (the lesser of a call alone and one of
 // several; least squares and logistic regression, momentum, T_max 0 ... 40; the least and the most of them):
@@ -118,6 +118,7 @@ namespace {
 //   d = 4096  M = 8      n = 40 1.49 ... 1.82, n = 72 0.82 ... 1.09        n = 64 1.50 ... 1.62, n = 100 0.66 ... 0.93
 //   d = 4096  M = 32     n = 28 1.29 ... 1.58, n = 48 0.75 ... 0.89        n = 48 1.21 ... 1.39
 //   d = 8192  M = 32     n = 20 1.17 ... 1.54, n = 28 0.90 ... 1.17        n = 48 0.98 ... 1.00
+// (drawn when an iteration evaluated half as many and the rounds read their rows twice; both are up to twice as fast now).
 // A direct exchange between 17 to 32 strips (d = 8192) is the slowest for its size.  The line keeps below the first loss of
 // any of them; beyond it the strips would still win in places (n = 32, M = 64: d = 4096 2356 / 3515 us a call;  n = 16,
 // M = 128, d = 20 000 6115 / 7528;  n = 32, M = 48, d = 1024 1218 / 1505) and lose near by (n = 16, M = 128, d = 300 2986 /
@@ -972,7 +973,7 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     const int32_t teams = strip_teams(M);
     StripProgram prog;
     try {
-        if (!build_strips(sc, 2 * teams, prog, strip_holders(M))) return ADPSGD_OK;
+        if (!build_strips(sc, 2 * teams, prog, teams)) return ADPSGD_OK;
     } catch (const std::bad_alloc&) {
         return ADPSGD_OK;
     }
@@ -1018,7 +1019,6 @@ int run_strips(adpsgd_t* h, EventCall& c, float* loss, bool& launched) {
     a.model = h->o.model;
     a.M = M;
     a.teams = teams;
-    a.holders = prog.holders;
     a.recs = reinterpret_cast<const StripEntry*>(dev);
     a.rec_len = prog.rec_len;
     a.iterations = static_cast<int32_t>(prog.iterations);

@@ -7,16 +7,21 @@
 // M dot products a_m . x^ of every gradient; models, momentum buffers and pending gradients of a strip stay in LDS,
 // minibatch rows are read once, into registers, ahead of the events that need them (the schedule names them), and are
 // still there when the coefficients arrive.
-// Measured, a call against the same call in rounds: n = 8, d = 1024, M = 32, 200 events 0.27 against 0.78 ms;  n = 16,
-// d = 4096, M = 8, 1280 events 1.08 against 7.2 ms;  n = 16, d = 20 001, M = 50, wait-free with momentum, 400 events 1.72
-// against 4.1 ms.  What binds now is the chain of an iteration, 4.7 us with 5.8 gradients for the second of these: updates
-// and x^ 1, dot products 0.2, exchange and coefficients 2.2, combination 0.3, barriers and records the rest; with many rows
-// per gradient (the third, 7.8 us) also their address translation, about 40 cycles per row and compute unit.
+// Measured, a call against the same call in rounds of three launches:  n = 8, d = 1024, M = 32, 200 events 0.24 against
+// 0.78 ms;  n = 16, d = 4096, M = 8, 1280 events 0.79 against 7.2 ms;  n = 16, d = 20 001, M = 50, wait-free with momentum, 400
+// events 1.17 against 4.1 ms.  What binds is the chain of an iteration (updates and x^, dot products, exchange and coefficients,
+// combination, barriers) times their number: 142, 5.2 us each with 9 gradients, for the second of these; with many rows per
+// gradient (the third, 103 of 11 us) also their address translation, about 40 cycles per row and compute unit.
+// An iteration evaluates a gradient per team.  With half of them, so that all rows are requested an iteration ahead, the three
+// took 72, 217 and 203 iterations and 0.28, 1.07 and 1.70 ms: most calls run out of teams before they run out of events that
+// could go on.  Where the events do not fill the teams the wider records cost up to 3 % (n = 8, d = 40 000, M = 8: 583 -> 602 us
+// for 107 iterations); two sets of rows per wavefront for M <= 8 were slower (0.88 ms for the second: a wavefront that works on
+// one set waits for the rows of the other).
 //
 // A block has 12 main wavefronts in `teams` teams, each team with the rows of one gradient in its registers, and 4
 // helper wavefronts (one thread per column, and one per minibatch sample).  An iteration has three phases:
 //   A  helpers: finish the gradients of the last iteration, apply updates, write x^ of the next gradients to LDS;
-//      main: idle teams request the rows of their next gradient
+//      main: idle teams request the rows of their next gradient (which may be one of this iteration)
 //   B  main: dot products of a team's rows with x^, published;  helpers: wait for the sums, make the coefficients
 //   C  main: sum_m c_m a_m of the team's rows to LDS
 // A compute unit returns vector loads in order, so a wait of phase B stands behind the rows requested before it: they go
@@ -24,6 +29,8 @@
 //
 // The sums go through the words of exchange.hpp: up to 32 strips exchange them directly; more sum within their XCD first
 // (the blocks of a group share out the samples), and only these sums cross the chip, at most 8 per sample.
+#include <type_traits>
+
 #include "device_common.hpp"
 #include "exchange.hpp"
 #include "strips.hpp"
@@ -98,7 +105,7 @@ __device__ __attribute__((noinline)) void run_alone(const StripArgs* args, int s
                 *xj = nj;
                 *xi = average_only ? nj : ni;
             }
-        if (tid < a.holders && (head.y >> tid & 1) != 0) {
+        if (tid < a.teams && (head.y >> tid & 1) != 0) {
             const v4u* e = rec + 1 + 2 * half + 2 * __popc(head.y & ((1u << tid) - 1));
             rows_of[tid][0] = e[0];
             rows_of[tid][1] = e[1];
@@ -154,15 +161,14 @@ __device__ __attribute__((noinline)) void run_alone(const StripArgs* args, int s
         for (int64_t c = tid; c < a.d; c += kStripThreads) a.slots[a.carry[2 * i + 1] * a.ld + c] = slots[a.carry[2 * i] * a.ld + c];
 }
 
-// kTeams teams of 12 / kTeams wavefronts, kRows rows per wavefront and holder, kSets holders per team (holder h: set h / kTeams
-// of team h % kTeams); kLds: the strip's models, momentum buffers and
+// kTeams teams of 12 / kTeams wavefronts, kRows rows per wavefront; kLds: the strip's models, momentum buffers and
 // slots in LDS, otherwise in their global places (every entry is touched by one thread only, its column's).
-template <int kTeams, int kRows, int kSets, bool kLds, bool kMom>
+template <int kTeams, int kRows, bool kLds, bool kMom>
 __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const StripParams p) {
     constexpr int kTeamWaves = kStripMainWaves / kTeams;
-    constexpr int kHolders = kTeams * kSets, kTeamHelpers = kSets == 2 ? 8 : kTeams == 12 ? 16 : kTeams == 6 ? 32 : kTeams == 4 ? 64 : 128;      // threads, one per sample
-    constexpr int kWordsInFlight = kTeams == 12 ? 6 : 4;        // per lane of a helper
-    static_assert(kHolders * kTeamHelpers <= kStripHelpers, "a helper per sample of every holder");
+    constexpr int kTeamHelpers = kTeams == 12 ? kRows : kTeams == 6 ? 32 : kTeams == 4 ? 64 : 128;      // threads, one per sample
+    constexpr int kWordsInFlight = kTeams == 12 && kLds ? 6 : 4;        // per lane of a helper
+    static_assert(kTeams * kTeamHelpers <= kStripHelpers, "a helper per sample of every team");
     // teams of one wavefront have the whole gradient and put it into its slot themselves
     constexpr bool kDirect = kLds && kTeamWaves == 1;
     constexpr int kChunk = kRows > 16 ? 4 : kRows < 8 ? kRows : 8;      // rows whose sums or addresses are in registers at a time
@@ -171,7 +177,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     __shared__ __attribute__((aligned(16))) v4f red_s[kStripMainWaves][64];      // partial gradients, in the same order
     __shared__ __attribute__((aligned(16))) float xh_s[kTeams][kStripCols];            // points, in the order of a record's evaluations
     __shared__ v4u rec_s[4][kStripMaxRec];
-    __shared__ const float* rowp_s[2][kStripHelpers];                    // [iteration][holder][sample]: the sample's row ...
+    __shared__ const float* rowp_s[2][kStripHelpers];                    // [iteration][team][sample]: the sample's row ...
     __shared__ int32_t index_s[2][kStripHelpers];                        // ... its number ...
     __shared__ float target_s[kStripHelpers];                            // ... and its target
     __shared__ float coef_s[kStripHelpers];
@@ -200,69 +206,63 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     if (wave < kStripMainWaves) {
         // ---- main wavefronts ------------------------------------------------------------------------------------
         const int team = wave / kTeamWaves, first = wave % kTeamWaves;       // rows first, first + kTeamWaves, ...
-        const int64_t at = col0 + 4 * lane;
         const bool ragged = col0 + kStripCols > a.d;
-        const int from = at < a.d ? 4 * lane : 0;       // lanes beyond d read (and drop) the strip's first columns
-        const int mine = first + kTeamWaves * lane;     // the sample whose target this lane brings
-        float target[kSets];
-        v4f row[kSets][kRows];
+        float target = 0.0f;
+        v4f row[kRows];
 #pragma unroll
-        for (int s = 0; s < kSets; ++s) {
-            target[s] = 0.0f;
-#pragma unroll
-            for (int r = 0; r < kRows; ++r) row[s][r] = v4f{0, 0, 0, 0};
-        }
+        for (int r = 0; r < kRows; ++r) row[r] = v4f{0, 0, 0, 0};
         __syncthreads();       // the first records
         __syncthreads();       // their addresses
         for (int it = 0; it < a.iterations; ++it) {
             const v4u* rec = rec_s[it & 3];
+            // what depends on the lane is computed anew in every iteration: kept, it would cost the rows registers
+            int l = lane;
+            asm volatile("" : "+v"(l));
+            const int64_t at = col0 + 4 * l;
+            const int from = at < a.d ? 4 * l : 0;       // lanes beyond d read (and drop) the strip's first columns
+            const int mine = first + kTeamWaves * l;     // the sample whose target this lane brings
             const uint32_t evaluate = __builtin_amdgcn_readfirstlane(rec[0].z), load = __builtin_amdgcn_readfirstlane(rec[0].y);
+            if ((load >> team & 1) != 0) {      // early: the polls of phase B stand behind these loads
+                // no branch around a load: the wavefront would wait for one row before it requests the next
 #pragma unroll
-            for (int s = 0; s < kSets; ++s) {
-                const int holder = team + kTeams * s;
-                if ((load >> holder & 1) != 0) {      // early: the polls of phase B stand behind these loads
-                    // no branch around a load: the wavefront would wait for one row before it requests the next
+                for (int r0 = 0; r0 < kRows; r0 += kChunk) {
+                    const float* src[kChunk];
 #pragma unroll
-                    for (int r0 = 0; r0 < kRows; r0 += kChunk) {
-                        const float* src[kChunk];
+                    for (int r = 0; r < kChunk; ++r) src[r] = rowp_s[it & 1][team * kTeamHelpers + min(first + kTeamWaves * (r0 + r), M - 1)];
 #pragma unroll
-                        for (int r = 0; r < kChunk; ++r) src[r] = rowp_s[it & 1][holder * kTeamHelpers + min(first + kTeamWaves * (r0 + r), M - 1)];
-#pragma unroll
-                        for (int r = 0; r < kChunk; ++r)
-                            if (r0 + r < kRows) row[s][r0 + r < kRows ? r0 + r : 0] = *reinterpret_cast<const v4f*>(src[r] + from);
-                    }
-                    const v4u e = rec[2 + 2 * kTeams + 2 * __popc(load & ((1u << holder) - 1))];
-                    const uint32_t low = __builtin_amdgcn_readfirstlane(e.x), high = __builtin_amdgcn_readfirstlane(e.y);      // not signed
-                    const float* const targets = reinterpret_cast<const float*>(static_cast<uint64_t>(high) << 32 | low);
-                    target[s] = targets[index_s[it & 1][holder * kTeamHelpers + min(mine, M - 1)]];
+                    for (int r = 0; r < kChunk; ++r)
+                        if (r0 + r < kRows) row[r0 + r < kRows ? r0 + r : 0] = *reinterpret_cast<const v4f*>(src[r] + from);
                 }
+                const v4u e = rec[2 + 2 * kTeams + 2 * __popc(load & ((1u << team) - 1))];
+                const uint32_t low = __builtin_amdgcn_readfirstlane(e.x), high = __builtin_amdgcn_readfirstlane(e.y);      // not signed
+                const float* const targets = reinterpret_cast<const float*>(static_cast<uint64_t>(high) << 32 | low);
+                target = targets[index_s[it & 1][team * kTeamHelpers + min(mine, M - 1)]];
             }
             __syncthreads();   // phase A done
-#pragma unroll
-            for (int s = 0; s < kSets; ++s) {
-                const int holder = team + kTeams * s, number = __builtin_amdgcn_readfirstlane(__popc(evaluate & ((1u << holder) - 1)));
-                if ((evaluate >> holder & 1) == 0) continue;
-                const v4u* eval = rec + 1 + 2 * number;
+            const bool evaluates = (evaluate >> team & 1) != 0;
+            const int number = __builtin_amdgcn_readfirstlane(__popc(evaluate & ((1u << team) - 1)));
+            const v4u* eval = rec + 1 + 2 * number;
+            if (evaluates) {
                 const uint32_t seq = __builtin_amdgcn_readfirstlane(eval[0].y);
                 const uint32_t words = ((seq % kStripRing) * groups + group) * S * kStripGroupBlocks + rank;
-                const v4f x = *reinterpret_cast<const v4f*>(&xh_s[number][4 * lane]);
+                const v4f x = *reinterpret_cast<const v4f*>(&xh_s[number][4 * l]);
                 if (ragged && at + 4 > a.d) {       // what lies beyond d in a padded row is arbitrary
 #pragma unroll
                     for (int r = 0; r < kRows; ++r) {
-                        if (at >= a.d) row[s][r].x = 0.0f;
-                        if (at + 1 >= a.d) row[s][r].y = 0.0f;
-                        if (at + 2 >= a.d) row[s][r].z = 0.0f;
-                        if (at + 3 >= a.d) row[s][r].w = 0.0f;
+                        if (at >= a.d) row[r].x = 0.0f;
+                        if (at + 1 >= a.d) row[r].y = 0.0f;
+                        if (at + 2 >= a.d) row[r].z = 0.0f;
+                        if (at + 3 >= a.d) row[r].w = 0.0f;
                     }
                 }
                 // the target of a sample is in LDS before any block can have the sample's sum
-                if (mine < M && lane < kRows) target_s[holder * kTeamHelpers + mine] = target[s];
+                if (mine < M && l < kRows) target_s[team * kTeamHelpers + mine] = target;
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
 #pragma unroll
                 for (int r0 = 0; r0 < kRows; r0 += kChunk) {
                     float v[kChunk];
 #pragma unroll
-                    for (int r = 0; r < kChunk; ++r) v[r] = r0 + r < kRows ? dot4(row[s][r0 + r < kRows ? r0 + r : 0], x) : 0.0f;
+                    for (int r = 0; r < kChunk; ++r) v[r] = r0 + r < kRows ? dot4(row[r0 + r < kRows ? r0 + r : 0], x) : 0.0f;
                     const float z = wave_sums(v, lane);
                     const int r = r0 + lane / (64 / kChunk), m = first + kTeamWaves * r;
                     if (lane % (64 / kChunk) == 0 && r < kRows && m < M) put_word(a.words, words + m * kStripGroupBlocks, z, seq);
@@ -273,37 +273,33 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                 }
             }
             __syncthreads();   // the coefficients are there
-#pragma unroll
-            for (int s = 0; s < kSets; ++s) {
-                const int holder = team + kTeams * s, number = __builtin_amdgcn_readfirstlane(__popc(evaluate & ((1u << holder) - 1)));
-                if ((evaluate >> holder & 1) == 0) continue;
-                const v4u* eval = rec + 1 + 2 * number;
+            if (evaluates) {
                 v4f acc = {0, 0, 0, 0};      // sums of four rows at a time: shorter chains, smaller error
 #pragma unroll
                 for (int r0 = 0; r0 < kRows; r0 += kChunk) {
                     float coef[kChunk];
 #pragma unroll
-                    for (int r = 0; r < kChunk; ++r) coef[r] = coef_s[holder * kTeamHelpers + min(first + kTeamWaves * (r0 + r), kTeamHelpers - 1)];
+                    for (int r = 0; r < kChunk; ++r) coef[r] = coef_s[team * kTeamHelpers + min(first + kTeamWaves * (r0 + r), kTeamHelpers - 1)];
 #pragma unroll
                     for (int r1 = 0; r1 < kChunk; r1 += 4) {
                         v4f part = {0, 0, 0, 0};
 #pragma unroll
                         for (int r = r1; r < r1 + 4 && r < kChunk; ++r)
-                            if (r0 + r < kRows && first + kTeamWaves * (r0 + r) < M) part += row[s][r0 + r < kRows ? r0 + r : 0] * coef[r];
+                            if (r0 + r < kRows && first + kTeamWaves * (r0 + r) < M) part += row[r0 + r < kRows ? r0 + r : 0] * coef[r];
                         acc += part;
                     }
                 }
                 if (a.loss && first == 0 && __builtin_amdgcn_readfirstlane(eval[1].w) == static_cast<uint32_t>(block)) {
-                    float sum = lane < M ? loss_s[holder * kTeamHelpers + lane] : 0.0f;
-                    if (lane + 64 < M) sum += loss_s[holder * kTeamHelpers + lane + 64];
+                    float sum = lane < M ? loss_s[team * kTeamHelpers + lane] : 0.0f;
+                    if (lane + 64 < M) sum += loss_s[team * kTeamHelpers + lane + 64];
                     sum = all_sum(sum);
                     if (lane == 0) a.loss[__builtin_amdgcn_readfirstlane(eval[1].z)] = sum * a.gscale;
                 }
                 if (kDirect) {
-                    if (a.model == ADPSGD_MODEL_LOGREG) acc += *reinterpret_cast<const v4f*>(&xh_s[number][4 * lane]) * regularise;
+                    if (a.model == ADPSGD_MODEL_LOGREG) acc += *reinterpret_cast<const v4f*>(&xh_s[number][4 * l]) * regularise;
                     *reinterpret_cast<v4f*>(state_s + slots_at + static_cast<int>(__builtin_amdgcn_readfirstlane(eval[0].w)) * kStripCols + 4 * lane) = acc;
                 } else {
-                    red_s[number * kTeamWaves + first][lane] = acc;
+                    red_s[number * kTeamWaves + first][l] = acc;
                 }
             }
             __syncthreads();   // phase C done
@@ -311,9 +307,9 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         return;
     }
 
-    // ---- helper wavefronts: column t, and sample t % kTeamHelpers of holder t / kTeamHelpers ---------------------------
+    // ---- helper wavefronts: column t, and sample t % kTeamHelpers of team t / kTeamHelpers ---------------------------
     const int t = tid - kMainThreads, hw = t >> 6;
-    const int holder = min(t / kTeamHelpers, kHolders - 1), m = t / kTeamHelpers < kHolders ? t % kTeamHelpers : kStripHelpers;
+    const int team = min(t / kTeamHelpers, kTeams - 1), m = t / kTeamHelpers < kTeams ? t % kTeamHelpers : kStripHelpers;
     const int64_t col = col0 + t;
     const bool inside = col < a.d;
     const uint32_t inside_bits = inside ? 0xFFFFFFFFu : 0u;      // a point is zero beyond d, whatever infinite coefficients have left there
@@ -333,15 +329,15 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     const bool copies = hw == 3 && lane < a.rec_len, copies_more = hw == 3 && lane + 64 < a.rec_len;
     v4u ahead = {0, 0, 0, 0}, ahead_more = {0, 0, 0, 0};       // wavefront 3: the record after the next one
     int32_t index = 0;                    // row of this thread's sample in the worker's data
-    const uint32_t below = (1u << holder) - 1;
+    const uint32_t below = (1u << team) - 1;
     auto load_entry = [&](const v4u* rec, uint32_t load) { return rec + 1 + 2 * kTeams + 2 * __popc(load & below); };
     auto fetch_index = [&](const v4u* rec) {
         const uint32_t load = rec[0].y;
-        if ((load >> holder & 1) != 0 && m < M) index = a.idx[static_cast<int64_t>(load_entry(rec, load)[0].x) * M + m];
+        if ((load >> team & 1) != 0 && m < M) index = a.idx[static_cast<int64_t>(load_entry(rec, load)[0].x) * M + m];
     };
     auto put_addresses = [&](const v4u* rec, int parity) {
         const uint32_t load = rec[0].y;
-        if ((load >> holder & 1) != 0 && m < M) {
+        if ((load >> team & 1) != 0 && m < M) {
             const v4u f = load_entry(rec, load)[0];
             rowp_s[parity][t] = reinterpret_cast<const float*>(static_cast<uint64_t>(f.w) << 32 | f.z) + static_cast<int64_t>(index) * f.y + col0;
             index_s[parity][t] = index;
@@ -372,17 +368,57 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     // word of sample q and partial sum `sub`: by groups of whole lines, or by samples
     const uint32_t q_pitch = groups > 1 ? 1 : kStripGroupBlocks, sub_pitch = groups > 1 ? p.sum_pitch : 1;
     const uint32_t ring_pitch = groups > 1 ? groups * p.sum_pitch : S * kStripGroupBlocks;
+    const int log_group = sum_width(group_blocks), part = t & ((1 << log_group) - 1), slots = kStripHelpers >> log_group;
+    const int mine = rank < S ? (S - rank + group_blocks - 1) / group_blocks : 0;      // samples of a gradient that this block sums
+    const uint32_t per_eval = (0xFFFFu + max(mine, 1)) / max(mine, 1);                  // d / mine = d per_eval >> 16 for d mine < 2^16
     const int pair0 = t >> log_width, pair_step = kStripHelpers >> log_width;
-    uint32_t at[kWordsInFlight], seq[kWordsInFlight], place[kWordsInFlight];
-    auto read_pairs = [&](const v4u* rec, int from, int count) {        // (gradient, sample) pairs, samples padded to a power of two
+    const unsigned long long* const base = groups > 1 ? p.sums : a.words;
+    bool given_up = a.lose;
+    // Coefficients of up to kWords (gradient, sample) pairs per group of lanes that share a sum, from pair `from` on; samples are
+    // padded to a power of two.
+    auto finish_pairs = [&](const v4u* rec, int from, int count, auto words_in_flight) {
+        constexpr int kWords = decltype(words_in_flight)::value;
+        uint32_t at[kWords], seq[kWords], place[kWords];
+        float z[kWords], reg[kWords];
 #pragma unroll
-        for (int u = 0; u < kWordsInFlight; ++u) {
+        for (int u = 0; u < kWords; ++u) {
             const int pair = from + u * pair_step + pair0, i = pair / kTeamHelpers, q = pair % kTeamHelpers;
             const bool live = i < count && q < M;
-            const v4u e = rec[1 + 2 * min(i, kTeams - 1)];
+            const v4u e = rec[1 + 2 * min(i, count - 1)];
             place[u] = live ? e.x * kTeamHelpers + q : kStripHelpers;
             seq[u] = live && sub < words ? e.y : 0;
-            at[u] = live ? (e.y % kStripRing) * ring_pitch + q * q_pitch + min(sub, words - 1) * sub_pitch : 0;
+            at[u] = !live ? 0 : (e.y % kStripRing) * ring_pitch + min(q, M - 1) * q_pitch + min(sub, words - 1) * sub_pitch;      // idle: near others
+            reg[u] = 0.0f;
+        }
+        wait_words<kWords>(base, at, seq, z, given_up);
+        if (S > M) {
+#pragma unroll
+            for (int u = 0; u < kWords; ++u) at[u] += place[u] == kStripHelpers ? 0 : (M - place[u] % kTeamHelpers) * q_pitch;
+            wait_words<kWords>(base, at, seq, reg, given_up);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+#pragma unroll
+        for (int u = 0; u < kWords; ++u) {
+            z[u] = group_sum(z[u], log_width);
+            if (S > M) reg[u] = group_sum(reg[u], log_width);
+        }
+        // every lane of a group has the sums of its pairs: the u-th lane finishes the u-th pair
+        const int lanes = kWords <= 4 ? kWords : min(1 << log_width, kWords);         // a group has four lanes at least
+        for (int u0 = 0; u0 < kWords; u0 += lanes) {
+            float dot = z[0], square = reg[0];
+            uint32_t to = kStripHelpers;
+#pragma unroll
+            for (int u = 0; u < kWords; ++u)
+                if (u0 + sub == u) {
+                    dot = z[u];
+                    square = reg[u];
+                    to = place[u];
+                }
+            if (sub < lanes && to != kStripHelpers) {
+                const v2f r = strip_coefficient(a, dot, target_s[to], square);
+                coef_s[to] = r.x;
+                loss_s[to] = r.y;
+            }
         }
     };
     if (copies) {
@@ -395,7 +431,6 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         rec_s[1][lane + 64] = recs[a.rec_len + 64];
         ahead_more = recs[2 * a.rec_len + 64];
     }
-    bool given_up = a.lose;
     __syncthreads();
     fetch_index(rec_s[0]);
     put_addresses(rec_s[0], 0);
@@ -501,14 +536,11 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         }
         put_addresses(next, (it + 1) & 1);
         if (groups > 1) {       // the group's sums: sample q is summed by the block of rank q mod group_blocks
-            const int log_group = sum_width(group_blocks), part = t & ((1 << log_group) - 1), slots = kStripHelpers >> log_group;
-            const int mine = rank < S ? (S - rank + group_blocks - 1) / group_blocks : 0;      // samples of a gradient
             for (int d0 = 0; d0 < n_evals * mine; d0 += slots) {
-                int d = d0 + (t >> log_group), i = 0;
+                int d = d0 + (t >> log_group);
                 const bool live = part < group_blocks && d < n_evals * mine;
-#pragma unroll
-                for (int k = 1; k < kTeams; ++k)
-                    if (d >= mine && i < n_evals - 1) d -= mine, ++i;
+                const int i = min(static_cast<int>(static_cast<uint32_t>(d) * per_eval >> 16), n_evals - 1);
+                d -= i * mine;
                 const uint32_t of = rec[1 + 2 * i].y;
                 const uint32_t where[1] = {live ? (((of % kStripRing) * groups + group) * S + rank + d * group_blocks) * kStripGroupBlocks + part : 0};
                 const uint32_t number[1] = {live ? of : 0};
@@ -518,42 +550,12 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                 if (part == 0 && live) put_word(p.sums, ((of % kStripRing) * groups + group) * p.sum_pitch + rank + d * group_blocks, sum, of);
             }
         }
-        for (int from = 0; from < n_evals * kTeamHelpers; from += kWordsInFlight * pair_step) {
-            float z[kWordsInFlight], reg[kWordsInFlight];
-            const unsigned long long* base = groups > 1 ? p.sums : a.words;
-            read_pairs(rec, from, n_evals);
-            wait_words<kWordsInFlight>(base, at, seq, z, given_up);
-#pragma unroll
-            for (int u = 0; u < kWordsInFlight; ++u) reg[u] = 0.0f;
-            if (S > M) {
-#pragma unroll
-                for (int u = 0; u < kWordsInFlight; ++u) at[u] += place[u] == kStripHelpers ? 0 : (M - place[u] % kTeamHelpers) * q_pitch;
-                wait_words<kWordsInFlight>(base, at, seq, reg, given_up);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-#pragma unroll
-            for (int u = 0; u < kWordsInFlight; ++u) {
-                z[u] = group_sum(z[u], log_width);
-                if (S > M) reg[u] = group_sum(reg[u], log_width);
-            }
-            // every lane of a group has the sums of its pairs: the u-th lane finishes the u-th pair
-            const int lanes = min(1 << log_width, kWordsInFlight);
-            for (int u0 = 0; u0 < kWordsInFlight; u0 += lanes) {
-                float dot = z[0], square = reg[0];
-                uint32_t to = kStripHelpers;
-#pragma unroll
-                for (int u = 0; u < kWordsInFlight; ++u)
-                    if (u0 + sub == u) {
-                        dot = z[u];
-                        square = reg[u];
-                        to = place[u];
-                    }
-                if (sub < lanes && to != kStripHelpers) {
-                    const v2f r = strip_coefficient(a, dot, target_s[to], square);
-                    coef_s[to] = r.x;
-                    loss_s[to] = r.y;
-                }
-            }
+        // few pairs take few words: what is polled in vain makes a poll longer (all lanes without a word poll the same one)
+        const int pairs = n_evals * kTeamHelpers;
+        if (n_evals > 0 && pairs <= 2 * pair_step) {
+            finish_pairs(rec, 0, n_evals, std::integral_constant<int, 2>{});
+        } else {
+            for (int from = 0; from < pairs; from += kWordsInFlight * pair_step) finish_pairs(rec, from, n_evals, std::integral_constant<int, kWordsInFlight>{});
         }
         if (given_up) lost_s = 1;
         __syncthreads();
@@ -576,14 +578,14 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     }
 }
 
-template <int kTeams, int kRows, int kSets = 1>
+template <int kTeams, int kRows>
 hipError_t launch_rows(StripParams& p, hipStream_t st) {
     const StripArgs& a = p.a;
     const size_t lds = a.lds_state ? static_cast<size_t>(a.n * (a.V ? 2 : 1) + a.n_lds_slots) * kStripCols * 4 : 0;
-    void* fn = a.lds_state ? (a.V ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, kSets, true, true>)
-                                  : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, kSets, true, false>))
-                           : (a.V ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, kSets, false, true>)
-                                  : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, kSets, false, false>));
+    void* fn = a.lds_state ? (a.V ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, true, true>)
+                                  : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, true, false>))
+                           : (a.V ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, false, true>)
+                                  : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, false, false>));
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (e != hipSuccess) return e;
     void* args[] = {&p};
@@ -614,7 +616,7 @@ size_t strip_lds_bytes(int32_t M, int32_t n, bool momentum, int32_t n_slots, boo
 
 hipError_t launch_strips(const StripArgs& a, hipStream_t st) {
     const int32_t blocks = strip_blocks(a.d);
-    if (a.d > kStripMaxD || a.M < 1 || a.M > kStripMaxM || a.rec_len > kStripMaxRec || a.teams != strip_teams(a.M) || a.holders != strip_holders(a.M) || a.grid < blocks)
+    if (a.d > kStripMaxD || a.M < 1 || a.M > kStripMaxM || a.rec_len > kStripMaxRec || a.teams != strip_teams(a.M) || a.grid < blocks)
         return hipErrorInvalidValue;
     StripParams p;
     p.a = a;
@@ -624,7 +626,7 @@ hipError_t launch_strips(const StripArgs& a, hipStream_t st) {
     p.sum_pitch = (p.samples + 15) & ~15;
     p.sums = a.words + static_cast<int64_t>(kStripRing) * strip_samples(a.model, a.M) * kStripGroups * kStripGroupBlocks;
     switch (a.teams) {
-        case 12: return a.M <= 8 ? launch_rows<12, 8, 2>(p, st) : launch_rows<12, 16>(p, st);
+        case 12: return a.M <= 8 ? launch_rows<12, 8>(p, st) : launch_rows<12, 16>(p, st);
         case 6: return launch_rows<6, 16>(p, st);
         case 4: return a.M <= 48 ? launch_rows<4, 16>(p, st) : launch_rows<4, 22>(p, st);
         default: return a.M <= 96 ? launch_rows<2, 16>(p, st) : launch_rows<2, 22>(p, st);

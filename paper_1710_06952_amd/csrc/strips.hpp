@@ -25,7 +25,7 @@ constexpr uint64_t kClockTicksPerUs = 100;      // the constant clock of the dev
 // A record is one iteration of the kernel: a header, two entries for each of up to teams / 2 evaluations, two for each of
 // as many loads (both in the order of their holders), then the updates.  A holder is a set of registers for the rows of one
 // gradient.  An iteration requests rows before it evaluates, so a holder may do both in one record: teams / 2 holders are
-// enough, and with as many as `teams` all rows are requested an iteration ahead.  All fields are 32-bit words.
+// enough (with as many as `teams` all rows would be requested an iteration ahead).  All fields are 32-bit words.
 //   header            updates, holders that load (bit mask), holders that evaluate (bit mask), -
 //   evaluation        holder, sequence number of the gradient, worker read, slot the gradient goes to;
 //                     slot of the pending gradient that compensates the read (or -1), its step size, the event, the
@@ -63,10 +63,9 @@ struct StripCall {
     uint32_t seq0;                       // sequence number of the first gradient
     int32_t strips;                      // blocks with a strip
 };
-// Teams of wavefronts for a minibatch of M samples, and holders: as many as their rows leave registers for (at most 22 rows
-// of a wavefront).  A record evaluates as many gradients as there are teams.
+// Teams of wavefronts (gradients whose rows are held) for a minibatch of M samples: as many as their rows leave
+// registers for (at most 22 rows of a wavefront).  A record evaluates as many gradients.
 inline int32_t strip_teams(int32_t M) { return M <= 16 ? 12 : M <= 32 ? 6 : M <= 64 ? 4 : 2; }
-inline int32_t strip_holders(int32_t M) { return M <= 8 ? 2 * strip_teams(M) : strip_teams(M); }
 // Gradients run at most this many events ahead of the first event not applied: as many as there are slots for, 64 at most
 // and T_max + 1 at least.  In LDS slots_fit slots fit (lds_state: more than T_max); in the workspace there are n_slots, which
 // may be fewer than T_max + 1 (the library uses 4096 at most): more than the largest tau of the call all the same, or there is
@@ -90,7 +89,7 @@ struct StripArgs {
     int64_t ld, d;
     int32_t n;
     int model;               // LSQ or LOGREG
-    int32_t M, teams, holders;
+    int32_t M, teams;
     const StripEntry* recs;  // device
     int32_t rec_len, iterations;
     const int32_t* idx;      // device, minibatch indices in the order of evaluation
