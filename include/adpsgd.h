@@ -293,9 +293,9 @@ typedef struct {
  * requests is host memory, valid during the call.  Return 0, or non-zero to abort the run. */
 typedef int (*adpsgd_gradient_fn)(void* user, int32_t n_requests, const adpsgd_grad_request_t* requests, void* stream);
 
-/* adpsgd_run_events for ADPSGD_MODEL_EXTERNAL (else ADPSGD_ERR_STATE): the same events, rounds and update
- * kernel, with every stale gradient obtained from fn (batch_idx of the schedule is not read: the caller
- * draws its own minibatches, e.g. from the event number).  If fn returns non-zero the call waits for the
+/* adpsgd_run_events for ADPSGD_MODEL_EXTERNAL (else ADPSGD_ERR_STATE): the same events with the same results,
+ * in the same rounds up to d = 4096 and in fewer beyond, with every stale gradient obtained from fn (batch_idx
+ * of the schedule is not read: the caller draws its own minibatches, e.g. from the event number).  If fn returns non-zero the call waits for the
  * stream and returns ADPSGD_ERR_CALLBACK; the updates of the rounds already enqueued have happened, which
  * is in general not a prefix of the serial order: restore the models before going on. */
 int adpsgd_run_events_with(adpsgd_t* h, const adpsgd_schedule_t* s, adpsgd_gradient_fn fn, void* user);

@@ -17,7 +17,7 @@ STREAM_BENCH = HERE / "stream_bench"       # stand-alone streaming microbenchmar
 SOURCES = ["api.cpp", "api_sync.cpp", "api_diag.cpp", "schedule.cpp", "planner.cpp", "strips.cpp", "kernels_fused.hip", "kernels_columns.hip",
            "kernels_strips.hip", "kernels_grad_linear.hip", "kernels_onepass.hip",
            "kernels_mlp.hip", "kernels_diag.hip", "kernels_sync.hip"]
-HEADERS = ["internal.hpp", "strips.hpp", "onepass.hpp", "exchange.hpp", "handle.hpp", "device_common.hpp"]
+HEADERS = ["internal.hpp", "strips.hpp", "onepass.hpp", "exchange.hpp", "handle.hpp", "device_common.hpp", "chains.hpp"]
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 instructions

@@ -443,11 +443,12 @@ struct EventCall {
     bool mlp_comp = false;      // perceptron, wait-free variant: compensated bf16 rows
     bool ext_comp = false;      // caller's function, wait-free variant: compensated fp32 rows
     bool factored = false;      // perceptron: dW1 stays in factored form until the update kernel
-    bool chained = false;       // perceptron: the updates of a round come in chains
-    std::vector<MlpChain> chains;           // chained: the updates, by round ...
+    int32_t chain = 1;          // updates of a round that may follow each other on a row
+    bool chained() const { return chain > 1; }
+    std::vector<UpdateChain> chains;        // chained: the updates, by round ...
     std::vector<int64_t> chain_off;         // ... and where those of a round begin
     std::vector<int64_t> chain_event;       // ... and the event of every operation, -1: averaging only
-    const MlpChain* d_chains = nullptr;
+    const UpdateChain* d_chains = nullptr;
     bool lin_factored = false;  // least squares on long models: the gradient stays M coefficients
     bool strips = false;        // linear models: all events in one launch (kernels_strips.hip)
     bool onepass = false;       // linear models: gradients in one pass over the rows (kernels_onepass.hip), dense
@@ -530,21 +531,26 @@ int prepare_call(adpsgd_t* h, const adpsgd_schedule_t* s, EventCall& c) {
     c.mlp_comp = h->o.model == ADPSGD_MODEL_MLP && comp;
     c.ext_comp = c.external && comp;
     c.factored = h->o.model == ADPSGD_MODEL_MLP && !dense && !comp && mlp_can_factor(h->o.mlp_in, h->o.mlp_hidden, c.M);
-    c.chained = h->o.model == ADPSGD_MODEL_MLP;
     c.lin_factored = with_data && !dense && !comp && linear_can_factor(h->o.model, h->d, c.M, h->o.ldx);
     // gradients pending from an earlier call come as it left them: dense vectors, or coefficients
     c.strips = with_data && can_run_strips(h) && (!any_carried || h->pending_dense);
     if (any_carried && h->pending_dense) c.lin_factored = false;
+    // Chains move a row once for several updates and make fewer rounds (caller's gradients, n = 8, d = 12 M, momentum, 60 events: 31
+    // rounds and 4.73 ms without, 19 and 3.91 with them; least squares, n = 32, M = 8, d = 4 Mi, 200 events: 33 and 10.75, 22 and
+    // 10.31; logistic, n = 64, M = 128, d = 65 536, 500 events: 36 and 4.59, 25 and 4.45).  A caller's gradients on short models keep
+    // the rounds of the synthetic model, as the interface has it (7 % in the mean of 20 such calls, which the caller's own
+    // launches bind).  A handle whose calls go in one launch keeps plain rounds for its short calls (small_call was drawn with them).
+    c.chain = h->o.model == ADPSGD_MODEL_MLP ? kMlpChain : (with_data && !c.strips) || (c.external && h->d > 4096) ? kChain : 1;
     c.onepass = with_data && onepass_for_events(h->onepass, h->o.model, c.M, comp) && can_run_onepass(h) && (!any_carried || h->pending_dense);
     if (c.onepass) c.lin_factored = false;
 
     std::string perr;
     const int rc = plan_rounds(h->n, c.K, s->worker, s->neighbour, s->tau, h->n_slots, c.with_grad, c.plan, perr,
-                               s->extra_ptr, s->extra_a, s->extra_b, comp, c.A, carried, c.chained ? kMlpChain : 1);
+                               s->extra_ptr, s->extra_a, s->extra_b, comp, c.A, carried, c.chain);
     if (rc != ADPSGD_OK) return fail(h, rc, perr);
     if ((h->o.flags & ADPSGD_FLAG_VERIFY_PLAN) &&
         !verify_plan(h->n, c.K, s->worker, s->neighbour, s->tau, h->n_slots, c.with_grad, c.plan, perr, s->extra_ptr, s->extra_a,
-                     s->extra_b, c.A, carried, c.chained))
+                     s->extra_b, c.A, carried, c.chained()))
         return fail(h, ADPSGD_ERR_STATE, perr);
 
     const int32_t R = c.plan.n_rounds;
@@ -579,15 +585,13 @@ void fill_update(adpsgd_t* h, EventCall& c, int64_t k, std::vector<int64_t>& u_f
     u.gamma = s->gamma ? s->gamma[k] : h->o.gamma;
     u.slot = c.with_grad ? c.plan.slot[k] : 0;
     u.flags = 0;
-    u.event = static_cast<int32_t>(k);
-    u.features = c.lin_factored ? h->data[u.i].features : nullptr;
-    u.feat_ld = c.lin_factored ? h->data[u.i].ld : 0;
+    u.pad = 0;
     if (s->extra_ptr)
         for (int64_t q = s->extra_ptr[k]; q < s->extra_ptr[k + 1]; ++q)
-            c.uops[u_fill[ur]++] = PairOp{s->extra_a[q], s->extra_b[q], 0u, 0u, 0.0f, 0, 1, 0, nullptr, 0};
+            c.uops[u_fill[ur]++] = PairOp{s->extra_a[q], s->extra_b[q], 0u, 0u, 0.0f, 0, 1, 0};
 }
 
-// The updates of a perceptron's call as the chains of every round.
+// The updates of a call as the chains of every round.
 int build_chains(adpsgd_t* h, EventCall& c) {
     const adpsgd_schedule_t* s = c.s;
     std::vector<ColumnPair> pairs(static_cast<size_t>(c.A + c.n_extra));
@@ -600,18 +604,18 @@ int build_chains(adpsgd_t* h, EventCall& c) {
     }
     ChainLayout layout;
     chain_rounds(pairs, c.u_off, h->n, layout);
-    if ((h->o.flags & ADPSGD_FLAG_VERIFY_PLAN) && !verify_chains(pairs, c.u_off, h->n, kMlpChain, layout))
+    if ((h->o.flags & ADPSGD_FLAG_VERIFY_PLAN) && !verify_chains(pairs, c.u_off, h->n, c.chain, layout))
         return fail(h, ADPSGD_ERR_STATE, "plan check: chains of updates out of order");
     c.chain_off = layout.round;
     c.chains.resize(layout.first.size() - 1);
     c.chain_event.resize(pairs.size());
     for (size_t t = 0; t < c.chains.size(); ++t) {
-        MlpChain& ch = c.chains[t];
-        ch = MlpChain{};
+        UpdateChain& ch = c.chains[t];
+        ch = UpdateChain{};
         ch.first = static_cast<int32_t>(layout.first[t]);
         ch.n_ops = static_cast<int32_t>(layout.first[t + 1] - layout.first[t]);
-        if (ch.n_ops > kMlpChain) return fail(h, ADPSGD_ERR_STATE, "run_events: a chain of updates is too long");
-        std::fill_n(ch.rows, kMlpChain + 1, -1);
+        if (ch.n_ops > c.chain) return fail(h, ADPSGD_ERR_STATE, "run_events: a chain of updates is too long");
+        std::fill_n(ch.rows, kChain + 1, -1);
         int32_t n_rows = 0;
         auto place = [&](int32_t row) {
             const int32_t at = static_cast<int32_t>(std::find(ch.rows, ch.rows + n_rows, row) - ch.rows);
@@ -624,10 +628,10 @@ int build_chains(adpsgd_t* h, EventCall& c) {
             const int32_t pi = place(pair.i), pj = place(pair.j);
             const WorkerData& w = h->data[pair.i];
             c.chain_event[ch.first + u] = k;
-            ch.ops[u] = MlpChainOp{w.features, w.ld, k >= 0 ? c.plan.slot[k] : 0, k < 0 ? 0.0f : s->gamma ? s->gamma[k] : h->o.gamma, pi | pj << 4, k < 0};
+            ch.ops[u] = UpdateOp{w.features, w.ld, k >= 0 ? c.plan.slot[k] : 0, k < 0 ? 0.0f : s->gamma ? s->gamma[k] : h->o.gamma, pi | pj << 4, static_cast<int32_t>(k)};
             if (k >= 0) ch.steps |= 1 << pi;
         }
-        std::fill(ch.ops + ch.n_ops, ch.ops + kMlpChain, ch.ops[ch.n_ops - 1]);
+        std::fill(ch.ops + ch.n_ops, ch.ops + kChain, ch.ops[ch.n_ops - 1]);
     }
     return ADPSGD_OK;
 }
@@ -663,11 +667,11 @@ int upload_tables(adpsgd_t* h, EventCall& c) {
     const int32_t M = c.M;
     if (c.mlp_comp) HIP_TRY(h, h->comp_rows.reserve(static_cast<size_t>(c.group) * h->o.ldx * sizeof(uint16_t)));
     if (c.ext_comp) HIP_TRY(h, h->comp_rows.reserve(static_cast<size_t>(c.group) * h->o.ldx * sizeof(float)));
-    if (c.chained) {
+    if (c.chained()) {
         const int rc = build_chains(h, c);
         if (rc != ADPSGD_OK) return rc;
     }
-    const size_t bytes_u = c.chained ? c.chains.size() * sizeof(MlpChain) : static_cast<size_t>(c.A + c.n_extra) * sizeof(PairOp);
+    const size_t bytes_u = c.chained() ? c.chains.size() * sizeof(UpdateChain) : static_cast<size_t>(c.A + c.n_extra) * sizeof(PairOp);
     const size_t bytes_r = c.with_grad ? static_cast<size_t>(K) * sizeof(GradOp) : 0;
     const size_t bytes_b = static_cast<size_t>(K) * M * sizeof(int32_t);
     const size_t off_r = bytes_u, off_b = (off_r + bytes_r + 15) & ~size_t(15);
@@ -694,7 +698,7 @@ int upload_tables(adpsgd_t* h, EventCall& c) {
         c.batch_r = reinterpret_cast<int32_t*>(stage + off_br);
         std::memset(stage + off_br, 0, bytes_br + bytes_bu);
     }
-    if (c.chained) std::memcpy(stage, c.chains.data(), bytes_u);
+    if (c.chained()) std::memcpy(stage, c.chains.data(), bytes_u);
     if (c.factored) {
         int32_t* batch_u = reinterpret_cast<int32_t*>(stage + off_bu);
         for (size_t q = 0; q < c.chain_event.size(); ++q)
@@ -702,14 +706,14 @@ int upload_tables(adpsgd_t* h, EventCall& c) {
     }
     std::vector<int64_t> u_fill(c.u_off.begin(), c.u_off.end() - 1), r_fill(c.r_off.begin(), c.r_off.end() - 1);
     for (int64_t k = 0; k < K; ++k) {
-        if (k < c.A && !c.chained) fill_update(h, c, k, u_fill);
+        if (k < c.A && !c.chained()) fill_update(h, c, k, u_fill);
         if (c.with_grad && c.plan.r_round[k] >= 0) fill_gradient(h, c, k, r_fill);
     }
     if (bytes_b > 0 && !by_op) std::memcpy(stage + off_b, s->batch_idx, bytes_b);
     HIP_TRY(h, hipMemcpyAsync(T.dev.p, T.stage.p, total, hipMemcpyHostToDevice, h->stream));
     const char* dev = static_cast<const char*>(T.dev.p);
     c.d_uops = reinterpret_cast<const PairOp*>(dev);
-    c.d_chains = reinterpret_cast<const MlpChain*>(dev);
+    c.d_chains = reinterpret_cast<const UpdateChain*>(dev);
     c.d_rops = reinterpret_cast<const GradOp*>(dev + off_r);
     c.d_batch = reinterpret_cast<const int32_t*>(dev + off_b);
     c.d_batch_r = reinterpret_cast<const int32_t*>(dev + off_br);
@@ -810,15 +814,19 @@ int launch_updates(adpsgd_t* h, const EventCall& c, int32_t r) {
     hipEvent_t e0, e1;
     int rc = begin_timing(h, e0, e1);
     if (rc != ADPSGD_OK) return rc;
+    const UpdateChain* d_chains = c.d_chains + (c.chained() ? c.chain_off[r] : 0);
+    const int32_t n_chains = c.chained() ? static_cast<int32_t>(c.chain_off[r + 1] - c.chain_off[r]) : 0;
     if (c.lin_factored) {
-        LinearApplyArgs a{h->o.X, h->o.ldx, h->d, d_ops, static_cast<int32_t>(nu), slots, c.d_batch, c.M,
+        LinearApplyArgs a{h->o.X, h->o.ldx, h->d, d_chains, n_chains, slots, c.d_batch, c.M,
                           h->streaming, h->o.V, h->o.momentum, h->o.weight_decay};
-        HIP_TRY(h, launch_linear_apply_factored(a, h->stream));
-    } else if (c.chained) {
-        MlpApplyArgs a{h->o.X, h->o.ldx, h->d, h->o.mlp_in, h->o.mlp_hidden, c.M, c.d_chains + c.chain_off[r],
-                       static_cast<int32_t>(c.chain_off[r + 1] - c.chain_off[r]), slots, h->o.Xbf16, c.d_batch_u, c.factored, h->o.V,
-                       h->o.momentum, h->o.weight_decay};
+        HIP_TRY(h, launch_linear_apply_chains(a, h->stream));
+    } else if (h->o.model == ADPSGD_MODEL_MLP) {
+        MlpApplyArgs a{h->o.X, h->o.ldx, h->d, h->o.mlp_in, h->o.mlp_hidden, c.M, d_chains, n_chains, slots, h->o.Xbf16, c.d_batch_u, c.factored,
+                       h->o.V, h->o.momentum, h->o.weight_decay};
         HIP_TRY(h, launch_mlp_apply_chains(a, h->stream));
+    } else if (c.chained()) {
+        const ChainArgs a{h->o.X, h->o.ldx, h->d, d_chains, n_chains, slots, h->streaming, h->o.V, h->o.momentum, h->o.weight_decay};
+        HIP_TRY(h, launch_gossip_chains(a, h->stream));
     } else {
         bool has_solo = false;
         for (int64_t t = c.u_off[r]; t < c.u_off[r + 1] && !has_solo; ++t) has_solo = c.uops[t].i == c.uops[t].j;

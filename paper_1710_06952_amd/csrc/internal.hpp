@@ -21,9 +21,25 @@ struct alignas(32) PairOp {
     float gamma;
     int32_t slot;     // pending-gradient slot holding g_k (data models)
     int32_t flags;    // bit 0: average only (an extra pair of a general W_k): no gradient, no step
-    int32_t event;    // index into the call's batch_idx array (least squares, factored gradient)
-    const void* features;   // worker i's inputs (least squares, factored gradient), else nullptr
+    int32_t pad;
+};
+
+// Updates of a round that share rows, executed one after the other (chain_rounds).
+constexpr int kChain = 4;               // operations of a chain, at most; they touch one row more
+constexpr int kMlpChain = 3;            // ... of the perceptron
+struct UpdateOp {
+    const void* features;               // worker i's inputs (average only: any worker's, read and dropped), or nullptr
     int64_t feat_ld;
+    int32_t slot;
+    float gamma;
+    int32_t places;                     // of rows i and j (bits 4 and up) in the chain's rows
+    int32_t event;                      // index into the call's arrays; -1: an extra pair of a general W_k, no gradient, no step
+};
+struct alignas(32) UpdateChain {
+    int32_t first, n_ops;               // position of the first operation in the order of the chains
+    int32_t rows[kChain + 1];           // -1: none
+    int32_t steps;                      // places whose row takes a gradient step (bits): their momentum is read and written
+    UpdateOp ops[kChain];               // beyond n_ops: the last one again (its operands may be requested, and dropped)
 };
 
 // One stale read / gradient evaluation as the gradient kernels see it.
@@ -119,6 +135,19 @@ struct FusedArgs {
 };
 hipError_t launch_fused_gossip_apply(const FusedArgs& a, hipStream_t st);
 
+// The updates of a round with dense gradients, in chains.
+struct ChainArgs {
+    float* X;
+    int64_t ld, d;
+    const UpdateChain* chains;      // device
+    int32_t n_chains;
+    const float* slots;
+    bool streaming;         // X does not fit the caches
+    float* V;               // momentum buffers or nullptr
+    float momentum, weight_decay;
+};
+hipError_t launch_gossip_chains(const ChainArgs& a, hipStream_t st);
+
 struct ColumnArgs {
     float* X;
     float* V;               // momentum buffers or nullptr
@@ -180,13 +209,13 @@ struct LinearGradArgs {
 int64_t linear_grad_chunks(int64_t d);
 bool linear_can_factor(int model, int64_t d, int32_t M, int64_t ld);
 
-// The update of a round with the least-squares gradients still in factored form (see the kernel).
+// The updates of a round with the least-squares gradients still in factored form (see the kernel).
 struct LinearApplyArgs {
     float* X;
     int64_t ld;
     int64_t d;
-    const PairOp* ops;      // device; features / feat_ld / event / slot name the factors
-    int32_t n_ops;
+    const UpdateChain* chains;      // device; features / feat_ld / event / slot name the factors
+    int32_t n_chains;
     const float* slots;
     const int32_t* batch_idx;
     int32_t M;
@@ -194,7 +223,7 @@ struct LinearApplyArgs {
     float* V;               // momentum buffers or nullptr
     float momentum, weight_decay;
 };
-hipError_t launch_linear_apply_factored(const LinearApplyArgs& a, hipStream_t st);
+hipError_t launch_linear_apply_chains(const LinearApplyArgs& a, hipStream_t st);
 hipError_t launch_linear_gradient(const LinearGradArgs& a, hipStream_t st, int* n_launches);
 
 struct MlpGradArgs {
@@ -223,29 +252,12 @@ bool mlp_can_factor(int32_t in, int32_t hid, int32_t M);
 // The perceptron's model update, with the first-layer gradient still in factored form where that is possible
 // (dW1 = Xb^T dH, rank <= M): the product is formed tile by tile on the matrix cores inside
 // the update kernel instead of being written to and read back from the pending slot.
-// The updates of a round come in chains of operations that share rows (chain_rounds).
-constexpr int kMlpChain = 3;            // operations of a chain, at most; they touch one row more
-struct MlpChainOp {
-    const void* features;               // worker i's inputs (average only: any worker's, read and dropped)
-    int64_t feat_ld;
-    int32_t slot;
-    float gamma;
-    int32_t places;                     // of rows i and j (bits 4 and up) in the chain's rows
-    int32_t average;                    // an extra pair of a general W_k: no gradient, no step
-};
-struct alignas(32) MlpChain {
-    int32_t first, n_ops;               // row of the first operation in the table of minibatch indices
-    int32_t rows[kMlpChain + 1];        // -1: none
-    int32_t steps;                      // places whose row takes a gradient step (bits): their momentum is read and written
-    int32_t pad;
-    MlpChainOp ops[kMlpChain];          // beyond n_ops: the last one again (its operands are requested, and dropped)
-};
 struct MlpApplyArgs {
     float* X;
     int64_t ld;
     int64_t d;
     int32_t in, hid, M;
-    const MlpChain* chains; // device
+    const UpdateChain* chains; // device
     int32_t n_chains;
     const float* slots;
     uint16_t* Xbf16;

@@ -12,6 +12,7 @@
 // bytes (one dword per lane) and every lane keeps 4 loads per row in flight;
 // this sustains 6.4 TB/s, against 5.8 TB/s for 128-bit accesses of any unroll
 // and 5.3-5.9 TB/s for deeper or shallower unrolls of the dword shape.
+#include "chains.hpp"
 #include "device_common.hpp"
 #include "internal.hpp"
 
@@ -114,6 +115,50 @@ __global__ __launch_bounds__(kThreads) void fused_gossip_apply_kernel(const Fuse
     }
 }
 
+struct ChainParams {
+    float* X;
+    int64_t ld, d;
+    const UpdateChain* chains;
+    const float* slots;
+    float* V;
+    float momentum, weight_decay;
+};
+
+// The same update for chains of operations that share rows, with gradients from the slots: 16 (24) bytes per parameter and
+// *row* instead of per event, and fewer rounds, each of which has to wait for its gradients.
+// grid = (ceil(d / 1024), chains of the round); pass u of thread t touches element 1024 blockIdx.x + 256 u + t of all rows.
+template <bool STREAM, bool MOM>
+__global__ __launch_bounds__(kThreads) void gossip_chains_kernel(const ChainParams p) {
+    constexpr int kPlaces = kChain + 1, kPitch = 4 * kThreads;
+    const UpdateChain chain = chain_at(p.chains + blockIdx.y);
+    const int64_t tile = static_cast<int64_t>(blockIdx.x) * kTileElems, left = p.d - tile;
+    const int bytes = left < kTileElems ? 4 * static_cast<int>(left) : 4 * static_cast<int>(kTileElems), offset = 4 * threadIdx.x;
+    ChainRows<MOM, kPlaces, 1> c;
+#pragma unroll
+    for (int q = 0; q < kPlaces; ++q) {        // entries at and beyond d are never touched: they stay zero
+        const int64_t at = static_cast<int64_t>(max(chain.rows[q], 0)) * p.ld + tile;
+        c.x[q][0] = buffer_gather4<STREAM>(buffer_of(p.X + at, chain.rows[q] >= 0 ? bytes : 0), offset, kPitch);
+        if constexpr (MOM) c.v[q][0] = buffer_gather4<STREAM>(buffer_of(p.V + at, (chain.steps >> q & 1) != 0 ? bytes : 0), offset, kPitch);
+    }
+    v4f g[kChain][1];
+#pragma unroll
+    for (int u = 0; u < kChain; ++u)
+        g[u][0] = buffer_gather4<STREAM>(buffer_of(p.slots + static_cast<int64_t>(chain.ops[u].slot) * p.ld + tile,
+                                                   u < chain.n_ops && chain.ops[u].event >= 0 ? bytes : 0), offset, kPitch);
+#pragma unroll
+    for (int u = 0; u < kChain; ++u)
+        if (u == 0 || u < chain.n_ops) c.update(chain.ops[u], p.momentum, p.weight_decay, g[u]);
+#pragma unroll
+    for (int q = 0; q < kPlaces; ++q) {
+        if (chain.rows[q] < 0) continue;
+        const int64_t at = static_cast<int64_t>(chain.rows[q]) * p.ld + tile;
+        buffer_scatter4<STREAM>(buffer_of(p.X + at, bytes), offset, kPitch, c.x[q][0]);
+        if constexpr (MOM) {
+            if ((chain.steps >> q & 1) != 0) buffer_scatter4<STREAM>(buffer_of(p.V + at, bytes), offset, kPitch, c.v[q][0]);
+        }
+    }
+}
+
 __global__ __launch_bounds__(kThreads) void synth_gradient_kernel(float* out, int64_t d, SynthScale scale, uint32_t k_lo,
                                                                   uint32_t k_hi, uint32_t key0, uint32_t key1) {
     const int64_t v = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
@@ -162,6 +207,19 @@ hipError_t launch_fused_gossip_apply(const FusedArgs& a, hipStream_t st) {
     const dim3 grid(static_cast<uint32_t>(tiles), static_cast<uint32_t>(a.n_ops));
     if (a.synth) return launch_variant<true>(p, grid, a.streaming, a.has_solo, st);
     return launch_variant<false>(p, grid, a.streaming, a.has_solo, st);
+}
+
+hipError_t launch_gossip_chains(const ChainArgs& a, hipStream_t st) {
+    if (a.n_chains <= 0) return hipSuccess;
+    const ChainParams p{a.X, a.ld, a.d, a.chains, a.slots, a.V, a.momentum, a.weight_decay};
+    const int64_t tiles = (p.d + kTileElems - 1) / kTileElems;
+    if (tiles > 0x7FFFFFFF || a.n_chains > 65535) return hipErrorInvalidValue;
+    const dim3 grid(static_cast<uint32_t>(tiles), static_cast<uint32_t>(a.n_chains));
+    if (a.streaming && a.V) hipLaunchKernelGGL((gossip_chains_kernel<true, true>), grid, dim3(kThreads), 0, st, p);
+    else if (a.streaming) hipLaunchKernelGGL((gossip_chains_kernel<true, false>), grid, dim3(kThreads), 0, st, p);
+    else if (a.V) hipLaunchKernelGGL((gossip_chains_kernel<false, true>), grid, dim3(kThreads), 0, st, p);
+    else hipLaunchKernelGGL((gossip_chains_kernel<false, false>), grid, dim3(kThreads), 0, st, p);
+    return hipGetLastError();
 }
 
 hipError_t launch_synth_gradient(uint64_t seed, uint64_t k, float std, int64_t d, float* out, hipStream_t st) {

@@ -20,6 +20,7 @@
 // exchange words one pass took 167 us for two gradients against 23.  Short models
 // (d <= 2048) take the single-block kernel at the end of this file.  Partial sums
 // are combined in a fixed order: results do not depend on scheduling.
+#include "chains.hpp"
 #include "device_common.hpp"
 #include "internal.hpp"
 
@@ -227,13 +228,14 @@ __global__ __launch_bounds__(kThreads) void linear_combine_kernel(const LinParam
 // The gradient of a linear model is a combination of its M minibatch rows, so the pending slot keeps
 // the M coefficients and the rows are read when the event is applied: the dense gradient is never
 // written to memory and read back (8 B per parameter and event less, and one launch per round less).
-// grid = (ceil(n_vec / kThreads), events of the round)
+// A block executes a chain of updates that share rows.
+// grid = (ceil(n_vec / kThreads), chains of the round)
 struct LinApplyParams {
     float* X;
     int64_t ld;
     int64_t d;
     int64_t n_vec;
-    const PairOp* ops;
+    const UpdateChain* chains;
     const float* slots;
     const int32_t* batch_idx;
     int32_t M;
@@ -242,45 +244,47 @@ struct LinApplyParams {
 };
 
 template <bool STREAM_ROWS, bool STREAM_X, bool MOM>
-__global__ __launch_bounds__(kThreads) void linear_apply_factored_kernel(const LinApplyParams p) {
-    const PairOp op = p.ops[blockIdx.y];
-    const int64_t v = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+__global__ __launch_bounds__(kThreads) void linear_apply_chains_kernel(const LinApplyParams p) {
+    constexpr int kPlaces = kChain + 1;
+    const UpdateChain chain = chain_at(p.chains + blockIdx.y);
+    const int64_t v0 = static_cast<int64_t>(blockIdx.x) * kThreads, v = v0 + threadIdx.x;
     if (v >= p.n_vec) return;
-    float* __restrict__ xi = p.X + static_cast<int64_t>(op.i) * p.ld + 4 * v;
-    float* __restrict__ xj = p.X + static_cast<int64_t>(op.j) * p.ld + 4 * v;
-    const v4f a = load4<STREAM_X>(xi), b = load4<STREAM_X>(xj);
-    const bool average_only = (op.flags & 1) != 0;      // extra pair of a general W_k: no gradient, no step
-    v4f g = {0, 0, 0, 0};
-    if (!average_only)
-        g = zero_beyond(combine_rows<STREAM_ROWS>(static_cast<const float*>(op.features), op.feat_ld,
-                                                  p.batch_idx + static_cast<int64_t>(op.event) * p.M,
-                                                  p.slots + static_cast<int64_t>(op.slot) * p.ld, p.M, v), 4 * v, p.d);
-    const float gamma = average_only ? 0.0f : op.gamma;
-    const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w}, gv[4] = {g.x, g.y, g.z, g.w};
-    float ni[4], nj[4];
-    if (MOM && !average_only) {       // an averaging-only pair leaves the momentum buffers alone
-        float* __restrict__ vi = p.V + static_cast<int64_t>(op.i) * p.ld + 4 * v;
-        const v4f vo = load4<STREAM_X>(vi);
-        const float vold[4] = {vo.x, vo.y, vo.z, vo.w};
-        float vn[4];
+    const int bytes = 16 * static_cast<int>(p.n_vec - v0 < kThreads ? p.n_vec - v0 : kThreads), offset = 16 * threadIdx.x;
+    ChainRows<MOM, kPlaces, 1> c;
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-            average_then_apply_momentum(av[c], bv[c], gv[c], vold[c], gamma, p.momentum, p.weight_decay, ni[c], nj[c], vn[c]);
-        store4<STREAM_X>(vi, v4f{vn[0], vn[1], vn[2], vn[3]});   // zero in the padding, as x and g are
-    } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) average_then_apply(av[c], bv[c], gv[c], gamma, ni[c], nj[c]);
+    for (int q = 0; q < kPlaces; ++q) {
+        const int64_t at = static_cast<int64_t>(max(chain.rows[q], 0)) * p.ld + 4 * v0;
+        c.x[q][0] = buffer_load4<STREAM_X>(buffer_of(p.X + at, chain.rows[q] >= 0 ? bytes : 0), offset);
+        if constexpr (MOM) c.v[q][0] = buffer_load4<STREAM_X>(buffer_of(p.V + at, (chain.steps >> q & 1) != 0 ? bytes : 0), offset);
     }
-    store4<STREAM_X>(xi, v4f{ni[0], ni[1], ni[2], ni[3]});     // the padding beyond d stays zero: g is zero there
-    if (op.i != op.j) store4<STREAM_X>(xj, v4f{nj[0], nj[1], nj[2], nj[3]});
+#pragma unroll
+    for (int u = 0; u < kChain; ++u) {
+        if (u > 0 && u >= chain.n_ops) break;
+        const UpdateOp& op = chain.ops[u];
+        v4f g[1] = {{0, 0, 0, 0}};
+        if (op.event >= 0)
+            g[0] = zero_beyond(combine_rows<STREAM_ROWS>(static_cast<const float*>(op.features), op.feat_ld,
+                                                         p.batch_idx + static_cast<int64_t>(op.event) * p.M,
+                                                         p.slots + static_cast<int64_t>(op.slot) * p.ld, p.M, v), 4 * v, p.d);
+        c.update(op, p.momentum, p.weight_decay, g);
+    }
+#pragma unroll
+    for (int q = 0; q < kPlaces; ++q) {       // the padding beyond d stays zero: g is zero there
+        if (chain.rows[q] < 0) continue;
+        const int64_t at = static_cast<int64_t>(chain.rows[q]) * p.ld + 4 * v;
+        store4<STREAM_X>(p.X + at, c.x[q][0]);
+        if constexpr (MOM) {
+            if ((chain.steps >> q & 1) != 0) store4<STREAM_X>(p.V + at, c.v[q][0]);
+        }
+    }
 }
 
 template <bool MOM>
 hipError_t launch_apply_variant(const LinApplyParams& p, dim3 grid, bool stream_rows, bool stream_x, hipStream_t st) {
-    if (stream_rows && stream_x) hipLaunchKernelGGL((linear_apply_factored_kernel<true, true, MOM>), grid, dim3(kThreads), 0, st, p);
-    else if (stream_rows) hipLaunchKernelGGL((linear_apply_factored_kernel<true, false, MOM>), grid, dim3(kThreads), 0, st, p);
-    else if (stream_x) hipLaunchKernelGGL((linear_apply_factored_kernel<false, true, MOM>), grid, dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((linear_apply_factored_kernel<false, false, MOM>), grid, dim3(kThreads), 0, st, p);
+    if (stream_rows && stream_x) hipLaunchKernelGGL((linear_apply_chains_kernel<true, true, MOM>), grid, dim3(kThreads), 0, st, p);
+    else if (stream_rows) hipLaunchKernelGGL((linear_apply_chains_kernel<true, false, MOM>), grid, dim3(kThreads), 0, st, p);
+    else if (stream_x) hipLaunchKernelGGL((linear_apply_chains_kernel<false, true, MOM>), grid, dim3(kThreads), 0, st, p);
+    else hipLaunchKernelGGL((linear_apply_chains_kernel<false, false, MOM>), grid, dim3(kThreads), 0, st, p);
     return hipGetLastError();
 }
 
@@ -403,14 +407,14 @@ bool linear_can_factor(int model, int64_t d, int32_t M, int64_t ld) {
     return model == ADPSGD_MODEL_LSQ && d > kSmallMaxD && M >= 1 && M <= ld;
 }
 
-hipError_t launch_linear_apply_factored(const LinearApplyArgs& a, hipStream_t st) {
-    if (a.n_ops <= 0) return hipSuccess;
+hipError_t launch_linear_apply_chains(const LinearApplyArgs& a, hipStream_t st) {
+    if (a.n_chains <= 0) return hipSuccess;
     LinApplyParams p;
     p.X = a.X;
     p.ld = a.ld;
     p.d = a.d;
     p.n_vec = (a.d + 3) / 4;
-    p.ops = a.ops;
+    p.chains = a.chains;
     p.slots = a.slots;
     p.batch_idx = a.batch_idx;
     p.M = a.M;
@@ -418,8 +422,8 @@ hipError_t launch_linear_apply_factored(const LinearApplyArgs& a, hipStream_t st
     p.momentum = a.momentum;
     p.weight_decay = a.weight_decay;
     const int64_t blocks = (p.n_vec + kThreads - 1) / kThreads;
-    if (blocks > 0x7FFFFFFF || a.n_ops > 65535) return hipErrorInvalidValue;
-    const dim3 grid(static_cast<uint32_t>(blocks), a.n_ops);
+    if (blocks > 0x7FFFFFFF || a.n_chains > 65535) return hipErrorInvalidValue;
+    const dim3 grid(static_cast<uint32_t>(blocks), a.n_chains);
     const bool stream_rows = static_cast<int64_t>(a.M) * a.d * 4 > (8ll << 20);
     return a.V ? launch_apply_variant<true>(p, grid, stream_rows, a.streaming, st)
                : launch_apply_variant<false>(p, grid, stream_rows, a.streaming, st);

@@ -19,6 +19,7 @@
 // model.  The kernels of a round form a serial chain of small grids, so each one
 // keeps all its global loads in flight at once instead of looping over them.  Every
 // reduction has a fixed order: results do not depend on scheduling.
+#include "chains.hpp"
 #include "device_common.hpp"
 #include "internal.hpp"
 
@@ -541,7 +542,7 @@ struct MlpApplyParams {
     int64_t ld;
     int64_t d;
     int in, hid, M;
-    const MlpChain* chains;
+    const UpdateChain* chains;
     const float* slots;
     uint16_t* Xbf16;
     const int32_t* batch_by_op;   // [op][M]
@@ -554,88 +555,12 @@ struct MlpApplyParams {
 constexpr int kApplyRows = 32;              // inputs of a tile
 constexpr int kPlaces = kMlpChain + 1;      // rows of a chain
 
-typedef __amdgpu_buffer_rsrc_t Buffer;
-// `bytes` bytes from p on: what lies beyond reads as zero and touches no memory
-__device__ __forceinline__ Buffer buffer_of(const float* p, int bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, bytes, 0x00027000);
-}
-__device__ __forceinline__ v4f buffer_load4(Buffer b, int offset) {
-    const v4u w = __builtin_amdgcn_raw_buffer_load_b128(b, offset, 0, 0);
-    return v4f{__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z), __uint_as_float(w.w)};
-}
-
-// A chain, all of it by scalar loads at once: no later load waits for a part of it.
-__device__ __forceinline__ MlpChain chain_at(const MlpChain* p) {
-    typedef uint32_t v8u __attribute__((ext_vector_type(8)));
-    typedef const v8u __attribute__((address_space(4))) * Constant;
-    struct Words {
-        v8u w[sizeof(MlpChain) / sizeof(v8u)];
-    } words;
-    static_assert(sizeof(Words) == sizeof(MlpChain), "a chain is whole vectors");
-    const Constant q = (Constant) reinterpret_cast<uintptr_t>(p);
-#pragma unroll
-    for (size_t i = 0; i < sizeof(MlpChain) / sizeof(v8u); ++i) words.w[i] = q[i];
-    return __builtin_bit_cast(MlpChain, words);
-}
-
-// The entries a thread holds of a chain's rows (and of their momentum buffers): kN pieces of four.
-template <bool MOM, int kN>
-struct ChainRows {
-    v4f x[kPlaces][kN], v[MOM ? kPlaces : 1][kN];
-
-    // masks of a place, the same for the whole block, in vector registers
-    struct Place {
-        uint32_t is[kPlaces];
-        __device__ __forceinline__ explicit Place(int place) {
-#pragma unroll
-            for (int q = 0; q < kPlaces; ++q) is[q] = in_vector(place == q ? 0xFFFFFFFFu : 0u);
-        }
-    };
-    // bit operations and no selects: of these the compiler makes a select of addresses, and with it the rows leave the registers
-    static __device__ __forceinline__ v4f pick4(uint32_t mask, v4f a, v4f b) { return v4f{pick(mask, a.x, b.x), pick(mask, a.y, b.y), pick(mask, a.z, b.z), pick(mask, a.w, b.w)}; }
-    static __device__ __forceinline__ v4f at(const v4f (&a)[kPlaces][kN], const Place& place, int r) {
-        v4f w = a[0][r];
-#pragma unroll
-        for (int q = 1; q < kPlaces; ++q) w = pick4(place.is[q], a[q][r], w);
-        return w;
-    }
-    static __device__ __forceinline__ void put(v4f (&a)[kPlaces][kN], const Place& place, int r, v4f w) {
-#pragma unroll
-        for (int q = 0; q < kPlaces; ++q) a[q][r] = pick4(place.is[q], w, a[q][r]);
-    }
-
-    __device__ __forceinline__ void update(const MlpApplyParams& p, const MlpChainOp& op, const v4f (&gr)[kN]) {
-        const Place pi(op.places & 15), pj(op.places >> 4);
-        const uint32_t step = in_vector(op.average == 0 ? 0xFFFFFFFFu : 0u);
-#pragma unroll
-        for (int r = 0; r < kN; ++r) {
-            const v4f a = at(x, pi, r), b = at(x, pj, r), g = gr[r];
-            const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w}, gv[4] = {g.x, g.y, g.z, g.w};
-            float ni[4], nj[4];
-            if constexpr (MOM) {
-                const v4f o = at(v, pi, r);
-                const float vo[4] = {o.x, o.y, o.z, o.w};
-                float vn[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) average_then_apply_momentum(av[c], bv[c], gv[c], vo[c], op.gamma, p.momentum, p.weight_decay, ni[c], nj[c], vn[c]);
-                put(v, pi, r, pick4(step, v4f{vn[0], vn[1], vn[2], vn[3]}, o));
-            } else {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) average_then_apply(av[c], bv[c], gv[c], op.gamma, ni[c], nj[c]);
-            }
-            const v4f to_j = {nj[0], nj[1], nj[2], nj[3]};
-            put(x, pj, r, to_j);              // before x^i: without a partner (i == j) the step stands
-            put(x, pi, r, pick4(step, v4f{ni[0], ni[1], ni[2], ni[3]}, to_j));
-        }
-    }
-};
-
 template <bool MOM>
 __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyParams p) {
     __shared__ __attribute__((aligned(16))) uint16_t At[kApplyRows][72];   // inputs transposed:  [i][m], 64 m + pad
     __shared__ __attribute__((aligned(16))) uint16_t Bt[64][72];           // hidden error transposed: [h][m]
     __shared__ __attribute__((aligned(16))) float Gs[kApplyRows][68];      // the tile of g, [input][hidden]
-    const MlpChain chain = chain_at(p.chains + blockIdx.z);
+    const UpdateChain chain = chain_at(p.chains + blockIdx.z);
     const int n_ops = chain.n_ops;
     if (static_cast<int>(blockIdx.y) >= p.in_tiles) {
         // elementwise, with dense gradients from the slots
@@ -643,20 +568,20 @@ __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyP
         const int64_t e = from + 4 * threadIdx.x, left = (p.d + 3) / 4 * 4 - from;       // rows are padded to whole vectors
         if (e >= p.d) return;
         const int bytes = left < 4 * kT ? 4 * static_cast<int>(left) : 16 * kT, offset = 16 * threadIdx.x;
-        ChainRows<MOM, 1> c;
+        ChainRows<MOM, kPlaces, 1> c;
 #pragma unroll
         for (int q = 0; q < kPlaces; ++q) {
             const int64_t at = static_cast<int64_t>(max(chain.rows[q], 0)) * p.ld + from;
-            c.x[q][0] = buffer_load4(buffer_of(p.X + at, chain.rows[q] >= 0 ? bytes : 0), offset);
-            if constexpr (MOM) c.v[q][0] = buffer_load4(buffer_of(p.V + at, (chain.steps >> q & 1) != 0 ? bytes : 0), offset);
+            c.x[q][0] = buffer_load4<false>(buffer_of(p.X + at, chain.rows[q] >= 0 ? bytes : 0), offset);
+            if constexpr (MOM) c.v[q][0] = buffer_load4<false>(buffer_of(p.V + at, (chain.steps >> q & 1) != 0 ? bytes : 0), offset);
         }
         v4f g[kMlpChain][1];
 #pragma unroll
         for (int u = 0; u < kMlpChain; ++u)
-            g[u][0] = buffer_load4(buffer_of(p.slots + static_cast<int64_t>(chain.ops[u].slot) * p.ld + from, u < n_ops ? bytes : 0), offset);
+            g[u][0] = buffer_load4<false>(buffer_of(p.slots + static_cast<int64_t>(chain.ops[u].slot) * p.ld + from, u < n_ops ? bytes : 0), offset);
 #pragma unroll
         for (int u = 0; u < kMlpChain; ++u)
-            if (u == 0 || u < n_ops) c.update(p, chain.ops[u], g[u]);
+            if (u == 0 || u < n_ops) c.update(chain.ops[u], p.momentum, p.weight_decay, g[u]);
 #pragma unroll
         for (int q = 0; q < kPlaces; ++q) {
             if (chain.rows[q] < 0) continue;
@@ -693,12 +618,12 @@ __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyP
         v8h x, d[2];
     };
     Factors f;
-    auto request_error = [&](const MlpChainOp& op) {
+    auto request_error = [&](const UpdateOp& op) {
         const uint16_t* const dH = reinterpret_cast<const uint16_t*>(p.slots + static_cast<int64_t>(op.slot) * p.ld);
 #pragma unroll
         for (int half = 0; half < 2; ++half) f.d[half] = *reinterpret_cast<const v8h*>(dH + static_cast<int64_t>(m) * p.hid + h0 + 16 * part + 8 * half);
     };
-    auto request_inputs = [&](const MlpChainOp& op, int32_t row) {
+    auto request_inputs = [&](const UpdateOp& op, int32_t row) {
         f.x = *reinterpret_cast<const v8h*>(static_cast<const uint16_t*>(op.features) + static_cast<int64_t>(row) * op.feat_ld + c_in);
     };
     // indices first: loads return in order, and the inputs wait for them
@@ -706,7 +631,7 @@ __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyP
     int32_t row_next = index[static_cast<int64_t>(min(1, n_ops - 1)) * p.M];
     request_error(chain.ops[0]);
     __builtin_amdgcn_sched_barrier(0);
-    ChainRows<MOM, 2> c;
+    ChainRows<MOM, kPlaces, 2> c;
     const int64_t corner = static_cast<int64_t>(i0) * p.hid + h0;
     const int bytes = 4 * (min(kApplyRows, p.in - i0) * p.hid - h0), offset = 4 * (rr * p.hid + hq), pitch = 64 * p.hid;
 #pragma unroll
@@ -714,11 +639,11 @@ __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyP
         const int64_t at = static_cast<int64_t>(max(chain.rows[q], 0)) * p.ld + corner;
         const Buffer x = buffer_of(p.X + at, chain.rows[q] >= 0 ? bytes : 0);
 #pragma unroll
-        for (int r = 0; r < 2; ++r) c.x[q][r] = buffer_load4(x, offset + r * pitch);
+        for (int r = 0; r < 2; ++r) c.x[q][r] = buffer_load4<false>(x, offset + r * pitch);
         if constexpr (MOM) {
             const Buffer v = buffer_of(p.V + at, (chain.steps >> q & 1) != 0 ? bytes : 0);
 #pragma unroll
-            for (int r = 0; r < 2; ++r) c.v[q][r] = buffer_load4(v, offset + r * pitch);
+            for (int r = 0; r < 2; ++r) c.v[q][r] = buffer_load4<false>(v, offset + r * pitch);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -727,7 +652,7 @@ __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyP
 #pragma unroll
     for (int u = 0; u < kMlpChain; ++u) {
         if (u > 0 && u >= n_ops) break;       // the same for the whole block; a chain has one at least
-        const MlpChainOp& op = chain.ops[u];
+        const UpdateOp& op = chain.ops[u];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             At[8 * part + e][m] = live ? f.x[e] : static_cast<uint16_t>(0);
@@ -753,7 +678,7 @@ __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyP
             for (int k = 0; k < 4; ++k) Gs[16 * it + 4 * (lane >> 4) + k][16 * wave + li] = acc[it][k];
         __syncthreads();
         const v4f g[2] = {*reinterpret_cast<const v4f*>(&Gs[rr][hq]), *reinterpret_cast<const v4f*>(&Gs[16 + rr][hq])};
-        c.update(p, op, g);
+        c.update(op, p.momentum, p.weight_decay, g);
     }
 #pragma unroll
     for (int q = 0; q < kPlaces; ++q) {

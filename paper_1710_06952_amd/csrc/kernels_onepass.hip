@@ -25,6 +25,7 @@
 // pending slots and losses are written, and each by the block that owns it.
 #include <algorithm>
 
+#include "chains.hpp"
 #include "device_common.hpp"
 #include "exchange.hpp"
 #include "onepass.hpp"
@@ -40,17 +41,7 @@ struct OnePassParams {
     int32_t pitch;               // words of a group: [samples][strips] sums, [samples] coefficients, [samples] losses
 };
 
-typedef __amdgpu_buffer_rsrc_t Buffer;
-// `bytes` bytes from p on; words read beyond are zero and touch no memory (checked per word, also of a 128-bit load), so what
-// lies beyond d in a padded row and rows beyond M need no masks
-__device__ __forceinline__ Buffer buffer_of(const float* p, int bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, bytes, 0x00027000);
-}
-template <bool kStream>
-__device__ __forceinline__ v4f buffer_load4(Buffer b, int offset) {
-    const v4u w = __builtin_amdgcn_raw_buffer_load_b128(b, offset, 0, kStream ? 2 : 0);
-    return v4f{__uint_as_float(w.x), __uint_as_float(w.y), __uint_as_float(w.z), __uint_as_float(w.w)};
-}
+// Buffers (chains.hpp) check every word, also of a 128-bit load: what lies beyond d in a padded row and rows beyond M need no masks.
 __device__ __forceinline__ float dot4(v4f a, v4f b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
 __device__ __forceinline__ v4f zero_beyond(v4f v, int64_t e, int64_t d) {
     if (e >= d) v.x = 0.0f;
