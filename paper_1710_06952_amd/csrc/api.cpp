@@ -108,31 +108,55 @@ int drain_profile(adpsgd_t* h) {
 namespace {
 
 // Workers up to which the one-launch path of the linear models (kernels_strips.hip) is the faster one.  An iteration of the
-// strip kernel evaluates as many gradients as there are teams at most, so its time per event jumps with the number of teams (M = 16, 32, 64)
-// and does not fall with n, while the kernels of a round, of n / 4 events on a ring and n / 5 or n / 6 on denser graphs, take
-// its gradients side by side.  Measured, rounds over strips for a call of 12 n events (the lesser of a call alone and one of
-// several; least squares and logistic regression, momentum, T_max 0 ... 40; the least and the most of them):
+// strip kernel evaluates as many gradients as there are teams at most (12, 6, 4 and 2 up to M = 16, 32, 64 and 128), so its time
+// per event jumps with their number and does not fall with n, while the kernels of a round take its gradients side by side.
+// Measured, rounds over strips for a call of 12 n or 400 events (800 set-ups on both sides of the lines: both models, momentum,
+// wait-free, losses, T_max 0 ... 40):
 //                        ring                                              random 4-regular graph
-//   d = 64    M <= 16    n = 16 1.15 ... 1.50, n = 28 0.76 ... 1.00        n = 24 1.02 ... 1.26, n = 40 0.73 ... 0.88
-//   d = 1024  M <= 16    n = 20 1.15 ... 1.58, n = 32 0.76 ... 1.02        n = 32 1.26 ... 1.67, n = 56 0.78 ... 0.99
-//   d = 4096  M = 8      n = 40 1.49 ... 1.82, n = 72 0.82 ... 1.09        n = 64 1.50 ... 1.62, n = 100 0.66 ... 0.93
-//   d = 4096  M = 32     n = 28 1.29 ... 1.58, n = 48 0.75 ... 0.89        n = 48 1.21 ... 1.39
-//   d = 8192  M = 32     n = 20 1.17 ... 1.54, n = 28 0.90 ... 1.17        n = 48 0.98 ... 1.00
-// (drawn when an iteration evaluated half as many and the rounds read their rows twice; both are up to twice as fast now).
-// A direct exchange between 17 to 32 strips (d = 8192) is the slowest for its size.  The line keeps below the first loss of
-// any of them; beyond it the strips would still win in places (n = 32, M = 64: d = 4096 2356 / 3515 us a call;  n = 16,
-// M = 128, d = 20 000 6115 / 7528;  n = 32, M = 48, d = 1024 1218 / 1505) and lose near by (n = 16, M = 128, d = 300 2986 /
-// 2800;  n = 1600, M = 1, d = 4096 10 200 / 1180).  Models and slots that do not fit LDS cost more than the table says.
-int32_t strip_workers(int64_t d, int32_t M, bool ring, bool lds_state) {
+//   d = 300   M <= 8     n = 17 ... 28 1.3 ... 1.8, n = 30 1.14            n = 27 ... 36 1.3 ... 1.7, n = 40 0.98
+//   d = 2000  M <= 8     n = 22 ... 36 1.1 ... 1.8, n = 38 0.92            n = 34 ... 46 1.1 ... 1.5 (n = 41 0.93), n = 59 0.50
+//   d = 4096  M <= 8     n = 33 ... 73 1.3 ... 2.3, n = 79 1.01            n = 35 ... 77 1.4 ... 2.7
+//   d = 8192  M <= 8     n = 31 ... 58 1.4 ... 2.3, n = 54 1.06            n = 38 ... 78 1.4 ... 2.0, n = 90 0.76
+//   d > 8192  M <= 8     n = 30 ... 45 1.2 ... 2.5, n = 60 1.14            n = 37 ... 56 1.4 ... 2.1, n = 83 1.40, n = 100 0.92
+//   d = 8192  M <= 16    n = 19, 29 1.35; T_max >= 8: n = 28 0.65          n = 25 ... 34 1.2 ... 1.3, n = 56 0.77 ... 0.86; T_max >= 8: n = 33 0.79
+//   d = 4096  M <= 32    n = 21 ... 25 1.06 ... 1.3; T_max = 40: 0.7        n = 25 1.32, n = 33 0.88, n = 40 0.63
+//   d = 8192  M <= 32    n = 13 1.08 ... 1.3, n = 15 0.5 ... 0.9, n = 20 0.45    n = 16 1.09, n = 22 0.66, n = 34 0.45
+//   d > 8192  M <= 32    n = 22 1.1 ... 1.4, n = 25 ... 28 0.83 ... 1.37  n = 29 1.22, n = 41 0.93
+//   d = 4096  M <= 64    T_max = 40: n = 15 0.66                           n = 13 1.21; T_max = 40: n = 22 0.62
+//   d = 8192  M <= 64    n = 6 0.8 ... 1.3, n = 11 0.40 ... 0.84           n = 6 1.28, n = 10 0.7 ... 1.07, n = 12 0.5, n = 16 0.54
+//   d = 4096  M <= 128   n = 8 1.04, n = 11 0.5 ... 0.8                    n = 8 1.22, n = 10 0.6
+//   d > 8192  M <= 128   n = 5 1.2 ... 1.4, n = 10 1.08; T_max >= 8: 0.7   n = 8 1.0 ... 1.1, n = 11 0.7 ... 1.07; T_max >= 8: 0.78
+// Long staleness lets a round take more gradients at once, where an iteration is held to its teams.
+// A direct exchange between 17 to 32 strips (d = 8192) is the slowest for its size.  Ten strips and fewer keep n = 48 for
+// M <= 32 on denser graphs.  Models and slots that do not fit LDS cost more than the table says.
+int32_t strip_workers(int64_t d, int32_t M, int64_t T_max, bool ring, bool lds_state) {
+    const bool late = T_max >= 8;
     const bool slow_exchange = d > 16 * kStripCols && d <= kStripGroupBlocks * kStripCols;
     int32_t n;
-    if (d < 1024) n = M <= 16 ? (ring ? 16 : 24) : M <= 32 ? (ring ? 12 : 16) : M <= 64 ? 8 : 5;
-    else if (d <= 2048) n = M <= 16 ? (ring ? 20 : 32) : M <= 32 ? (ring ? 16 : 24) : M <= 64 ? 16 : 8;
-    else if (M <= 3) n = ring ? 28 : 32;
-    else if (M <= 16) n = ring ? 40 : 64;
-    else if (M <= 32) n = ring ? (slow_exchange ? 20 : 28) : 48;
-    else if (M <= 64) n = ring ? 16 : slow_exchange ? 20 : 24;
-    else n = slow_exchange ? (ring ? 5 : 8) : 12;
+    if (M <= 8) {
+        if (d < 1024) n = ring ? 28 : 36;
+        else if (d <= 2048) n = ring ? 34 : 40;
+        else if (slow_exchange) n = ring ? 50 : 64;
+        else if (M <= 3) n = ring ? 46 : 54;
+        else n = ring ? 60 : 76;
+    } else if (d <= 2048) {
+        const bool shorter = d < 1024;
+        if (M <= 16) n = shorter ? (ring ? 16 : 24) : (ring ? 20 : 32);
+        else if (M <= 32) n = shorter ? (ring ? 12 : 16) : (ring ? 16 : 24);
+        else if (M <= 64) n = shorter ? 8 : 16;
+        else n = shorter ? 5 : 8;
+    } else if (slow_exchange) {
+        n = M <= 16 ? (late ? 24 : ring ? 34 : 44) : M <= 32 ? (ring ? (late ? 10 : 14) : 16) : M <= 48 && !late ? 10 : M <= 64 ? 6 : late ? 4 : 5;
+    } else if (d <= 16 * kStripCols) {
+        if (M <= 16) n = ring ? 40 : 64;
+        else if (M <= 32) n = ring ? (late ? 20 : 28) : d <= 10 * kStripCols ? 48 : 28;
+        else n = M > 64 ? 8 : late ? (M <= 48 ? 12 : 8) : 16;
+    } else {
+        if (M <= 16) n = ring ? 40 : 64;
+        else if (M <= 32) n = ring ? 28 : 36;
+        else if (M <= 64) n = ring ? (M <= 48 ? 16 : 14) : (M <= 48 ? 22 : 20);
+        else n = M > 96 ? 9 : late ? 8 : 11;
+    }
     return lds_state ? n : std::min(n, 16);
 }
 
@@ -150,7 +174,7 @@ void settle_strips(adpsgd_t* h) {
     const int32_t model = h->o.model;
     if ((model != ADPSGD_MODEL_LSQ && model != ADPSGD_MODEL_LOGREG) || h->d > kStripMaxD || h->o.M > kStripMaxM) return;
     const bool ring = h->rowptr[h->n] <= 3 * static_cast<int64_t>(h->n), lds_state = strip_lds_slots(h) >= static_cast<int64_t>(h->o.T_max) + 1;
-    if (h->n > strip_workers(h->d, h->o.M, ring, lds_state)) return;
+    if (h->n > strip_workers(h->d, h->o.M, h->o.T_max, ring, lds_state)) return;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     int dev = 0, cus = 0, cooperative = 0;
     const size_t words = strip_exchange_bytes(model, h->o.M);
