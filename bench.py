@@ -308,11 +308,11 @@ def main():
     one_launch = ps["fused_launches"] == n_prof < ps["rounds"]     # all events of a call in one launch
     in_columns = synth and one_launch                              # ... with X crossing HBM once per call
     if in_columns:
-        # bound by the generator's arithmetic: a quad of normals takes a SIMD 411 cycles per 64 lanes (csrc/device_common.hpp);
+        # bound by the generator's arithmetic: a quad of normals takes a SIMD 326 cycles per 64 lanes (csrc/device_common.hpp);
         # 1024 SIMDs at 2.4 GHz
         launch_s = ps["fused_ms"] * 1e-3 / n_prof
         per_call = ps["events"] / n_prof
-        peak = 1024 * 2.4e9 / 411 * 64 * 4 / 1e9
+        peak = 1024 * 2.4e9 / 326 * 64 * 4 / 1e9
         achieved = per_call * d / launch_s / 1e9
         roof = {"bound": "valu", "achieved": achieved, "peak": peak, "unit": "1e9 normals/s", "frac": achieved / peak,
                 "traffic": None, "traffic_source": None, "kernel": "column_events_kernel", "avg_launch_ms": launch_s * 1e3,

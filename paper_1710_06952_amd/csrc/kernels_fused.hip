@@ -125,7 +125,10 @@ struct ChainParams {
 };
 
 // The same update for chains of operations that share rows, with gradients from the slots: 16 (24) bytes per parameter and
-// *row* instead of per event, and fewer rounds, each of which has to wait for its gradients.
+// *row* instead of per event, and fewer rounds, each of which has to wait for its gradients.  Bound by HBM like the kernel
+// above (n = 8, d = 12 M, momentum, 60 events with a caller's gradients: 4.73 -> 3.91 ms, 1.52 rows and 0.88 momentum buffers
+// moved per event instead of 2 and 1).  Chains of up to six would move 5 % less there (18 % on graphs with hops and long
+// staleness), for half as many registers again.
 // grid = (ceil(d / 1024), chains of the round); pass u of thread t touches element 1024 blockIdx.x + 256 u + t of all rows.
 template <bool STREAM, bool MOM>
 __global__ __launch_bounds__(kThreads) void gossip_chains_kernel(const ChainParams p) {
