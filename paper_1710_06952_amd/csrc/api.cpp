@@ -468,7 +468,7 @@ struct EventCall {
     bool ext_comp = false;      // caller's function, wait-free variant: compensated fp32 rows
     bool factored = false;      // perceptron: dW1 stays in factored form until the update kernel
     int32_t chain = 1;          // updates of a round that may follow each other on a row
-    bool chained() const { return chain > 1; }
+    bool chained() const { return chain > 1 || lin_factored; }      // the update kernel takes chains (of one, where chain is 1)
     std::vector<UpdateChain> chains;        // chained: the updates, by round ...
     std::vector<int64_t> chain_off;         // ... and where those of a round begin
     std::vector<int64_t> chain_event;       // ... and the event of every operation, -1: averaging only
@@ -574,7 +574,7 @@ int prepare_call(adpsgd_t* h, const adpsgd_schedule_t* s, EventCall& c) {
     if (rc != ADPSGD_OK) return fail(h, rc, perr);
     if ((h->o.flags & ADPSGD_FLAG_VERIFY_PLAN) &&
         !verify_plan(h->n, c.K, s->worker, s->neighbour, s->tau, h->n_slots, c.with_grad, c.plan, perr, s->extra_ptr, s->extra_a,
-                     s->extra_b, c.A, carried, c.chained()))
+                     s->extra_b, c.A, carried, c.chain > 1))
         return fail(h, ADPSGD_ERR_STATE, perr);
 
     const int32_t R = c.plan.n_rounds;

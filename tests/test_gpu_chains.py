@@ -107,3 +107,26 @@ def test_linear_models_in_chains_are_event_by_event(P, model, d, M, mu, dense):
     assert np.array_equal(out[0][0], out[1][0])
     assert mu == 0.0 or np.array_equal(out[0][1], out[1][1])
     assert out[0][2] < out[1][2] == K
+
+
+@pytest.mark.parametrize("model,n,d,M,mu,extra", [("lsq", 16, 4096, 8, 0.0, True), ("lsq", 8, 2050, 4, 0.9, False), ("logreg", 8, 4096, 8, 0.9, False)])
+def test_short_calls_of_a_handle_that_runs_in_one_launch(P, model, n, d, M, mu, extra):
+    """A few events of such a handle go by rounds without chains, with the gradients of least squares as coefficients."""
+    print("chains, short call %s n=%d d=%d M=%d mu=%g" % (model, n, d, M, mu), flush=True)
+    rows, K = 32, 3
+    g = random_regular4_graph(n, 3)
+    sched = schedule(g, K, 2, extra, M=M, rows=[rows] * n)
+    feats, targs, _ = lsq_data(n, rows, d, seed=5, feature_var=1.0 / d) if model == "lsq" else logreg_data(n, rows, d, seed=5)
+    x0 = np.random.default_rng(3).standard_normal((n, d)).astype(np.float32)
+    out = []
+    for rounds in (False, True):
+        eng = P.Engine(g, d, model, M=M, gamma=0.05, lam=1e-3 if model == "logreg" else 0.0, T_max=2, momentum=mu,
+                       weight_decay=1e-3 if mu else 0.0, rounds=rounds, verify_plan=True)
+        eng.load_data(feats, targs)
+        eng.set_models(x0, broadcast=False)
+        eng.run_events(sched)
+        out.append((eng.get_models(), eng.get_momentum() if mu else None, eng.get_stats()["grad_launches"]))
+        eng.close()
+    assert out[0][2] > 0                                       # not in one launch
+    assert np.array_equal(out[0][0], out[1][0]) and not np.array_equal(out[0][0], x0)
+    assert mu == 0.0 or np.array_equal(out[0][1], out[1][1])
