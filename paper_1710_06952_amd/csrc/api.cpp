@@ -618,45 +618,15 @@ void fill_update(adpsgd_t* h, EventCall& c, int64_t k, std::vector<int64_t>& u_f
 // The updates of a call as the chains of every round.
 int build_chains(adpsgd_t* h, EventCall& c) {
     const adpsgd_schedule_t* s = c.s;
-    std::vector<ColumnPair> pairs(static_cast<size_t>(c.A + c.n_extra));
-    std::vector<int64_t> fill(c.u_off.begin(), c.u_off.end() - 1);
-    for (int64_t k = 0; k < c.A; ++k) {
-        int64_t& at = fill[c.plan.u_round[k]];
-        pairs[at++] = ColumnPair{s->worker[k], s->neighbour[k], k};
-        if (s->extra_ptr)
-            for (int64_t q = s->extra_ptr[k]; q < s->extra_ptr[k + 1]; ++q) pairs[at++] = ColumnPair{s->extra_a[q], s->extra_b[q], -1};
-    }
+    const ChainCall call{h->n, c.A, s->worker, s->neighbour, s->extra_ptr, s->extra_a, s->extra_b, s->gamma, h->o.gamma, &c.plan, h->data.data(), &c.u_off};
     ChainLayout layout;
+    std::vector<ColumnPair> pairs;
+    chain_pairs(call, pairs);
     chain_rounds(pairs, c.u_off, h->n, layout);
     if ((h->o.flags & ADPSGD_FLAG_VERIFY_PLAN) && !verify_chains(pairs, c.u_off, h->n, c.chain, layout))
         return fail(h, ADPSGD_ERR_STATE, "plan check: chains of updates out of order");
+    if (!fill_chains(call, pairs, layout, c.chain, c.chains, c.chain_event)) return fail(h, ADPSGD_ERR_STATE, "run_events: a chain of updates is too long");
     c.chain_off = layout.round;
-    c.chains.resize(layout.first.size() - 1);
-    c.chain_event.resize(pairs.size());
-    for (size_t t = 0; t < c.chains.size(); ++t) {
-        UpdateChain& ch = c.chains[t];
-        ch = UpdateChain{};
-        ch.first = static_cast<int32_t>(layout.first[t]);
-        ch.n_ops = static_cast<int32_t>(layout.first[t + 1] - layout.first[t]);
-        if (ch.n_ops > c.chain) return fail(h, ADPSGD_ERR_STATE, "run_events: a chain of updates is too long");
-        std::fill_n(ch.rows, kChain + 1, -1);
-        int32_t n_rows = 0;
-        auto place = [&](int32_t row) {
-            const int32_t at = static_cast<int32_t>(std::find(ch.rows, ch.rows + n_rows, row) - ch.rows);
-            if (at == n_rows) ch.rows[n_rows++] = row;
-            return at;
-        };
-        for (int32_t u = 0; u < ch.n_ops; ++u) {
-            const ColumnPair& pair = pairs[layout.order[ch.first + u]];
-            const int64_t k = pair.event;
-            const int32_t pi = place(pair.i), pj = place(pair.j);
-            const WorkerData& w = h->data[pair.i];
-            c.chain_event[ch.first + u] = k;
-            ch.ops[u] = UpdateOp{w.features, w.ld, k >= 0 ? c.plan.slot[k] : 0, k < 0 ? 0.0f : s->gamma ? s->gamma[k] : h->o.gamma, pi | pj << 4, static_cast<int32_t>(k)};
-            if (k >= 0) ch.steps |= 1 << pi;
-        }
-        std::fill(ch.ops + ch.n_ops, ch.ops + kChain, ch.ops[ch.n_ops - 1]);
-    }
     return ADPSGD_OK;
 }
 

@@ -28,7 +28,7 @@ struct alignas(32) PairOp {
 constexpr int kChain = 4;               // operations of a chain, at most; they touch one row more
 constexpr int kMlpChain = 3;            // ... of the perceptron
 struct UpdateOp {
-    const void* features;               // worker i's inputs (average only: any worker's, read and dropped), or nullptr
+    const void* features;               // worker i's inputs (average only: those of a worker that has some, read and dropped), or nullptr
     int64_t feat_ld;
     int32_t slot;
     float gamma;
@@ -177,6 +177,25 @@ struct ChainLayout {
 void chain_rounds(const std::vector<ColumnPair>& pairs, const std::vector<int64_t>& offset, int32_t n_rows, ChainLayout& out);
 // Whether a layout keeps the order of every row and has at most `most` operations in a chain (ADPSGD_FLAG_VERIFY_PLAN).
 bool verify_chains(const std::vector<ColumnPair>& pairs, const std::vector<int64_t>& offset, int32_t n_rows, int32_t most, const ChainLayout& c);
+// The updates of a call, for the two functions below.
+struct ChainCall {
+    int32_t n;
+    int64_t A;                      // events applied
+    const int32_t *worker, *neighbour;
+    const int64_t* extra_ptr;       // or nullptr
+    const int32_t *extra_a, *extra_b;
+    const float* gamma;             // per event, or nullptr: gamma_default
+    float gamma_default;
+    const Plan* plan;
+    const WorkerData* data;         // by worker; the workers of the events have some, or none has
+    const std::vector<int64_t>* offset;     // first update operation of every round (and the end)
+};
+// Its operations in the order of the rounds, as chain_rounds takes them.
+void chain_pairs(const ChainCall& c, std::vector<ColumnPair>& pairs);
+// The chains as the update kernels take them, and the event of every operation in their order (-1: averaging only).
+// false: a chain has more than `most` operations.
+bool fill_chains(const ChainCall& c, const std::vector<ColumnPair>& pairs, const ChainLayout& layout, int32_t most,
+                 std::vector<UpdateChain>& chains, std::vector<int64_t>& events);
 // Packs the operations into batches of `capacity` with pairwise disjoint rows such that the operations of every row
 // keep their order from batch to batch: every operation goes into the first batch with room behind those of its rows.
 // place[t] = batch * capacity + position; returns the number of batches.

@@ -323,6 +323,51 @@ bool verify_chains(const std::vector<ColumnPair>& pairs, const std::vector<int64
                          // rows that no two chains share, no operation can be named twice
 }
 
+void chain_pairs(const ChainCall& c, std::vector<ColumnPair>& pairs) {
+    pairs.resize(static_cast<size_t>(c.offset->back()));
+    std::vector<int64_t> fill(c.offset->begin(), c.offset->end() - 1);
+    for (int64_t k = 0; k < c.A; ++k) {
+        int64_t& at = fill[c.plan->u_round[k]];
+        pairs[at++] = ColumnPair{c.worker[k], c.neighbour[k], k};
+        if (c.extra_ptr)
+            for (int64_t q = c.extra_ptr[k]; q < c.extra_ptr[k + 1]; ++q) pairs[at++] = ColumnPair{c.extra_a[q], c.extra_b[q], -1};
+    }
+}
+
+bool fill_chains(const ChainCall& c, const std::vector<ColumnPair>& pairs, const ChainLayout& layout, int32_t most,
+                 std::vector<UpdateChain>& chains, std::vector<int64_t>& events) {
+    chains.resize(layout.first.size() - 1);
+    events.resize(pairs.size());
+    // A kernel may request the inputs of every operation before it looks at the event.  An extra pair can name a worker without
+    // data: the pair takes the inputs of a worker that steps in this call, of which the first row is read.
+    const WorkerData* const some = c.A > 0 ? &c.data[c.worker[0]] : nullptr;
+    for (size_t t = 0; t < chains.size(); ++t) {
+        UpdateChain& ch = chains[t];
+        ch = UpdateChain{};
+        ch.first = static_cast<int32_t>(layout.first[t]);
+        ch.n_ops = static_cast<int32_t>(layout.first[t + 1] - layout.first[t]);
+        if (ch.n_ops > most) return false;
+        std::fill_n(ch.rows, kChain + 1, -1);
+        int32_t n_rows = 0;
+        auto place = [&](int32_t row) {
+            const int32_t at = static_cast<int32_t>(std::find(ch.rows, ch.rows + n_rows, row) - ch.rows);
+            if (at == n_rows) ch.rows[n_rows++] = row;
+            return at;
+        };
+        for (int32_t u = 0; u < ch.n_ops; ++u) {
+            const ColumnPair& pair = pairs[layout.order[ch.first + u]];
+            const int64_t k = pair.event;
+            const int32_t pi = place(pair.i), pj = place(pair.j);
+            const WorkerData& w = k >= 0 ? c.data[pair.i] : *some;
+            events[ch.first + u] = k;
+            ch.ops[u] = UpdateOp{w.features, w.ld, k >= 0 ? c.plan->slot[k] : 0, k < 0 ? 0.0f : c.gamma ? c.gamma[k] : c.gamma_default, pi | pj << 4, static_cast<int32_t>(k)};
+            if (k >= 0) ch.steps |= 1 << pi;
+        }
+        std::fill(ch.ops + ch.n_ops, ch.ops + kChain, ch.ops[ch.n_ops - 1]);
+    }
+    return true;
+}
+
 int64_t pack_columns(const std::vector<ColumnPair>& pairs, int32_t n_rows, int32_t capacity, std::vector<int64_t>& place) {
     place.resize(pairs.size());
     std::vector<int64_t> after(n_rows, 0);       // first batch behind the operations of the row so far

@@ -1,5 +1,6 @@
-"""CPU: rounds whose updates come in chains (csrc/planner.cpp, chains_layout_check.cpp), and records of the strip kernel that
-request rows and use them at once (csrc/strips.cpp, strips_holders_check.cpp), against the serial order."""
+"""CPU: rounds whose updates come in chains and the tables of these chains (csrc/planner.cpp, chains_layout_check.cpp,
+chains_table_check.cpp), and records of the strip kernel that request rows and use them at once (csrc/strips.cpp,
+strips_holders_check.cpp), against the serial order."""
 import os
 import subprocess
 import sys
@@ -10,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 
 
-@pytest.mark.parametrize("check", ["chains_layout_check", "strips_holders_check"])
+@pytest.mark.parametrize("check", ["chains_layout_check", "chains_table_check", "strips_holders_check"])
 def test_layouts_reproduce_the_serial_order(tmp_path, check):
     from paper_1710_06952_amd import build
     exe = str(tmp_path / "check")

@@ -130,3 +130,32 @@ def test_short_calls_of_a_handle_that_runs_in_one_launch(P, model, n, d, M, mu, 
     assert out[0][2] > 0                                       # not in one launch
     assert np.array_equal(out[0][0], out[1][0]) and not np.array_equal(out[0][0], x0)
     assert mu == 0.0 or np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("mu", [0.0, 0.9])
+def test_extra_pairs_of_workers_without_data(P, mu):
+    """Workers that never step need no data; an extra pair may average them all the same."""
+    print("chains, perceptron, extra pairs of workers without data mu=%g" % mu, flush=True)
+    n, dims, M, rows, K, T, stepping = 9, (40, 64, 5), 16, 48, 80, 2, 5
+    d = dims[0] * dims[1] + dims[1] + dims[1] * dims[2] + dims[2]
+    g = random_regular4_graph(n, 4)
+    rng = np.random.default_rng(8)
+    worker = rng.integers(0, stepping, K).astype(np.int32)
+    sched = {"worker": worker, "neighbour": np.array([rng.choice(g[1][g[0][i]:g[0][i + 1]]) for i in worker], np.int32),
+             "tau": np.minimum(rng.integers(0, T + 1, K), np.arange(K)).astype(np.int32),
+             "batch_idx": rng.integers(0, rows, (K, M)).astype(np.int32)}
+    extra = random_extra_pairs(g, sched["worker"], sched["neighbour"], max_extra=2, seed=2)
+    assert (extra[1] >= stepping).any() and (extra[1] < stepping).any()
+    feats, labels, _ = mixture_data(n, rows, din=dims[0], classes=dims[2], seed=9)
+    x0 = np.stack([mlp_init(*dims, seed=s) for s in range(n)])
+    eng = P.Engine(g, d, "mlp", M=M, gamma=0.05, T_max=T, mlp=dims, momentum=mu, weight_decay=1e-3 if mu else 0.0, verify_plan=True)
+    eng.load_data(feats[:stepping], labels[:stepping])
+    eng.set_models(x0, broadcast=False)
+    eng.run_events(dict(sched, extra_pairs=extra))
+    Xr, Vr = x0.copy(), np.zeros_like(x0)
+    oracle.run_events(Xr, sched, oracle.MODEL_MLP, 0.05, M=M, gscale=1.0 / M, mlp=dims, features=feats, targets=labels, extra_pairs=extra,
+                      momentum=mu, weight_decay=1e-3 if mu else 0.0, V=Vr if mu else None)
+    # a hidden error next to a boundary of its bf16 rounding may fall on the other side: 2^-8 of one sample's share (1/16, times
+    # an error of 0.1 and an input of 3) of a step of 0.05, 4e-6 an event and ten times that with momentum; 80 events
+    assert np.max(np.abs(eng.get_models() - Xr)) <= 80 * (4e-5 if mu else 4e-6)
+    eng.close()
