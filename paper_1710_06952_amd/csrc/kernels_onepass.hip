@@ -17,7 +17,8 @@
 // The exchange has two steps, both in words of exchange.hpp (value and sequence number in one relaxed 8-byte access, never
 // cleared: a number is used once): every block publishes its partial sums, one block (sample mod strips) adds those of a
 // sample, in the order of the strips, and publishes its coefficient.  A block writes the words of its next gradient only after
-// it has all coefficients of this one, which need all sums of this one, so nothing is overwritten early.
+// it has the words of all samples of this one, which need all sums of this one, so nothing is overwritten early.  Among the
+// samples is the point itself where losses are wanted (|x^|^2 of logistic regression): its word is awaited for that reason alone.
 //
 // The launch is not cooperative: nothing makes sure that all blocks of a group are resident.  A block that waits longer than
 // a limit goes on by itself, for the rest of the launch: it computes the dot products of whole rows, combines its own strip
@@ -37,7 +38,7 @@ struct OnePassParams {
     OnePassArgs a;
     int64_t n_vec;
     int32_t tile_cols;           // columns of a strip
-    int32_t samples;             // M, and |x^|^2 of the logistic loss
+    int32_t samples;             // onepass_samples
     int32_t pitch;               // words of a group: [samples][strips] sums, [samples] coefficients, [samples] losses
 };
 
@@ -255,8 +256,9 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
                 if (a.loss) put_word(losses, m, r.y, seq);
             }
         }
-        if (there && wave < (M + 63) / 64) {
-            const int at[1] = {tid < M ? tid : -1};
+        const int awaited = onepass_awaited(p.samples);
+        if (there && wave < (awaited + 63) / 64) {
+            const int at[1] = {tid < awaited ? tid : -1};
             float v[1];
             there = take_words(coefs, at, seq, until, v);
             if (tid < M) coef_s[tid] = v[0];
@@ -395,7 +397,7 @@ hipError_t launch_onepass_gradient(const OnePassArgs& a, hipStream_t st) {
     p.a = a;
     p.n_vec = (a.d + 3) / 4;
     p.tile_cols = 256 * a.shape.chunks * (kOnePassWaves / a.shape.row_groups);
-    p.samples = a.M + (a.model == ADPSGD_MODEL_LOGREG && a.loss ? 1 : 0);
+    p.samples = onepass_samples(a.model, a.M, a.loss != nullptr);
     p.pitch = p.samples * (a.shape.strips + 2);
     switch (a.shape.rows * 100 + a.shape.chunks) {
         case 204: return launch_shape<2, 4>(p, st);

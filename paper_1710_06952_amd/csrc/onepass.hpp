@@ -25,6 +25,12 @@ OnePassShape onepass_shape(int model, int64_t d, int32_t M, int32_t compute_unit
 bool onepass_for_events(const OnePassShape& s, int model, int32_t M, bool wait_free);
 size_t onepass_exchange_bytes(const OnePassShape& s, int32_t M);
 
+// Sums of a gradient that the blocks exchange: one per sample, and |x^|^2 for the logistic loss.
+constexpr int32_t onepass_samples(int model, int32_t M, bool loss) { return M + (model == ADPSGD_MODEL_LOGREG && loss ? 1 : 0); }
+// Of these, how many have to be finished before a block may publish sums of its next gradient in the same words: all.  One
+// that is not awaited could be overwritten under the block that adds it up.
+constexpr __host__ __device__ int32_t onepass_awaited(int32_t samples) { return samples; }
+
 struct OnePassArgs {
     OnePassShape shape;
     int model;
