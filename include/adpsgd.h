@@ -236,6 +236,11 @@ int adpsgd_set_route(adpsgd_t* h, int32_t route);
  * Applies to the calls from now on. */
 int adpsgd_set_wait_limits(adpsgd_t* h, int64_t assembly_us, int32_t lose_exchange);
 
+/* How many blocks have gone on by themselves since the handle was created because the others of their gradient did not come in
+ * time (gradients in one pass over the minibatch rows, see adpsgd_set_wait_limits): 0 as long as nothing else holds the compute
+ * units.  The results are the same within rounding, the launches slower.  Waits for the handle's work. */
+int adpsgd_get_late_blocks(adpsgd_t* h, int64_t* out);
+
 /* Waits for the handle's work.  Afterwards what the caller reads through its own pointers (the models, a loss array) is
  * there, and a launch that was given up (adpsgd_set_wait_limits) is reported: ADPSGD_ERR_HIP. */
 int adpsgd_synchronize(adpsgd_t* h);

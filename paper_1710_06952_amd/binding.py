@@ -19,7 +19,7 @@ ROUTE_AUTO, ROUTE_ROUNDS = 0, 1
 FLAG_PROFILE, FLAG_DENSE_GRADIENT, FLAG_VERIFY_PLAN, FLAG_SYNC_IN_PLACE = 1, 2, 4, 8
 
 EXPORTS = [
-    "adpsgd_create", "adpsgd_destroy", "adpsgd_last_error", "adpsgd_load_data", "adpsgd_set_models", "adpsgd_set_route", "adpsgd_set_wait_limits", "adpsgd_synchronize",
+    "adpsgd_create", "adpsgd_destroy", "adpsgd_last_error", "adpsgd_load_data", "adpsgd_set_models", "adpsgd_set_route", "adpsgd_set_wait_limits", "adpsgd_get_late_blocks", "adpsgd_synchronize",
     "adpsgd_run_events", "adpsgd_run_events_with", "adpsgd_get_models", "adpsgd_get_mean_model", "adpsgd_consensus_distance", "adpsgd_consensus_distance_weighted",
     "adpsgd_consensus_distance_static",
     "adpsgd_get_bf16_models", "adpsgd_classification_error", "adpsgd_get_momentum", "adpsgd_get_stats", "adpsgd_make_schedule", "adpsgd_plan_rounds",
@@ -116,6 +116,7 @@ def lib():
         L.adpsgd_set_route.argtypes = [vp, i32]
         L.adpsgd_synchronize.argtypes = [vp]
         L.adpsgd_set_wait_limits.argtypes = [vp, i64, i32]
+        L.adpsgd_get_late_blocks.argtypes = [vp, P(i64)]
         L.adpsgd_run_events.argtypes = [vp, P(Schedule), vp]
         L.adpsgd_get_models.argtypes = [vp, vp, i64, i32]
         L.adpsgd_get_mean_model.argtypes = [vp, vp, i32]
@@ -308,6 +309,12 @@ class Handle:
     def set_wait_limits(self, assembly_us=10_000_000, lose_exchange=False):
         """How long the blocks of a call in one launch wait for each other (see the header)."""
         _check(self._h, lib().adpsgd_set_wait_limits(self._h, assembly_us, 1 if lose_exchange else 0))
+
+    def get_late_blocks(self):
+        """How many blocks have gone on without the others of their gradient (see the header)."""
+        out = C.c_int64()
+        _check(self._h, lib().adpsgd_get_late_blocks(self._h, C.byref(out)))
+        return out.value
 
     def synchronize(self):
         """Waits for the handle's work; raises when a launch was given up."""

@@ -207,7 +207,7 @@ void settle_onepass(adpsgd_t* h) {
     }
     const OnePassShape s = onepass_shape(h->o.model, h->d, h->o.M, cus);
     if (!s.ok()) return;
-    if (h->onepass_words.reserve(onepass_exchange_bytes(s, h->o.M)) == hipSuccess &&
+    if (h->onepass_words.reserve(onepass_exchange_bytes(s, h->o.M) + sizeof(unsigned long long)) == hipSuccess &&
         hipMemset(h->onepass_words.p, 0, h->onepass_words.cap) == hipSuccess && hipStreamSynchronize(nullptr) == hipSuccess) {
         h->onepass = s;
         return;
@@ -227,13 +227,15 @@ bool can_run_onepass(const adpsgd_t* h) {
 }
 
 int launch_onepass(adpsgd_t* h, const LinearGradArgs& a) {
+    const size_t bytes = onepass_exchange_bytes(h->onepass, a.M);
     if (h->onepass_seq > 0xFFFFFFFFu - static_cast<uint32_t>(a.n_ops)) {      // before the numbers wrap
-        HIP_TRY(h, hipMemsetAsync(h->onepass_words.p, 0, h->onepass_words.cap, h->stream));
+        HIP_TRY(h, hipMemsetAsync(h->onepass_words.p, 0, bytes, h->stream));
         h->onepass_seq = 0;
     }
     const uint64_t wait_us = static_cast<uint64_t>(std::min(h->assembly_us, kOnePassWaitUs));
     const OnePassArgs o{h->onepass, a.model, a.X, a.ld, a.d, a.ops, a.n_ops, a.M, a.batch_idx, a.slots, a.gscale, a.lambda, a.loss,
-                        static_cast<unsigned long long*>(h->onepass_words.p), h->onepass_seq + 1, wait_us * kClockTicksPerUs};
+                        static_cast<unsigned long long*>(h->onepass_words.p), static_cast<unsigned long long*>(h->onepass_words.p) + bytes / sizeof(unsigned long long),
+                        h->onepass_seq + 1, wait_us * kClockTicksPerUs};
     HIP_TRY(h, launch_onepass_gradient(o, h->stream));
     h->onepass_seq += static_cast<uint32_t>(a.n_ops);
     return ADPSGD_OK;
@@ -1156,6 +1158,17 @@ extern "C" int adpsgd_set_route(adpsgd_t* h, int32_t route) {
     if (!h) return ADPSGD_ERR_ARG;
     if (route != ADPSGD_ROUTE_AUTO && route != ADPSGD_ROUTE_ROUNDS) return fail(h, ADPSGD_ERR_ARG, "set_route: unknown route");
     h->route = route;
+    return ADPSGD_OK;
+}
+
+extern "C" int adpsgd_get_late_blocks(adpsgd_t* h, int64_t* out) {
+    if (!h) return ADPSGD_ERR_ARG;
+    if (!out) return fail(h, ADPSGD_ERR_ARG, "get_late_blocks: out is NULL");
+    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    unsigned long long count = 0;
+    if (h->onepass.ok())
+        HIP_TRY(h, hipMemcpy(&count, static_cast<char*>(h->onepass_words.p) + onepass_exchange_bytes(h->onepass, h->o.M), sizeof(count), hipMemcpyDeviceToHost));
+    *out = static_cast<int64_t>(count);
     return ADPSGD_OK;
 }
 

@@ -83,7 +83,7 @@ struct adpsgd {
     adpsgd_impl::HostBuf exchange_status; // ... a word the kernel sets when a wait had to be given up ...
     adpsgd_impl::DevBuf alone_slots;      // ... and slots for a block that executes a call alone
     adpsgd_impl::OnePassShape onepass;    // linear models, gradients in one pass over the rows; not ok(): in three launches ...
-    adpsgd_impl::DevBuf onepass_words;    // ... the words the blocks exchange ...
+    adpsgd_impl::DevBuf onepass_words;    // ... the words the blocks exchange, and behind them a count of late blocks ...
     uint32_t onepass_seq = 0;             // ... the sequence number of the last gradient
     int64_t assembly_us = adpsgd_impl::kAssemblyUs;      // adpsgd_set_wait_limits ...
     bool lose_exchange = false;                          // ...

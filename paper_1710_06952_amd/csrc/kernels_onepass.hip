@@ -273,6 +273,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
         if (!there && lane == 0) late_s = 1;
         __syncthreads();
         if (late_s != 0) {                         // on its own from here, uniform over the block
+            if (tid == 0) __hip_atomic_fetch_add(a.late, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             run_alone(static_cast<const OnePassParams*>((const void*)__builtin_amdgcn_kernarg_segment_ptr()), q, group, strip, &part_s[0][0], coef_s, loss_s);
             return;
         }

@@ -43,6 +43,7 @@ struct OnePassArgs {
     float gscale, lambda;
     float* loss;                // device, by event, or nullptr
     unsigned long long* words;  // onepass_exchange_bytes, zero before the first launch
+    unsigned long long* late;   // counts the blocks that go on by themselves
     uint32_t seq0;              // sequence number of the first gradient; n_ops of them are used
     uint64_t wait_ticks;        // of the constant clock
 };

@@ -84,6 +84,7 @@ def test_events(P, model, M, d):
         assert not eng.X[:, d:].any()
         st = eng.get_stats()
         assert st["grad_launches"] <= st["rounds"]          # one launch per round that evaluates gradients
+        assert (eng.h.get_late_blocks() > 0) == (limit == 0)      # nothing else on the device: the blocks find each other
         eng.close()
 
 
@@ -103,7 +104,7 @@ def test_synchronous_iterations(P, model, M, d):
                               gscale=1.0 / M, lam=1e-3 if model == "logreg" else 0.0, features=feats, targets=targs, steps=S, want_loss=True)
     assert _err(eng.get_models(), Xr) <= TOL
     assert np.allclose(eng.get_loss().reshape(-1), np.asarray(r["loss"]).reshape(-1), rtol=2e-5, atol=1e-6)
-    assert eng.get_stats()["grad_launches"] == S
+    assert eng.get_stats()["grad_launches"] == S and eng.h.get_late_blocks() == 0
     eng.close()
 
 
@@ -126,5 +127,6 @@ def test_a_cut_schedule_gives_the_same_bits(P, model, M, d):
             sc["lookahead"] = end - b
             eng.run_events(sc)
         got.append(eng.get_models())
+        assert eng.h.get_late_blocks() == 0
         eng.close()
     assert np.array_equal(got[0], got[1])
