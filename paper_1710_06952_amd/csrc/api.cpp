@@ -208,7 +208,7 @@ void settle_onepass(adpsgd_t* h) {
     const OnePassShape s = onepass_shape(h->o.model, h->d, h->o.M, cus);
     if (!s.ok()) return;
     if (h->onepass_words.reserve(onepass_exchange_bytes(s, h->o.M) + sizeof(unsigned long long)) == hipSuccess &&
-        hipMemset(h->onepass_words.p, 0, h->onepass_words.cap) == hipSuccess && hipStreamSynchronize(nullptr) == hipSuccess) {
+        hipMemsetAsync(h->onepass_words.p, 0, h->onepass_words.cap, h->stream) == hipSuccess) {       // before all launches of the handle
         h->onepass = s;
         return;
     }
@@ -244,6 +244,30 @@ int launch_onepass(adpsgd_t* h, const LinearGradArgs& a) {
 }  // namespace adpsgd_impl
 
 using namespace adpsgd_impl;
+
+namespace {
+
+// Everything a handle holds, once no work of it is under way.
+void release_all(adpsgd_t* h) {
+    for (auto& t : h->tables) {
+        t.stage.release();
+        t.dev.release();
+        if (t.done) (void)hipEventDestroy(t.done);
+    }
+    for (auto& pr : h->ev_fused) { (void)hipEventDestroy(pr.first); (void)hipEventDestroy(pr.second); }
+    for (auto& pr : h->ev_grad) { (void)hipEventDestroy(pr.first); (void)hipEventDestroy(pr.second); }
+    for (auto e : h->ev_pool) (void)hipEventDestroy(e);
+    h->grad_scratch.release();
+    h->comp_rows.release();
+    h->diag.release();
+    h->sync_other.release();
+    h->exchange.release();
+    h->exchange_status.release();
+    h->alone_slots.release();
+    h->onepass_words.release();
+}
+
+}  // namespace
 
 extern "C" const char* adpsgd_last_error(const adpsgd_t* h) { return h ? h->err.c_str() : create_error().c_str(); }
 
@@ -303,17 +327,12 @@ extern "C" int adpsgd_create(adpsgd_t** out, const adpsgd_graph_t* graph, int64_
     h->stream = static_cast<hipStream_t>(o.stream);
     h->streaming = static_cast<int64_t>(n) * o.ldx * 4 > kStreamingThreshold;
     h->stats.slots = n_slots;
-    settle_onepass(h.get());
     settle_strips(h.get());
     settle_onepass(h.get());
     for (auto& t : h->tables) {
-        hipError_t e = hipEventCreateWithFlags(&t.done, hipEventDisableTiming);
+        const hipError_t e = hipEventCreateWithFlags(&t.done, hipEventDisableTiming);
         if (e != hipSuccess) {
-            for (auto& u : h->tables)
-                if (u.done) (void)hipEventDestroy(u.done);
-            h->exchange.release();
-            h->exchange_status.release();
-            h->alone_slots.release();
+            release_all(h.get());
             return hip_fail(nullptr, e, "create: hipEventCreate");
         }
     }
@@ -324,22 +343,7 @@ extern "C" int adpsgd_create(adpsgd_t** out, const adpsgd_graph_t* graph, int64_
 extern "C" void adpsgd_destroy(adpsgd_t* h) {
     if (!h) return;
     (void)hipStreamSynchronize(h->stream);
-    for (auto& t : h->tables) {
-        t.stage.release();
-        t.dev.release();
-        if (t.done) (void)hipEventDestroy(t.done);
-    }
-    for (auto& pr : h->ev_fused) { (void)hipEventDestroy(pr.first); (void)hipEventDestroy(pr.second); }
-    for (auto& pr : h->ev_grad) { (void)hipEventDestroy(pr.first); (void)hipEventDestroy(pr.second); }
-    for (auto e : h->ev_pool) (void)hipEventDestroy(e);
-    h->grad_scratch.release();
-    h->comp_rows.release();
-    h->diag.release();
-    h->sync_other.release();
-    h->exchange.release();
-    h->exchange_status.release();
-    h->alone_slots.release();
-    h->onepass_words.release();
+    release_all(h);
     delete h;
 }
 

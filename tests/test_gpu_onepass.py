@@ -130,3 +130,23 @@ def test_a_cut_schedule_gives_the_same_bits(P, model, M, d):
         assert eng.h.get_late_blocks() == 0
         eng.close()
     assert np.array_equal(got[0], got[1])
+
+
+def test_a_handle_is_created_without_waiting_for_other_streams(P):
+    import torch
+    print("one pass, handle created beside work of the default stream", flush=True)
+    other = torch.cuda.Stream()
+    x = torch.zeros(256 << 20, device="cuda:0")
+    with torch.cuda.stream(other):
+        warm = P.Engine(ring_graph(40), 70_000, "logreg", M=16, gamma=0.1, T_max=2)
+    torch.cuda.synchronize()
+    for _ in range(600):                    # 1 GB read and written each: about 0.2 s
+        x.add_(1.0)
+    done = torch.cuda.Event()
+    done.record()
+    with torch.cuda.stream(other):
+        eng = P.Engine(ring_graph(40), 70_000, "logreg", M=16, gamma=0.1, T_max=2)
+    assert not done.query()
+    torch.cuda.synchronize()
+    eng.close()
+    warm.close()
