@@ -227,18 +227,19 @@ int adpsgd_set_route(adpsgd_t* h, int32_t route);
  *                   compute units for longer than this, one block executes the call by itself, which is slow but gives the
  *                   same results within rounding.  0: always so.  Default 10 000 000.  The gradients that are evaluated
  *                   in one pass over the minibatch rows (rounds and synchronous iterations of linear models) wait for
- *                   each other too, for this long or 1000 us if that is less; then a block goes on by itself likewise.
+ *                   each other too, for this long or 300 us if that is less; then the blocks that are there share out the
+ *                   work of all, at two to three times the cost, with the same bits.
  *                   Outside [0, 2^31): ADPSGD_ERR_ARG.
  *   lose_exchange   Once all blocks are on the device they exchange partial sums.  One that does not find a sum after 2^21
- *                   polls (about a second: a fault of the device) gives the launch up and the models are undefined, which
- *                   every later call on the handle that reads or advances them reports (ADPSGD_ERR_HIP) until
+ *                   polls (about a second: a fault of the device; 10 s for a gradient whose work is shared out) gives the launch up
+ *                   and the models are undefined, which every later call on the handle that reads or advances them reports (ADPSGD_ERR_HIP) until
  *                   adpsgd_set_models.  Non-zero: every launch ends like that, to see what a program does about it.
  * Applies to the calls from now on. */
 int adpsgd_set_wait_limits(adpsgd_t* h, int64_t assembly_us, int32_t lose_exchange);
 
-/* How many blocks have gone on by themselves since the handle was created because the others of their gradient did not come in
- * time (gradients in one pass over the minibatch rows, see adpsgd_set_wait_limits): 0 as long as nothing else holds the compute
- * units.  The results are the same within rounding, the launches slower.  Waits for the handle's work. */
+/* How many blocks have left the exchange of their gradient since the handle was created because the others did not come in time
+ * (gradients in one pass over the minibatch rows, see adpsgd_set_wait_limits): 0 as long as nothing else holds the compute
+ * units.  The results are the same bits, the launches slower.  Waits for the handle's work. */
 int adpsgd_get_late_blocks(adpsgd_t* h, int64_t* out);
 
 /* Waits for the handle's work.  Afterwards what the caller reads through its own pointers (the models, a loss array) is

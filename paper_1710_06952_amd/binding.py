@@ -311,7 +311,7 @@ class Handle:
         _check(self._h, lib().adpsgd_set_wait_limits(self._h, assembly_us, 1 if lose_exchange else 0))
 
     def get_late_blocks(self):
-        """How many blocks have gone on without the others of their gradient (see the header)."""
+        """How many blocks have left the exchange of their gradient (see the header)."""
         out = C.c_int64()
         _check(self._h, lib().adpsgd_get_late_blocks(self._h, C.byref(out)))
         return out.value

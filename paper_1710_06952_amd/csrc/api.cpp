@@ -207,13 +207,17 @@ void settle_onepass(adpsgd_t* h) {
     }
     const OnePassShape s = onepass_shape(h->o.model, h->d, h->o.M, cus);
     if (!s.ok()) return;
+    const bool has_status = h->exchange_status.p != nullptr;
     if (h->onepass_words.reserve(onepass_exchange_bytes(s, h->o.M) + sizeof(unsigned long long)) == hipSuccess &&
+        h->exchange_status.reserve(sizeof(int)) == hipSuccess &&
         hipMemsetAsync(h->onepass_words.p, 0, h->onepass_words.cap, h->stream) == hipSuccess) {       // before all launches of the handle
+        if (!has_status) *static_cast<int*>(h->exchange_status.p) = 0;
         h->onepass = s;
         return;
     }
     (void)hipGetLastError();
     h->onepass_words.release();
+    if (!has_status) h->exchange_status.release();
 }
 
 bool can_run_onepass(const adpsgd_t* h) {
@@ -235,7 +239,7 @@ int launch_onepass(adpsgd_t* h, const LinearGradArgs& a) {
     const uint64_t wait_us = static_cast<uint64_t>(std::min(h->assembly_us, kOnePassWaitUs));
     const OnePassArgs o{h->onepass, a.model, a.X, a.ld, a.d, a.ops, a.n_ops, a.M, a.batch_idx, a.slots, a.gscale, a.lambda, a.loss,
                         static_cast<unsigned long long*>(h->onepass_words.p), static_cast<unsigned long long*>(h->onepass_words.p) + bytes / sizeof(unsigned long long),
-                        h->onepass_seq + 1, wait_us * kClockTicksPerUs};
+                        static_cast<int*>(h->exchange_status.p), h->onepass_seq + 1, wait_us * kClockTicksPerUs};
     HIP_TRY(h, launch_onepass_gradient(o, h->stream));
     h->onepass_seq += static_cast<uint32_t>(a.n_ops);
     return ADPSGD_OK;
@@ -371,7 +375,7 @@ extern "C" int adpsgd_load_data(adpsgd_t* h, int32_t worker, const void* feature
 extern "C" int adpsgd_set_models(adpsgd_t* h, const float* x, int64_t ld_in, int32_t on_device) {
     if (!h || !x) return h ? fail(h, ADPSGD_ERR_ARG, "set_models: x is NULL") : ADPSGD_ERR_ARG;
     if (ld_in != 0 && ld_in < h->d) return fail(h, ADPSGD_ERR_ARG, "set_models: ld_in < d");
-    if (h->strip_units > 0) {                  // what a launch that was given up has left is replaced; one may still be under way
+    if (h->exchange_status.p) {                // what a launch that was given up has left is replaced; one may still be under way
         HIP_TRY(h, hipStreamSynchronize(h->stream));
         *static_cast<int*>(h->exchange_status.p) = 0;
     }

@@ -9,7 +9,10 @@ constexpr int kOnePassThreads = 512;
 constexpr int kOnePassWaves = kOnePassThreads / 64;
 constexpr int kOnePassMaxM = 128;
 constexpr int kOnePassMaxStrips = 256;
-constexpr int64_t kOnePassWaitUs = 1000;      // how long a block waits for the others before it goes on by itself
+// How long a block waits for the others before it leaves the exchange: about twice a launch of 20 gradients.  Where the others
+// come late because other work holds compute units, a longer wait is lost (1000 us: 4.0 and 4.6 ms for the 3.8 and 4.2 at
+// take_tickets), a shorter one gains nothing (100 us: the same).
+constexpr int64_t kOnePassWaitUs = 300;
 
 // How a gradient lies on the chip: its columns in `strips` strips of one block each, the rows of a strip over
 // `row_groups` groups of wavefronts with `rows` rows each, the strip's columns over 8 / row_groups wavefronts of `chunks` times
@@ -18,7 +21,8 @@ struct OnePassShape {
     int32_t rows = 0, chunks = 0, row_groups = 0, strips = 0, groups = 0;
     bool ok() const { return strips > 0; }
 };
-// The shape for a handle, by its sizes alone (so that a gradient has the same bits in every call), or one that is not ok():
+// The shape for a handle, by its sizes alone (so that a gradient has the same bits in every call and however its blocks are
+// scheduled), or one that is not ok():
 // three launches per round (kernels_grad_linear.hip) are the better route, or the only one.
 OnePassShape onepass_shape(int model, int64_t d, int32_t M, int32_t compute_units);
 // Whether run_events takes it too (the synchronous schedule does wherever there is a shape).
@@ -43,7 +47,8 @@ struct OnePassArgs {
     float gscale, lambda;
     float* loss;                // device, by event, or nullptr
     unsigned long long* words;  // onepass_exchange_bytes, zero before the first launch
-    unsigned long long* late;   // counts the blocks that go on by themselves
+    unsigned long long* late;   // counts the blocks that leave the exchange
+    int* status;                // set when the launch is lost
     uint32_t seq0;              // sequence number of the first gradient; n_ops of them are used
     uint64_t wait_ticks;        // of the constant clock
 };

@@ -12,6 +12,85 @@
 
 using namespace adpsgd_impl;
 
+// Gradients of a group in shares (take_tickets of kernels_onepass.hip), on paper: any number of blocks, also fewer than strips,
+// claim the shares in order.  Some block can always go on, no word is replaced before all that need it have read it, and every
+// strip of every gradient is combined once, with the coefficients of that gradient.
+int shares_check(std::mt19937& rng) {
+    auto below = [&](int n) { return static_cast<int>(rng() % static_cast<unsigned>(n)); };
+    long combined = 0;
+    for (int trial = 0; trial < 2000; ++trial) {
+        const int S = 1 + below(7), samples = 1 + below(9), gradients = 1 + below(4), resident = 1 + below(S + 2);
+        const int per = 2 * S + 1, shares = gradients * per;
+        std::vector<int> sums(static_cast<size_t>(samples) * S, -1), coefs(samples, -1), times(static_cast<size_t>(gradients) * S, 0);
+        std::vector<int> sums_read(gradients, 0), coefs_taken(gradients, 0);
+        int tickets = 0, taken = 0;
+        struct Block {
+            int ticket = -1, sample = 0;
+        };
+        std::vector<Block> blocks(resident);
+        int left = resident;
+        // one step of a block, if it can take one
+        auto step = [&](Block& b) -> int {
+            if (b.ticket == -1) {
+                b.ticket = tickets++;
+                b.sample = 0;
+                if (b.ticket >= shares) --left;
+                return 1;
+            }
+            const int i = b.ticket / per, share = b.ticket % per;
+            if (share < S) {
+                for (int m = 0; i > 0 && m < samples; ++m)
+                    if (coefs[m] != i - 1) return 0;
+                if (i > 0 && sums_read[i - 1] != samples) return -1;         // replaced before it was read
+                for (int m = 0; m < samples; ++m) sums[m * S + share] = i;
+            } else if (share == S) {
+                if (i > 0 && taken < S * i) return 0;
+                for (int s = 0; s < S; ++s)
+                    if (sums[b.sample * S + s] != i) return 0;
+                if (i > 0 && coefs_taken[i - 1] != S) return -1;
+                ++sums_read[i];
+                coefs[b.sample] = i;
+                if (++b.sample < samples) return 1;
+            } else {
+                for (int m = 0; m < samples; ++m)
+                    if (coefs[m] != i) return 0;
+                ++coefs_taken[i];
+                ++taken;
+                ++times[i * S + share - S - 1];
+                ++combined;
+            }
+            b.ticket = -1;
+            return 1;
+        };
+        while (left > 0) {
+            bool any = false;
+            const int first = below(resident), turns = 1 + below(resident);
+            for (int t = 0; t < resident; ++t) {
+                Block& b = blocks[(first + t) % resident];
+                if (b.ticket >= shares) continue;
+                const int r = step(b);
+                if (r < 0) {
+                    std::printf("shares, trial %d: S %d, %d blocks: a word replaced early\n", trial, S, resident);
+                    return 1;
+                }
+                any |= r > 0;
+                if (any && t >= turns) break;
+            }
+            if (!any) {
+                std::printf("shares, trial %d: S %d, %d blocks: no block can go on\n", trial, S, resident);
+                return 1;
+            }
+        }
+        for (int t : times)
+            if (t != 1) {
+                std::printf("shares, trial %d: a strip combined %d times\n", trial, t);
+                return 1;
+            }
+    }
+    std::printf("shares ok, combined %ld\n", combined);
+    return 0;
+}
+
 int main() {
     std::mt19937 rng(11);
     auto below = [&](int n) { return static_cast<int>(rng() % static_cast<unsigned>(n)); };
@@ -81,5 +160,6 @@ int main() {
             else begin(b);
         }
     }
+    if (shares_check(rng) != 0) return 1;
     std::printf("ok, steps %ld, blocks left behind %ld\n", steps, ahead);
 }

@@ -71,7 +71,8 @@ def test_events(P, model, M, d):
     r = oracle.run_events(Xr, sched, oracle.MODEL_LOGREG if model == "logreg" else oracle.MODEL_LSQ, 0.3, M=M, gscale=1.0 / M,
                           lam=1e-3 if model == "logreg" else 0.0, features=feats, targets=targs, V=Vr if mu else None, want_loss=True,
                           local_compensation=wait_free, **kw)
-    for limit in (None, 0):                 # 0: every block goes on by itself at once
+    got = []
+    for limit in (None, 0):                 # 0: every block leaves the exchange at once, the gradients go in shares
         eng = _engine(P, model, g, d, M, T, feats, targs, local_compensation=wait_free, **kw)
         if limit is not None:
             eng.h.set_wait_limits(limit)
@@ -85,7 +86,9 @@ def test_events(P, model, M, d):
         st = eng.get_stats()
         assert st["grad_launches"] <= st["rounds"]          # one launch per round that evaluates gradients
         assert (eng.h.get_late_blocks() > 0) == (limit == 0)      # nothing else on the device: the blocks find each other
+        got.append((eng.get_models(), eng.get_loss()))
         eng.close()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])      # the sums in the same order
 
 
 @pytest.mark.parametrize("model,M,d", [("lsq", 4, 100_003), ("logreg", 16, 8193), ("lsq", 128, 2053)])
@@ -130,6 +133,43 @@ def test_a_cut_schedule_gives_the_same_bits(P, model, M, d):
         assert eng.h.get_late_blocks() == 0
         eng.close()
     assert np.array_equal(got[0], got[1])
+
+
+def test_beside_a_call_in_one_launch_of_another_handle(P):
+    """Compute units that another stream's work holds for milliseconds: the blocks of the one pass cannot all be there."""
+    import time
+    import torch
+    print("one pass beside a call in one launch on another stream", flush=True)
+    n, d, M, rows, K, T = 16, 65_536, 128, 128, 40, 4
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    handles = []
+    for stream, (hn, hd, hM, hrows, hK, model) in zip(streams, [(n, d, M, rows, K, "logreg"), (16, 4096, 8, 64, 16_000, "lsq")]):
+        with torch.cuda.stream(stream):
+            g = ring_graph(hn)
+            eng = P.Engine(g, hd, model, M=hM, gamma=0.1, lam=1e-3 if model == "logreg" else 0.0, T_max=T, rounds=model == "logreg")
+            eng.load_data(*_data(model, hn, hrows, hd))
+            handles.append((eng, oracle.make_schedule(g, hK, seed=3, T_max=T, M=hM, rows=[hrows] * hn)))
+    (eng, sched), (long, long_sched) = handles
+    alone = []
+    for e, s in handles * 2:
+        e.set_models(np.zeros(e.d, np.float32))
+        start = time.perf_counter()
+        e.run_events(s)
+        e.h.synchronize()
+        alone.append(time.perf_counter() - start)
+    ref, before = eng.get_models(), eng.h.get_late_blocks()
+    eng.set_models(np.zeros(d, np.float32))
+    torch.cuda.synchronize()
+    start = time.perf_counter()
+    long.run_events(long_sched)
+    eng.run_events(sched)
+    eng.h.synchronize()
+    elapsed = time.perf_counter() - start
+    assert before == 0 and eng.h.get_late_blocks() > 0
+    assert np.array_equal(eng.get_models(), ref)
+    assert elapsed <= 3 * (alone[2] + alone[3]), (elapsed, alone)          # at most one after the other, and the waits
+    eng.close()
+    long.close()
 
 
 def test_a_handle_is_created_without_waiting_for_other_streams(P):
