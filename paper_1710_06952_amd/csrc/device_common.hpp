@@ -91,7 +91,7 @@ template <bool kVector = false>
 __device__ __forceinline__ NormalConstants normal_constants(SynthScale s) {
     const uint32_t one = 0x3F800000u, fraction = 0x007FFFFEu, top = 0x80000000u;
     if (!kVector) return NormalConstants{s, one, fraction, top};
-    return NormalConstants{{in_vector(s.hi), in_vector(s.lo)}, in_vector(one), in_vector(fraction), in_vector(top)};
+    return NormalConstants{{in_vector(s.hi), in_vector(s.lo), s.refine}, in_vector(one), in_vector(fraction), in_vector(top)};
 }
 
 // Box-Muller on two 32-bit words: u1 = ((wa >> 9) + 1/2) 2^-23 in (0,1) and u2 = (wb >> 8) 2^-24 in [0,1) are exact
@@ -100,21 +100,35 @@ __device__ __forceinline__ NormalConstants normal_constants(SynthScale s) {
 // ranges above rule out (no subnormals, infinities or large arguments):
 //   u1      the 23 bits as the fraction of a number in [1, 2), less 1 - 2^-24 (exact);
 //   r       std r = sqrt(-log2(u1)) std sqrt(2 ln 2), v_log_f32 and v_sqrt_f32 (which rounds all but correctly), the constant
-//           in two parts (SynthScale);
+//           in two parts (SynthScale).  Where std is a power of two (refine) the root keeps its remainder, by a Newton step on
+//           v_rsq_f32, so that r is rounded once: a product by such a std is exact, and this form has the error of one;
 //   angle   quarter turns: n = round(4 u2) and f = 4 u2 - n in [-1/2, 1/2), whose 22 bits become the fraction of 1.5 + f, are
 //           read off the word; then polynomials in f^2 for sin(pi/2 f) / f (four terms) and cos(pi/2 f) (four terms beside the
 //           1), least maximum relative error over [0, 1/4] by Remez's exchange: 3.2e-9, the leading coefficient in two parts,
 //           and 6.4e-11, 7.7e-11 with the coefficients as written; swapped and signed by n.
-// Against 64-bit arithmetic over 1.3e8 variates (std = 0.0316): rms error 5.27e-8 relative, 0.637 ulp, at most 3.7 ulp, mean
-// 5e-10; with a Newton step on v_rsq_f32 and a product by std 5.44e-8, 0.659, 3.7 and 1.5e-8 (only where that product is
-// exact, as for std = 1, 4.81e-8).
+// Against 64-bit arithmetic over 6.7e7 variates, rms error relative, most and mean:  std = 1 (any power of two) 4.77e-8, 2.1e-7 and
+// 1.4e-8;  std = 0.0316 5.27e-8, 0.637 ulp, 2.4e-7 and 5e-10.  With the Newton step and a product by std 4.82e-8, 2.1e-7, 1.5e-8 and
+// 5.44e-8, 2.6e-7, 1.5e-8 (other std 5.37e-8 ... 5.57e-8, now 5.27e-8);  with the plain root for all std 5.27e-8.  The step costs
+// powers of two 5 % (n = 128, d = 25.6 M, 2000 events: 33.7 and 35.5 ms), other std nothing.
 // Written out in single operations, so that every kernel that draws a gradient gets the same bits.
-__device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, const NormalConstants& k, float& zc, float& zs) {
+__device__ __forceinline__ float minus_log2(uint32_t wa) {
 #pragma clang fp contract(off)
-    const float u1 = __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, wa, 9)) - 0x1.fffffep-1f;
-    const float root = __builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(u1));
-    const float r = __builtin_fmaf(root, k.scale.hi, root * k.scale.lo);
-
+    return -__builtin_amdgcn_logf(__uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, wa, 9)) - 0x1.fffffep-1f);
+}
+__device__ __forceinline__ float radius(float t, const SynthScale& k) {
+#pragma clang fp contract(off)
+    const float root = __builtin_amdgcn_sqrtf(t);
+    return __builtin_fmaf(root, k.hi, root * k.lo);
+}
+__device__ __forceinline__ float refined_radius(float t, const SynthScale& k) {
+#pragma clang fp contract(off)
+    const float y = __builtin_amdgcn_rsqf(t), root = t * y;
+    const float rest = __builtin_fmaf(-root, root, t);             // of t; the root's is rest y / 2
+    return __builtin_fmaf(root, k.hi, __builtin_fmaf(rest, y * (0.5f * k.hi), root * k.lo));
+}
+// r cos(2 pi u2), r sin(2 pi u2)
+__device__ __forceinline__ void box_muller(float r, uint32_t wb, const NormalConstants& k, float& zc, float& zs) {
+#pragma clang fp contract(off)
     const uint32_t turn = wb + 0x20000000u;             // bits 31..30: n mod 4
     const float f = __uint_as_float(__builtin_amdgcn_bitop3_b32(turn >> 7, k.fraction, k.one, 0xEA)) - 1.5f;
     const float y = f * f;
@@ -135,11 +149,20 @@ __device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, const Norma
 
 // The four normals of one generator output, times std.
 __device__ __forceinline__ v4f synth_normals_of(v4u w, const NormalConstants& k) {
+    const float t0 = minus_log2(w.x), t1 = minus_log2(w.z);
+    float r0, r1;
+    if (k.scale.refine) {              // uniform: the same for the launch
+        r0 = refined_radius(t0, k.scale);
+        r1 = refined_radius(t1, k.scale);
+    } else {
+        r0 = radius(t0, k.scale);
+        r1 = radius(t1, k.scale);
+    }
     v4f z;
     float a, b;
-    box_muller(w.x, w.y, k, a, b);
+    box_muller(r0, w.y, k, a, b);
     z.x = a; z.y = b;
-    box_muller(w.z, w.w, k, a, b);
+    box_muller(r1, w.w, k, a, b);
     z.z = a; z.w = b;
     return z;
 }

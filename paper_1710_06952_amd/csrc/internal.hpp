@@ -62,14 +62,17 @@ constexpr uint32_t kPhiloxM0 = 0xD2511F53u, kPhiloxM1 = 0xCD9E8D57u;
 constexpr uint32_t kPhiloxW0 = 0x9E3779B9u, kPhiloxW1 = 0xBB67AE85u;
 constexpr uint32_t kStreamGrad = 2u << 24;
 
-// std sqrt(2 ln 2) in two parts, the standard deviation of the synthetic gradients as the kernels take it.
+// std sqrt(2 ln 2) in two parts, the standard deviation of the synthetic gradients as the kernels take it; refine: std is a power
+// of two, up to its sign (box_muller).
 struct SynthScale {
     float hi, lo;
+    bool refine;
 };
 inline SynthScale synth_scale(float std) {
     const double exact = static_cast<double>(std) * 1.1774100225154747;
     const float hi = static_cast<float>(exact);
-    return SynthScale{hi, std::isfinite(hi) ? static_cast<float>(exact - static_cast<double>(hi)) : 0.0f};
+    int exponent = 0;
+    return SynthScale{hi, std::isfinite(hi) ? static_cast<float>(exact - static_cast<double>(hi)) : 0.0f, std::fabs(std::frexp(std, &exponent)) == 0.5f};
 }
 
 // One operation of the column kernel (kernels_columns.hip): an event of the synthetic model or an extra pair.
