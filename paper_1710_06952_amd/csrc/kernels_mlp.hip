@@ -19,6 +19,8 @@
 // model.  The kernels of a round form a serial chain of small grids, so each one
 // keeps all its global loads in flight at once instead of looping over them.  Every
 // reduction has a fixed order: results do not depend on scheduling.
+#include <algorithm>
+
 #include "chains.hpp"
 #include "device_common.hpp"
 #include "internal.hpp"
@@ -532,10 +534,11 @@ __global__ __launch_bounds__(kT) void mlp_dw1_kernel(const MlpParams p) {
 // (11.6 forward, 6.6 softmax, 15.2 here) instead of 296 of 28 (9.8, 6.2, 13.1), 8.36 -> 6.0 ms; 64-256-10 with momentum (n = 16,
 // M = 32, 1024 events) 164 rounds instead of 254, 4.0 -> 2.85 ms.  Chains of four would save another 6 % and 2 % of the rounds,
 // but with momentum their rows do not fit the 128 registers at which four blocks share a compute unit.
-//   grid = (hid / 64, in_tiles + further rows, chains of the round)
-//   blockIdx.y <  in_tiles: one 32 x 64 tile of W1.  The tile of g goes through LDS so that
+//   grid = (hid / 64, in_tiles + further rows, chains of the round), in launches of 65 535 rows at most (more than 2 M
+//   inputs, or 1 M with dense gradients, need several); row = row0 + blockIdx.y:
+//   row <  in_tiles: one 32 x 64 tile of W1.  The tile of g goes through LDS so that
 //                 each thread updates float4 pieces of contiguous rows (16 lanes per 256-byte row);
-//   blockIdx.y >= in_tiles: 1024 consecutive floats of the remainder (or, where the gradients are dense,
+//   row >= in_tiles: 1024 consecutive floats of the remainder (or, where the gradients are dense,
 //                 of all parameters), elementwise.
 struct MlpApplyParams {
     float* X;
@@ -547,6 +550,7 @@ struct MlpApplyParams {
     uint16_t* Xbf16;
     const int32_t* batch_by_op;   // [op][M]
     int in_tiles;            // rows of tiles of W1: ceil(in / 32), or 0 with dense gradients
+    int row0;                // first row of blocks of this launch
     int64_t dense_from;      // the parameters behind them
     float* V;                // momentum buffers (MOM), else nullptr
     float momentum, weight_decay;
@@ -562,9 +566,10 @@ __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyP
     __shared__ __attribute__((aligned(16))) float Gs[kApplyRows][68];      // the tile of g, [input][hidden]
     const UpdateChain chain = chain_at(p.chains + blockIdx.z);
     const int n_ops = chain.n_ops;
-    if (static_cast<int>(blockIdx.y) >= p.in_tiles) {
+    const int block_row = p.row0 + static_cast<int>(blockIdx.y);
+    if (block_row >= p.in_tiles) {
         // elementwise, with dense gradients from the slots
-        const int64_t from = p.dense_from + 4 * kT * (static_cast<int64_t>(blockIdx.y - p.in_tiles) * gridDim.x + blockIdx.x);
+        const int64_t from = p.dense_from + 4 * kT * (static_cast<int64_t>(block_row - p.in_tiles) * gridDim.x + blockIdx.x);
         const int64_t e = from + 4 * threadIdx.x, left = (p.d + 3) / 4 * 4 - from;       // rows are padded to whole vectors
         if (e >= p.d) return;
         const int bytes = left < 4 * kT ? 4 * static_cast<int>(left) : 16 * kT, offset = 16 * threadIdx.x;
@@ -607,7 +612,7 @@ __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyP
         }
         return;
     }
-    const int h0 = blockIdx.x * kTileH, i0 = blockIdx.y * kApplyRows;
+    const int h0 = blockIdx.x * kTileH, i0 = block_row * kApplyRows;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, li = lane & 15, kb = 8 * (lane >> 4);
     const int rr = threadIdx.x >> 4, hq = (threadIdx.x & 15) * 4;      // this thread's rows 16 r + rr, columns hq .. hq + 3
     const int m = threadIdx.x >> 2, part = threadIdx.x & 3;            // staging role: sample, quarter of the tile's columns
@@ -785,11 +790,16 @@ hipError_t launch_mlp_apply_chains(const MlpApplyArgs& a, hipStream_t st) {
     p.dense_from = a.factored ? static_cast<int64_t>(a.in) * a.hid : 0;
     const int64_t bx = a.hid / kTileH, per_row = bx * kT * 4;                   // floats one grid row of blocks covers
     const int64_t by = p.in_tiles + (a.d - p.dense_from + per_row - 1) / per_row;
-    if (by > 65535) return hipErrorInvalidValue;
-    const dim3 grid(static_cast<uint32_t>(bx), static_cast<uint32_t>(by), a.n_chains);
-    if (a.V) hipLaunchKernelGGL(mlp_apply_chains_kernel<true>, grid, dim3(kT), 0, st, p);
-    else hipLaunchKernelGGL(mlp_apply_chains_kernel<false>, grid, dim3(kT), 0, st, p);
-    return hipGetLastError();
+    if (by > 0x7FFFFFFF) return hipErrorInvalidValue;
+    for (int64_t row0 = 0; row0 < by; row0 += 65535) {
+        p.row0 = static_cast<int>(row0);
+        const dim3 grid(static_cast<uint32_t>(bx), static_cast<uint32_t>(std::min<int64_t>(by - row0, 65535)), a.n_chains);
+        if (a.V) hipLaunchKernelGGL(mlp_apply_chains_kernel<true>, grid, dim3(kT), 0, st, p);
+        else hipLaunchKernelGGL(mlp_apply_chains_kernel<false>, grid, dim3(kT), 0, st, p);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_mlp_gradient(const MlpGradArgs& a, hipStream_t st, int* n_launches) {

@@ -159,3 +159,41 @@ def test_extra_pairs_of_workers_without_data(P, mu):
     # an error of 0.1 and an input of 3) of a step of 0.05, 4e-6 an event and ten times that with momentum; 80 events
     assert np.max(np.abs(eng.get_models() - Xr)) <= 80 * (4e-5 if mu else 4e-6)
     eng.close()
+
+
+def test_perceptron_with_more_inputs_than_a_grid_has_rows(P):
+    """Update kernel: 32 inputs (16 with dense gradients) to a row of blocks, 65 535 rows to a launch."""
+    import torch
+    n, dims, gamma = 2, (2_097_160, 64, 2), 1.0
+    d = dims[0] * dims[1] + dims[1] + dims[1] * dims[2] + dims[2]
+    g = ring_graph(n)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(5)
+    scale = torch.full((d,), 0.3, device="cuda:0")
+    scale[:dims[0] * dims[1]] = dims[0] ** -0.5
+    x0 = torch.randn((n, d), device="cuda:0", generator=gen) * scale
+    feats = [torch.randn((1, dims[0]), device="cuda:0", generator=gen).to(torch.bfloat16) for _ in range(n)]
+    labels = [torch.zeros(1, dtype=torch.int32, device="cuda:0") for _ in range(n)]
+    got = []
+    for dense in (False, True):
+        print("chains, perceptron with %d inputs, dense=%d" % (dims[0], dense), flush=True)
+        eng = P.Engine(g, d, "mlp", M=1, gamma=gamma, T_max=0, mlp=dims, dense_gradient=dense, n_slots=1)
+        eng.load_data(feats, labels)
+        eng.h.set_models(x0.data_ptr(), d, on_device=True)
+        eng.run_events({"worker": np.array([0], np.int32), "neighbour": np.array([1], np.int32), "tau": np.zeros(1, np.int32),
+                        "batch_idx": np.zeros((1, 1), np.int32)})
+        eng.h.synchronize()
+        got.append((eng.X[:, :d].clone(), eng.Xbf16[:, :d].clone()))
+        eng.close()
+        del eng
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert torch.equal(got[0][1], got[0][0].to(torch.bfloat16))
+    avg = (x0[0] + x0[1]) * 0.5
+    assert torch.equal(got[0][0][1], avg)
+    step = avg - got[0][0][0]
+    inputs, hidden = dims[0], dims[1]
+    error = step[inputs * hidden:inputs * hidden + hidden]                       # one sample: the gradient of b1 is dH itself
+    assert int((error != 0).sum()) > hidden // 8
+    want = feats[0][0].float()[:, None] * error[None, :]
+    # the product of two bf16 values is exact; the step is what a subtraction from avg leaves: half a unit of the larger of them
+    assert torch.all((step[:inputs * hidden].view(inputs, hidden) - want).abs() <= 2.0 ** -23 * torch.maximum(want.abs(), avg[:inputs * hidden].view(inputs, hidden).abs()) + 2.0 ** -23 * feats[0][0].float().abs()[:, None])
