@@ -550,7 +550,7 @@ struct MlpApplyParams {
     uint16_t* Xbf16;
     const int32_t* batch_by_op;   // [op][M]
     int in_tiles;            // rows of tiles of W1: ceil(in / 32), or 0 with dense gradients
-    int row0;                // first row of blocks of this launch
+    int row0;                // first row of blocks of this launch (MORE), else 0
     int64_t dense_from;      // the parameters behind them
     float* V;                // momentum buffers (MOM), else nullptr
     float momentum, weight_decay;
@@ -559,14 +559,14 @@ struct MlpApplyParams {
 constexpr int kApplyRows = 32;              // inputs of a tile
 constexpr int kPlaces = kMlpChain + 1;      // rows of a chain
 
-template <bool MOM>
+template <bool MOM, bool MORE>
 __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyParams p) {
     __shared__ __attribute__((aligned(16))) uint16_t At[kApplyRows][72];   // inputs transposed:  [i][m], 64 m + pad
     __shared__ __attribute__((aligned(16))) uint16_t Bt[64][72];           // hidden error transposed: [h][m]
     __shared__ __attribute__((aligned(16))) float Gs[kApplyRows][68];      // the tile of g, [input][hidden]
     const UpdateChain chain = chain_at(p.chains + blockIdx.z);
     const int n_ops = chain.n_ops;
-    const int block_row = p.row0 + static_cast<int>(blockIdx.y);
+    const int block_row = (MORE ? p.row0 : 0) + static_cast<int>(blockIdx.y);
     if (block_row >= p.in_tiles) {
         // elementwise, with dense gradients from the slots
         const int64_t from = p.dense_from + 4 * kT * (static_cast<int64_t>(block_row - p.in_tiles) * gridDim.x + blockIdx.x);
@@ -794,8 +794,10 @@ hipError_t launch_mlp_apply_chains(const MlpApplyArgs& a, hipStream_t st) {
     for (int64_t row0 = 0; row0 < by; row0 += 65535) {
         p.row0 = static_cast<int>(row0);
         const dim3 grid(static_cast<uint32_t>(bx), static_cast<uint32_t>(std::min<int64_t>(by - row0, 65535)), a.n_chains);
-        if (a.V) hipLaunchKernelGGL(mlp_apply_chains_kernel<true>, grid, dim3(kT), 0, st, p);
-        else hipLaunchKernelGGL(mlp_apply_chains_kernel<false>, grid, dim3(kT), 0, st, p);
+        if (row0 > 0 && a.V) hipLaunchKernelGGL((mlp_apply_chains_kernel<true, true>), grid, dim3(kT), 0, st, p);
+        else if (row0 > 0) hipLaunchKernelGGL((mlp_apply_chains_kernel<false, true>), grid, dim3(kT), 0, st, p);
+        else if (a.V) hipLaunchKernelGGL((mlp_apply_chains_kernel<true, false>), grid, dim3(kT), 0, st, p);
+        else hipLaunchKernelGGL((mlp_apply_chains_kernel<false, false>), grid, dim3(kT), 0, st, p);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
