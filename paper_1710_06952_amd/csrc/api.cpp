@@ -107,6 +107,9 @@ int drain_profile(adpsgd_t* h) {
 
 namespace {
 
+// 17 to 32 strips, which exchange their sums directly: the slowest for its size.
+bool slow_exchange(int64_t d) { return d > 16 * kStripCols && d <= kStripGroupBlocks * kStripCols; }
+
 // Workers up to which the one-launch path of the linear models (kernels_strips.hip) is the faster one.  An iteration of the
 // strip kernel evaluates as many gradients as there are teams at most (12, 6, 4 and 2 up to M = 16, 32, 64 and 128), so its time
 // per event jumps with their number and does not fall with n, while the kernels of a round take its gradients side by side.
@@ -127,16 +130,15 @@ namespace {
 //   d = 4096  M <= 128   n = 8 1.04, n = 11 0.5 ... 0.8                    n = 8 1.22, n = 10 0.6
 //   d > 8192  M <= 128   n = 5 1.2 ... 1.4, n = 10 1.08; T_max >= 8: 0.7   n = 8 1.0 ... 1.1, n = 11 0.7 ... 1.07; T_max >= 8: 0.78
 // Long staleness lets a round take more gradients at once, where an iteration is held to its teams.
-// A direct exchange between 17 to 32 strips (d = 8192) is the slowest for its size.  Ten strips and fewer keep n = 48 for
+// 17 to 32 strips (d = 8192) have lines of their own (slow_exchange).  Ten strips and fewer keep n = 48 for
 // M <= 32 on denser graphs.  Models and slots that do not fit LDS cost more than the table says.
 int32_t strip_workers(int64_t d, int32_t M, int64_t T_max, bool ring, bool lds_state) {
-    const bool late = T_max >= 8;
-    const bool slow_exchange = d > 16 * kStripCols && d <= kStripGroupBlocks * kStripCols;
+    const bool late = T_max >= 8, slow = slow_exchange(d);
     int32_t n;
     if (M <= 8) {
         if (d < 1024) n = ring ? 28 : 36;
         else if (d <= 2048) n = ring ? 34 : 40;
-        else if (slow_exchange) n = ring ? 50 : 64;
+        else if (slow) n = ring ? 50 : 64;
         else if (M <= 3) n = ring ? 46 : 54;
         else n = ring ? 60 : 76;
     } else if (d <= 2048) {
@@ -145,7 +147,7 @@ int32_t strip_workers(int64_t d, int32_t M, int64_t T_max, bool ring, bool lds_s
         else if (M <= 32) n = shorter ? (ring ? 12 : 16) : (ring ? 16 : 24);
         else if (M <= 64) n = shorter ? 8 : 16;
         else n = shorter ? 5 : 8;
-    } else if (slow_exchange) {
+    } else if (slow) {
         n = M <= 16 ? (late ? 24 : ring ? 34 : 44) : M <= 32 ? (ring ? (late ? 10 : 14) : 16) : M <= 48 && !late ? 10 : M <= 64 ? 6 : late ? 4 : 5;
     } else if (d <= 16 * kStripCols) {
         if (M <= 16) n = ring ? 40 : 64;
@@ -518,21 +520,28 @@ bool can_run_strips(const adpsgd_t* h) {
     return true;
 }
 
-// A call of few events: the cooperative launch, the assembly of its blocks and the first iterations take 44 us, where a call in
-// rounds takes 14 and 2.6 for each launch (plus the minibatch rows, read once or twice).  Measured among other calls, strips /
-// rounds in us:  n = 8, d = 1024, M = 32: 1 event 47 / 23, 8 events 55 / 38, 16 events 66 / 63, 32 events 84 / 116;  n = 16,
-// d = 4096, M = 8: 4 events 50 / 40, 8 events 54 / 54, 16 events 60 / 82;  n = 16, d = 7395, M = 6, T_max = 100, where most
-// reads of a short call precede its first update and share their launches: 23 events 83 / 48.
+// A call of few events: the cooperative launch, the assembly of its blocks and the first iterations take 50 us, where a call in
+// rounds takes 14 and 2.8 for each round with updates, and for each with gradients 8.6 in one pass over the rows, 7 and 11.6 in two
+// and three launches, or on short models, whose gradients are a block each, 3.8 and what the block takes to read the rows of one.
+// Fitted to 290 such calls, each by both routes (K 1 ... 100, M 1 ... 128, d 300 ... 65 536, T_max 1 ... 40): on these and 280 others
+// it takes 1.004 times as long as the better route in the mean and 1.24 at most; the estimate before it, which counted three
+// launches and two reads of the rows for every gradient of a long model and no time for the single blocks, 1.026 and 2.5 (rounds
+// always: 1.28, one launch always: 1.26).  Strips / rounds in us:  n = 8, d = 2000, M = 64, 64 events 166 / 412;  n = 16, d = 65 536, M = 16, 12
+// events 87 / 64;  n = 8, d = 1024, M = 32: 1 event 47 / 23, 16 events 66 / 63, 32 events 84 / 116;  n = 16, d = 7395, M = 6,
+// T_max = 100, where most reads of a short call precede its first update and share their launches: 23 events 83 / 48.
 // Calls that are cut out of one schedule (looking ahead, or without stale reads at all) keep the handle's route, up to 25 us
 // slower for a few events, so that the cut does not change the order of any sum.
 bool small_call(const adpsgd_t* h, const EventCall& c) {
     if (c.K > 128 || h->o.T_max == 0 || c.s->lookahead > 0 || !h->pending.empty()) return false;
-    const int32_t per_set = h->d <= 2048 ? 1 : c.lin_factored ? 2 : 3, teams = strip_teams(c.M);
-    int64_t launches = 0;
-    for (int32_t r = 0; r < c.plan.n_rounds; ++r) launches += (c.u_off[r + 1] > c.u_off[r]) + per_set * (c.r_off[r + 1] > c.r_off[r]);
-    const double row_us = 4.0 * c.M * static_cast<double>(h->d) * static_cast<double>(c.K) / 6.0e6;
-    const double per_event = teams == 12 ? 0.9 : teams == 6 ? 1.4 : teams == 4 ? 2.2 : 4.5;
-    return 14.0 + 2.6 * static_cast<double>(launches) + row_us * (per_set == 1 ? 1.0 : 2.0) < 44.0 + per_event * static_cast<double>(c.K) + row_us;
+    const bool short_model = h->d <= 2048;
+    const double events = static_cast<double>(c.K), gradient_mb = 4.0e-6 * c.M * static_cast<double>(h->d);
+    const double per_set = short_model ? 3.8 + 17.0 * gradient_mb : c.onepass ? 8.6 : c.lin_factored ? 7.0 : 11.6;
+    const double per_mb = short_model ? 0.0 : c.onepass ? 0.25 : 2.0;
+    double rounds = 14.0 + per_mb * events * gradient_mb;
+    for (int32_t r = 0; r < c.plan.n_rounds; ++r) rounds += (c.u_off[r + 1] > c.u_off[r] ? 2.8 : 0.0) + (c.r_off[r + 1] > c.r_off[r] ? per_set : 0.0);
+    const int32_t teams = strip_teams(c.M);
+    const double per_event = teams == 12 ? 0.8 : (teams == 6 ? 1.1 : teams == 4 ? 1.7 : 3.5) * (slow_exchange(h->d) ? strip_blocks(h->d) / 16.0 : 1.0);
+    return rounds < 50.0 + (per_event + 0.3 * gradient_mb) * events;
 }
 
 // Validation, choice of paths, plan of rounds, counting sort of the operations by round.

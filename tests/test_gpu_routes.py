@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
-from workloads import logreg_data, lsq_data, random_extra_pairs, ring_graph
+from workloads import logreg_data, lsq_data, random_extra_pairs, random_regular4_graph, ring_graph
 
 pytestmark = pytest.mark.gpu
 
@@ -78,4 +78,29 @@ def test_unknown_route_is_refused():
     with pytest.raises(P.AdpsgdError) as ei:
         eng.h.set_route(2)
     assert ei.value.code == -1
+    eng.close()
+
+
+# on both sides of the line, where the two routes differ by 1.3 to 2.5 times
+@pytest.mark.parametrize("model,n,d,M,K,T,one", [("lsq", 8, 2000, 64, 64, 3, True), ("logreg", 8, 2000, 96, 64, 3, True), ("lsq", 8, 1024, 48, 48, 1, True),
+                                                 ("lsq", 16, 65_536, 16, 12, 8, False), ("logreg", 6, 8192, 48, 16, 8, False), ("lsq", 8, 4096, 8, 2, 3, False)])
+def test_route_of_short_calls(model, n, d, M, K, T, one):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1710_06952_amd as P
+    print("route of a short call %s n=%d d=%d M=%d K=%d" % (model, n, d, M, K), flush=True)
+    g = random_regular4_graph(n, 1) if (d, n) == (65_536, 16) else ring_graph(n)
+    rows = max(M, 32)
+    feats, targs, _ = lsq_data(n, rows, d, seed=5, feature_var=1.0 / d) if model == "lsq" else logreg_data(n, rows, d, seed=5)
+    sched = oracle.make_schedule(g, K, seed=5, T_max=T, M=M, rows=[rows] * n)
+    lam = 1e-3 if model == "logreg" else 0.0
+    eng = P.Engine(g, d, model, M=M, gamma=0.1, lam=lam, T_max=T, verify_plan=True)
+    eng.load_data(feats, targs)
+    eng.set_models(np.zeros(d, np.float32))
+    eng.run_events(sched)
+    assert (eng.get_stats()["grad_launches"] == 0) == one
+    ref = np.zeros((n, d), np.float32)
+    oracle.run_events(ref, sched, oracle.MODEL_LSQ if model == "lsq" else oracle.MODEL_LOGREG, 0.1, M=M, gscale=1.0 / M, lam=lam, features=feats, targets=targs)
+    assert rel_err(eng.get_models(), ref) <= TOL
     eng.close()
