@@ -39,7 +39,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0   # MI355X published HBM3E bandwidth
 
 
-KERNEL_SOURCES = ("device_common.hpp", "kernels_fused.hip", "kernels_grad_linear.hip", "kernels_mlp.hip")
+KERNEL_SOURCES = ("chains.hpp", "device_common.hpp", "kernels_fused.hip", "kernels_grad_linear.hip", "kernels_mlp.hip", "kernels_onepass.hip")
 
 
 def kernel_sources_sha256():

@@ -14,9 +14,12 @@
 // gradient (the third, 103 of 11 us) also their address translation, about 40 cycles per row and compute unit.
 // An iteration evaluates a gradient per team.  With half of them, so that all rows are requested an iteration ahead, the three
 // took 72, 217 and 203 iterations and 0.28, 1.07 and 1.70 ms: most calls run out of teams before they run out of events that
-// could go on.  Where the events do not fill the teams the wider records cost up to 3 % (n = 8, d = 40 000, M = 8: 583 -> 602 us
-// for 107 iterations); two sets of rows per wavefront for M <= 8 were slower (0.88 ms for the second: a wavefront that works on
-// one set waits for the rows of the other).
+// could go on.  Where the events do not fill the teams an iteration takes 2 ... 9 % longer than it did then (n = 8, d = 40 000,
+// M = 8, 400 events 550 -> 565 us;  n = 5, d = 20 001, M = 16, T_max = 0, 400 events 965 -> 1040).  That is not the wider records (with
+// half as many evaluations and the present code 1034) but the polls of two sizes, whose code takes scalar registers
+// from the helpers' chain: with one size of four words 970 there, and 829 for 800 us in the second of the above.  Two sets
+// of rows per wavefront for M <= 8 were slower (0.88 ms for the second: a wavefront that works on one set waits for the rows of
+// the other).
 //
 // A block has 12 main wavefronts in `teams` teams, each team with the rows of one gradient in its registers, and 4
 // helper wavefronts (one thread per column, and one per minibatch sample).  An iteration has three phases:

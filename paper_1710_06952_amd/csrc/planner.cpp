@@ -270,7 +270,6 @@ void chain_rounds(const std::vector<ColumnPair>& pairs, const std::vector<int64_
     for (size_t r = 0; r + 1 < offset.size(); ++r) {
         parent.clear();
         members.clear();
-        std::fill(chain_of.begin(), chain_of.end(), -1);
         for (int64_t q = offset[r]; q < offset[r + 1]; ++q) {
             int32_t a = chain_of[pairs[q].i], b = chain_of[pairs[q].j];
             if (a >= 0) a = root(a);
@@ -296,6 +295,7 @@ void chain_rounds(const std::vector<ColumnPair>& pairs, const std::vector<int64_
             out.order.insert(out.order.end(), m.begin(), m.end());
         }
         out.round.push_back(static_cast<int64_t>(out.first.size()));
+        for (int64_t q = offset[r]; q < offset[r + 1]; ++q) chain_of[pairs[q].i] = chain_of[pairs[q].j] = -1;      // few of the rows, for many rounds
     }
     out.first.push_back(static_cast<int64_t>(out.order.size()));
 }
