@@ -865,7 +865,7 @@ struct ColumnPlan {
 // 64 / q operations in a batch: narrow strips let more wavefronts share a compute unit, wide ones lose less to batches
 // that the dependences leave half empty.  The estimate below (cycles of a SIMD; measured at n = 128, d = 25.6 M: a
 // batch costs a wavefront about 1500 cycles from its operands to its results, and a SIMD with several of them one per
-// 350) is compared for every width whose strips leave at least eight wavefronts to a compute unit.  Below that the
+// 350, which the lines below, drawn at 420, leave as a margin) is compared for every width whose strips leave at least eight wavefronts to a compute unit.  Below that the
 // rounds are the better route: 32 KB strips (n = 500, four quads) leave one wavefront per SIMD to hide that latency.
 //
 // The rounds are also the better route for a call that touches its rows once or twice: they move 16 (24) bytes per
@@ -876,9 +876,7 @@ struct ColumnPlan {
 // 29 events 199 / 128, 117 events 461 / 506.  And a launch of its own costs 4.5 us where a round costs 2.5 at least, so a call
 // of a single round stays one (one event: 25 / 22), and what cannot gain is turned away before the strips are laid out.
 // Of 700 set-ups measured (n 4 ... 320, d 1000 ... 16 M, up to 5 n events, with and without momentum) the line takes none to
-// the slower route by more than 5 %, where all to the column kernel lost up to 2.0 times (drawn with 420 cycles a batch, since
-// when a batch takes 350: of 250 set-ups measured again none changes its route with the one or the other, and what is left is 1.02 in
-// the mean and 1.3 at most, calls of a few rounds of 20 ... 90 us).
+// the slower route by more than 5 %, where all to the column kernel lost up to 2.0 times.
 void plan_columns(adpsgd_t* h, const EventCall& c, ColumnPlan& out) {
     const adpsgd_schedule_t* s = c.s;
     if (h->d > (1ll << 34)) return;                 // the quad has to fit one word of the generator's counter
@@ -905,7 +903,7 @@ void plan_columns(adpsgd_t* h, const EventCall& c, ColumnPlan& out) {
             }
     }
     const int64_t n_vec = (h->d + 3) / 4, n_rows = static_cast<int64_t>(out.rows.size());
-    constexpr double kIssue = 350.0, kLatency = 1500.0, kSimds = 1024.0, kLdsPerCu = 160.0 * 1024.0;
+    constexpr double kIssue = 420.0, kLatency = 1500.0, kSimds = 1024.0, kLdsPerCu = 160.0 * 1024.0;
     constexpr double kCycle = 1.0 / 2.4e9, kRoundRate = 6.4e12, kLaunch = 4.5e-6, kRound = 2.5e-6;
     const double state = static_cast<double>(h->n) * h->o.ldx * 4.0 * (h->o.V ? 2.0 : 1.0), row_bytes = 4.0 * static_cast<double>(h->d);
     const double moved = static_cast<double>(n_rows) * row_bytes * (h->o.V ? 4.0 : 2.0), rate = state > kStreamingThreshold ? 0.3e12 : 0.45e12;
