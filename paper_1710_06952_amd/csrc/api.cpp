@@ -863,9 +863,12 @@ struct ColumnPlan {
 
 // The operations and the width of the strips.  A strip of q quads takes rows * 16 q bytes of LDS and leaves room for
 // 64 / q operations in a batch: narrow strips let more wavefronts share a compute unit, wide ones lose less to batches
-// that the dependences leave half empty.  The estimate below (cycles of a SIMD; measured at n = 128, d = 25.6 M: a
-// batch costs a wavefront about 1500 cycles from its operands to its results, and a SIMD with several of them one per
-// 350, which the lines below, drawn at 420, leave as a margin) is compared for every width whose strips leave at least eight wavefronts to a compute unit.  Below that the
+// that the dependences leave half empty.  The estimate below is in cycles of a SIMD: a batch costs a wavefront about 1500
+// from its operands to its results, and a SIMD with several of them one per 350.  The constant stays at 420: with 350 the
+// route is the same for nearly all of 250 set-ups, but some take another width, which loses more often than it
+// gains (n = 6, d = 262 923, 254 events in a ring 88 -> 135 us; n = 13, d = 9109, 845 events 114 -> 120; n = 53,
+// d = 1.44 M, 72 events 199 -> 163).  The cost is compared for every width whose strips leave at least eight wavefronts to
+// a compute unit.  Below that the
 // rounds are the better route: 32 KB strips (n = 500, four quads) leave one wavefront per SIMD to hide that latency.
 //
 // The rounds are also the better route for a call that touches its rows once or twice: they move 16 (24) bytes per
