@@ -866,7 +866,7 @@ struct ColumnPlan {
 // that the dependences leave half empty.  The estimate below is in cycles of a SIMD: a batch costs a wavefront about 1500
 // from its operands to its results, and a SIMD with several of them one per 350.  The constant stays at 420: with 350 the
 // route is the same for nearly all of 250 set-ups, but some take another width, which loses more often than it
-// gains (n = 6, d = 262 923, 254 events in a ring 88 -> 135 us; n = 13, d = 9109, 845 events 114 -> 120; n = 53,
+// gains (n = 6, d = 262 923, 254 events in a ring 91 -> 135 us; n = 53,
 // d = 1.44 M, 72 events 199 -> 163).  The cost is compared for every width whose strips leave at least eight wavefronts to
 // a compute unit.  Below that the
 // rounds are the better route: 32 KB strips (n = 500, four quads) leave one wavefront per SIMD to hide that latency.

@@ -110,7 +110,7 @@ __device__ __forceinline__ NormalConstants normal_constants(SynthScale s) {
 // Against 64-bit arithmetic over 6.7e7 variates, rms error relative, most and mean:  std = 1 (any power of two) 4.77e-8, 2.1e-7 and
 // 1.4e-8;  std = 0.0316 5.27e-8, 0.637 ulp, 2.4e-7 and 5e-10.  With the Newton step and a product by std 4.82e-8, 2.1e-7, 1.5e-8 and
 // 5.44e-8, 2.6e-7, 1.5e-8 (other std 5.37e-8 ... 5.57e-8, now 5.27e-8);  with the plain root for all std 5.27e-8.  The step costs
-// powers of two 5 % (n = 128, d = 25.6 M, 2000 events: 33.7 and 35.5 ms), other std nothing.
+// powers of two 6 % (n = 128, d = 25.6 M, 2000 events: 32.0 and 34.1 ms), other std nothing.
 // Written out in single operations, so that every kernel that draws a gradient gets the same bits.
 __device__ __forceinline__ float minus_log2(uint32_t wa) {
 #pragma clang fp contract(off)

@@ -14,7 +14,7 @@
 // of the two products of the second depend either on the quad alone or on the event alone.  The quad's part is
 // computed once per wavefront, the event's part once on the host (ColumnOp); the rest is in vector registers, since an
 // operand in a scalar one nearly doubles the time of an instruction (see device_common.hpp).  Measured at n = 128, d = 25.6 M
-// on the ring, 2000 events per call: 32.9 ms (39.7 with keys in scalar registers, one batch per turn of the loop and a Newton
+// on the ring, 2000 events per call: 32.1 ms (39.7 with keys in scalar registers, one batch per turn of the loop and a Newton
 // step on the root), 128.8 ms in rounds of the streaming kernel; an operation takes a SIMD 168 ns per 64 quads, of which the
 // instructions issue for about 145.  n = 32, d = 3.0 M with momentum, 500 events: 1.34 ms (1.62 before), 6.18 in rounds.
 #include <algorithm>
@@ -43,8 +43,10 @@ __device__ __forceinline__ v4u philox_rest(uint32_t hq, uint32_t lq, const Colum
     return philox4x32_rounds<8>(static_cast<uint32_t>(pb >> 32) ^ op.b, static_cast<uint32_t>(pb), lq ^ op.c, op.d, keys);
 }
 
-// grid: one wavefront per kQuads float4 columns; AVERAGES: some operations average only
-template <int kQuads, bool MOM, bool AVERAGES>
+// grid: one wavefront per kQuads float4 columns; AVERAGES: some operations average only; REFINE: SynthScale's, a kernel of its own
+// since a branch in the middle of the generator keeps its two halves from overlapping (n = 13, d = 9109, 845 events 119.5 us with
+// the branch, 114.5 without; n = 128, d = 25.6 M, 2000 events 33.7 and 32.1 ms)
+template <int kQuads, bool MOM, bool AVERAGES, bool REFINE>
 __global__ __launch_bounds__(256) void column_events_kernel(const ColumnParams p) {
     constexpr int P = 64 / kQuads;
     extern __shared__ __attribute__((aligned(16))) v4f strips[];
@@ -83,7 +85,7 @@ __global__ __launch_bounds__(256) void column_events_kernel(const ColumnParams p
     const uint64_t mq = static_cast<uint64_t>(kPhiloxM0) * static_cast<uint32_t>(q);       // d <= 2^34: the quad fits a word
     const uint32_t hq = static_cast<uint32_t>(mq >> 32), lq = static_cast<uint32_t>(mq);
     const PhiloxKeys<8> keys = philox_keys<8, true>(p.key0 + 2u * kPhiloxW0, p.key1 + 2u * kPhiloxW1);
-    const NormalConstants normal = normal_constants<true>(p.synth);
+    const NormalConstants normal = normal_constants<true>(SynthScale{p.synth.hi, p.synth.lo, REFINE});
     const float mu = MOM ? in_vector(p.momentum) : 0.0f, wd = MOM ? in_vector(p.weight_decay) : 0.0f;
     const int v_at = p.n_rows * kQuads;                    // from a row of the strip to its momentum buffer
     auto execute = [&](const ColumnOp& op) {
@@ -143,6 +145,11 @@ __global__ __launch_bounds__(256) void column_events_kernel(const ColumnParams p
     }
 }
 
+template <int kQuads, bool MOM, bool AVERAGES>
+void launch_columns(const ColumnParams& p, dim3 grid, dim3 block, size_t lds, hipStream_t st) {
+    if (p.synth.refine) hipLaunchKernelGGL((column_events_kernel<kQuads, MOM, AVERAGES, true>), grid, block, lds, st, p);
+    else hipLaunchKernelGGL((column_events_kernel<kQuads, MOM, AVERAGES, false>), grid, block, lds, st, p);
+}
 // Four wavefronts to a block, one to each SIMD, as far as 64 KB of LDS go.  Measured with 1 / 2 / 3 / 4 / 5 / 8 / 10 / 16 at
 // n = 128, d = 25.6 M, 2000 events: 35.5 / 34.9 / 35.1 / 33.9 / 34.8 / 34.3 / 35.7 / 36.9 ms; at n = 32, d = 3.0 M with momentum,
 // 500 events: 1.37 / 1.40 / 1.49 / 1.36 / 1.40 / 1.38 / 1.43 / 1.56.
@@ -153,10 +160,11 @@ hipError_t launch_quads(const ColumnParams& p, bool averages, hipStream_t st) {
     const int64_t blocks = ((p.n_vec + kQuads - 1) / kQuads + waves - 1) / waves;
     if (waves < 1 || blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
     const dim3 grid(static_cast<uint32_t>(blocks)), block(64 * waves);
-    if (p.V && averages) hipLaunchKernelGGL((column_events_kernel<kQuads, true, true>), grid, block, strip * waves, st, p);
-    else if (p.V) hipLaunchKernelGGL((column_events_kernel<kQuads, true, false>), grid, block, strip * waves, st, p);
-    else if (averages) hipLaunchKernelGGL((column_events_kernel<kQuads, false, true>), grid, block, strip * waves, st, p);
-    else hipLaunchKernelGGL((column_events_kernel<kQuads, false, false>), grid, block, strip * waves, st, p);
+    const size_t lds = static_cast<size_t>(strip * waves);
+    if (p.V && averages) launch_columns<kQuads, true, true>(p, grid, block, lds, st);
+    else if (p.V) launch_columns<kQuads, true, false>(p, grid, block, lds, st);
+    else if (averages) launch_columns<kQuads, false, true>(p, grid, block, lds, st);
+    else launch_columns<kQuads, false, false>(p, grid, block, lds, st);
     return hipGetLastError();
 }
 

@@ -84,3 +84,28 @@ def test_calls_without_extra_pairs(P, K, d, mu):
     assert np.array_equal(got[0][0], got[1][0])
     if mu:
         assert np.array_equal(got[0][1], got[1][1])
+
+
+# a standard deviation that is a power of two has kernels of its own: each strip width, with and without momentum and extra pairs
+@pytest.mark.parametrize("extra", [False, True])
+@pytest.mark.parametrize("n,d,K,mu", [(5, 17, 40, 0.9), (6, 257, 60, 0.0), (64, 1030, 300, 0.0), (128, 515, 700, 0.9), (160, 70, 900, 0.9),
+                                      (320, 66, 1500, 0.0), (6, 262_923, 60, 0.0), (13, 9109, 300, 0.9), (16, 2_000_001, 64, 0.0)])
+def test_columns_with_a_power_of_two(P, n, d, K, mu, extra):
+    print("columns n=%d d=%d K=%d mu=%g extra=%d" % (n, d, K, mu, extra), flush=True)
+    g = ring_graph(n) if n % 2 else random_regular4_graph(n, 3)
+    sched = oracle.make_schedule(g, K, seed=6, T_max=4)
+    if extra:
+        sched["extra_pairs"] = random_extra_pairs(g, sched["worker"], sched["neighbour"], max_extra=1, seed=2)
+    x0 = np.random.default_rng(3).standard_normal((n, d)).astype(np.float32)
+    out = []
+    for rounds in (False, True):
+        eng = P.Engine(g, d, "synth", gamma=0.1, T_max=4, synth_std=0.5, synth_seed=11, momentum=mu, weight_decay=1e-3 if mu else 0.0,
+                       rounds=rounds)
+        eng.set_models(x0, broadcast=False)
+        eng.run_events(sched)
+        out.append((eng.get_models(), eng.get_momentum() if mu else None, eng.get_stats()["fused_launches"]))
+        eng.close()
+    assert out[0][2] == 1 < out[1][2]
+    assert np.array_equal(out[0][0], out[1][0])
+    if mu:
+        assert np.array_equal(out[0][1], out[1][1])
