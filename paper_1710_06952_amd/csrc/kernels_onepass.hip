@@ -21,11 +21,13 @@
 // samples is the point itself where losses are wanted (|x^|^2 of logistic regression): its word is awaited for that reason alone.
 //
 // The launch is not cooperative: nothing makes sure that all blocks of a group are resident, while other work of the device
-// (another handle's call in one launch, say) holds compute units.  A block that waits longer than a limit, or finds that another
-// one of its group did, leaves the exchange and the group's gradients are executed in shares that need no more blocks than there
-// are (take_tickets): the blocks that are there claim the dot products of a strip, the coefficients, the combination of a strip
-// one after the other, in an order in which a share waits for earlier ones only, and these belong to blocks that run.  The sums
-// are formed in the same order, so a gradient has the same bits whichever way it goes.
+// (another handle's call in one launch, say) holds compute units.  A block that waits longer than a limit leaves the exchange and
+// the group's gradients are executed in shares that need no more blocks than there are (take_tickets): the blocks that are there
+// claim the dot products of a strip, the coefficients, the combination of a strip one after the other, in an order in which a
+// share waits for earlier ones only, and these belong to blocks that run.  The sums are formed in the same order, so a gradient
+// has the same bits whichever way it goes.  A block that comes later finds out by waiting itself: to ask at the start whether the
+// others have left holds up the first rows (n = 23, d = 67 471, M = 10, 392 events 911 us, 895 without), to ask while it waits
+// lengthens the loop that waits (902; n = 32, M = 8, d = 1 M, synchronous, 10 iterations 3373, 3353 without).
 #include <algorithm>
 
 #include "chains.hpp"
@@ -53,23 +55,9 @@ __device__ __forceinline__ v4f zero_beyond(v4f v, int64_t e, int64_t d) {
     if (e + 3 >= d) v.w = 0.0f;
     return v;
 }
-// Whether the count of a launch (its number, the count) has begun: the same for the wavefront.
-__device__ __forceinline__ bool counts(const unsigned long long* word, uint32_t launch) {
-    return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 32))) == launch;
-}
-// How long a wait lasts: until `until`, from `early` on only as long as the count of the launch has not begun.
-struct Patience {
-    uint64_t early, until;
-    const unsigned long long* count;
-    uint32_t launch;
-    __device__ __forceinline__ bool over() const {
-        const uint64_t now = wall_clock64();
-        return now >= until || (now >= early && counts(count, launch));
-    }
-};
 // The word at[u] of gradient seq, for the lanes that want one; false when the time is up.
 template <int N>
-__device__ __forceinline__ bool take_words(const unsigned long long* base, const int (&at)[N], uint32_t seq, const Patience& wait, float (&v)[N]) {
+__device__ __forceinline__ bool take_words(const unsigned long long* base, const int (&at)[N], uint32_t seq, uint64_t until, float (&v)[N]) {
     unsigned long long w[N];
     for (;;) {
         bool complete = true;
@@ -78,7 +66,7 @@ __device__ __forceinline__ bool take_words(const unsigned long long* base, const
 #pragma unroll
         for (int u = 0; u < N; ++u) complete &= at[u] < 0 || static_cast<uint32_t>(w[u] >> 32) == seq;
         if (__all(complete)) break;
-        if (wait.over()) return false;
+        if (wall_clock64() >= until) return false;
     }
 #pragma unroll
     for (int u = 0; u < N; ++u) v[u] = __uint_as_float(static_cast<uint32_t>(w[u]));
@@ -100,9 +88,6 @@ __device__ __forceinline__ v2f coefficient(const OnePassArgs& a, float dot, floa
     return v2f{coef * a.gscale, loss};
 }
 
-// Of the constant clock: how long a block waits in the exchange before it asks whether others of its group have left it.  Not
-// before the first rows, whose requests it would hold up (n = 23, d = 67 471, M = 10, 392 events: 911 us, 893 so).
-constexpr uint64_t kEarlyTicks = 20 * 100;
 constexpr uint64_t kShareTicks = 10ull * 1000 * 1000 * 100;      // of the constant clock: how long a share waits for one that is running
 
 template <int kChunks>
@@ -185,7 +170,7 @@ __device__ __forceinline__ float strip_sum(const OnePassParams& p, const float (
 }
 // Sums over the strips of samples m, m + step, ... below samples, kN at most, by a wavefront; false when the time is up.
 template <int kN>
-__device__ __forceinline__ bool take_sums(const unsigned long long* sums, int m, int step, int samples, int S, uint32_t seq, const Patience& wait, float (&dot)[kN]) {
+__device__ __forceinline__ bool take_sums(const unsigned long long* sums, int m, int step, int samples, int S, uint32_t seq, uint64_t until, float (&dot)[kN]) {
     constexpr int kLines = kOnePassMaxStrips / 64;
     const int lane = threadIdx.x & 63;
     int at[kN * kLines];
@@ -194,7 +179,7 @@ __device__ __forceinline__ bool take_sums(const unsigned long long* sums, int m,
     for (int i = 0; i < kN; ++i)
 #pragma unroll
         for (int u = 0; u < kLines; ++u) at[i * kLines + u] = m + i * step < samples && lane + 64 * u < S ? (m + i * step) * S + lane + 64 * u : -1;
-    const bool there = take_words(sums, at, seq, wait, v);
+    const bool there = take_words(sums, at, seq, until, v);
 #pragma unroll
     for (int i = 0; i < kN; ++i) {
         dot[i] = 0.0f;
@@ -285,7 +270,7 @@ __device__ __forceinline__ uint32_t count_up(unsigned long long* word) {       /
 // its combinations have taken them;  combinations for the coefficients.  The rows are read twice.  Blocks of the group that
 // have stayed in the exchange write the same bits to the same places.  A wait is bounded all the same: the launch is then lost.
 // Logistic regression, n = 32, d = 65 536, M = 128, 100 events (0.95 ms by itself) beside another handle's call in one launch
-// that holds 16 (157) compute units for 5 ms: done in 3.9 (4.3) ms;  when a block that had waited in vain computed the dot
+// that holds 16 (157) compute units for 5 ms: done in 4.0 (4.1) ms;  when a block that had waited in vain computed the dot
 // products of whole rows by itself, for the rest of the launch, 88 (97);  three launches a round, which need no block to be
 // there, 2.2 (2.5), of which the other call then took more.  All in shares from the start (limit 0) and without other work: 3.1 ms.
 // A function of its own with its arguments in memory, since the kernel has no registers to spare for it.
@@ -315,7 +300,6 @@ __device__ __attribute__((noinline)) void take_tickets(const OnePassParams* para
         const int strip = share < S ? share : share - S - 1;
         const uint32_t seq = a.seq0 + static_cast<uint32_t>(q);
         const uint64_t until = wall_clock64() + kShareTicks;
-        const Patience wait{until, until, words.tickets, launch};
         const GradOp op = a.ops[q];
         if (tid < kOnePassMaxM) s.idx[0][tid] = tid < M ? a.batch_idx[static_cast<int64_t>(op.event) * M + tid] : 0;
         __syncthreads();
@@ -343,7 +327,7 @@ __device__ __attribute__((noinline)) void take_tickets(const OnePassParams* para
                 put_parts<kRows>(a, at, r0, v, s.part);
             }
             put_square(p, at, x, s.part);
-            if (i > 0 && wave < word_waves) there = take_words(words.share_coefs, word_at, seq - groups, wait, word);
+            if (i > 0 && wave < word_waves) there = take_words(words.share_coefs, word_at, seq - groups, until, word);
             if (!there && lane == 0) s.lost = 1;
             __syncthreads();
             if (s.lost != 0) break;
@@ -368,7 +352,7 @@ __device__ __attribute__((noinline)) void take_tickets(const OnePassParams* para
                     const int m = m0 + u * kOnePassWaves;
                     target[u] = m < M ? static_cast<const float*>(op.targets)[s.idx[0][m]] : 0.0f;
                 }
-                there = take_sums(words.share_sums, m0, kOnePassWaves, p.samples, S, seq, wait, dot);
+                there = take_sums(words.share_sums, m0, kOnePassWaves, p.samples, S, seq, until, dot);
 #pragma unroll
                 for (int u = 0; u < kAtOnce; ++u) {
                     const int m = m0 + u * kOnePassWaves;
@@ -386,7 +370,7 @@ __device__ __attribute__((noinline)) void take_tickets(const OnePassParams* para
         } else {
             const StripPlace at(p, strip, kChunks);
             if (wave < word_waves) {
-                there = take_words(words.share_coefs, word_at, seq, wait, word);
+                there = take_words(words.share_coefs, word_at, seq, until, word);
                 if (tid < M) s.coef[tid] = word[0];
             }
             if (!there && lane == 0) s.lost = 1;
@@ -473,13 +457,12 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
 
         // ---- the exchange
         if (tid < p.samples) put_word(words.sums, tid * S + strip, strip_sum(p, s.part, tid), seq);
-        const uint64_t now = wall_clock64();
-        const Patience wait{now + kEarlyTicks, now + a.wait_ticks, words.tickets, a.seq0};
+        const uint64_t until = wall_clock64() + a.wait_ticks;
         bool there = a.wait_ticks > 0;
         for (int m = strip + S * wave; there && m < p.samples; m += S * kOnePassWaves) {
             const float target = m < M ? static_cast<const float*>(op.targets)[s.idx[turn][m]] : 0.0f;
             float dot[1];
-            there = take_sums(words.sums, m, 0, p.samples, S, seq, wait, dot);
+            there = take_sums(words.sums, m, 0, p.samples, S, seq, until, dot);
             if (there && lane == 0) {
                 const v2f r = finish_sample(a, m, dot[0], target);
                 put_word(words.coefs, m, r.x, seq);
@@ -490,14 +473,14 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
         if (there && wave < (awaited + 63) / 64) {
             const int word_at[1] = {tid < awaited ? tid : -1};
             float v[1];
-            there = take_words(words.coefs, word_at, seq, wait, v);
+            there = take_words(words.coefs, word_at, seq, until, v);
             if (tid < M) s.coef[tid] = v[0];
         }
         if (there && a.loss && strip == 0 && wave >= 4 && wave - 4 < (p.samples + 63) / 64) {
             const int m = tid - 256;
             const int word_at[1] = {m < p.samples ? m : -1};
             float v[1];
-            there = take_words(words.losses, word_at, seq, wait, v);
+            there = take_words(words.losses, word_at, seq, until, v);
             if (m < p.samples) s.loss[m] = v[0];
         }
         if (!there && lane == 0) s.late = 1;
