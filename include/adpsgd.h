@@ -227,7 +227,7 @@ int adpsgd_set_route(adpsgd_t* h, int32_t route);
  *                   compute units for longer than this, one block executes the call by itself, which is slow but gives the
  *                   same results within rounding.  0: always so.  Default 10 000 000.  The gradients that are evaluated
  *                   in one pass over the minibatch rows (rounds and synchronous iterations of linear models) wait for
- *                   each other too, for this long or 100 us if that is less; then the blocks that are there share out the
+ *                   each other too, for this long or 300 us if that is less; then the blocks that are there share out the
  *                   work of all, at two to three times the cost, with the same bits.
  *                   Outside [0, 2^31): ADPSGD_ERR_ARG.
  *   lose_exchange   Once all blocks are on the device they exchange partial sums.  One that does not find a sum after 2^21

@@ -270,7 +270,7 @@ __device__ __forceinline__ uint32_t count_up(unsigned long long* word) {       /
 // its combinations have taken them;  combinations for the coefficients.  The rows are read twice.  Blocks of the group that
 // have stayed in the exchange write the same bits to the same places.  A wait is bounded all the same: the launch is then lost.
 // Logistic regression, n = 32, d = 65 536, M = 128, 100 events (0.95 ms by itself) beside another handle's call in one launch
-// that holds 16 (157) compute units for 5 ms: done in 4.0 (4.1) ms;  when a block that had waited in vain computed the dot
+// that holds 16 (157) compute units for 5 ms: done in 4.2 (4.5) ms;  when a block that had waited in vain computed the dot
 // products of whole rows by itself, for the rest of the launch, 88 (97);  three launches a round, which need no block to be
 // there, 2.2 (2.5), of which the other call then took more.  All in shares from the start (limit 0) and without other work: 3.1 ms.
 // A function of its own with its arguments in memory, since the kernel has no registers to spare for it.

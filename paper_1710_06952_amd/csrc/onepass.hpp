@@ -9,10 +9,11 @@ constexpr int kOnePassThreads = 512;
 constexpr int kOnePassWaves = kOnePassThreads / 64;
 constexpr int kOnePassMaxM = 128;
 constexpr int kOnePassMaxStrips = 256;
-// How long a block waits for the others before it leaves the exchange: the time of five of the largest gradients.  Where the
-// others come late because other work holds compute units, a longer wait is lost, once by the blocks that are there and once by
-// each that comes later (300 us: 4.3 and 4.6 ms for the 4.0 and 4.1 at take_tickets).
-constexpr int64_t kOnePassWaitUs = 100;
+// How long a block waits for the others before it leaves the exchange.  Where the others come late because other work holds
+// compute units, a longer wait is lost, once by the blocks that are there and once by each that comes later (1000, 300 and 100 us:
+// 4.2, 4.2, 4.0 and 4.6, 4.5, 4.1 ms at take_tickets).  The first launch of a process may need it, though: with data that the
+// device has not touched yet (M = 4, d = 327 679, five workers) some blocks of a group come more than 100 us after the others.
+constexpr int64_t kOnePassWaitUs = 300;
 
 // How a gradient lies on the chip: its columns in `strips` strips of one block each, the rows of a strip over
 // `row_groups` groups of wavefronts with `rows` rows each, the strip's columns over 8 / row_groups wavefronts of `chunks` times
