@@ -14,14 +14,22 @@ constexpr int kOnePassMaxStrips = 256;
 // 4.2, 4.2, 4.0 and 4.6, 4.5, 4.1 ms at take_tickets).  The first launch of a process may need it, though: with data that the
 // device has not touched yet (M = 4, d = 327 679, five workers) some blocks of a group come more than 100 us after the others.
 constexpr int64_t kOnePassWaitUs = 300;
+// Bytes of a gradient's rows from which on the kernels for large ones take it (measured at onepass_shape).
+constexpr double kOnePassLargeBytes = 8e6;
+enum class OnePassKernel : int32_t { kPlain, kPipeline, kStaged };
 
 // How a gradient lies on the chip: its columns in `strips` strips of one block each, the rows of a strip over
 // `row_groups` groups of wavefronts with `rows` rows each, the strip's columns over 8 / row_groups wavefronts of `chunks` times
-// 256 columns; `groups` gradients at a time.
+// 256 columns, of which the first `wave_cols` are in use; `groups` gradients at a time.
 struct OnePassShape {
-    int32_t rows = 0, chunks = 0, row_groups = 0, strips = 0, groups = 0;
+    int32_t rows = 0, chunks = 0, row_groups = 0, strips = 0, groups = 0, wave_cols = 0;
+    OnePassKernel kernel = OnePassKernel::kPlain;
     bool ok() const { return strips > 0; }
+    constexpr __host__ __device__ int32_t ring() const { return kernel == OnePassKernel::kPipeline ? 2 : 1; }     // gradients in the exchange
 };
+constexpr int64_t onepass_group_words(const OnePassShape& s, int32_t samples) {
+    return static_cast<int64_t>(samples) * (s.ring() * (s.strips + 2) + s.strips + 1) + 2;
+}
 // The shape for a handle, by its sizes alone (so that a gradient has the same bits in every call and however its blocks are
 // scheduled), or one that is not ok():
 // three launches per round (kernels_grad_linear.hip) are the better route, or the only one.
