@@ -16,10 +16,24 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef uint16_t v4h __attribute__((ext_vector_type(4)));
 
+// A pointer out of a table, known to the compiler to point to global memory.  Else it takes loads that may be from LDS as well
+// (flat_load): these pass through LDS too, hold up its other accesses, and every wait after one is for all requests.
+template <typename T>
+using Global = const __attribute__((address_space(1))) T*;
+template <typename T>
+__device__ __forceinline__ Global<T> in_global(const void* p) {
+    return (Global<T>)p;
+}
+
 template <bool STREAM>
 __device__ __forceinline__ v4f load4(const float* p) {
     if (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const v4f*>(p));
     return *reinterpret_cast<const v4f*>(p);
+}
+template <bool STREAM>
+__device__ __forceinline__ v4f load4(Global<float> p) {
+    if (STREAM) return __builtin_nontemporal_load(reinterpret_cast<Global<v4f>>(p));
+    return *reinterpret_cast<Global<v4f>>(p);
 }
 template <bool STREAM>
 __device__ __forceinline__ void store4(float* p, v4f v) {

@@ -192,15 +192,15 @@ __global__ __launch_bounds__(kThreads) void objective_partial_kernel(int model, 
                                                                     int rows_per_wave, int count_errors) {
     __shared__ double red[kWaves];
     const ObjectiveWorker w = workers[blockIdx.y];
-    const float* __restrict__ A = static_cast<const float*>(w.features);
-    const float* __restrict__ tg = static_cast<const float*>(w.targets);
+    const Global<float> A = in_global<float>(w.features);
+    const Global<float> tg = in_global<float>(w.targets);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t n_vec = d >> 2;            // full float4 groups; the ragged tail is handled separately
     double acc = 0.0;
     for (int r = 0; r < rows_per_wave; ++r) {
         const int64_t row = (static_cast<int64_t>(blockIdx.x) * kWaves + wave) * rows_per_wave + r;
         if (row >= w.rows) break;            // uniform over the wavefront
-        const float* __restrict__ a = A + row * w.ld;
+        const Global<float> a = A + row * w.ld;
         float z = 0.0f;
         for (int64_t v0 = lane; v0 < n_vec; v0 += 64 * 8) {
             v4f av[8], xv[8];

@@ -83,7 +83,7 @@ template <bool STREAM>
 __global__ __launch_bounds__(kThreads) void linear_dots_kernel(const LinParams p) {
     __shared__ float red[kWaves][kRowsPerBlock];
     const GradOp op = p.ops[blockIdx.z];
-    const float* __restrict__ A = static_cast<const float*>(op.features);
+    const Global<float> A = in_global<float>(op.features);
     const int32_t* __restrict__ idx = p.batch_idx + static_cast<int64_t>(op.event) * p.M;
     const int64_t v0 = static_cast<int64_t>(blockIdx.x) * (kDotChunk / 4) + threadIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kThreads) void linear_dots_kernel(const LinParams p
         if (m == p.M && p.model != ADPSGD_MODEL_LOGREG) break;
         float acc = 0.0f;
         if (m < p.M) {
-            const float* __restrict__ row = A + static_cast<int64_t>(idx[m]) * op.ld;
+            const Global<float> row = A + static_cast<int64_t>(idx[m]) * op.ld;
 #pragma unroll
             for (int u = 0; u < kDotUnroll; ++u) {
                 const int64_t v = v0 + static_cast<int64_t>(u) * kThreads;
@@ -151,7 +151,7 @@ __device__ __forceinline__ float sum_chunks(const float* __restrict__ part, int6
 __global__ __launch_bounds__(kThreads) void linear_finalize_kernel(const LinParams p, const int L) {
     __shared__ float red[kWaves];
     const GradOp op = p.ops[blockIdx.x];
-    const float* __restrict__ tg = static_cast<const float*>(op.targets);
+    const Global<float> tg = in_global<float>(op.targets);
     const int32_t* __restrict__ idx = p.batch_idx + static_cast<int64_t>(op.event) * p.M;
     const float* __restrict__ part = p.partial + static_cast<int64_t>(blockIdx.x) * (p.M + 1) * p.n_chunks;
     const int sub = threadIdx.x & (L - 1), grp = threadIdx.x / L, groups = kThreads / L;
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(kThreads) void linear_finalize_kernel(const LinPara
 // four elements of sum_m c_m a_m at vector index v (the one place this sum is written, so that the dense
 // and the factored path produce the same bits)
 template <bool STREAM>
-__device__ __forceinline__ v4f combine_rows(const float* __restrict__ A, int64_t lda, const int32_t* __restrict__ idx,
+__device__ __forceinline__ v4f combine_rows(Global<float> A, int64_t lda, const int32_t* __restrict__ idx,
                                             const float* __restrict__ cf, int M, int64_t v) {
     v4f acc = {0, 0, 0, 0};
 #pragma unroll 8
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kThreads) void linear_combine_kernel(const LinParam
     const GradOp op = p.ops[blockIdx.y];
     const int64_t v = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
     if (v >= p.n_vec) return;
-    const float* __restrict__ A = static_cast<const float*>(op.features);
+    const Global<float> A = in_global<float>(op.features);
     const int32_t* __restrict__ idx = p.batch_idx + static_cast<int64_t>(op.event) * p.M;
     const float* __restrict__ cf = p.coef + static_cast<int64_t>(blockIdx.y) * p.M;
     v4f acc = combine_rows<STREAM>(A, op.ld, idx, cf, p.M, v);
@@ -264,7 +264,7 @@ __global__ __launch_bounds__(kThreads) void linear_apply_chains_kernel(const Lin
         const UpdateOp& op = chain.ops[u];
         v4f g[1] = {{0, 0, 0, 0}};
         if (op.event >= 0)
-            g[0] = zero_beyond(combine_rows<STREAM_ROWS>(static_cast<const float*>(op.features), op.feat_ld,
+            g[0] = zero_beyond(combine_rows<STREAM_ROWS>(in_global<float>(op.features), op.feat_ld,
                                                          p.batch_idx + static_cast<int64_t>(op.event) * p.M,
                                                          p.slots + static_cast<int64_t>(op.slot) * p.ld, p.M, v), 4 * v, p.d);
         c.update(op, p.momentum, p.weight_decay, g);
@@ -309,8 +309,8 @@ __global__ __launch_bounds__(kSmallT) void linear_small_kernel(const LinParams p
     __shared__ float loss_s[kSmallMaxM];
     __shared__ v4f part_s[kSmallT];        // [group][column]
     const GradOp op = p.ops[blockIdx.x];
-    const float* __restrict__ A = static_cast<const float*>(op.features);
-    const float* __restrict__ tg = static_cast<const float*>(op.targets);
+    const Global<float> A = in_global<float>(op.features);
+    const Global<float> tg = in_global<float>(op.targets);
     const int32_t* __restrict__ idx = p.batch_idx + static_cast<int64_t>(op.event) * p.M;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     float target = 0.0f;
@@ -331,11 +331,11 @@ __global__ __launch_bounds__(kSmallT) void linear_small_kernel(const LinParams p
             acc[r] = 0.0f;
             const int m = m0 + r * kSmallWaves;
             if (m < p.M) {
-                const float* __restrict__ row = A + static_cast<int64_t>(idx[m]) * op.ld;
+                const Global<float> row = A + static_cast<int64_t>(idx[m]) * op.ld;
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int64_t v = lane + 64 * u;
-                    a[r][u] = v < p.n_vec ? zero_beyond(*reinterpret_cast<const v4f*>(row + 4 * v), 4 * v, p.d) : v4f{0, 0, 0, 0};
+                    a[r][u] = v < p.n_vec ? zero_beyond(*reinterpret_cast<Global<v4f>>(row + 4 * v), 4 * v, p.d) : v4f{0, 0, 0, 0};
                 }
             } else {
 #pragma unroll
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(kSmallT) void linear_small_kernel(const LinParams p
         if (v < p.n_vec) {
 #pragma unroll 8
             for (int m = grp; m < p.M; m += kGroups) {
-                const v4f a = *reinterpret_cast<const v4f*>(A + static_cast<int64_t>(idx[m]) * op.ld + 4 * v);
+                const v4f a = *reinterpret_cast<Global<v4f>>(A + static_cast<int64_t>(idx[m]) * op.ld + 4 * v);
                 acc += a * coef_s[m];
             }
         }

@@ -123,11 +123,10 @@ __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
     const int m0 = kFwdRows * blockIdx.z;          // first minibatch row of this block
     const bool first_rows = blockIdx.z == 0;       // this block also leaves what does not depend on the rows
     const GradOp op = p.ops[blockIdx.y];
-    const uint16_t* __restrict__ feat = static_cast<const uint16_t*>(op.features);
+    const Global<uint16_t> feat = in_global<uint16_t>(op.features);
     const int32_t* __restrict__ idx = p.batch_by_op + static_cast<int64_t>(blockIdx.y) * p.M;   // independent of op
-    const uint16_t* __restrict__ W1 = op.xrow_bf16 ? static_cast<const uint16_t*>(op.xrow_bf16)
-                                                   : p.Xb + static_cast<int64_t>(op.worker) * p.ld;
-    const uint16_t* __restrict__ b1 = W1 + static_cast<int64_t>(p.in) * p.hid;
+    const Global<uint16_t> W1 = in_global<uint16_t>(op.xrow_bf16 ? op.xrow_bf16 : p.Xb + static_cast<int64_t>(op.worker) * p.ld);
+    const Global<uint16_t> b1 = W1 + static_cast<int64_t>(p.in) * p.hid;
     // Blocks go to the 8 XCDs round robin, each with an L2 of its own, and a 32-column tile of bf16 weights
     // is half a 128-byte line: neighbouring tiles are given to blocks of the same XCD, so that a line of W1
     // is fetched from memory once instead of twice (rocprofv3 FETCH_SIZE at 784-1024-10: 3.8 -> 2.35 MB per
@@ -142,12 +141,12 @@ __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
     int32_t label = -1;
     const uint16_t b1raw = b1[h0 + 16 * ((wave >> 2) & 1) + li];   // bias of the hidden unit this thread finishes
     {
-        const uint16_t* __restrict__ W2 = b1 + p.hid;
+        const Global<uint16_t> W2 = b1 + p.hid;
         const int hh = threadIdx.x / kMaxOut, o = threadIdx.x % kMaxOut;     // 512 = 32 x 16
         w2raw = o < p.out ? W2[static_cast<int64_t>(h0 + hh) * p.out + o] : static_cast<uint16_t>(0);
         if (tile == 0 && first_rows) {   // one block also leaves the labels and the output bias for the next kernel
             if (threadIdx.x < kMaxM && static_cast<int>(threadIdx.x) < p.M)
-                label = static_cast<const int32_t*>(op.targets)[idx[threadIdx.x]];
+                label = in_global<int32_t>(op.targets)[idx[threadIdx.x]];
             if (threadIdx.x < kMaxOut && static_cast<int>(threadIdx.x) < p.out)
                 b2raw = W2[static_cast<int64_t>(p.hid) * p.out + threadIdx.x];
         }
@@ -155,7 +154,7 @@ __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
     uint16_t(*Bt)[40] = reinterpret_cast<uint16_t(*)[40]>(smem + wave * (kFwdTileH * 40 * 2));   // [h][k]
     float* red = reinterpret_cast<float*>(smem);
 
-    const uint16_t* rowp[kFwdMT];
+    Global<uint16_t> rowp[kFwdMT];
 #pragma unroll
     for (int mt = 0; mt < kFwdMT; ++mt) {
         const int m = m0 + 16 * mt + li;
@@ -168,11 +167,11 @@ __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
             const int k = k0 + skk + 16 * r;
-            f.w[r] = k < p.in ? *reinterpret_cast<const v8h*>(W1 + static_cast<int64_t>(k) * p.hid + h0 + shh) : zero;
+            f.w[r] = k < p.in ? *reinterpret_cast<Global<v8h>>(W1 + static_cast<int64_t>(k) * p.hid + h0 + shh) : zero;
         }
 #pragma unroll
         for (int mt = 0; mt < kFwdMT; ++mt)
-            f.a[mt] = (rowp[mt] && k0 + kb < p.in) ? *reinterpret_cast<const v8h*>(rowp[mt] + k0 + kb) : zero;
+            f.a[mt] = (rowp[mt] && k0 + kb < p.in) ? *reinterpret_cast<Global<v8h>>(rowp[mt] + k0 + kb) : zero;
     };
 
     v4f acc[kFwdMT][2];
@@ -465,7 +464,7 @@ __global__ __launch_bounds__(kBwdT) void mlp_loss_kernel(const MlpParams p, doub
 // ([kMaxM][hid] bf16, rows >= M zero) are transposed through LDS, then wavefront w multiplies the
 // four 16-row input tiles with hidden columns [16 w, 16 w + 16).  Lane l ends up with
 // acc[it][v] = dW1[i0 + 16 it + 4 (l / 16) + v][h0 + 16 w + l % 16].
-__device__ __forceinline__ void dw1_tile(const uint16_t* __restrict__ feat, int64_t feat_ld, const int32_t* __restrict__ idx,
+__device__ __forceinline__ void dw1_tile(Global<uint16_t> feat, int64_t feat_ld, const int32_t* __restrict__ idx,
                                          int M, int in, const uint16_t* __restrict__ dH, int hid, int h0, int i0,
                                          uint16_t (*At)[72], uint16_t (*Bt)[72], v4f acc[4]) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -476,7 +475,7 @@ __device__ __forceinline__ void dw1_tile(const uint16_t* __restrict__ feat, int6
         for (int half = 0; half < 2; ++half) {
             const int c = seg + 8 * half;
             v8h xv = {0, 0, 0, 0, 0, 0, 0, 0};
-            if (m < M && i0 + c < in) xv = *reinterpret_cast<const v8h*>(feat + static_cast<int64_t>(idx[m]) * feat_ld + i0 + c);
+            if (m < M && i0 + c < in) xv = *reinterpret_cast<Global<v8h>>(feat + static_cast<int64_t>(idx[m]) * feat_ld + i0 + c);
             const v8h dv = *reinterpret_cast<const v8h*>(dH + static_cast<int64_t>(m) * hid + h0 + c);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -506,7 +505,7 @@ __global__ __launch_bounds__(kT) void mlp_dw1_kernel(const MlpParams p) {
     const GradOp op = p.ops[blockIdx.z];
     const int h0 = blockIdx.x * kTileH, i0 = blockIdx.y * 64;
     v4f acc[4];
-    dw1_tile(static_cast<const uint16_t*>(op.features), op.ld, p.batch_by_op + static_cast<int64_t>(blockIdx.z) * p.M, p.M, p.in,
+    dw1_tile(in_global<uint16_t>(op.features), op.ld, p.batch_by_op + static_cast<int64_t>(blockIdx.z) * p.M, p.M, p.in,
              p.dHb + static_cast<int64_t>(blockIdx.z) * kMaxM * p.hid, p.hid, h0, i0, At, Bt, acc);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     float* __restrict__ g = p.slots + static_cast<int64_t>(op.slot) * p.ld;
@@ -629,7 +628,7 @@ __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyP
         for (int half = 0; half < 2; ++half) f.d[half] = *reinterpret_cast<const v8h*>(dH + static_cast<int64_t>(m) * p.hid + h0 + 16 * part + 8 * half);
     };
     auto request_inputs = [&](const UpdateOp& op, int32_t row) {
-        f.x = *reinterpret_cast<const v8h*>(static_cast<const uint16_t*>(op.features) + static_cast<int64_t>(row) * op.feat_ld + c_in);
+        f.x = *reinterpret_cast<Global<v8h>>(in_global<uint16_t>(op.features) + static_cast<int64_t>(row) * op.feat_ld + c_in);
     };
     // indices first: loads return in order, and the inputs wait for them
     int32_t row = index[0];

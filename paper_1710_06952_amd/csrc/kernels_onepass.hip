@@ -234,10 +234,7 @@ struct Touched {
     }
     __device__ __forceinline__ void held() { asm volatile("" : "+s"(event), "+s"(ld)); }
 };
-// (A load whose place the compiler does not know to be global memory would count as one from LDS too, and all requests be awaited.)
-__device__ __forceinline__ float target_at(const GradOp& op, int32_t row) {
-    return reinterpret_cast<const __attribute__((address_space(1))) float*>(reinterpret_cast<uintptr_t>(op.targets))[row];
-}
+__device__ __forceinline__ float target_at(const GradOp& op, int32_t row) { return in_global<float>(op.targets)[row]; }
 // Where coefficient and index of sample m are; beyond the last row of the groups none is.
 template <int kRows>
 __device__ __forceinline__ int place_of(const OnePassParams& p, int m) { return (m & (p.a.shape.row_groups - 1)) * kRows + (m >> p.log_groups); }
@@ -687,7 +684,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
         const uint64_t until = wall_clock64() + a.wait_ticks;
         bool there = a.wait_ticks > 0;
         for (int m = strip + S * wave; there && m < p.samples; m += S * kOnePassWaves) {
-            const float target = m < M ? static_cast<const float*>(op.targets)[s.idx[turn][m]] : 0.0f;
+            const float target = m < M ? target_at(op, s.idx[turn][m]) : 0.0f;
             float dot[1];
             there = take_sums(words.sums, m, 0, p.samples, S, seq, until, dot);
             if (there && lane == 0) {
