@@ -8,9 +8,9 @@
 // minibatch rows are read once, into registers, ahead of the events that need them (the schedule names them), and are
 // still there when the coefficients arrive.
 // Measured, a call against the same call in rounds of three launches:  n = 8, d = 1024, M = 32, 200 events 0.24 against
-// 0.78 ms;  n = 16, d = 4096, M = 8, 1280 events 0.79 against 7.2 ms;  n = 16, d = 20 001, M = 50, wait-free with momentum, 400
+// 0.78 ms;  n = 16, d = 4096, M = 8, 1280 events 0.70 against 7.2 ms;  n = 16, d = 20 001, M = 50, wait-free with momentum, 400
 // events 1.17 against 4.1 ms.  What binds is the chain of an iteration (updates and x^, dot products, exchange and coefficients,
-// combination, barriers) times their number: 142, 5.2 us each with 9 gradients, for the second of these; with many rows per
+// combination, barriers) times their number: 142, 4.6 us each with 9 gradients, for the second of these; with many rows per
 // gradient (the third, 103 of 11 us) also their address translation, about 40 cycles per row and compute unit.
 // An iteration evaluates a gradient per team.  With half of them, so that all rows are requested an iteration ahead, the three
 // took 72, 217 and 203 iterations and 0.28, 1.07 and 1.70 ms: most calls run out of teams before they run out of events that
@@ -23,12 +23,15 @@
 //
 // A block has 12 main wavefronts in `teams` teams, each team with the rows of one gradient in its registers, and 4
 // helper wavefronts (one thread per column, and one per minibatch sample).  An iteration has three phases:
-//   A  helpers: finish the gradients of the last iteration, apply updates, write x^ of the next gradients to LDS;
+//   A  helpers: finish the gradients of the last iteration, apply updates, write x^ of the next gradients to LDS (teams of one
+//      wavefront take it from the state in LDS themselves: a third of the helpers' phase, 0.82 -> 0.71 ms for the second of the above);
 //      main: idle teams request the rows of their next gradient (which may be one of this iteration)
 //   B  main: dot products of a team's rows with x^, published;  helpers: wait for the sums, make the coefficients
 //   C  main: sum_m c_m a_m of the team's rows to LDS
 // A compute unit returns vector loads in order, so a wait of phase B stands behind the rows requested before it: they go
 // out at the start of phase A (in phase B they cost 0.5 us per iteration), and the helpers load nothing else before a wait.
+// Where several groups exchange, the helpers do not poll before the block's own words are out (kGate).
+// Rows beyond M are requested again in vain (no branch around a load): hence a kernel for every four rows or so.
 //
 // The sums go through the words of exchange.hpp: up to 32 strips exchange them directly; more sum within their XCD first
 // (the blocks of a group share out the samples), and only these sums cross the chip, at most 8 per sample.
@@ -129,11 +132,11 @@ __device__ __attribute__((noinline)) void run_alone(const StripArgs* args, int s
             }
             __syncthreads();
             const v4u f = rows_of[ev.x][0], g = rows_of[ev.x][1];
-            const float* const features = reinterpret_cast<const float*>(static_cast<uint64_t>(f.w) << 32 | f.z);
-            const float* const targets = reinterpret_cast<const float*>(static_cast<uint64_t>(g.y) << 32 | g.x);
+            const Global<float> features = in_global<float>(reinterpret_cast<const void*>(static_cast<uint64_t>(f.w) << 32 | f.z));
+            const Global<float> targets = in_global<float>(reinterpret_cast<const void*>(static_cast<uint64_t>(g.y) << 32 | g.x));
             const int32_t* const index = a.idx + static_cast<int64_t>(ev.y - a.seq0) * M;
             for (int m = wave; m < samples; m += kStripThreads / 64) {
-                const float* const row = m < M ? features + static_cast<int64_t>(index[m]) * f.y : point;      // the last: |x^|^2
+                const Global<float> row = m < M ? features + static_cast<int64_t>(index[m]) * f.y : in_global<float>(point);      // the last: |x^|^2
                 double z = 0.0;
                 for (int64_t c = lane; c < a.d; c += 64) z += static_cast<double>(row[c]) * static_cast<double>(point[c]);
                 z = wave_sum(z);
@@ -166,15 +169,23 @@ __device__ __attribute__((noinline)) void run_alone(const StripArgs* args, int s
 
 // kTeams teams of 12 / kTeams wavefronts, kRows rows per wavefront; kLds: the strip's models, momentum buffers and
 // slots in LDS, otherwise in their global places (every entry is touched by one thread only, its column's).
-template <int kTeams, int kRows, bool kLds, bool kMom>
+template <int kTeams, int kRows, bool kLds, bool kMom, bool kFar>
 __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const StripParams p) {
     constexpr int kTeamWaves = kStripMainWaves / kTeams;
     constexpr int kTeamHelpers = kTeams == 12 ? kRows : kTeams == 6 ? 32 : kTeams == 4 ? 64 : 128;      // threads, one per sample
     constexpr int kWordsInFlight = kTeams == 12 && kLds ? 6 : 4;        // per lane of a helper
+    // with two teams in a launch of several groups the rows are requested by flat loads, which go out more slowly, while the helpers
+    // poll: n = 5, d = 12 000, M = 128 1.39 ms, 1.44 without
+    using Row = std::conditional_t<kFar && kTeams == 2, const float*, Global<float>>;
+    using Vector = std::conditional_t<kFar && kTeams == 2, const v4f*, Global<v4f>>;
     static_assert(kTeams * kTeamHelpers <= kStripHelpers, "a helper per sample of every team");
     // teams of one wavefront have the whole gradient and put it into its slot themselves
     constexpr bool kDirect = kLds && kTeamWaves == 1;
     constexpr int kChunk = kRows > 16 ? 4 : kRows < 8 ? kRows : 8;      // rows whose sums or addresses are in registers at a time
+    // In a launch of several groups the polls wait until the block's own words are out, so that they do not stand behind rows and
+    // are not in vain: n = 6, d = 20 000, M = 64, 300 events 1.17 -> 1.03 ms, n = 8, d = 40 000, M = 8 0.63 -> 0.60.  Not with two teams
+    // (n = 5, d = 12 000, M = 128 1.39 -> 1.43) nor in one group, where words are a short way off (n = 16, d = 4096, M = 8 0.71 -> 0.75).
+    constexpr bool kGate = kFar && kTeams > 2;
     const StripArgs& a = p.a;
     extern __shared__ __attribute__((aligned(16))) float state_s[];      // [rows of X][rows of V][slots] x 256
     __shared__ __attribute__((aligned(16))) v4f red_s[kStripMainWaves][64];      // partial gradients, in the same order
@@ -187,10 +198,12 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     __shared__ float loss_s[kStripHelpers];
     __shared__ Assembly assembly_s;
     __shared__ int lost_s;
+    __shared__ uint32_t published_s[2];                                  // by iteration: wavefronts whose words are out (kGate)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int M = a.M, S = p.samples;
     if (tid == 0) lost_s = 0;
+    if (kGate && tid < 2) published_s[tid] = 0;
     if (tid == 0) assembly_s = assemble(a.counters, p.blocks, p.group_size, a.wait_ticks);
     __syncthreads();
     const Assembly as = assembly_s;
@@ -229,16 +242,16 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                 // no branch around a load: the wavefront would wait for one row before it requests the next
 #pragma unroll
                 for (int r0 = 0; r0 < kRows; r0 += kChunk) {
-                    const float* src[kChunk];
+                    Row src[kChunk];
 #pragma unroll
-                    for (int r = 0; r < kChunk; ++r) src[r] = rowp_s[it & 1][team * kTeamHelpers + min(first + kTeamWaves * (r0 + r), M - 1)];
+                    for (int r = 0; r < kChunk; ++r) src[r] = (Row)rowp_s[it & 1][team * kTeamHelpers + min(first + kTeamWaves * (r0 + r), M - 1)];
 #pragma unroll
                     for (int r = 0; r < kChunk; ++r)
-                        if (r0 + r < kRows) row[r0 + r < kRows ? r0 + r : 0] = *reinterpret_cast<const v4f*>(src[r] + from);
+                        if (r0 + r < kRows) row[r0 + r < kRows ? r0 + r : 0] = *reinterpret_cast<Vector>(src[r] + from);
                 }
                 const v4u e = rec[2 + 2 * kTeams + 2 * __popc(load & ((1u << team) - 1))];
                 const uint32_t low = __builtin_amdgcn_readfirstlane(e.x), high = __builtin_amdgcn_readfirstlane(e.y);      // not signed
-                const float* const targets = reinterpret_cast<const float*>(static_cast<uint64_t>(high) << 32 | low);
+                const Global<float> targets = in_global<float>(reinterpret_cast<const void*>(static_cast<uint64_t>(high) << 32 | low));
                 target = targets[index_s[it & 1][team * kTeamHelpers + min(mine, M - 1)]];
             }
             __syncthreads();   // phase A done
@@ -248,7 +261,27 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
             if (evaluates) {
                 const uint32_t seq = __builtin_amdgcn_readfirstlane(eval[0].y);
                 const uint32_t words = ((seq % kStripRing) * groups + group) * S * kStripGroupBlocks + rank;
-                const v4f x = *reinterpret_cast<const v4f*>(&xh_s[number][4 * l]);
+                v4f x;
+                if (kDirect) {         // the point of evaluation, from the state
+#pragma clang fp contract(off)
+                    const v4u e2 = eval[1];
+                    x = *reinterpret_cast<const v4f*>(state_s + static_cast<int>(__builtin_amdgcn_readfirstlane(eval[0].z)) * kStripCols + 4 * l);
+                    const uint32_t comp = __builtin_amdgcn_readfirstlane(e2.x);
+                    if (comp != 0xFFFFFFFFu) {
+                        const v4f step = *reinterpret_cast<const v4f*>(state_s + slots_at + static_cast<int>(comp) * kStripCols + 4 * l) *
+                                         __uint_as_float(__builtin_amdgcn_readfirstlane(e2.y));
+                        x = x - step;
+                    }
+                    if (ragged) {      // zero beyond d, whatever infinite coefficients have left there
+                        if (at >= a.d) x.x = 0.0f;
+                        if (at + 1 >= a.d) x.y = 0.0f;
+                        if (at + 2 >= a.d) x.z = 0.0f;
+                        if (at + 3 >= a.d) x.w = 0.0f;
+                    }
+                    if (a.model == ADPSGD_MODEL_LOGREG && first == 0) *reinterpret_cast<v4f*>(&xh_s[number][4 * l]) = x;      // for lambda x^
+                } else {
+                    x = *reinterpret_cast<const v4f*>(&xh_s[number][4 * l]);
+                }
                 if (ragged && at + 4 > a.d) {       // what lies beyond d in a padded row is arbitrary
 #pragma unroll
                     for (int r = 0; r < kRows; ++r) {
@@ -274,6 +307,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
                     const float z = all_sum(dot4(x, x));
                     if (lane == 0) put_word(a.words, words + M * kStripGroupBlocks, z, seq);
                 }
+                if (kGate && lane == 0) __hip_atomic_fetch_add(&published_s[it & 1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             __syncthreads();   // the coefficients are there
             if (evaluates) {
@@ -366,16 +400,16 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         for (int u = 0; u < kUps; ++u) up[u] = rec[1 + 4 * kTeams + min(from + u, max(count, 1) - 1)];      // none: row 0, unused
         read_rows();
     };
-    const int log_width = sum_width(groups > 1 ? groups : group_blocks), sub = t & ((1 << log_width) - 1);
-    const int words = groups > 1 ? groups : group_blocks;               // of a sum
+    const int log_width = sum_width(kFar ? groups : group_blocks), sub = t & ((1 << log_width) - 1);
+    const int words = kFar ? groups : group_blocks;               // of a sum
     // word of sample q and partial sum `sub`: by groups of whole lines, or by samples
-    const uint32_t q_pitch = groups > 1 ? 1 : kStripGroupBlocks, sub_pitch = groups > 1 ? p.sum_pitch : 1;
-    const uint32_t ring_pitch = groups > 1 ? groups * p.sum_pitch : S * kStripGroupBlocks;
+    const uint32_t q_pitch = kFar ? 1 : kStripGroupBlocks, sub_pitch = kFar ? p.sum_pitch : 1;
+    const uint32_t ring_pitch = kFar ? groups * p.sum_pitch : S * kStripGroupBlocks;
     const int log_group = sum_width(group_blocks), part = t & ((1 << log_group) - 1), slots = kStripHelpers >> log_group;
     const int mine = rank < S ? (S - rank + group_blocks - 1) / group_blocks : 0;      // samples of a gradient that this block sums
     const uint32_t per_eval = (0xFFFFu + max(mine, 1)) / max(mine, 1);                  // d / mine = d per_eval >> 16 for d mine < 2^16
     const int pair0 = t >> log_width, pair_step = kStripHelpers >> log_width;
-    const unsigned long long* const base = groups > 1 ? p.sums : a.words;
+    const unsigned long long* const base = kFar ? p.sums : a.words;
     bool given_up = a.lose;
     // Coefficients of up to kWords (gradient, sample) pairs per group of lanes that share a sum, from pair `from` on; samples are
     // padded to a power of two.
@@ -500,7 +534,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         }
         // ---- A3: points of evaluation
         n_evals = __popc(evaluate);
-        for (int i0 = 0; i0 < n_evals; i0 += kEvals) {
+        for (int i0 = 0; !kDirect && i0 < n_evals; i0 += kEvals) {
             float x[kEvals];
             if (i0 > 0) {
 #pragma unroll
@@ -538,7 +572,11 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
             ev2[i] = next[2 + 2 * i];
         }
         put_addresses(next, (it + 1) & 1);
-        if (groups > 1) {       // the group's sums: sample q is summed by the block of rank q mod group_blocks
+        if (kGate) {
+            const uint32_t all = static_cast<uint32_t>(n_evals * kTeamWaves);
+            while (__hip_atomic_load(&published_s[it & 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < all) __builtin_amdgcn_s_sleep(1);
+        }
+        if (kFar) {             // the group's sums: sample q is summed by the block of rank q mod group_blocks
             for (int d0 = 0; d0 < n_evals * mine; d0 += slots) {
                 int d = d0 + (t >> log_group);
                 const bool live = part < group_blocks && d < n_evals * mine;
@@ -563,6 +601,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         if (given_up) lost_s = 1;
         __syncthreads();
 
+        if (kGate && t == 0) published_s[it & 1] = 0;
         // ---- C: indices and record of the iterations after the next (what a helper loads here has arrived when the next
         // waits of phase B begin)
         fetch_index(rec_s[(it + 2) & 3]);
@@ -581,14 +620,18 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     }
 }
 
+template <int kTeams, int kRows, bool kLds, bool kMom>
+void* strip_kernel(bool far) {
+    return far ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, kLds, kMom, true>)
+               : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, kLds, kMom, false>);
+}
 template <int kTeams, int kRows>
 hipError_t launch_rows(StripParams& p, hipStream_t st) {
     const StripArgs& a = p.a;
     const size_t lds = a.lds_state ? static_cast<size_t>(a.n * (a.V ? 2 : 1) + a.n_lds_slots) * kStripCols * 4 : 0;
-    void* fn = a.lds_state ? (a.V ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, true, true>)
-                                  : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, true, false>))
-                           : (a.V ? reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, false, true>)
-                                  : reinterpret_cast<void*>(&strip_events_kernel<kTeams, kRows, false, false>));
+    const bool far = p.blocks > p.group_size;          // several groups
+    void* fn = a.lds_state ? (a.V ? strip_kernel<kTeams, kRows, true, true>(far) : strip_kernel<kTeams, kRows, true, false>(far))
+                           : (a.V ? strip_kernel<kTeams, kRows, false, true>(far) : strip_kernel<kTeams, kRows, false, false>(far));
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
     if (e != hipSuccess) return e;
     void* args[] = {&p};
@@ -629,10 +672,10 @@ hipError_t launch_strips(const StripArgs& a, hipStream_t st) {
     p.sum_pitch = (p.samples + 15) & ~15;
     p.sums = a.words + static_cast<int64_t>(kStripRing) * strip_samples(a.model, a.M) * kStripGroups * kStripGroupBlocks;
     switch (a.teams) {
-        case 12: return a.M <= 8 ? launch_rows<12, 8>(p, st) : launch_rows<12, 16>(p, st);
-        case 6: return launch_rows<6, 16>(p, st);
-        case 4: return a.M <= 48 ? launch_rows<4, 16>(p, st) : launch_rows<4, 22>(p, st);
-        default: return a.M <= 96 ? launch_rows<2, 16>(p, st) : launch_rows<2, 22>(p, st);
+        case 12: return a.M <= 4 ? launch_rows<12, 4>(p, st) : a.M <= 8 ? launch_rows<12, 8>(p, st) : a.M <= 12 ? launch_rows<12, 12>(p, st) : launch_rows<12, 16>(p, st);
+        case 6: return a.M <= 24 ? launch_rows<6, 12>(p, st) : launch_rows<6, 16>(p, st);
+        case 4: return a.M <= 48 ? launch_rows<4, 16>(p, st) : a.M <= 54 ? launch_rows<4, 18>(p, st) : launch_rows<4, 22>(p, st);
+        default: return a.M <= 96 ? launch_rows<2, 16>(p, st) : a.M <= 108 ? launch_rows<2, 18>(p, st) : launch_rows<2, 22>(p, st);
     }
 }
 
