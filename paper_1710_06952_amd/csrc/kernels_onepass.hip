@@ -1094,7 +1094,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
 // spill.  Two gradients fit up to 16 vectors (8 where a wavefront has few rows and with them many columns of x^): 33 MB on all compute
 // units.  The line to the pipeline, 64 and 61 set-ups below and above 4 MB a gradient, against one gradient at a time: below 1 MB 0.80
 // ... 1.25 times as fast, 3 to 8 MB 0.90 ... 1.17, from 8 MB on 0.98 ... 1.29; with 6 rows, of 16 vectors only 12 in use, 0.92 ... 1.1 at
-// 9.6 MB.  The strips of a group are of equal width, as many as its compute units (with widths in whole vectors of a wavefront M = 128,
+// 9.6 MB.  Strips of large gradients are of equal width, as many as the compute units of their group (with widths in whole vectors of a wavefront M = 128,
 // d = 131 073 had 171 strips on 256 compute units).  Below 20 strips the blocks hold less, so that a gradient spreads over more compute units (n = 16, M = 8, d = 131 000
 // on the 4-regular graph: 786 us for 40 events in three launches a round, 708 with 16 strips, 609 with 32).
 // Measured against the three launches, 450 set-ups of 16 and 40 workers, M = 1 ... 128, 0.25 to 100 MB a gradient:
@@ -1128,9 +1128,9 @@ OnePassShape onepass_shape(int model, int64_t d, int32_t M, int32_t compute_unit
     }
     if (strips > most) return s;
     s.groups = static_cast<int32_t>(most / strips);
-    // as many strips as the compute units of a group, of equal width
+    // large: as many strips as the compute units of a group, of equal width
     const int64_t waves = kOnePassWaves / s.row_groups, parts = most / s.groups * waves;
-    s.wave_cols = static_cast<int32_t>(((d + parts - 1) / parts + 31) / 32 * 32);
+    s.wave_cols = large ? static_cast<int32_t>(((d + parts - 1) / parts + 31) / 32 * 32) : 256 * s.chunks;
     s.strips = static_cast<int32_t>((d + waves * s.wave_cols - 1) / (waves * s.wave_cols));
     return s;
 }
