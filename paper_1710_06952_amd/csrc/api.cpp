@@ -583,7 +583,7 @@ int prepare_call(adpsgd_t* h, const adpsgd_schedule_t* s, EventCall& c) {
     // 10.31; logistic, n = 64, M = 128, d = 65 536, 500 events: 36 and 4.59, 25 and 4.45).  A caller's gradients on short models keep
     // the rounds of the synthetic model, as the interface has it (7 % in the mean of 20 such calls, which the caller's own
     // launches bind).  A handle whose calls go in one launch keeps plain rounds for its short calls (small_call was drawn with them).
-    c.chain = h->o.model == ADPSGD_MODEL_MLP ? kMlpChain : (with_data && !c.strips) || (c.external && h->d > 4096) ? kChain : 1;
+    c.chain = h->o.model == ADPSGD_MODEL_MLP ? mlp_chain(h->o.V != nullptr, h->d) : (with_data && !c.strips) || (c.external && h->d > 4096) ? kChain : 1;
     c.onepass = with_data && onepass_for_events(h->onepass, h->o.model, c.M, comp) && can_run_onepass(h) && (!any_carried || h->pending_dense);
     if (c.onepass) c.lin_factored = false;
 

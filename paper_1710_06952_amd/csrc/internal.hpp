@@ -26,7 +26,10 @@ struct alignas(32) PairOp {
 
 // Updates of a round that share rows, executed one after the other (chain_rounds).
 constexpr int kChain = 4;               // operations of a chain, at most; they touch one row more
-constexpr int kMlpChain = 3;            // ... of the perceptron
+// ... of the perceptron: with momentum buffers the rows of a longer chain do not fit the registers, and on large models rounds are
+// bound by the updates' traffic (784-1024-10, 1000 events: 165 rounds, 5.44 ms, with chains of four, 175 and 5.35 with three; 64-256-10,
+// 300 events 1.36 and 1.45 ms, 256-960-3 0.78 and 0.80, 1024-1024-16 2.85 and 2.79)
+constexpr int mlp_chain(bool momentum, int64_t d) { return momentum || d > (1 << 18) ? 3 : kChain; }
 struct UpdateOp {
     const void* features;               // worker i's inputs (average only: those of a worker that has some, read and dropped), or nullptr
     int64_t feat_ld;

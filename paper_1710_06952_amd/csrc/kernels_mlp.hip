@@ -8,8 +8,7 @@
 //   backward  dW1 = Xb^T dH                in x M  times  M x hid
 // The hidden activations and their back-propagated error are rounded to bf16
 // before they enter those products.  The second layer (hid x out, out <= 16) is
-// small: its forward products are on the vector ALUs, its backward ones on the
-// matrix cores, both in fp32.
+// small: its products are on the matrix cores in fp32.
 //
 // Launches per group of gradient operations: forward; softmax with the second-layer
 // gradients and the hidden error dH; and, only where a dense gradient is wanted
@@ -95,9 +94,13 @@ __global__ __launch_bounds__(kT) void mlp_compensated_rows_kernel(const MlpParam
 // the input features is split across the eight wavefronts (k-steps of 32, step s goes to
 // wavefront s % 8), each with its own transposed W1 tile in LDS; the operands of up to kFwdDepth
 // steps of a wavefront (all of them for 784 inputs) are requested before the first MFMA, so the
-// kernel pays the memory latency once.  The eight partial tiles are added in a fixed order
-// through LDS -- (w, w + 4) first, then the four sums in sequence, every thread finishing four
-// elements of the tile -- and the block adds its share of the logits, one thread per two of them.
+// kernel pays the memory latency once.  The eight partial tiles are added through LDS in a fixed order
+// -- pairs (w, w + 4) first, then the four sums in sequence -- every thread finishing two elements of the
+// tile, and two wavefronts add the block's share of the logits on the matrix cores.  What follows the
+// contraction is a chain of short steps: partial tiles in memory of their own and one step instead of two for their sum
+// (two barriers instead of five), the logits on the matrix cores instead of 32 products a thread, and two rows of W1 to
+// a word where the tile is transposed took 784-1024-10 (M = 64, six gradients) from 11.6 to 9.5 us, 64-256-10 (M = 32) from 5.3
+// to 4.6.
 // tile handled by block x of a row of G blocks: consecutive tiles on the same XCD (block x runs on XCD x % 8
 // when G is a multiple of 8, as it is for every supported hidden size that is a multiple of 256)
 __device__ __forceinline__ int xcd_neighbours(int x, int G) { return (G & 7) == 0 ? (x & 7) * (G >> 3) + (x >> 3) : x; }
@@ -116,8 +119,8 @@ struct FwdOperands {
 };
 
 __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
-    // per-wavefront W1 tiles during the contraction (8 x 2560 B), then four partial tiles (4 x 4 KiB)
-    __shared__ __attribute__((aligned(16))) unsigned char smem[8 * kFwdTileH * 40 * 2];
+    __shared__ __attribute__((aligned(16))) uint16_t tiles[kFwdWaves][kFwdTileH][40];      // W1 tiles of the wavefronts, [h][k]
+    __shared__ float red[kFwdWaves * kFwdElems * 64];                                      // their partial tiles
     __shared__ float W2s[kFwdTileH][kMaxOut];     // this tile's rows of W2, zero beyond `out`
     __shared__ float Hs[kFwdRows][kFwdTileH + 1];  // the finished tile, as the next layer sees it
     const int m0 = kFwdRows * blockIdx.z;          // first minibatch row of this block
@@ -151,8 +154,7 @@ __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
                 b2raw = W2[static_cast<int64_t>(p.hid) * p.out + threadIdx.x];
         }
     }
-    uint16_t(*Bt)[40] = reinterpret_cast<uint16_t(*)[40]>(smem + wave * (kFwdTileH * 40 * 2));   // [h][k]
-    float* red = reinterpret_cast<float*>(smem);
+    uint16_t(*const Bt)[40] = tiles[wave];
 
     Global<uint16_t> rowp[kFwdMT];
 #pragma unroll
@@ -160,13 +162,13 @@ __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
         const int m = m0 + 16 * mt + li;
         rowp[mt] = m < p.M ? feat + static_cast<int64_t>(idx[m]) * op.ld : nullptr;
     }
-    const int skk = lane >> 2, shh = (lane & 3) * 8;   // staging role inside the wavefront
+    const int skk = 2 * (lane >> 2), shh = (lane & 3) * 8;   // staging role inside the wavefront: two rows, which share words in LDS
     auto fetch = [&](int step, FwdOperands& f) {
         const int k0 = 32 * step;
         const v8h zero = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
         for (int r = 0; r < 2; ++r) {
-            const int k = k0 + skk + 16 * r;
+            const int k = k0 + skk + r;
             f.w[r] = k < p.in ? *reinterpret_cast<Global<v8h>>(W1 + static_cast<int64_t>(k) * p.hid + h0 + shh) : zero;
         }
 #pragma unroll
@@ -190,9 +192,8 @@ __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
         for (int u = 0; u < kFwdDepth; ++u) {
             if (it0 + u < iters) {        // the same for every thread of the block
 #pragma unroll
-                for (int r = 0; r < 2; ++r)
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) Bt[shh + e][skk + 16 * r] = f[u].w[r][e];
+                for (int e = 0; e < 8; ++e)
+                    *reinterpret_cast<uint32_t*>(&Bt[shh + e][skk]) = static_cast<uint32_t>(f[u].w[1][e]) << 16 | f[u].w[0][e];
                 wave_lds_sync();      // the tile is this wavefront's own: no other wavefront has to wait
                 v8h bfrag[2];
 #pragma unroll
@@ -214,36 +215,22 @@ __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
             if (threadIdx.x < kMaxOut) p.b2f[static_cast<int64_t>(blockIdx.y) * kMaxOut + threadIdx.x] = bf16_to_float(b2raw);
         }
     }
-    __syncthreads();      // the partial tiles below reuse the memory of the wavefronts' weight tiles
-
     // element q = (mt, ht, v) of lane l of partial tile w at red[(w * kFwdElems + q) * 64 + l]
-    auto spill = [&](int w) {
 #pragma unroll
-        for (int mt = 0; mt < kFwdMT; ++mt)
+    for (int mt = 0; mt < kFwdMT; ++mt)
 #pragma unroll
-            for (int ht = 0; ht < 2; ++ht)
+        for (int ht = 0; ht < 2; ++ht)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) red[(w * kFwdElems + (mt * 2 + ht) * 4 + v) * 64 + lane] = acc[mt][ht][v];
-    };
-    if (wave >= 4) spill(wave - 4);
-    __syncthreads();
-    if (wave < 4) {
-#pragma unroll
-        for (int mt = 0; mt < kFwdMT; ++mt)
-#pragma unroll
-            for (int ht = 0; ht < 2; ++ht)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[mt][ht][v] += red[((wave * kFwdElems) + (mt * 2 + ht) * 4 + v) * 64 + lane];
-    }
-    __syncthreads();
-    if (wave < 4) spill(wave);
+            for (int v = 0; v < 4; ++v) red[(wave * kFwdElems + (mt * 2 + ht) * 4 + v) * 64 + lane] = acc[mt][ht][v];
     __syncthreads();
     // every thread finishes kFwdElems / 8 elements: q = wave + 8 j
 #pragma unroll
     for (int j = 0; j < kFwdElems / kFwdWaves; ++j) {
         const int q = wave + kFwdWaves * j;
-        const float sum = ((red[(0 * kFwdElems + q) * 64 + lane] + red[(1 * kFwdElems + q) * 64 + lane]) +
-                           red[(2 * kFwdElems + q) * 64 + lane]) + red[(3 * kFwdElems + q) * 64 + lane];
+        float pair[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) pair[w] = red[(w * kFwdElems + q) * 64 + lane] + red[((w + 4) * kFwdElems + q) * 64 + lane];
+        const float sum = ((pair[0] + pair[1]) + pair[2]) + pair[3];
         const int mt = q >> 3, ht = (q >> 2) & 1, v = q & 3;
         const int ml = 16 * mt + 4 * (lane >> 4) + v, m = m0 + ml, hh = 16 * ht + li;    // row inside the block, and of the minibatch
         float hval = 0.0f;
@@ -256,13 +243,17 @@ __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
         Hs[ml][hh] = hval;
     }
     __syncthreads();
-    // this tile's share of the logits: thread (m, o) sums over the 32 hidden units in order
-    {
-        const int ml = threadIdx.x >> 4, o = threadIdx.x & 15;       // 512 = 32 rows x 16 outputs
-        float part = 0.0f;
-#pragma unroll 8
-        for (int hh = 0; hh < kFwdTileH; ++hh) part += Hs[ml][hh] * W2s[hh][o];
-        p.logit_part[((static_cast<int64_t>(blockIdx.y) * gridDim.x + tile) * kMaxM + m0 + ml) * kMaxOut + o] = part;
+    // this tile's share of the logits, over the 32 hidden units in order: a step of the matrix cores adds its four products one after
+    // the other, so an entry has the bits of a chain of fused multiply-adds
+    if (wave < kFwdMT) {
+        const int lgrp = lane >> 4;
+        v4f part = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < kFwdTileH / 4; ++s)
+            part = __builtin_amdgcn_mfma_f32_16x16x4f32(Hs[16 * wave + li][4 * s + lgrp], W2s[4 * s + lgrp][li], part, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            p.logit_part[((static_cast<int64_t>(blockIdx.y) * gridDim.x + tile) * kMaxM + m0 + 16 * wave + 4 * lgrp + v) * kMaxOut + li] = part[v];
     }
 }
 
@@ -283,7 +274,8 @@ __global__ __launch_bounds__(kFwdT) void mlp_forward_kernel(const MlpParams p) {
 //      lanes in registers.
 //   c. the last two steps of the tree through LDS, one thread per (h, o).
 // (On the vector ALUs, with a tree of eight barriers over 16 row groups, this kernel took 8.8 us for the rounds of
-// 784-1024-10, M = 64, and 7.3 us for those of 64-256-10, M = 32; now 6.2 and 5.5.)
+// 784-1024-10, M = 64, and 7.3 us for those of 64-256-10, M = 32; 6.6 and 5.7 with the products on the matrix cores, 6.4 and 5.5 with
+// the softmax's maximum and sum by rotations in a row of 16 lanes instead of trips through LDS.)
 constexpr int kBwdT = 1024;
 
 // r[v] of the lanes 16 g .. + 15  <->  r[g] of the lanes 16 v .. + 15
@@ -300,6 +292,25 @@ __device__ __forceinline__ void transpose_groups(float (&r)[4]) {
         r[v] = __uint_as_float(s[0]);
         r[v + 1] = __uint_as_float(s[1]);
     }
+}
+
+// the value k lanes further in a row of 16: no trip through LDS.  After k = 8 both halves of a row hold the same, after 4 all quarters,
+// so rotations by 8, 4, 2, 1 pair the values that a butterfly pairs.
+template <int k>
+__device__ __forceinline__ float rotated(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + k, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float row_max(float v) {
+    v = fmaxf(v, rotated<8>(v));
+    v = fmaxf(v, rotated<4>(v));
+    v = fmaxf(v, rotated<2>(v));
+    return fmaxf(v, rotated<1>(v));
+}
+__device__ __forceinline__ float row_total(float v) {
+    v += rotated<8>(v);
+    v += rotated<4>(v);
+    v += rotated<2>(v);
+    return v + rotated<1>(v);
 }
 
 __global__ __launch_bounds__(kBwdT) void mlp_backward_small_kernel(const MlpParams p) {
@@ -345,13 +356,9 @@ __global__ __launch_bounds__(kBwdT) void mlp_backward_small_kernel(const MlpPara
         }
         const bool live = so < p.out;
         const float logit = live ? z + b2v : -INFINITY;
-        float zmax = logit;
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, off, 64));
+        const float zmax = row_max(logit);
         const float ez = live ? expf(logit - zmax) : 0.0f;
-        float zsum = ez;
-#pragma unroll
-        for (int off = 8; off > 0; off >>= 1) zsum += __shfl_xor(zsum, off, 64);
+        const float zsum = row_total(ez);
         const int lsrc = (threadIdx.x & 48) + (label >= 0 && label < p.out ? label : 0);   // lane of the labelled class
         const float lsel = __shfl(logit, lsrc, 64);
         dl_s[sm][so] = (live && sm < p.M) ? ez / zsum - (so == label ? 1.0f : 0.0f) : 0.0f;
@@ -525,14 +532,13 @@ __global__ __launch_bounds__(kT) void mlp_dw1_kernel(const MlpParams p) {
 // perceptron, with the first-layer part of g formed here from its factors (the same product
 // as above, so the values are those of the dense gradient) and only the small remainder
 // (b1, W2, b2) read from the pending slot.  The bf16 shadow of the rows is rewritten.
-// A block executes a chain of up to kMlpChain updates that share rows on its tile: the rows are
+// A block executes a chain of up to kLinks updates that share rows on its tile: the rows are
 // read once, stay in registers from update to update and are written once, and the operands of the
 // next product are on their way while one is applied.
 // A round is a chain of three kernels with latency for most of its time, so fewer rounds count for more than their length: with
-// updates that may follow each other in a round 784-1024-10 (n = 16, M = 64, T_max = 4, 1000 events) takes 175 rounds of 33 us
-// (11.6 forward, 6.6 softmax, 15.2 here) instead of 296 of 28 (9.8, 6.2, 13.1), 8.36 -> 6.0 ms; 64-256-10 with momentum (n = 16,
-// M = 32, 1024 events) 164 rounds instead of 254, 4.0 -> 2.85 ms.  Chains of four would save another 6 % and 2 % of the rounds,
-// but with momentum their rows do not fit the 128 registers at which four blocks share a compute unit.
+// updates that may follow each other in a round 784-1024-10 (n = 16, M = 64, T_max = 4, 1000 events) takes 175 rounds instead of 296,
+// 8.36 -> 6.0 ms when they were written (5.4 now: 9.5 us forward, 6.4 softmax, 15.2 here); 64-256-10 with momentum (n = 16, M = 32,
+// 1024 events) 164 rounds instead of 254, 4.0 -> 2.85 ms (2.6 now: 4.6, 5.5, 6.3).  mlp_chain has how long a chain may be.
 //   grid = (hid / 64, in_tiles + further rows, chains of the round), in launches of 65 535 rows at most (more than 2 M
 //   inputs, or 1 M with dense gradients, need several); row = row0 + blockIdx.y:
 //   row <  in_tiles: one 32 x 64 tile of W1.  The tile of g goes through LDS so that
@@ -556,10 +562,10 @@ struct MlpApplyParams {
 };
 
 constexpr int kApplyRows = 32;              // inputs of a tile
-constexpr int kPlaces = kMlpChain + 1;      // rows of a chain
 
-template <bool MOM, bool MORE>
+template <int kLinks, bool MOM, bool MORE>
 __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyParams p) {
+    constexpr int kPlaces = kLinks + 1;       // rows of a chain of kLinks operations
     __shared__ __attribute__((aligned(16))) uint16_t At[kApplyRows][72];   // inputs transposed:  [i][m], 64 m + pad
     __shared__ __attribute__((aligned(16))) uint16_t Bt[64][72];           // hidden error transposed: [h][m]
     __shared__ __attribute__((aligned(16))) float Gs[kApplyRows][68];      // the tile of g, [input][hidden]
@@ -579,12 +585,12 @@ __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyP
             c.x[q][0] = buffer_load4<false>(buffer_of(p.X + at, chain.rows[q] >= 0 ? bytes : 0), offset);
             if constexpr (MOM) c.v[q][0] = buffer_load4<false>(buffer_of(p.V + at, (chain.steps >> q & 1) != 0 ? bytes : 0), offset);
         }
-        v4f g[kMlpChain][1];
+        v4f g[kLinks][1];
 #pragma unroll
-        for (int u = 0; u < kMlpChain; ++u)
+        for (int u = 0; u < kLinks; ++u)
             g[u][0] = buffer_load4<false>(buffer_of(p.slots + static_cast<int64_t>(chain.ops[u].slot) * p.ld + from, u < n_ops ? bytes : 0), offset);
 #pragma unroll
-        for (int u = 0; u < kMlpChain; ++u)
+        for (int u = 0; u < kLinks; ++u)
             if (u == 0 || u < n_ops) c.update(chain.ops[u], p.momentum, p.weight_decay, g[u]);
 #pragma unroll
         for (int q = 0; q < kPlaces; ++q) {
@@ -654,7 +660,7 @@ __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyP
     asm volatile("" : "+v"(row), "+v"(row_next));       // no address before the rows are requested
     request_inputs(chain.ops[0], row);
 #pragma unroll
-    for (int u = 0; u < kMlpChain; ++u) {
+    for (int u = 0; u < kLinks; ++u) {
         if (u > 0 && u >= n_ops) break;       // the same for the whole block; a chain has one at least
         const UpdateOp& op = chain.ops[u];
 #pragma unroll
@@ -664,9 +670,9 @@ __global__ __launch_bounds__(kT, 4) void mlp_apply_chains_kernel(const MlpApplyP
             Bt[16 * part + 8 + e][m] = f.d[1][e];
         }
         __syncthreads();
-        if (u + 1 < kMlpChain) {
-            request_error(chain.ops[u + 1 < kMlpChain ? u + 1 : u]);
-            request_inputs(chain.ops[u + 1 < kMlpChain ? u + 1 : u], row_next);
+        if (u + 1 < kLinks) {
+            request_error(chain.ops[u + 1 < kLinks ? u + 1 : u]);
+            request_inputs(chain.ops[u + 1 < kLinks ? u + 1 : u], row_next);
             row_next = index[static_cast<int64_t>(min(u + 2, n_ops - 1)) * p.M];
         }
         v4f acc[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
@@ -793,10 +799,11 @@ hipError_t launch_mlp_apply_chains(const MlpApplyArgs& a, hipStream_t st) {
     for (int64_t row0 = 0; row0 < by; row0 += 65535) {
         p.row0 = static_cast<int>(row0);
         const dim3 grid(static_cast<uint32_t>(bx), static_cast<uint32_t>(std::min<int64_t>(by - row0, 65535)), a.n_chains);
-        if (row0 > 0 && a.V) hipLaunchKernelGGL((mlp_apply_chains_kernel<true, true>), grid, dim3(kT), 0, st, p);
-        else if (row0 > 0) hipLaunchKernelGGL((mlp_apply_chains_kernel<false, true>), grid, dim3(kT), 0, st, p);
-        else if (a.V) hipLaunchKernelGGL((mlp_apply_chains_kernel<true, false>), grid, dim3(kT), 0, st, p);
-        else hipLaunchKernelGGL((mlp_apply_chains_kernel<false, false>), grid, dim3(kT), 0, st, p);
+        if (row0 > 0 && a.V) hipLaunchKernelGGL((mlp_apply_chains_kernel<3, true, true>), grid, dim3(kT), 0, st, p);
+        else if (row0 > 0) hipLaunchKernelGGL((mlp_apply_chains_kernel<3, false, true>), grid, dim3(kT), 0, st, p);
+        else if (a.V) hipLaunchKernelGGL((mlp_apply_chains_kernel<3, true, false>), grid, dim3(kT), 0, st, p);
+        else if (mlp_chain(false, a.d) == 3) hipLaunchKernelGGL((mlp_apply_chains_kernel<3, false, false>), grid, dim3(kT), 0, st, p);
+        else hipLaunchKernelGGL((mlp_apply_chains_kernel<kChain, false, false>), grid, dim3(kT), 0, st, p);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
