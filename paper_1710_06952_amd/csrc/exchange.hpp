@@ -6,8 +6,8 @@
 // A block publishes a gradient only after it has consumed all but the last few before it, which the other blocks publish
 // after they have consumed theirs: the ring is never overwritten early.  A word takes 0.36 us from block to block on one
 // XCD and 0.64 us across the chip (0.9 and 1.2 us for all of 16 or 256 blocks to have the words of all).  So the blocks
-// of an XCD (hardware register XCC_ID) form a group, and up to 32 strips are given to the blocks of a single XCD, of one
-// block per compute unit launched.  Partial sums are added in a fixed order of the groups and blocks.
+// of an XCD (hardware register XCC_ID) form a group, and up to 32 strips are given to the blocks of a single XCD, of eight
+// blocks launched for each.  Partial sums are added in a fixed order of the groups and blocks.
 // Every block waits for all others.  A cooperative launch makes sure that the grid fits the device, not that the device is
 // free: work of other streams or processes may hold compute units while the first blocks are there.  So the blocks agree
 // once, before any of them touches the state (assemble): all have arrived, or the first one that has waited longer than the
