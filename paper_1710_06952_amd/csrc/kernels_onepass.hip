@@ -149,7 +149,8 @@ struct OnePassShared {
     int32_t idx[3][kOnePassMaxM];
     float loss[kOnePassMaxM + 1];
     uint32_t ticket;
-    int late, lost;
+    int late[2];                            // the wait of a wavefront was in vain; the pipeline has one a turn (late_seen), the others the first
+    int lost;
 };
 
 // What a thread has of a strip: the same in every block that works on it.
@@ -651,7 +652,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
     int q = group, turn = 0;
     if (q >= a.n_ops) return;
     GradOp op = a.ops[q];
-    if (tid == 0) s.late = 0;
+    if (tid == 0) s.late[0] = 0;
     if (tid < kOnePassMaxM) {
         s.coef[tid] = 0.0f;
         s.idx[0][tid] = tid < M ? a.batch_idx[static_cast<int64_t>(op.event) * M + tid] : 0;
@@ -707,9 +708,9 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
             there = take_words(words.losses, word_at, seq, until, v);
             if (m < p.samples) s.loss[m] = v[0];
         }
-        if (!there && lane == 0) s.late = 1;
+        if (!there && lane == 0) s.late[0] = 1;
         __syncthreads();
-        if (s.late != 0) {                         // uniform over the block
+        if (s.late[0] != 0) {                         // uniform over the block
             take_tickets<kRows, kChunks, false>(static_cast<const OnePassParams*>((const void*)__builtin_amdgcn_kernarg_segment_ptr()), group, &s);
             return;
         }
@@ -763,7 +764,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
     v4f(*const stage)[kChunks][64] = s.stage[wave];
     int q = group, turn = 0, turn1 = 1, turn2 = 2;                   // places of the indices: of this gradient and the two that follow
     if (q >= a.n_ops) return;
-    if (tid == 0) s.late = 0;
+    if (tid == 0) s.late[0] = 0;
     if (tid < kOnePassMaxM) s.coef[tid] = 0.0f;
     GradOp op = op_at(a.ops + q);
     {
@@ -835,10 +836,10 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
             there = take_words(words.losses, word_at, seq, until, v);
             if (m < p.samples) s.loss[m] = v[0];
         }
-        if (!there && lane == 0) s.late = 1;
+        if (!there && lane == 0) s.late[0] = 1;
         put_index<kRows>(p, s.idx[turn2], after_index);
         __syncthreads();
-        if (s.late != 0) {                         // uniform over the block
+        if (s.late[0] != 0) {                         // uniform over the block
             __builtin_amdgcn_s_waitcnt(0);         // for rows on their way to LDS
             take_tickets<kRows, kChunks, true>(static_cast<const OnePassParams*>((const void*)__builtin_amdgcn_kernarg_segment_ptr()), group, &s);
             return;
@@ -937,7 +938,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
     for (int c = 0; c < kChunks; ++c) x_a[c] = x_b[c] = v4f{0, 0, 0, 0};
     clear_stage<kRows, kChunks, kRows>(at, stage);
-    if (tid == 0) s.late = 0;
+    if (tid < 2) s.late[tid] = 0;
     if (tid < kOnePassMaxM) s.coef[tid] = 0.0f;
     auto stage_rows = [&](int t, int from, int to, uint64_t places) {
         const int bytes = t < count ? at.bytes : 0, rows = anew(at.rows);      // none: the requests touch no memory
@@ -969,10 +970,10 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
                                             a.wait_ticks, word, v);
             if (there && tid < M) s.coef[place_of<kRows>(p, tid)] = v[0];
             if (there && tid >= 256 && word_at[0] >= 0) s.loss[tid - 256] = v[0];
-            if (!there && lane == 0) s.late = 1;
+            if (!there && lane == 0) s.late[late_of_coefficients(t)] = 1;
         }
         block_barrier();
-        if (s.late != 0) return false;                   // uniform over the block
+        if (s.late[late_seen(t)] != 0) return false;     // uniform over the block
 
         // ---- 2
         v4f acc[kChunks];
@@ -1041,7 +1042,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
                         if (a.loss) put_word(words.losses + (t & 1) * p.samples, m, r.y, seq);
                     }
                 }
-            } else if (lane == 0) s.late = 1;
+            } else if (lane == 0) s.late[late_of_sums(t)] = 1;
         }
 
         stage_rows(t + 2, kQuarter, kHalf, places);

@@ -44,6 +44,13 @@ constexpr int32_t onepass_samples(int model, int32_t M, bool loss) { return M + 
 // that is not awaited could be overwritten under the block that adds it up.
 constexpr __host__ __device__ int32_t onepass_awaited(int32_t samples) { return samples; }
 
+// The pipeline's flags for a wait that ended in vain, by turn.  A turn looks at its flag behind the barrier of step 1, and no barrier
+// stands between that look and its wait for the sums: what this wait raises is the next turn's flag, or a wavefront that has
+// not looked yet would leave a turn before the others.
+constexpr __host__ __device__ int late_seen(int turn) { return turn & 1; }
+constexpr __host__ __device__ int late_of_coefficients(int turn) { return late_seen(turn); }
+constexpr __host__ __device__ int late_of_sums(int turn) { return late_seen(turn + 1); }
+
 struct OnePassArgs {
     OnePassShape shape;
     int model;
