@@ -109,15 +109,17 @@ __device__ __forceinline__ bool take_words(const unsigned long long* base, const
     return true;
 }
 
-// A number that the compiler takes for a new one: what follows from it is not kept from turn to turn, for which there are no
-// registers.
+// A number that the compiler takes for a new one: what follows from it is not kept from turn to turn, for which the kernels that
+// stage rows have no registers.  The one for small gradients has them, and keeps it: with the thread as a new number in every use and
+// strips of any width its calls of 2 to 3 MB a gradient took 1 to 2.5 % longer (n = 16, d = 8000, M = 88, 200 events 557 us, 546 with it).
 __device__ __forceinline__ int anew(int v) {
     asm volatile("" : "+s"(v));
     return v;
 }
+template <bool kAnew = true>
 __device__ __forceinline__ int my_thread() {
     int v = threadIdx.x;
-    asm volatile("" : "+v"(v));
+    if (kAnew) asm volatile("" : "+v"(v));
     return v;
 }
 // Coefficient (times gscale) and loss of a sample from its dot product with the point.
@@ -139,9 +141,10 @@ constexpr uint64_t kShareTicks = 10ull * 1000 * 1000 * 100;      // of the const
 
 template <int kRows, int kChunks, bool kStage>
 struct OnePassShared {
-    static constexpr int kReduce = kChunks == 4 ? 2 : kChunks < 3 ? kChunks : 3;       // chunks whose partial gradients are in LDS at a time
+    // chunks whose partial gradients are in LDS at a time
+    static constexpr int kReduce = !kStage ? (kChunks < 4 ? kChunks : 4) : kChunks == 4 ? 2 : kChunks < 3 ? kChunks : 3;
     static constexpr int kStaged = !kStage ? 0 : kRows * kChunks <= 16 ? kRows : 16 / kChunks;       // last rows of a wavefront's
-    __attribute__((aligned(16))) v4f stage[kOnePassWaves][kStaged + (kStage ? 0 : 1)][kStage ? kChunks : 1][64];       // of the next gradient
+    __attribute__((aligned(16))) v4f stage[kStage ? kOnePassWaves : 1][kStage ? kStaged : 1][kStage ? kChunks : 1][kStage ? 64 : 1];       // of the next gradient
     __attribute__((aligned(16))) v4f red[kOnePassWaves][kReduce][64];
     float part[kOnePassWaves][kOnePassMaxM + 1];            // [column group][sample]
     // by row group and row: entry place_of(m) is sample m's; beyond M: coefficient 0, row 0 (of which nothing is read)
@@ -153,17 +156,19 @@ struct OnePassShared {
     int lost;
 };
 
+// Columns of a wavefront: whole vectors where rows are not staged.
+template <int kChunks, bool kStage>
+__device__ __forceinline__ int wave_columns(const OnePassParams& p) { return kStage ? p.a.shape.wave_cols : 256 * kChunks; }
 // What a thread has of a strip: the same in every block that works on it.
 struct StripPlace {
     int64_t col0;                                // of its wavefront
     int bytes, offset, row_group, col_group;     // in bounds from col0 on; of its lane
     int rows;                                    // of its row group
-    __device__ __forceinline__ StripPlace(const OnePassParams& p, int strip) {
+    __device__ __forceinline__ StripPlace(const OnePassParams& p, int strip, int columns) {
         const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
         row_group = wave & (p.a.shape.row_groups - 1);
         col_group = wave >> p.log_groups;
         rows = (p.a.M - row_group + p.a.shape.row_groups - 1) >> p.log_groups;
-        const int columns = p.a.shape.wave_cols;
         col0 = (static_cast<int64_t>(strip) * (kOnePassWaves >> p.log_groups) + col_group) * columns;
         const int64_t left = 4 * (p.a.d - col0);
         bytes = left <= 0 ? 0 : left < 4 * columns ? static_cast<int>(left) : 4 * columns;
@@ -314,7 +319,7 @@ __device__ __forceinline__ float row_dot(const v4f (&row)[kChunks], const v4f (&
 // Partial dot products of rows r0, r0 + 1, ... of the wavefront's, summed over its lanes, to part[column group][sample].
 template <int kRows, bool kAside, int kBatch>
 __device__ __forceinline__ void put_parts(const OnePassArgs& a, const StripPlace& at, int r0, const float (&v)[kBatch], float (*part)[kOnePassMaxM + 1]) {
-    const int lane = my_thread() & 63;
+    const int lane = my_thread<kAside>() & 63;
     const float z = wave_sums(v, lane);
     const int r = r0 + lane / (64 / kBatch), m = at.row_group + a.shape.row_groups * r;
     if (lane % (64 / kBatch) == 0 && r < kRows && m < a.M) put_part<kAside>(&part[at.col_group][m], z);
@@ -323,7 +328,7 @@ template <bool kAside, int kChunks>
 __device__ __forceinline__ void put_square(const OnePassParams& p, const StripPlace& at, const v4f (&x)[kChunks], float (*part)[kOnePassMaxM + 1]) {
     if (p.samples <= p.a.M || at.row_group != 0) return;
     const float z = all_sum(row_dot(x, x));
-    if ((my_thread() & 63) == 0) put_part<kAside>(&part[at.col_group][p.a.M], z);
+    if ((my_thread<kAside>() & 63) == 0) put_part<kAside>(&part[at.col_group][p.a.M], z);
 }
 // A sample's sum over the column groups of a strip.
 template <bool kAside>
@@ -343,9 +348,9 @@ __device__ __forceinline__ float strip_sum(const OnePassParams& p, const float (
 }
 // Sums over the strips of samples m, m + step, ... below samples, kN at most, by a wavefront; false when the time is up.
 constexpr int kLines = kOnePassMaxStrips / 64;
-template <int kN>
+template <bool kAnew, int kN>
 __device__ __forceinline__ void sums_at(int m, int step, int samples, int S, int (&at)[kN * kLines]) {
-    const int lane = my_thread() & 63;
+    const int lane = my_thread<kAnew>() & 63;
 #pragma unroll
     for (int i = 0; i < kN; ++i)
 #pragma unroll
@@ -361,11 +366,11 @@ __device__ __forceinline__ void add_sums(const float (&v)[kN * kLines], float (&
         dot[i] = all_sum(dot[i]);
     }
 }
-template <int kN>
+template <bool kAnew, int kN>
 __device__ __forceinline__ bool take_sums(const unsigned long long* sums, int m, int step, int samples, int S, uint32_t seq, uint64_t until, float (&dot)[kN]) {
     int at[kN * kLines];
     float v[kN * kLines];
-    sums_at<kN>(m, step, samples, S, at);
+    sums_at<kAnew, kN>(m, step, samples, S, at);
     const bool there = take_words(sums, at, seq, until, v);
     add_sums<kN>(v, dot);
     return there;
@@ -408,8 +413,9 @@ __device__ __forceinline__ v2f finish_sample(const OnePassArgs& a, int m, float 
     return m < a.M ? coefficient(a, dot, target) : v2f{0.0f, 0.5f * a.lambda * static_cast<float>(a.M) * dot};
 }
 // The minibatch loss from those of its samples, by a wavefront.
+template <bool kAnew>
 __device__ __forceinline__ void put_loss(const OnePassParams& p, const GradOp& op, const float* loss) {
-    const int lane = my_thread() & 63;
+    const int lane = my_thread<kAnew>() & 63;
     float sum = 0.0f;
     for (int m = lane; m < p.samples; m += 64) sum += loss[m];
     sum = all_sum(sum);
@@ -423,18 +429,20 @@ __device__ __forceinline__ float point_weight(const OnePassArgs& a, const StripP
 template <int kRows, int kChunks, bool kStage>
 __device__ __forceinline__ void put_gradient(const OnePassParams& p, const GradOp& op, const StripPlace& at, int strip, const v4f (&acc)[kChunks], OnePassShared<kRows, kChunks, kStage>& s) {
     constexpr int kReduce = OnePassShared<kRows, kChunks, kStage>::kReduce;
-    const int tid = my_thread(), lane = tid & 63, wave = tid >> 6, row_groups = p.a.shape.row_groups, col_groups = kOnePassWaves / row_groups;
+    const int tid = my_thread<kStage>(), lane = tid & 63, wave = tid >> 6, row_groups = p.a.shape.row_groups, col_groups = kOnePassWaves / row_groups;
     float* const g = p.a.slots + static_cast<int64_t>(op.slot) * p.a.ld;
     if (row_groups == 1) {
 #pragma unroll
         for (int c = 0; c < kChunks; ++c) {
             const int64_t e = at.col0 + 256 * c + 4 * lane;
-            if (16 * lane + 1024 * c + 16 <= at.bytes) *reinterpret_cast<v4f*>(g + e) = acc[c];
+            if (!kStage) {                               // whole vectors: the strip ends where its last one does
+                if (e < 4 * p.n_vec) *reinterpret_cast<v4f*>(g + e) = zero_beyond(acc[c], e, p.a.d);
+            } else if (16 * lane + 1024 * c + 16 <= at.bytes) *reinterpret_cast<v4f*>(g + e) = acc[c];
             else if (16 * lane + 1024 * c < at.bytes) *reinterpret_cast<v4f*>(g + e) = zero_beyond(acc[c], e, p.a.d);
         }
         return;
     }
-    const int columns = p.a.shape.wave_cols;
+    const int columns = wave_columns<kChunks, kStage>(p);
     const int64_t tile0 = static_cast<int64_t>(strip) * (col_groups * columns);       // the sums of the row groups through LDS
 #pragma unroll
     for (int c0 = 0; c0 < kChunks; c0 += kReduce) {
@@ -531,7 +539,7 @@ __device__ __attribute__((noinline)) void take_tickets(const OnePassParams* para
         const int word_at[1] = {tid < p.samples ? tid : -1};
         float word[1];
         if (share < S) {
-            const StripPlace at(p, strip);
+            const StripPlace at(p, strip, wave_columns<kChunks, kStage>(p));
             v4f x[kChunks];
             request_point(a, op, at, at.bytes, x);
             if (op.comp_slot >= 0) compensate_point(a, op, at, x);
@@ -577,7 +585,7 @@ __device__ __attribute__((noinline)) void take_tickets(const OnePassParams* para
                     const int m = m0 + u * kOnePassWaves;
                     target[u] = m < M ? target_at(op, s.idx[0][place_of<kRows>(p, m)]) : 0.0f;
                 }
-                there = take_sums(words.share_sums, m0, kOnePassWaves, p.samples, S, seq, until, dot);
+                there = take_sums<true>(words.share_sums, m0, kOnePassWaves, p.samples, S, seq, until, dot);
 #pragma unroll
                 for (int u = 0; u < kAtOnce; ++u) {
                     const int m = m0 + u * kOnePassWaves;
@@ -591,9 +599,9 @@ __device__ __attribute__((noinline)) void take_tickets(const OnePassParams* para
             if (!there && lane == 0) s.lost = 1;
             __syncthreads();
             if (s.lost != 0) break;
-            if (a.loss && wave == 0) put_loss(p, op, s.loss);
+            if (a.loss && wave == 0) put_loss<true>(p, op, s.loss);
         } else {
-            const StripPlace at(p, strip);
+            const StripPlace at(p, strip, wave_columns<kChunks, kStage>(p));
             if (wave < word_waves) {
                 there = take_words(words.share_coefs, word_at, seq, until, word);
                 if (tid < M) s.coef[place_of<kRows>(p, tid)] = word[0];
@@ -646,7 +654,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
     const int group = blockIdx.x % groups, strip = blockIdx.x / groups;
     const bool logistic = a.model == ADPSGD_MODEL_LOGREG;
     const GroupWords words(p, group);
-    const StripPlace at(p, strip);
+    const StripPlace at(p, strip, wave_columns<kChunks, false>(p));
 
     v4f row[kRows][kChunks], x[kChunks];
     int q = group, turn = 0;
@@ -687,7 +695,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
         for (int m = strip + S * wave; there && m < p.samples; m += S * kOnePassWaves) {
             const float target = m < M ? target_at(op, s.idx[turn][m]) : 0.0f;
             float dot[1];
-            there = take_sums(words.sums, m, 0, p.samples, S, seq, until, dot);
+            there = take_sums<false>(words.sums, m, 0, p.samples, S, seq, until, dot);
             if (there && lane == 0) {
                 const v2f r = finish_sample(a, m, dot[0], target);
                 put_word(words.coefs, m, r.x, seq);
@@ -735,7 +743,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
             __builtin_amdgcn_sched_barrier(0);
         }
         put_gradient(p, op, at, strip, acc, s);
-        if (a.loss && strip == 0 && wave == 7) put_loss(p, op, s.loss);
+        if (a.loss && strip == 0 && wave == 7) put_loss<false>(p, op, s.loss);
         if (!more) break;
         q += groups;
         op = next;
@@ -758,7 +766,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
     const int group = blockIdx.x % groups, strip = blockIdx.x / groups;
     const bool logistic = a.model == ADPSGD_MODEL_LOGREG;
     const GroupWords words(p, group);
-    const StripPlace at(p, strip);
+    const StripPlace at(p, strip, wave_columns<kChunks, true>(p));
 
     v4f row[kRows][kChunks], x[kChunks];
     v4f(*const stage)[kChunks][64] = s.stage[wave];
@@ -815,7 +823,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
         for (int m = strip + S * wave; there && m < p.samples; m += S * kOnePassWaves) {
             const float target = m < M ? target_at(op, s.idx[turn][place_of<kRows>(p, m)]) : 0.0f;
             float dot[1];
-            there = take_sums(words.sums, m, 0, p.samples, S, seq, until, dot);
+            there = take_sums<true>(words.sums, m, 0, p.samples, S, seq, until, dot);
             if (there && lane == 0) {
                 const v2f r = finish_sample(a, m, dot[0], target);
                 put_word(words.coefs, m, r.x, seq);
@@ -868,7 +876,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
         }
         put_gradient(p, op, at, strip, acc, s);
         if (kPointLast) request_point(a, next, at, next_bytes, x);
-        if (a.loss && strip == 0 && wave == 7) put_loss(p, op, s.loss);
+        if (a.loss && strip == 0 && wave == 7) put_loss<true>(p, op, s.loss);
         if (!more) {
             __builtin_amdgcn_s_waitcnt(0);             // nothing is on its way to LDS when the block ends
             break;
@@ -915,7 +923,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
     const int count = (a.n_ops - group + groups - 1) / groups;           // gradients of the group
     const bool logistic = a.model == ADPSGD_MODEL_LOGREG;
     const GroupWords words(p, group);
-    const StripPlace at(p, strip);
+    const StripPlace at(p, strip, wave_columns<kChunks, true>(p));
     v4f(*const stage)[kChunks][64] = s.stage[wave];
     if (count <= 0) return;
 
@@ -1051,7 +1059,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
         if (t >= 1) {
             const GradOp op = op_of(t - 1);
             put_gradient(p, op, at, strip, acc, s);
-            if (a.loss && strip == 0 && wave == 7) put_loss(p, op, s.loss);
+            if (a.loss && strip == 0 && wave == 7) put_loss<true>(p, op, s.loss);
         }
 
         stage_rows(t + 2, kHalf, kRest, places);
