@@ -14,7 +14,7 @@ LIB = HERE / "libadpsgd.so"
 OBJ = HERE / "_build"
 STREAM_BENCH = HERE / "stream_bench"       # stand-alone streaming microbenchmarks (csrc/stream_bench.hip)
 
-SOURCES = ["api.cpp", "api_sync.cpp", "api_diag.cpp", "schedule.cpp", "planner.cpp", "strips.cpp", "kernels_fused.hip", "kernels_columns.hip",
+SOURCES = ["api.cpp", "api_sync.cpp", "api_diag.cpp", "schedule.cpp", "planner.cpp", "strips.cpp", "onepass.cpp", "kernels_fused.hip", "kernels_columns.hip",
            "kernels_strips.hip", "kernels_grad_linear.hip", "kernels_onepass.hip",
            "kernels_mlp.hip", "kernels_diag.hip", "kernels_sync.hip"]
 HEADERS = ["internal.hpp", "strips.hpp", "onepass.hpp", "exchange.hpp", "handle.hpp", "device_common.hpp", "chains.hpp"]

@@ -30,6 +30,16 @@ struct OnePassShape {
 constexpr int64_t onepass_group_words(const OnePassShape& s, int32_t samples) {
     return static_cast<int64_t>(samples) * (s.ring() * (s.strips + 2) + s.strips + 1) + 2;
 }
+// Rows and chunks of the kernels that are built, and which of the three for them.
+struct OnePassHeld {
+    int rows, chunks;
+};
+constexpr OnePassHeld kOnePassHeld[] = {{2, 4}, {2, 8}, {4, 2}, {4, 4}, {4, 8}, {6, 1}, {6, 2}, {6, 5}, {6, 6}, {6, 8}, {8, 1},
+                                        {8, 2}, {8, 4}, {8, 5}, {8, 6}, {12, 1}, {12, 2}, {12, 3}, {12, 4}, {16, 1}, {16, 2}, {16, 3}};
+constexpr bool onepass_built(OnePassKernel kernel, int rows, int chunks) {
+    const int held = rows * chunks;
+    return kernel == OnePassKernel::kPipeline ? held <= (rows <= 4 ? 8 : 16) : kernel == OnePassKernel::kStaged ? held > 16 || rows == 2 : held <= 32;
+}
 // The shape for a handle, by its sizes alone (so that a gradient has the same bits in every call and however its blocks are
 // scheduled), or one that is not ok():
 // three launches per round (kernels_grad_linear.hip) are the better route, or the only one.

@@ -1,0 +1,40 @@
+// The shapes of the linear gradients in one pass (csrc/onepass.cpp), over minibatches, lengths and numbers of compute units from a
+// partition of the device to more than one has: whatever is accepted is built, covers the gradient and fits the chip.
+#include <cmath>
+#include <cstdio>
+#include <random>
+
+#include "onepass.hpp"
+
+using namespace adpsgd_impl;
+
+int main() {
+    std::mt19937 rng(3);
+    long ok = 0, by_kernel[3] = {0, 0, 0};
+    auto fail = [](const char* what, int model, long long d, int M, int cus, const OnePassShape& s) {
+        std::printf("%s: model %d, d %lld, M %d, %d compute units: %d rows, %d chunks, %d row groups, %d strips, %d groups, %d columns, kernel %d\n", what, model, d, M,
+                    cus, s.rows, s.chunks, s.row_groups, s.strips, s.groups, s.wave_cols, static_cast<int>(s.kernel));
+        return 1;
+    };
+    for (int cus : {16, 20, 32, 38, 64, 80, 104, 128, 228, 256, 304})
+        for (int M = 1; M <= 128; ++M)
+            for (int i = 0; i < 500; ++i) {
+                const int model = i & 1 ? ADPSGD_MODEL_LSQ : ADPSGD_MODEL_LOGREG;
+                const auto d = static_cast<int64_t>(std::exp(std::uniform_real_distribution<double>(std::log(2000.0), std::log(4e7))(rng)));
+                const OnePassShape s = onepass_shape(model, d, M, cus);
+                if (!s.ok()) continue;
+                ++ok;
+                ++by_kernel[static_cast<int>(s.kernel)];
+                bool held = false;
+                for (const OnePassHeld& h : kOnePassHeld) held |= h.rows == s.rows && h.chunks == s.chunks;
+                if (!held || !onepass_built(s.kernel, s.rows, s.chunks)) return fail("not built", model, d, M, cus, s);
+                const int64_t columns = static_cast<int64_t>(kOnePassWaves / s.row_groups) * s.wave_cols;
+                if (s.rows * s.row_groups < M || s.rows * s.row_groups > kOnePassMaxM) return fail("rows", model, d, M, cus, s);
+                if (s.wave_cols > 256 * s.chunks || s.wave_cols % 32 != 0 || (s.kernel == OnePassKernel::kPlain && s.wave_cols != 256 * s.chunks)) return fail("columns", model, d, M, cus, s);
+                if (columns * s.strips < d || columns * (s.strips - 1) >= d) return fail("strips", model, d, M, cus, s);
+                if (s.groups < 1 || s.strips * s.groups > cus || s.strips > kOnePassMaxStrips) return fail("compute units", model, d, M, cus, s);
+            }
+    if (by_kernel[0] == 0 || by_kernel[1] == 0 || by_kernel[2] == 0) return std::printf("a kernel without shapes\n"), 1;
+    std::printf("ok, %ld shapes, %ld + %ld + %ld\n", ok, by_kernel[0], by_kernel[1], by_kernel[2]);
+    return 0;
+}
