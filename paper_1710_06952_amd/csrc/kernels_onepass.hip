@@ -377,18 +377,13 @@ __device__ __forceinline__ bool take_sums(const unsigned long long* sums, int m,
     add_sums<kN>(v, dot);
     return there;
 }
-// The same for one sample, or for two, m and m + 8 S, where there are up to 16 strips, in two steps.  Lanes without a word look at
-// the one of the last lane.
-__device__ __forceinline__ void ask_sums(const unsigned long long* sums, int m, int samples, int S, unsigned long long (&w)[kLines]) {
+// The same for one sample in two steps.  Lanes without a word look at the one of the last lane.
+__device__ __forceinline__ void ask_sums(const unsigned long long* sums, int m, int S, unsigned long long (&w)[kLines]) {
     const int lane = my_thread() & 63;
 #pragma unroll
-    for (int u = 0; u < kLines; ++u) {
-        const int from = S > 16 ? m : min(m + 8 * S * u, samples - 1), word = S > 16 ? lane + 64 * u : lane;
-        w[u] = __hip_atomic_load(sums + from * S + min(word, S - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    for (int u = 0; u < kLines; ++u) w[u] = __hip_atomic_load(sums + m * S + min(lane + 64 * u, S - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ bool answer_sums(const unsigned long long* sums, int m, int samples, int S, uint32_t seq, uint64_t ticks, unsigned long long (&w)[kLines],
-                                            float (&dot)[2]) {
+__device__ __forceinline__ bool answer_sums(const unsigned long long* sums, int m, int S, uint32_t seq, uint64_t ticks, unsigned long long (&w)[kLines], float& dot) {
     auto missing = [&]() {
         bool complete = true;
 #pragma unroll
@@ -399,16 +394,15 @@ __device__ __forceinline__ bool answer_sums(const unsigned long long* sums, int 
         const uint64_t until = wall_clock64() + ticks;
         do {
             if (wall_clock64() >= until) return false;
-            ask_sums(sums, m, samples, S, w);
+            ask_sums(sums, m, S, w);
         } while (missing());
     }
     const int lane = my_thread() & 63;
     float v[kLines];
 #pragma unroll
-    for (int u = 0; u < kLines; ++u) v[u] = (S > 16 ? lane + 64 * u : lane) < S ? __uint_as_float(static_cast<uint32_t>(w[u])) : 0.0f;
+    for (int u = 0; u < kLines; ++u) v[u] = lane + 64 * u < S ? __uint_as_float(static_cast<uint32_t>(w[u])) : 0.0f;
     static_assert(kLines == 4, "");
-    dot[0] = all_sum(S > 16 ? ((v[0] + v[1]) + v[2]) + v[3] : v[0]);
-    dot[1] = S > 16 ? 0.0f : all_sum(v[1]);
+    dot = all_sum(((v[0] + v[1]) + v[2]) + v[3]);
     return true;
 }
 __device__ __forceinline__ v2f finish_sample(const OnePassArgs& a, int m, float dot, float target) {
@@ -915,7 +909,6 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
 template <int kRows, int kChunks>
 __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void onepass_pipeline_kernel(const OnePassParams p) {
     constexpr int kQuarter = kRows / 4, kHalf = kRows / 2, kRest = kRows - (kRows + 3) / 4, kBatch = kRows % 8 == 0 ? 8 : 4;
-    constexpr int kAdds = 2;            // samples that a wavefront adds up at most
     static_assert(OnePassShared<kRows, kChunks, true>::kStaged == kRows, "all rows go through LDS");
     __shared__ OnePassShared<kRows, kChunks, true> s;
     const OnePassArgs& a = p.a;
@@ -932,13 +925,12 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
     auto op_of = [&](int t) { return op_at(a.ops + group + groups * max(0, min(t, count - 1))); };
     auto index_at = [&](int t, int m) { return a.batch_idx[static_cast<int64_t>(op_of(t).event) * M + min(m, M - 1)]; };
     const int my_row = at.row_group + (min(lane, kRows - 1) << p.log_groups);
-    const int adds = strip + S * ((wave + 5) & 7);       // sample that the wavefront adds up (and the one 8 S further); the first on wavefront 3
+    const int adds = strip + S * ((wave + 5) & 7);       // sample that the wavefront adds up; the first on wavefront 3
     int word_at[1] = {-1};                               // coefficients on the first wavefronts, losses from the fifth on
     if (tid < 256) word_at[0] = tid < p.samples ? tid : -1;
     else if (a.loss && strip == 0) word_at[0] = tid - 256 < p.samples ? tid - 256 : -1;
     unsigned long long word[1] = {0};
     int32_t indices;                                     // of the rows of t + 2
-    int32_t target_row[kAdds];
 
     v4f rows_a[kRows][kChunks], rows_b[kRows][kChunks], x_a[kChunks], x_b[kChunks], x_in[kChunks];
 #pragma unroll
@@ -957,8 +949,7 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
             if (r >= from && r < to) stage_row<kChunks>(row_buffer(places, r, rows, bytes), at, stage[r]);
     };
     indices = index_at(0, my_row);
-#pragma unroll
-    for (int i = 0; i < kAdds; ++i) target_row[i] = index_at(0, adds + 8 * S * i);
+    int32_t target_row = index_at(0, adds);              // of the sample that it adds up
     request_point(a, op_of(0), at, at.bytes, x_in);
     {
         const uint64_t places = row_places(op_of(0), at, indices);
@@ -1019,18 +1010,11 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
         const unsigned long long* const sums = words.sums + (t & 1) * p.samples * S;
         const uint64_t places = row_places(op_of(t + 2), at, indices);
         indices = index_at(t + 3, my_row);
-        float target[kAdds];
         unsigned long long sum_word[kLines];
-        {
-            const GradOp op = op_of(t);
-#pragma unroll
-            for (int i = 0; i < kAdds; ++i) {
-                target[i] = target_at(op, target_row[i]);
-                target_row[i] = index_at(t + 1, adds + 8 * S * i);
-            }
-        }
+        const float target = target_at(op_of(t), target_row);
+        target_row = index_at(t + 1, adds);
         const bool adding = sums_due && adds < p.samples;
-        if (adding) ask_sums(sums, adds, p.samples, S, sum_word);
+        if (adding) ask_sums(sums, adds, S, sum_word);
         request_point(a, op_of(t + 2), at, t + 2 < count ? at.bytes : 0, x_in);
         stage_rows(t + 2, 0, kQuarter, places);
 
@@ -1040,17 +1024,12 @@ __global__ __launch_bounds__(kOnePassThreads) __attribute__((amdgpu_waves_per_eu
         take_rows(kHalf, kRows);
         if (adding) {
             const uint32_t seq = a.seq0 + static_cast<uint32_t>(group + groups * t);
-            float dot[kAdds];
-            if (a.wait_ticks > 0 && answer_sums(sums, adds, p.samples, S, seq, a.wait_ticks, sum_word, dot)) {
-#pragma unroll
-                for (int i = 0; i < kAdds; ++i) {
-                    const int m = adds + 8 * S * i;
-                    if (m >= p.samples) break;
-                    const v2f r = finish_sample(a, m, dot[i], target[i]);
-                    if (lane == 0) {
-                        put_word(words.coefs + (t & 1) * p.samples, m, r.x, seq);
-                        if (a.loss) put_word(words.losses + (t & 1) * p.samples, m, r.y, seq);
-                    }
+            float dot;
+            if (a.wait_ticks > 0 && answer_sums(sums, adds, S, seq, a.wait_ticks, sum_word, dot)) {
+                const v2f r = finish_sample(a, adds, dot, target);
+                if (lane == 0) {
+                    put_word(words.coefs + (t & 1) * p.samples, adds, r.x, seq);
+                    if (a.loss) put_word(words.losses + (t & 1) * p.samples, adds, r.y, seq);
                 }
             } else if (lane == 0) s.late[late_of_sums(t)] = 1;
         }
@@ -1109,6 +1088,7 @@ hipError_t launch_shape(const OnePassParams& p, hipStream_t st) {
     q.a.shape.groups = groups;
     const dim3 grid(groups * p.a.shape.strips), block(kOnePassThreads);
     if (q.a.shape.kernel == OnePassKernel::kPipeline) {
+        if (kOnePassWaves * q.a.shape.strips < q.samples) return hipErrorInvalidValue;         // a wavefront adds up one sample
         if constexpr (onepass_built(OnePassKernel::kPipeline, kRows, kChunks)) hipLaunchKernelGGL((onepass_pipeline_kernel<kRows, kChunks>), grid, block, 0, st, q);
         else return hipErrorInvalidValue;
     } else if (q.a.shape.kernel == OnePassKernel::kStaged) {

@@ -28,13 +28,14 @@ OnePassShape onepass_shape(int model, int64_t d, int32_t M, int32_t compute_unit
     const int rows = (M + s.row_groups - 1) / s.row_groups, most = std::min(compute_units, kOnePassMaxStrips);
     s.rows = rows <= 2 ? 2 : rows <= 4 ? 4 : rows <= 6 ? 6 : rows <= 8 ? 8 : rows <= 12 ? 12 : 16;
     int64_t strips = 0;
-    auto hold = [&](int held) {
-        s.chunks = std::max(1, held / s.rows);
+    auto cut = [&](int chunks) {
+        s.chunks = chunks;
         const int64_t tile = 256ll * s.chunks * (kOnePassWaves / s.row_groups);
         strips = (d + tile - 1) / tile;
     };
+    auto hold = [&](int held) { cut(std::max(1, held / s.rows)); };
     const bool large = 4.0 * M * static_cast<double>(d) >= (s.rows == 6 ? 2.0 : 1.0) * kOnePassLargeBytes;
-    if (large) hold(s.rows <= 4 ? 8 : 16);
+    if (large) cut(onepass_pipeline_chunks(s.rows));
     s.kernel = !large ? OnePassKernel::kPlain : strips <= most ? OnePassKernel::kPipeline : OnePassKernel::kStaged;
     if (s.kernel != OnePassKernel::kPipeline) {
         hold(s.rows == 2 ? 16 : 32);

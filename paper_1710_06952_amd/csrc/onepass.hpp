@@ -36,9 +36,11 @@ struct OnePassHeld {
 };
 constexpr OnePassHeld kOnePassHeld[] = {{2, 4}, {2, 8}, {4, 2}, {4, 4}, {4, 8}, {6, 1}, {6, 2}, {6, 5}, {6, 6}, {6, 8}, {8, 1},
                                         {8, 2}, {8, 4}, {8, 5}, {8, 6}, {12, 1}, {12, 2}, {12, 3}, {12, 4}, {16, 1}, {16, 2}, {16, 3}};
+constexpr int onepass_pipeline_chunks(int rows) { return rows <= 4 ? 8 / rows : rows <= 8 ? 2 : 1; }      // two gradients of them fit
 constexpr bool onepass_built(OnePassKernel kernel, int rows, int chunks) {
-    const int held = rows * chunks;
-    return kernel == OnePassKernel::kPipeline ? held <= (rows <= 4 ? 8 : 16) : kernel == OnePassKernel::kStaged ? held > 16 || rows == 2 : held <= 32;
+    return kernel == OnePassKernel::kPipeline ? chunks == onepass_pipeline_chunks(rows)
+           : kernel == OnePassKernel::kStaged ? rows * chunks > (rows == 2 ? 8 : 16)
+                                              : rows * chunks <= 32;
 }
 // The shape for a handle, by its sizes alone (so that a gradient has the same bits in every call and however its blocks are
 // scheduled), or one that is not ok():

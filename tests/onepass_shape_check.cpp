@@ -1,5 +1,6 @@
 // The shapes of the linear gradients in one pass (csrc/onepass.cpp), over minibatches, lengths and numbers of compute units from a
-// partition of the device to more than one has: whatever is accepted is built, covers the gradient and fits the chip.
+// partition of the device to more than one has: whatever is accepted is built, covers the gradient and fits the chip, and
+// whatever is built is chosen.
 #include <cmath>
 #include <cstdio>
 #include <random>
@@ -10,7 +11,7 @@ using namespace adpsgd_impl;
 
 int main() {
     std::mt19937 rng(3);
-    long ok = 0, by_kernel[3] = {0, 0, 0};
+    long ok = 0, by_kernel[3] = {0, 0, 0}, chosen[3][17][9] = {};
     auto fail = [](const char* what, int model, long long d, int M, int cus, const OnePassShape& s) {
         std::printf("%s: model %d, d %lld, M %d, %d compute units: %d rows, %d chunks, %d row groups, %d strips, %d groups, %d columns, kernel %d\n", what, model, d, M,
                     cus, s.rows, s.chunks, s.row_groups, s.strips, s.groups, s.wave_cols, static_cast<int>(s.kernel));
@@ -27,13 +28,19 @@ int main() {
                 ++by_kernel[static_cast<int>(s.kernel)];
                 bool held = false;
                 for (const OnePassHeld& h : kOnePassHeld) held |= h.rows == s.rows && h.chunks == s.chunks;
+                ++chosen[static_cast<int>(s.kernel)][s.rows][s.chunks];
                 if (!held || !onepass_built(s.kernel, s.rows, s.chunks)) return fail("not built", model, d, M, cus, s);
                 const int64_t columns = static_cast<int64_t>(kOnePassWaves / s.row_groups) * s.wave_cols;
                 if (s.rows * s.row_groups < M || s.rows * s.row_groups > kOnePassMaxM) return fail("rows", model, d, M, cus, s);
                 if (s.wave_cols > 256 * s.chunks || s.wave_cols % 32 != 0 || (s.kernel == OnePassKernel::kPlain && s.wave_cols != 256 * s.chunks)) return fail("columns", model, d, M, cus, s);
                 if (columns * s.strips < d || columns * (s.strips - 1) >= d) return fail("strips", model, d, M, cus, s);
+                if (s.kernel == OnePassKernel::kPipeline && kOnePassWaves * s.strips < onepass_samples(model, M, true)) return fail("a wavefront would add up two samples", model, d, M, cus, s);
                 if (s.groups < 1 || s.strips * s.groups > cus || s.strips > kOnePassMaxStrips) return fail("compute units", model, d, M, cus, s);
             }
+    for (const OnePassHeld& h : kOnePassHeld)
+        for (OnePassKernel kernel : {OnePassKernel::kPlain, OnePassKernel::kPipeline, OnePassKernel::kStaged})
+            if (onepass_built(kernel, h.rows, h.chunks) && chosen[static_cast<int>(kernel)][h.rows][h.chunks] == 0)
+                return std::printf("kernel %d of %d rows, %d chunks is built and never chosen\n", static_cast<int>(kernel), h.rows, h.chunks), 1;
     if (by_kernel[0] == 0 || by_kernel[1] == 0 || by_kernel[2] == 0) return std::printf("a kernel without shapes\n"), 1;
     std::printf("ok, %ld shapes, %ld + %ld + %ld\n", ok, by_kernel[0], by_kernel[1], by_kernel[2]);
     return 0;
