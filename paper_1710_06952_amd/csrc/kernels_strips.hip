@@ -31,7 +31,8 @@
 // A compute unit returns vector loads in order, so a wait of phase B stands behind the rows requested before it: they go
 // out at the start of phase A (in phase B they cost 0.5 us per iteration), and the helpers load nothing else before a wait.
 // Where several groups exchange, the helpers do not poll before the block's own words are out (kGate).
-// Rows beyond M are requested again in vain (no branch around a load): hence a kernel for every four rows or so.
+// Rows beyond M are requested again in vain (no branch around a load), up to 31 of 96 (M = 65): hence kernels for several numbers of
+// rows of a wavefront (launch_strips).
 //
 // The sums go through the words of exchange.hpp: up to 32 strips exchange them directly; more sum within their XCD first
 // (the blocks of a group share out the samples), and only these sums cross the chip, at most 8 per sample.
@@ -175,7 +176,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     constexpr int kTeamHelpers = kTeams == 12 ? kRows : kTeams == 6 ? 32 : kTeams == 4 ? 64 : 128;      // threads, one per sample
     constexpr int kWordsInFlight = kTeams == 12 && kLds ? 6 : 4;        // per lane of a helper
     // with two teams in a launch of several groups the rows are requested by flat loads, which go out more slowly, while the helpers
-    // poll: n = 5, d = 12 000, M = 128 1.39 ms, 1.44 without
+    // poll: n = 5, d = 12 000, M = 128 1.39 ms, 1.44 without (what a compiler that finds out that these are global would cost)
     using Row = std::conditional_t<kFar && kTeams == 2, const float*, Global<float>>;
     using Vector = std::conditional_t<kFar && kTeams == 2, const v4f*, Global<v4f>>;
     static_assert(kTeams * kTeamHelpers <= kStripHelpers, "a helper per sample of every team");
@@ -412,7 +413,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     const unsigned long long* const base = kFar ? p.sums : a.words;
     bool given_up = a.lose;
     // Coefficients of up to kWords (gradient, sample) pairs per group of lanes that share a sum, from pair `from` on; samples are
-    // padded to a power of two.
+    // padded to kTeamHelpers.
     auto finish_pairs = [&](const v4u* rec, int from, int count, auto words_in_flight) {
         constexpr int kWords = decltype(words_in_flight)::value;
         uint32_t at[kWords], seq[kWords], place[kWords];
@@ -671,6 +672,10 @@ hipError_t launch_strips(const StripArgs& a, hipStream_t st) {
     p.group_size = strip_group_size(a.d);
     p.sum_pitch = (p.samples + 15) & ~15;
     p.sums = a.words + static_cast<int64_t>(kStripRing) * strip_samples(a.model, a.M) * kStripGroups * kStripGroupBlocks;
+    // Rows of a wavefront: the next of 4, 8, 12, 16 with teams of one or two wavefronts (M = 3: 231 us with 4 rows, 285 with 8), of 16, 18, 22
+    // with teams of three or six.  18 where 22 would request 18 to 27 % in vain, for all M = 49 ... 54 and 97 ... 108, 200 events:
+    // n = 8, d = 1500  M = 49, 54, 97, 108: 400, 449, 692, 719 us, with 22 rows 428, 465, 756, 770;  n = 12, d = 20 001  M = 49, 50, 54: 608,
+    // 603, 615 and 627, 624, 633.
     switch (a.teams) {
         case 12: return a.M <= 4 ? launch_rows<12, 4>(p, st) : a.M <= 8 ? launch_rows<12, 8>(p, st) : a.M <= 12 ? launch_rows<12, 12>(p, st) : launch_rows<12, 16>(p, st);
         case 6: return a.M <= 24 ? launch_rows<6, 12>(p, st) : launch_rows<6, 16>(p, st);

@@ -89,7 +89,7 @@ struct StripArgs {
     int64_t ld, d;
     int32_t n;
     int model;               // LSQ or LOGREG
-    int32_t M, teams;
+    int32_t M, teams;        // teams of wavefronts (strip_teams): the evaluations of a record, half the program's teams
     const StripEntry* recs;  // device
     int32_t rec_len, iterations;
     const int32_t* idx;      // device, minibatch indices in the order of evaluation
