@@ -26,9 +26,10 @@ struct alignas(32) PairOp {
 
 // Updates of a round that share rows, executed one after the other (chain_rounds).
 constexpr int kChain = 4;               // operations of a chain, at most; they touch one row more
-// ... of the perceptron: with momentum buffers the rows of a longer chain do not fit the registers, and on large models rounds are
-// bound by the updates' traffic (784-1024-10, 1000 events: 165 rounds, 5.44 ms, with chains of four, 175 and 5.35 with three; 64-256-10,
-// 300 events 1.36 and 1.45 ms, 256-960-3 0.78 and 0.80, 1024-1024-16 2.85 and 2.79)
+// ... of the perceptron: with momentum buffers the rows of a longer chain do not fit the registers, and the larger the model, the more
+// the kernel for four costs where chains of four save no round (T_max = 0, many workers).  Four against three: 36 set-ups up to 2^18
+// parameters 0.97 ... 1.06 times as fast;  24 from there to 684 000  0.995 ... 1.08 with stale gradients, 0.965 ... 1.04 without;  728 650
+// 0.998 and 1.045, 814 090 0.975 and 1.017 (M = 64 and 32).
 constexpr int mlp_chain(bool momentum, int64_t d) { return momentum || d > (1 << 18) ? 3 : kChain; }
 struct UpdateOp {
     const void* features;               // worker i's inputs (average only: those of a worker that has some, read and dropped), or nullptr
