@@ -9,7 +9,8 @@
 // What binds is the memory while rows arrive and the exchange in between.  Three kernels, by the size of a gradient's rows
 // (onepass_shape):
 //   onepass_gradient_kernel   below 8 MB: a gradient at a time, nothing covers the exchange.
-//   onepass_pipeline_kernel   to 33 MB: two gradients in registers, the rows of a third on their way to LDS meanwhile.  n = 32,
+//   onepass_pipeline_kernel   as long as two gradients fit the registers (17 to 33 MB, onepass_pipeline_chunks), and the rows of a third
+//                             are on their way to LDS meanwhile; with 6 rows a wavefront from 16 MB on.  n = 32,
 //                             M = 8, d = 1 M, all 32 gradients of a synchronous iteration: 8.2 us a gradient with the kernel above (of
 //                             the 16 us of two groups side by side 9.6 were the rows of both at the rate of the memory, the rest dot
 //                             products, two steps of the exchange and combination), 6.7 now, of which 6.4 are its 42 MB (rows, x^, g)

@@ -6,8 +6,8 @@
 namespace adpsgd_impl {
 
 // A thread holds up to 32 vectors of four columns, 256 KB a block: with 40 and 48, which gradients beyond 67 MB need, registers
-// spill.  Two gradients fit up to 16 vectors (8 where a wavefront has few rows and with them many columns of x^): 33 MB on all compute
-// units.  The line to the pipeline, 64 and 61 set-ups below and above 4 MB a gradient, against one gradient at a time: below 1 MB 0.80
+// spill.  Two gradients fit up to 16 vectors, 33 MB on all 256 compute units, with 8 or 16 rows a wavefront;  12 and 25 MB with 6 or 12
+// rows, 8 and 17 MB with 2 or 4 (few rows, and with them many columns of x^).  The line to the pipeline, 64 and 61 set-ups below and above 4 MB a gradient, against one gradient at a time: below 1 MB 0.80
 // ... 1.25 times as fast, 3 to 8 MB 0.90 ... 1.17, from 8 MB on 0.98 ... 1.29; with 6 rows, of 16 vectors only 12 in use, 0.92 ... 1.1 at
 // 9.6 MB.  Strips of large gradients are of equal width, as many as the compute units of their group (with widths in whole vectors of a wavefront M = 128,
 // d = 131 073 had 171 strips on 256 compute units).  Below 20 strips the blocks hold less, so that a gradient spreads over more compute units (n = 16, M = 8, d = 131 000

@@ -14,7 +14,7 @@ constexpr int kOnePassMaxStrips = 256;
 // 4.2, 4.2, 4.0 and 4.6, 4.5, 4.1 ms at take_tickets).  The first launch of a process may need it, though: with data that the
 // device has not touched yet (M = 4, d = 327 679, five workers) some blocks of a group come more than 100 us after the others.
 constexpr int64_t kOnePassWaitUs = 300;
-// Bytes of a gradient's rows from which on the kernels for large ones take it (measured at onepass_shape).
+// Bytes of a gradient's rows from which on the kernels for large ones take it, twice as many with 6 rows a wavefront (measured at onepass_shape).
 constexpr double kOnePassLargeBytes = 8e6;
 enum class OnePassKernel : int32_t { kPlain, kPipeline, kStaged };
 
