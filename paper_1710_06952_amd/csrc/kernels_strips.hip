@@ -175,10 +175,13 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
     constexpr int kTeamWaves = kStripMainWaves / kTeams;
     constexpr int kTeamHelpers = kTeams == 12 ? kRows : kTeams == 6 ? 32 : kTeams == 4 ? 64 : 128;      // threads, one per sample
     constexpr int kWordsInFlight = kTeams == 12 && kLds ? 6 : 4;        // per lane of a helper
-    // with two teams in a launch of several groups the rows are requested by flat loads, which go out more slowly, while the helpers
-    // poll: n = 5, d = 12 000, M = 128 1.39 ms, 1.44 without (what a compiler that finds out that these are global would cost)
-    using Row = std::conditional_t<kFar && kTeams == 2, const float*, Global<float>>;
-    using Vector = std::conditional_t<kFar && kTeams == 2, const v4f*, Global<v4f>>;
+    // In a launch of several groups with many rows to a wavefront the rows are requested by flat loads, which go out more slowly, while the
+    // helpers poll (what a compiler that finds out that these are global would cost):  two teams, n = 5, d = 12 000, M = 128 1.39 ms, 1.44
+    // without;  four teams with 18 or 22 rows, 25 calls of M = 49 ... 64, d = 9001 ... 60 000 1.02 times as fast in the mean (0.99 ... 1.05), with
+    // 16 rows (M = 36, 44) 0.955 ... 1.00 times.
+    constexpr bool kSlowRows = kFar && (kTeams == 2 || (kTeams == 4 && kRows > 16));
+    using Row = std::conditional_t<kSlowRows, const float*, Global<float>>;
+    using Vector = std::conditional_t<kSlowRows, const v4f*, Global<v4f>>;
     static_assert(kTeams * kTeamHelpers <= kStripHelpers, "a helper per sample of every team");
     // teams of one wavefront have the whole gradient and put it into its slot themselves
     constexpr bool kDirect = kLds && kTeamWaves == 1;
