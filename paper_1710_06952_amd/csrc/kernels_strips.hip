@@ -404,16 +404,19 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
         for (int u = 0; u < kUps; ++u) up[u] = rec[1 + 4 * kTeams + min(from + u, max(count, 1) - 1)];      // none: row 0, unused
         read_rows();
     };
-    const int log_width = sum_width(kFar ? groups : group_blocks), sub = t & ((1 << log_width) - 1);
-    const int words = kFar ? groups : group_blocks;               // of a sum
+    // Known to the compiler but for two teams in several groups, whose code is the better when it is not: 1 ... 2.5 % of 20 calls of M = 66 ... 128;
+    // in one group, where it is, M = 66 ... 104 gain 1 ... 4 %.
+    const bool several = kFar && kTeams == 2 ? groups > 1 : kFar;
+    const int log_width = sum_width(several ? groups : group_blocks), sub = t & ((1 << log_width) - 1);
+    const int words = several ? groups : group_blocks;               // of a sum
     // word of sample q and partial sum `sub`: by groups of whole lines, or by samples
-    const uint32_t q_pitch = kFar ? 1 : kStripGroupBlocks, sub_pitch = kFar ? p.sum_pitch : 1;
-    const uint32_t ring_pitch = kFar ? groups * p.sum_pitch : S * kStripGroupBlocks;
+    const uint32_t q_pitch = several ? 1 : kStripGroupBlocks, sub_pitch = several ? p.sum_pitch : 1;
+    const uint32_t ring_pitch = several ? groups * p.sum_pitch : S * kStripGroupBlocks;
     const int log_group = sum_width(group_blocks), part = t & ((1 << log_group) - 1), slots = kStripHelpers >> log_group;
     const int mine = rank < S ? (S - rank + group_blocks - 1) / group_blocks : 0;      // samples of a gradient that this block sums
     const uint32_t per_eval = (0xFFFFu + max(mine, 1)) / max(mine, 1);                  // d / mine = d per_eval >> 16 for d mine < 2^16
     const int pair0 = t >> log_width, pair_step = kStripHelpers >> log_width;
-    const unsigned long long* const base = kFar ? p.sums : a.words;
+    const unsigned long long* const base = several ? p.sums : a.words;
     bool given_up = a.lose;
     // Coefficients of up to kWords (gradient, sample) pairs per group of lanes that share a sum, from pair `from` on; samples are
     // padded to kTeamHelpers.
@@ -580,7 +583,7 @@ __global__ __launch_bounds__(kStripThreads) void strip_events_kernel(const Strip
             const uint32_t all = static_cast<uint32_t>(n_evals * kTeamWaves);
             while (__hip_atomic_load(&published_s[it & 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < all) __builtin_amdgcn_s_sleep(1);
         }
-        if (kFar) {             // the group's sums: sample q is summed by the block of rank q mod group_blocks
+        if (several) {          // the group's sums: sample q is summed by the block of rank q mod group_blocks
             for (int d0 = 0; d0 < n_evals * mine; d0 += slots) {
                 int d = d0 + (t >> log_group);
                 const bool live = part < group_blocks && d < n_evals * mine;
@@ -678,12 +681,13 @@ hipError_t launch_strips(const StripArgs& a, hipStream_t st) {
     // Rows of a wavefront: the next of 4, 8, 12, 16 with teams of one or two wavefronts (M = 3: 231 us with 4 rows, 285 with 8), of 16, 18, 22
     // with teams of three or six.  18 where 22 would request 18 to 27 % in vain, for all M = 49 ... 54 and 97 ... 108, 200 events:
     // n = 8, d = 1500  M = 49, 54, 97, 108: 400, 449, 692, 719 us, with 22 rows 428, 465, 756, 770;  n = 12, d = 20 001  M = 49, 50, 54: 608,
-    // 603, 615 and 627, 624, 633.
+    // 603, 615 and 627, 624, 633.  With two teams up to 160 strips: d = 20 001, 30 000, 40 001 1.04 ... 1.07, 1.01 ... 1.03, 1.01 ... 1.03 times as
+    // fast as with 22 rows, 45 001 0.99 ... 1.0, 52 001 and 60 000 0.955 ... 1.0.
     switch (a.teams) {
         case 12: return a.M <= 4 ? launch_rows<12, 4>(p, st) : a.M <= 8 ? launch_rows<12, 8>(p, st) : a.M <= 12 ? launch_rows<12, 12>(p, st) : launch_rows<12, 16>(p, st);
         case 6: return a.M <= 24 ? launch_rows<6, 12>(p, st) : launch_rows<6, 16>(p, st);
         case 4: return a.M <= 48 ? launch_rows<4, 16>(p, st) : a.M <= 54 ? launch_rows<4, 18>(p, st) : launch_rows<4, 22>(p, st);
-        default: return a.M <= 96 ? launch_rows<2, 16>(p, st) : a.M <= 108 ? launch_rows<2, 18>(p, st) : launch_rows<2, 22>(p, st);
+        default: return a.M <= 96 ? launch_rows<2, 16>(p, st) : a.M <= 108 && p.blocks <= 160 ? launch_rows<2, 18>(p, st) : launch_rows<2, 22>(p, st);
     }
 }
 

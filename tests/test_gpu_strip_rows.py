@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 ROWS = [1, 4, 5, 12, 13, 17, 24, 25, 49, 54, 55, 97, 108, 109]
 
 
-@pytest.mark.parametrize("d", [259, 9001])
-@pytest.mark.parametrize("M", ROWS)
+# the last two: 160 strips, up to which six wavefronts with up to 108 samples have 18 rows each, and 161
+@pytest.mark.parametrize("M,d", [(M, d) for d in (259, 9001) for M in ROWS] + [(108, 40_960), (108, 40_961)])
 def test_rows_of_a_variant(P, M, d):  # noqa: F811
     print("strip rows M=%d d=%d" % (M, d), flush=True)
     n, K, T, rows = 5, 40, 4, max(M, 24)
