@@ -9,7 +9,14 @@ namespace adpsgd_impl {
 // spill.  Two gradients fit up to 16 vectors, 33 MB on all 256 compute units, with 8 or 16 rows a wavefront;  12 and 25 MB with 6 or 12
 // rows, 8 and 17 MB with 2 or 4 (few rows, and with them many columns of x^).  The line to the pipeline, 64 and 61 set-ups below and above 4 MB a gradient, against one gradient at a time: below 1 MB 0.80
 // ... 1.25 times as fast, 3 to 8 MB 0.90 ... 1.17, from 8 MB on 0.98 ... 1.29; with 6 rows, of 16 vectors only 12 in use, 0.92 ... 1.1 at
-// 9.6 MB.  Strips of large gradients are of equal width, as many as the compute units of their group (with widths in whole vectors of a wavefront M = 128,
+// 9.6 MB.  But strips are whole compute units, so a gradient a little beyond a half or a third of the device takes one place of the pipeline
+// where the kernel for one at a time has five places for two of them, or three for one, and blocks that are full.  460 set-ups of 8 to 33 MB,
+// rounds of 6 and 14 gradients and synchronous iterations of 24, by places of the one and the other:
+//   1 and 2, 2 and 4, 3 and 5, 3 and 6, 4 and 8   0.97 ... 1.32 times as fast (below 1 only rounds of 6 of 8 to 9.5 MB with M > 64);
+//   1 and 3, 2 and 5   M > 64 0.84 ... 0.99, M = 52 and 64 0.95 ... 1.05 (the least with 1 and 3), M = 26 and 32 0.97 ... 1.12, M <= 8 1.0 ... 1.11;
+//                      M = 45, six rows 1.02 ... 1.07;
+//   1 and 6            M = 4 0.90 ... 1.04; with 1 and 5 0.99 ... 1.03.
+// Strips of large gradients are of equal width, as many as the compute units of their group (with widths in whole vectors of a wavefront M = 128,
 // d = 131 073 had 171 strips on 256 compute units).  Below 20 strips the blocks hold less, so that a gradient spreads over more compute units (n = 16, M = 8, d = 131 000
 // on the 4-regular graph: 786 us for 40 events in three launches a round, 708 with 16 strips, 609 with 32).
 // Measured against the three launches, 450 set-ups of 16 and 40 workers, M = 1 ... 128, 0.25 to 100 MB a gradient:
@@ -34,11 +41,17 @@ OnePassShape onepass_shape(int model, int64_t d, int32_t M, int32_t compute_unit
         strips = (d + tile - 1) / tile;
     };
     auto hold = [&](int held) { cut(std::max(1, held / s.rows)); };
-    const bool large = 4.0 * M * static_cast<double>(d) >= (s.rows == 6 ? 2.0 : 1.0) * kOnePassLargeBytes;
-    if (large) cut(onepass_pipeline_chunks(s.rows));
-    s.kernel = !large ? OnePassKernel::kPlain : strips <= most ? OnePassKernel::kPipeline : OnePassKernel::kStaged;
+    auto at_a_time = [&] { return strips <= most ? most / strips : 0; };
+    const int held = s.rows == 2 ? 16 : 32;
+    if (4.0 * M * static_cast<double>(d) >= (s.rows == 6 ? 2.0 : 1.0) * kOnePassLargeBytes) {
+        hold(held);
+        const int64_t plain = at_a_time();
+        cut(onepass_pipeline_chunks(s.rows));
+        const int64_t pipeline = at_a_time();
+        s.kernel = pipeline == 0 ? OnePassKernel::kStaged : plain <= (s.row_groups == 8 && s.rows >= 8 ? 2 : 5) * pipeline ? OnePassKernel::kPipeline : OnePassKernel::kPlain;
+    }
     if (s.kernel != OnePassKernel::kPipeline) {
-        hold(s.rows == 2 ? 16 : 32);
+        hold(held);
         if (strips > most && s.rows >= 6) hold(40);
         if (strips > most && s.rows >= 6) hold(48);
         if (strips < 20) hold(16);

@@ -41,6 +41,18 @@ int main() {
         for (OnePassKernel kernel : {OnePassKernel::kPlain, OnePassKernel::kPipeline, OnePassKernel::kStaged})
             if (onepass_built(kernel, h.rows, h.chunks) && chosen[static_cast<int>(kernel)][h.rows][h.chunks] == 0)
                 return std::printf("kernel %d of %d rows, %d chunks is built and never chosen\n", static_cast<int>(kernel), h.rows, h.chunks), 1;
+    // next to the sizes from which the pipeline has too few places on 256 compute units, and where places do not count (M <= 32)
+    struct Size {
+        int M;
+        int64_t d;
+        OnePassKernel kernel;
+    };
+    for (const Size& z : {Size{96, 32767, OnePassKernel::kPipeline}, Size{96, 32769, OnePassKernel::kPlain}, Size{128, 16384, OnePassKernel::kPipeline},
+                          Size{128, 16385, OnePassKernel::kPlain}, Size{128, 32768, OnePassKernel::kPipeline}, Size{128, 32769, OnePassKernel::kPlain},
+                          Size{128, 43521, OnePassKernel::kPipeline}, Size{64, 65537, OnePassKernel::kPlain}, Size{32, 131073, OnePassKernel::kPipeline},
+                          Size{8, 524289, OnePassKernel::kPipeline}, Size{45, 98305, OnePassKernel::kPipeline}, Size{4, 688128, OnePassKernel::kPlain},
+                          Size{4, 688129, OnePassKernel::kPipeline}, Size{128, 65537, OnePassKernel::kStaged}})
+        if (onepass_shape(ADPSGD_MODEL_LOGREG, z.d, z.M, 256).kernel != z.kernel) return fail("another kernel", ADPSGD_MODEL_LOGREG, z.d, z.M, 256, onepass_shape(ADPSGD_MODEL_LOGREG, z.d, z.M, 256));
     if (by_kernel[0] == 0 || by_kernel[1] == 0 || by_kernel[2] == 0) return std::printf("a kernel without shapes\n"), 1;
     std::printf("ok, %ld shapes, %ld + %ld + %ld\n", ok, by_kernel[0], by_kernel[1], by_kernel[2]);
     return 0;

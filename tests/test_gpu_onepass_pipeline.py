@@ -10,10 +10,12 @@ from workloads import random_regular4_graph, ring_graph
 pytestmark = pytest.mark.gpu
 
 # (model, M, d): rows of a wavefront 2, 4, 6, 8, 12, 16 in 1, 2, 4 and 8 groups; from 8 MB a gradient (16 MB with 6 rows) on.  The
-# last of a model's rows: whole strips, one column beyond them, odd
+# last of a model's rows: whole strips, one column beyond them, odd.  (96, 32 769), (128, 16 411) and (64, 65 537) are beyond what leaves
+# the pipeline enough places, and go to the kernel for one gradient at a time; (96, 32 767) and (128, 16 383) are not.
 SHAPES = [("logreg", 2, 1_000_003), ("logreg", 3, 699_999), ("lsq", 4, 524_289), ("lsq", 6, 699_999), ("lsq", 8, 262_144), ("lsq", 7, 300_001),
           ("logreg", 8, 1_048_573), ("lsq", 11, 400_002), ("logreg", 16, 131_075), ("lsq", 21, 200_003), ("logreg", 32, 65_541), ("lsq", 45, 100_001),
-          ("lsq", 64, 40_003), ("logreg", 90, 30_017), ("lsq", 96, 32_769), ("logreg", 128, 16_411), ("lsq", 127, 65_533)]
+          ("lsq", 64, 40_003), ("logreg", 90, 30_017), ("lsq", 96, 32_769), ("logreg", 128, 16_411), ("lsq", 127, 65_533),
+          ("lsq", 96, 32_767), ("logreg", 128, 16_383), ("logreg", 64, 65_537)]
 
 
 @pytest.mark.parametrize("model,M,d", SHAPES)
@@ -48,7 +50,8 @@ def test_events(P, model, M, d):  # noqa: F811
 # are beyond the pipeline: one gradient in registers, part of the next one's rows in LDS, six and five to the one group of blocks
 @pytest.mark.parametrize("want_loss", [True, False])
 @pytest.mark.parametrize("model,M,d,n", [("logreg", 128, 16_411, 3), ("lsq", 128, 16_411, 4), ("logreg", 8, 262_147, 7), ("lsq", 8, 1_000_003, 9),
-                                         ("lsq", 32, 65_541, 16), ("lsq", 16, 600_001, 6), ("logreg", 64, 140_003, 5)])
+                                         ("lsq", 32, 65_541, 16), ("logreg", 128, 16_383, 5),
+                                         ("lsq", 16, 600_001, 6), ("logreg", 64, 140_003, 5)])
 def test_synchronous_iterations(P, model, M, d, n, want_loss):  # noqa: F811
     print("pipeline, synchronous %s M=%d d=%d n=%d loss=%s" % (model, M, d, n, want_loss), flush=True)
     S, rows = 3, max(M // 4, 4)
