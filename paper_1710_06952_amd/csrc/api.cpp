@@ -207,14 +207,17 @@ void settle_onepass(adpsgd_t* h) {
         (void)hipGetLastError();
         return;
     }
-    const OnePassShape s = onepass_shape(h->o.model, h->d, h->o.M, cus);
-    if (!s.ok()) return;
+    const OnePassShape s = onepass_shape(h->o.model, h->d, h->o.M, cus), sync = onepass_shape(h->o.model, h->d, h->o.M, cus, h->n);
+    if (!s.ok() || !sync.ok()) return;
+    const size_t bytes = std::max(onepass_exchange_bytes(s, h->o.M), onepass_exchange_bytes(sync, h->o.M));
     const bool has_status = h->exchange_status.p != nullptr;
-    if (h->onepass_words.reserve(onepass_exchange_bytes(s, h->o.M) + sizeof(unsigned long long)) == hipSuccess &&
+    if (h->onepass_words.reserve(bytes + sizeof(unsigned long long)) == hipSuccess &&
         h->exchange_status.reserve(sizeof(int)) == hipSuccess &&
         hipMemsetAsync(h->onepass_words.p, 0, h->onepass_words.cap, h->stream) == hipSuccess) {       // before all launches of the handle
         if (!has_status) *static_cast<int*>(h->exchange_status.p) = 0;
         h->onepass = s;
+        h->onepass_sync = sync;
+        h->onepass_bytes = bytes;
         return;
     }
     (void)hipGetLastError();
@@ -232,14 +235,14 @@ bool can_run_onepass(const adpsgd_t* h) {
     return capture == hipStreamCaptureStatusNone;
 }
 
-int launch_onepass(adpsgd_t* h, const LinearGradArgs& a) {
-    const size_t bytes = onepass_exchange_bytes(h->onepass, a.M);
+int launch_onepass(adpsgd_t* h, const OnePassShape& shape, const LinearGradArgs& a) {
+    const size_t bytes = h->onepass_bytes;
     if (h->onepass_seq > 0xFFFFFFFFu - static_cast<uint32_t>(a.n_ops)) {      // before the numbers wrap
         HIP_TRY(h, hipMemsetAsync(h->onepass_words.p, 0, bytes, h->stream));
         h->onepass_seq = 0;
     }
     const uint64_t wait_us = static_cast<uint64_t>(std::min(h->assembly_us, kOnePassWaitUs));
-    const OnePassArgs o{h->onepass, a.model, a.X, a.ld, a.d, a.ops, a.n_ops, a.M, a.batch_idx, a.slots, a.gscale, a.lambda, a.loss,
+    const OnePassArgs o{shape, a.model, a.X, a.ld, a.d, a.ops, a.n_ops, a.M, a.batch_idx, a.slots, a.gscale, a.lambda, a.loss,
                         static_cast<unsigned long long*>(h->onepass_words.p), static_cast<unsigned long long*>(h->onepass_words.p) + bytes / sizeof(unsigned long long),
                         static_cast<int*>(h->exchange_status.p), h->onepass_seq + 1, wait_us * kClockTicksPerUs};
     HIP_TRY(h, launch_onepass_gradient(o, h->stream));
@@ -804,7 +807,7 @@ int launch_gradients(adpsgd_t* h, const EventCall& c, int32_t r, float* loss, ad
                              static_cast<float*>(h->grad_scratch.p),
                              reinterpret_cast<float*>(static_cast<char*>(h->grad_scratch.p) + c.off_coef), loss, c.lin_factored};
             if (c.onepass) {
-                rc = launch_onepass(h, a);
+                rc = launch_onepass(h, h->onepass, a);
                 if (rc != ADPSGD_OK) return rc;
                 launches = 1;
             } else {
@@ -1187,7 +1190,7 @@ extern "C" int adpsgd_get_late_blocks(adpsgd_t* h, int64_t* out) {
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     unsigned long long count = 0;
     if (h->onepass.ok())
-        HIP_TRY(h, hipMemcpy(&count, static_cast<char*>(h->onepass_words.p) + onepass_exchange_bytes(h->onepass, h->o.M), sizeof(count), hipMemcpyDeviceToHost));
+        HIP_TRY(h, hipMemcpy(&count, static_cast<char*>(h->onepass_words.p) + h->onepass_bytes, sizeof(count), hipMemcpyDeviceToHost));
     *out = static_cast<int64_t>(count);
     return ADPSGD_OK;
 }

@@ -162,7 +162,7 @@ int run_sync_steps_impl(adpsgd_t* h, const adpsgd_sync_schedule_t* s, float* los
                                  static_cast<float*>(h->grad_scratch.p),
                                  reinterpret_cast<float*>(static_cast<char*>(h->grad_scratch.p) + off_coef), loss, false};
                 if (onepass) {
-                    const int rc = launch_onepass(h, a);
+                    const int rc = launch_onepass(h, h->onepass_sync, a);
                     if (rc != ADPSGD_OK) return rc;
                     launches = 1;
                 } else {

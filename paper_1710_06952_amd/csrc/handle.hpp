@@ -82,8 +82,11 @@ struct adpsgd {
     uint32_t exchange_seq = 0;            // ... the sequence number of the last gradient
     adpsgd_impl::HostBuf exchange_status; // ... a word the kernel sets when a wait had to be given up ...
     adpsgd_impl::DevBuf alone_slots;      // ... and slots for a block that executes a call alone
-    adpsgd_impl::OnePassShape onepass;    // linear models, gradients in one pass over the rows; not ok(): in three launches ...
-    adpsgd_impl::DevBuf onepass_words;    // ... the words the blocks exchange, and behind them a count of late blocks ...
+    // linear models, gradients in one pass over the rows, those of events and the n of a synchronous iteration; not ok(), both: in
+    // three launches ...
+    adpsgd_impl::OnePassShape onepass, onepass_sync;
+    adpsgd_impl::DevBuf onepass_words;    // ... the words the blocks exchange, and behind them, at onepass_bytes, a count of late blocks ...
+    size_t onepass_bytes = 0;
     uint32_t onepass_seq = 0;             // ... the sequence number of the last gradient
     int64_t assembly_us = adpsgd_impl::kAssemblyUs;      // adpsgd_set_wait_limits ...
     bool lose_exchange = false;                          // ...
@@ -117,8 +120,8 @@ void settle_strips(adpsgd_t* h);
 void settle_onepass(adpsgd_t* h);
 // Whether this call can take them: a stream under capture would replay their sequence numbers.
 bool can_run_onepass(const adpsgd_t* h);
-// One group of them; `a` as for launch_linear_gradient.
-int launch_onepass(adpsgd_t* h, const LinearGradArgs& a);
+// One group of them; `a` as for launch_linear_gradient, shape: onepass or onepass_sync.
+int launch_onepass(adpsgd_t* h, const OnePassShape& shape, const LinearGradArgs& a);
 // Fold the timings of finished launches into the statistics (synchronises the stream).
 int drain_profile(adpsgd_t* h);
 

@@ -16,6 +16,9 @@ namespace adpsgd_impl {
 //   1 and 3, 2 and 5   M > 64 0.84 ... 0.99, M = 52 and 64 0.95 ... 1.05 (the least with 1 and 3), M = 26 and 32 0.97 ... 1.12, M <= 8 1.0 ... 1.11;
 //                      M = 45, six rows 1.02 ... 1.07;
 //   1 and 6            M = 4 0.90 ... 1.04; with 1 and 5 0.99 ... 1.03.
+// And filling and draining counts where a launch is short: synchronous iterations of 3 to 16 workers, 49 sizes, by the turns of a place of the
+// pipeline against the steps of the other:  2 and more against 1  0.84 ... 1.01 times as fast, 1 against 1 0.98 ... 1.19;  4 against 2  M > 32
+// 0.92 ... 1.03, else 0.985 ... 1.10;  6 against 2 0.91 ... 1.0;  3 against 2 1.03 ... 1.2;  6 against 3 0.97 ... 1.10, all others 1.0 and more.
 // Strips of large gradients are of equal width, as many as the compute units of their group (with widths in whole vectors of a wavefront M = 128,
 // d = 131 073 had 171 strips on 256 compute units).  Below 20 strips the blocks hold less, so that a gradient spreads over more compute units (n = 16, M = 8, d = 131 000
 // on the 4-regular graph: 786 us for 40 events in three launches a round, 708 with 16 strips, 609 with 32).
@@ -27,7 +30,7 @@ namespace adpsgd_impl {
 // On devices (or partitions of one) with fewer compute units a smaller gradient may need more than 32 vectors a thread, for which
 // there is the staged kernel alone: with 64 M = 9, d = 443 604, with 32 M = 80, d = 16 860.
 // What does not fit the chip (beyond 100 MB) and short models (d <= 2048: one block a gradient) stay with them.
-OnePassShape onepass_shape(int model, int64_t d, int32_t M, int32_t compute_units) {
+OnePassShape onepass_shape(int model, int64_t d, int32_t M, int32_t compute_units, int32_t at_once) {
     OnePassShape s;
     if ((model != ADPSGD_MODEL_LSQ && model != ADPSGD_MODEL_LOGREG) || M < (model == ADPSGD_MODEL_LSQ ? 4 : 1) || M > kOnePassMaxM) return s;
     if (d <= 2048 || static_cast<double>(M) * static_cast<double>(d) < 50000.0) return s;
@@ -48,7 +51,12 @@ OnePassShape onepass_shape(int model, int64_t d, int32_t M, int32_t compute_unit
         const int64_t plain = at_a_time();
         cut(onepass_pipeline_chunks(s.rows));
         const int64_t pipeline = at_a_time();
-        s.kernel = pipeline == 0 ? OnePassKernel::kStaged : plain <= (s.row_groups == 8 && s.rows >= 8 ? 2 : 5) * pipeline ? OnePassKernel::kPipeline : OnePassKernel::kPlain;
+        bool places = pipeline > 0 && plain <= (s.row_groups == 8 && s.rows >= 8 ? 2 : 5) * pipeline;
+        if (places && at_once > 0) {
+            const int64_t steps = (at_once + plain - 1) / plain, turns = (at_once + pipeline - 1) / pipeline;
+            places = steps > 2 || turns < (steps == 1 || s.row_groups == 8 ? 2 : 3) * steps;
+        }
+        s.kernel = pipeline == 0 ? OnePassKernel::kStaged : places ? OnePassKernel::kPipeline : OnePassKernel::kPlain;
     }
     if (s.kernel != OnePassKernel::kPipeline) {
         hold(held);

@@ -45,7 +45,8 @@ constexpr bool onepass_built(OnePassKernel kernel, int rows, int chunks) {
 // The shape for a handle, by its sizes alone (so that a gradient has the same bits in every call and however its blocks are
 // scheduled), or one that is not ok():
 // three launches per round (kernels_grad_linear.hip) are the better route, or the only one.
-OnePassShape onepass_shape(int model, int64_t d, int32_t M, int32_t compute_units);
+// at_once: gradients of every launch, where that is known (the synchronous schedule), else 0.
+OnePassShape onepass_shape(int model, int64_t d, int32_t M, int32_t compute_units, int32_t at_once = 0);
 // Whether run_events takes it too (the synchronous schedule does wherever there is a shape).
 bool onepass_for_events(const OnePassShape& s, int model, int32_t M, bool wait_free);
 size_t onepass_exchange_bytes(const OnePassShape& s, int32_t M);

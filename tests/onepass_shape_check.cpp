@@ -22,7 +22,9 @@ int main() {
             for (int i = 0; i < 500; ++i) {
                 const int model = i & 1 ? ADPSGD_MODEL_LSQ : ADPSGD_MODEL_LOGREG;
                 const auto d = static_cast<int64_t>(std::exp(std::uniform_real_distribution<double>(std::log(2000.0), std::log(4e7))(rng)));
-                const OnePassShape s = onepass_shape(model, d, M, cus);
+                const int at_once = i % 3 == 0 ? 1 + static_cast<int>(rng() % 40) : 0;
+                const OnePassShape s = onepass_shape(model, d, M, cus, at_once);
+                if (s.ok() != onepass_shape(model, d, M, cus).ok()) return fail("accepted by the number of gradients", model, d, M, cus, s);
                 if (!s.ok()) continue;
                 ++ok;
                 ++by_kernel[static_cast<int>(s.kernel)];
@@ -53,6 +55,20 @@ int main() {
                           Size{8, 524289, OnePassKernel::kPipeline}, Size{45, 98305, OnePassKernel::kPipeline}, Size{4, 688128, OnePassKernel::kPlain},
                           Size{4, 688129, OnePassKernel::kPipeline}, Size{128, 65537, OnePassKernel::kStaged}})
         if (onepass_shape(ADPSGD_MODEL_LOGREG, z.d, z.M, 256).kernel != z.kernel) return fail("another kernel", ADPSGD_MODEL_LOGREG, z.d, z.M, 256, onepass_shape(ADPSGD_MODEL_LOGREG, z.d, z.M, 256));
+    // ... and by the gradients of a launch: 4 and 8 places, 3 and 6, 1 and 3
+    struct Launch {
+        int M;
+        int64_t d;
+        int at_once;
+        OnePassKernel kernel;
+    };
+    for (const Launch& z : {Launch{64, 32768, 4, OnePassKernel::kPipeline}, Launch{64, 32768, 5, OnePassKernel::kPlain}, Launch{64, 32768, 8, OnePassKernel::kPlain},
+                            Launch{64, 32768, 9, OnePassKernel::kPipeline}, Launch{128, 21504, 3, OnePassKernel::kPipeline}, Launch{128, 21504, 6, OnePassKernel::kPlain},
+                            Launch{128, 21504, 9, OnePassKernel::kPipeline}, Launch{128, 21504, 12, OnePassKernel::kPlain}, Launch{128, 21504, 13, OnePassKernel::kPipeline},
+                            Launch{32, 131073, 3, OnePassKernel::kPlain}, Launch{32, 131073, 4, OnePassKernel::kPipeline}, Launch{32, 131073, 6, OnePassKernel::kPlain},
+                            Launch{32, 131073, 7, OnePassKernel::kPipeline}})
+        if (onepass_shape(ADPSGD_MODEL_LOGREG, z.d, z.M, 256, z.at_once).kernel != z.kernel)
+            return std::printf("%d gradients: ", z.at_once), fail("another kernel", ADPSGD_MODEL_LOGREG, z.d, z.M, 256, onepass_shape(ADPSGD_MODEL_LOGREG, z.d, z.M, 256, z.at_once));
     if (by_kernel[0] == 0 || by_kernel[1] == 0 || by_kernel[2] == 0) return std::printf("a kernel without shapes\n"), 1;
     std::printf("ok, %ld shapes, %ld + %ld + %ld\n", ok, by_kernel[0], by_kernel[1], by_kernel[2]);
     return 0;

@@ -46,11 +46,12 @@ def test_events(P, model, M, d):  # noqa: F811
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])      # the sums in the same order
 
 
-# all n gradients of an iteration in one launch: n / groups of blocks each, twice with the words of the launch before.  The last two
-# are beyond the pipeline: one gradient in registers, part of the next one's rows in LDS, six and five to the one group of blocks
+# all n gradients of an iteration in one launch: n / groups of blocks each, twice with the words of the launch before.  Those that the
+# kernel for one gradient at a time takes in one step go there (n = 5, 7; and 128 x 16 411, see above).  The last two are beyond the pipeline: one gradient in registers, part of the next one's rows in LDS, six and five to the one group of blocks
 @pytest.mark.parametrize("want_loss", [True, False])
 @pytest.mark.parametrize("model,M,d,n", [("logreg", 128, 16_411, 3), ("lsq", 128, 16_411, 4), ("logreg", 8, 262_147, 7), ("lsq", 8, 1_000_003, 9),
                                          ("lsq", 32, 65_541, 16), ("logreg", 128, 16_383, 5),
+                                         ("logreg", 128, 16_383, 9), ("logreg", 8, 262_147, 3), ("lsq", 8, 262_147, 16),
                                          ("lsq", 16, 600_001, 6), ("logreg", 64, 140_003, 5)])
 def test_synchronous_iterations(P, model, M, d, n, want_loss):  # noqa: F811
     print("pipeline, synchronous %s M=%d d=%d n=%d loss=%s" % (model, M, d, n, want_loss), flush=True)
