@@ -19,6 +19,8 @@ namespace adpsgd_impl {
 // And filling and draining counts where a launch is short: synchronous iterations of 3 to 16 workers, 49 sizes, by the turns of a place of the
 // pipeline against the steps of the other:  2 and more against 1  0.84 ... 1.01 times as fast, 1 against 1 0.98 ... 1.19;  4 against 2  M > 32
 // 0.92 ... 1.03, else 0.985 ... 1.10;  6 against 2 0.91 ... 1.0;  3 against 2 1.03 ... 1.2;  6 against 3 0.97 ... 1.10, all others 1.0 and more.
+// Staged rows against none where two gradients do not fit and one does (17 or 33 to 67 MB), 241 set-ups: M <= 32, 42, 45 and 97 ... 128 0.97 ... 1.14
+// times as fast, 1.04 in the mean; M = 49 ... 96 0.94 ... 1.07, 0.98 in the mean.
 // Strips of large gradients are of equal width, as many as the compute units of their group (with widths in whole vectors of a wavefront M = 128,
 // d = 131 073 had 171 strips on 256 compute units).  Below 20 strips the blocks hold less, so that a gradient spreads over more compute units (n = 16, M = 8, d = 131 000
 // on the 4-regular graph: 786 us for 40 events in three launches a round, 708 with 16 strips, 609 with 32).
@@ -56,7 +58,8 @@ OnePassShape onepass_shape(int model, int64_t d, int32_t M, int32_t compute_unit
             const int64_t steps = (at_once + plain - 1) / plain, turns = (at_once + pipeline - 1) / pipeline;
             places = steps > 2 || turns < (steps == 1 || s.row_groups == 8 ? 2 : 3) * steps;
         }
-        s.kernel = pipeline == 0 ? OnePassKernel::kStaged : places ? OnePassKernel::kPipeline : OnePassKernel::kPlain;
+        const bool staged = pipeline == 0 && (s.row_groups < 8 || s.rows == 6 || s.rows == 16);
+        s.kernel = staged ? OnePassKernel::kStaged : places ? OnePassKernel::kPipeline : OnePassKernel::kPlain;
     }
     if (s.kernel != OnePassKernel::kPipeline) {
         hold(held);

@@ -39,7 +39,7 @@ constexpr OnePassHeld kOnePassHeld[] = {{2, 4}, {2, 8}, {4, 2}, {4, 4}, {4, 8}, 
 constexpr int onepass_pipeline_chunks(int rows) { return rows <= 4 ? 8 / rows : rows <= 8 ? 2 : 1; }      // two gradients of them fit
 constexpr bool onepass_built(OnePassKernel kernel, int rows, int chunks) {
     return kernel == OnePassKernel::kPipeline ? chunks == onepass_pipeline_chunks(rows)
-           : kernel == OnePassKernel::kStaged ? rows * chunks > (rows == 2 ? 8 : 16)
+           : kernel == OnePassKernel::kStaged ? rows * chunks > (rows == 2 ? 8 : rows == 12 ? 32 : 16)
                                               : rows * chunks <= 32;
 }
 // The shape for a handle, by its sizes alone (so that a gradient has the same bits in every call and however its blocks are

@@ -53,7 +53,8 @@ int main() {
                           Size{128, 16385, OnePassKernel::kPlain}, Size{128, 32768, OnePassKernel::kPipeline}, Size{128, 32769, OnePassKernel::kPlain},
                           Size{128, 43521, OnePassKernel::kPipeline}, Size{64, 65537, OnePassKernel::kPlain}, Size{32, 131073, OnePassKernel::kPipeline},
                           Size{8, 524289, OnePassKernel::kPipeline}, Size{45, 98305, OnePassKernel::kPipeline}, Size{4, 688128, OnePassKernel::kPlain},
-                          Size{4, 688129, OnePassKernel::kPipeline}, Size{128, 65537, OnePassKernel::kStaged}})
+                          Size{4, 688129, OnePassKernel::kPipeline}, Size{128, 65537, OnePassKernel::kStaged}, Size{64, 131073, OnePassKernel::kPlain},
+                          Size{96, 65537, OnePassKernel::kPlain}, Size{96, 131073, OnePassKernel::kStaged}, Size{32, 262145, OnePassKernel::kStaged}})
         if (onepass_shape(ADPSGD_MODEL_LOGREG, z.d, z.M, 256).kernel != z.kernel) return fail("another kernel", ADPSGD_MODEL_LOGREG, z.d, z.M, 256, onepass_shape(ADPSGD_MODEL_LOGREG, z.d, z.M, 256));
     // ... and by the gradients of a launch: 4 and 8 places, 3 and 6, 1 and 3
     struct Launch {

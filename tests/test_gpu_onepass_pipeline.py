@@ -52,7 +52,7 @@ def test_events(P, model, M, d):  # noqa: F811
 @pytest.mark.parametrize("model,M,d,n", [("logreg", 128, 16_411, 3), ("lsq", 128, 16_411, 4), ("logreg", 8, 262_147, 7), ("lsq", 8, 1_000_003, 9),
                                          ("lsq", 32, 65_541, 16), ("logreg", 128, 16_383, 5),
                                          ("logreg", 128, 16_383, 9), ("logreg", 8, 262_147, 3), ("lsq", 8, 262_147, 16),
-                                         ("lsq", 16, 600_001, 6), ("logreg", 64, 140_003, 5)])
+                                         ("logreg", 64, 140_003, 5), ("lsq", 16, 600_001, 6), ("logreg", 128, 70_001, 5)])
 def test_synchronous_iterations(P, model, M, d, n, want_loss):  # noqa: F811
     print("pipeline, synchronous %s M=%d d=%d n=%d loss=%s" % (model, M, d, n, want_loss), flush=True)
     S, rows = 3, max(M // 4, 4)
