@@ -9,7 +9,7 @@
 // still there when the coefficients arrive.
 // Measured, a call against the same call in rounds of three launches:  n = 8, d = 1024, M = 32, 200 events 0.24 against
 // 0.78 ms;  n = 16, d = 4096, M = 8, 1280 events 0.70 against 7.2 ms;  n = 16, d = 20 001, M = 50, wait-free with momentum, 400
-// events 1.17 against 4.1 ms.  What binds is the chain of an iteration (updates and x^, dot products, exchange and coefficients,
+// events 1.14 against 4.1 ms.  What binds is the chain of an iteration (updates and x^, dot products, exchange and coefficients,
 // combination, barriers) times their number: 142, 4.6 us each with 9 gradients, for the second of these; with many rows per
 // gradient (the third, 103 of 11 us) also their address translation, about 40 cycles per row and compute unit.
 // An iteration evaluates a gradient per team.  With half of them, so that all rows are requested an iteration ahead, the three

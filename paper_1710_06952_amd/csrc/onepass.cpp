@@ -7,18 +7,19 @@ namespace adpsgd_impl {
 
 // A thread holds up to 32 vectors of four columns, 256 KB a block: with 40 and 48, which gradients beyond 67 MB need, registers
 // spill.  Two gradients fit up to 16 vectors, 33 MB on all 256 compute units, with 8 or 16 rows a wavefront;  12 and 25 MB with 6 or 12
-// rows, 8 and 17 MB with 2 or 4 (few rows, and with them many columns of x^).  The line to the pipeline, 64 and 61 set-ups below and above 4 MB a gradient, against one gradient at a time: below 1 MB 0.80
-// ... 1.25 times as fast, 3 to 8 MB 0.90 ... 1.17, from 8 MB on 0.98 ... 1.29; with 6 rows, of 16 vectors only 12 in use, 0.92 ... 1.1 at
-// 9.6 MB.  But strips are whole compute units, so a gradient a little beyond a half or a third of the device takes one place of the pipeline
-// where the kernel for one at a time has five places for two of them, or three for one, and blocks that are full.  460 set-ups of 8 to 33 MB,
-// rounds of 6 and 14 gradients and synchronous iterations of 24, by places of the one and the other:
-//   1 and 2, 2 and 4, 3 and 5, 3 and 6, 4 and 8   0.97 ... 1.32 times as fast (below 1 only rounds of 6 of 8 to 9.5 MB with M > 64);
-//   1 and 3, 2 and 5   M > 64 0.84 ... 0.99, M = 52 and 64 0.95 ... 1.05 (the least with 1 and 3), M = 26 and 32 0.97 ... 1.12, M <= 8 1.0 ... 1.11;
+// rows, 8 and 17 MB with 2 or 4 (few rows, and with them many columns of x^).  The line to the pipeline, 64 and 61 set-ups below and
+// above 4 MB a gradient, against one gradient at a time: below 1 MB 0.80 ... 1.25 times as fast, 3 to 8 MB 0.90 ... 1.17, from 8 MB on
+// 0.98 ... 1.29 (but see below); with 6 rows, of 16 vectors only 12 in use, 0.92 ... 1.1 at 9.6 MB.
+// A place is the compute units of a gradient, of two in the pipeline.  A gradient a little beyond a half or a third of the device leaves the
+// pipeline one place where the kernel for one at a time has three, or two where it has five, and most of the device idle.  460 set-ups of
+// 8 to 33 MB, rounds of 6 and 14 gradients and synchronous iterations of 24, by places of the pipeline and of the other:
+//   1 and 2, 2 and 4, 3 and 5, 3 and 6, 4 and 8   0.96 ... 1.32 times as fast (below 1 only rounds of 6 of 8 to 9.5 MB with M > 64);
+//   1 and 3, 2 and 5   M > 64 0.84 ... 1.02, M = 52 and 64 0.95 ... 1.05 (the least with 1 and 3), M = 26 and 32 0.97 ... 1.12, M <= 8 1.0 ... 1.11;
 //                      M = 45, six rows 1.02 ... 1.07;
 //   1 and 6            M = 4 0.90 ... 1.04; with 1 and 5 0.99 ... 1.03.
-// And filling and draining counts where a launch is short: synchronous iterations of 3 to 16 workers, 49 sizes, by the turns of a place of the
-// pipeline against the steps of the other:  2 and more against 1  0.84 ... 1.01 times as fast, 1 against 1 0.98 ... 1.19;  4 against 2  M > 32
-// 0.92 ... 1.03, else 0.985 ... 1.10;  6 against 2 0.91 ... 1.0;  3 against 2 1.03 ... 1.2;  6 against 3 0.97 ... 1.10, all others 1.0 and more.
+// And to fill and drain the pipeline counts where a launch is short: synchronous iterations of 3 to 16 workers, 49 sizes, by the turns of a
+// place of the pipeline against the steps of the other:  2 and more against 1  0.84 ... 1.01 times as fast, 1 against 1 0.98 ... 1.19;  4 against
+// 2  M > 32 0.92 ... 1.03, else 0.985 ... 1.10;  6 against 2 0.91 ... 1.0;  3 against 2 1.03 ... 1.2;  6 against 3 0.97 ... 1.10;  others 0.97 ... 1.25.
 // Staged rows against none where two gradients do not fit and one does (17 or 33 to 67 MB), 241 set-ups: M <= 32, 42, 45 and 97 ... 128 0.97 ... 1.14
 // times as fast, 1.04 in the mean; M = 49 ... 96 0.94 ... 1.07, 0.98 in the mean.
 // Strips of large gradients are of equal width, as many as the compute units of their group (with widths in whole vectors of a wavefront M = 128,
